@@ -90,7 +90,7 @@ int sj_model_free(sj_model* m);
 
 /* Creates the per-batch state: a KV cache with `capacity[b]` positions for sequence b (rounded
  * up to a multiple of 64 internally), lengths 0, pending tokens 0, and the step workspace for
- * batch * (max_gamma + 1) query rows.  capacity is a host array of `batch` entries (ignored
+ * batch * (max_gamma + 1) query rows (at least one prompt chunk, see sj_prefill).  capacity is a host array of `batch` entries (ignored
  * and may be NULL for a head-only model).  Synchronous.  For a model with layers the call also
  * measures, on the device's default stream and on the model's own weights, which launch shape of
  * each projection kernel is fastest for this row count (some tens of milliseconds; the workspace
@@ -124,7 +124,9 @@ int sj_kv_state(const sj_kv* kv, int32_t* len_host, int32_t* pending_host);
 
 /* Runs the target over n prompt tokens (host array) of sequence seq, appends their K/V, advances
  * the length by n and sets the pending token to the arg-max continuation of the last prompt
- * token.  Uses the same kernels as the verification forward.  Synchronises `stream`. */
+ * token.  A prompt of more than max_gamma + 1 tokens runs in chunks of up to 576 rows (the cache
+ * object keeps buffers for them; where those did not fit, in blocks of max_gamma + 1 rows).
+ * Synchronises `stream`. */
 int sj_prefill(sj_model* m, sj_kv* kv, int32_t seq, const int32_t* tokens_host, int32_t n, void* stream);
 
 /* One verification cycle for every sequence of the batch (Sec. 3.1 - 3.2).

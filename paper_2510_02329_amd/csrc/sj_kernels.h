@@ -780,13 +780,13 @@ __global__ void advance_len_kernel(const StepParams* __restrict__ sp, int32_t* _
 }
 
 // Prefill bookkeeping: advance the length by the chunk; after the last chunk the pending token is the
-// arg-max continuation of the last prompt token.
+// arg-max continuation of the last prompt token (the last of the head_rows rows that the LM head ran over).
 __global__ void prefill_commit_kernel(const StepParams* __restrict__ sp, const float4* __restrict__ rowstat,
-                                      int32_t* __restrict__ len, int32_t* __restrict__ pending, int last) {
+                                      int32_t* __restrict__ len, int32_t* __restrict__ pending, int last, int head_rows) {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
         const int b = sp->seq_base;
         len[b] += sp->rps;
-        if (last) pending[b] = __float_as_int(rowstat[sp->rps - 1].z);
+        if (last) pending[b] = __float_as_int(rowstat[head_rows - 1].z);
     }
 }
 

@@ -3,6 +3,7 @@
 #include "../../include/sj.h"
 #include "sj_kernels.h"
 #include "sj_attn.h"
+#include "sj_prefill.h"
 #include "sj_gemm_rows.h"
 #include "sj_gemm_ring.h"
 
@@ -95,6 +96,7 @@ struct TunedPlans { GemmPlan qkv, o, d, gu, lm; };
 struct sj_kv {
     const sj_model* m = nullptr;
     int batch = 0, max_rows = 0, rpad = 0, mpad = 0;
+    int pf_rows = 0;           // rows of one prompt chunk of sj_prefill (0: chunks of max_gamma + 1 rows)
     std::vector<int32_t> cap, len_upper;
     std::vector<int64_t> seq_off;
     int64_t layer_stride = 0;
@@ -369,6 +371,42 @@ static GemmPlan plan_partial(int ntiles, int ksteps, bool one_row_tile) {
     return best;
 }
 
+// K-slices of a split-K projection on the loader-wave kernel, which works in groups of `group` rows.  One group: the
+// rule's (one round of the chip).  With several, the groups fill the chip by themselves and every further slice costs a
+// write and a read of the partials: the slice count (never above the rule's) with the least estimated time, in units of
+// one k-step of a workgroup (0.58 us on two-plane operands) - rounds of 256 workgroups x (k-steps of a slice + 5 for ramp
+// and epilogue) + the partials' bytes at 4 TB/s.
+static int rows_split(int rule, int ntiles, int ksteps, int rows, int group) {
+    if (rows <= group) return rule;
+    const int rgroups = (rows + group - 1) / group, wgs = (ntiles + 7) / 8 * rgroups;
+    int best = 1;
+    double best_cost = 1e30;
+    for (int s = 1; s <= rule; ++s) {
+        const double rounds = (wgs * s + 255) / 256;
+        const double cost = rounds * ((double)ksteps / s + 5.0) + (double)s * rgroups * group * ntiles * 16 * 8 / 4e12 / 0.58e-6;
+        if (cost < best_cost - 1e-9) { best = s; best_cost = cost; }
+    }
+    return best;
+}
+constexpr int row_group(int planes) { return planes == 1 ? 2 * ROWS_MT * 16 : ROWS_MT * 16; }
+
+// fp32 elements of the partials of a projection with up to `rows` rows on the loader-wave kernel, whatever the plane count
+// (the slice count depends on the number of row groups alone)
+static size_t rows_part_elems(int rule, int N, int ksteps, int rows) {
+    size_t most = 0;
+    for (int planes = 1; planes <= 2; ++planes)
+        for (int group = row_group(planes), r = 0; r < rows; r += group) {
+            const int upto = std::min(r + group, rows);
+            most = std::max(most, (size_t)rows_split(rule, N / 16, ksteps, upto, group) * upto * N);
+        }
+    return most;
+}
+
+// Rows of one prompt chunk.  Every chunk streams all weights once, so a chunk should be as long as the work it brings
+// outweighs that: four row groups of the loader-wave kernel (the two-plane products of 576 rows take 4 x the time of the
+// weight stream).
+constexpr int PREFILL_ROWS = 4 * ROWS_MT * 16;
+
 static int tune_plans(sj_kv* kv, int rows);
 
 // the launch shapes the rule gives (before any measurement)
@@ -445,9 +483,7 @@ extern "C" int sj_kv_create(const sj_model* m, int32_t batch, const int32_t* cap
     ALLOC(kv->len_dev, sizeof(int32_t) * 2 * batch);           // lengths, then pending tokens: one copy rewinds both
     kv->pending_dev = kv->len_dev + batch;
     ALLOC(kv->sp_dev, sizeof(StepParams));
-    ALLOC(kv->xn, (size_t)3 * kv->rpad * d * m->esz);          // up to three operand planes
     ALLOC(kv->hn32, (size_t)R * d * 4);
-    ALLOC(kv->row_tok, (size_t)R * 4);
     ALLOC(kv->logits, (size_t)R * V * 4);
     kv->lm_nt = 2;
     ALLOC(kv->stats, (size_t)R * (V / 16) * sizeof(float4));
@@ -466,16 +502,11 @@ extern "C" int sj_kv_create(const sj_model* m, int32_t batch, const int32_t* cap
     }
     ALLOC(kv->epart, (size_t)batch * kv->nslab * 8);
     ALLOC(kv->wpart, (size_t)batch * kv->nslab * 8);
+    if (c.n_layers == 0) ALLOC(kv->xn, (size_t)3 * kv->rpad * d * m->esz);          // up to three operand planes
     if (c.n_layers > 0) {
         const int hd = c.head_dim, Nq = c.n_q_heads * hd, Nk = c.n_kv_heads * hd, F = c.d_ffn;
         const int G = c.n_q_heads / c.n_kv_heads;
-        size_t part_elems = 0;
         rule_plans(kv);
-        for (int i = 0; i < 2; ++i)
-            part_elems = std::max({part_elems, (size_t)kv->plan_qkv[i].split * R * (Nq + 2 * Nk),
-                                   (size_t)kv->plan_o[i].split * R * d, (size_t)kv->plan_d[i].split * R * d});
-        // room for any few-row plan the start-up measurement may pick (at most 8 K-slices of at most 32 rows)
-        part_elems = std::max(part_elems, (size_t)8 * std::min(R, FEW_ROWS) * std::max(Nq + 2 * Nk, d));
         kv->mpad = (G * (c.max_gamma + 1) + 63) / 64 * 64;   // whole groups of 4 MFMA tiles
         // key ranges of attention: one wave takes chunk_keys keys (at least one 32-key step, more when the
         // total context would otherwise need more than 1024 waves: every range costs a partial
@@ -490,16 +521,45 @@ extern "C" int sj_kv_create(const sj_model* m, int32_t batch, const int32_t* cap
         }
         ALLOC(kv->K, (size_t)kv->layer_stride * c.n_layers * m->esz);
         ALLOC(kv->V, (size_t)kv->layer_stride * c.n_layers * m->esz);
-        ALLOC(kv->x, (size_t)R * d * 4);
-        if (part_elems >= ((size_t)1 << 31)) return bail(fail(SJ_EINVAL, "batch * (max_gamma + 1) rows need a projection workspace beyond 2^31 elements"));
-        ALLOC(kv->part, part_elems * 4);
         // per (sequence, kv head, key range): mpad rows of hd accumulators + (max, sum) in lane order
         ALLOC(kv->opart, (size_t)batch * c.n_kv_heads * kv->nchunk_max * kv->mpad * (hd + 8) * 4);
         ALLOC(kv->tickets, (size_t)batch * c.n_kv_heads * (kv->mpad / 16) * 4);
-        ALLOC(kv->attn_out, (size_t)3 * kv->rpad * Nq * m->esz);
-        ALLOC(kv->act, (size_t)3 * kv->rpad * F * m->esz);
-        ALLOC(kv->cs, (size_t)R * hd * 4);
-        ALLOC(kv->prefill_tok, (size_t)R * 4);
+        // the buffers of the forward, for `rows` rows
+        const int kstep = (c.dtype == SJ_DTYPE_FP32) ? 16 : 32;
+        auto forward_elems = [&](int rows) {
+            size_t e = std::max({rows_part_elems(kv->plan_qkv[1].split, Nq + 2 * Nk, d / kstep, rows),
+                                 rows_part_elems(kv->plan_o[1].split, d, Nq / kstep, rows), rows_part_elems(kv->plan_d[1].split, d, F / kstep, rows)});
+            // room for any few-row plan the start-up measurement may pick (at most 8 K-slices of at most 32 rows)
+            return std::max(e, (size_t)8 * std::min(rows, FEW_ROWS) * std::max(Nq + 2 * Nk, d));
+        };
+        auto forward_buffers = [&](int rows, size_t part_elems) -> int {
+            kv->rpad = (rows + 15) / 16 * 16;
+            int rc2;
+            if ((rc2 = dev_alloc(A, &kv->xn, (size_t)3 * kv->rpad * d * m->esz)) ||                    // up to three operand planes
+                (rc2 = dev_alloc(A, &kv->row_tok, (size_t)rows * 4)) || (rc2 = dev_alloc(A, &kv->x, (size_t)rows * d * 4)) ||
+                (rc2 = dev_alloc(A, &kv->part, part_elems * 4)) || (rc2 = dev_alloc(A, &kv->attn_out, (size_t)3 * kv->rpad * Nq * m->esz)) ||
+                // also holds the rotated query fragments of a prompt chunk (rpad x Nq elements per plane) until the gate / up projection
+                (rc2 = dev_alloc(A, &kv->act, (size_t)3 * kv->rpad * std::max(F, Nq) * m->esz)) ||
+                (rc2 = dev_alloc(A, &kv->cs, (size_t)rows * hd * 4)) || (rc2 = dev_alloc(A, &kv->prefill_tok, (size_t)rows * 4)))
+                return rc2;
+            return SJ_OK;
+        };
+        const size_t limit = (size_t)1 << 31;              // element offsets into the partials are 32-bit
+        if (forward_elems(R) >= limit) return bail(fail(SJ_EINVAL, "batch * (max_gamma + 1) rows need a projection workspace beyond 2^31 elements"));
+        // A prompt chunk of sj_prefill is as long as the longest sequence allows, up to PREFILL_ROWS.  Its buffers are a
+        // convenience: where they do not fit, prompts go through in chunks of max_gamma + 1 rows.
+        const int pf = std::min(PREFILL_ROWS, cap_max);
+        bool placed = false;
+        if (pf > c.max_gamma + 1 && forward_elems(std::max(R, pf)) < limit) {
+            const size_t mark = A.size();
+            if (forward_buffers(std::max(R, pf), forward_elems(std::max(R, pf))) == SJ_OK) { placed = true; kv->pf_rows = pf; }
+            else {
+                (void)hipGetLastError();
+                for (size_t i = mark; i < A.size(); ++i) (void)hipFree(A[i]);
+                A.resize(mark);
+            }
+        }
+        if (!placed && (rc = forward_buffers(R, forward_elems(R)))) return bail(rc);
     }
 #undef ALLOC
     if (hipMemcpy(kv->seq_off_dev, kv->seq_off.data(), sizeof(int64_t) * batch, hipMemcpyHostToDevice) != hipSuccess ||
@@ -574,9 +634,14 @@ extern "C" int sj_kernel_class_shape(const sj_kv* kv, int32_t kernel_class, int3
     if (kernel_class < 1 || kernel_class > 5) return fail(SJ_EINVAL, "kernel_class must be in 1..5");
     if (rows < 1) return fail(SJ_EINVAL, "rows must be positive");
     if (rows > FEW_ROWS) {
+        const sj_config& c = kv->m->cfg;
+        const int Nq = c.n_q_heads * c.head_dim, kstep = c.dtype == SJ_DTYPE_FP32 ? 16 : 32;
+        const int group = row_group(c.dtype == SJ_DTYPE_FP32 ? 1 : kv->planes);
         const GemmPlan* p = kernel_class == 1 ? &kv->plan_qkv[1] : kernel_class == 2 ? &kv->plan_o[1] : kernel_class == 4 ? &kv->plan_d[1] : nullptr;
-        snprintf(buf, (size_t)buf_len, "gemm_rows%s: row groups of 144 in one launch, 8 or 7 n-tiles per workgroup, %d K-slice(s)",
-                 kv->planes == 3 ? "2" : "8", p ? p->split : 1);
+        const int N = kernel_class == 1 ? Nq + 2 * c.n_kv_heads * c.head_dim : c.d_model;
+        const int K = kernel_class == 1 ? c.d_model : kernel_class == 2 ? Nq : c.d_ffn;
+        snprintf(buf, (size_t)buf_len, "gemm_rows%s: row groups of %d in one launch, 8 or 7 n-tiles per workgroup, %d K-slice(s)",
+                 kv->planes == 3 ? "2" : "8", group, p ? rows_split(p->split, N / 16, K / kstep, rows, group) : 1);
         return SJ_OK;
     }
     const GemmPlan& p = kernel_class == 1 ? kv->plan_qkv[0] : kernel_class == 2 ? kv->plan_o[0] : kernel_class == 3 ? kv->plan_gu
@@ -1178,11 +1243,25 @@ struct Runner {
     int tks(int K) const { return tiled() ? K / Traits<T>::KSTEP : 0; }
     // the same for a single exact plane (hidden states handed in by the caller), whatever SPL is
     int tks1(int K) const { return R > FEW_ROWS ? K / Traits<T>::KSTEP : 0; }
-    int partial_gemm(const void* W, const void* X, int ldx, int K, int N, const GemmPlan (&pl)[2]) {
-        if (R > FEW_ROWS) return gemm_rows<T, EPI_PARTIAL, SPL>(st, W, X, plane(ldx), ldx, K, N, R, pl[1].split, kv->part, nullptr, 0, nullptr, 0.f, tiled());
-        return few_partial<T, SPL>(pl[0], st, W, X, plane(ldx), ldx, K, N, R, kv->part);
+    // Launch shape of a split-K projection for this row count.  A prompt chunk of at most 32 rows can have more rows than
+    // the plan was made for: the LDS-ring shape then gives way to the register-ring kernel's rule shape.
+    GemmPlan plan_of(const GemmPlan (&pl)[2], int K, int N) const {
+        const int ksteps = K / Traits<T>::KSTEP;
+        if (R > FEW_ROWS) {
+            GemmPlan p = pl[1];
+            p.split = rows_split(p.split, N / 16, ksteps, R, row_group(SPL));
+            return p;
+        }
+        if (pl[0].waves == RING_WAVES && !ring_fits(pl[0], N / 16, ksteps, R, SPL, std::is_same<T, bf16_t>::value)) return plan_partial(N / 16, ksteps, true);
+        return pl[0];
     }
-    int nparts(const GemmPlan (&pl)[2]) const { return pl[R <= FEW_ROWS ? 0 : 1].split; }
+    // `parts`: the K-slices it leaves in kv->part
+    int partial_gemm(const void* W, const void* X, int ldx, int K, int N, const GemmPlan (&pl)[2], int* parts = nullptr) {
+        const GemmPlan p = plan_of(pl, K, N);
+        if (parts) *parts = p.split;
+        if (R > FEW_ROWS) return gemm_rows<T, EPI_PARTIAL, SPL>(st, W, X, plane(ldx), ldx, K, N, R, p.split, kv->part, nullptr, 0, nullptr, 0.f, tiled());
+        return few_partial<T, SPL>(p, st, W, X, plane(ldx), ldx, K, N, R, kv->part);
+    }
     // gate / up projection with the SwiGLU epilogue: 7 n-tiles per workgroup when that gives a whole
     // number of workgroups per CU (2F/16 = 1792 tiles -> 256 workgroups), else 8
     int gate_up(const void* W) {
@@ -1192,8 +1271,9 @@ struct Runner {
     }
 
     // rotary + cache append + attention of one layer from the QKV partials in kv->part
-    int attention(int layer) {
+    int attention(int layer, int parts) {
         const ModelDims& md = m->md;
+        if (rps > m->cfg.max_gamma + 1) return prefill_attention(layer, parts);
         const int M = md.G * rps;
         const int mtiles = (M + 15) / 16;
         // one query tile per workgroup while the launch stays small (shortest dependent chain per wave;
@@ -1202,9 +1282,9 @@ struct Runner {
         const int mq = small ? 1 : std::min(mtiles, 4);
         const int qgroups = (mtiles + mq - 1) / mq;
         dim3 grid(kv->nchunk_max, md.Hkv * qgroups, nseq);
-        const bool pb2 = nparts(kv->plan_qkv) <= 2;        // at most two QKV partials: fetch them two at a time
+        const bool pb2 = parts <= 2;        // at most two QKV partials: fetch them two at a time
 #define ATTN_PB(HD, MQ, PB)                                                                                            \
-    attn_fused_kernel<T, HD, MQ, SPL, PB><<<grid, 256, 0, st>>>(kv->sp_dev, md, kv->part, nparts(kv->plan_qkv), R, kv->cs, view(), \
+    attn_fused_kernel<T, HD, MQ, SPL, PB><<<grid, 256, 0, st>>>(kv->sp_dev, md, kv->part, parts, R, kv->cs, view(), \
                                                                 layer, kv->chunk_keys, kv->nchunk_max, kv->opart, kv->tickets,  \
                                                                 (T*)kv->attn_out, plane(md.Hq * md.hd), tks(md.Hq * md.hd))
 #define ATTN(HD, MQ)                                                                                                   \
@@ -1220,50 +1300,77 @@ struct Runner {
         return SJ_OK;
     }
 
-    // residual add of `parts` pending split-K partials + RMSNorm into the operand planes (batches of loads as wide as
-    // the partials there are: an eight-wide clamped batch for two partials repeats six loads)
-    void norm(int parts, const void* gain, float* xn32) {
-        const int d = m->md.d;
-        if (parts <= 2)
-            add_rmsnorm_kernel<T, 2><<<R, 1024, 0, st>>>(R, d, m->md.eps, kv->x, kv->part, parts, (const T*)gain, (T*)kv->xn, plane(d), xn32, tks(d));
-        else if (parts <= 4)
-            add_rmsnorm_kernel<T, 4><<<R, 1024, 0, st>>>(R, d, m->md.eps, kv->x, kv->part, parts, (const T*)gain, (T*)kv->xn, plane(d), xn32, tks(d));
-        else
-            add_rmsnorm_kernel<T, 8><<<R, 1024, 0, st>>>(R, d, m->md.eps, kv->x, kv->part, parts, (const T*)gain, (T*)kv->xn, plane(d), xn32, tks(d));
+    // the same for a prompt chunk (one sequence, more rows than the decode kernel's workspace has room for)
+    int prefill_attention(int layer, int parts) {
+        const ModelDims& md = m->md;
+        const int blocks = (rps + PF_POS - 1) / PF_POS, ntiles = md.G * blocks;
+        u32x4* qbuf = (u32x4*)kv->act;
+        // two query tiles a wave halve the K / V reads where that still leaves a workgroup for every CU
+        const bool two = (long long)((ntiles + 7) / 8) * md.Hkv >= 256;
+        const dim3 grid(two ? (ntiles + 7) / 8 : (ntiles + 3) / 4, md.Hkv);
+#define PF_ATTN(HD)                                                                                                    \
+    do {                                                                                                               \
+        prefill_rotary_kernel<T, HD, SPL><<<dim3(blocks, md.Hkv), 256, 0, st>>>(kv->sp_dev, md, kv->part, parts, R, kv->cs, view(), layer, qbuf); \
+        LAUNCHCHK("prefill_rotary");                                                                                   \
+        if (two) prefill_attn_kernel<T, HD, 2, SPL><<<grid, 256, 0, st>>>(kv->sp_dev, md, view(), layer, qbuf, ntiles, (T*)kv->attn_out, plane(md.Hq * md.hd), tks(md.Hq * md.hd)); \
+        else prefill_attn_kernel<T, HD, 1, SPL><<<grid, 256, 0, st>>>(kv->sp_dev, md, view(), layer, qbuf, ntiles, (T*)kv->attn_out, plane(md.Hq * md.hd), tks(md.Hq * md.hd)); \
+        LAUNCHCHK("prefill_attn");                                                                                     \
+    } while (0)
+        if (md.hd == 128) PF_ATTN(128); else PF_ATTN(64);
+#undef PF_ATTN
+        return SJ_OK;
     }
 
-    // decoder layers (Eq. 2 / Eq. 4): leaves the last down-projection partials pending in kv->part
-    int layers() {
+    // residual add of `parts` pending split-K partials + RMSNorm into the operand planes (batches of loads as wide as
+    // the partials there are: an eight-wide clamped batch for two partials repeats six loads)
+    void norm(int parts, const void* gain, float* xn32) { norm_rows(parts, gain, xn32, 0, R, 0, tks(m->md.d)); }
+    // rows r0 .. r0 + n - 1 of the block into rows o0 .. of the operand planes (o0 a multiple of 16 in tiled planes) and of xn32
+    void norm_rows(int parts, const void* gain, float* xn32, int r0, int n, int o0, int otks) {
+        const int d = m->md.d;
+        float *x = kv->x + (size_t)r0 * d, *part = kv->part + (size_t)r0 * d, *h = xn32 ? xn32 + (size_t)o0 * d : nullptr;
+        T* xn = (T*)kv->xn + (size_t)o0 * d;
+        if (parts <= 2) add_rmsnorm_kernel<T, 2><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, plane(d), h, otks);
+        else if (parts <= 4) add_rmsnorm_kernel<T, 4><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, plane(d), h, otks);
+        else add_rmsnorm_kernel<T, 8><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, plane(d), h, otks);
+    }
+
+    // decoder layers (Eq. 2 / Eq. 4): leaves the last down-projection's K-slices pending in kv->part (their number in `parts`)
+    int decoder(int& parts) {
         const ModelDims& md = m->md;
         const sj_config& c = m->cfg;
         const int d = md.d, Nq = md.Hq * md.hd, Nk = md.Hkv * md.hd, Nqkv = Nq + 2 * Nk;
         step_begin_kernel<T><<<R, 256, 0, st>>>(kv->sp_dev, md, (const T*)m->embed, kv->len_dev, kv->pending_dev, kv->x,
                                                  kv->cs, kv->row_tok, std::log((double)c.rope_base));
         LAUNCHCHK("step_begin");
-        int pending_parts = 0;
+        parts = 0;
         int rc;
         for (int l = 0; l < c.n_layers; ++l) {
             const LayerW& L = m->layers[l];
-            norm(pending_parts, L.attn_norm, nullptr);
+            norm(parts, L.attn_norm, nullptr);
             LAUNCHCHK("add_rmsnorm");
             if ((rc = time_mark(kv, 1, st))) return rc;
-            if ((rc = partial_gemm(L.wqkv, kv->xn, d, d, Nqkv, kv->plan_qkv))) return rc;
+            if ((rc = partial_gemm(L.wqkv, kv->xn, d, d, Nqkv, kv->plan_qkv, &parts))) return rc;
             if ((rc = time_mark(kv, 1, st))) return rc;
-            if ((rc = attention(l))) return rc;
+            if ((rc = attention(l, parts))) return rc;
             if ((rc = time_mark(kv, 2, st))) return rc;
-            if ((rc = partial_gemm(L.wo, kv->attn_out, Nq, Nq, d, kv->plan_o))) return rc;
+            if ((rc = partial_gemm(L.wo, kv->attn_out, Nq, Nq, d, kv->plan_o, &parts))) return rc;
             if ((rc = time_mark(kv, 2, st))) return rc;
-            norm(nparts(kv->plan_o), L.ffn_norm, nullptr);
+            norm(parts, L.ffn_norm, nullptr);
             LAUNCHCHK("add_rmsnorm");
             if ((rc = time_mark(kv, 3, st))) return rc;
             if ((rc = gate_up(L.wgu))) return rc;
             if ((rc = time_mark(kv, 3, st))) return rc;
             if ((rc = time_mark(kv, 4, st))) return rc;
-            if ((rc = partial_gemm(L.wd, kv->act, md.F, md.F, d, kv->plan_d))) return rc;
+            if ((rc = partial_gemm(L.wd, kv->act, md.F, md.F, d, kv->plan_d, &parts))) return rc;
             if ((rc = time_mark(kv, 4, st))) return rc;
-            pending_parts = nparts(kv->plan_d);
         }
-        norm(pending_parts, m->final_norm, kv->hn32);
+        return SJ_OK;
+    }
+    int layers() {
+        int parts = 0;
+        const int rc = decoder(parts);
+        if (rc) return rc;
+        norm(parts, m->final_norm, kv->hn32);
         LAUNCHCHK("add_rmsnorm");
         return SJ_OK;
     }
@@ -1700,21 +1807,48 @@ extern "C" int sj_verify_head_static(sj_model* m, int32_t batch, int32_t gamma, 
     return dispatch_step(m, &kv, gamma, p, st, true, hidden);
 }
 
+// A prompt of at most max_gamma + 1 tokens is one block of the decode kernels.  A longer one goes through in chunks of up to
+// pf_rows rows of nearly equal length: every chunk streams all weights, so their number is what a prompt costs (509 tokens of a
+// 4-layer 8B shape: 85 chunks of 6 rows took 36.9 ms).  The LM head, and the final norm, run over the
+// rows that a chain of max_gamma + 1 - row blocks would have in its last block; sj_debug_fetch finds them where that chain leaves
+// them (rows after those of the last block: the ones just before it).
 template <typename T, int SPL>
 static int prefill_impl(sj_model* m, sj_kv* kv, int seq, const int32_t* tokens, int n, hipStream_t st) {
-    const int chunk_max = std::min(kv->max_rows, m->cfg.max_gamma + 1);
-    for (int t0 = 0; t0 < n; t0 += chunk_max) {
-        const int cn = std::min(chunk_max, n - t0);
-        const bool last = (t0 + cn == n);
+    const int block = std::min(kv->max_rows, m->cfg.max_gamma + 1);
+    const int rows_max = n > block && kv->pf_rows > block ? kv->pf_rows : block;
+    const bool long_chunks = rows_max > block;
+    const int nchunks = (n + rows_max - 1) / rows_max;
+    for (int i = 0; i < nchunks; ++i) {
+        const int t0 = long_chunks ? (int)((long long)n * i / nchunks) : i * rows_max;
+        const int t1 = long_chunks ? (int)((long long)n * (i + 1) / nchunks) : std::min(n, t0 + rows_max);
+        const int cn = t1 - t0;
+        const bool last = (t1 == n);
         HIPCHK(hipMemcpyAsync(kv->prefill_tok, tokens + t0, sizeof(int32_t) * cn, hipMemcpyHostToDevice, st));
         StepParams p{};
         p.nseq = 1; p.seq_base = seq; p.rps = cn; p.gamma = cn - 1; p.tok_mode = 1; p.prefill_tokens = kv->prefill_tok;
         int rc = set_params(kv, st, p);
         if (rc) return rc;
         Runner<T, SPL> run{m, kv, st, 1, cn, cn};
-        if ((rc = run.layers())) return rc;
-        if (last && (rc = run.lm_head(false))) return rc;
-        prefill_commit_kernel<<<1, 1, 0, st>>>(kv->sp_dev, kv->rowstat, kv->len_dev, kv->pending_dev, last ? 1 : 0);
+        int head_rows = cn;
+        if (!long_chunks) {
+            if ((rc = run.layers())) return rc;
+        } else {
+            int parts = 0;
+            if ((rc = run.decoder(parts))) return rc;
+            if (last) {
+                head_rows = n - (n - 1) / block * block;
+                const int keep = std::min(block, cn);          // chunks are longer than a block: cn > block
+                Runner<T, SPL> head{m, kv, st, 1, head_rows, head_rows};
+                if (keep > head_rows) run.norm_rows(parts, m->final_norm, kv->hn32, cn - keep, keep - head_rows, head_rows, 0);
+                run.norm_rows(parts, m->final_norm, kv->hn32, cn - head_rows, head_rows, 0, head.tks(m->md.d));
+                LAUNCHCHK("add_rmsnorm");
+            }
+        }
+        if (last) {
+            Runner<T, SPL> head{m, kv, st, 1, head_rows, head_rows};
+            if ((rc = head.lm_head(false))) return rc;
+        }
+        prefill_commit_kernel<<<1, 1, 0, st>>>(kv->sp_dev, kv->rowstat, kv->len_dev, kv->pending_dev, last ? 1 : 0, head_rows);
         LAUNCHCHK("prefill_commit");
         HIPCHK(hipStreamSynchronize(st));     // the pageable token copy of the next chunk must not race
     }
