@@ -111,3 +111,23 @@ def test_judge_training_at_paper_size_meets_optimality_conditions():
     assert abs(out["auc"][0] - jt.roc_auc(sv, yv)) <= _auc_slack(sv, yv, 1e-9) + 1e-15
     assert abs(out["theta_recall"] - jt.best_recall_threshold(sv, yv)) < 1e-9
     assert abs(out["theta_f1"] - jt.best_f1_threshold(sv, yv)["theta"]) < 1e-9
+
+
+@pytest.mark.parametrize("n,d,n_C", [(700, 512, 10), (61, 1024, 3), (5, 4, 2), (257, 2048, 5), (130, 2052, 6), (90, 6144, 3)])
+def test_grid_equals_its_values_one_at_a_time(n, d, n_C):
+    """Problems share the passes over the matrix (up to four at a time, two for wide rows) and take each other's place when one
+    is done: every model of a grid is bit for bit the one that its C gives alone, over all forms of the pass (teams of 1, 2, 4
+    and 8 waves a row, 1 - 4 column pieces a wave, rows left over, fewer rows than workgroups)."""
+    H, y = synth.make_judge_dataset(31, n, d)
+    y[:2] = [0, 1]
+    Hd, yd = _dev(H), _dev(y)
+    grid = np.logspace(-2, 0.5, n_C)
+    out = sj.sj_judge_train(Hd, yd, Hd, yd, grid, torch.cuda.current_stream())
+    for c in range(n_C):
+        one = sj.sj_judge_train(Hd, yd, Hd, yd, [grid[c]], torch.cuda.current_stream())
+        assert (out["w_all"][c] == one["w_all"][0]).all() and out["passes"][c] == one["passes"][0] and out["auc"][c] == one["auc"][0]
+    x = np.concatenate([H.astype(np.float64), np.ones((n, 1))], axis=1)
+    for c in range(n_C):
+        w = out["w_all"][c]
+        g = np.append(w[:d], 0.0) + grid[c] * (x.T @ (1.0 / (1.0 + np.exp(-(x @ w))) - y))
+        assert np.abs(g).max() <= 2e-11 * max(1.0, grid[c] * n) + 1e-12 * np.abs(x).sum(axis=0).max() * grid[c]
