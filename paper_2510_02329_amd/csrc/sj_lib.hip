@@ -93,9 +93,18 @@ constexpr int RING_ROWS = 16;                  // one MFMA row tile
 constexpr int RING_PACK_ROWS = 8;              // both operand planes in one product
 struct TunedPlans { GemmPlan qkv, o, d, gu, lm; };
 
-struct sj_kv {
+// Buffers of a forward over up to `rpad` rows: residual stream, operand planes, projection partials, rotary table.
+struct Forward {
+    int rpad = 0;
+    float *x = nullptr, *part = nullptr, *cs = nullptr;
+    void *xn = nullptr, *attn_out = nullptr, *act = nullptr;
+    int32_t *row_tok = nullptr, *prefill_tok = nullptr;
+};
+
+struct sj_kv : Forward {       // the inherited buffers serve the blocks of up to max_gamma + 1 rows per sequence
     const sj_model* m = nullptr;
-    int batch = 0, max_rows = 0, rpad = 0, mpad = 0;
+    int batch = 0, max_rows = 0, mpad = 0;
+    Forward chunk;             // those of a prompt chunk of sj_prefill
     int pf_rows = 0;           // rows of one prompt chunk of sj_prefill (0: chunks of max_gamma + 1 rows)
     std::vector<int32_t> cap, len_upper;
     std::vector<int64_t> seq_off;
@@ -105,14 +114,13 @@ struct sj_kv {
     int32_t *cap_dev = nullptr, *len_dev = nullptr, *pending_dev = nullptr;
     // workspace
     StepParams* sp_dev = nullptr;
-    float *x = nullptr, *hn32 = nullptr, *part = nullptr, *opart = nullptr, *cs = nullptr, *logits = nullptr;
+    float *hn32 = nullptr, *opart = nullptr, *logits = nullptr;
     float *scores = nullptr, *p_at_d = nullptr;
     int32_t* ranks = nullptr;        // [R] rank of every draft token in its target row (top-k mode)
     int topk = 2;
-    void *xn = nullptr, *attn_out = nullptr, *act = nullptr;
     unsigned* tickets = nullptr;
     float4 *stats = nullptr, *rowstat = nullptr;
-    int32_t *row_tok = nullptr, *bits = nullptr, *nacc = nullptr, *prefill_tok = nullptr, *draft_tok = nullptr;
+    int32_t *bits = nullptr, *nacc = nullptr, *draft_tok = nullptr;
     double *epart = nullptr, *wpart = nullptr;
     int chunk_keys = 64, nchunk_max = 1, nslab = 0, slab_len = 0;
     GemmPlan plan_qkv[2], plan_o[2], plan_d[2];   // [0]: few-row kernel (at most 32 rows), [1]: more
@@ -532,34 +540,44 @@ extern "C" int sj_kv_create(const sj_model* m, int32_t batch, const int32_t* cap
             // room for any few-row plan the start-up measurement may pick (at most 8 K-slices of at most 32 rows)
             return std::max(e, (size_t)8 * std::min(rows, FEW_ROWS) * std::max(Nq + 2 * Nk, d));
         };
-        auto forward_buffers = [&](int rows, size_t part_elems) -> int {
-            kv->rpad = (rows + 15) / 16 * 16;
-            int rc2;
-            if ((rc2 = dev_alloc(A, &kv->xn, (size_t)3 * kv->rpad * d * m->esz)) ||                    // up to three operand planes
-                (rc2 = dev_alloc(A, &kv->row_tok, (size_t)rows * 4)) || (rc2 = dev_alloc(A, &kv->x, (size_t)rows * d * 4)) ||
-                (rc2 = dev_alloc(A, &kv->part, part_elems * 4)) || (rc2 = dev_alloc(A, &kv->attn_out, (size_t)3 * kv->rpad * Nq * m->esz)) ||
-                // also holds the rotated query fragments of a prompt chunk (rpad x Nq elements per plane) until the gate / up projection
-                (rc2 = dev_alloc(A, &kv->act, (size_t)3 * kv->rpad * std::max(F, Nq) * m->esz)) ||
-                (rc2 = dev_alloc(A, &kv->cs, (size_t)rows * hd * 4)) || (rc2 = dev_alloc(A, &kv->prefill_tok, (size_t)rows * 4)))
-                return rc2;
-            return SJ_OK;
-        };
         const size_t limit = (size_t)1 << 31;              // element offsets into the partials are 32-bit
-        if (forward_elems(R) >= limit) return bail(fail(SJ_EINVAL, "batch * (max_gamma + 1) rows need a projection workspace beyond 2^31 elements"));
-        // A prompt chunk of sj_prefill is as long as the longest sequence allows, up to PREFILL_ROWS.  Its buffers are a
-        // convenience: where they do not fit, prompts go through in chunks of max_gamma + 1 rows.
-        const int pf = std::min(PREFILL_ROWS, cap_max);
-        bool placed = false;
-        if (pf > c.max_gamma + 1 && forward_elems(std::max(R, pf)) < limit) {
-            const size_t mark = A.size();
-            if (forward_buffers(std::max(R, pf), forward_elems(std::max(R, pf))) == SJ_OK) { placed = true; kv->pf_rows = pf; }
-            else {
-                (void)hipGetLastError();
-                for (size_t i = mark; i < A.size(); ++i) (void)hipFree(A[i]);
-                A.resize(mark);
+        const size_t part_elems = forward_elems(R);
+        if (part_elems >= limit) return bail(fail(SJ_EINVAL, "batch * (max_gamma + 1) rows need a projection workspace beyond 2^31 elements"));
+        ALLOC(kv->xn, (size_t)3 * kv->rpad * d * m->esz);      // up to three operand planes
+        ALLOC(kv->row_tok, (size_t)R * 4);
+        ALLOC(kv->x, (size_t)R * d * 4);
+        ALLOC(kv->part, part_elems * 4);
+        ALLOC(kv->attn_out, (size_t)3 * kv->rpad * Nq * m->esz);
+        ALLOC(kv->act, (size_t)3 * kv->rpad * F * m->esz);
+        ALLOC(kv->cs, (size_t)R * hd * 4);
+        ALLOC(kv->prefill_tok, (size_t)R * 4);
+        // A prompt chunk of sj_prefill is as long as the longest sequence allows, up to PREFILL_ROWS.  Its buffers are apart from
+        // those of the blocks (a block's planes then stay close together: with one set for both, the steps of small models took
+        // 3 % longer), in one allocation.  Where it does not fit, prompts go through in blocks of max_gamma + 1 rows.
+        const int pf = std::min(PREFILL_ROWS, cap_max), pad = (pf + 15) / 16 * 16;
+        if (pf > c.max_gamma + 1 && forward_elems(pf) < limit) {
+            Forward& w = kv->chunk;
+            char* base = nullptr;
+            size_t used = 0;
+            auto carve = [&](auto*& ptr, size_t bytes) {
+                if (base) ptr = reinterpret_cast<std::remove_reference_t<decltype(ptr)>>(base + used);
+                used = (used + bytes + 255) / 256 * 256;
+            };
+            for (int round = 0; round < 2; ++round) {          // sizes first, then the pieces
+                used = 0;
+                carve(w.xn, (size_t)3 * pad * d * m->esz);
+                carve(w.row_tok, (size_t)pf * 4);
+                carve(w.x, (size_t)pf * d * 4);
+                carve(w.part, forward_elems(pf) * 4);
+                carve(w.attn_out, (size_t)3 * pad * Nq * m->esz);
+                // also holds the chunk's rotated query fragments (pad x Nq elements per plane) until the gate / up projection
+                carve(w.act, (size_t)3 * pad * std::max(F, Nq) * m->esz);
+                carve(w.cs, (size_t)pf * hd * 4);
+                carve(w.prefill_tok, (size_t)pf * 4);
+                if (round == 0 && hipMalloc((void**)&base, used) != hipSuccess) { (void)hipGetLastError(); base = nullptr; break; }
             }
+            if (base) { A.push_back(base); w.rpad = pad; kv->pf_rows = pf; }
         }
-        if (!placed && (rc = forward_buffers(R, forward_elems(R)))) return bail(rc);
     }
 #undef ALLOC
     if (hipMemcpy(kv->seq_off_dev, kv->seq_off.data(), sizeof(int64_t) * batch, hipMemcpyHostToDevice) != hipSuccess ||
@@ -1229,6 +1247,7 @@ struct Runner {
     sj_kv* kv;
     hipStream_t st;
     int nseq, rps, R;
+    const Forward* w = kv;     // the buffers it works in
 
     KvView<T> view() const {
         KvView<T> v;
@@ -1236,7 +1255,7 @@ struct Runner {
         v.len = kv->len_dev; v.pending = kv->pending_dev; v.layer_stride = kv->layer_stride;
         return v;
     }
-    size_t plane(int ld) const { return (size_t)kv->rpad * ld; }
+    size_t plane(int ld) const { return (size_t)w->rpad * ld; }
     // Operand planes are written as MFMA fragments when the many-row kernel that reads operands through LDS
     // consumes them (more than FEW_ROWS rows, at most two planes); row-major otherwise.
     bool tiled() const { return R > FEW_ROWS && SPL <= 2; }
@@ -1255,22 +1274,22 @@ struct Runner {
         if (pl[0].waves == RING_WAVES && !ring_fits(pl[0], N / 16, ksteps, R, SPL, std::is_same<T, bf16_t>::value)) return plan_partial(N / 16, ksteps, true);
         return pl[0];
     }
-    // `parts`: the K-slices it leaves in kv->part
+    // `parts`: the K-slices it leaves in w->part
     int partial_gemm(const void* W, const void* X, int ldx, int K, int N, const GemmPlan (&pl)[2], int* parts = nullptr) {
         const GemmPlan p = plan_of(pl, K, N);
         if (parts) *parts = p.split;
-        if (R > FEW_ROWS) return gemm_rows<T, EPI_PARTIAL, SPL>(st, W, X, plane(ldx), ldx, K, N, R, p.split, kv->part, nullptr, 0, nullptr, 0.f, tiled());
-        return few_partial<T, SPL>(p, st, W, X, plane(ldx), ldx, K, N, R, kv->part);
+        if (R > FEW_ROWS) return gemm_rows<T, EPI_PARTIAL, SPL>(st, W, X, plane(ldx), ldx, K, N, R, p.split, w->part, nullptr, 0, nullptr, 0.f, tiled());
+        return few_partial<T, SPL>(p, st, W, X, plane(ldx), ldx, K, N, R, w->part);
     }
     // gate / up projection with the SwiGLU epilogue: 7 n-tiles per workgroup when that gives a whole
     // number of workgroups per CU (2F/16 = 1792 tiles -> 256 workgroups), else 8
     int gate_up(const void* W) {
         const ModelDims& md = m->md;
-        if (R > FEW_ROWS) return gemm_rows<T, EPI_SWIGLU, SPL>(st, W, kv->xn, plane(md.d), md.d, md.d, 2 * md.F, R, 1, nullptr, kv->act, plane(md.F), nullptr, 0.f, tiled());
-        return few_swiglu<T, SPL>(kv->plan_gu, st, W, kv->xn, plane(md.d), md.d, 2 * md.F, R, kv->act, plane(md.F));
+        if (R > FEW_ROWS) return gemm_rows<T, EPI_SWIGLU, SPL>(st, W, w->xn, plane(md.d), md.d, md.d, 2 * md.F, R, 1, nullptr, w->act, plane(md.F), nullptr, 0.f, tiled());
+        return few_swiglu<T, SPL>(kv->plan_gu, st, W, w->xn, plane(md.d), md.d, 2 * md.F, R, w->act, plane(md.F));
     }
 
-    // rotary + cache append + attention of one layer from the QKV partials in kv->part
+    // rotary + cache append + attention of one layer from the QKV partials in w->part
     int attention(int layer, int parts) {
         const ModelDims& md = m->md;
         if (rps > m->cfg.max_gamma + 1) return prefill_attention(layer, parts);
@@ -1284,9 +1303,9 @@ struct Runner {
         dim3 grid(kv->nchunk_max, md.Hkv * qgroups, nseq);
         const bool pb2 = parts <= 2;        // at most two QKV partials: fetch them two at a time
 #define ATTN_PB(HD, MQ, PB)                                                                                            \
-    attn_fused_kernel<T, HD, MQ, SPL, PB><<<grid, 256, 0, st>>>(kv->sp_dev, md, kv->part, parts, R, kv->cs, view(), \
+    attn_fused_kernel<T, HD, MQ, SPL, PB><<<grid, 256, 0, st>>>(kv->sp_dev, md, w->part, parts, R, w->cs, view(), \
                                                                 layer, kv->chunk_keys, kv->nchunk_max, kv->opart, kv->tickets,  \
-                                                                (T*)kv->attn_out, plane(md.Hq * md.hd), tks(md.Hq * md.hd))
+                                                                (T*)w->attn_out, plane(md.Hq * md.hd), tks(md.Hq * md.hd))
 #define ATTN(HD, MQ)                                                                                                   \
     do { if (pb2) ATTN_PB(HD, MQ, 2); else ATTN_PB(HD, MQ, 4); } while (0)
         if (md.hd == 128) {
@@ -1304,16 +1323,16 @@ struct Runner {
     int prefill_attention(int layer, int parts) {
         const ModelDims& md = m->md;
         const int blocks = (rps + PF_POS - 1) / PF_POS, ntiles = md.G * blocks;
-        u32x4* qbuf = (u32x4*)kv->act;
+        u32x4* qbuf = (u32x4*)w->act;
         // two query tiles a wave halve the K / V reads where that still leaves a workgroup for every CU
         const bool two = (long long)((ntiles + 7) / 8) * md.Hkv >= 256;
         const dim3 grid(two ? (ntiles + 7) / 8 : (ntiles + 3) / 4, md.Hkv);
 #define PF_ATTN(HD)                                                                                                    \
     do {                                                                                                               \
-        prefill_rotary_kernel<T, HD, SPL><<<dim3(blocks, md.Hkv), 256, 0, st>>>(kv->sp_dev, md, kv->part, parts, R, kv->cs, view(), layer, qbuf); \
+        prefill_rotary_kernel<T, HD, SPL><<<dim3(blocks, md.Hkv), 256, 0, st>>>(kv->sp_dev, md, w->part, parts, R, w->cs, view(), layer, qbuf); \
         LAUNCHCHK("prefill_rotary");                                                                                   \
-        if (two) prefill_attn_kernel<T, HD, 2, SPL><<<grid, 256, 0, st>>>(kv->sp_dev, md, view(), layer, qbuf, ntiles, (T*)kv->attn_out, plane(md.Hq * md.hd), tks(md.Hq * md.hd)); \
-        else prefill_attn_kernel<T, HD, 1, SPL><<<grid, 256, 0, st>>>(kv->sp_dev, md, view(), layer, qbuf, ntiles, (T*)kv->attn_out, plane(md.Hq * md.hd), tks(md.Hq * md.hd)); \
+        if (two) prefill_attn_kernel<T, HD, 2, SPL><<<grid, 256, 0, st>>>(kv->sp_dev, md, view(), layer, qbuf, ntiles, (T*)w->attn_out, plane(md.Hq * md.hd), tks(md.Hq * md.hd)); \
+        else prefill_attn_kernel<T, HD, 1, SPL><<<grid, 256, 0, st>>>(kv->sp_dev, md, view(), layer, qbuf, ntiles, (T*)w->attn_out, plane(md.Hq * md.hd), tks(md.Hq * md.hd)); \
         LAUNCHCHK("prefill_attn");                                                                                     \
     } while (0)
         if (md.hd == 128) PF_ATTN(128); else PF_ATTN(64);
@@ -1327,20 +1346,20 @@ struct Runner {
     // rows r0 .. r0 + n - 1 of the block into rows o0 .. of the operand planes (o0 a multiple of 16 in tiled planes) and of xn32
     void norm_rows(int parts, const void* gain, float* xn32, int r0, int n, int o0, int otks) {
         const int d = m->md.d;
-        float *x = kv->x + (size_t)r0 * d, *part = kv->part + (size_t)r0 * d, *h = xn32 ? xn32 + (size_t)o0 * d : nullptr;
-        T* xn = (T*)kv->xn + (size_t)o0 * d;
+        float *x = w->x + (size_t)r0 * d, *part = w->part + (size_t)r0 * d, *h = xn32 ? xn32 + (size_t)o0 * d : nullptr;
+        T* xn = (T*)w->xn + (size_t)o0 * d;
         if (parts <= 2) add_rmsnorm_kernel<T, 2><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, plane(d), h, otks);
         else if (parts <= 4) add_rmsnorm_kernel<T, 4><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, plane(d), h, otks);
         else add_rmsnorm_kernel<T, 8><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, plane(d), h, otks);
     }
 
-    // decoder layers (Eq. 2 / Eq. 4): leaves the last down-projection's K-slices pending in kv->part (their number in `parts`)
+    // decoder layers (Eq. 2 / Eq. 4): leaves the last down-projection's K-slices pending in w->part (their number in `parts`)
     int decoder(int& parts) {
         const ModelDims& md = m->md;
         const sj_config& c = m->cfg;
         const int d = md.d, Nq = md.Hq * md.hd, Nk = md.Hkv * md.hd, Nqkv = Nq + 2 * Nk;
-        step_begin_kernel<T><<<R, 256, 0, st>>>(kv->sp_dev, md, (const T*)m->embed, kv->len_dev, kv->pending_dev, kv->x,
-                                                 kv->cs, kv->row_tok, std::log((double)c.rope_base));
+        step_begin_kernel<T><<<R, 256, 0, st>>>(kv->sp_dev, md, (const T*)m->embed, kv->len_dev, kv->pending_dev, w->x,
+                                                 w->cs, w->row_tok, std::log((double)c.rope_base));
         LAUNCHCHK("step_begin");
         parts = 0;
         int rc;
@@ -1349,11 +1368,11 @@ struct Runner {
             norm(parts, L.attn_norm, nullptr);
             LAUNCHCHK("add_rmsnorm");
             if ((rc = time_mark(kv, 1, st))) return rc;
-            if ((rc = partial_gemm(L.wqkv, kv->xn, d, d, Nqkv, kv->plan_qkv, &parts))) return rc;
+            if ((rc = partial_gemm(L.wqkv, w->xn, d, d, Nqkv, kv->plan_qkv, &parts))) return rc;
             if ((rc = time_mark(kv, 1, st))) return rc;
             if ((rc = attention(l, parts))) return rc;
             if ((rc = time_mark(kv, 2, st))) return rc;
-            if ((rc = partial_gemm(L.wo, kv->attn_out, Nq, Nq, d, kv->plan_o, &parts))) return rc;
+            if ((rc = partial_gemm(L.wo, w->attn_out, Nq, Nq, d, kv->plan_o, &parts))) return rc;
             if ((rc = time_mark(kv, 2, st))) return rc;
             norm(parts, L.ffn_norm, nullptr);
             LAUNCHCHK("add_rmsnorm");
@@ -1361,7 +1380,7 @@ struct Runner {
             if ((rc = gate_up(L.wgu))) return rc;
             if ((rc = time_mark(kv, 3, st))) return rc;
             if ((rc = time_mark(kv, 4, st))) return rc;
-            if ((rc = partial_gemm(L.wd, kv->act, md.F, md.F, d, kv->plan_d, &parts))) return rc;
+            if ((rc = partial_gemm(L.wd, w->act, md.F, md.F, d, kv->plan_d, &parts))) return rc;
             if ((rc = time_mark(kv, 4, st))) return rc;
         }
         return SJ_OK;
@@ -1382,13 +1401,13 @@ struct Runner {
         int rc;
         if (R > FEW_ROWS) {
             rc = exact_operand
-                ? gemm_rows<T, EPI_LOGITS, 1>(st, m->lm_head, kv->xn, plane(md.d), md.d, md.d, md.V, R, 1, kv->logits, nullptr, 0, kv->stats, md.inv_temp, true)
-                : gemm_rows<T, EPI_LOGITS, SPL>(st, m->lm_head, kv->xn, plane(md.d), md.d, md.d, md.V, R, 1, kv->logits, nullptr, 0, kv->stats, md.inv_temp, tiled());
+                ? gemm_rows<T, EPI_LOGITS, 1>(st, m->lm_head, w->xn, plane(md.d), md.d, md.d, md.V, R, 1, kv->logits, nullptr, 0, kv->stats, md.inv_temp, true)
+                : gemm_rows<T, EPI_LOGITS, SPL>(st, m->lm_head, w->xn, plane(md.d), md.d, md.d, md.V, R, 1, kv->logits, nullptr, 0, kv->stats, md.inv_temp, tiled());
             nblk = md.V / 16;
         } else {
             rc = exact_operand
-                ? few_logits<T, 1>(kv->plan_lm, st, m->lm_head, kv->xn, plane(md.d), md.d, md.V, R, kv->logits, kv->stats, md.inv_temp)
-                : few_logits<T, SPL>(kv->plan_lm, st, m->lm_head, kv->xn, plane(md.d), md.d, md.V, R, kv->logits, kv->stats, md.inv_temp);
+                ? few_logits<T, 1>(kv->plan_lm, st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, kv->logits, kv->stats, md.inv_temp)
+                : few_logits<T, SPL>(kv->plan_lm, st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, kv->logits, kv->stats, md.inv_temp);
             nblk = md.V / 16 / kv->plan_lm.nt;
         }
         return rc;
@@ -1823,12 +1842,13 @@ static int prefill_impl(sj_model* m, sj_kv* kv, int seq, const int32_t* tokens, 
         const int t1 = long_chunks ? (int)((long long)n * (i + 1) / nchunks) : std::min(n, t0 + rows_max);
         const int cn = t1 - t0;
         const bool last = (t1 == n);
-        HIPCHK(hipMemcpyAsync(kv->prefill_tok, tokens + t0, sizeof(int32_t) * cn, hipMemcpyHostToDevice, st));
+        const Forward* fw = long_chunks ? &kv->chunk : kv;
+        HIPCHK(hipMemcpyAsync(fw->prefill_tok, tokens + t0, sizeof(int32_t) * cn, hipMemcpyHostToDevice, st));
         StepParams p{};
-        p.nseq = 1; p.seq_base = seq; p.rps = cn; p.gamma = cn - 1; p.tok_mode = 1; p.prefill_tokens = kv->prefill_tok;
+        p.nseq = 1; p.seq_base = seq; p.rps = cn; p.gamma = cn - 1; p.tok_mode = 1; p.prefill_tokens = fw->prefill_tok;
         int rc = set_params(kv, st, p);
         if (rc) return rc;
-        Runner<T, SPL> run{m, kv, st, 1, cn, cn};
+        Runner<T, SPL> run{m, kv, st, 1, cn, cn, fw};
         int head_rows = cn;
         if (!long_chunks) {
             if ((rc = run.layers())) return rc;
@@ -1838,14 +1858,14 @@ static int prefill_impl(sj_model* m, sj_kv* kv, int seq, const int32_t* tokens, 
             if (last) {
                 head_rows = n - (n - 1) / block * block;
                 const int keep = std::min(block, cn);          // chunks are longer than a block: cn > block
-                Runner<T, SPL> head{m, kv, st, 1, head_rows, head_rows};
+                Runner<T, SPL> head{m, kv, st, 1, head_rows, head_rows, fw};
                 if (keep > head_rows) run.norm_rows(parts, m->final_norm, kv->hn32, cn - keep, keep - head_rows, head_rows, 0);
                 run.norm_rows(parts, m->final_norm, kv->hn32, cn - head_rows, head_rows, 0, head.tks(m->md.d));
                 LAUNCHCHK("add_rmsnorm");
             }
         }
         if (last) {
-            Runner<T, SPL> head{m, kv, st, 1, head_rows, head_rows};
+            Runner<T, SPL> head{m, kv, st, 1, head_rows, head_rows, fw};
             if ((rc = head.lm_head(false))) return rc;
         }
         prefill_commit_kernel<<<1, 1, 0, st>>>(kv->sp_dev, kv->rowstat, kv->len_dev, kv->pending_dev, last ? 1 : 0, head_rows);
