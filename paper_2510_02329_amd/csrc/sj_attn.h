@@ -440,7 +440,7 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(const StepParams* __res
     auto write_out = [&](int mq, int ht, const float (&v)[4]) {
         if (rowvalid[mq]) {
             const int row = bi * rps + jrow[mq];
-            Traits<T>::store_split4(attn_out + opnd_off<T>(row, (kvh * md.G + girow[mq]) * HD + ht * 16 + 4 * g, md.Hq * HD, otks), aplane, v);
+            Traits<T>::template store_split4<SPL>(attn_out + opnd_off<T>(row, (kvh * md.G + girow[mq]) * HD + ht * 16 + 4 * g, md.Hq * HD, otks), aplane, v);
         }
     };
 

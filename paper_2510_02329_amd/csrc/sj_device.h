@@ -56,9 +56,9 @@ template <> struct Traits<float> {
     // packs 4*KF/4.. probabilities of one lane into a B fragment: fp32 takes 4 values
     static __device__ __forceinline__ void pack(Frag& f, int j, float v) { f.f[j] = v; }
     template <int SPL> static __device__ __forceinline__ void pack_split(Frag* f, int j, float v) { f[0].f[j] = v; }
-    static __device__ __forceinline__ void store_split(float* p, size_t, float v) { *p = v; }
+    template <int SPL = 1> static __device__ __forceinline__ void store_split(float* p, size_t, float v) { *p = v; }
     // four neighbouring values (p 16-byte aligned)
-    static __device__ __forceinline__ void store_split4(float* p, size_t, const float (&v)[4]) {
+    template <int SPL = 1> static __device__ __forceinline__ void store_split4(float* p, size_t, const float (&v)[4]) {
         *reinterpret_cast<float4*>(p) = float4{v[0], v[1], v[2], v[3]};
     }
 };
@@ -84,16 +84,19 @@ template <> struct Traits<bf16_t> {
             if constexpr (SPL >= 3) f[2].s[j] = f32_to_bf16(r1 - bf16_to_f32(m));
         }
     }
-    static __device__ __forceinline__ void store_split(bf16_t* p, size_t plane, float v) {
+    // the first SPL planes of a value
+    template <int SPL = 3> static __device__ __forceinline__ void store_split(bf16_t* p, size_t plane, float v) {
         const bf16_t h = f32_to_bf16(v);
-        const float r1 = v - bf16_to_f32(h);
-        const bf16_t m = f32_to_bf16(r1);
         p[0] = h;
-        p[plane] = m;
-        p[2 * plane] = f32_to_bf16(r1 - bf16_to_f32(m));
+        if constexpr (SPL >= 2) {
+            const float r1 = v - bf16_to_f32(h);
+            const bf16_t m = f32_to_bf16(r1);
+            p[plane] = m;
+            if constexpr (SPL >= 3) p[2 * plane] = f32_to_bf16(r1 - bf16_to_f32(m));
+        }
     }
     // four neighbouring values (p 8-byte aligned): one 8-byte store per plane
-    static __device__ __forceinline__ void store_split4(bf16_t* p, size_t plane, const float (&v)[4]) {
+    template <int SPL = 3> static __device__ __forceinline__ void store_split4(bf16_t* p, size_t plane, const float (&v)[4]) {
         bf16_t h[4], m[4], l[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -104,8 +107,8 @@ template <> struct Traits<bf16_t> {
         }
         auto pack = [](const bf16_t (&x)[4]) { return uint2{(uint32_t)x[0] | ((uint32_t)x[1] << 16), (uint32_t)x[2] | ((uint32_t)x[3] << 16)}; };
         *reinterpret_cast<uint2*>(p) = pack(h);
-        *reinterpret_cast<uint2*>(p + plane) = pack(m);
-        *reinterpret_cast<uint2*>(p + 2 * plane) = pack(l);
+        if constexpr (SPL >= 2) *reinterpret_cast<uint2*>(p + plane) = pack(m);
+        if constexpr (SPL >= 3) *reinterpret_cast<uint2*>(p + 2 * plane) = pack(l);
     }
 };
 

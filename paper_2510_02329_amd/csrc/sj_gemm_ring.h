@@ -19,6 +19,9 @@
 // PACK (two operand planes, at most 8 rows): MFMA row r < 8 of the B operand carries plane 0 of row r,
 // row r + 8 plane 1 of the same row, so ONE product per weight fragment yields both planes' contributions
 // in output columns r and r + 8, which the reduction adds (hi first).  Without PACK one product per plane.
+// The operand of such a block is stored that way, too (packed planes: [k-step][16 rows][KSTEP], plane 1 in rows 8 - 15): a fragment is
+// 1 KB of consecutive memory instead of halves of twelve cache lines, which counts where a workgroup has one n-tile and
+// reads as much operand as weights.
 #pragma once
 #include "sj_kernels.h"
 
@@ -47,6 +50,7 @@ __global__ __launch_bounds__(RING_THREADS) void gemm_ring_kernel(GemmArgs a) {
     constexpr int LDS_STAGES = NSA > NT ? NSA : NT;    // the reduction needs NT x 8 KB
     static_assert((NSA - 1) * PER < 64, "the load counter holds 63");
     __shared__ u32x4 ring[LDS_STAGES][RING_CW][64];
+    __shared__ float inv_rms[16];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int r = lane & 15, g = lane >> 4;
     const int KS = a.K / KSTEP;
@@ -94,38 +98,61 @@ __global__ __launch_bounds__(RING_THREADS) void gemm_ring_kernel(GemmArgs a) {
     if constexpr (PACK) {
         const int row = r & 7;
         Xr[0] = reinterpret_cast<const T*>(a.X) + (size_t)(r >> 3) * a.xplane + (size_t)(row < a.R ? row : 0) * a.ldx +
-                (size_t)(ks0 + w) * KSTEP + g * KF;
+                (size_t)(ks0 + w) * a.kstride + g * KF;
     } else {
 #pragma unroll
         for (int sp = 0; sp < NB; ++sp)
             Xr[sp] = reinterpret_cast<const T*>(a.X) + (size_t)sp * a.xplane + (size_t)(r < a.R ? r : 0) * a.ldx +
-                     (size_t)(ks0 + w) * KSTEP + g * KF;
+                     (size_t)(ks0 + w) * a.kstride + g * KF;
     }
     f32x4 acc[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    Frag fb[NB], fbn[NB];
+    // Operand fragments of the next DB - 1 k-blocks are requested ahead.  With several n-tiles per workgroup a k-block lasts
+    // several stages and one block ahead covers the L2; with one tile a stage is a block (0.3 us at the streaming rate).
+    constexpr int DB = NT == 1 ? 4 : 2;
+    Frag fb[DB][NB];
     auto load_b = [&](Frag (&f)[NB], int kb) {
 #pragma unroll
-        for (int sp = 0; sp < NB; ++sp) f[sp].u = *reinterpret_cast<const u32x4*>(Xr[sp] + (size_t)kb * (RING_CW * KSTEP));
+        for (int sp = 0; sp < NB; ++sp) f[sp].u = *reinterpret_cast<const u32x4*>(Xr[sp] + (size_t)kb * (RING_CW * a.kstride));
     };
-    load_b(fb, 0);
+    // what the epilogue needs from memory, requested (and the row factors finished) while the first stage is on its way
+    f32x4 res_x = f32x4{0.f, 0.f, 0.f, 0.f};
+    float res_g[4] = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (EPI == EPI_RESID) {
+        if (w < NT) {
+            const int row = lane >> 2, col = (nt0 + w) * 16 + (lane & 3) * 4;
+            if (row < a.R) res_x = *reinterpret_cast<const f32x4*>(a.x + (size_t)row * a.N + col);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) res_g[i] = Traits<T>::load(reinterpret_cast<const T*>(a.gain) + col + i);
+        }
+    }
+    if (a.ss_in) {                                     // uniform
+        for (int row = w; row < a.R; row += RING_CW) {
+            const float inv = row_inv_rms(a, row, lane);
+            if (lane == 0) inv_rms[row] = inv;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < DB - 1; ++j) load_b(fb[j], min(j, nkb - 1));
     lds_barrier();                                     // stage 0 is in LDS
     int buf = 0;
-    for (int kb = 0; kb < nkb; ++kb) {
-        load_b(fbn, min(kb + 1, nkb - 1));             // always issued: no load under a branch
+    for (int kb0 = 0; kb0 < nkb; kb0 += DB)
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            Frag fa;
-            fa.u = ring[buf][w][lane];
+        for (int j = 0; j < DB; ++j) {
+            load_b(fb[(j + DB - 1) % DB], min(kb0 + j + DB - 1, nkb - 1));   // always issued: no load under a branch
+            if (kb0 + j < nkb) {                       // uniform
 #pragma unroll
-            for (int sp = 0; sp < NB; ++sp) Traits<T>::mma(fa, fb[sp], acc[t]);
-            buf = (buf + 1) & (NSA - 1);
-            lds_barrier();                             // this buffer is free; the next stage has landed
+                for (int t = 0; t < NT; ++t) {
+                    Frag fa;
+                    fa.u = ring[buf][w][lane];
+#pragma unroll
+                    for (int sp = 0; sp < NB; ++sp) Traits<T>::mma(fa, fb[j][sp], acc[t]);
+                    buf = (buf + 1) & (NSA - 1);
+                    lds_barrier();                     // this buffer is free; the next stage has landed
+                }
+            }
         }
-#pragma unroll
-        for (int sp = 0; sp < NB; ++sp) fb[sp] = fbn[sp];
-    }
 
     // every stage has been read (last barrier above): the ring's memory now holds the 8 waves' accumulators,
     // red[w][t][row * 16 + n] with D[n = 4g + i][row = r] in lane 16g + r
@@ -149,6 +176,23 @@ __global__ __launch_bounds__(RING_THREADS) void gemm_ring_kernel(GemmArgs a) {
         };
         f32x4 v = sum_at(lane * 4);
         if constexpr (PACK) v += sum_at(((lane + 32) & 63) * 4);   // the second plane's products sit 8 rows further on
+        if (a.ss_in && row < a.R) v *= inv_rms[row];
+        if constexpr (EPI == EPI_RESID) {
+            f32x4 xv = res_x + v;
+            const int col = (nt0 + t) * 16 + n0;
+            float ss = 0.f;
+            if (row < a.R) {
+                *reinterpret_cast<f32x4*>(a.x + (size_t)row * a.N + col) = xv;
+                float y[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { y[i] = xv[i] * res_g[i]; ss += xv[i] * xv[i]; }
+                Traits<T>::template store_split4<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, col, a.N, a.act_tks), a.actplane, y);
+            }
+            ss += __shfl_xor(ss, 1, 64);
+            ss += __shfl_xor(ss, 2, 64);
+            if (row < a.R && (lane & 3) == 0) a.ss_out[(size_t)row * (a.N / 16) + nt0 + t] = ss;
+            return;
+        }
         if constexpr (EPI == EPI_PARTIAL) {
             if (row < a.R)
                 *reinterpret_cast<f32x4*>(a.out + ((size_t)blockIdx.y * a.slice_rows + row) * a.N + (size_t)(nt0 + t) * 16 + n0) = v;
@@ -161,7 +205,7 @@ __global__ __launch_bounds__(RING_THREADS) void gemm_ring_kernel(GemmArgs a) {
                 float y[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) y[i] = v[i] / (1.0f + expf(-v[i])) * up[i];
-                Traits<T>::store_split4(reinterpret_cast<T*>(a.act) + (size_t)row * (a.N / 2) + (size_t)(nt0 + t) * 8 + n0, a.actplane, y);
+                Traits<T>::template store_split4<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, (nt0 + t) * 8 + n0, a.N / 2, a.act_tks), a.actplane, y);
             }
         }
         return;
@@ -184,7 +228,7 @@ __global__ __launch_bounds__(RING_THREADS) void gemm_ring_kernel(GemmArgs a) {
         }
         v[t] = sum;
     }
-    few_epilogue<T, NT, EPI>(a, v, er, en, nt0);
+    few_epilogue<T, NT, EPI, SPL>(a, v, er, en, nt0);
 }
 
 }  // namespace sj

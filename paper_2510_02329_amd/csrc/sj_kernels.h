@@ -86,15 +86,18 @@ __global__ void set_state_kernel(int32_t* len, int32_t* pending, int seq, int l,
 }
 
 // ---------------------------------------------------------------------------------------------
-// Step start (Eq. 2 input): one workgroup per query row.  Resolves the row's token and position,
-// gathers its embedding into the fp32 residual stream and writes the row's rotary cos/sin table
+// Step start (Eq. 2 input): one workgroup of 1024 threads per query row.  Resolves the row's token and position,
+// gathers its embedding into the fp32 residual stream, writes the first layer's normed operand planes (RMSNorm as in
+// add_rmsnorm_kernel) and the row's rotary cos/sin table
 // (angle = pos * base^(-2i/hd), evaluated in double so the table is correctly rounded fp32).
-template <typename T>
-__global__ __launch_bounds__(256) void step_begin_kernel(const StepParams* __restrict__ sp, ModelDims md,
-                                                         const T* __restrict__ embed, const int32_t* __restrict__ len,
-                                                         const int32_t* __restrict__ pending, float* __restrict__ x,
-                                                         float* __restrict__ cs, int32_t* __restrict__ row_tok,
-                                                         double log_base) {
+template <typename T, int SPL>
+__global__ __launch_bounds__(1024) void step_begin_kernel(const StepParams* __restrict__ sp, ModelDims md,
+                                                          const T* __restrict__ embed, const int32_t* __restrict__ len,
+                                                          const int32_t* __restrict__ pending, float* __restrict__ x,
+                                                          float* __restrict__ cs, int32_t* __restrict__ row_tok,
+                                                          double log_base, const T* __restrict__ gain, T* __restrict__ xn,
+                                                          size_t xplane, int tks) {
+    __shared__ float red[16];
     const int r = blockIdx.x;
     const int rps = sp->rps;
     const int bi = r / rps, j = r % rps;
@@ -107,22 +110,52 @@ __global__ __launch_bounds__(256) void step_begin_kernel(const StepParams* __res
     const int pos = len[b] + j;
     if (threadIdx.x == 0) row_tok[r] = tok;
     const T* e = embed + (size_t)tok * md.d;
-    for (int c = threadIdx.x; c < md.d; c += 256) x[(size_t)r * md.d + c] = Traits<T>::load(e + c);
+    constexpr int MAXP = 4;                            // d <= 16384 (host-checked), a multiple of 64
+    float v[MAXP][4], ss = 0.f;
+#pragma unroll
+    for (int p = 0; p < MAXP; ++p) {
+        const int c = (p * 1024 + threadIdx.x) * 4;
+        if (c < md.d) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                v[p][i] = Traits<T>::load(e + c + i);
+                ss += v[p][i] * v[p][i];
+            }
+            *reinterpret_cast<f32x4*>(x + (size_t)r * md.d + c) = f32x4{v[p][0], v[p][1], v[p][2], v[p][3]};
+        }
+    }
     const int half = md.hd >> 1;
-    for (int i = threadIdx.x; i < half; i += 256) {
+    for (int i = threadIdx.x; i < half; i += 1024) {
         const double inv_freq = exp(-2.0 * (double)i / (double)md.hd * log_base);
         double s, c;
         sincos((double)pos * inv_freq, &s, &c);
         cs[((size_t)r * half + i) * 2 + 0] = (float)c;
         cs[((size_t)r * half + i) * 2 + 1] = (float)s;
     }
+    ss = wave_sum(ss);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ss;
+    __syncthreads();
+    float tot = 0.f;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) tot += red[w];
+    const float inv = 1.0f / sqrtf(tot / (float)md.d + md.eps);
+#pragma unroll
+    for (int p = 0; p < MAXP; ++p) {
+        const int c = (p * 1024 + threadIdx.x) * 4;
+        if (c < md.d) {
+            float y[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) y[i] = v[p][i] * inv * Traits<T>::load(gain + c + i);
+            Traits<T>::template store_split4<SPL>(xn + opnd_off<T>(r, c, md.d, tks), xplane, y);
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------------------------
 // Residual add + RMSNorm.  x[r] += sum_s part[s][r] (fixed order), then
-// xn[r] = x[r] * gain / sqrt(mean(x[r]^2) + eps) as the next GEMM's operand (three planes in bf16),
+// xn[r] = x[r] * gain / sqrt(mean(x[r]^2) + eps) as the next GEMM's operand (SPL planes in bf16),
 // optionally also in fp32 (final hidden state for the judge, Eq. 4).
-template <typename T, int PB = 8>
+template <typename T, int PB, int SPL>
 __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(int R, int d, float eps, float* __restrict__ x,
                                                            const float* __restrict__ part, int nparts,
                                                            const T* __restrict__ gain, T* __restrict__ xn,
@@ -169,7 +202,7 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(int R, int d, float e
             float y[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) y[i] = v[p][i] * inv * Traits<T>::load(gain + c + i);
-            Traits<T>::store_split4(xn + opnd_off<T>(r, c, d, tks), xplane, y);
+            Traits<T>::template store_split4<SPL>(xn + opnd_off<T>(r, c, d, tks), xplane, y);
             if (xn32) *reinterpret_cast<f32x4*>(xn32 + (size_t)r * d + c) = f32x4{y[0], y[1], y[2], y[3]};
         }
     }
@@ -180,7 +213,11 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(int R, int d, float e
 // Every byte of W is read exactly once; X (a few rows) is re-read from cache.
 // Workgroup (bx, by): n-tiles [bx*NT, bx*NT+NT), K-slice by of gridDim.y; its 4 waves split that
 // slice again and are summed through LDS in wave order (deterministic).
-enum { EPI_PARTIAL = 0, EPI_SWIGLU = 1, EPI_LOGITS = 2 };
+// EPI_RESID closes a sub-layer without a norm launch: the workgroup holds finished output columns (no K-slices), adds them to
+// the fp32 residual stream, writes the next product's operand planes WITHOUT the 1/rms factor - (x + y) * gain - and each
+// tile's share of every row's sum of squares.  The consumer (any epilogue, `ss_in` set) sums the shares and multiplies its finished
+// sums by 1/rms: a factor of the row commutes with the product.
+enum { EPI_PARTIAL = 0, EPI_SWIGLU = 1, EPI_LOGITS = 2, EPI_RESID = 3 };
 
 struct GemmArgs {
     const void* Wt;     // tiled weights
@@ -188,6 +225,7 @@ struct GemmArgs {
     size_t xplane;      // elements between consecutive planes of X
     size_t actplane;    // same for act
     int32_t ldx, K, N, R;
+    int32_t kstride;    // few-row kernels: elements between consecutive k-steps of an operand row (KSTEP in a row-major plane)
     int32_t slice_rows; // EPI_PARTIAL: rows between consecutive K-slices of out (>= R)
     float* out;         // EPI_PARTIAL: [gridDim.y][slice_rows][N] fp32;  EPI_LOGITS: [R][N] fp32
     void* act;          // EPI_SWIGLU: [MT*16][N/2] storage dtype = silu(gate) * up
@@ -197,14 +235,47 @@ struct GemmArgs {
     int32_t act_tks;    // same for act (its K is N/2)
     int32_t rgroups;    // many-row kernel: row groups of one launch (0 or 1: the launch is one group of R rows); with
                         // more, R is the total row count and every workgroup derives its group's rows and pointers
+    const float* ss_in; // few-row kernels: null, or [R][K / 16] shares of the rows' sums of squares: the operand lacks 1/rms
+    float eps;
+    float* x;           // EPI_RESID: [R][N] residual stream, updated in place
+    const void* gain;   // EPI_RESID: [N] norm gain of the next product, storage dtype
+    float* ss_out;      // EPI_RESID: [R][N / 16]; the operand planes go to act / actplane ([R][N])
 };
+
+// 1/rms of row r from the shares of its sum of squares, by one wave (fixed order); K = width of the row, a multiple of 64
+__device__ __forceinline__ float row_inv_rms(const GemmArgs& a, int r, int lane) {
+    const int n = a.K / 16;
+    float s = 0.f;
+    for (int i = lane * 4; i < n; i += 256) {
+        const float4 v = *reinterpret_cast<const float4*>(a.ss_in + (size_t)r * n + i);
+        s += (v.x + v.y) + (v.z + v.w);
+    }
+    s = wave_sum(s);
+    return 1.0f / sqrtf(s / (float)a.K + a.eps);
+}
 
 // Epilogue of the few-row kernels for one (row, column en of every tile) position: v[t] is the finished sum of tile
 // nt0 + t.  Every thread of the first 256 of the workgroup calls it (16 consecutive lanes share a row; rows >= R
 // take part in the shuffles and store nothing).
-template <typename T, int NT, int EPI>
+template <typename T, int NT, int EPI, int SPL>
 __device__ __forceinline__ void few_epilogue(const GemmArgs& a, const float (&v)[NT], int row, int en, int nt0) {
-    if constexpr (EPI == EPI_PARTIAL) {
+    if constexpr (EPI == EPI_RESID) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const int col = (nt0 + t) * 16 + en;
+            float xv = 0.f;
+            if (row < a.R) {
+                xv = a.x[(size_t)row * a.N + col] + v[t];
+                a.x[(size_t)row * a.N + col] = xv;
+                Traits<T>::template store_split<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, col, a.N, a.act_tks), a.actplane,
+                                                     xv * Traits<T>::load(reinterpret_cast<const T*>(a.gain) + col));
+            }
+            float ss = xv * xv;
+#pragma unroll
+            for (int o = 1; o < 16; o <<= 1) ss += __shfl_xor(ss, o, 64);
+            if (row < a.R && en == 0) a.ss_out[(size_t)row * (a.N / 16) + nt0 + t] = ss;
+        }
+    } else if constexpr (EPI == EPI_PARTIAL) {
         if (row < a.R) {
 #pragma unroll
             for (int t = 0; t < NT; ++t)
@@ -218,8 +289,8 @@ __device__ __forceinline__ void few_epilogue(const GemmArgs& a, const float (&v)
             if (row < a.R && en < 8) {
                 const float gate = v[t];
                 const float y = gate / (1.0f + expf(-gate)) * up;
-                Traits<T>::store_split(reinterpret_cast<T*>(a.act) + (size_t)row * (a.N / 2) + (size_t)(nt0 + t) * 8 + en,
-                                       a.actplane, y);
+                Traits<T>::template store_split<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, (nt0 + t) * 8 + en, a.N / 2, a.act_tks),
+                                                     a.actplane, y);
             }
         }
     } else {
@@ -261,7 +332,14 @@ template <typename T, int NT, int MT, int EPI, int SPL, int WAVES, int D = 2>
 __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(GemmArgs a) {
     constexpr int KF = Traits<T>::KF, KSTEP = Traits<T>::KSTEP;
     __shared__ float red[WAVES][NT * MT][256];
+    __shared__ float inv_rms[MT * 16];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (a.ss_in) {                                       // uniform; read after the reduction's barrier
+        for (int row = w; row < a.R; row += WAVES) {
+            const float inv = row_inv_rms(a, row, lane);
+            if (lane == 0) inv_rms[row] = inv;
+        }
+    }
     const int r = lane & 15, g = lane >> 4;
     const int KS = a.K / KSTEP;
     const int nt0 = blockIdx.x * NT;
@@ -274,7 +352,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(GemmArgs a) {
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
         const int row = m * 16 + r;
-        Xr[m] = reinterpret_cast<const T*>(a.X) + (size_t)(row < a.R ? row : 0) * a.ldx + (size_t)ks0 * KSTEP + g * KF;
+        Xr[m] = reinterpret_cast<const T*>(a.X) + (size_t)(row < a.R ? row : 0) * a.ldx + (size_t)ks0 * a.kstride + g * KF;
     }
 
     f32x4 acc[NT][MT];
@@ -295,7 +373,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(GemmArgs a) {
         for (int m = 0; m < MT; ++m)
 #pragma unroll
             for (int sp = 0; sp < SPL; ++sp)
-                fb[buf][m][sp].u = *reinterpret_cast<const u32x4*>(Xr[m] + sp * a.xplane + (size_t)ks * KSTEP);
+                fb[buf][m][sp].u = *reinterpret_cast<const u32x4*>(Xr[m] + sp * a.xplane + (size_t)ks * a.kstride);
     };
     auto compute = [&](int buf) {
 #pragma unroll
@@ -345,9 +423,9 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(GemmArgs a) {
             float sum = red[0][t * MT + m][tid];
 #pragma unroll
             for (int ww = 1; ww < WAVES; ++ww) sum += red[ww][t * MT + m][tid];
-            v[t] = sum;
+            v[t] = a.ss_in && row < a.R ? sum * inv_rms[row] : sum;
         }
-        few_epilogue<T, NT, EPI>(a, v, row, en, nt0);
+        few_epilogue<T, NT, EPI, SPL>(a, v, row, en, nt0);
     }
 }
 

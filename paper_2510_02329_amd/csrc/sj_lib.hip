@@ -96,7 +96,7 @@ struct TunedPlans { GemmPlan qkv, o, d, gu, lm; };
 // Buffers of a forward over up to `rpad` rows: residual stream, operand planes, projection partials, rotary table.
 struct Forward {
     int rpad = 0;
-    float *x = nullptr, *part = nullptr, *cs = nullptr;
+    float *x = nullptr, *part = nullptr, *cs = nullptr, *ss = nullptr;
     void *xn = nullptr, *attn_out = nullptr, *act = nullptr;
     int32_t *row_tok = nullptr, *prefill_tok = nullptr;
 };
@@ -128,6 +128,7 @@ struct sj_kv : Forward {       // the inherited buffers serve the blocks of up t
     GemmPlan plan_lm{8, 4, 1, 2};                 // LM head with few rows: nt in {4, 8}, waves in {4, 8}
     int lm_nt = 2;
     int mode = SJ_MODE_TWO_STAGE;
+    int ring_rows = RING_PACK_ROWS;       // the rules take the LDS-ring kernel up to this many rows
     int planes = 2;            // bf16 planes of the activation operand (fp32 storage: always 1)
     int32_t* pinned_state = nullptr;      // [2*batch] staging of sj_kv_rewind
     hipEvent_t rewind_done = nullptr;
@@ -435,9 +436,8 @@ static void rule_plans(sj_kv* kv) {
     // 8B-shaped projections at 6 rows; the start-up measurement may still prefer another shape)
     // (SJ_RING_ROWS = 0..16 moves the row limit of this rule; from 9 rows on, and with one plane, the kernel takes one
     // product per plane and measures equal to the register-ring kernel)
-    int ring_rows = RING_PACK_ROWS;
-    if (const char* e = std::getenv("SJ_RING_ROWS")) ring_rows = std::min(std::max(std::atoi(e), 0), RING_ROWS);
-    if (c.dtype == SJ_DTYPE_BF16 && kv->planes <= 2 && kv->max_rows <= ring_rows) {
+    if (const char* e = std::getenv("SJ_RING_ROWS")) kv->ring_rows = std::min(std::max(std::atoi(e), 0), RING_ROWS);
+    if (c.dtype == SJ_DTYPE_BF16 && kv->planes <= 2 && kv->max_rows <= kv->ring_rows) {
         const GemmPlan rq = ring_rule_partial((Nq + 2 * Nk) / 16, d / kstep), ro = ring_rule_partial(d / 16, Nq / kstep),
                        rd = ring_rule_partial(d / 16, F / kstep);
         if (rq.waves) kv->plan_qkv[0] = rq;
@@ -550,6 +550,7 @@ extern "C" int sj_kv_create(const sj_model* m, int32_t batch, const int32_t* cap
         ALLOC(kv->attn_out, (size_t)3 * kv->rpad * Nq * m->esz);
         ALLOC(kv->act, (size_t)3 * kv->rpad * F * m->esz);
         ALLOC(kv->cs, (size_t)R * hd * 4);
+        ALLOC(kv->ss, (size_t)std::min(R, FEW_ROWS) * (d / 16) * 4);
         ALLOC(kv->prefill_tok, (size_t)R * 4);
         // A prompt chunk of sj_prefill is as long as the longest sequence allows, up to PREFILL_ROWS.  Its buffers are apart from
         // those of the blocks (a block's planes then stay close together: with one set for both, the steps of small models took
@@ -573,6 +574,7 @@ extern "C" int sj_kv_create(const sj_model* m, int32_t batch, const int32_t* cap
                 // also holds the chunk's rotated query fragments (pad x Nq elements per plane) until the gate / up projection
                 carve(w.act, (size_t)3 * pad * std::max(F, Nq) * m->esz);
                 carve(w.cs, (size_t)pf * hd * 4);
+                carve(w.ss, (size_t)std::min(pf, FEW_ROWS) * (d / 16) * 4);
                 carve(w.prefill_tok, (size_t)pf * 4);
                 if (round == 0 && hipMalloc((void**)&base, used) != hipSuccess) { (void)hipGetLastError(); base = nullptr; break; }
             }
@@ -647,6 +649,8 @@ extern "C" int sj_set_kernel_timing(sj_kv* kv, int32_t kernel_class) {
     return SJ_OK;
 }
 
+static GemmPlan resid_plan(int N, int K, int kstep, int rows, int planes, bool bf16, int ring_rows);
+
 extern "C" int sj_kernel_class_shape(const sj_kv* kv, int32_t kernel_class, int32_t rows, char* buf, int32_t buf_len) {
     if (!kv || !buf || buf_len < 1) return fail(SJ_EINVAL, "kv / buf is null");
     if (kernel_class < 1 || kernel_class > 5) return fail(SJ_EINVAL, "kernel_class must be in 1..5");
@@ -662,8 +666,14 @@ extern "C" int sj_kernel_class_shape(const sj_kv* kv, int32_t kernel_class, int3
                  kv->planes == 3 ? "2" : "8", group, p ? rows_split(p->split, N / 16, K / kstep, rows, group) : 1);
         return SJ_OK;
     }
-    const GemmPlan& p = kernel_class == 1 ? kv->plan_qkv[0] : kernel_class == 2 ? kv->plan_o[0] : kernel_class == 3 ? kv->plan_gu
-                        : kernel_class == 4 ? kv->plan_d[0] : kv->plan_lm;
+    GemmPlan p = kernel_class == 1 ? kv->plan_qkv[0] : kernel_class == 2 ? kv->plan_o[0] : kernel_class == 3 ? kv->plan_gu
+                 : kernel_class == 4 ? kv->plan_d[0] : kv->plan_lm;
+    if (kernel_class == 2 || kernel_class == 4) {
+        const sj_config& c = kv->m->cfg;
+        const GemmPlan r = resid_plan(c.d_model, kernel_class == 2 ? c.n_q_heads * c.head_dim : c.d_ffn, c.dtype == SJ_DTYPE_FP32 ? 16 : 32, rows,
+                                      c.dtype == SJ_DTYPE_FP32 ? 1 : kv->planes, c.dtype == SJ_DTYPE_BF16, kv->ring_rows);
+        if (r.nt) p = r;
+    }
     const bool ring = p.waves == RING_WAVES && rows <= RING_ROWS && kv->planes <= 2 && kv->m->cfg.dtype == SJ_DTYPE_BF16;
     if (ring)
         snprintf(buf, (size_t)buf_len, "gemm_ring: %d n-tiles per workgroup, 8 compute + 2 loader waves, %d K-slice(s), LDS ring of %d stages",
@@ -837,9 +847,31 @@ extern "C" int sj_kv_state(const sj_kv* kv, int32_t* len_host, int32_t* pending_
 // Few rows (at most 32 = two MFMA row tiles): Y = X W^T with the few-row kernel.  X has SPL planes `xplane`
 // elements apart; act (EPI_SWIGLU) planes are `actplane` apart.  NT n-tiles per workgroup (N/16 must be a
 // multiple of NT), WAVES waves split the K-slice, D = depth of the register ring.
+// What a few-row product knows of its surroundings: whether its operand and result planes are packed (gemm_ring_kernel), and of
+// the norms around it `ss_in` when its operand lacks the 1/rms factor, the others for EPI_RESID (GemmArgs).
+struct FewArgs {
+    bool packed = false;
+    const float* ss_in = nullptr;
+    float eps = 0.f;
+    float* x = nullptr;
+    const void* gain = nullptr;
+    float* ss_out = nullptr;
+    template <typename T, int EPI> void put(GemmArgs& a) const {
+        constexpr int KSTEP = Traits<T>::KSTEP;
+        a.kstride = KSTEP;
+        if (packed) {
+            a.ldx = KSTEP; a.kstride = 16 * KSTEP; a.xplane = a.actplane = 8 * KSTEP;
+            a.act_tks = (EPI == EPI_SWIGLU ? a.N / 2 : a.N) / KSTEP;
+        }
+        a.ss_in = ss_in; a.eps = eps; a.x = x; a.gain = gain; a.ss_out = ss_out;
+    }
+};
+// blocks whose operand planes are packed: both planes of at most 8 rows in one fragment
+template <typename T, int SPL> constexpr bool packed_rows(int rows) { return std::is_same<T, bf16_t>::value && SPL == 2 && rows <= RING_PACK_ROWS; }
+
 template <typename T, int NT, int EPI, int SPL, int WAVES, int D = 2>
 static int gemm(hipStream_t st, const void* Wt, const void* X, size_t xplane, int ldx, int K, int N, int rows, int split,
-                float* out, void* act, size_t actplane, float4* stats, float inv_temp) {
+                float* out, void* act, size_t actplane, float4* stats, float inv_temp, const FewArgs& fa = FewArgs{}) {
     if (rows > FEW_ROWS) return fail(SJ_EINVAL, "internal: few-row kernel called with %d rows", rows);
     const int ngroups = N / 16 / NT;
     GemmArgs a{};
@@ -847,6 +879,7 @@ static int gemm(hipStream_t st, const void* Wt, const void* X, size_t xplane, in
     a.ldx = ldx; a.K = K; a.N = N; a.R = rows; a.slice_rows = rows;
     a.inv_temp = inv_temp;
     a.out = out; a.stats = stats; a.act = act;
+    fa.put<T, EPI>(a);
     if (rows <= 16) gemm_skinny_kernel<T, NT, 1, EPI, SPL, WAVES, D><<<dim3(ngroups, split), WAVES * 64, 0, st>>>(a);
     else gemm_skinny_kernel<T, NT, 2, EPI, SPL, WAVES, D><<<dim3(ngroups, split), WAVES * 64, 0, st>>>(a);
     LAUNCHCHK("gemm_skinny");
@@ -856,12 +889,13 @@ static int gemm(hipStream_t st, const void* Wt, const void* X, size_t xplane, in
 // The same product on the LDS-ring kernel (bf16, at most two planes, at most 16 rows; ring_fits has been checked).
 template <typename T, int NT, int EPI, int SPL, int NSA>
 static int gemm_ring(hipStream_t st, const void* Wt, const void* X, size_t xplane, int ldx, int K, int N, int rows, int split,
-                     float* out, void* act, size_t actplane, float4* stats, float inv_temp) {
+                     float* out, void* act, size_t actplane, float4* stats, float inv_temp, const FewArgs& fa = FewArgs{}) {
     GemmArgs a{};
     a.Wt = Wt; a.X = X; a.xplane = xplane; a.actplane = actplane;
     a.ldx = ldx; a.K = K; a.N = N; a.R = rows; a.slice_rows = rows;
     a.inv_temp = inv_temp;
     a.out = out; a.stats = stats; a.act = act;
+    fa.put<T, EPI>(a);
     const dim3 grid(N / 16 / NT, split);
     if (SPL == 2 && rows <= RING_PACK_ROWS) gemm_ring_kernel<T, NT, EPI, 2, true, NSA><<<grid, RING_THREADS, 0, st>>>(a);
     else gemm_ring_kernel<T, NT, EPI, SPL, false, NSA><<<grid, RING_THREADS, 0, st>>>(a);
@@ -873,24 +907,24 @@ static int gemm_ring(hipStream_t st, const void* Wt, const void* X, size_t xplan
 // default two-plane / one-plane operands only (they are what the start-up measurement may pick).
 template <typename T, int SPL>
 static int few_partial(const GemmPlan& p, hipStream_t st, const void* W, const void* X, size_t xplane, int ldx, int K, int N,
-                       int rows, float* out) {
+                       int rows, float* out, const FewArgs& fa = FewArgs{}) {
     if (p.waves == RING_WAVES) {
         if constexpr (std::is_same<T, bf16_t>::value && SPL <= 2) {
             if (ring_fits(p, N / 16, K / Traits<T>::KSTEP, rows, SPL, true)) {
 #define SJ_RING(NT, NSA)                                                                                            \
     if (p.nt == NT && p.depth == NSA)                                                                               \
-        return gemm_ring<T, NT, EPI_PARTIAL, SPL, NSA>(st, W, X, xplane, ldx, K, N, rows, p.split, out, nullptr, 0, nullptr, 0.f);
+        return gemm_ring<T, NT, EPI_PARTIAL, SPL, NSA>(st, W, X, xplane, ldx, K, N, rows, p.split, out, nullptr, 0, nullptr, 0.f, fa);
                 SJ_RING(1, 8) SJ_RING(2, 8) SJ_RING(3, 8) SJ_RING(4, 8) SJ_RING(8, 8)
                 SJ_RING(1, 4) SJ_RING(2, 4) SJ_RING(3, 4) SJ_RING(4, 4)
 #undef SJ_RING
             }
         }
         // more rows than the kernel takes, or a shape that is not instantiated: the register-ring kernel's rule shape
-        return few_partial<T, SPL>(plan_partial(N / 16, K / Traits<T>::KSTEP, true), st, W, X, xplane, ldx, K, N, rows, out);
+        return few_partial<T, SPL>(plan_partial(N / 16, K / Traits<T>::KSTEP, true), st, W, X, xplane, ldx, K, N, rows, out, fa);
     }
 #define SJ_SHAPE(NT, WV, D)                                                                                         \
     if (p.nt == NT && p.waves == WV && p.depth == D)                                                                \
-        return gemm<T, NT, EPI_PARTIAL, SPL, WV, D>(st, W, X, xplane, ldx, K, N, rows, p.split, out, nullptr, 0, nullptr, 0.f);
+        return gemm<T, NT, EPI_PARTIAL, SPL, WV, D>(st, W, X, xplane, ldx, K, N, rows, p.split, out, nullptr, 0, nullptr, 0.f, fa);
     SJ_SHAPE(4, 4, 2) SJ_SHAPE(4, 4, 4) SJ_SHAPE(3, 8, 2) SJ_SHAPE(6, 4, 2)
     if constexpr (SPL <= 2) {
         SJ_SHAPE(5, 4, 2) SJ_SHAPE(8, 8, 2) SJ_SHAPE(4, 8, 2) SJ_SHAPE(8, 4, 2) SJ_SHAPE(3, 4, 4)
@@ -899,31 +933,31 @@ static int few_partial(const GemmPlan& p, hipStream_t st, const void* W, const v
 #undef SJ_SHAPE
     // a shape that is not instantiated for this plane count: the rule's shape always is
     const GemmPlan q = plan_partial(N / 16, K / Traits<T>::KSTEP, true);
-    if (q.nt != p.nt || q.waves != p.waves || q.depth != p.depth) return few_partial<T, SPL>(q, st, W, X, xplane, ldx, K, N, rows, out);
+    if (q.nt != p.nt || q.waves != p.waves || q.depth != p.depth) return few_partial<T, SPL>(q, st, W, X, xplane, ldx, K, N, rows, out, fa);
     return fail(SJ_EINVAL, "internal: no few-row kernel for %d tiles x %d waves, ring %d", p.nt, p.waves, p.depth);
 }
 
 // The few-row gate / up projection (SwiGLU epilogue, no K-slices) in the launch shape of a plan.
 template <typename T, int SPL>
 static int few_swiglu(const GemmPlan& p, hipStream_t st, const void* W, const void* X, size_t xplane, int K, int N2, int rows,
-                      void* act, size_t actplane) {
+                      void* act, size_t actplane, const FewArgs& fa = FewArgs{}) {
     if (p.waves == RING_WAVES) {
         if constexpr (std::is_same<T, bf16_t>::value && SPL <= 2) {
             if (ring_fits(p, N2 / 16, K / Traits<T>::KSTEP, rows, SPL, true)) {
 #define SJ_RING(NT, NSA)                                                                                            \
     if (p.nt == NT && p.depth == NSA)                                                                               \
-        return gemm_ring<T, NT, EPI_SWIGLU, SPL, NSA>(st, W, X, xplane, K, K, N2, rows, 1, nullptr, act, actplane, nullptr, 0.f);
+        return gemm_ring<T, NT, EPI_SWIGLU, SPL, NSA>(st, W, X, xplane, K, K, N2, rows, 1, nullptr, act, actplane, nullptr, 0.f, fa);
                 SJ_RING(7, 8) SJ_RING(8, 8) SJ_RING(4, 8) SJ_RING(2, 8) SJ_RING(7, 4) SJ_RING(8, 4) SJ_RING(4, 4)
 #undef SJ_RING
             }
         }
         GemmPlan q;
         q.nt = (N2 / 16) % 7 == 0 ? 7 : 8; q.waves = 8; q.split = 1; q.depth = 2;
-        return few_swiglu<T, SPL>(q, st, W, X, xplane, K, N2, rows, act, actplane);
+        return few_swiglu<T, SPL>(q, st, W, X, xplane, K, N2, rows, act, actplane, fa);
     }
 #define SJ_SHAPE(NT, WV, D)                                                                                         \
     if (p.nt == NT && p.waves == WV && p.depth == D)                                                                \
-        return gemm<T, NT, EPI_SWIGLU, SPL, WV, D>(st, W, X, xplane, K, K, N2, rows, 1, nullptr, act, actplane, nullptr, 0.f);
+        return gemm<T, NT, EPI_SWIGLU, SPL, WV, D>(st, W, X, xplane, K, K, N2, rows, 1, nullptr, act, actplane, nullptr, 0.f, fa);
     SJ_SHAPE(7, 8, 2) SJ_SHAPE(8, 8, 2)
     if constexpr (SPL <= 2) {
         SJ_SHAPE(4, 8, 2) SJ_SHAPE(4, 4, 2) SJ_SHAPE(2, 8, 2) SJ_SHAPE(2, 4, 2) SJ_SHAPE(1, 8, 2)
@@ -932,38 +966,75 @@ static int few_swiglu(const GemmPlan& p, hipStream_t st, const void* W, const vo
 #undef SJ_SHAPE
     GemmPlan q;
     q.nt = (N2 / 16) % 7 == 0 ? 7 : 8; q.waves = 8; q.split = 1; q.depth = 2;
-    if (q.nt != p.nt || q.waves != p.waves || q.depth != p.depth) return few_swiglu<T, SPL>(q, st, W, X, xplane, K, N2, rows, act, actplane);
+    if (q.nt != p.nt || q.waves != p.waves || q.depth != p.depth) return few_swiglu<T, SPL>(q, st, W, X, xplane, K, N2, rows, act, actplane, fa);
     return fail(SJ_EINVAL, "internal: no few-row gate/up kernel for %d tiles x %d waves", p.nt, p.waves);
+}
+
+// A projection that closes a sub-layer (O, down) with the residual add in its epilogue (EPI_RESID; no K-slices): one launch
+// instead of two.  Without slices a workgroup has one n-tile (two, four where that fills the chip) and reads as much operand as
+// weights, so it pays up to 8 rows, where both planes are one packed fragment: 8B shape, 6 rows: down 20.3 -> 21.0 us, O 8.5 ->
+// 8.7, the norm launches (4.7 us each) gone, step 3.45 -> 3.30 ms; 1B draft, 1 row: 5.18 -> 4.85 ms a block.  At 12 and 20 rows
+// (operand twice and four times the weights) steps took 8 % and 11 % longer.  nt = 0: not taken.
+static GemmPlan resid_plan(int N, int K, int kstep, int rows, int planes, bool bf16, int ring_rows) {
+    GemmPlan p;
+    p.nt = 0;
+    const int ntiles = N / 16, ksteps = K / kstep, nt = ntiles > 512 ? 4 : ntiles > 256 ? 2 : 1;
+    if (rows > RING_PACK_ROWS || planes > 2 || ntiles % nt) return p;
+    p.nt = nt; p.split = 1;
+    p.waves = RING_WAVES;
+    p.depth = ksteps / RING_CW * nt >= 16 ? 8 : 4;
+    if (rows <= ring_rows && ring_fits(p, ntiles, ksteps, rows, planes, bf16)) return p;
+    p.waves = 8; p.depth = 2;
+    return p;
+}
+template <typename T, int SPL>
+static int few_resid(const GemmPlan& p, hipStream_t st, const void* W, const void* X, size_t xplane, int K, int N, int rows, void* xg,
+                     size_t xgplane, const FewArgs& fa) {
+    if constexpr (SPL <= 2) {
+        if constexpr (std::is_same<T, bf16_t>::value) {
+#define SJ_RING(NT, NSA)                                                                                            \
+    if (p.waves == RING_WAVES && p.nt == NT && p.depth == NSA)                                                      \
+        return gemm_ring<T, NT, EPI_RESID, SPL, NSA>(st, W, X, xplane, K, K, N, rows, 1, nullptr, xg, xgplane, nullptr, 0.f, fa);
+            SJ_RING(1, 8) SJ_RING(2, 8) SJ_RING(4, 8) SJ_RING(1, 4) SJ_RING(2, 4) SJ_RING(4, 4)
+#undef SJ_RING
+        }
+#define SJ_SHAPE(NT)                                                                                                \
+    if (p.waves == 8 && p.nt == NT)                                                                                 \
+        return gemm<T, NT, EPI_RESID, SPL, 8, 2>(st, W, X, xplane, K, K, N, rows, 1, nullptr, xg, xgplane, nullptr, 0.f, fa);
+        SJ_SHAPE(1) SJ_SHAPE(2) SJ_SHAPE(4)
+#undef SJ_SHAPE
+    }
+    return fail(SJ_EINVAL, "internal: no residual kernel for %d tiles x %d waves", p.nt, p.waves);
 }
 
 // The few-row LM head (logits + per-workgroup softmax statistics: V / 16 / nt entries per row) in the launch shape of a plan.
 template <typename T, int SPL>
 static int few_logits(const GemmPlan& p, hipStream_t st, const void* W, const void* X, size_t xplane, int K, int V, int rows,
-                      float* logits, float4* stats, float inv_temp) {
+                      float* logits, float4* stats, float inv_temp, const FewArgs& fa = FewArgs{}) {
     if (p.waves == RING_WAVES) {
         if constexpr (std::is_same<T, bf16_t>::value && SPL <= 2) {
             if (ring_fits(p, V / 16, K / Traits<T>::KSTEP, rows, SPL, true)) {
 #define SJ_RING(NT, NSA)                                                                                            \
     if (p.nt == NT && p.depth == NSA)                                                                               \
-        return gemm_ring<T, NT, EPI_LOGITS, SPL, NSA>(st, W, X, xplane, K, K, V, rows, 1, logits, nullptr, 0, stats, inv_temp);
+        return gemm_ring<T, NT, EPI_LOGITS, SPL, NSA>(st, W, X, xplane, K, K, V, rows, 1, logits, nullptr, 0, stats, inv_temp, fa);
                 SJ_RING(8, 4) SJ_RING(8, 8) SJ_RING(4, 8)
 #undef SJ_RING
             }
         }
         // the statistics are laid out for p.nt tiles per workgroup: only a kernel with the same count may stand in
-        if (p.nt == 8) return few_logits<T, SPL>(GemmPlan{8, 4, 1, 2}, st, W, X, xplane, K, V, rows, logits, stats, inv_temp);
+        if (p.nt == 8) return few_logits<T, SPL>(GemmPlan{8, 4, 1, 2}, st, W, X, xplane, K, V, rows, logits, stats, inv_temp, fa);
         if (p.nt == 4) {
-            if constexpr (SPL <= 2) return few_logits<T, SPL>(GemmPlan{4, 8, 1, 2}, st, W, X, xplane, K, V, rows, logits, stats, inv_temp);
+            if constexpr (SPL <= 2) return few_logits<T, SPL>(GemmPlan{4, 8, 1, 2}, st, W, X, xplane, K, V, rows, logits, stats, inv_temp, fa);
         }
         return fail(SJ_EINVAL, "internal: no few-row LM-head kernel for %d tiles per workgroup", p.nt);
     }
 #define SJ_SHAPE(NT, WV)                                                                                            \
     if (p.nt == NT && p.waves == WV)                                                                                \
-        return gemm<T, NT, EPI_LOGITS, SPL, WV>(st, W, X, xplane, K, K, V, rows, 1, logits, nullptr, 0, stats, inv_temp);
+        return gemm<T, NT, EPI_LOGITS, SPL, WV>(st, W, X, xplane, K, K, V, rows, 1, logits, nullptr, 0, stats, inv_temp, fa);
     SJ_SHAPE(8, 4)
     if constexpr (SPL <= 2) { SJ_SHAPE(8, 8) SJ_SHAPE(4, 8) SJ_SHAPE(4, 4) }
 #undef SJ_SHAPE
-    if (p.nt != 8 || p.waves != 4) return few_logits<T, SPL>(GemmPlan{8, 4, 1, 2}, st, W, X, xplane, K, V, rows, logits, stats, inv_temp);
+    if (p.nt != 8 || p.waves != 4) return few_logits<T, SPL>(GemmPlan{8, 4, 1, 2}, st, W, X, xplane, K, V, rows, logits, stats, inv_temp, fa);
     return fail(SJ_EINVAL, "internal: no few-row LM-head kernel for %d tiles x %d waves", p.nt, p.waves);
 }
 
@@ -1009,12 +1080,14 @@ static int tune_one(sj_kv* kv, GemmPlan& plan, void* LayerW::*which, const void*
     const int ksteps = K / Traits<T>::KSTEP, ntiles = N / 16;
     const int nl = std::min(m->cfg.n_layers, 16);
     const size_t xplane = (size_t)kv->rpad * K;
+    FewArgs fa;
+    fa.packed = packed_rows<T, SPL>(rows);
     auto time_plan = [&](const GemmPlan& p, double& us) -> int {
         float ms = 0.f;
         for (int rep = 0; rep < 2; ++rep) {                 // the first repetition warms up
             HIPCHK(hipEventRecord(e0, nullptr));
             for (int l = 0; l < nl; ++l) {
-                const int rc = few_partial<T, SPL>(p, nullptr, m->layers[l].*which, X, xplane, K, K, N, rows, kv->part);
+                const int rc = few_partial<T, SPL>(p, nullptr, m->layers[l].*which, X, xplane, K, K, N, rows, kv->part, fa);
                 if (rc) return rc;
             }
             HIPCHK(hipEventRecord(e1, nullptr));
@@ -1059,13 +1132,15 @@ static int tune_gate_up(sj_kv* kv, int rows, hipEvent_t e0, hipEvent_t e1) {
     const sj_model* m = kv->m;
     const int d = m->cfg.d_model, F = m->cfg.d_ffn, ntiles = 2 * F / 16;
     const int nl = std::min(m->cfg.n_layers, 16);
+    FewArgs fa;
+    fa.packed = packed_rows<T, SPL>(rows);
     auto time_plan = [&](const GemmPlan& p, double& us) -> int {
         float ms = 0.f;
         for (int rep = 0; rep < 2; ++rep) {                 // the first repetition warms up
             HIPCHK(hipEventRecord(e0, nullptr));
             for (int l = 0; l < nl; ++l) {
                 const int rc = few_swiglu<T, SPL>(p, nullptr, m->layers[l].wgu, kv->xn, (size_t)kv->rpad * d, d, 2 * F, rows, kv->act,
-                                                  (size_t)kv->rpad * F);
+                                                  (size_t)kv->rpad * F, fa);
                 if (rc) return rc;
             }
             HIPCHK(hipEventRecord(e1, nullptr));
@@ -1100,13 +1175,15 @@ template <typename T, int SPL>
 static int tune_lm_head(sj_kv* kv, int rows, hipEvent_t e0, hipEvent_t e1) {
     const sj_model* m = kv->m;
     const int d = m->cfg.d_model, V = m->cfg.vocab;
+    FewArgs fa;
+    fa.packed = packed_rows<T, SPL>(rows);
     auto time_plan = [&](const GemmPlan& p, double& us) -> int {
         float ms = 0.f;
         for (int rep = 0; rep < 2; ++rep) {                 // the first repetition warms up
             HIPCHK(hipEventRecord(e0, nullptr));
             for (int l = 0; l < 3; ++l) {
                 const int rc = few_logits<T, SPL>(p, nullptr, m->lm_head, kv->xn, (size_t)kv->rpad * d, d, V, rows, kv->logits, kv->stats,
-                                                  m->md.inv_temp);
+                                                  m->md.inv_temp, fa);
                 if (rc) return rc;
             }
             HIPCHK(hipEventRecord(e1, nullptr));
@@ -1255,11 +1332,12 @@ struct Runner {
         v.len = kv->len_dev; v.pending = kv->pending_dev; v.layer_stride = kv->layer_stride;
         return v;
     }
-    size_t plane(int ld) const { return (size_t)w->rpad * ld; }
+    bool packed() const { return packed_rows<T, SPL>(R); }
+    size_t plane(int ld) const { return packed() ? 8 * Traits<T>::KSTEP : (size_t)w->rpad * ld; }
     // Operand planes are written as MFMA fragments when the many-row kernel that reads operands through LDS
     // consumes them (more than FEW_ROWS rows, at most two planes); row-major otherwise.
     bool tiled() const { return R > FEW_ROWS && SPL <= 2; }
-    int tks(int K) const { return tiled() ? K / Traits<T>::KSTEP : 0; }
+    int tks(int K) const { return tiled() || packed() ? K / Traits<T>::KSTEP : 0; }
     // the same for a single exact plane (hidden states handed in by the caller), whatever SPL is
     int tks1(int K) const { return R > FEW_ROWS ? K / Traits<T>::KSTEP : 0; }
     // Launch shape of a split-K projection for this row count.  A prompt chunk of at most 32 rows can have more rows than
@@ -1275,18 +1353,48 @@ struct Runner {
         return pl[0];
     }
     // `parts`: the K-slices it leaves in w->part
-    int partial_gemm(const void* W, const void* X, int ldx, int K, int N, const GemmPlan (&pl)[2], int* parts = nullptr) {
+    int partial_gemm(const void* W, const void* X, int ldx, int K, int N, const GemmPlan (&pl)[2], int* parts = nullptr, bool unscaled = false) {
         const GemmPlan p = plan_of(pl, K, N);
         if (parts) *parts = p.split;
         if (R > FEW_ROWS) return gemm_rows<T, EPI_PARTIAL, SPL>(st, W, X, plane(ldx), ldx, K, N, R, p.split, w->part, nullptr, 0, nullptr, 0.f, tiled());
-        return few_partial<T, SPL>(p, st, W, X, plane(ldx), ldx, K, N, R, w->part);
+        return few_partial<T, SPL>(p, st, W, X, plane(ldx), ldx, K, N, R, w->part, few_args(unscaled));
+    }
+    // the operand in w->xn lacks its 1/rms factors (it came from a residual epilogue)
+    FewArgs few_args(bool unscaled) const {
+        FewArgs n;
+        n.packed = packed();
+        if (unscaled) { n.ss_in = w->ss; n.eps = m->md.eps; }
+        return n;
+    }
+    // O or down projection with its sub-layer's residual add, either in its epilogue (`unscaled`: the next operand, with the norm
+    // gain, is in w->xn without its 1/rms factors) or left in `parts` K-slices for norm()
+    int closing_gemm(const void* W, const void* X, int K, const GemmPlan (&pl)[2], const void* gain, int& parts, bool& unscaled) {
+        const int d = m->md.d;
+        const GemmPlan p = resid_plan(d, K, Traits<T>::KSTEP, R, SPL, std::is_same<T, bf16_t>::value, kv->ring_rows);
+        unscaled = p.nt > 0;
+        if (!unscaled) return partial_gemm(W, X, K, K, d, pl, &parts);
+        FewArgs n = few_args(false);
+        n.x = w->x; n.gain = gain; n.ss_out = w->ss;
+        return few_resid<T, SPL>(p, st, W, X, plane(K), K, d, R, w->xn, plane(d), n);
+    }
+    // the same up to and including the next norm
+    int close(const void* W, const void* X, int K, const GemmPlan (&pl)[2], const void* gain, int cls, bool& unscaled) {
+        int rc, parts = 0;
+        if ((rc = time_mark(kv, cls, st))) return rc;
+        if ((rc = closing_gemm(W, X, K, pl, gain, parts, unscaled))) return rc;
+        if ((rc = time_mark(kv, cls, st))) return rc;
+        if (!unscaled) {
+            norm(parts, gain, nullptr);
+            LAUNCHCHK("add_rmsnorm");
+        }
+        return SJ_OK;
     }
     // gate / up projection with the SwiGLU epilogue: 7 n-tiles per workgroup when that gives a whole
     // number of workgroups per CU (2F/16 = 1792 tiles -> 256 workgroups), else 8
-    int gate_up(const void* W) {
+    int gate_up(const void* W, bool unscaled = false) {
         const ModelDims& md = m->md;
         if (R > FEW_ROWS) return gemm_rows<T, EPI_SWIGLU, SPL>(st, W, w->xn, plane(md.d), md.d, md.d, 2 * md.F, R, 1, nullptr, w->act, plane(md.F), nullptr, 0.f, tiled());
-        return few_swiglu<T, SPL>(kv->plan_gu, st, W, w->xn, plane(md.d), md.d, 2 * md.F, R, w->act, plane(md.F));
+        return few_swiglu<T, SPL>(kv->plan_gu, st, W, w->xn, plane(md.d), md.d, 2 * md.F, R, w->act, plane(md.F), few_args(unscaled));
     }
 
     // rotary + cache append + attention of one layer from the QKV partials in w->part
@@ -1342,15 +1450,15 @@ struct Runner {
 
     // residual add of `parts` pending split-K partials + RMSNorm into the operand planes (batches of loads as wide as
     // the partials there are: an eight-wide clamped batch for two partials repeats six loads)
-    void norm(int parts, const void* gain, float* xn32) { norm_rows(parts, gain, xn32, 0, R, 0, tks(m->md.d)); }
+    void norm(int parts, const void* gain, float* xn32) { norm_rows(parts, gain, xn32, 0, R, 0, tks(m->md.d), plane(m->md.d)); }
     // rows r0 .. r0 + n - 1 of the block into rows o0 .. of the operand planes (o0 a multiple of 16 in tiled planes) and of xn32
-    void norm_rows(int parts, const void* gain, float* xn32, int r0, int n, int o0, int otks) {
+    void norm_rows(int parts, const void* gain, float* xn32, int r0, int n, int o0, int otks, size_t oplane) {
         const int d = m->md.d;
         float *x = w->x + (size_t)r0 * d, *part = w->part + (size_t)r0 * d, *h = xn32 ? xn32 + (size_t)o0 * d : nullptr;
         T* xn = (T*)w->xn + (size_t)o0 * d;
-        if (parts <= 2) add_rmsnorm_kernel<T, 2><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, plane(d), h, otks);
-        else if (parts <= 4) add_rmsnorm_kernel<T, 4><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, plane(d), h, otks);
-        else add_rmsnorm_kernel<T, 8><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, plane(d), h, otks);
+        if (parts <= 2) add_rmsnorm_kernel<T, 2, SPL><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, oplane, h, otks);
+        else if (parts <= 4) add_rmsnorm_kernel<T, 4, SPL><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, oplane, h, otks);
+        else add_rmsnorm_kernel<T, 8, SPL><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, oplane, h, otks);
     }
 
     // decoder layers (Eq. 2 / Eq. 4): leaves the last down-projection's K-slices pending in w->part (their number in `parts`)
@@ -1358,30 +1466,29 @@ struct Runner {
         const ModelDims& md = m->md;
         const sj_config& c = m->cfg;
         const int d = md.d, Nq = md.Hq * md.hd, Nk = md.Hkv * md.hd, Nqkv = Nq + 2 * Nk;
-        step_begin_kernel<T><<<R, 256, 0, st>>>(kv->sp_dev, md, (const T*)m->embed, kv->len_dev, kv->pending_dev, w->x,
-                                                 w->cs, w->row_tok, std::log((double)c.rope_base));
+        step_begin_kernel<T, SPL><<<R, 1024, 0, st>>>(kv->sp_dev, md, (const T*)m->embed, kv->len_dev, kv->pending_dev, w->x, w->cs, w->row_tok,
+                                                  std::log((double)c.rope_base), (const T*)m->layers[0].attn_norm, (T*)w->xn, plane(d), tks(d));
         LAUNCHCHK("step_begin");
         parts = 0;
+        bool unscaled = false;
         int rc;
         for (int l = 0; l < c.n_layers; ++l) {
             const LayerW& L = m->layers[l];
-            norm(parts, L.attn_norm, nullptr);
-            LAUNCHCHK("add_rmsnorm");
             if ((rc = time_mark(kv, 1, st))) return rc;
-            if ((rc = partial_gemm(L.wqkv, w->xn, d, d, Nqkv, kv->plan_qkv, &parts))) return rc;
+            if ((rc = partial_gemm(L.wqkv, w->xn, d, d, Nqkv, kv->plan_qkv, &parts, unscaled))) return rc;
             if ((rc = time_mark(kv, 1, st))) return rc;
             if ((rc = attention(l, parts))) return rc;
-            if ((rc = time_mark(kv, 2, st))) return rc;
-            if ((rc = partial_gemm(L.wo, w->attn_out, Nq, Nq, d, kv->plan_o, &parts))) return rc;
-            if ((rc = time_mark(kv, 2, st))) return rc;
-            norm(parts, L.ffn_norm, nullptr);
-            LAUNCHCHK("add_rmsnorm");
+            if ((rc = close(L.wo, w->attn_out, Nq, kv->plan_o, L.ffn_norm, 2, unscaled))) return rc;
             if ((rc = time_mark(kv, 3, st))) return rc;
-            if ((rc = gate_up(L.wgu))) return rc;
+            if ((rc = gate_up(L.wgu, unscaled))) return rc;
             if ((rc = time_mark(kv, 3, st))) return rc;
-            if ((rc = time_mark(kv, 4, st))) return rc;
-            if ((rc = partial_gemm(L.wd, w->act, md.F, md.F, d, kv->plan_d, &parts))) return rc;
-            if ((rc = time_mark(kv, 4, st))) return rc;
+            if (l + 1 < c.n_layers) {
+                if ((rc = close(L.wd, w->act, md.F, kv->plan_d, m->layers[l + 1].attn_norm, 4, unscaled))) return rc;
+            } else {
+                if ((rc = time_mark(kv, 4, st))) return rc;
+                if ((rc = partial_gemm(L.wd, w->act, md.F, md.F, d, kv->plan_d, &parts))) return rc;
+                if ((rc = time_mark(kv, 4, st))) return rc;
+            }
         }
         return SJ_OK;
     }
@@ -1407,7 +1514,7 @@ struct Runner {
         } else {
             rc = exact_operand
                 ? few_logits<T, 1>(kv->plan_lm, st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, kv->logits, kv->stats, md.inv_temp)
-                : few_logits<T, SPL>(kv->plan_lm, st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, kv->logits, kv->stats, md.inv_temp);
+                : few_logits<T, SPL>(kv->plan_lm, st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, kv->logits, kv->stats, md.inv_temp, few_args(false));
             nblk = md.V / 16 / kv->plan_lm.nt;
         }
         return rc;
@@ -1537,7 +1644,8 @@ static int time_kernel_impl(sj_model* m, sj_kv* kv, int cls, int launches, int g
     hipEvent_t e0, e1;
     HIPCHK(hipEventCreate(&e0));
     HIPCHK(hipEventCreate(&e1));
-    int rc = SJ_OK;
+    int rc = SJ_OK, parts = 0;
+    bool unscaled = false;
     HIPCHK(hipEventRecord(e0, st));
     for (int i = 0; i < launches && !rc; ++i) {
         if (cls == 5) {                                          // LM head (1 GB at the paper's vocabulary: no reuse either)
@@ -1548,9 +1656,9 @@ static int time_kernel_impl(sj_model* m, sj_kv* kv, int cls, int launches, int g
         const LayerW& L = m->layers[i % m->cfg.n_layers];        // a different layer each time: no cache reuse
         switch (cls) {
             case 1: rc = run.partial_gemm(L.wqkv, kv->xn, d, d, Nq + 2 * Nk, kv->plan_qkv); break;
-            case 2: rc = run.partial_gemm(L.wo, kv->attn_out, Nq, Nq, d, kv->plan_o); break;
+            case 2: rc = run.closing_gemm(L.wo, kv->attn_out, Nq, kv->plan_o, L.ffn_norm, parts, unscaled); break;
             case 3: rc = run.gate_up(L.wgu); break;
-            default: rc = run.partial_gemm(L.wd, kv->act, md.F, md.F, d, kv->plan_d); break;
+            default: rc = run.closing_gemm(L.wd, kv->act, md.F, kv->plan_d, L.ffn_norm, parts, unscaled); break;
         }
     }
     hipError_t e = hipEventRecord(e1, st);
@@ -1859,8 +1967,8 @@ static int prefill_impl(sj_model* m, sj_kv* kv, int seq, const int32_t* tokens, 
                 head_rows = n - (n - 1) / block * block;
                 const int keep = std::min(block, cn);          // chunks are longer than a block: cn > block
                 Runner<T, SPL> head{m, kv, st, 1, head_rows, head_rows, fw};
-                if (keep > head_rows) run.norm_rows(parts, m->final_norm, kv->hn32, cn - keep, keep - head_rows, head_rows, 0);
-                run.norm_rows(parts, m->final_norm, kv->hn32, cn - head_rows, head_rows, 0, head.tks(m->md.d));
+                if (keep > head_rows) run.norm_rows(parts, m->final_norm, kv->hn32, cn - keep, keep - head_rows, head_rows, 0, run.plane(m->md.d));
+                run.norm_rows(parts, m->final_norm, kv->hn32, cn - head_rows, head_rows, 0, head.tks(m->md.d), head.plane(m->md.d));
                 LAUNCHCHK("add_rmsnorm");
             }
         }

@@ -232,7 +232,7 @@ __global__ __launch_bounds__(256) void prefill_attn_kernel(const StepParams* __r
 #pragma unroll
             for (int ht = 0; ht < HT; ++ht) {
                 const float v[4] = {o[ht][mq][0] * inv, o[ht][mq][1] * inv, o[ht][mq][2] * inv, o[ht][mq][3] * inv};
-                Traits<T>::store_split4(attn_out + opnd_off<T>(jrow[mq], (kvh * md.G + girow[mq]) * HD + ht * 16 + 4 * g, md.Hq * HD, otks), aplane, v);
+                Traits<T>::template store_split4<SPL>(attn_out + opnd_off<T>(jrow[mq], (kvh * md.G + girow[mq]) * HD + ht * 16 + 4 * g, md.Hq * HD, otks), aplane, v);
             }
         }
     }
