@@ -38,6 +38,35 @@ constexpr int R2_NB = 4;           // LDS stage buffers
 constexpr int R2_MTW = 3;          // row tiles per compute wave (4 waves x 3 >= 9 row tiles)
 constexpr int R2_RING = 4;         // operand ring (k-steps) = k-steps per stage
 
+// Softmax partial (max, sum exp((l - max)/T), lowest arg-max) of a row over `n` <= NTILES neighbouring n-tiles from nt on: the row's four
+// lanes hold four columns of each tile; all of them get the result.
+template <int NTILES>
+__device__ __forceinline__ float4 rows_softmax_stat(const f32x4* v, int nt, int n, float inv_temp, int g) {
+    float mx = v[0][0];
+    int arg = nt * 16 + 4 * g;
+#pragma unroll
+    for (int t = 0; t < NTILES; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (t < n && v[t][e] > mx) { mx = v[t][e]; arg = (nt + t) * 16 + 4 * g + e; }
+#pragma unroll
+    for (int o = 16; o < 64; o <<= 1) {
+        const float omx = __shfl_xor(mx, o, 64);
+        const int oarg = __shfl_xor(arg, o, 64);
+        if (omx > mx || (omx == mx && oarg < arg)) { mx = omx; arg = oarg; }
+    }
+    float se = 0.f;
+    if (inv_temp > 0.f) {
+#pragma unroll
+        for (int t = 0; t < NTILES; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) se += t < n ? expf((v[t][e] - mx) * inv_temp) : 0.f;
+        se += __shfl_xor(se, 16, 64);
+        se += __shfl_xor(se, 32, 64);
+    }
+    return float4{mx, se, __int_as_float(arg), 0.f};
+}
+
 // Epilogue of the many-row kernels for ONE accumulator tile (row tile m, n-tile nt): the lane holds columns
 // nt*16 + 4g .. +3 of row m*16 + r.  Uniform per wave; rows >= R take part in the shuffles and store nothing.
 template <typename T, int EPI>
@@ -60,28 +89,11 @@ __device__ __forceinline__ void rows_epilogue_tile(const GemmArgs& a, const f32x
         if (valid && g < 2)
             Traits<T>::store_split4(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, nt * 8 + 4 * g, a.N / 2, a.act_tks), a.actplane, y);
     } else {
-        // logits + this tile's softmax partial of the row (max, sum exp((l - max)/T), lowest arg-max)
-        float mx = v[0];
-        int arg = nt * 16 + 4 * g;
-#pragma unroll
-        for (int e = 1; e < 4; ++e)
-            if (v[e] > mx) { mx = v[e]; arg = nt * 16 + 4 * g + e; }
-#pragma unroll
-        for (int o = 16; o < 64; o <<= 1) {
-            const float omx = __shfl_xor(mx, o, 64);
-            const int oarg = __shfl_xor(arg, o, 64);
-            if (omx > mx || (omx == mx && oarg < arg)) { mx = omx; arg = oarg; }
-        }
-        float se = 0.f;
-        if (a.inv_temp > 0.f) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) se += expf((v[e] - mx) * a.inv_temp);
-            se += __shfl_xor(se, 16, 64);
-            se += __shfl_xor(se, 32, 64);
-        }
+        // logits + this tile's softmax partial of the row
+        const float4 st = rows_softmax_stat<1>(&v, nt, 1, a.inv_temp, g);
         if (valid) {
             *reinterpret_cast<f32x4*>(a.out + (size_t)row * a.N + (size_t)nt * 16 + 4 * g) = v;
-            if (g == 0) a.stats[(size_t)row * ntiles + nt] = float4{mx, se, __int_as_float(arg), 0.f};
+            if (g == 0) a.stats[(size_t)row * ntiles + nt] = st;
         }
     }
 }
@@ -262,7 +274,7 @@ __global__ __launch_bounds__((R8_CW + R4_LW) * 64) void gemm_rows8_kernel(GemmAr
         a.X = reinterpret_cast<const char*>(a.X) + (size_t)row0 * a.ldx * sizeof(T);
         if (EPI == EPI_SWIGLU) a.act = reinterpret_cast<char*>(a.act) + (size_t)row0 * (a.N / 2) * sizeof(T);
         else a.out += (size_t)row0 * a.N;
-        if (EPI == EPI_LOGITS) a.stats += (size_t)row0 * ntiles;
+        if (EPI == EPI_LOGITS) a.stats += (size_t)row0 * ((ntiles + NT - 1) / NT);
         a.R = nr;
         mt = (nr + 15) / 16;
     }
@@ -303,6 +315,7 @@ __global__ __launch_bounds__((R8_CW + R4_LW) * 64) void gemm_rows8_kernel(GemmAr
                 lds_barrier();
             }
             wait_vm0();
+            if constexpr (EPI == EPI_LOGITS) { lds_barrier(); lds_barrier(); }   // the statistics' barriers
         };
         if (lw < 2) {
             auto make_src = [&](int j, const char*& sp, size_t& st) {
@@ -389,6 +402,61 @@ __global__ __launch_bounds__((R8_CW + R4_LW) * 64) void gemm_rows8_kernel(GemmAr
             multiply(fB);
             lds_barrier();                             // stage s + 3 has landed
         }
+    }
+    if constexpr (EPI == EPI_LOGITS) {
+        // Logits, and ONE softmax partial per row and workgroup: a partial per n-tile (16 bytes for 64 bytes of logits) was 74 MB
+        // to write and to read again for the 576 rows of a 64-sequence batch (merge launch 41 us, now a tenth of the bytes).
+        // A wave reduces its n-tiles of a row in registers; the waves' partials meet in the ring's memory.
+        static_assert(NT == 8, "two halves of four n-tiles");
+        constexpr int HALVES = 2;
+        float4* st_full = reinterpret_cast<float4*>(&Wst[0][0][0]);      // [4 * NFULL row tiles][half][16 rows]
+        float4* st_rem = st_full + 4 * NFULL * HALVES * 16;              // [NREM][8 waves][16 rows]
+        static_assert((4 * NFULL * HALVES + NREM * R8_CW) * 16 * sizeof(float4) <= sizeof(Wst), "fits the weight ring");
+        lds_barrier();                                 // the loaders' last requests have landed, every fragment has been read
+        const int nv = min(nh, ntiles - (nt0 + t0));   // n-tiles of this wave's half that exist
+#pragma unroll
+        for (int i = 0; i < NFULL; ++i) {
+            const int m = ra + 4 * i, row = m * 16 + r;
+            if (m >= mt) continue;                     // uniform
+            float4 st = float4{-INFINITY, 0.f, __int_as_float(0x7fffffff), 0.f};
+            if (nv > 0) st = rows_softmax_stat<NH>(acc[i], nt0 + t0, nv, a.inv_temp, g);
+            if (g == 0) st_full[(m * HALVES + nb) * 16 + r] = st;
+            if (row < a.R)
+#pragma unroll
+                for (int t = 0; t < NH; ++t)
+                    if (t < nv) *reinterpret_cast<f32x4*>(a.out + (size_t)row * a.N + (size_t)(nt0 + t0 + t) * 16 + 4 * g) = acc[i][t];
+        }
+#pragma unroll
+        for (int j = 0; j < NREM; ++j) {
+            const int m = 4 * NFULL + j, row = m * 16 + r;
+            if (m >= mt) continue;
+            float4 st = float4{-INFINITY, 0.f, __int_as_float(0x7fffffff), 0.f};
+            if (nt0 + w < ntiles) {
+                st = rows_softmax_stat<1>(&acc8[j], nt0 + w, 1, a.inv_temp, g);
+                if (row < a.R) *reinterpret_cast<f32x4*>(a.out + (size_t)row * a.N + (size_t)(nt0 + w) * 16 + 4 * g) = acc8[j];
+            }
+            if (g == 0) st_rem[(j * R8_CW + w) * 16 + r] = st;
+        }
+        lds_barrier();
+        for (int row = tid; row < a.R; row += R8_CW * 64) {
+            const int m = row >> 4, rr = row & 15;
+            const bool full = m < 4 * NFULL;
+            const float4* p = full ? st_full + m * HALVES * 16 + rr : st_rem + (m - 4 * NFULL) * R8_CW * 16 + rr;
+            const int n = full ? HALVES : R8_CW;
+            float4 s = p[0];
+            for (int k = 1; k < n; ++k) {              // ascending columns: an equal maximum keeps the lower index
+                const float4 o = p[k * 16];
+                if (o.x > s.x) { s.x = o.x; s.z = o.z; }
+            }
+            float se = 0.f;
+            if (a.inv_temp > 0.f)
+                for (int k = 0; k < n; ++k) {
+                    const float4 o = p[k * 16];
+                    if (o.y > 0.f) se += o.y * expf((o.x - s.x) * a.inv_temp);
+                }
+            a.stats[(size_t)row * ((ntiles + NT - 1) / NT) + bx] = float4{s.x, se, s.z, 0.f};
+        }
+        return;
     }
 #pragma unroll
     for (int t = 0; t < NH; ++t) {

@@ -91,7 +91,7 @@ __global__ void set_state_kernel(int32_t* len, int32_t* pending, int seq, int l,
 // add_rmsnorm_kernel) and the row's rotary cos/sin table
 // (angle = pos * base^(-2i/hd), evaluated in double so the table is correctly rounded fp32).
 template <typename T, int SPL>
-__global__ __launch_bounds__(1024) void step_begin_kernel(const StepParams* __restrict__ sp, ModelDims md,
+__global__ __launch_bounds__(1024) void step_begin_kernel(StepParams* __restrict__ sp, ModelDims md,
                                                           const T* __restrict__ embed, const int32_t* __restrict__ len,
                                                           const int32_t* __restrict__ pending, float* __restrict__ x,
                                                           float* __restrict__ cs, int32_t* __restrict__ row_tok,
@@ -109,6 +109,7 @@ __global__ __launch_bounds__(1024) void step_begin_kernel(const StepParams* __re
     tok = min(max(tok, 0), md.V - 1);
     const int pos = len[b] + j;
     if (threadIdx.x == 0) row_tok[r] = tok;
+    if (r == 0 && threadIdx.x == 0) ++sp->step;        // read by the step's last kernels only
     const T* e = embed + (size_t)tok * md.d;
     constexpr int MAXP = 4;                            // d <= 16384 (host-checked), a multiple of 64
     float v[MAXP][4], ss = 0.f;
@@ -589,9 +590,13 @@ __global__ __launch_bounds__(64) void accept_scan_kernel(const StepParams* __res
 //   all accepted:  w_k = e_k          else:  w_k = max(0, e_k - Z * q_k)   (q = draft law of the
 // first rejected token);  if sum w = 0 fall back to w = e.
 // Element k belongs to slab k / slab_len; slab s is owned by thread s % 256 of workgroup s / 256.
-//   pass 1 (resample_e):    per-slab sums of e               -> epart
-//   pass 2 (resample_w):    Z from epart, per-slab sums of w -> wpart
-//   pass 3 (resample_pick): scan the slab sums, walk the hit slab, commit the sequence state.
+//   pass 1 (resample_e):    per-slab and per-workgroup sums of e -> epart, eblk
+//   pass 2 (resample_w):    Z from eblk, the same sums of w      -> wpart, wblk
+//   pass 3 (resample_pick): scan the workgroup sums, then the slab sums of the workgroup that holds the target, then that
+//                           slab's weights; commit the sequence state.
+// The passes are chains of dependent memory round trips over little data, so the search goes down three levels with one round
+// trip each; scanning all slab sums of a 128256-entry vocabulary (8192) in every workgroup that needs Z took 64 KB of reads
+// each (64 sequences: pass 2 29 us, pick 23 us).
 struct ResampleArgs {
     int32_t V, nslab, slab_len;   // nslab = 256 * gridDim.x of passes 1, 2
     float inv_temp;
@@ -600,18 +605,23 @@ struct ResampleArgs {
     const int32_t* nacc;
     double* epart;    // [nseq][nslab]
     double* wpart;    // [nseq][nslab]
+    double* eblk;     // [nseq][nslab / 256]
+    double* wblk;     // [nseq][nslab / 256]
 };
 
 __device__ __forceinline__ double e_of(float logit, float mx, float inv_temp) {
     return exp(((double)logit - (double)mx) * (double)inv_temp);
 }
 
-// pass 1 of the draw for the row after `n` accepted tokens
-__device__ __forceinline__ void resample_e_slab(const StepParams* __restrict__ sp, const ResampleArgs& a, int n) {
+// pass 1 of the draw for the row after `n` accepted tokens; q_out (a plain decode step of a draft block): the row's law as fp32
+// probabilities
+__device__ __forceinline__ void resample_e_slab(const StepParams* __restrict__ sp, const ResampleArgs& a, int n, float* __restrict__ q_out) {
+    __shared__ double red[4];
     const int bi = blockIdx.y, slab = blockIdx.x * 256 + threadIdx.x;
     const int gamma = sp->gamma;
     const int row = bi * (gamma + 1) + n;
-    const float mx = a.rowstat[row].x;
+    const float4 st = a.rowstat[row];
+    const float mx = st.x, invz = 1.0f / st.y;
     const float* l = a.logits + (size_t)row * a.V;
     const int k0 = slab * a.slab_len, k1 = min(a.V, k0 + a.slab_len);
     double s = 0.0;
@@ -627,10 +637,12 @@ __device__ __forceinline__ void resample_e_slab(const StepParams* __restrict__ s
         for (int k = k0; k < k1; ++k) s += e_of(l[k], mx, a.inv_temp);
     }
     a.epart[(size_t)bi * a.nslab + slab] = s;
-}
-
-__global__ __launch_bounds__(256) void resample_e_kernel(const StepParams* __restrict__ sp, ResampleArgs a) {
-    resample_e_slab(sp, a, a.nacc[blockIdx.y]);
+    s = block_sum_256(s, red);
+    if (threadIdx.x == 0) a.eblk[(size_t)bi * (a.nslab / 256) + blockIdx.x] = s;
+    if (q_out) {                                       // uniform; consecutive entries per thread, whatever the slabs are
+        const int lo = blockIdx.x * 256 * a.slab_len, hi = min(a.V, lo + 256 * a.slab_len);
+        for (int k = lo + threadIdx.x; k < hi; k += 256) q_out[k] = expf((l[k] - mx) * a.inv_temp) * invz;
+    }
 }
 
 // Scan and pass 1 in one launch: pass 1 only needs accepted_len to know its row, and the scan is a handful of loads,
@@ -647,35 +659,28 @@ __global__ __launch_bounds__(256) void scan_resample_e_kernel(const StepParams* 
         if (threadIdx.x == 0) n_sh = n;
     }
     __syncthreads();
-    resample_e_slab(sp, a, n_sh);
+    resample_e_slab(sp, a, n_sh, sp->emit_probs ? sp->emit_probs + ((size_t)blockIdx.y * sp->emit_gamma + sp->step) * a.V : nullptr);
 }
 
-// sum of n slab sums by a 256-thread block: 8 independent loads per thread and batch (index clamped,
-// surplus ignored), fixed order
-__device__ __forceinline__ double total_of(const double* part, int n, double* lds4) {
+// sum of n workgroup sums by one wave; fixed order, every lane gets the result
+__device__ __forceinline__ double total_of(const double* part, int n) {
     double s = 0.0;
-    for (int i0 = threadIdx.x; i0 < n; i0 += 256 * 8) {
-        double t[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) t[u] = part[min(i0 + 256 * u, n - 1)];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) s += (i0 + 256 * u < n) ? t[u] : 0.0;
-    }
-    return block_sum_256(s, lds4);
+    for (int i = threadIdx.x & 63; i < n; i += 64) s += part[i];
+    return wave_sum(s);
 }
 
 __global__ __launch_bounds__(256) void resample_w_kernel(const StepParams* __restrict__ sp, ResampleArgs a) {
     __shared__ double red[4];
-    const int bi = blockIdx.y, slab = blockIdx.x * 256 + threadIdx.x;
+    const int bi = blockIdx.y, slab = blockIdx.x * 256 + threadIdx.x, nblk = a.nslab / 256;
     const int gamma = sp->gamma;
     const int n = a.nacc[bi];
-    const double Z = total_of(a.epart + (size_t)bi * a.nslab, a.nslab, red);
-    const int row = bi * (gamma + 1) + n;
-    const float mx = a.rowstat[row].x;
-    const float* l = a.logits + (size_t)row * a.V;
-    const int k0 = slab * a.slab_len, k1 = min(a.V, k0 + a.slab_len);
     double s = 0.0;
-    if (n < gamma) {
+    if (n < gamma) {                                   // uniform for the workgroup
+        const double Z = total_of(a.eblk + (size_t)bi * nblk, nblk);
+        const int row = bi * (gamma + 1) + n;
+        const float mx = a.rowstat[row].x;
+        const float* l = a.logits + (size_t)row * a.V;
+        const int k0 = slab * a.slab_len, k1 = min(a.V, k0 + a.slab_len);
         const float* q = sp->draft_probs + ((size_t)bi * gamma + n) * a.V;
         if (((a.slab_len | a.V) & 3) == 0 && (reinterpret_cast<uintptr_t>(q) & 15) == 0) {   // 16-byte loads; same order
             for (int k = k0; k < k1; k += 4) {
@@ -691,21 +696,19 @@ __global__ __launch_bounds__(256) void resample_w_kernel(const StepParams* __res
         }
     }
     a.wpart[(size_t)bi * a.nslab + slab] = s;
+    s = block_sum_256(s, red);
+    if (threadIdx.x == 0) a.wblk[(size_t)bi * nblk + blockIdx.x] = s;
 }
 
 __global__ __launch_bounds__(256) void resample_pick_kernel(const StepParams* __restrict__ sp, ResampleArgs a,
                                                             int32_t* __restrict__ len, int32_t* __restrict__ pending) {
-    __shared__ double red[4];
     __shared__ double wave_tot[4];
-    constexpr int PICK_LDS = 8192;               // slab sums staged in LDS (64 KB)
-    __shared__ double before_of[257];
     __shared__ double slab_w[256];
-    __shared__ double part_lds[PICK_LDS];
-    __shared__ int hit_slab;
-    __shared__ double hit_before;
-    const int bi = blockIdx.x;
+    __shared__ int hit_slab, last_slab;
+    __shared__ double hit_before, last_before;
+    const int bi = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const int b = sp->seq_base + bi;
-    const int gamma = sp->gamma;
+    const int gamma = sp->gamma, nblk = a.nslab / 256;
     const int n = a.nacc[bi];
     const int row = bi * (gamma + 1) + n;
     const float4 st = a.rowstat[row];
@@ -713,66 +716,69 @@ __global__ __launch_bounds__(256) void resample_pick_kernel(const StepParams* __
     if (!(a.inv_temp > 0.f)) {
         next = __float_as_int(st.z);                 // one-hot target: residual and bonus are the arg-max
     } else {
-        const double* ep = a.epart + (size_t)bi * a.nslab;
-        const double* wp = a.wpart + (size_t)bi * a.nslab;
-        const double Z = total_of(ep, a.nslab, red);
-        double W = (n < gamma) ? total_of(wp, a.nslab, red) : 0.0;
+        const double Z = total_of(a.eblk + (size_t)bi * nblk, nblk);
+        double W = (n < gamma) ? total_of(a.wblk + (size_t)bi * nblk, nblk) : 0.0;
         const bool use_e = (n == gamma) || !(W > 0.0);
-        const double* part = use_e ? ep : wp;
+        const double* part = (use_e ? a.epart : a.wpart) + (size_t)bi * a.nslab;
+        const double* blk = (use_e ? a.eblk : a.wblk) + (size_t)bi * nblk;
         if (use_e) W = Z;
-        const double target = (double)sp->uniforms[bi * (gamma + 1) + gamma] * W;
-        // exclusive scan of the slab sums in slab order: thread t owns slabs [t*per, t*per+per).  The sums
-        // are staged in LDS with coalesced loads first when they fit (a thread's own range is strided
-        // in memory: reading it directly is `per` dependent round trips)
-        const int per = a.nslab / 256;
-        const bool in_lds = a.nslab <= PICK_LDS;
-        if (in_lds) {
-            for (int i0 = threadIdx.x; i0 < a.nslab; i0 += 256 * 8) {
-                double t[8];
+        const double target = (double)sp->uniforms[(size_t)sp->step * sp->nseq + bi * (gamma + 1) + gamma] * W;
+        if (tid == 0) { hit_slab = 0x7fffffff; last_slab = -1; }
+        // level 1, every wave alike: the first workgroup sum whose range of the cumulative sum holds the target
+        int owner = -1;
+        double base = 0.0, carry = 0.0;
+        for (int i0 = 0; i0 < nblk && owner < 0; i0 += 64) {
+            const double mine = i0 + lane < nblk ? blk[i0 + lane] : 0.0;
+            double incl = mine;
 #pragma unroll
-                for (int u = 0; u < 8; ++u) t[u] = part[min(i0 + 256 * u, a.nslab - 1)];
+            for (int o = 1; o < 64; o <<= 1) {
+                const double t = __shfl_up(incl, o, 64);
+                if (lane >= o) incl += t;
+            }
+            incl += carry;
+            const double up = __shfl_up(incl, 1, 64);      // every lane takes part in the exchange
+            const double excl = lane ? up : carry;
+            const unsigned long long hit = __ballot(mine > 0.0 && target < incl);
+            // the last range with weight takes what rounding leaves above the total
+            const unsigned long long any = __ballot(mine > 0.0);
+            if (hit) {
+                owner = i0 + __builtin_ctzll(hit);
+                base = __shfl(excl, __builtin_ctzll(hit), 64);
+            } else if (i0 + 64 >= nblk && any && target == target) {
+                const int l = 63 - __builtin_clzll(any);
+                owner = i0 + l;
+                base = __shfl(excl, l, 64);
+            }
+            carry = __shfl(incl, 63, 64);
+        }
+        __syncthreads();
+        // level 2: the slab sums of that workgroup, scanned in slab order
+        if (owner >= 0) {                                // uniform
+            const double mine = part[owner * 256 + tid];
+            double incl = mine;
 #pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (i0 + 256 * u < a.nslab) part_lds[i0 + 256 * u] = t[u];
+            for (int o = 1; o < 64; o <<= 1) {
+                const double t = __shfl_up(incl, o, 64);
+                if (lane >= o) incl += t;
+            }
+            if (lane == 63) wave_tot[tid >> 6] = incl;
+            __syncthreads();
+            double before = base;
+            for (int w = 0; w < (tid >> 6); ++w) before += wave_tot[w];
+            incl += before;
+            const double up = __shfl_up(incl, 1, 64);
+            const double excl = lane ? up : before;
+            if (mine > 0.0) {
+                if (target < incl) atomicMin(&hit_slab, tid);
+                atomicMax(&last_slab, tid);
             }
             __syncthreads();
+            if (tid == hit_slab) hit_before = excl;
+            if (tid == last_slab) last_before = excl;
+            __syncthreads();
         }
-        auto slab_sum = [&](int i) { return in_lds ? part_lds[i] : part[i]; };
-        double mine = 0.0;
-        for (int i = 0; i < per; ++i) mine += slab_sum(threadIdx.x * per + i);
-        double incl = mine;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const double t = __shfl_up(incl, o, 64);
-            if ((int)(threadIdx.x & 63) >= o) incl += t;
-        }
-        if ((threadIdx.x & 63) == 63) wave_tot[threadIdx.x >> 6] = incl;
-        if (threadIdx.x == 0) { hit_slab = 0x7fffffff; hit_before = 0.0; before_of[256] = INFINITY; }
-        __syncthreads();
-        double before = incl - mine;
-        for (int w = 0; w < (int)(threadIdx.x >> 6); ++w) before += wave_tot[w];
-        before_of[threadIdx.x] = before;
-        __syncthreads();
-        // owner: the thread whose range of the cumulative sum holds the target (lowest wins a tie)
-        if (before <= target && target < before_of[threadIdx.x + 1] && mine > 0.0) atomicMin(&hit_slab, (int)threadIdx.x);
-        __syncthreads();
-        const int owner = hit_slab;
-        __syncthreads();
-        if ((int)threadIdx.x == owner) {
-            double c = before;
-            int hs = -1, last_pos = -1;
-            double hb = 0.0, last_before = 0.0;
-            for (int i = 0; i < per; ++i) {
-                const double v = slab_sum(threadIdx.x * per + i);
-                if (v > 0.0) { last_pos = threadIdx.x * per + i; last_before = c; }
-                if (c + v > target) { hs = threadIdx.x * per + i; hb = c; break; }
-                c += v;
-            }
-            if (hs < 0) { hs = last_pos; hb = last_before; }
-            hit_slab = hs;
-            hit_before = hb;
-        }
-        __syncthreads();
+        const bool have_slab = owner >= 0 && last_slab >= 0;
+        const bool in_range = hit_slab != 0x7fffffff;
         const float mx = st.x;
         const float* l = a.logits + (size_t)row * a.V;
         const float* q = (n < gamma) ? sp->draft_probs + ((size_t)bi * gamma + n) * a.V : nullptr;
@@ -780,16 +786,16 @@ __global__ __launch_bounds__(256) void resample_pick_kernel(const StepParams* __
             const double e = e_of(l[k], mx, a.inv_temp);
             return use_e ? e : fmax(0.0, e - Z * (double)q[k]);
         };
-        // the weights of the slab that holds the target, one per thread (slabs of up to 256 entries),
+        // level 3: the weights of the slab that holds the target, one per thread (slabs of up to 256 entries),
         // then scanned in vocabulary order by one thread
-        const bool have_slab = (owner != 0x7fffffff && hit_slab >= 0);
-        const int hk0 = have_slab ? hit_slab * a.slab_len : 0, hk1 = have_slab ? min(a.V, hk0 + a.slab_len) : 0;
+        const int hs = owner * 256 + (in_range ? hit_slab : last_slab);
+        const int hk0 = have_slab ? hs * a.slab_len : 0, hk1 = have_slab ? min(a.V, hk0 + a.slab_len) : 0;
         const bool staged = have_slab && a.slab_len <= 256;
-        if (staged && hk0 + (int)threadIdx.x < hk1) slab_w[threadIdx.x] = weight(hk0 + threadIdx.x);
+        if (staged && hk0 + tid < hk1) slab_w[tid] = weight(hk0 + tid);
         __syncthreads();
-        if (threadIdx.x == 0) {
+        if (tid == 0) {
             if (have_slab) {
-                double c = hit_before;
+                double c = in_range ? hit_before : last_before;
                 int last_pos = -1;
                 for (int k = hk0; k < hk1; ++k) {
                     const double v = staged ? slab_w[k - hk0] : weight(k);
@@ -799,36 +805,30 @@ __global__ __launch_bounds__(256) void resample_pick_kernel(const StepParams* __
                 }
                 if (next < 0) next = last_pos;
             }
-            if (next < 0) {            // rounding at the very top of the CDF: last token with weight
+            if (next < 0) {            // no weight anywhere the sums say: last token with weight, else the arg-max
                 for (int k = a.V - 1; k >= 0; --k)
                     if (weight(k) > 0.0) { next = k; break; }
                 if (next < 0) next = __float_as_int(st.z);
             }
         }
     }
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         sp->next_token[bi] = next;
         len[b] += 1 + n;           // commit: rows beyond the new length are dead
         pending[b] = next;
+        if (sp->emit_tokens) sp->emit_tokens[(size_t)bi * sp->emit_gamma + sp->step] = next;
     }
 }
 
-// Draft proposal (Eq. 1), output of one single-row decode: the row's next-token law q = softmax(l / T)
-// as fp32 probabilities into column j of draft_probs [nseq][gamma][V], and the token just drawn from it
-// (the sequence's new pending token) into draft_tokens [nseq][gamma].  T = 0: one-hot at the arg-max.
-__global__ __launch_bounds__(256) void draft_emit_kernel(int V, float inv_temp, const float* __restrict__ logits,
-                                                         const float4* __restrict__ rowstat,
-                                                         const int32_t* __restrict__ pending, int seq_base, int gamma, int j,
-                                                         int32_t* __restrict__ draft_tokens, float* __restrict__ draft_probs) {
+// Draft proposal (Eq. 1) at T = 0: the row's next-token law, one-hot at the arg-max, into column `step` of draft_probs
+// [nseq][gamma][V].  (T > 0: pass 1 of the draw writes it; the token is written with the state in either case.)
+__global__ __launch_bounds__(256) void draft_onehot_kernel(const StepParams* __restrict__ sp, int V, const float4* __restrict__ rowstat) {
     const int bi = blockIdx.y;
-    const float4 st = rowstat[bi];
-    const float* l = logits + (size_t)bi * V;
-    float* q = draft_probs + ((size_t)bi * gamma + j) * V;
-    const float invz = 1.0f / st.y;
-    const int arg = __float_as_int(st.z);
-    for (int k = blockIdx.x * 256 + threadIdx.x; k < V; k += gridDim.x * 256)
-        q[k] = (inv_temp > 0.f) ? expf((l[k] - st.x) * inv_temp) * invz : (k == arg ? 1.f : 0.f);
-    if (blockIdx.x == 0 && threadIdx.x == 0) draft_tokens[bi * gamma + j] = pending[seq_base + bi];
+    float* q = sp->emit_probs;
+    if (!q) return;
+    q += ((size_t)bi * sp->emit_gamma + sp->step) * V;
+    const int arg = __float_as_int(rowstat[bi].z);
+    for (int k = blockIdx.x * 256 + threadIdx.x; k < V; k += gridDim.x * 256) q[k] = k == arg ? 1.f : 0.f;
 }
 
 // Teacher-forced scoring (Sec. 3.3, the terms of Eq. 7): log-probability of a given next token under every

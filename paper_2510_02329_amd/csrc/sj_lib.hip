@@ -121,12 +121,11 @@ struct sj_kv : Forward {       // the inherited buffers serve the blocks of up t
     unsigned* tickets = nullptr;
     float4 *stats = nullptr, *rowstat = nullptr;
     int32_t *bits = nullptr, *nacc = nullptr, *draft_tok = nullptr;
-    double *epart = nullptr, *wpart = nullptr;
+    double *epart = nullptr, *wpart = nullptr, *eblk = nullptr, *wblk = nullptr;
     int chunk_keys = 64, nchunk_max = 1, nslab = 0, slab_len = 0;
     GemmPlan plan_qkv[2], plan_o[2], plan_d[2];   // [0]: few-row kernel (at most 32 rows), [1]: more
     GemmPlan plan_gu;                             // gate / up projection with few rows (no K-slices)
     GemmPlan plan_lm{8, 4, 1, 2};                 // LM head with few rows: nt in {4, 8}, waves in {4, 8}
-    int lm_nt = 2;
     int mode = SJ_MODE_TWO_STAGE;
     int ring_rows = RING_PACK_ROWS;       // the rules take the LDS-ring kernel up to this many rows
     int planes = 2;            // bf16 planes of the activation operand (fp32 storage: always 1)
@@ -493,7 +492,6 @@ extern "C" int sj_kv_create(const sj_model* m, int32_t batch, const int32_t* cap
     ALLOC(kv->sp_dev, sizeof(StepParams));
     ALLOC(kv->hn32, (size_t)R * d * 4);
     ALLOC(kv->logits, (size_t)R * V * 4);
-    kv->lm_nt = 2;
     ALLOC(kv->stats, (size_t)R * (V / 16) * sizeof(float4));
     ALLOC(kv->rowstat, (size_t)R * sizeof(float4));
     ALLOC(kv->scores, (size_t)R * 4);
@@ -510,6 +508,8 @@ extern "C" int sj_kv_create(const sj_model* m, int32_t batch, const int32_t* cap
     }
     ALLOC(kv->epart, (size_t)batch * kv->nslab * 8);
     ALLOC(kv->wpart, (size_t)batch * kv->nslab * 8);
+    ALLOC(kv->eblk, (size_t)batch * (kv->nslab / 256) * 8);
+    ALLOC(kv->wblk, (size_t)batch * (kv->nslab / 256) * 8);
     if (c.n_layers == 0) ALLOC(kv->xn, (size_t)3 * kv->rpad * d * m->esz);          // up to three operand planes
     if (c.n_layers > 0) {
         const int hd = c.head_dim, Nq = c.n_q_heads * hd, Nk = c.n_kv_heads * hd, F = c.d_ffn;
@@ -1265,7 +1265,7 @@ static int tune_plans(sj_kv* kv, int rows) {
 }
 
 // More rows: groups of at most 144 rows (9 MFMA row tiles) through the loader-wave kernel; the statistics
-// of EPI_LOGITS are per n-tile there ([rows][N/16]).
+// of EPI_LOGITS are per workgroup (of 8 n-tiles) there, per n-tile with three operand planes.
 template <typename T, int EPI, int SPL>
 static int gemm_rows(hipStream_t st, const void* Wt, const void* X, size_t xplane, int ldx, int K, int N, int rows, int split,
                      float* out, void* act, size_t actplane, float4* stats, float inv_temp, bool tiled) {
@@ -1303,8 +1303,10 @@ static int gemm_rows(hipStream_t st, const void* Wt, const void* X, size_t xplan
         const int per = seven ? 7 : R2_NT, ngroups = (ntiles + per - 1) / per;
         const int gx = rgroups > 1 ? (ngroups + 7) / 8 * 8 * rgroups : ngroups;
         const dim3 grid(gx, EPI == EPI_PARTIAL ? split : 1);
-        if (seven) gemm_rows8_kernel<T, EPI, SPL, 7, RT><<<grid, (R8_CW + R4_LW) * 64, 0, st>>>(a, mt);
-        else gemm_rows8_kernel<T, EPI, SPL, R2_NT, RT><<<grid, (R8_CW + R4_LW) * 64, 0, st>>>(a, mt);
+        if constexpr (EPI == EPI_SWIGLU) {
+            if (seven) gemm_rows8_kernel<T, EPI, SPL, 7, RT><<<grid, (R8_CW + R4_LW) * 64, 0, st>>>(a, mt);
+        }
+        if (!seven) gemm_rows8_kernel<T, EPI, SPL, R2_NT, RT><<<grid, (R8_CW + R4_LW) * 64, 0, st>>>(a, mt);
         LAUNCHCHK("gemm_rows");
     } else {
         for (int row0 = 0; row0 < rows; row0 += group_rows) {
@@ -1510,7 +1512,7 @@ struct Runner {
             rc = exact_operand
                 ? gemm_rows<T, EPI_LOGITS, 1>(st, m->lm_head, w->xn, plane(md.d), md.d, md.d, md.V, R, 1, kv->logits, nullptr, 0, kv->stats, md.inv_temp, true)
                 : gemm_rows<T, EPI_LOGITS, SPL>(st, m->lm_head, w->xn, plane(md.d), md.d, md.d, md.V, R, 1, kv->logits, nullptr, 0, kv->stats, md.inv_temp, tiled());
-            nblk = md.V / 16;
+            nblk = exact_operand || SPL <= 2 ? md.V / 16 / R2_NT : md.V / 16;      // gemm_rows8: per workgroup; gemm_rows2: per n-tile
         } else {
             rc = exact_operand
                 ? few_logits<T, 1>(kv->plan_lm, st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, kv->logits, kv->stats, md.inv_temp)
@@ -1549,6 +1551,7 @@ struct Runner {
         ResampleArgs ra{};
         ra.V = md.V; ra.nslab = kv->nslab; ra.slab_len = kv->slab_len; ra.inv_temp = md.inv_temp;
         ra.logits = kv->logits; ra.rowstat = kv->rowstat; ra.nacc = kv->nacc; ra.epart = kv->epart; ra.wpart = kv->wpart;
+        ra.eblk = kv->eblk; ra.wblk = kv->wblk;
         if (md.inv_temp > 0.f) {
             dim3 g(kv->nslab / 256, nseq);
             scan_resample_e_kernel<<<g, 256, 0, st>>>(kv->sp_dev, ra, kv->scores, kv->p_at_d, kv->bits, kv->nacc, kv->ranks);
@@ -1561,6 +1564,10 @@ struct Runner {
             accept_scan_kernel<<<nseq, 64, 0, st>>>(kv->sp_dev, md.V, md.inv_temp, kv->logits, kv->rowstat, kv->scores, kv->p_at_d,
                                                      kv->bits, kv->nacc, kv->ranks);
             LAUNCHCHK("accept_scan");
+        }
+        if (gamma == 0 && !(md.inv_temp > 0.f)) {          // a draft block's decode step: its law (T > 0: written by pass 1)
+            draft_onehot_kernel<<<dim3(std::min(64, (md.V + 255) / 256), nseq), 256, 0, st>>>(kv->sp_dev, md.V, kv->rowstat);
+            LAUNCHCHK("draft_onehot");
         }
         resample_pick_kernel<<<nseq, 256, 0, st>>>(kv->sp_dev, ra, kv->len_dev, kv->pending_dev);
         LAUNCHCHK("resample_pick");
@@ -1588,29 +1595,21 @@ static int enqueue_step(sj_model* m, sj_kv* kv, int gamma, hipStream_t st, bool 
     return run.tail(gamma, gamma > 0);
 }
 
-// The full step is ~200 dependent launches of a few microseconds each: it is captured once per
-// (gamma, planes) into a launch graph and replayed; only the per-call parameter block, written by a
-// tiny kernel in front of the replay, changes between calls.
-template <typename T, int SPL>
-static int verify_step_impl(sj_model* m, sj_kv* kv, int gamma, const StepParams& p, hipStream_t st, bool head_only,
-                            const void* hidden) {
-    int rc;
-    const bool graph = kv->use_graph && !head_only && kv->timing_class == 0;
-    if (!graph) {
-        if ((rc = set_params(kv, st, p))) return rc;
-        return enqueue_step<T, SPL>(m, kv, gamma, st, head_only, hidden);
-    }
+// Launches what `enqueue` puts on a stream, from a launch graph captured once per key: a forward is ~200 dependent launches of a few
+// microseconds each.  Only the per-call parameter block, written by a tiny kernel in front of the replay, changes between calls.
+template <typename Enqueue>
+static int replay(const sj_model* m, sj_kv* kv, int key, hipStream_t st, Enqueue enqueue) {
+    if (!kv->use_graph || kv->timing_class != 0) return enqueue(st);
     if (kv->graph_gen != m->temp_gen) {                        // the temperature changed: the graphs hold the old one
         for (auto& g : kv->graphs) (void)hipGraphExecDestroy(g.second);
         kv->graphs.clear();
         kv->graph_gen = m->temp_gen;
     }
-    const int key = gamma * 4 + SPL;
     auto it = kv->graphs.find(key);
     if (it == kv->graphs.end()) {
         if (!kv->cap_stream) HIPCHK(hipStreamCreateWithFlags(&kv->cap_stream, hipStreamNonBlocking));
         HIPCHK(hipStreamBeginCapture(kv->cap_stream, hipStreamCaptureModeRelaxed));
-        rc = enqueue_step<T, SPL>(m, kv, gamma, kv->cap_stream, false, nullptr);
+        const int rc = enqueue(kv->cap_stream);
         hipGraph_t g = nullptr;
         hipError_t e = hipStreamEndCapture(kv->cap_stream, &g);
         if (rc) { if (g) (void)hipGraphDestroy(g); return rc; }
@@ -1621,9 +1620,18 @@ static int verify_step_impl(sj_model* m, sj_kv* kv, int gamma, const StepParams&
         if (e != hipSuccess) return fail(SJ_EHIP, "hipGraphInstantiate failed: %s", hipGetErrorString(e));
         it = kv->graphs.emplace(key, ex).first;
     }
-    if ((rc = set_params(kv, st, p))) return rc;
     HIPCHK(hipGraphLaunch(it->second, st));
     return SJ_OK;
+}
+constexpr int FEED_KEY = 64 * 4;                               // keys below: gamma * 4 + planes, gamma <= 63
+
+template <typename T, int SPL>
+static int verify_step_impl(sj_model* m, sj_kv* kv, int gamma, const StepParams& p, hipStream_t st, bool head_only,
+                            const void* hidden) {
+    const int rc = set_params(kv, st, p);
+    if (rc) return rc;
+    if (head_only) return enqueue_step<T, SPL>(m, kv, gamma, st, true, hidden);
+    return replay(m, kv, gamma * 4 + SPL, st, [&](hipStream_t s) { return enqueue_step<T, SPL>(m, kv, gamma, s, false, nullptr); });
 }
 
 static int dispatch_step(sj_model* m, sj_kv* kv, int gamma, const StepParams& p, hipStream_t st, bool head_only,
@@ -1725,15 +1733,25 @@ extern "C" int sj_verify_step(sj_model* m, sj_kv* kv, int32_t gamma, const int32
     return SJ_OK;
 }
 
-// Layers only (no LM head, no decisions) over one row per sequence, then the rows are kept.
+// gamma decode steps - each a verification step without draft tokens: the "all accepted" token is drawn from the row's distribution
+// with the step's uniform and becomes the pending token, length += 1 - and, with feed_last, the layers alone (no LM head, no
+// decisions) over the last token, whose rows are kept.  The parameters are written once: the steps count themselves, and write
+// their column of the block's outputs (a launch between two replays cost a gap of 8 us before and after it, and the layers of the
+// last token, launched one by one, 0.4 ms of a 5 ms block).
 template <typename T, int SPL>
-static int feed_pending_impl(sj_model* m, sj_kv* kv, hipStream_t st) {
-    Runner<T, SPL> run{m, kv, st, kv->batch, 1, kv->batch};
-    int rc = run.layers();
-    if (rc) return rc;
-    advance_len_kernel<<<(kv->batch + 63) / 64, 64, 0, st>>>(kv->sp_dev, kv->len_dev);
-    LAUNCHCHK("advance_len");
-    return SJ_OK;
+static int draft_block_impl(sj_model* m, sj_kv* kv, int gamma, bool feed_last, const StepParams& p, hipStream_t st) {
+    int rc = set_params(kv, st, p);
+    for (int j = 0; j < gamma && !rc; ++j)
+        rc = replay(m, kv, SPL, st, [&](hipStream_t s) { return enqueue_step<T, SPL>(m, kv, 0, s, false, nullptr); });
+    if (rc || !feed_last) return rc;
+    return replay(m, kv, FEED_KEY + SPL, st, [&](hipStream_t s) -> int {
+        Runner<T, SPL> run{m, kv, s, kv->batch, 1, kv->batch};
+        const int rc2 = run.layers();
+        if (rc2) return rc2;
+        advance_len_kernel<<<(kv->batch + 63) / 64, 64, 0, s>>>(kv->sp_dev, kv->len_dev);
+        LAUNCHCHK("advance_len");
+        return SJ_OK;
+    });
 }
 
 extern "C" int sj_draft_block(sj_model* m, sj_kv* kv, int32_t gamma, const float* uniforms, int32_t feed_last,
@@ -1750,30 +1768,17 @@ extern "C" int sj_draft_block(sj_model* m, sj_kv* kv, int32_t gamma, const float
         if (kv->len_upper[b] + need > kv->cap[b])
             return fail(SJ_ECAPACITY, "sequence %d: len %d + %d rows exceeds capacity %d", b, kv->len_upper[b], need, kv->cap[b]);
     hipStream_t st = (hipStream_t)stream;
-    const int V = m->cfg.vocab;
-    for (int j = 0; j < gamma; ++j) {
-        // one decode step = a verification step without draft tokens: the "all accepted" token is drawn from
-        // the row's distribution with the step's uniform and becomes the pending token; length += 1
-        StepParams p{};
-        p.nseq = kv->batch; p.seq_base = 0; p.rps = 1; p.gamma = 0; p.tok_mode = 0; p.mode = kv->mode; p.topk = kv->topk;
-        p.theta = 0.5f;
-        p.draft_tokens = nullptr; p.draft_probs = nullptr; p.uniforms = uniforms + (size_t)j * kv->batch;
-        p.accepted_len = kv->nacc; p.next_token = kv->draft_tok;   // scratch: the token is read back from the state
-        if ((rc = dispatch_step(m, kv, 0, p, st, false, nullptr))) return rc;
-        draft_emit_kernel<<<dim3(std::min(64, (V + 255) / 256), kv->batch), 256, 0, st>>>(V, m->md.inv_temp, kv->logits, kv->rowstat,
-                                                                                          kv->pending_dev, 0, gamma, j, draft_tokens, draft_probs);
-        LAUNCHCHK("draft_emit");
-    }
-    if (feed_last) {
-        StepParams p{};
-        p.nseq = kv->batch; p.seq_base = 0; p.rps = 1; p.gamma = 0; p.tok_mode = 0; p.mode = kv->mode; p.topk = kv->topk;
-        if ((rc = set_params(kv, st, p))) return rc;
-        if (m->cfg.dtype == SJ_DTYPE_FP32) rc = feed_pending_impl<float, 1>(m, kv, st);
-        else if (kv->planes == 1) rc = feed_pending_impl<bf16_t, 1>(m, kv, st);
-        else if (kv->planes == 3) rc = feed_pending_impl<bf16_t, 3>(m, kv, st);
-        else rc = feed_pending_impl<bf16_t, 2>(m, kv, st);
-        if (rc) return rc;
-    }
+    StepParams p{};
+    p.nseq = kv->batch; p.seq_base = 0; p.rps = 1; p.gamma = 0; p.tok_mode = 0; p.mode = kv->mode; p.topk = kv->topk;
+    p.theta = 0.5f;
+    p.draft_tokens = nullptr; p.draft_probs = nullptr; p.uniforms = uniforms;
+    p.accepted_len = kv->nacc; p.next_token = kv->draft_tok;       // scratch: the tokens go to emit_tokens and the state
+    p.emit_gamma = gamma; p.emit_tokens = draft_tokens; p.emit_probs = draft_probs;
+    if (m->cfg.dtype == SJ_DTYPE_FP32) rc = draft_block_impl<float, 1>(m, kv, gamma, feed_last != 0, p, st);
+    else if (kv->planes == 1) rc = draft_block_impl<bf16_t, 1>(m, kv, gamma, feed_last != 0, p, st);
+    else if (kv->planes == 3) rc = draft_block_impl<bf16_t, 3>(m, kv, gamma, feed_last != 0, p, st);
+    else rc = draft_block_impl<bf16_t, 2>(m, kv, gamma, feed_last != 0, p, st);
+    if (rc) return rc;
     for (int b = 0; b < kv->batch; ++b) kv->len_upper[b] += need;
     kv->last_gamma = 0;
     kv->last_rows = kv->batch;
@@ -1835,6 +1840,7 @@ extern "C" int sj_verify_head(sj_model* m, sj_kv* kv, int32_t gamma, const void*
     p.theta = judge_threshold;
     p.draft_tokens = draft_tokens; p.draft_probs = draft_probs; p.uniforms = uniforms;
     p.accepted_len = accepted_len; p.next_token = next_token;
+    p.step = 0;
     hipStream_t st = (hipStream_t)stream;
     rc = dispatch_step(m, kv, gamma, p, st, true, hidden);
     if (rc) return rc;
@@ -1919,6 +1925,9 @@ extern "C" int sj_verify_head_static(sj_model* m, int32_t batch, int32_t gamma, 
     kv.nacc = (int32_t*)take((size_t)batch * 4);
     kv.epart = (double*)take((size_t)batch * kv.nslab * 8);
     kv.wpart = (double*)take((size_t)batch * kv.nslab * 8);
+    // the few-row LM head leaves one statistic per 8 n-tiles: the workgroup sums of the draw take the rest of `stats`
+    kv.eblk = (double*)(kv.stats + (size_t)R * (V / 128));
+    kv.wblk = kv.eblk + (size_t)batch * (kv.nslab / 256);
     if (!fits)
         return fail(SJ_EINVAL, "%lld rows of vocabulary %d, width %d need more than the %zu bytes of the static workspace", (long long)R, V, d,
                     SJ_STATIC_BYTES);
@@ -1931,6 +1940,7 @@ extern "C" int sj_verify_head_static(sj_model* m, int32_t batch, int32_t gamma, 
     p.theta = judge_threshold;
     p.draft_tokens = draft_tokens; p.draft_probs = draft_probs; p.uniforms = uniforms;
     p.accepted_len = accepted_len; p.next_token = next_token;
+    p.step = 0;
     return dispatch_step(m, &kv, gamma, p, st, true, hidden);
 }
 

@@ -22,6 +22,11 @@ struct StepParams {
     int32_t* accepted_len;         // [nseq]
     int32_t* next_token;           // [nseq]
     const int32_t* prefill_tokens; // [rps] (tok_mode 1)
+    int32_t step = -1;             // forwards since the parameters were set, counted by a forward's first kernel (a head-only
+                                   // call has none: 0)
+    int32_t emit_gamma;            // draft block: columns of emit_tokens / emit_probs
+    int32_t* emit_tokens;          // draft block: [nseq, emit_gamma], column `step`
+    float* emit_probs;             // draft block: [nseq, emit_gamma, V]
 };
 
 struct ModelDims {
