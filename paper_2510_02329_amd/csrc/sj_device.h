@@ -153,16 +153,15 @@ __device__ __forceinline__ void st_coh(unsigned long long* p, unsigned long long
 __device__ __forceinline__ unsigned ld_coh(const unsigned* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ float ld_coh(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-// Element offset of operand element (row, k) inside one plane.  tks == 0: row-major with leading dimension ld.
-// tks > 0 (= K / KSTEP): the plane is stored in blocks of one MFMA fragment, [row tile][k-step][16 rows][KSTEP
-// elements]: the 1 KB that the many-row GEMM moves into LDS with one load instruction is consecutive memory (lane
-// 16 g + r of that load reads the 16 bytes at row r, element g * KF of the block), where a row-major fragment
-// touches 16 cache lines and uses half of each; a producer still writes a row's KSTEP elements contiguously.
+// Element offset of operand element (row, k) inside one plane of rows of width K.  A plane is stored in blocks of one MFMA
+// fragment, [row tile][k-step][4 lane groups][16 rows][KF elements]: lane 16 g + r's 16 bytes of a fragment sit at lane * 16, like the
+// re-tiled weights.  A wave's load of a fragment is then 1 KB that four neighbouring lanes at a time read from one 64-byte
+// piece; with row-major planes, or rows side by side inside the block, neighbouring lanes are in different rows and
+// the vector cache looks up every lane's 16 bytes by itself (64 look-ups a load instead of 16).
 template <typename T>
-__device__ __forceinline__ size_t opnd_off(int row, int k, int ld, int tks) {
-    constexpr int KSTEP = Traits<T>::KSTEP;
-    if (tks == 0) return (size_t)row * ld + k;
-    return (((size_t)(row >> 4) * tks + k / KSTEP) * 16 + (row & 15)) * KSTEP + (k % KSTEP);
+__device__ __forceinline__ size_t opnd_off(int row, int k, int K) {
+    constexpr int KF = Traits<T>::KF, KSTEP = Traits<T>::KSTEP;
+    return ((((size_t)(row >> 4) * (K / KSTEP) + k / KSTEP) * 4 + (k % KSTEP) / KF) * 16 + (row & 15)) * KF + k % KF;
 }
 
 // Workgroup barrier that waits for this wave's LDS traffic only.  __syncthreads() also waits for every

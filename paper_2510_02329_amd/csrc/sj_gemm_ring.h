@@ -19,9 +19,7 @@
 // PACK (two operand planes, at most 8 rows): MFMA row r < 8 of the B operand carries plane 0 of row r,
 // row r + 8 plane 1 of the same row, so ONE product per weight fragment yields both planes' contributions
 // in output columns r and r + 8, which the reduction adds (hi first).  Without PACK one product per plane.
-// The operand of such a block is stored that way, too (packed planes: [k-step][16 rows][KSTEP], plane 1 in rows 8 - 15): a fragment is
-// 1 KB of consecutive memory instead of halves of twelve cache lines, which counts where a workgroup has one n-tile and
-// reads as much operand as weights.
+// The operand of such a block is stored that way, too (packed planes: one plane whose rows 8 - 15 are plane 1).
 #pragma once
 #include "sj_kernels.h"
 
@@ -94,17 +92,10 @@ __global__ __launch_bounds__(RING_THREADS) void gemm_ring_kernel(GemmArgs a) {
 
     // ---------------- compute waves ----------------
     constexpr int NB = PACK ? 1 : SPL;                 // operand fragments (products) per weight fragment
+    // fragment of k-step ks0 + w; packed planes are one plane of 16 rows.  Rows past R are read (stale) and never stored.
     const T* Xr[NB];
-    if constexpr (PACK) {
-        const int row = r & 7;
-        Xr[0] = reinterpret_cast<const T*>(a.X) + (size_t)(r >> 3) * a.xplane + (size_t)(row < a.R ? row : 0) * a.ldx +
-                (size_t)(ks0 + w) * a.kstride + g * KF;
-    } else {
 #pragma unroll
-        for (int sp = 0; sp < NB; ++sp)
-            Xr[sp] = reinterpret_cast<const T*>(a.X) + (size_t)sp * a.xplane + (size_t)(r < a.R ? r : 0) * a.ldx +
-                     (size_t)(ks0 + w) * a.kstride + g * KF;
-    }
+    for (int sp = 0; sp < NB; ++sp) Xr[sp] = reinterpret_cast<const T*>(a.X) + (size_t)sp * a.xplane + ((size_t)(ks0 + w) * 64 + lane) * KF;
     f32x4 acc[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -114,7 +105,7 @@ __global__ __launch_bounds__(RING_THREADS) void gemm_ring_kernel(GemmArgs a) {
     Frag fb[DB][NB];
     auto load_b = [&](Frag (&f)[NB], int kb) {
 #pragma unroll
-        for (int sp = 0; sp < NB; ++sp) f[sp].u = *reinterpret_cast<const u32x4*>(Xr[sp] + (size_t)kb * (RING_CW * a.kstride));
+        for (int sp = 0; sp < NB; ++sp) f[sp].u = *reinterpret_cast<const u32x4*>(Xr[sp] + (size_t)kb * (RING_CW * 16 * KSTEP));
     };
     // what the epilogue needs from memory, requested (and the row factors finished) while the first stage is on its way
     f32x4 res_x = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -186,7 +177,7 @@ __global__ __launch_bounds__(RING_THREADS) void gemm_ring_kernel(GemmArgs a) {
                 float y[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) { y[i] = xv[i] * res_g[i]; ss += xv[i] * xv[i]; }
-                Traits<T>::template store_split4<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, col, a.N, a.act_tks), a.actplane, y);
+                Traits<T>::template store_split4<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, col, a.N), a.actplane, y);
             }
             ss += __shfl_xor(ss, 1, 64);
             ss += __shfl_xor(ss, 2, 64);
@@ -205,7 +196,7 @@ __global__ __launch_bounds__(RING_THREADS) void gemm_ring_kernel(GemmArgs a) {
                 float y[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) y[i] = v[i] / (1.0f + expf(-v[i])) * up[i];
-                Traits<T>::template store_split4<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, (nt0 + t) * 8 + n0, a.N / 2, a.act_tks), a.actplane, y);
+                Traits<T>::template store_split4<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, (nt0 + t) * 8 + n0, a.N / 2), a.actplane, y);
             }
         }
         return;

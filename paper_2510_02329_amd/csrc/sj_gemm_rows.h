@@ -87,7 +87,7 @@ __device__ __forceinline__ void rows_epilogue_tile(const GemmArgs& a, const f32x
             y[e] = gate / (1.0f + expf(-gate)) * up;
         }
         if (valid && g < 2)
-            Traits<T>::store_split4(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, nt * 8 + 4 * g, a.N / 2, a.act_tks), a.actplane, y);
+            Traits<T>::store_split4(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, nt * 8 + 4 * g, a.N / 2), a.actplane, y);
     } else {
         // logits + this tile's softmax partial of the row
         const float4 st = rows_softmax_stat<1>(&v, nt, 1, a.inv_temp, g);
@@ -163,12 +163,12 @@ __global__ __launch_bounds__((R2_CW + R2_LW) * 64) void gemm_rows2_kernel(GemmAr
     }
 
     // ---------------- compute waves ----------------
-    // row tiles of this wave and their operand rows (rows past R re-read row 0; never stored)
+    // row tiles of this wave (tiles past the rows re-read tile 0; rows past R are stale; neither is stored)
     const T* Xr[R2_MTW];
 #pragma unroll
     for (int i = 0; i < R2_MTW; ++i) {
-        const int row = (w + R2_CW * i) * 16 + r;
-        Xr[i] = reinterpret_cast<const T*>(a.X) + (size_t)(row < a.R ? row : 0) * a.ldx + (size_t)ks0 * KSTEP + g * KF;
+        const int m = (w + R2_CW * i) * 16 < a.R ? w + R2_CW * i : 0;
+        Xr[i] = reinterpret_cast<const T*>(a.X) + (((size_t)m * KS + ks0) * 64 + lane) * KF;
     }
     const int my_tiles = (mt > w) ? (mt - w + R2_CW - 1) / R2_CW : 0;     // row tiles w, w+4, .. below mt
 
@@ -180,7 +180,7 @@ __global__ __launch_bounds__((R2_CW + R2_LW) * 64) void gemm_rows2_kernel(GemmAr
 
     Frag bq[R2_RING][R2_MTW][SPL];
     auto load_b = [&](int slot, int kk) {
-        const size_t k = (size_t)min(kk, nks - 1) * KSTEP;
+        const size_t k = (size_t)min(kk, nks - 1) * (16 * KSTEP);
 #pragma unroll
         for (int i = 0; i < R2_MTW; ++i)
 #pragma unroll
@@ -271,7 +271,7 @@ __global__ __launch_bounds__((R8_CW + R4_LW) * 64) void gemm_rows8_kernel(GemmAr
         bx = (j / a.rgroups) * 8 + xcd;
         if (bx * NT >= ntiles) return;                 // padding of the grid to whole XCD rounds (uniform)
         const int row0 = rg * (RT * 16), nr = min(RT * 16, a.R - row0);
-        a.X = reinterpret_cast<const char*>(a.X) + (size_t)row0 * a.ldx * sizeof(T);
+        a.X = reinterpret_cast<const char*>(a.X) + (size_t)row0 * a.K * sizeof(T);
         if (EPI == EPI_SWIGLU) a.act = reinterpret_cast<char*>(a.act) + (size_t)row0 * (a.N / 2) * sizeof(T);
         else a.out += (size_t)row0 * a.N;
         if (EPI == EPI_LOGITS) a.stats += (size_t)row0 * ((ntiles + NT - 1) / NT);
@@ -334,15 +334,9 @@ __global__ __launch_bounds__((R8_CW + R4_LW) * 64) void gemm_rows8_kernel(GemmAr
                 const int it = min(x + 2 * j, NX - 1);
                 const int m = it / SPL, p = it % SPL;
                 const T* plane = reinterpret_cast<const T*>(a.X) + (size_t)p * a.xplane;
-                if (a.x_tks) {
-                    const size_t mt_ok = m * 16 < a.R ? m : 0;
-                    sp = reinterpret_cast<const char*>(plane + ((mt_ok * a.x_tks + ks0) * 16 + r) * KSTEP + g * KF);
-                    st = (size_t)16 * KSTEP * sizeof(T);
-                } else {
-                    const int row = m * 16 + r;
-                    sp = reinterpret_cast<const char*>(plane + (size_t)(row < a.R ? row : 0) * a.ldx + (size_t)ks0 * KSTEP + g * KF);
-                    st = (size_t)KSTEP * sizeof(T);
-                }
+                const size_t mt_ok = m * 16 < a.R ? m : 0;
+                sp = reinterpret_cast<const char*>(plane + ((mt_ok * KS + ks0) * 64 + lane) * KF);
+                st = 1024;
             };
             auto dst_of = [&](int buf, int j) { return &Xst[buf][min(x + 2 * j, NX - 1)][0]; };
             run(std::integral_constant<int, (NX + 1) / 2>{}, std::integral_constant<int, R4_NSX>{}, std::integral_constant<int, 0>{}, make_src, dst_of);

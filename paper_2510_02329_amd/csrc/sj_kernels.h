@@ -63,11 +63,11 @@ __global__ void kv_gather_kernel(T* __restrict__ kdst, T* __restrict__ vdst, con
 // reads (opnd_off), and their fp32 copy for the judge.  One thread per 4 consecutive columns.
 template <typename T>
 __global__ __launch_bounds__(256) void hidden_in_kernel(const T* __restrict__ src, T* __restrict__ xn, float* __restrict__ hn32,
-                                                        int R, int d, int tks) {
+                                                        int R, int d) {
     const size_t n4 = (size_t)R * d / 4;
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += (size_t)gridDim.x * blockDim.x) {
         const int row = (int)(i / (d / 4)), k = (int)(i % (d / 4)) * 4;
-        T* out = xn + opnd_off<T>(row, k, d, tks);
+        T* out = xn + opnd_off<T>(row, k, d);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const T v = src[(size_t)row * d + k + e];
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(1024) void step_begin_kernel(StepParams* __restrict
                                                           const int32_t* __restrict__ pending, float* __restrict__ x,
                                                           float* __restrict__ cs, int32_t* __restrict__ row_tok,
                                                           double log_base, const T* __restrict__ gain, T* __restrict__ xn,
-                                                          size_t xplane, int tks) {
+                                                          size_t xplane) {
     __shared__ float red[16];
     const int r = blockIdx.x;
     const int rps = sp->rps;
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(1024) void step_begin_kernel(StepParams* __restrict
             float y[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) y[i] = v[p][i] * inv * Traits<T>::load(gain + c + i);
-            Traits<T>::template store_split4<SPL>(xn + opnd_off<T>(r, c, md.d, tks), xplane, y);
+            Traits<T>::template store_split4<SPL>(xn + opnd_off<T>(r, c, md.d), xplane, y);
         }
     }
 }
@@ -160,7 +160,7 @@ template <typename T, int PB, int SPL>
 __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(int R, int d, float eps, float* __restrict__ x,
                                                            const float* __restrict__ part, int nparts,
                                                            const T* __restrict__ gain, T* __restrict__ xn,
-                                                           size_t xplane, float* __restrict__ xn32, int tks) {
+                                                           size_t xplane, float* __restrict__ xn32) {
     // one workgroup of 1024 threads per row, 4 columns per thread and pass; all loads of a pass are
     // independent.  Rows wider than 16384 columns are not supported (host-checked).
     constexpr int MAXP = 4;
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(int R, int d, float e
             float y[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) y[i] = v[p][i] * inv * Traits<T>::load(gain + c + i);
-            Traits<T>::template store_split4<SPL>(xn + opnd_off<T>(r, c, d, tks), xplane, y);
+            Traits<T>::template store_split4<SPL>(xn + opnd_off<T>(r, c, d), xplane, y);
             if (xn32) *reinterpret_cast<f32x4*>(xn32 + (size_t)r * d + c) = f32x4{y[0], y[1], y[2], y[3]};
         }
     }
@@ -222,18 +222,15 @@ enum { EPI_PARTIAL = 0, EPI_SWIGLU = 1, EPI_LOGITS = 2, EPI_RESID = 3 };
 
 struct GemmArgs {
     const void* Wt;     // tiled weights
-    const void* X;      // [SPL planes][MT*16][ldx] storage dtype, rows >= R are padding
+    const void* X;      // [SPL planes] of fragments (opnd_off), storage dtype; rows >= R are padding
     size_t xplane;      // elements between consecutive planes of X
     size_t actplane;    // same for act
-    int32_t ldx, K, N, R;
-    int32_t kstride;    // few-row kernels: elements between consecutive k-steps of an operand row (KSTEP in a row-major plane)
+    int32_t K, N, R;
     int32_t slice_rows; // EPI_PARTIAL: rows between consecutive K-slices of out (>= R)
     float* out;         // EPI_PARTIAL: [gridDim.y][slice_rows][N] fp32;  EPI_LOGITS: [R][N] fp32
-    void* act;          // EPI_SWIGLU: [MT*16][N/2] storage dtype = silu(gate) * up
+    void* act;          // EPI_SWIGLU: planes of rows of width N/2 (opnd_off), storage dtype = silu(gate) * up
     float4* stats;      // EPI_LOGITS: [R][gridDim.x] (max, sum exp((l-max)/T), argmax as float bits, 0)
     float inv_temp;     // 1/T, 0 when T = 0
-    int32_t x_tks;      // 0: X planes are row-major; else K / KSTEP: fragment-tiled planes (opnd_off)
-    int32_t act_tks;    // same for act (its K is N/2)
     int32_t rgroups;    // many-row kernel: row groups of one launch (0 or 1: the launch is one group of R rows); with
                         // more, R is the total row count and every workgroup derives its group's rows and pointers
     const float* ss_in; // few-row kernels: null, or [R][K / 16] shares of the rows' sums of squares: the operand lacks 1/rms
@@ -268,7 +265,7 @@ __device__ __forceinline__ void few_epilogue(const GemmArgs& a, const float (&v)
             if (row < a.R) {
                 xv = a.x[(size_t)row * a.N + col] + v[t];
                 a.x[(size_t)row * a.N + col] = xv;
-                Traits<T>::template store_split<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, col, a.N, a.act_tks), a.actplane,
+                Traits<T>::template store_split<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, col, a.N), a.actplane,
                                                      xv * Traits<T>::load(reinterpret_cast<const T*>(a.gain) + col));
             }
             float ss = xv * xv;
@@ -290,7 +287,7 @@ __device__ __forceinline__ void few_epilogue(const GemmArgs& a, const float (&v)
             if (row < a.R && en < 8) {
                 const float gate = v[t];
                 const float y = gate / (1.0f + expf(-gate)) * up;
-                Traits<T>::template store_split<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, (nt0 + t) * 8 + en, a.N / 2, a.act_tks),
+                Traits<T>::template store_split<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, (nt0 + t) * 8 + en, a.N / 2),
                                                      a.actplane, y);
             }
         }
@@ -347,14 +344,10 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(GemmArgs a) {
     const int parts = gridDim.y * WAVES, part = blockIdx.y * WAVES + w;
     const int ks0 = (int)((long long)part * KS / parts), ks1 = (int)((long long)(part + 1) * KS / parts);
     const u32x4* Wt = reinterpret_cast<const u32x4*>(a.Wt) + ((size_t)nt0 * KS + ks0) * 64 + lane;
-    // padding rows (>= R) feed columns of D that are never stored: let them re-read row 0 instead of
-    // touching more cache lines
+    // padding rows (>= R, stale memory) feed columns of D that are never stored
     const T* Xr[MT];
 #pragma unroll
-    for (int m = 0; m < MT; ++m) {
-        const int row = m * 16 + r;
-        Xr[m] = reinterpret_cast<const T*>(a.X) + (size_t)(row < a.R ? row : 0) * a.ldx + (size_t)ks0 * a.kstride + g * KF;
-    }
+    for (int m = 0; m < MT; ++m) Xr[m] = reinterpret_cast<const T*>(a.X) + (((size_t)m * KS + ks0) * 64 + lane) * KF;
 
     f32x4 acc[NT][MT];
 #pragma unroll
@@ -374,7 +367,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(GemmArgs a) {
         for (int m = 0; m < MT; ++m)
 #pragma unroll
             for (int sp = 0; sp < SPL; ++sp)
-                fb[buf][m][sp].u = *reinterpret_cast<const u32x4*>(Xr[m] + sp * a.xplane + (size_t)ks * a.kstride);
+                fb[buf][m][sp].u = *reinterpret_cast<const u32x4*>(Xr[m] + sp * a.xplane + (size_t)ks * (16 * KSTEP));
     };
     auto compute = [&](int buf) {
 #pragma unroll

@@ -3,7 +3,7 @@
 #include "../../include/sj.h"
 #include "sj_kernels.h"
 #include "sj_attn.h"
-#include "sj_prefill.h"
+#include "sj_attn_rows.h"
 #include "sj_gemm_rows.h"
 #include "sj_gemm_ring.h"
 
@@ -548,7 +548,9 @@ extern "C" int sj_kv_create(const sj_model* m, int32_t batch, const int32_t* cap
         ALLOC(kv->x, (size_t)R * d * 4);
         ALLOC(kv->part, part_elems * 4);
         ALLOC(kv->attn_out, (size_t)3 * kv->rpad * Nq * m->esz);
-        ALLOC(kv->act, (size_t)3 * kv->rpad * F * m->esz);
+        // also holds the rotated query fragments of many-row attention until the gate / up projection (whole tiles of 16 columns)
+        const size_t qcols = (size_t)(G * (c.max_gamma + 1) + 15) / 16 * 16;
+        ALLOC(kv->act, (size_t)3 * std::max((size_t)kv->rpad * F, R > FEW_ROWS ? batch * c.n_kv_heads * qcols * hd : 0) * m->esz);
         ALLOC(kv->cs, (size_t)R * hd * 4);
         ALLOC(kv->ss, (size_t)std::min(R, FEW_ROWS) * (d / 16) * 4);
         ALLOC(kv->prefill_tok, (size_t)R * 4);
@@ -856,13 +858,8 @@ struct FewArgs {
     float* x = nullptr;
     const void* gain = nullptr;
     float* ss_out = nullptr;
-    template <typename T, int EPI> void put(GemmArgs& a) const {
-        constexpr int KSTEP = Traits<T>::KSTEP;
-        a.kstride = KSTEP;
-        if (packed) {
-            a.ldx = KSTEP; a.kstride = 16 * KSTEP; a.xplane = a.actplane = 8 * KSTEP;
-            a.act_tks = (EPI == EPI_SWIGLU ? a.N / 2 : a.N) / KSTEP;
-        }
+    template <typename T> void put(GemmArgs& a) const {
+        if (packed) a.xplane = a.actplane = 8 * Traits<T>::KF;
         a.ss_in = ss_in; a.eps = eps; a.x = x; a.gain = gain; a.ss_out = ss_out;
     }
 };
@@ -870,16 +867,16 @@ struct FewArgs {
 template <typename T, int SPL> constexpr bool packed_rows(int rows) { return std::is_same<T, bf16_t>::value && SPL == 2 && rows <= RING_PACK_ROWS; }
 
 template <typename T, int NT, int EPI, int SPL, int WAVES, int D = 2>
-static int gemm(hipStream_t st, const void* Wt, const void* X, size_t xplane, int ldx, int K, int N, int rows, int split,
+static int gemm(hipStream_t st, const void* Wt, const void* X, size_t xplane, int K, int N, int rows, int split,
                 float* out, void* act, size_t actplane, float4* stats, float inv_temp, const FewArgs& fa = FewArgs{}) {
     if (rows > FEW_ROWS) return fail(SJ_EINVAL, "internal: few-row kernel called with %d rows", rows);
     const int ngroups = N / 16 / NT;
     GemmArgs a{};
     a.Wt = Wt; a.X = X; a.xplane = xplane; a.actplane = actplane;
-    a.ldx = ldx; a.K = K; a.N = N; a.R = rows; a.slice_rows = rows;
+    a.K = K; a.N = N; a.R = rows; a.slice_rows = rows;
     a.inv_temp = inv_temp;
     a.out = out; a.stats = stats; a.act = act;
-    fa.put<T, EPI>(a);
+    fa.put<T>(a);
     if (rows <= 16) gemm_skinny_kernel<T, NT, 1, EPI, SPL, WAVES, D><<<dim3(ngroups, split), WAVES * 64, 0, st>>>(a);
     else gemm_skinny_kernel<T, NT, 2, EPI, SPL, WAVES, D><<<dim3(ngroups, split), WAVES * 64, 0, st>>>(a);
     LAUNCHCHK("gemm_skinny");
@@ -888,14 +885,14 @@ static int gemm(hipStream_t st, const void* Wt, const void* X, size_t xplane, in
 
 // The same product on the LDS-ring kernel (bf16, at most two planes, at most 16 rows; ring_fits has been checked).
 template <typename T, int NT, int EPI, int SPL, int NSA>
-static int gemm_ring(hipStream_t st, const void* Wt, const void* X, size_t xplane, int ldx, int K, int N, int rows, int split,
+static int gemm_ring(hipStream_t st, const void* Wt, const void* X, size_t xplane, int K, int N, int rows, int split,
                      float* out, void* act, size_t actplane, float4* stats, float inv_temp, const FewArgs& fa = FewArgs{}) {
     GemmArgs a{};
     a.Wt = Wt; a.X = X; a.xplane = xplane; a.actplane = actplane;
-    a.ldx = ldx; a.K = K; a.N = N; a.R = rows; a.slice_rows = rows;
+    a.K = K; a.N = N; a.R = rows; a.slice_rows = rows;
     a.inv_temp = inv_temp;
     a.out = out; a.stats = stats; a.act = act;
-    fa.put<T, EPI>(a);
+    fa.put<T>(a);
     const dim3 grid(N / 16 / NT, split);
     if (SPL == 2 && rows <= RING_PACK_ROWS) gemm_ring_kernel<T, NT, EPI, 2, true, NSA><<<grid, RING_THREADS, 0, st>>>(a);
     else gemm_ring_kernel<T, NT, EPI, SPL, false, NSA><<<grid, RING_THREADS, 0, st>>>(a);
@@ -906,25 +903,25 @@ static int gemm_ring(hipStream_t st, const void* Wt, const void* X, size_t xplan
 // The few-row split-K projection in the launch shape of a plan.  Shapes beyond the first four exist for the
 // default two-plane / one-plane operands only (they are what the start-up measurement may pick).
 template <typename T, int SPL>
-static int few_partial(const GemmPlan& p, hipStream_t st, const void* W, const void* X, size_t xplane, int ldx, int K, int N,
+static int few_partial(const GemmPlan& p, hipStream_t st, const void* W, const void* X, size_t xplane, int K, int N,
                        int rows, float* out, const FewArgs& fa = FewArgs{}) {
     if (p.waves == RING_WAVES) {
         if constexpr (std::is_same<T, bf16_t>::value && SPL <= 2) {
             if (ring_fits(p, N / 16, K / Traits<T>::KSTEP, rows, SPL, true)) {
 #define SJ_RING(NT, NSA)                                                                                            \
     if (p.nt == NT && p.depth == NSA)                                                                               \
-        return gemm_ring<T, NT, EPI_PARTIAL, SPL, NSA>(st, W, X, xplane, ldx, K, N, rows, p.split, out, nullptr, 0, nullptr, 0.f, fa);
+        return gemm_ring<T, NT, EPI_PARTIAL, SPL, NSA>(st, W, X, xplane, K, N, rows, p.split, out, nullptr, 0, nullptr, 0.f, fa);
                 SJ_RING(1, 8) SJ_RING(2, 8) SJ_RING(3, 8) SJ_RING(4, 8) SJ_RING(8, 8)
                 SJ_RING(1, 4) SJ_RING(2, 4) SJ_RING(3, 4) SJ_RING(4, 4)
 #undef SJ_RING
             }
         }
         // more rows than the kernel takes, or a shape that is not instantiated: the register-ring kernel's rule shape
-        return few_partial<T, SPL>(plan_partial(N / 16, K / Traits<T>::KSTEP, true), st, W, X, xplane, ldx, K, N, rows, out, fa);
+        return few_partial<T, SPL>(plan_partial(N / 16, K / Traits<T>::KSTEP, true), st, W, X, xplane, K, N, rows, out, fa);
     }
 #define SJ_SHAPE(NT, WV, D)                                                                                         \
     if (p.nt == NT && p.waves == WV && p.depth == D)                                                                \
-        return gemm<T, NT, EPI_PARTIAL, SPL, WV, D>(st, W, X, xplane, ldx, K, N, rows, p.split, out, nullptr, 0, nullptr, 0.f, fa);
+        return gemm<T, NT, EPI_PARTIAL, SPL, WV, D>(st, W, X, xplane, K, N, rows, p.split, out, nullptr, 0, nullptr, 0.f, fa);
     SJ_SHAPE(4, 4, 2) SJ_SHAPE(4, 4, 4) SJ_SHAPE(3, 8, 2) SJ_SHAPE(6, 4, 2)
     if constexpr (SPL <= 2) {
         SJ_SHAPE(5, 4, 2) SJ_SHAPE(8, 8, 2) SJ_SHAPE(4, 8, 2) SJ_SHAPE(8, 4, 2) SJ_SHAPE(3, 4, 4)
@@ -933,7 +930,7 @@ static int few_partial(const GemmPlan& p, hipStream_t st, const void* W, const v
 #undef SJ_SHAPE
     // a shape that is not instantiated for this plane count: the rule's shape always is
     const GemmPlan q = plan_partial(N / 16, K / Traits<T>::KSTEP, true);
-    if (q.nt != p.nt || q.waves != p.waves || q.depth != p.depth) return few_partial<T, SPL>(q, st, W, X, xplane, ldx, K, N, rows, out, fa);
+    if (q.nt != p.nt || q.waves != p.waves || q.depth != p.depth) return few_partial<T, SPL>(q, st, W, X, xplane, K, N, rows, out, fa);
     return fail(SJ_EINVAL, "internal: no few-row kernel for %d tiles x %d waves, ring %d", p.nt, p.waves, p.depth);
 }
 
@@ -946,7 +943,7 @@ static int few_swiglu(const GemmPlan& p, hipStream_t st, const void* W, const vo
             if (ring_fits(p, N2 / 16, K / Traits<T>::KSTEP, rows, SPL, true)) {
 #define SJ_RING(NT, NSA)                                                                                            \
     if (p.nt == NT && p.depth == NSA)                                                                               \
-        return gemm_ring<T, NT, EPI_SWIGLU, SPL, NSA>(st, W, X, xplane, K, K, N2, rows, 1, nullptr, act, actplane, nullptr, 0.f, fa);
+        return gemm_ring<T, NT, EPI_SWIGLU, SPL, NSA>(st, W, X, xplane, K, N2, rows, 1, nullptr, act, actplane, nullptr, 0.f, fa);
                 SJ_RING(7, 8) SJ_RING(8, 8) SJ_RING(4, 8) SJ_RING(2, 8) SJ_RING(7, 4) SJ_RING(8, 4) SJ_RING(4, 4)
 #undef SJ_RING
             }
@@ -957,7 +954,7 @@ static int few_swiglu(const GemmPlan& p, hipStream_t st, const void* W, const vo
     }
 #define SJ_SHAPE(NT, WV, D)                                                                                         \
     if (p.nt == NT && p.waves == WV && p.depth == D)                                                                \
-        return gemm<T, NT, EPI_SWIGLU, SPL, WV, D>(st, W, X, xplane, K, K, N2, rows, 1, nullptr, act, actplane, nullptr, 0.f, fa);
+        return gemm<T, NT, EPI_SWIGLU, SPL, WV, D>(st, W, X, xplane, K, N2, rows, 1, nullptr, act, actplane, nullptr, 0.f, fa);
     SJ_SHAPE(7, 8, 2) SJ_SHAPE(8, 8, 2)
     if constexpr (SPL <= 2) {
         SJ_SHAPE(4, 8, 2) SJ_SHAPE(4, 4, 2) SJ_SHAPE(2, 8, 2) SJ_SHAPE(2, 4, 2) SJ_SHAPE(1, 8, 2)
@@ -994,13 +991,13 @@ static int few_resid(const GemmPlan& p, hipStream_t st, const void* W, const voi
         if constexpr (std::is_same<T, bf16_t>::value) {
 #define SJ_RING(NT, NSA)                                                                                            \
     if (p.waves == RING_WAVES && p.nt == NT && p.depth == NSA)                                                      \
-        return gemm_ring<T, NT, EPI_RESID, SPL, NSA>(st, W, X, xplane, K, K, N, rows, 1, nullptr, xg, xgplane, nullptr, 0.f, fa);
+        return gemm_ring<T, NT, EPI_RESID, SPL, NSA>(st, W, X, xplane, K, N, rows, 1, nullptr, xg, xgplane, nullptr, 0.f, fa);
             SJ_RING(1, 8) SJ_RING(2, 8) SJ_RING(4, 8) SJ_RING(1, 4) SJ_RING(2, 4) SJ_RING(4, 4)
 #undef SJ_RING
         }
 #define SJ_SHAPE(NT)                                                                                                \
     if (p.waves == 8 && p.nt == NT)                                                                                 \
-        return gemm<T, NT, EPI_RESID, SPL, 8, 2>(st, W, X, xplane, K, K, N, rows, 1, nullptr, xg, xgplane, nullptr, 0.f, fa);
+        return gemm<T, NT, EPI_RESID, SPL, 8, 2>(st, W, X, xplane, K, N, rows, 1, nullptr, xg, xgplane, nullptr, 0.f, fa);
         SJ_SHAPE(1) SJ_SHAPE(2) SJ_SHAPE(4)
 #undef SJ_SHAPE
     }
@@ -1016,7 +1013,7 @@ static int few_logits(const GemmPlan& p, hipStream_t st, const void* W, const vo
             if (ring_fits(p, V / 16, K / Traits<T>::KSTEP, rows, SPL, true)) {
 #define SJ_RING(NT, NSA)                                                                                            \
     if (p.nt == NT && p.depth == NSA)                                                                               \
-        return gemm_ring<T, NT, EPI_LOGITS, SPL, NSA>(st, W, X, xplane, K, K, V, rows, 1, logits, nullptr, 0, stats, inv_temp, fa);
+        return gemm_ring<T, NT, EPI_LOGITS, SPL, NSA>(st, W, X, xplane, K, V, rows, 1, logits, nullptr, 0, stats, inv_temp, fa);
                 SJ_RING(8, 4) SJ_RING(8, 8) SJ_RING(4, 8)
 #undef SJ_RING
             }
@@ -1030,7 +1027,7 @@ static int few_logits(const GemmPlan& p, hipStream_t st, const void* W, const vo
     }
 #define SJ_SHAPE(NT, WV)                                                                                            \
     if (p.nt == NT && p.waves == WV)                                                                                \
-        return gemm<T, NT, EPI_LOGITS, SPL, WV>(st, W, X, xplane, K, K, V, rows, 1, logits, nullptr, 0, stats, inv_temp, fa);
+        return gemm<T, NT, EPI_LOGITS, SPL, WV>(st, W, X, xplane, K, V, rows, 1, logits, nullptr, 0, stats, inv_temp, fa);
     SJ_SHAPE(8, 4)
     if constexpr (SPL <= 2) { SJ_SHAPE(8, 8) SJ_SHAPE(4, 8) SJ_SHAPE(4, 4) }
 #undef SJ_SHAPE
@@ -1087,7 +1084,7 @@ static int tune_one(sj_kv* kv, GemmPlan& plan, void* LayerW::*which, const void*
         for (int rep = 0; rep < 2; ++rep) {                 // the first repetition warms up
             HIPCHK(hipEventRecord(e0, nullptr));
             for (int l = 0; l < nl; ++l) {
-                const int rc = few_partial<T, SPL>(p, nullptr, m->layers[l].*which, X, xplane, K, K, N, rows, kv->part, fa);
+                const int rc = few_partial<T, SPL>(p, nullptr, m->layers[l].*which, X, xplane, K, N, rows, kv->part, fa);
                 if (rc) return rc;
             }
             HIPCHK(hipEventRecord(e1, nullptr));
@@ -1267,24 +1264,21 @@ static int tune_plans(sj_kv* kv, int rows) {
 // More rows: groups of at most 144 rows (9 MFMA row tiles) through the loader-wave kernel; the statistics
 // of EPI_LOGITS are per workgroup (of 8 n-tiles) there, per n-tile with three operand planes.
 template <typename T, int EPI, int SPL>
-static int gemm_rows(hipStream_t st, const void* Wt, const void* X, size_t xplane, int ldx, int K, int N, int rows, int split,
-                     float* out, void* act, size_t actplane, float4* stats, float inv_temp, bool tiled) {
+static int gemm_rows(hipStream_t st, const void* Wt, const void* X, size_t xplane, int K, int N, int rows, int split,
+                     float* out, void* act, size_t actplane, float4* stats, float inv_temp) {
     const int ntiles = N / 16;
-    // fragment-tiled operand planes: a group of 144 rows starts row0 * K elements into the plane in either layout
-    if (tiled && ldx != K) return fail(SJ_EINVAL, "a tiled operand has no padding between rows");
+    // a group of rows (whole row tiles) starts row0 * K elements into the plane
     // a single operand plane: row groups of 288 (the 18 operand fragments of a k-step fill the same LDS stages)
     constexpr int RT = (SPL == 1) ? 2 * ROWS_MT : ROWS_MT;
     const int group_rows = RT * 16;
     auto args_of = [&](int row0, int nr) {
         GemmArgs a{};
         a.Wt = Wt;
-        a.X = (const char*)X + (size_t)row0 * ldx * sizeof(T);
+        a.X = (const char*)X + (size_t)row0 * K * sizeof(T);
         a.xplane = xplane; a.actplane = actplane;
-        a.ldx = ldx; a.K = K; a.N = N;
+        a.K = K; a.N = N;
         a.R = nr; a.slice_rows = rows;
         a.inv_temp = inv_temp;
-        a.x_tks = tiled ? K / Traits<T>::KSTEP : 0;
-        a.act_tks = tiled ? (N / 2) / Traits<T>::KSTEP : 0;
         if (EPI == EPI_PARTIAL) a.out = out + (size_t)row0 * N;            // [split][rows][N]
         else if (EPI == EPI_LOGITS) { a.out = out + (size_t)row0 * N; a.stats = stats + (size_t)row0 * ntiles; }
         else a.act = (char*)act + (size_t)row0 * (N / 2) * sizeof(T);
@@ -1320,6 +1314,13 @@ static int gemm_rows(hipStream_t st, const void* Wt, const void* X, size_t xplan
     return SJ_OK;
 }
 
+// Blocks whose attention runs in two launches: more rows than the few-row kernels take, and at least one full query tile per kv
+// head and sequence.
+static bool many_rows_attention(const ModelDims& md, int rows, int rps) {
+    static const bool off = std::getenv("SJ_NO_ROWS_ATTN") != nullptr;
+    return !off && rows > FEW_ROWS && rps * md.G >= 16;
+}
+
 template <typename T, int SPL>
 struct Runner {
     const sj_model* m;
@@ -1335,13 +1336,7 @@ struct Runner {
         return v;
     }
     bool packed() const { return packed_rows<T, SPL>(R); }
-    size_t plane(int ld) const { return packed() ? 8 * Traits<T>::KSTEP : (size_t)w->rpad * ld; }
-    // Operand planes are written as MFMA fragments when the many-row kernel that reads operands through LDS
-    // consumes them (more than FEW_ROWS rows, at most two planes); row-major otherwise.
-    bool tiled() const { return R > FEW_ROWS && SPL <= 2; }
-    int tks(int K) const { return tiled() || packed() ? K / Traits<T>::KSTEP : 0; }
-    // the same for a single exact plane (hidden states handed in by the caller), whatever SPL is
-    int tks1(int K) const { return R > FEW_ROWS ? K / Traits<T>::KSTEP : 0; }
+    size_t plane(int ld) const { return packed() ? 8 * Traits<T>::KF : (size_t)w->rpad * ld; }
     // Launch shape of a split-K projection for this row count.  A prompt chunk of at most 32 rows can have more rows than
     // the plan was made for: the LDS-ring shape then gives way to the register-ring kernel's rule shape.
     GemmPlan plan_of(const GemmPlan (&pl)[2], int K, int N) const {
@@ -1355,11 +1350,11 @@ struct Runner {
         return pl[0];
     }
     // `parts`: the K-slices it leaves in w->part
-    int partial_gemm(const void* W, const void* X, int ldx, int K, int N, const GemmPlan (&pl)[2], int* parts = nullptr, bool unscaled = false) {
+    int partial_gemm(const void* W, const void* X, int K, int N, const GemmPlan (&pl)[2], int* parts = nullptr, bool unscaled = false) {
         const GemmPlan p = plan_of(pl, K, N);
         if (parts) *parts = p.split;
-        if (R > FEW_ROWS) return gemm_rows<T, EPI_PARTIAL, SPL>(st, W, X, plane(ldx), ldx, K, N, R, p.split, w->part, nullptr, 0, nullptr, 0.f, tiled());
-        return few_partial<T, SPL>(p, st, W, X, plane(ldx), ldx, K, N, R, w->part, few_args(unscaled));
+        if (R > FEW_ROWS) return gemm_rows<T, EPI_PARTIAL, SPL>(st, W, X, plane(K), K, N, R, p.split, w->part, nullptr, 0, nullptr, 0.f);
+        return few_partial<T, SPL>(p, st, W, X, plane(K), K, N, R, w->part, few_args(unscaled));
     }
     // the operand in w->xn lacks its 1/rms factors (it came from a residual epilogue)
     FewArgs few_args(bool unscaled) const {
@@ -1374,7 +1369,7 @@ struct Runner {
         const int d = m->md.d;
         const GemmPlan p = resid_plan(d, K, Traits<T>::KSTEP, R, SPL, std::is_same<T, bf16_t>::value, kv->ring_rows);
         unscaled = p.nt > 0;
-        if (!unscaled) return partial_gemm(W, X, K, K, d, pl, &parts);
+        if (!unscaled) return partial_gemm(W, X, K, d, pl, &parts);
         FewArgs n = few_args(false);
         n.x = w->x; n.gain = gain; n.ss_out = w->ss;
         return few_resid<T, SPL>(p, st, W, X, plane(K), K, d, R, w->xn, plane(d), n);
@@ -1395,14 +1390,14 @@ struct Runner {
     // number of workgroups per CU (2F/16 = 1792 tiles -> 256 workgroups), else 8
     int gate_up(const void* W, bool unscaled = false) {
         const ModelDims& md = m->md;
-        if (R > FEW_ROWS) return gemm_rows<T, EPI_SWIGLU, SPL>(st, W, w->xn, plane(md.d), md.d, md.d, 2 * md.F, R, 1, nullptr, w->act, plane(md.F), nullptr, 0.f, tiled());
+        if (R > FEW_ROWS) return gemm_rows<T, EPI_SWIGLU, SPL>(st, W, w->xn, plane(md.d), md.d, 2 * md.F, R, 1, nullptr, w->act, plane(md.F), nullptr, 0.f);
         return few_swiglu<T, SPL>(kv->plan_gu, st, W, w->xn, plane(md.d), md.d, 2 * md.F, R, w->act, plane(md.F), few_args(unscaled));
     }
 
     // rotary + cache append + attention of one layer from the QKV partials in w->part
     int attention(int layer, int parts) {
         const ModelDims& md = m->md;
-        if (rps > m->cfg.max_gamma + 1) return prefill_attention(layer, parts);
+        if (rps > m->cfg.max_gamma + 1 || many_rows_attention(md, R, rps)) return rows_attention(layer, parts);
         const int M = md.G * rps;
         const int mtiles = (M + 15) / 16;
         // one query tile per workgroup while the launch stays small (shortest dependent chain per wave;
@@ -1415,7 +1410,7 @@ struct Runner {
 #define ATTN_PB(HD, MQ, PB)                                                                                            \
     attn_fused_kernel<T, HD, MQ, SPL, PB><<<grid, 256, 0, st>>>(kv->sp_dev, md, w->part, parts, R, w->cs, view(), \
                                                                 layer, kv->chunk_keys, kv->nchunk_max, kv->opart, kv->tickets,  \
-                                                                (T*)w->attn_out, plane(md.Hq * md.hd), tks(md.Hq * md.hd))
+                                                                (T*)w->attn_out, plane(md.Hq * md.hd))
 #define ATTN(HD, MQ)                                                                                                   \
     do { if (pb2) ATTN_PB(HD, MQ, 2); else ATTN_PB(HD, MQ, 4); } while (0)
         if (md.hd == 128) {
@@ -1429,38 +1424,43 @@ struct Runner {
         return SJ_OK;
     }
 
-    // the same for a prompt chunk (one sequence, more rows than the decode kernel's workspace has room for)
-    int prefill_attention(int layer, int parts) {
+    // the same in two launches, for many rows (sj_attn_rows.h)
+    int rows_attention(int layer, int parts) {
         const ModelDims& md = m->md;
-        const int blocks = (rps + PF_POS - 1) / PF_POS, ntiles = md.G * blocks;
+        const int blocks = (rps + ROT_POS - 1) / ROT_POS, ntiles = (rps * md.G + 15) / 16;
         u32x4* qbuf = (u32x4*)w->act;
-        // two query tiles a wave halve the K / V reads where that still leaves a workgroup for every CU
-        const bool two = (long long)((ntiles + 7) / 8) * md.Hkv >= 256;
-        const dim3 grid(two ? (ntiles + 7) / 8 : (ntiles + 3) / 4, md.Hkv);
-#define PF_ATTN(HD)                                                                                                    \
+        // waves per tile: as many as leave a workgroup for every CU
+        const long long tiles = (long long)ntiles * md.Hkv * nseq;
+        int kw = tiles >= 1024 ? 2 : tiles >= 512 ? 4 : 8;
+        if (const char* e = std::getenv("SJ_KW")) kw = std::atoi(e);
+        const int grid = (ntiles * kw + ROWS_WAVES - 1) / ROWS_WAVES * ((nseq * md.Hkv + 7) / 8 * 8);
+#define ROWS_ATTN_KW(HD, KW)                                                                                           \
+    rows_attn_kernel<T, HD, KW, SPL><<<grid, ROWS_WAVES * 64, 0, st>>>(kv->sp_dev, md, view(), layer, qbuf, ntiles,    \
+                                                                       (T*)w->attn_out, plane(md.Hq * md.hd))
+#define ROWS_ATTN(HD)                                                                                                  \
     do {                                                                                                               \
-        prefill_rotary_kernel<T, HD, SPL><<<dim3(blocks, md.Hkv), 256, 0, st>>>(kv->sp_dev, md, w->part, parts, R, w->cs, view(), layer, qbuf); \
-        LAUNCHCHK("prefill_rotary");                                                                                   \
-        if (two) prefill_attn_kernel<T, HD, 2, SPL><<<grid, 256, 0, st>>>(kv->sp_dev, md, view(), layer, qbuf, ntiles, (T*)w->attn_out, plane(md.Hq * md.hd), tks(md.Hq * md.hd)); \
-        else prefill_attn_kernel<T, HD, 1, SPL><<<grid, 256, 0, st>>>(kv->sp_dev, md, view(), layer, qbuf, ntiles, (T*)w->attn_out, plane(md.Hq * md.hd), tks(md.Hq * md.hd)); \
-        LAUNCHCHK("prefill_attn");                                                                                     \
+        rows_rotary_kernel<T, HD, SPL><<<dim3(blocks, 3 * md.Hkv, nseq), 256, 0, st>>>(kv->sp_dev, md, w->part, parts, R, w->cs, view(), layer, qbuf, ntiles); \
+        LAUNCHCHK("rows_rotary");                                                                                      \
+        if (kw == 2) ROWS_ATTN_KW(HD, 2); else if (kw == 4) ROWS_ATTN_KW(HD, 4); else ROWS_ATTN_KW(HD, 8);             \
+        LAUNCHCHK("rows_attn");                                                                                        \
     } while (0)
-        if (md.hd == 128) PF_ATTN(128); else PF_ATTN(64);
-#undef PF_ATTN
+        if (md.hd == 128) ROWS_ATTN(128); else ROWS_ATTN(64);
+#undef ROWS_ATTN
+#undef ROWS_ATTN_KW
         return SJ_OK;
     }
 
     // residual add of `parts` pending split-K partials + RMSNorm into the operand planes (batches of loads as wide as
     // the partials there are: an eight-wide clamped batch for two partials repeats six loads)
-    void norm(int parts, const void* gain, float* xn32) { norm_rows(parts, gain, xn32, 0, R, 0, tks(m->md.d), plane(m->md.d)); }
-    // rows r0 .. r0 + n - 1 of the block into rows o0 .. of the operand planes (o0 a multiple of 16 in tiled planes) and of xn32
-    void norm_rows(int parts, const void* gain, float* xn32, int r0, int n, int o0, int otks, size_t oplane) {
+    void norm(int parts, const void* gain, float* xn32) { norm_rows(parts, gain, xn32, 0, R, 0, plane(m->md.d)); }
+    // rows r0 .. r0 + n - 1 of the block into rows 0 .. of the operand planes and rows o0 .. of xn32
+    void norm_rows(int parts, const void* gain, float* xn32, int r0, int n, int o0, size_t oplane) {
         const int d = m->md.d;
         float *x = w->x + (size_t)r0 * d, *part = w->part + (size_t)r0 * d, *h = xn32 ? xn32 + (size_t)o0 * d : nullptr;
-        T* xn = (T*)w->xn + (size_t)o0 * d;
-        if (parts <= 2) add_rmsnorm_kernel<T, 2, SPL><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, oplane, h, otks);
-        else if (parts <= 4) add_rmsnorm_kernel<T, 4, SPL><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, oplane, h, otks);
-        else add_rmsnorm_kernel<T, 8, SPL><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, oplane, h, otks);
+        T* xn = (T*)w->xn;
+        if (parts <= 2) add_rmsnorm_kernel<T, 2, SPL><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, oplane, h);
+        else if (parts <= 4) add_rmsnorm_kernel<T, 4, SPL><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, oplane, h);
+        else add_rmsnorm_kernel<T, 8, SPL><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, oplane, h);
     }
 
     // decoder layers (Eq. 2 / Eq. 4): leaves the last down-projection's K-slices pending in w->part (their number in `parts`)
@@ -1469,7 +1469,7 @@ struct Runner {
         const sj_config& c = m->cfg;
         const int d = md.d, Nq = md.Hq * md.hd, Nk = md.Hkv * md.hd, Nqkv = Nq + 2 * Nk;
         step_begin_kernel<T, SPL><<<R, 1024, 0, st>>>(kv->sp_dev, md, (const T*)m->embed, kv->len_dev, kv->pending_dev, w->x, w->cs, w->row_tok,
-                                                  std::log((double)c.rope_base), (const T*)m->layers[0].attn_norm, (T*)w->xn, plane(d), tks(d));
+                                                  std::log((double)c.rope_base), (const T*)m->layers[0].attn_norm, (T*)w->xn, plane(d));
         LAUNCHCHK("step_begin");
         parts = 0;
         bool unscaled = false;
@@ -1477,7 +1477,7 @@ struct Runner {
         for (int l = 0; l < c.n_layers; ++l) {
             const LayerW& L = m->layers[l];
             if ((rc = time_mark(kv, 1, st))) return rc;
-            if ((rc = partial_gemm(L.wqkv, w->xn, d, d, Nqkv, kv->plan_qkv, &parts, unscaled))) return rc;
+            if ((rc = partial_gemm(L.wqkv, w->xn, d, Nqkv, kv->plan_qkv, &parts, unscaled))) return rc;
             if ((rc = time_mark(kv, 1, st))) return rc;
             if ((rc = attention(l, parts))) return rc;
             if ((rc = close(L.wo, w->attn_out, Nq, kv->plan_o, L.ffn_norm, 2, unscaled))) return rc;
@@ -1488,7 +1488,7 @@ struct Runner {
                 if ((rc = close(L.wd, w->act, md.F, kv->plan_d, m->layers[l + 1].attn_norm, 4, unscaled))) return rc;
             } else {
                 if ((rc = time_mark(kv, 4, st))) return rc;
-                if ((rc = partial_gemm(L.wd, w->act, md.F, md.F, d, kv->plan_d, &parts))) return rc;
+                if ((rc = partial_gemm(L.wd, w->act, md.F, d, kv->plan_d, &parts))) return rc;
                 if ((rc = time_mark(kv, 4, st))) return rc;
             }
         }
@@ -1510,8 +1510,8 @@ struct Runner {
         int rc;
         if (R > FEW_ROWS) {
             rc = exact_operand
-                ? gemm_rows<T, EPI_LOGITS, 1>(st, m->lm_head, w->xn, plane(md.d), md.d, md.d, md.V, R, 1, kv->logits, nullptr, 0, kv->stats, md.inv_temp, true)
-                : gemm_rows<T, EPI_LOGITS, SPL>(st, m->lm_head, w->xn, plane(md.d), md.d, md.d, md.V, R, 1, kv->logits, nullptr, 0, kv->stats, md.inv_temp, tiled());
+                ? gemm_rows<T, EPI_LOGITS, 1>(st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, 1, kv->logits, nullptr, 0, kv->stats, md.inv_temp)
+                : gemm_rows<T, EPI_LOGITS, SPL>(st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, 1, kv->logits, nullptr, 0, kv->stats, md.inv_temp);
             nblk = exact_operand || SPL <= 2 ? md.V / 16 / R2_NT : md.V / 16;      // gemm_rows8: per workgroup; gemm_rows2: per n-tile
         } else {
             rc = exact_operand
@@ -1586,7 +1586,7 @@ static int enqueue_step(sj_model* m, sj_kv* kv, int gamma, hipStream_t st, bool 
     int rc;
     Runner<T, SPL> run{m, kv, st, kv->batch, gamma + 1, kv->batch * (gamma + 1)};
     if (head_only) {
-        hidden_in_kernel<T><<<1024, 256, 0, st>>>((const T*)hidden, (T*)kv->xn, kv->hn32, run.R, m->md.d, run.tks1(m->md.d));
+        hidden_in_kernel<T><<<1024, 256, 0, st>>>((const T*)hidden, (T*)kv->xn, kv->hn32, run.R, m->md.d);
         LAUNCHCHK("hidden_in");
     } else {
         if ((rc = run.layers())) return rc;
@@ -1663,7 +1663,7 @@ static int time_kernel_impl(sj_model* m, sj_kv* kv, int cls, int launches, int g
         }
         const LayerW& L = m->layers[i % m->cfg.n_layers];        // a different layer each time: no cache reuse
         switch (cls) {
-            case 1: rc = run.partial_gemm(L.wqkv, kv->xn, d, d, Nq + 2 * Nk, kv->plan_qkv); break;
+            case 1: rc = run.partial_gemm(L.wqkv, kv->xn, d, Nq + 2 * Nk, kv->plan_qkv); break;
             case 2: rc = run.closing_gemm(L.wo, kv->attn_out, Nq, kv->plan_o, L.ffn_norm, parts, unscaled); break;
             case 3: rc = run.gate_up(L.wgu); break;
             default: rc = run.closing_gemm(L.wd, kv->act, md.F, kv->plan_d, L.ffn_norm, parts, unscaled); break;
@@ -1977,8 +1977,8 @@ static int prefill_impl(sj_model* m, sj_kv* kv, int seq, const int32_t* tokens, 
                 head_rows = n - (n - 1) / block * block;
                 const int keep = std::min(block, cn);          // chunks are longer than a block: cn > block
                 Runner<T, SPL> head{m, kv, st, 1, head_rows, head_rows, fw};
-                if (keep > head_rows) run.norm_rows(parts, m->final_norm, kv->hn32, cn - keep, keep - head_rows, head_rows, 0, run.plane(m->md.d));
-                run.norm_rows(parts, m->final_norm, kv->hn32, cn - head_rows, head_rows, 0, head.tks(m->md.d), head.plane(m->md.d));
+                if (keep > head_rows) run.norm_rows(parts, m->final_norm, kv->hn32, cn - keep, keep - head_rows, head_rows, run.plane(m->md.d));   // (its operand rows give way to the next ones)
+                run.norm_rows(parts, m->final_norm, kv->hn32, cn - head_rows, head_rows, 0, head.plane(m->md.d));
                 LAUNCHCHK("add_rmsnorm");
             }
         }
