@@ -73,7 +73,7 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(const StepParams* __res
                                                          const float* __restrict__ cs, KvView<T> kv, int layer,
                                                          int wave_keys, int nchunk_max, float* __restrict__ opart,
                                                          unsigned* __restrict__ tickets, T* __restrict__ attn_out,
-                                                         size_t aplane) {
+                                                         size_t aplane, int rm) {
     constexpr int KF = Traits<T>::KF, KSTEP = Traits<T>::KSTEP;
     constexpr int NS = KF / 4;       // S^T tiles per step of KSTEP keys
     static_assert(SPL <= Traits<T>::NS, "more planes than the storage type has");
@@ -108,16 +108,13 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(const StepParams* __res
     // two register sets of one key step each: the next step is requested before the current one is used
     Frag kf[2][NS][KK], vf[2][HT];
     auto load_keys = [&](int set, int key0) {
+        const T *kb = Kb + (size_t)key0 * HD + lane * KF, *vb = Vb + (size_t)key0 * HD + lane * KF;
 #pragma unroll
-        for (int t = 0; t < NS; ++t) {
-            const int krow = key0 + KF * (r >> 2) + 4 * t + (r & 3);
+        for (int t = 0; t < NS; ++t)
 #pragma unroll
-            for (int kk = 0; kk < KK; ++kk)
-                kf[set][t][kk].u = *reinterpret_cast<const u32x4*>(Kb + (size_t)krow * HD + kk * KSTEP + g * KF);
-        }
+            for (int kk = 0; kk < KK; ++kk) kf[set][t][kk].u = *reinterpret_cast<const u32x4*>(kb + (t * KK + kk) * 64 * KF);
 #pragma unroll
-        for (int ht = 0; ht < HT; ++ht)
-            vf[set][ht].u = *reinterpret_cast<const u32x4*>(Vb + (size_t)(ht * 16 + r) * cap + key0 + g * KF);
+        for (int ht = 0; ht < HT; ++ht) vf[set][ht].u = *reinterpret_cast<const u32x4*>(vb + ht * 64 * KF);
     };
     load_keys(0, min(key_lo, cap - KSTEP));            // capacities are multiples of 64: always inside
 
@@ -247,15 +244,15 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(const StepParams* __res
                         Traits<T>::store(&sm.in.knew[j][i], olo);
                         Traits<T>::store(&sm.in.knew[j][i + HALF], ohi);
                         if (in_cap) {
-                            Kb[(size_t)(L + j) * HD + i] = sm.in.knew[j][i];
-                            Kb[(size_t)(L + j) * HD + i + HALF] = sm.in.knew[j][i + HALF];
+                            Kb[kv_k_off<T>(L + j, i, HD)] = sm.in.knew[j][i];
+                            Kb[kv_k_off<T>(L + j, i + HALF, HD)] = sm.in.knew[j][i + HALF];
                         }
                     } else {
                         Traits<T>::store(&sm.in.vnewT[i][j], olo);
                         Traits<T>::store(&sm.in.vnewT[i + HALF][j], ohi);
                         if (in_cap) {
-                            Vb[(size_t)i * cap + L + j] = sm.in.vnewT[i][j];
-                            Vb[(size_t)(i + HALF) * cap + L + j] = sm.in.vnewT[i + HALF][j];
+                            Vb[kv_v_off<T>(L + j, i, HD)] = sm.in.vnewT[i][j];
+                            Vb[kv_v_off<T>(L + j, i + HALF, HD)] = sm.in.vnewT[i + HALF][j];
                         }
                     }
                 }
@@ -440,7 +437,7 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(const StepParams* __res
     auto write_out = [&](int mq, int ht, const float (&v)[4]) {
         if (rowvalid[mq]) {
             const int row = bi * rps + jrow[mq];
-            Traits<T>::template store_split4<SPL>(attn_out + opnd_off<T>(row, (kvh * md.G + girow[mq]) * HD + ht * 16 + 4 * g, md.Hq * HD), aplane, v);
+            Traits<T>::template store_split4<SPL>(attn_out + opnd_off<T>(row, (kvh * md.G + girow[mq]) * HD + ht * 16 + 4 * g, md.Hq * HD, rm), aplane, v);
         }
     };
 

@@ -15,7 +15,9 @@
 //
 // What bounds it: per step of 32 keys and tile, 32 MFMAs (two operand planes) and about 150 vector instructions, which
 // two waves of a SIMD overlap (one tile a wave: about 200 registers; the decode kernel's three tiles a wave take 478 and leave one).
-// ROWS_ATTN_MEASURED
+// Measured (8B shape, two planes): 6 blocks of 21 rows over 60 - 700 keys: 83 us in one launch, 13 + 13 us in two; a prompt chunk of
+// 509 rows: 19 + 11 us; 16 blocks of 9 rows over 512 - 4096 keys: 66 + 15 us against 69 in one launch, whose key ranges fill the
+// chip better - the rule at many_rows_attention keeps it there.
 #pragma once
 #include "sj_attn.h"
 
@@ -24,7 +26,7 @@ namespace sj {
 constexpr int ROT_POS = 16;        // positions per workgroup of the rotary kernel (= G whole query tiles)
 
 // Query fragments: qbuf[sequence][kv head][query tile][head-dim step][plane][64 lanes] of 16 bytes; ntiles = ceil(rps * G / 16).
-template <typename T, int HD, int SPL>
+template <typename T, int HD, int SPL, int PB>
 __global__ __launch_bounds__(256) void rows_rotary_kernel(const StepParams* __restrict__ sp, ModelDims md,
                                                              const float* __restrict__ part, int nparts, int R,
                                                              const float* __restrict__ cs, KvView<T> kv, int layer,
@@ -36,21 +38,21 @@ __global__ __launch_bounds__(256) void rows_rotary_kernel(const StepParams* __re
     const int Nq = md.Hq * HD, Nk = md.Hkv * HD, N = Nq + 2 * Nk;
     T* Kb = kv.K + (size_t)layer * kv.layer_stride + kv.seq_off[b] + (size_t)kvh * cap * HD;
     T* Vb = kv.V + (size_t)layer * kv.layer_stride + kv.seq_off[b] + (size_t)kvh * HD * cap;
-    // sums of the partials of four neighbouring columns of one row (at each of n places), in slice order; four slices of
+    // sums of the partials of four neighbouring columns of one row (at each of n places), in slice order; PB slices of
     // independent loads at a time (index clamped, surplus ignored)
     auto sums = [&](auto& v, int row, auto col_of) {
         constexpr int n = sizeof(v) / sizeof(v[0]);
 #pragma unroll
         for (int i = 0; i < n; ++i) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int s0 = 0; s0 < nparts; s0 += 4) {
-            f32x4 t[4][n];
+        for (int s0 = 0; s0 < nparts; s0 += PB) {
+            f32x4 t[PB][n];
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+            for (int u = 0; u < PB; ++u)
 #pragma unroll
                 for (int i = 0; i < n; ++i)
                     t[u][i] = *reinterpret_cast<const f32x4*>(part + ((size_t)min(s0 + u, nparts - 1) * R + row) * N + col_of(i));
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+            for (int u = 0; u < PB; ++u)
 #pragma unroll
                 for (int i = 0; i < n; ++i)
                     if (s0 + u < nparts) v[i] += t[u][i];
@@ -95,12 +97,12 @@ __global__ __launch_bounds__(256) void rows_rotary_kernel(const StepParams* __re
             sums(v, r0 + row, [&](int k) { return Nq + kvh * HD + k * HALF + i; });
             const f32x4 lo = v[0], hi = v[1];
             const float* csr = cs + ((size_t)(r0 + row) * HALF + i) * 2;
-            T* k = Kb + (size_t)(L + row) * HD + i;
+            T *k0 = Kb + kv_k_off<T>(L + row, i, HD), *k1 = Kb + kv_k_off<T>(L + row, HALF + i, HD);   // four neighbours each
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const float c = csr[2 * e], s = csr[2 * e + 1];
-                Traits<T>::store(k + e, lo[e] * c - hi[e] * s);
-                Traits<T>::store(k + HALF + e, hi[e] * c + lo[e] * s);
+                Traits<T>::store(k0 + e, lo[e] * c - hi[e] * s);
+                Traits<T>::store(k1 + e, hi[e] * c + lo[e] * s);
             }
         }
     }
@@ -116,7 +118,7 @@ __global__ __launch_bounds__(256) void rows_rotary_kernel(const StepParams* __re
     __syncthreads();
     for (int it = tid; it < ROT_POS * HD; it += 256) {
         const int j = it % ROT_POS, i = it / ROT_POS, pos = L + p0 + j;
-        if (p0 + j < rps && pos < cap) Vb[(size_t)i * cap + pos] = vt[i][j];
+        if (p0 + j < rps && pos < cap) Vb[kv_v_off<T>(pos, i, HD)] = vt[i][j];
     }
 }
 
@@ -158,16 +160,15 @@ __global__ __launch_bounds__(ROWS_WAVES * 64) void rows_attn_kernel(const StepPa
     }
 
     Frag kf[2][NS][KK], vf[2][HT];
-    auto load_keys = [&](int set, int key) {           // any key: clamped to the cache (capacities are multiples of 64)
+    auto load_keys = [&](int set, int key) {           // any whole step: clamped to the cache
         key = min(key, cap - KSTEP);
+        const T *kb = Kb + (size_t)key * HD + lane * KF, *vb = Vb + (size_t)key * HD + lane * KF;
 #pragma unroll
-        for (int t = 0; t < NS; ++t) {
-            const int krow = key + KF * (r >> 2) + 4 * t + (r & 3);
+        for (int t = 0; t < NS; ++t)
 #pragma unroll
-            for (int kk = 0; kk < KK; ++kk) kf[set][t][kk].u = *reinterpret_cast<const u32x4*>(Kb + (size_t)krow * HD + kk * KSTEP + g * KF);
-        }
+            for (int kk = 0; kk < KK; ++kk) kf[set][t][kk].u = *reinterpret_cast<const u32x4*>(kb + (t * KK + kk) * 64 * KF);
 #pragma unroll
-        for (int ht = 0; ht < HT; ++ht) vf[set][ht].u = *reinterpret_cast<const u32x4*>(Vb + (size_t)(ht * 16 + r) * cap + key + g * KF);
+        for (int ht = 0; ht < HT; ++ht) vf[set][ht].u = *reinterpret_cast<const u32x4*>(vb + ht * 64 * KF);
     };
 
     f32x4 o[HT];

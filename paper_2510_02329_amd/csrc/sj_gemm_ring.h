@@ -92,10 +92,12 @@ __global__ __launch_bounds__(RING_THREADS) void gemm_ring_kernel(GemmArgs a) {
 
     // ---------------- compute waves ----------------
     constexpr int NB = PACK ? 1 : SPL;                 // operand fragments (products) per weight fragment
-    // fragment of k-step ks0 + w; packed planes are one plane of 16 rows.  Rows past R are read (stale) and never stored.
+    // fragment of k-step ks0 + w; packed planes are one plane of 16 rows (lanes of rows past R repeat row 0 of their plane)
+    const int xr = PACK ? ((r & 7) < a.R ? r : r & 8) : (r < a.R ? r : 0);
     const T* Xr[NB];
 #pragma unroll
-    for (int sp = 0; sp < NB; ++sp) Xr[sp] = reinterpret_cast<const T*>(a.X) + (size_t)sp * a.xplane + ((size_t)(ks0 + w) * 64 + lane) * KF;
+    for (int sp = 0; sp < NB; ++sp)
+        Xr[sp] = reinterpret_cast<const T*>(a.X) + (size_t)sp * a.xplane + ((size_t)(ks0 + w) * 64 + (a.rm ? xr * 4 + g : g * 16 + xr)) * KF;
     f32x4 acc[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -177,7 +179,7 @@ __global__ __launch_bounds__(RING_THREADS) void gemm_ring_kernel(GemmArgs a) {
                 float y[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) { y[i] = xv[i] * res_g[i]; ss += xv[i] * xv[i]; }
-                Traits<T>::template store_split4<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, col, a.N), a.actplane, y);
+                Traits<T>::template store_split4<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, col, a.N, a.rm), a.actplane, y);
             }
             ss += __shfl_xor(ss, 1, 64);
             ss += __shfl_xor(ss, 2, 64);
@@ -196,7 +198,7 @@ __global__ __launch_bounds__(RING_THREADS) void gemm_ring_kernel(GemmArgs a) {
                 float y[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) y[i] = v[i] / (1.0f + expf(-v[i])) * up[i];
-                Traits<T>::template store_split4<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, (nt0 + t) * 8 + n0, a.N / 2), a.actplane, y);
+                Traits<T>::template store_split4<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, (nt0 + t) * 8 + n0, a.N / 2, a.rm), a.actplane, y);
             }
         }
         return;

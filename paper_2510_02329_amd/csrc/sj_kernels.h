@@ -30,7 +30,7 @@ __global__ void retile_kernel(const T* __restrict__ src, T* __restrict__ dst, in
     }
 }
 
-// K/V upload of one (seq, layer): host layout [Hkv][len][hd] -> K [Hkv][cap][hd], V [Hkv][hd][cap].
+// K/V upload of one (seq, layer): host layout [Hkv][len][hd] -> fragments (kv_k_off, kv_v_off).
 template <typename T>
 __global__ void kv_scatter_kernel(const T* __restrict__ ksrc, const T* __restrict__ vsrc, T* __restrict__ K,
                                   T* __restrict__ V, int Hkv, int len, int cap, int hd) {
@@ -40,8 +40,8 @@ __global__ void kv_scatter_kernel(const T* __restrict__ ksrc, const T* __restric
         const int dcol = (int)(idx % hd);
         const int pos = (int)((idx / hd) % len);
         const int h = (int)(idx / ((size_t)hd * len));
-        K[((size_t)h * cap + pos) * hd + dcol] = ksrc[idx];
-        V[((size_t)h * hd + dcol) * cap + pos] = vsrc[idx];
+        K[(size_t)h * cap * hd + kv_k_off<T>(pos, dcol, hd)] = ksrc[idx];
+        V[(size_t)h * cap * hd + kv_v_off<T>(pos, dcol, hd)] = vsrc[idx];
     }
 }
 
@@ -54,8 +54,8 @@ __global__ void kv_gather_kernel(T* __restrict__ kdst, T* __restrict__ vdst, con
         const int dcol = (int)(idx % hd);
         const int pos = pos0 + (int)((idx / hd) % n);
         const int h = (int)(idx / ((size_t)hd * n));
-        kdst[idx] = K[((size_t)h * cap + pos) * hd + dcol];
-        vdst[idx] = V[((size_t)h * hd + dcol) * cap + pos];
+        kdst[idx] = K[(size_t)h * cap * hd + kv_k_off<T>(pos, dcol, hd)];
+        vdst[idx] = V[(size_t)h * cap * hd + kv_v_off<T>(pos, dcol, hd)];
     }
 }
 
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(1024) void step_begin_kernel(StepParams* __restrict
                                                           const int32_t* __restrict__ pending, float* __restrict__ x,
                                                           float* __restrict__ cs, int32_t* __restrict__ row_tok,
                                                           double log_base, const T* __restrict__ gain, T* __restrict__ xn,
-                                                          size_t xplane) {
+                                                          size_t xplane, int rm) {
     __shared__ float red[16];
     const int r = blockIdx.x;
     const int rps = sp->rps;
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(1024) void step_begin_kernel(StepParams* __restrict
             float y[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) y[i] = v[p][i] * inv * Traits<T>::load(gain + c + i);
-            Traits<T>::template store_split4<SPL>(xn + opnd_off<T>(r, c, md.d), xplane, y);
+            Traits<T>::template store_split4<SPL>(xn + opnd_off<T>(r, c, md.d, rm), xplane, y);
         }
     }
 }
@@ -160,7 +160,7 @@ template <typename T, int PB, int SPL>
 __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(int R, int d, float eps, float* __restrict__ x,
                                                            const float* __restrict__ part, int nparts,
                                                            const T* __restrict__ gain, T* __restrict__ xn,
-                                                           size_t xplane, float* __restrict__ xn32) {
+                                                           size_t xplane, float* __restrict__ xn32, int rm) {
     // one workgroup of 1024 threads per row, 4 columns per thread and pass; all loads of a pass are
     // independent.  Rows wider than 16384 columns are not supported (host-checked).
     constexpr int MAXP = 4;
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(int R, int d, float e
             float y[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) y[i] = v[p][i] * inv * Traits<T>::load(gain + c + i);
-            Traits<T>::template store_split4<SPL>(xn + opnd_off<T>(r, c, d), xplane, y);
+            Traits<T>::template store_split4<SPL>(xn + opnd_off<T>(r, c, d, rm), xplane, y);
             if (xn32) *reinterpret_cast<f32x4*>(xn32 + (size_t)r * d + c) = f32x4{y[0], y[1], y[2], y[3]};
         }
     }
@@ -226,6 +226,7 @@ struct GemmArgs {
     size_t xplane;      // elements between consecutive planes of X
     size_t actplane;    // same for act
     int32_t K, N, R;
+    int32_t rm;         // few-row kernels: operand and result planes have rows side by side in a block (opnd_off)
     int32_t slice_rows; // EPI_PARTIAL: rows between consecutive K-slices of out (>= R)
     float* out;         // EPI_PARTIAL: [gridDim.y][slice_rows][N] fp32;  EPI_LOGITS: [R][N] fp32
     void* act;          // EPI_SWIGLU: planes of rows of width N/2 (opnd_off), storage dtype = silu(gate) * up
@@ -265,7 +266,7 @@ __device__ __forceinline__ void few_epilogue(const GemmArgs& a, const float (&v)
             if (row < a.R) {
                 xv = a.x[(size_t)row * a.N + col] + v[t];
                 a.x[(size_t)row * a.N + col] = xv;
-                Traits<T>::template store_split<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, col, a.N), a.actplane,
+                Traits<T>::template store_split<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, col, a.N, a.rm), a.actplane,
                                                      xv * Traits<T>::load(reinterpret_cast<const T*>(a.gain) + col));
             }
             float ss = xv * xv;
@@ -287,7 +288,7 @@ __device__ __forceinline__ void few_epilogue(const GemmArgs& a, const float (&v)
             if (row < a.R && en < 8) {
                 const float gate = v[t];
                 const float y = gate / (1.0f + expf(-gate)) * up;
-                Traits<T>::template store_split<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, (nt0 + t) * 8 + en, a.N / 2),
+                Traits<T>::template store_split<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, (nt0 + t) * 8 + en, a.N / 2, a.rm),
                                                      a.actplane, y);
             }
         }
@@ -344,10 +345,13 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(GemmArgs a) {
     const int parts = gridDim.y * WAVES, part = blockIdx.y * WAVES + w;
     const int ks0 = (int)((long long)part * KS / parts), ks1 = (int)((long long)(part + 1) * KS / parts);
     const u32x4* Wt = reinterpret_cast<const u32x4*>(a.Wt) + ((size_t)nt0 * KS + ks0) * 64 + lane;
-    // padding rows (>= R, stale memory) feed columns of D that are never stored
+    // padding rows (>= R) feed columns of D that are never stored: their lanes repeat row 0 of the tile
     const T* Xr[MT];
 #pragma unroll
-    for (int m = 0; m < MT; ++m) Xr[m] = reinterpret_cast<const T*>(a.X) + (((size_t)m * KS + ks0) * 64 + lane) * KF;
+    for (int m = 0; m < MT; ++m) {
+        const int xr = m * 16 + r < a.R ? r : 0;
+        Xr[m] = reinterpret_cast<const T*>(a.X) + (((size_t)m * KS + ks0) * 64 + (a.rm ? xr * 4 + g : g * 16 + xr)) * KF;
+    }
 
     f32x4 acc[NT][MT];
 #pragma unroll

@@ -103,7 +103,7 @@ struct Forward {
 
 struct sj_kv : Forward {       // the inherited buffers serve the blocks of up to max_gamma + 1 rows per sequence
     const sj_model* m = nullptr;
-    int batch = 0, max_rows = 0, mpad = 0;
+    int batch = 0, max_rows = 0, mpad = 0, cap_max = 64;
     Forward chunk;             // those of a prompt chunk of sj_prefill
     int pf_rows = 0;           // rows of one prompt chunk of sj_prefill (0: chunks of max_gamma + 1 rows)
     std::vector<int32_t> cap, len_upper;
@@ -476,6 +476,7 @@ extern "C" int sj_kv_create(const sj_model* m, int32_t batch, const int32_t* cap
         off += (int64_t)cp * c.n_kv_heads * c.head_dim;
         cap_max = std::max(cap_max, cp);
     }
+    kv->cap_max = cap_max;
     kv->layer_stride = off;
     const int R = batch * (c.max_gamma + 1);
     kv->max_rows = R;
@@ -851,15 +852,19 @@ extern "C" int sj_kv_state(const sj_kv* kv, int32_t* len_host, int32_t* pending_
 // multiple of NT), WAVES waves split the K-slice, D = depth of the register ring.
 // What a few-row product knows of its surroundings: whether its operand and result planes are packed (gemm_ring_kernel), and of
 // the norms around it `ss_in` when its operand lacks the 1/rms factor, the others for EPI_RESID (GemmArgs).
+constexpr int RM_ROWS = 2;             // packed planes of up to this many rows keep a row's lane groups side by side
+template <typename T> constexpr size_t packed_plane(int rm) { return rm ? 8 * Traits<T>::KSTEP : 8 * Traits<T>::KF; }
 struct FewArgs {
     bool packed = false;
+    int rm = 0;                        // inner order of packed planes (opnd_off)
     const float* ss_in = nullptr;
     float eps = 0.f;
     float* x = nullptr;
     const void* gain = nullptr;
     float* ss_out = nullptr;
     template <typename T> void put(GemmArgs& a) const {
-        if (packed) a.xplane = a.actplane = 8 * Traits<T>::KF;
+        if (packed) a.xplane = a.actplane = packed_plane<T>(rm);
+        a.rm = rm;
         a.ss_in = ss_in; a.eps = eps; a.x = x; a.gain = gain; a.ss_out = ss_out;
     }
 };
@@ -1079,6 +1084,7 @@ static int tune_one(sj_kv* kv, GemmPlan& plan, void* LayerW::*which, const void*
     const size_t xplane = (size_t)kv->rpad * K;
     FewArgs fa;
     fa.packed = packed_rows<T, SPL>(rows);
+    fa.rm = fa.packed && rows <= RM_ROWS;
     auto time_plan = [&](const GemmPlan& p, double& us) -> int {
         float ms = 0.f;
         for (int rep = 0; rep < 2; ++rep) {                 // the first repetition warms up
@@ -1131,6 +1137,7 @@ static int tune_gate_up(sj_kv* kv, int rows, hipEvent_t e0, hipEvent_t e1) {
     const int nl = std::min(m->cfg.n_layers, 16);
     FewArgs fa;
     fa.packed = packed_rows<T, SPL>(rows);
+    fa.rm = fa.packed && rows <= RM_ROWS;
     auto time_plan = [&](const GemmPlan& p, double& us) -> int {
         float ms = 0.f;
         for (int rep = 0; rep < 2; ++rep) {                 // the first repetition warms up
@@ -1174,6 +1181,7 @@ static int tune_lm_head(sj_kv* kv, int rows, hipEvent_t e0, hipEvent_t e1) {
     const int d = m->cfg.d_model, V = m->cfg.vocab;
     FewArgs fa;
     fa.packed = packed_rows<T, SPL>(rows);
+    fa.rm = fa.packed && rows <= RM_ROWS;
     auto time_plan = [&](const GemmPlan& p, double& us) -> int {
         float ms = 0.f;
         for (int rep = 0; rep < 2; ++rep) {                 // the first repetition warms up
@@ -1314,11 +1322,13 @@ static int gemm_rows(hipStream_t st, const void* Wt, const void* X, size_t xplan
     return SJ_OK;
 }
 
-// Blocks whose attention runs in two launches: more rows than the few-row kernels take, and at least one full query tile per kv
-// head and sequence.
-static bool many_rows_attention(const ModelDims& md, int rows, int rps) {
-    static const bool off = std::getenv("SJ_NO_ROWS_ATTN") != nullptr;
-    return !off && rows > FEW_ROWS && rps * md.G >= 16;
+// Blocks whose attention runs in two launches: more rows than the few-row kernels take, at least one full query tile per kv head
+// and sequence, and contexts of at most 2048 keys.  The single launch sums and rotates the query rows again for every key range
+// (score block of 6 x 21 rows, up to 721 keys: 83 us a layer against 26); with long contexts that work is small beside the keys, and
+// its split of a sequence's keys over workgroups balances a ragged batch better (16 x 9 rows, up to 4096 keys: 69 against 81).
+constexpr int ROWS_ATTN_KEYS = 2048;
+static bool many_rows_attention(const ModelDims& md, int rows, int rps, int cap_max) {
+    return rows > FEW_ROWS && rps * md.G >= 16 && cap_max <= ROWS_ATTN_KEYS;
 }
 
 template <typename T, int SPL>
@@ -1336,7 +1346,8 @@ struct Runner {
         return v;
     }
     bool packed() const { return packed_rows<T, SPL>(R); }
-    size_t plane(int ld) const { return packed() ? 8 * Traits<T>::KF : (size_t)w->rpad * ld; }
+    int rm() const { return packed() && R <= RM_ROWS; }
+    size_t plane(int ld) const { return packed() ? packed_plane<T>(rm()) : (size_t)w->rpad * ld; }
     // Launch shape of a split-K projection for this row count.  A prompt chunk of at most 32 rows can have more rows than
     // the plan was made for: the LDS-ring shape then gives way to the register-ring kernel's rule shape.
     GemmPlan plan_of(const GemmPlan (&pl)[2], int K, int N) const {
@@ -1360,6 +1371,7 @@ struct Runner {
     FewArgs few_args(bool unscaled) const {
         FewArgs n;
         n.packed = packed();
+        n.rm = rm();
         if (unscaled) { n.ss_in = w->ss; n.eps = m->md.eps; }
         return n;
     }
@@ -1397,7 +1409,7 @@ struct Runner {
     // rotary + cache append + attention of one layer from the QKV partials in w->part
     int attention(int layer, int parts) {
         const ModelDims& md = m->md;
-        if (rps > m->cfg.max_gamma + 1 || many_rows_attention(md, R, rps)) return rows_attention(layer, parts);
+        if (rps > m->cfg.max_gamma + 1 || many_rows_attention(md, R, rps, kv->cap_max)) return rows_attention(layer, parts);
         const int M = md.G * rps;
         const int mtiles = (M + 15) / 16;
         // one query tile per workgroup while the launch stays small (shortest dependent chain per wave;
@@ -1410,7 +1422,7 @@ struct Runner {
 #define ATTN_PB(HD, MQ, PB)                                                                                            \
     attn_fused_kernel<T, HD, MQ, SPL, PB><<<grid, 256, 0, st>>>(kv->sp_dev, md, w->part, parts, R, w->cs, view(), \
                                                                 layer, kv->chunk_keys, kv->nchunk_max, kv->opart, kv->tickets,  \
-                                                                (T*)w->attn_out, plane(md.Hq * md.hd))
+                                                                (T*)w->attn_out, plane(md.Hq * md.hd), rm())
 #define ATTN(HD, MQ)                                                                                                   \
     do { if (pb2) ATTN_PB(HD, MQ, 2); else ATTN_PB(HD, MQ, 4); } while (0)
         if (md.hd == 128) {
@@ -1431,15 +1443,16 @@ struct Runner {
         u32x4* qbuf = (u32x4*)w->act;
         // waves per tile: as many as leave a workgroup for every CU
         const long long tiles = (long long)ntiles * md.Hkv * nseq;
-        int kw = tiles >= 1024 ? 2 : tiles >= 512 ? 4 : 8;
-        if (const char* e = std::getenv("SJ_KW")) kw = std::atoi(e);
+        const int kw = tiles >= 1024 ? 2 : tiles >= 512 ? 4 : 8;
         const int grid = (ntiles * kw + ROWS_WAVES - 1) / ROWS_WAVES * ((nseq * md.Hkv + 7) / 8 * 8);
 #define ROWS_ATTN_KW(HD, KW)                                                                                           \
     rows_attn_kernel<T, HD, KW, SPL><<<grid, ROWS_WAVES * 64, 0, st>>>(kv->sp_dev, md, view(), layer, qbuf, ntiles,    \
                                                                        (T*)w->attn_out, plane(md.Hq * md.hd))
 #define ROWS_ATTN(HD)                                                                                                  \
     do {                                                                                                               \
-        rows_rotary_kernel<T, HD, SPL><<<dim3(blocks, 3 * md.Hkv, nseq), 256, 0, st>>>(kv->sp_dev, md, w->part, parts, R, w->cs, view(), layer, qbuf, ntiles); \
+        const dim3 rgrid(blocks, 3 * md.Hkv, nseq);                                                                    \
+        if (parts <= 2) rows_rotary_kernel<T, HD, SPL, 2><<<rgrid, 256, 0, st>>>(kv->sp_dev, md, w->part, parts, R, w->cs, view(), layer, qbuf, ntiles); \
+        else rows_rotary_kernel<T, HD, SPL, 6><<<rgrid, 256, 0, st>>>(kv->sp_dev, md, w->part, parts, R, w->cs, view(), layer, qbuf, ntiles); \
         LAUNCHCHK("rows_rotary");                                                                                      \
         if (kw == 2) ROWS_ATTN_KW(HD, 2); else if (kw == 4) ROWS_ATTN_KW(HD, 4); else ROWS_ATTN_KW(HD, 8);             \
         LAUNCHCHK("rows_attn");                                                                                        \
@@ -1452,15 +1465,15 @@ struct Runner {
 
     // residual add of `parts` pending split-K partials + RMSNorm into the operand planes (batches of loads as wide as
     // the partials there are: an eight-wide clamped batch for two partials repeats six loads)
-    void norm(int parts, const void* gain, float* xn32) { norm_rows(parts, gain, xn32, 0, R, 0, plane(m->md.d)); }
+    void norm(int parts, const void* gain, float* xn32) { norm_rows(parts, gain, xn32, 0, R, 0, plane(m->md.d), rm()); }
     // rows r0 .. r0 + n - 1 of the block into rows 0 .. of the operand planes and rows o0 .. of xn32
-    void norm_rows(int parts, const void* gain, float* xn32, int r0, int n, int o0, size_t oplane) {
+    void norm_rows(int parts, const void* gain, float* xn32, int r0, int n, int o0, size_t oplane, int orm) {
         const int d = m->md.d;
         float *x = w->x + (size_t)r0 * d, *part = w->part + (size_t)r0 * d, *h = xn32 ? xn32 + (size_t)o0 * d : nullptr;
         T* xn = (T*)w->xn;
-        if (parts <= 2) add_rmsnorm_kernel<T, 2, SPL><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, oplane, h);
-        else if (parts <= 4) add_rmsnorm_kernel<T, 4, SPL><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, oplane, h);
-        else add_rmsnorm_kernel<T, 8, SPL><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, oplane, h);
+        if (parts <= 2) add_rmsnorm_kernel<T, 2, SPL><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, oplane, h, orm);
+        else if (parts <= 4) add_rmsnorm_kernel<T, 4, SPL><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, oplane, h, orm);
+        else add_rmsnorm_kernel<T, 8, SPL><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, oplane, h, orm);
     }
 
     // decoder layers (Eq. 2 / Eq. 4): leaves the last down-projection's K-slices pending in w->part (their number in `parts`)
@@ -1469,7 +1482,7 @@ struct Runner {
         const sj_config& c = m->cfg;
         const int d = md.d, Nq = md.Hq * md.hd, Nk = md.Hkv * md.hd, Nqkv = Nq + 2 * Nk;
         step_begin_kernel<T, SPL><<<R, 1024, 0, st>>>(kv->sp_dev, md, (const T*)m->embed, kv->len_dev, kv->pending_dev, w->x, w->cs, w->row_tok,
-                                                  std::log((double)c.rope_base), (const T*)m->layers[0].attn_norm, (T*)w->xn, plane(d));
+                                                  std::log((double)c.rope_base), (const T*)m->layers[0].attn_norm, (T*)w->xn, plane(d), rm());
         LAUNCHCHK("step_begin");
         parts = 0;
         bool unscaled = false;
@@ -1977,8 +1990,8 @@ static int prefill_impl(sj_model* m, sj_kv* kv, int seq, const int32_t* tokens, 
                 head_rows = n - (n - 1) / block * block;
                 const int keep = std::min(block, cn);          // chunks are longer than a block: cn > block
                 Runner<T, SPL> head{m, kv, st, 1, head_rows, head_rows, fw};
-                if (keep > head_rows) run.norm_rows(parts, m->final_norm, kv->hn32, cn - keep, keep - head_rows, head_rows, run.plane(m->md.d));   // (its operand rows give way to the next ones)
-                run.norm_rows(parts, m->final_norm, kv->hn32, cn - head_rows, head_rows, 0, head.plane(m->md.d));
+                if (keep > head_rows) run.norm_rows(parts, m->final_norm, kv->hn32, cn - keep, keep - head_rows, head_rows, run.plane(m->md.d), 0);   // (its operand rows give way to the next ones)
+                run.norm_rows(parts, m->final_norm, kv->hn32, cn - head_rows, head_rows, 0, head.plane(m->md.d), head.rm());
                 LAUNCHCHK("add_rmsnorm");
             }
         }

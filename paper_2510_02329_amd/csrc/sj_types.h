@@ -34,9 +34,25 @@ struct ModelDims {
     float eps, inv_temp, temperature, scale;   // scale = 1/sqrt(hd)
 };
 
-// KV cache view.  K of (layer, seq): [Hkv][cap][hd]; V is stored transposed: [Hkv][hd][cap], so that
-// both MFMA operands of attention are 16-byte contiguous loads.  seq_off[b] = element offset of
-// sequence b inside one layer; layer_stride = elements per layer.
+// KV cache view.  K and V of (layer, seq, kv head): `cap` positions in blocks of KSTEP (capacities are multiples of 64), each block
+// the MFMA fragments that attention multiplies, in lane order (16 bytes a lane, 1 KB a fragment): a wave's load is consecutive
+// memory.  (With rows of head-dim elements, and V as rows of positions, every lane's 16 bytes were a look-up of their own in the
+// vector cache: 62 a load.)  K fragments [t][head-dim step]: row r of fragment t is key KF * (r / 4) + 4 t + r % 4 of the block,
+// the order in which the accumulators of K . Q^T are the second product's operand; V fragments [16 head-dim columns]: rows are
+// columns, the contraction runs over the block's keys.  seq_off[b] = element offset of sequence b inside one layer; layer_stride =
+// elements per layer.
+template <typename T>
+__host__ __device__ __forceinline__ size_t kv_k_off(int pos, int c, int hd) {
+    constexpr int KF = Traits<T>::KF, KSTEP = Traits<T>::KSTEP;
+    const int i = pos % KSTEP, r = i / KF * 4 + i % 4, t = i % KF / 4;
+    return (size_t)(pos / KSTEP) * KSTEP * hd + (size_t)(((t * (hd / KSTEP) + c / KSTEP) * 4 + c % KSTEP / KF) * 16 + r) * KF + c % KF;
+}
+template <typename T>
+__host__ __device__ __forceinline__ size_t kv_v_off(int pos, int c, int hd) {
+    constexpr int KF = Traits<T>::KF, KSTEP = Traits<T>::KSTEP;
+    const int i = pos % KSTEP;
+    return (size_t)(pos / KSTEP) * KSTEP * hd + (size_t)((c / 16 * 4 + i / KF) * 16 + c % 16) * KF + i % KF;
+}
 template <typename T> struct KvView {
     T* K;
     T* V;
