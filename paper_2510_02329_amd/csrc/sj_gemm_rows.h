@@ -248,9 +248,10 @@ constexpr int R4_LW = 4;           // loader waves: two for the weights, two for
 // the pace, and 12 % slower on the one-plane LM head of the verify-head workload (909 -> 799 us).
 constexpr int R8_CW = 8;
 
-// RT = row tiles of a row group: 9 (144 rows), or 18 with a single operand plane (288 rows: the same 18 operand
+// RT = row tiles of a row group: up to 9 (144 rows), or 18 with a single operand plane (288 rows: the same 18 operand
 // fragments per k-step in LDS, half as many workgroups re-reading every weight tile through L2).  A wave owns RT / 4
-// whole row tiles for its half of the n-tiles and n-tile w of each of the RT % 4 tiles left over.
+// whole row tiles for its half of the n-tiles and n-tile w of each of the RT % 4 tiles left over.  Every tile of the group is
+// fetched and multiplied whether it has rows or not, so the group is chosen to fit the rows (row_tiles in sj_lib.hip).
 template <typename T, int EPI, int SPL, int NT = R2_NT, int RT = ROWS_MT>
 __global__ __launch_bounds__((R8_CW + R4_LW) * 64) void gemm_rows8_kernel(GemmArgs a, int mt) {
     static_assert(SPL <= 2, "three operand planes do not fit");
@@ -348,7 +349,7 @@ __global__ __launch_bounds__((R8_CW + R4_LW) * 64) void gemm_rows8_kernel(GemmAr
     const int ra = w & 3, nb = w >> 2;                 // row tiles ra, ra + 4; n-tiles of half nb; n-tile w of row tile 8
     constexpr int NH = 4;                              // n-tiles of half 0 (half 1 has NT - 4)
     const int t0 = nb * NH, nh = nb == 0 ? NH : NT - NH;
-    f32x4 acc[NFULL][NH], acc8[NREM];
+    f32x4 acc[NFULL][NH], acc8[NREM ? NREM : 1];
 #pragma unroll
     for (int i = 0; i < NFULL; ++i)
 #pragma unroll

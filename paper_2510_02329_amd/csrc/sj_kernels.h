@@ -85,6 +85,14 @@ __global__ void set_state_kernel(int32_t* len, int32_t* pending, int seq, int l,
     if (threadIdx.x == 0 && blockIdx.x == 0) { len[seq] = l; pending[seq] = p; }
 }
 
+// lengths and pending tokens of a small batch, given with the launch
+constexpr int REWIND_SEQS = 64;
+struct RewindArgs { int32_t len[REWIND_SEQS], pending[REWIND_SEQS]; };
+__global__ __launch_bounds__(REWIND_SEQS) void rewind_kernel(RewindArgs a, int batch, int32_t* __restrict__ len, int32_t* __restrict__ pending) {
+    const int b = threadIdx.x;
+    if (b < batch) { len[b] = a.len[b]; pending[b] = a.pending[b]; }
+}
+
 // ---------------------------------------------------------------------------------------------
 // Step start (Eq. 2 input): one workgroup of 1024 threads per query row.  Resolves the row's token and position,
 // gathers its embedding into the fp32 residual stream, writes the first layer's normed operand planes (RMSNorm as in

@@ -379,12 +379,27 @@ static GemmPlan plan_partial(int ntiles, int ksteps, bool one_row_tile) {
     return best;
 }
 
+// Row tiles of a row group of the loader-wave kernel: the smallest group that holds all rows, or, with more rows than the largest
+// holds, the one of the two largest that pads them least (equal: fewer groups).  The kernel spends matrix and L2 time on
+// every tile of a group: 126 rows in groups of 144 (score block of 6 x 21, 8B shape): QKV / O / down 30.6 us, LM head 348, in
+// one group of 128: 29.3, 325; 509 rows, 4 x 144 against 4 x 128: gate / up 277 -> 249 us.
+static int row_tiles(int planes, int rows) {
+    static const int one[] = {4, 9, 16, 18}, two[] = {4, 6, 8, 9};
+    if (planes > 2) return ROWS_MT;
+    const int* rt = planes == 1 ? one : two;
+    for (int i = 0; i < 4; ++i)
+        if (rows <= rt[i] * 16) return rt[i];
+    auto padded = [&](int t) { return (rows + t * 16 - 1) / (t * 16) * t; };
+    return padded(rt[2]) < padded(rt[3]) ? rt[2] : rt[3];
+}
+
 // K-slices of a split-K projection on the loader-wave kernel, which works in groups of `group` rows.  One group: the
 // rule's (one round of the chip).  With several, the groups fill the chip by themselves and every further slice costs a
 // write and a read of the partials: the slice count (never above the rule's) with the least estimated time, in units of
 // one k-step of a workgroup (0.58 us on two-plane operands) - rounds of 256 workgroups x (k-steps of a slice + 5 for ramp
 // and epilogue) + the partials' bytes at 4 TB/s.
-static int rows_split(int rule, int ntiles, int ksteps, int rows, int group) {
+static int rows_split(int rule, int ntiles, int ksteps, int rows, int planes) {
+    const int group = row_tiles(planes, rows) * 16;
     if (rows <= group) return rule;
     const int rgroups = (rows + group - 1) / group, wgs = (ntiles + 7) / 8 * rgroups;
     int best = 1;
@@ -396,22 +411,20 @@ static int rows_split(int rule, int ntiles, int ksteps, int rows, int group) {
     }
     return best;
 }
-constexpr int row_group(int planes) { return planes == 1 ? 2 * ROWS_MT * 16 : ROWS_MT * 16; }
-
 // fp32 elements of the partials of a projection with up to `rows` rows on the loader-wave kernel, whatever the plane count
-// (the slice count depends on the number of row groups alone)
+// (slices and group depend on the rows in steps of 16)
 static size_t rows_part_elems(int rule, int N, int ksteps, int rows) {
     size_t most = 0;
     for (int planes = 1; planes <= 2; ++planes)
-        for (int group = row_group(planes), r = 0; r < rows; r += group) {
-            const int upto = std::min(r + group, rows);
-            most = std::max(most, (size_t)rows_split(rule, N / 16, ksteps, upto, group) * upto * N);
+        for (int r = 0; r < rows; r += 16) {
+            const int upto = std::min(r + 16, rows);
+            most = std::max(most, (size_t)rows_split(rule, N / 16, ksteps, upto, planes) * upto * N);
         }
     return most;
 }
 
-// Rows of one prompt chunk.  Every chunk streams all weights once, so a chunk should be as long as the work it brings
-// outweighs that: four row groups of the loader-wave kernel (the two-plane products of 576 rows take 4 x the time of the
+// Rows of one prompt chunk.  Every chunk streams all weights once, so a chunk should be so long that its work outweighs
+// that: four row groups of the loader-wave kernel (the two-plane products of 576 rows take 5 x the time of the
 // weight stream).
 constexpr int PREFILL_ROWS = 4 * ROWS_MT * 16;
 
@@ -630,6 +643,14 @@ extern "C" int sj_kv_rewind(sj_kv* kv, const int32_t* len_host, const int32_t* p
         if (pending_host[b] < 0 || pending_host[b] >= kv->m->cfg.vocab) return fail(SJ_EINVAL, "pending[%d] out of range", b);
     }
     hipStream_t st = (hipStream_t)stream;
+    if (kv->batch <= REWIND_SEQS) {                            // the values travel as kernel arguments: no staging, no copy
+        RewindArgs a{};
+        for (int b = 0; b < kv->batch; ++b) { a.len[b] = len_host[b]; a.pending[b] = pending_host[b]; }
+        rewind_kernel<<<1, REWIND_SEQS, 0, st>>>(a, kv->batch, kv->len_dev, kv->pending_dev);
+        LAUNCHCHK("rewind");
+        for (int b = 0; b < kv->batch; ++b) kv->len_upper[b] = len_host[b];
+        return SJ_OK;
+    }
     if (!kv->pinned_state) {
         HIPCHK(hipHostMalloc((void**)&kv->pinned_state, sizeof(int32_t) * 2 * kv->batch, hipHostMallocDefault));
         HIPCHK(hipEventCreateWithFlags(&kv->rewind_done, hipEventDisableTiming));
@@ -661,12 +682,12 @@ extern "C" int sj_kernel_class_shape(const sj_kv* kv, int32_t kernel_class, int3
     if (rows > FEW_ROWS) {
         const sj_config& c = kv->m->cfg;
         const int Nq = c.n_q_heads * c.head_dim, kstep = c.dtype == SJ_DTYPE_FP32 ? 16 : 32;
-        const int group = row_group(c.dtype == SJ_DTYPE_FP32 ? 1 : kv->planes);
+        const int planes = c.dtype == SJ_DTYPE_FP32 ? 1 : kv->planes;
         const GemmPlan* p = kernel_class == 1 ? &kv->plan_qkv[1] : kernel_class == 2 ? &kv->plan_o[1] : kernel_class == 4 ? &kv->plan_d[1] : nullptr;
         const int N = kernel_class == 1 ? Nq + 2 * c.n_kv_heads * c.head_dim : c.d_model;
         const int K = kernel_class == 1 ? c.d_model : kernel_class == 2 ? Nq : c.d_ffn;
         snprintf(buf, (size_t)buf_len, "gemm_rows%s: row groups of %d in one launch, 8 or 7 n-tiles per workgroup, %d K-slice(s)",
-                 kv->planes == 3 ? "2" : "8", group, p ? rows_split(p->split, N / 16, K / kstep, rows, group) : 1);
+                 kv->planes == 3 ? "2" : "8", row_tiles(planes, rows) * 16, p ? rows_split(p->split, N / 16, K / kstep, rows, planes) : 1);
         return SJ_OK;
     }
     GemmPlan p = kernel_class == 1 ? kv->plan_qkv[0] : kernel_class == 2 ? kv->plan_o[0] : kernel_class == 3 ? kv->plan_gu
@@ -1276,9 +1297,7 @@ static int gemm_rows(hipStream_t st, const void* Wt, const void* X, size_t xplan
                      float* out, void* act, size_t actplane, float4* stats, float inv_temp) {
     const int ntiles = N / 16;
     // a group of rows (whole row tiles) starts row0 * K elements into the plane
-    // a single operand plane: row groups of 288 (the 18 operand fragments of a k-step fill the same LDS stages)
-    constexpr int RT = (SPL == 1) ? 2 * ROWS_MT : ROWS_MT;
-    const int group_rows = RT * 16;
+    const int rt = row_tiles(SPL, rows), group_rows = rt * 16;
     auto args_of = [&](int row0, int nr) {
         GemmArgs a{};
         a.Wt = Wt;
@@ -1301,14 +1320,34 @@ static int gemm_rows(hipStream_t st, const void* Wt, const void* X, size_t xplan
         const int mt = (std::min(rows, group_rows) + 15) / 16;
         GemmArgs a = args_of(0, rgroups > 1 ? rows : std::min(rows, group_rows));
         a.rgroups = rgroups;
-        const bool seven = EPI == EPI_SWIGLU && mt >= 8 && ntiles % 7 == 0 && (ntiles / 7) % 256 == 0 && ((ntiles + 7) / 8) % 256 != 0;
+        const bool seven = EPI == EPI_SWIGLU && mt >= 8 && rt >= 8 && ntiles % 7 == 0 && (ntiles / 7) % 256 == 0 && ((ntiles + 7) / 8) % 256 != 0;
         const int per = seven ? 7 : R2_NT, ngroups = (ntiles + per - 1) / per;
         const int gx = rgroups > 1 ? (ngroups + 7) / 8 * 8 * rgroups : ngroups;
         const dim3 grid(gx, EPI == EPI_PARTIAL ? split : 1);
-        if constexpr (EPI == EPI_SWIGLU) {
-            if (seven) gemm_rows8_kernel<T, EPI, SPL, 7, RT><<<grid, (R8_CW + R4_LW) * 64, 0, st>>>(a, mt);
+        auto launch = [&](auto rt_tag) {
+            constexpr int RT = decltype(rt_tag)::value;
+            if constexpr (RT * SPL <= 2 * ROWS_MT) {
+                if constexpr (EPI == EPI_SWIGLU && RT >= 8) {
+                    if (seven) gemm_rows8_kernel<T, EPI, SPL, 7, RT><<<grid, (R8_CW + R4_LW) * 64, 0, st>>>(a, mt);
+                }
+                if (!seven) gemm_rows8_kernel<T, EPI, SPL, R2_NT, RT><<<grid, (R8_CW + R4_LW) * 64, 0, st>>>(a, mt);
+            }
+        };
+        if constexpr (SPL == 1) {
+            switch (rt) {
+                case 4: launch(std::integral_constant<int, 4>{}); break;
+                case 9: launch(std::integral_constant<int, 9>{}); break;
+                case 16: launch(std::integral_constant<int, 16>{}); break;
+                default: launch(std::integral_constant<int, 18>{}); break;
+            }
+        } else {
+            switch (rt) {
+                case 4: launch(std::integral_constant<int, 4>{}); break;
+                case 6: launch(std::integral_constant<int, 6>{}); break;
+                case 8: launch(std::integral_constant<int, 8>{}); break;
+                default: launch(std::integral_constant<int, 9>{}); break;
+            }
         }
-        if (!seven) gemm_rows8_kernel<T, EPI, SPL, R2_NT, RT><<<grid, (R8_CW + R4_LW) * 64, 0, st>>>(a, mt);
         LAUNCHCHK("gemm_rows");
     } else {
         for (int row0 = 0; row0 < rows; row0 += group_rows) {
@@ -1354,7 +1393,7 @@ struct Runner {
         const int ksteps = K / Traits<T>::KSTEP;
         if (R > FEW_ROWS) {
             GemmPlan p = pl[1];
-            p.split = rows_split(p.split, N / 16, ksteps, R, row_group(SPL));
+            p.split = rows_split(p.split, N / 16, ksteps, R, SPL);
             return p;
         }
         if (pl[0].waves == RING_WAVES && !ring_fits(pl[0], N / 16, ksteps, R, SPL, std::is_same<T, bf16_t>::value)) return plan_partial(N / 16, ksteps, true);

@@ -1,0 +1,45 @@
+"""GPU parity of the many-row GEMM over its row-group sizes: one group that fits the rows, several groups, remainders of every kind,
+one, two and three operand planes - as verification steps and as the head alone."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import paper_2510_02329_amd as sj
+import synth
+from oracle import selfjudge_oracle as orc
+from tests import gpu_common as G
+from tests import helpers
+from tests.test_gpu_bf16 import SMALL, _fill_caches
+
+pytestmark = pytest.mark.gpu
+
+
+# rows = batch * (gamma + 1): edges of the groups of 64, 96, 128, 144 (two planes), 64, 144, 256, 288 (one), and two groups
+@pytest.mark.parametrize("batch,gamma,planes,dtype", [(11, 2, 2, "bf16"), (16, 3, 2, "bf16"), (13, 4, 2, "bf16"), (12, 7, 2, "bf16"), (14, 8, 2, "bf16"),
+                                                      (16, 7, 2, "bf16"), (15, 8, 2, "bf16"), (16, 8, 2, "bf16"), (29, 4, 2, "bf16"), (37, 6, 2, "bf16"),
+                                                      (13, 4, 1, "bf16"), (17, 8, 1, "bf16"), (32, 8, 1, "bf16"), (13, 4, 3, "bf16"),
+                                                      (9, 3, 1, "fp32"), (29, 4, 1, "fp32")])
+def test_step_over_row_groups(batch, gamma, planes, dtype):
+    shape = dataclasses.replace(SMALL, name=f"groups_{batch}_{gamma}_{planes}_{dtype}", dtype=dtype, n_layers=1, batch=batch, gamma=gamma)
+    src = synth.WeightSource(shape, seed=51, norm_jitter=0.1)
+    lens = [(7 * b) % 40 for b in range(batch)]
+    cap = [64] * batch
+    gpu = G.Gpu(shape, src, cap)
+    try:
+        if dtype == "bf16":
+            sj.sj_set_operand_planes(gpu.kv, planes)
+        cfg = helpers.oracle_config(shape)
+        W = helpers.oracle_weights(src)
+        caches = _fill_caches(shape, gpu, cfg, lens, seed=52, capacity=cap)
+        draft = synth.make_draft(shape, seed=53)
+        out = gpu.step(draft, 0.5, gamma)
+        fw = orc.block_forward(cfg, W, caches, [[caches[b].pending] + draft["tokens"][b].tolist() for b in range(batch)])
+        scale = 20.0 if dtype == "bf16" and planes == 1 else 1.0       # one plane rounds every operand to 8 bits
+        for b in range(batch):
+            G.close_enough(out["hn"][b], fw[b]["hn"], dtype, f"hidden seq {b}", scale=scale)
+            G.close_enough(out["logits"][b], fw[b]["logits"], dtype, f"logits seq {b}", scale=scale)
+        bad, _ = G.replay_matches(shape, out, draft, 0.5)
+        assert not bad, bad
+    finally:
+        gpu.close()
