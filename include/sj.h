@@ -219,7 +219,7 @@ int sj_verify_head_static(sj_model* m, int32_t batch, int32_t gamma, const void*
  *   passes [n_C] (may be NULL)               HOST out: passes over H_train the solver made
  *   best_index, w_best [d + 1], theta_f1, theta_recall   HOST out: the kept model (w, then b) and its thresholds
  * Everything is computed on the device in fp64 (features read as fp32); the call allocates its workspace
- * (about 8 (n_train + 3 n_val) + 2 MB * (d / 1024) bytes), synchronises `stream` and frees it before returning.
+ * (about 32 n_train + 16 n_val min(n_C, 2^22 / n_val) + 8 MB * (d / 1024) bytes), synchronises `stream` and frees it before returning.
  * Errors: SJ_EINVAL (null / misaligned pointer, sizes, a label other than 0 / 1, a set with one class only,
  * non-positive C), SJ_ENOMEM, SJ_EHIP (also when the solver fails to converge). */
 int sj_judge_train(const float* H_train, const int32_t* y_train, int64_t n_train, const float* H_val,

@@ -3,8 +3,9 @@
 // rotate the query rows they need and keep the block's own K / V rows in LDS; with many rows that work is repeated for every key
 // range.  Here it is done once:
 //
-//  rows_rotary_kernel  (a workgroup each for queries, keys and values) sums the QKV split-K partials of 16 positions x one kv head, rotates Q and K, appends K and (through LDS,
-//                      transposed) V to the cache and writes the query rows as MFMA fragments;
+//  rows_rotary_kernel  (a workgroup each for queries, keys and values) sums the QKV split-K partials of 16 positions x one kv
+//                      head, rotates Q and K, appends K and (through LDS, transposed) V to the cache and writes the query rows as
+//                      MFMA fragments;
 //  rows_attn_kernel    reads the cache only: a workgroup of eight waves takes 8 / KW tiles of 16 query columns, KW waves share a
 //                      tile's keys (every KW-th step of 32) and meet in LDS.
 //
@@ -106,7 +107,7 @@ __global__ __launch_bounds__(256) void rows_rotary_kernel(const StepParams* __re
             }
         }
     }
-    // values: transposed through LDS, then 16 consecutive positions per row of the cache
+    // values: transposed through LDS, then into the cache's fragments (16 positions of a column are two runs of 16 bytes)
     if (role != 2) return;                               // uniform for the workgroup
     for (int it = tid; it < ROT_POS * (HD / 4); it += 256) {
         const int j = it / (HD / 4), i = (it % (HD / 4)) * 4, row = min(p0 + j, rps - 1);

@@ -8,7 +8,7 @@
 //   fp32: KF = 4, four v_mfma_f32_16x16x4_f32 (element i of both fragments feeds product i), so
 //         the contraction covers the same 16 k-values in a different order.
 //
-// Activations (the few-row operand) are fp32 values.  In bf16 mode they are written as three bf16
+// Activations (the few-row operand) are fp32 values.  In bf16 mode they are written as up to three bf16
 // planes (hi = bf16(x), mid = bf16(x - hi), lo = x - hi - mid, together all 24 significant bits)
 // and a kernel multiplies the first SPL of them by the same weight fragment, accumulating in fp32:
 // SPL = 1 is plain bf16 rounding (2^-9), SPL = 2 carries 16 bits (2^-18), SPL = 3 is exact.

@@ -222,8 +222,7 @@ __global__ __launch_bounds__((R2_CW + R2_LW) * 64) void gemm_rows2_kernel(GemmAr
 // max(weight stream, MFMA), with them near the sum, and a row-major operand fragment touches 16 cache
 // lines of which it uses half.  Here the compute waves issue no global loads at all: loader waves
 // fetch the operand fragments of all row tiles next to the weight tiles of the same k-step, from
-// planes that the producing kernels wrote as fragments (opnd_off: 1 KB of consecutive memory each;
-// row-major planes are still accepted).  A stage is ONE k-step; a wave's loads come back in the order
+// planes that the producing kernels wrote as fragments (opnd_off: 1 KB of consecutive memory each).  A stage is ONE k-step; a wave's loads come back in the order
 // it issued them, so weights (HBM: 8 stages of 8 KB) and operand (an L2 hit: 5 stages of
 // 9 x SPL KB) are fetched by different loader waves with rings of their own; one barrier per k-step;
 // the compute waves read the fragments of step s + 1 from LDS while they multiply step s.  An
