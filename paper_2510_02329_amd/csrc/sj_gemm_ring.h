@@ -22,11 +22,10 @@
 // The operand of such a block is stored that way, too (packed planes: one plane whose rows 8 - 15 are plane 1).
 #pragma once
 #include "sj_kernels.h"
+#include "sj_plan.h"
 
 namespace sj {
 
-constexpr int RING_CW = 8;         // compute waves = fragments (k-steps) per stage
-constexpr int RING_LW = 2;         // loader waves
 constexpr int RING_THREADS = (RING_CW + RING_LW) * 64;
 
 // the loader's last NSA - 1 iterations: iteration I may leave NSA - 3 - I stages of its loads in flight

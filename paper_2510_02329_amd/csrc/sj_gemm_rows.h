@@ -26,10 +26,10 @@
 #include <type_traits>
 
 #include "sj_kernels.h"
+#include "sj_plan.h"
 
 namespace sj {
 
-constexpr int ROWS_MT = 9;         // row tiles per launch (144 rows)
 constexpr int R2_CW = 4;           // compute waves
 constexpr int R2_LW = 2;           // loader waves (each moves half of the n-tiles)
 constexpr int R2_NT = 8;           // n-tiles per workgroup
@@ -250,7 +250,7 @@ constexpr int R8_CW = 8;
 // RT = row tiles of a row group: up to 9 (144 rows), or 18 with a single operand plane (288 rows: the same 18 operand
 // fragments per k-step in LDS, half as many workgroups re-reading every weight tile through L2).  A wave owns RT / 4
 // whole row tiles for its half of the n-tiles and n-tile w of each of the RT % 4 tiles left over.  Every tile of the group is
-// fetched and multiplied whether it has rows or not, so the group is chosen to fit the rows (row_tiles in sj_lib.hip).
+// fetched and multiplied whether it has rows or not, so the group is chosen to fit the rows (row_tiles in sj_plan.h).
 template <typename T, int EPI, int SPL, int NT = R2_NT, int RT = ROWS_MT>
 __global__ __launch_bounds__((R8_CW + R4_LW) * 64) void gemm_rows8_kernel(GemmArgs a, int mt) {
     static_assert(SPL <= 2, "three operand planes do not fit");

@@ -2,6 +2,7 @@
 // upload / re-tiling, and the kernel sequence of one verification step.
 #include "../../include/sj.h"
 #include "sj_kernels.h"
+#include "sj_plan.h"
 #include "sj_attn.h"
 #include "sj_attn_rows.h"
 #include "sj_gemm_rows.h"
@@ -56,7 +57,6 @@ struct LayerW {
     void *attn_norm = nullptr, *wqkv = nullptr, *wo = nullptr, *ffn_norm = nullptr, *wgu = nullptr, *wd = nullptr;
 };
 
-struct GemmPlan;
 struct TunedPlans;
 
 struct sj_model {
@@ -75,22 +75,6 @@ struct sj_model {
     mutable std::map<std::pair<int, int>, std::shared_ptr<TunedPlans>> tuned;
 };
 
-// Up to two row tiles (32 rows) the few-row kernel (every wave fetches its own operand fragments) is the faster
-// one (gate/up of the 70B shape at 24 rows: 179 us against 262 us); from three on the loader-wave kernels.
-constexpr int FEW_ROWS = 32;
-
-// Shape of a split-K projection launch: NT n-tiles and `waves` waves per workgroup, `split` K-slices
-// across workgroups (summed by the consumer), `depth` k-steps in the few-row kernel's load ring.  The chip has
-// 256 CUs and these kernels are a single wave of workgroups long, so a launch whose workgroup count is not a
-// multiple of 256 leaves CUs idle for its whole duration: plan_partial takes, among the first tile groupings
-// the kernel is instantiated for, the one that wastes the fewest workgroup slots, every wave keeping at least
-// 8 k-steps; tune_plans then measures that choice against the other shapes on the model's own weights.
-// waves == RING_WAVES selects the LDS-ring kernel (8 compute + 2 loader waves); `depth` is then its ring depth in
-// stages (4 or 8).
-struct GemmPlan { int nt = 4, waves = 4, split = 1, depth = 2; };
-constexpr int RING_WAVES = RING_CW + RING_LW;
-constexpr int RING_ROWS = 16;                  // one MFMA row tile
-constexpr int RING_PACK_ROWS = 8;              // both operand planes in one product
 struct TunedPlans { GemmPlan qkv, o, d, gu, lm; };
 
 // Buffers of a forward over up to `rpad` rows: residual stream, operand planes, projection partials, rotary table.
@@ -320,108 +304,6 @@ extern "C" int sj_set_temperature(sj_model* m, float temperature) {
 
 // ------------------------------------------------------------------------------------------------
 // kv / workspace
-
-// Can the LDS-ring kernel run this product in this launch shape?  bf16 with one or two operand planes, one row tile,
-// whole groups of n-tiles, K-slices of whole 8-k-step stages, and at least `depth` stages per workgroup.
-static bool ring_fits(const GemmPlan& p, int ntiles, int ksteps, int rows, int planes, bool bf16) {
-    if (p.waves != RING_WAVES || !bf16 || planes > 2 || rows > RING_ROWS) return false;
-    if (p.nt < 1 || p.split < 1 || ntiles % p.nt || ksteps % (RING_CW * p.split)) return false;
-    const int nstages = ksteps / RING_CW / p.split * p.nt;
-    return (p.depth == 4 || p.depth == 8) && nstages >= p.depth;
-}
-
-// Rule shape of a split-K projection on the LDS-ring kernel (rows <= 8, two planes: the measured case), or waves = 0
-// when no shape fits.  Fewest idle workgroup slots first (256 CUs, one round); among those at least two n-tiles per
-// workgroup (with one, the operand is as much traffic as the weights) and two K-slices, else four, else one, else
-// eight (measured on 4096 x 4096, 4096 x 14336 and 6144 x 4096: the middle of the range wins, and fewer slices are
-// less work for the kernel that adds them).
-static GemmPlan ring_rule_partial(int ntiles, int ksteps) {
-    static const int nts[] = {2, 3, 4, 8, 1}, splits[] = {2, 4, 1, 8};
-    GemmPlan best;
-    best.waves = 0;
-    double best_waste = 1e30;
-    for (int split : splits)
-        for (int nt : nts) {
-            GemmPlan p;
-            p.nt = nt; p.waves = RING_WAVES; p.split = split;
-            const int nstages = (ksteps / RING_CW / split) * nt;
-            p.depth = nstages >= 16 ? 8 : 4;
-            if (!ring_fits(p, ntiles, ksteps, 1, 2, true)) continue;
-            const int wgs = ntiles / nt * split;
-            const double waste = (double)((wgs + 255) / 256 * 256) / wgs + (nt == 1 ? 0.25 : 0.0);
-            if (waste < best_waste - 1e-9) { best = p; best_waste = waste; }
-        }
-    return best;
-}
-
-static GemmPlan plan_partial(int ntiles, int ksteps, bool one_row_tile) {
-    static const int cand[3][2] = {{4, 4}, {3, 8}, {6, 4}};
-    GemmPlan best;
-    if (!one_row_tile) {
-        // loader-wave kernel: 8 n-tiles per workgroup, one workgroup per CU; as many K-slices (at most 8, of at
-        // least 8 k-steps each) as fit one round of the chip - a second, partly filled round costs a whole one
-        const int groups = (ntiles + 7) / 8;
-        best.nt = 8; best.waves = 8;
-        best.split = std::max(1, std::min({8, 256 / std::max(groups, 1), ksteps / 8}));
-        return best;
-    }
-    double best_waste = 1e30;
-    for (const auto& c : cand) {
-        if (ntiles % c[0]) continue;
-        int split = 1;
-        while (split < 8 && ksteps / (c[1] * split * 2) >= 8) split *= 2;
-        const int wgs = ntiles / c[0] * split;
-        const double waste = (double)((wgs + 255) / 256 * 256) / wgs;
-        if (waste < best_waste - 1e-9) { best.nt = c[0]; best.waves = c[1]; best.split = split; best_waste = waste; }
-    }
-    // short K-slices (at most 8 k-steps per wave): a deeper register ring puts the whole slice in flight
-    best.depth = (best.nt == 4 && best.waves == 4 && ksteps / (best.split * 4) <= 8) ? 4 : 2;
-    return best;
-}
-
-// Row tiles of a row group of the loader-wave kernel: the smallest group that holds all rows, or, with more rows than the largest
-// holds, the one of the two largest that pads them least (equal: fewer groups).  The kernel spends matrix and L2 time on
-// every tile of a group: 126 rows in groups of 144 (score block of 6 x 21, 8B shape): QKV / O / down 30.6 us, LM head 348, in
-// one group of 128: 29.3, 325; 509 rows, 4 x 144 against 4 x 128: gate / up 277 -> 249 us.
-static int row_tiles(int planes, int rows) {
-    static const int one[] = {4, 9, 16, 18}, two[] = {4, 6, 8, 9};
-    if (planes > 2) return ROWS_MT;
-    const int* rt = planes == 1 ? one : two;
-    for (int i = 0; i < 4; ++i)
-        if (rows <= rt[i] * 16) return rt[i];
-    auto padded = [&](int t) { return (rows + t * 16 - 1) / (t * 16) * t; };
-    return padded(rt[2]) < padded(rt[3]) ? rt[2] : rt[3];
-}
-
-// K-slices of a split-K projection on the loader-wave kernel, which works in groups of `group` rows.  One group: the
-// rule's (one round of the chip).  With several, the groups fill the chip by themselves and every further slice costs a
-// write and a read of the partials: the slice count (never above the rule's) with the least estimated time, in units of
-// one k-step of a workgroup (0.58 us on two-plane operands) - rounds of 256 workgroups x (k-steps of a slice + 5 for ramp
-// and epilogue) + the partials' bytes at 4 TB/s.
-static int rows_split(int rule, int ntiles, int ksteps, int rows, int planes) {
-    const int group = row_tiles(planes, rows) * 16;
-    if (rows <= group) return rule;
-    const int rgroups = (rows + group - 1) / group, wgs = (ntiles + 7) / 8 * rgroups;
-    int best = 1;
-    double best_cost = 1e30;
-    for (int s = 1; s <= rule; ++s) {
-        const double rounds = (wgs * s + 255) / 256;
-        const double cost = rounds * ((double)ksteps / s + 5.0) + (double)s * rgroups * group * ntiles * 16 * 8 / 4e12 / 0.58e-6;
-        if (cost < best_cost - 1e-9) { best = s; best_cost = cost; }
-    }
-    return best;
-}
-// fp32 elements of the partials of a projection with up to `rows` rows on the loader-wave kernel, whatever the plane count
-// (slices and group depend on the rows in steps of 16)
-static size_t rows_part_elems(int rule, int N, int ksteps, int rows) {
-    size_t most = 0;
-    for (int planes = 1; planes <= 2; ++planes)
-        for (int r = 0; r < rows; r += 16) {
-            const int upto = std::min(r + 16, rows);
-            most = std::max(most, (size_t)rows_split(rule, N / 16, ksteps, upto, planes) * upto * N);
-        }
-    return most;
-}
 
 // Rows of one prompt chunk.  Every chunk streams all weights once, so a chunk should be so long that its work outweighs
 // that: four row groups of the loader-wave kernel (the two-plane products of 576 rows take 5 x the time of the
@@ -672,8 +554,6 @@ extern "C" int sj_set_kernel_timing(sj_kv* kv, int32_t kernel_class) {
     kv->tev_used = 0;
     return SJ_OK;
 }
-
-static GemmPlan resid_plan(int N, int K, int kstep, int rows, int planes, bool bf16, int ring_rows);
 
 extern "C" int sj_kernel_class_shape(const sj_kv* kv, int32_t kernel_class, int32_t rows, char* buf, int32_t buf_len) {
     if (!kv || !buf || buf_len < 1) return fail(SJ_EINVAL, "kv / buf is null");
@@ -993,23 +873,6 @@ static int few_swiglu(const GemmPlan& p, hipStream_t st, const void* W, const vo
     return fail(SJ_EINVAL, "internal: no few-row gate/up kernel for %d tiles x %d waves", p.nt, p.waves);
 }
 
-// A projection that closes a sub-layer (O, down) with the residual add in its epilogue (EPI_RESID; no K-slices): one launch
-// instead of two.  Without slices a workgroup has one n-tile (two, four where that fills the chip) and reads as much operand as
-// weights, so it pays up to 8 rows, where both planes are one packed fragment: 8B shape, 6 rows: down 20.3 -> 21.0 us, O 8.5 ->
-// 8.7, the norm launches (4.7 us each) gone, step 3.45 -> 3.30 ms; 1B draft, 1 row: 5.18 -> 4.85 ms a block.  At 12 and 20 rows
-// (operand twice and four times the weights) steps took 8 % and 11 % longer.  nt = 0: not taken.
-static GemmPlan resid_plan(int N, int K, int kstep, int rows, int planes, bool bf16, int ring_rows) {
-    GemmPlan p;
-    p.nt = 0;
-    const int ntiles = N / 16, ksteps = K / kstep, nt = ntiles > 512 ? 4 : ntiles > 256 ? 2 : 1;
-    if (rows > RING_PACK_ROWS || planes > 2 || ntiles % nt) return p;
-    p.nt = nt; p.split = 1;
-    p.waves = RING_WAVES;
-    p.depth = ksteps / RING_CW * nt >= 16 ? 8 : 4;
-    if (rows <= ring_rows && ring_fits(p, ntiles, ksteps, rows, planes, bf16)) return p;
-    p.waves = 8; p.depth = 2;
-    return p;
-}
 template <typename T, int SPL>
 static int few_resid(const GemmPlan& p, hipStream_t st, const void* W, const void* X, size_t xplane, int K, int N, int rows, void* xg,
                      size_t xgplane, const FewArgs& fa) {
