@@ -80,6 +80,7 @@ struct TunedPlans { GemmPlan qkv, o, d, gu, lm; };
 // Buffers of a forward over up to `rpad` rows: residual stream, operand planes, projection partials, rotary table.
 struct Forward {
     int rpad = 0;
+    size_t part_elems = 0;     // of `part`
     float *x = nullptr, *part = nullptr, *cs = nullptr, *ss = nullptr;
     void *xn = nullptr, *attn_out = nullptr, *act = nullptr;
     int32_t *row_tok = nullptr, *prefill_tok = nullptr;
@@ -431,18 +432,16 @@ extern "C" int sj_kv_create(const sj_model* m, int32_t batch, const int32_t* cap
         // the buffers of the forward, for `rows` rows
         const int kstep = (c.dtype == SJ_DTYPE_FP32) ? 16 : 32;
         auto forward_elems = [&](int rows) {
-            size_t e = std::max({rows_part_elems(kv->plan_qkv[1].split, Nq + 2 * Nk, d / kstep, rows),
-                                 rows_part_elems(kv->plan_o[1].split, d, Nq / kstep, rows), rows_part_elems(kv->plan_d[1].split, d, F / kstep, rows)});
-            // room for any few-row plan the start-up measurement may pick (at most 8 K-slices of at most 32 rows)
-            return std::max(e, (size_t)8 * std::min(rows, FEW_ROWS) * std::max(Nq + 2 * Nk, d));
+            return std::max({part_elems(kv->plan_qkv[1].split, Nq + 2 * Nk, d / kstep, rows), part_elems(kv->plan_o[1].split, d, Nq / kstep, rows),
+                             part_elems(kv->plan_d[1].split, d, F / kstep, rows)});
         };
         const size_t limit = (size_t)1 << 31;              // element offsets into the partials are 32-bit
-        const size_t part_elems = forward_elems(R);
-        if (part_elems >= limit) return bail(fail(SJ_EINVAL, "batch * (max_gamma + 1) rows need a projection workspace beyond 2^31 elements"));
+        kv->part_elems = forward_elems(R);
+        if (kv->part_elems >= limit) return bail(fail(SJ_EINVAL, "batch * (max_gamma + 1) rows need a projection workspace beyond 2^31 elements"));
         ALLOC(kv->xn, (size_t)3 * kv->rpad * d * m->esz);      // up to three operand planes
         ALLOC(kv->row_tok, (size_t)R * 4);
         ALLOC(kv->x, (size_t)R * d * 4);
-        ALLOC(kv->part, part_elems * 4);
+        ALLOC(kv->part, kv->part_elems * 4);
         ALLOC(kv->attn_out, (size_t)3 * kv->rpad * Nq * m->esz);
         // also holds the rotated query fragments of many-row attention until the gate / up projection (whole tiles of 16 columns)
         const size_t qcols = (size_t)(G * (c.max_gamma + 1) + 15) / 16 * 16;
@@ -476,7 +475,7 @@ extern "C" int sj_kv_create(const sj_model* m, int32_t batch, const int32_t* cap
                 carve(w.prefill_tok, (size_t)pf * 4);
                 if (round == 0 && hipMalloc((void**)&base, used) != hipSuccess) { (void)hipGetLastError(); base = nullptr; break; }
             }
-            if (base) { A.push_back(base); w.rpad = pad; kv->pf_rows = pf; }
+            if (base) { A.push_back(base); w.rpad = pad; w.part_elems = forward_elems(pf); kv->pf_rows = pf; }
         }
     }
 #undef ALLOC
@@ -1266,6 +1265,7 @@ struct Runner {
     int partial_gemm(const void* W, const void* X, int K, int N, const GemmPlan (&pl)[2], int* parts = nullptr, bool unscaled = false) {
         const GemmPlan p = plan_of(pl, K, N);
         if (parts) *parts = p.split;
+        if ((size_t)p.split * R * N > w->part_elems) return fail(SJ_EINVAL, "internal: %d K-slices of %d rows exceed the partials' buffer", p.split, R);
         if (R > FEW_ROWS) return gemm_rows<T, EPI_PARTIAL, SPL>(st, W, X, plane(K), K, N, R, p.split, w->part, nullptr, 0, nullptr, 0.f);
         return few_partial<T, SPL>(p, st, W, X, plane(K), K, N, R, w->part, few_args(unscaled));
     }

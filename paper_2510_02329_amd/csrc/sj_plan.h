@@ -118,11 +118,12 @@ inline int rows_split(int rule, int ntiles, int ksteps, int rows, int planes) {
     }
     return best;
 }
-// fp32 elements of the partials of a projection with up to `rows` rows on the loader-wave kernel, whatever the plane count
-// (slices and group depend on the rows in steps of 16)
-inline size_t rows_part_elems(int rule, int N, int ksteps, int rows) {
-    size_t most = 0;
-    for (int planes = 1; planes <= 2; ++planes)
+// fp32 elements of the partials of a projection with up to `rows` rows, for every plane count, since a cache object's can be changed
+// between steps (slices and group depend on the rows in steps of 16; three planes work in groups of 144 rows where two have chosen 128,
+// and fewer groups can mean more slices), and for any few-row plan the start-up measurement may pick (at most 8 K-slices)
+inline size_t part_elems(int rule, int N, int ksteps, int rows) {
+    size_t most = (size_t)8 * std::min(rows, FEW_ROWS) * N;
+    for (int planes = 1; planes <= 3; ++planes)
         for (int r = 0; r < rows; r += 16) {
             const int upto = std::min(r + 16, rows);
             most = std::max(most, (size_t)rows_split(rule, N / 16, ksteps, upto, planes) * upto * N);
