@@ -805,38 +805,28 @@ static int gemm_ring(hipStream_t st, const void* Wt, const void* X, size_t xplan
     return SJ_OK;
 }
 
-// The few-row split-K projection in the launch shape of a plan.  Shapes beyond the first four exist for the
-// default two-plane / one-plane operands only (they are what the start-up measurement may pick).
+// The few-row split-K projection in exactly the launch shape of a plan (partial_fits has been checked): the consumer of the partials
+// goes by the plan's K-slices.
 template <typename T, int SPL>
 static int few_partial(const GemmPlan& p, hipStream_t st, const void* W, const void* X, size_t xplane, int K, int N,
                        int rows, float* out, const FewArgs& fa = FewArgs{}) {
-    if (p.waves == RING_WAVES) {
-        if constexpr (std::is_same<T, bf16_t>::value && SPL <= 2) {
-            if (ring_fits(p, N / 16, K / Traits<T>::KSTEP, rows, SPL, true)) {
+    constexpr bool BF16 = std::is_same<T, bf16_t>::value;
+    if (partial_fits(p, N / 16, K / Traits<T>::KSTEP, rows, SPL, BF16)) {
+        if constexpr (BF16 && SPL <= 2) {
 #define SJ_RING(NT, NSA)                                                                                            \
-    if (p.nt == NT && p.depth == NSA)                                                                               \
+    if (p.waves == RING_WAVES && p.nt == NT && p.depth == NSA)                                                      \
         return gemm_ring<T, NT, EPI_PARTIAL, SPL, NSA>(st, W, X, xplane, K, N, rows, p.split, out, nullptr, 0, nullptr, 0.f, fa);
-                SJ_RING(1, 8) SJ_RING(2, 8) SJ_RING(3, 8) SJ_RING(4, 8) SJ_RING(8, 8)
-                SJ_RING(1, 4) SJ_RING(2, 4) SJ_RING(3, 4) SJ_RING(4, 4)
+            SJ_RING_PARTIAL_SHAPES(SJ_RING)
 #undef SJ_RING
-            }
         }
-        // more rows than the kernel takes, or a shape that is not instantiated: the register-ring kernel's rule shape
-        return few_partial<T, SPL>(plan_partial(N / 16, K / Traits<T>::KSTEP, true), st, W, X, xplane, K, N, rows, out, fa);
-    }
 #define SJ_SHAPE(NT, WV, D)                                                                                         \
     if (p.nt == NT && p.waves == WV && p.depth == D)                                                                \
         return gemm<T, NT, EPI_PARTIAL, SPL, WV, D>(st, W, X, xplane, K, N, rows, p.split, out, nullptr, 0, nullptr, 0.f, fa);
-    SJ_SHAPE(4, 4, 2) SJ_SHAPE(4, 4, 4) SJ_SHAPE(3, 8, 2) SJ_SHAPE(6, 4, 2)
-    if constexpr (SPL <= 2) {
-        SJ_SHAPE(5, 4, 2) SJ_SHAPE(8, 8, 2) SJ_SHAPE(4, 8, 2) SJ_SHAPE(8, 4, 2) SJ_SHAPE(3, 4, 4)
-        SJ_SHAPE(2, 4, 4) SJ_SHAPE(2, 4, 2) SJ_SHAPE(2, 8, 2)
-    }
+        SJ_FEW_PARTIAL_SHAPES(SJ_SHAPE)
+        if constexpr (SPL <= 2) { SJ_FEW_PARTIAL_SHAPES_2(SJ_SHAPE) }
 #undef SJ_SHAPE
-    // a shape that is not instantiated for this plane count: the rule's shape always is
-    const GemmPlan q = plan_partial(N / 16, K / Traits<T>::KSTEP, true);
-    if (q.nt != p.nt || q.waves != p.waves || q.depth != p.depth) return few_partial<T, SPL>(q, st, W, X, xplane, K, N, rows, out, fa);
-    return fail(SJ_EINVAL, "internal: no few-row kernel for %d tiles x %d waves, ring %d", p.nt, p.waves, p.depth);
+    }
+    return fail(SJ_EINVAL, "internal: no few-row kernel for %d tiles x %d waves, %d K-slice(s), ring %d", p.nt, p.waves, p.split, p.depth);
 }
 
 // The few-row gate / up projection (SwiGLU epilogue, no K-slices) in the launch shape of a plan.
@@ -919,7 +909,7 @@ static int few_logits(const GemmPlan& p, hipStream_t st, const void* W, const vo
     SJ_SHAPE(8, 4)
     if constexpr (SPL <= 2) { SJ_SHAPE(8, 8) SJ_SHAPE(4, 8) SJ_SHAPE(4, 4) }
 #undef SJ_SHAPE
-    if (p.nt != 8 || p.waves != 4) return few_logits<T, SPL>(GemmPlan{8, 4, 1, 2}, st, W, X, xplane, K, V, rows, logits, stats, inv_temp, fa);
+    if (p.nt == 8 && p.waves != 4) return few_logits<T, SPL>(GemmPlan{8, 4, 1, 2}, st, W, X, xplane, K, V, rows, logits, stats, inv_temp, fa);
     return fail(SJ_EINVAL, "internal: no few-row LM-head kernel for %d tiles x %d waves", p.nt, p.waves);
 }
 
@@ -983,34 +973,7 @@ static int tune_one(sj_kv* kv, GemmPlan& plan, void* LayerW::*which, const void*
         us = (double)ms * 1e3 / nl;
         return SJ_OK;
     };
-    static const int shapes[][3] = {{4, 4, 2}, {4, 4, 4}, {3, 8, 2}, {6, 4, 2}, {5, 4, 2}, {8, 8, 2}, {4, 8, 2}, {8, 4, 2}, {3, 4, 4},
-                                    {2, 4, 4}, {2, 4, 2}, {2, 8, 2}};
-    std::vector<GemmPlan> cands;
-    for (int i = 0; i < (int)(sizeof(shapes) / sizeof(shapes[0])); ++i) {
-        if (SPL > 2 && i >= 4) break;
-        const int nt = shapes[i][0], wv = shapes[i][1], dp = shapes[i][2];
-        if (ntiles % nt) continue;
-        for (int split = 1; split <= 8; split *= 2) {
-            const int kpw = ksteps / (wv * split);          // k-steps of a wave
-            const long long wgs = (long long)ntiles / nt * split;
-            if (kpw < 4 || (dp == 4 && kpw > 8) || wgs < 128 || wgs > 4096) continue;
-            GemmPlan p;
-            p.nt = nt; p.waves = wv; p.split = split; p.depth = dp;
-            cands.push_back(p);
-        }
-    }
-    // the LDS-ring kernel's shapes
-    for (int nt : {1, 2, 3, 4, 8})
-        for (int split = 1; split <= 8; split *= 2)
-            for (int depth : {8, 4}) {
-                GemmPlan p;
-                p.nt = nt; p.waves = RING_WAVES; p.split = split; p.depth = depth;
-                if (!ring_fits(p, ntiles, ksteps, rows, SPL, std::is_same<T, bf16_t>::value)) continue;
-                const long long wgs = (long long)ntiles / nt * split;
-                if (wgs < 128 || wgs > 4096) continue;
-                cands.push_back(p);
-            }
-    return pick_plan(plan, cands, time_plan);
+    return pick_plan(plan, partial_candidates(ntiles, ksteps, rows, SPL, std::is_same<T, bf16_t>::value), time_plan);
 }
 
 template <typename T, int SPL>
@@ -1249,17 +1212,13 @@ struct Runner {
     bool packed() const { return packed_rows<T, SPL>(R); }
     int rm() const { return packed() && R <= RM_ROWS; }
     size_t plane(int ld) const { return packed() ? packed_plane<T>(rm()) : (size_t)w->rpad * ld; }
-    // Launch shape of a split-K projection for this row count.  A prompt chunk of at most 32 rows can have more rows than
-    // the plan was made for: the LDS-ring shape then gives way to the register-ring kernel's rule shape.
+    // launch shape of a split-K projection for this row count
     GemmPlan plan_of(const GemmPlan (&pl)[2], int K, int N) const {
         const int ksteps = K / Traits<T>::KSTEP;
-        if (R > FEW_ROWS) {
-            GemmPlan p = pl[1];
-            p.split = rows_split(p.split, N / 16, ksteps, R, SPL);
-            return p;
-        }
-        if (pl[0].waves == RING_WAVES && !ring_fits(pl[0], N / 16, ksteps, R, SPL, std::is_same<T, bf16_t>::value)) return plan_partial(N / 16, ksteps, true);
-        return pl[0];
+        if (R <= FEW_ROWS) return resolve_partial(pl[0], N / 16, ksteps, R, SPL, std::is_same<T, bf16_t>::value);
+        GemmPlan p = pl[1];
+        p.split = rows_split(p.split, N / 16, ksteps, R, SPL);
+        return p;
     }
     // `parts`: the K-slices it leaves in w->part
     int partial_gemm(const void* W, const void* X, int K, int N, const GemmPlan (&pl)[2], int* parts = nullptr, bool unscaled = false) {

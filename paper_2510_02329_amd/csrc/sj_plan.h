@@ -4,6 +4,7 @@
 #pragma once
 #include <algorithm>
 #include <cstddef>
+#include <vector>
 
 namespace sj {
 
@@ -37,6 +38,28 @@ inline bool ring_fits(const GemmPlan& p, int ntiles, int ksteps, int rows, int p
     return (p.depth == 4 || p.depth == 8) && nstages >= p.depth;
 }
 
+// The shapes the split-K projections are instantiated for: (n-tiles, waves, ring depth) of the register-ring kernel - the second list
+// for one and two operand planes only - and (n-tiles, ring depth in stages) of the LDS-ring kernel.
+#define SJ_FEW_PARTIAL_SHAPES(X) X(4, 4, 2) X(4, 4, 4) X(3, 8, 2) X(6, 4, 2)
+#define SJ_FEW_PARTIAL_SHAPES_2(X) X(5, 4, 2) X(8, 8, 2) X(4, 8, 2) X(8, 4, 2) X(3, 4, 4) X(2, 4, 4) X(2, 4, 2) X(2, 8, 2)
+#define SJ_RING_PARTIAL_SHAPES(X) X(1, 8) X(2, 8) X(3, 8) X(4, 8) X(8, 8) X(1, 4) X(2, 4) X(3, 4) X(4, 4)
+
+// Is there a kernel for exactly this split-K launch?  The consumer adds p.split K-slices, so no other shape may stand in for it.
+inline bool partial_fits(const GemmPlan& p, int ntiles, int ksteps, int rows, int planes, bool bf16) {
+    if (p.waves == RING_WAVES) {
+#define SJ_IS(NT, NSA) if (p.nt == NT && p.depth == NSA) return ring_fits(p, ntiles, ksteps, rows, planes, bf16);
+        SJ_RING_PARTIAL_SHAPES(SJ_IS)
+#undef SJ_IS
+        return false;
+    }
+    if (p.nt < 1 || ntiles % p.nt) return false;
+#define SJ_IS(NT, WV, D) if (p.nt == NT && p.waves == WV && p.depth == D) return true;
+    SJ_FEW_PARTIAL_SHAPES(SJ_IS)
+    if (planes <= 2) { SJ_FEW_PARTIAL_SHAPES_2(SJ_IS) }
+#undef SJ_IS
+    return false;
+}
+
 // Rule shape of a split-K projection on the LDS-ring kernel (rows <= 8, two planes: the measured case), or waves = 0
 // when no shape fits.  Fewest idle workgroup slots first (256 CUs, one round); among those at least two n-tiles per
 // workgroup (with one, the operand is as much traffic as the weights) and two K-slices, else four, else one, else
@@ -53,7 +76,7 @@ inline GemmPlan ring_rule_partial(int ntiles, int ksteps) {
             p.nt = nt; p.waves = RING_WAVES; p.split = split;
             const int nstages = (ksteps / RING_CW / split) * nt;
             p.depth = nstages >= 16 ? 8 : 4;
-            if (!ring_fits(p, ntiles, ksteps, 1, 2, true)) continue;
+            if (!partial_fits(p, ntiles, ksteps, 1, 2, true)) continue;
             const int wgs = ntiles / nt * split;
             const double waste = (double)((wgs + 255) / 256 * 256) / wgs + (nt == 1 ? 0.25 : 0.0);
             if (waste < best_waste - 1e-9) { best = p; best_waste = waste; }
@@ -84,6 +107,36 @@ inline GemmPlan plan_partial(int ntiles, int ksteps, bool one_row_tile) {
     // short K-slices (at most 8 k-steps per wave): a deeper register ring puts the whole slice in flight
     best.depth = (best.nt == 4 && best.waves == 4 && ksteps / (best.split * 4) <= 8) ? 4 : 2;
     return best;
+}
+
+// The launch of a split-K projection with at most 32 rows: the plan, or, where its kernel does not take these rows or planes (a prompt
+// chunk can have more rows than the plan was made for), the register-ring kernel's rule shape, which is always instantiated.
+inline GemmPlan resolve_partial(const GemmPlan& p, int ntiles, int ksteps, int rows, int planes, bool bf16) {
+    return partial_fits(p, ntiles, ksteps, rows, planes, bf16) ? p : plan_partial(ntiles, ksteps, true);
+}
+
+// Shapes that the start-up measurement tries for a split-K projection with at most 32 rows.
+inline std::vector<GemmPlan> partial_candidates(int ntiles, int ksteps, int rows, int planes, bool bf16) {
+    std::vector<GemmPlan> cands;
+    auto offer = [&](int nt, int waves, int depth) {
+        for (int split = 1; split <= 8; split *= 2) {
+            GemmPlan p;
+            p.nt = nt; p.waves = waves; p.split = split; p.depth = depth;
+            const long long wgs = (long long)ntiles / nt * split;
+            if (!partial_fits(p, ntiles, ksteps, rows, planes, bf16) || wgs < 128 || wgs > 4096) continue;
+            const int kpw = ksteps / (waves * split);       // k-steps of a wave of the register-ring kernel
+            if (waves != RING_WAVES && (kpw < 4 || (depth == 4 && kpw > 8))) continue;
+            cands.push_back(p);
+        }
+    };
+#define SJ_OFFER(NT, WV, D) offer(NT, WV, D);
+    SJ_FEW_PARTIAL_SHAPES(SJ_OFFER)
+    SJ_FEW_PARTIAL_SHAPES_2(SJ_OFFER)
+#undef SJ_OFFER
+#define SJ_OFFER(NT, NSA) offer(NT, RING_WAVES, NSA);
+    SJ_RING_PARTIAL_SHAPES(SJ_OFFER)
+#undef SJ_OFFER
+    return cands;
 }
 
 // Row tiles of a row group of the loader-wave kernel: the smallest group that holds all rows, or, with more rows than the largest

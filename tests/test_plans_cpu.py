@@ -30,3 +30,43 @@ int main() {
 def test_partials_of_every_launch_fit_their_buffer(tmp_path):
     out = run_program(tmp_path, PARTIALS)
     assert out.splitlines()[-1].startswith("0 of "), out
+
+LAUNCHES = shapes_array() + r"""
+// what a split-K projection of at most 32 rows may be launched as: the rule shapes, whatever the measurement tries, and their stand-ins
+int main() {
+    long bad = 0, checked = 0;
+    for (const auto& s : shapes)
+        for (int kstep : {32, 16})
+            for (int rows = 1; rows <= 32; ++rows)
+                for (int planes = 1; planes <= 3; ++planes) {
+                    const bool bf16 = kstep == 32;
+                    if (!bf16 && planes > 1) continue;
+                    const int prod[3][2] = {{s[1], s[0]}, {s[0], s[2]}, {s[0], s[3]}};      // N, K of QKV, O, down
+                    for (const auto& p : prod) {
+                        const int ntiles = p[0] / 16, ksteps = p[1] / kstep;
+                        auto see = [&](const char* what, const GemmPlan& q) {
+                            ++checked;
+                            // a kernel, and every K-slice written: none is empty
+                            if ((!partial_fits(q, ntiles, ksteps, rows, planes, bf16) || q.split > std::max(ksteps, 1)) && bad++ < 10)
+                                printf("%s: %d tiles, %d k-steps, %d rows, %d planes: {%d, %d, %d, %d}\n", what, ntiles, ksteps, rows, planes, q.nt, q.waves, q.split, q.depth);
+                        };
+                        see("rule", plan_partial(ntiles, ksteps, true));
+                        GemmPlan ring = ring_rule_partial(ntiles, ksteps);
+                        if (ring.waves && bf16 && planes <= 2 && rows <= 8) see("ring rule", ring);
+                        for (const GemmPlan& q : partial_candidates(ntiles, ksteps, rows, planes, bf16)) see("candidate", q);
+                        // plans of other row and plane counts, as a prompt chunk or a changed plane count finds them
+                        if (ring.waves) see("resolved ring rule", resolve_partial(ring, ntiles, ksteps, rows, planes, bf16));
+                        for (int r2 : {1, 8, 12, 24})
+                            for (const GemmPlan& q : partial_candidates(ntiles, ksteps, r2, bf16 ? 2 : 1, bf16))
+                                see("resolved candidate", resolve_partial(q, ntiles, ksteps, rows, planes, bf16));
+                    }
+                }
+    printf("%ld of %ld without a kernel\n", bad, checked);
+}
+"""
+
+
+def test_every_split_k_launch_is_an_instantiated_shape(tmp_path):
+    """The consumer adds the plan's K-slices: a launch in another shape would leave some of them from an earlier product."""
+    out = run_program(tmp_path, LAUNCHES)
+    assert out.splitlines()[-1].startswith("0 of "), out
