@@ -18,7 +18,8 @@
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  Calls that take
  *     a stream are asynchronous on it; their outputs are valid once the stream is synchronised.
  *   - The library owns sj_model / sj_kv and all workspace; it allocates at load / create time
- *     (plus a one-time launch-graph build on the first step of a given gamma), never per step.
+ *     (plus a one-time launch-graph build on the first step of a given gamma, and the prompt-chunk
+ *     buffers with a cache object's first long prompt, see sj_prefill), never per step.
  *   - On an argument error no sequence state is modified.
  *   - Storage dtype (sj_config.dtype) applies to weights and the KV cache: 0 = fp32,
  *     1 = bf16 (bit pattern in uint16).  Host tensors handed over are in that dtype.
@@ -90,7 +91,7 @@ int sj_model_free(sj_model* m);
 
 /* Creates the per-batch state: a KV cache with `capacity[b]` positions for sequence b (rounded
  * up to a multiple of 64 internally), lengths 0, pending tokens 0, and the step workspace for
- * batch * (max_gamma + 1) query rows (at least one prompt chunk, see sj_prefill).  capacity is a host array of `batch` entries (ignored
+ * batch * (max_gamma + 1) query rows.  capacity is a host array of `batch` entries (ignored
  * and may be NULL for a head-only model).  Synchronous.  For a model with layers the call also
  * measures, on the device's default stream and on the model's own weights, which launch shape of
  * each projection kernel is fastest for this row count (some tens of milliseconds; the workspace
@@ -124,9 +125,12 @@ int sj_kv_state(const sj_kv* kv, int32_t* len_host, int32_t* pending_host);
 
 /* Runs the target over n prompt tokens (host array) of sequence seq, appends their K/V, advances
  * the length by n and sets the pending token to the arg-max continuation of the last prompt
- * token.  A prompt of more than max_gamma + 1 tokens runs in chunks of up to 576 rows (the cache
- * object keeps buffers for them; where those did not fit, in blocks of max_gamma + 1 rows).
- * Synchronises `stream`. */
+ * token.  A prompt of more than max_gamma + 1 tokens runs in chunks of up to 576 rows.  The first such
+ * call on a cache object allocates buffers for them, which it keeps until sj_kv_free: for
+ * P = min(576, longest capacity rounded up to 64) rows about P * (3 s (d + q + max(f, q)) + 4 d) bytes (s: bytes
+ * of the storage type, d = d_model, q = n_q_heads * head_dim, f = d_ffn) and the fp32 partial sums of the projections,
+ * 120 MB in all for d = 4096, f = 14336 in bf16.  Where they do not fit, prompts run in blocks of
+ * max_gamma + 1 rows.  Synchronises `stream`. */
 int sj_prefill(sj_model* m, sj_kv* kv, int32_t seq, const int32_t* tokens_host, int32_t n, void* stream);
 
 /* One verification cycle for every sequence of the batch (Sec. 3.1 - 3.2).

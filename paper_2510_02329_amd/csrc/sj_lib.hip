@@ -90,7 +90,7 @@ struct sj_kv : Forward {       // the inherited buffers serve the blocks of up t
     const sj_model* m = nullptr;
     int batch = 0, max_rows = 0, mpad = 0, cap_max = 64;
     Forward chunk;             // those of a prompt chunk of sj_prefill
-    int pf_rows = 0;           // rows of one prompt chunk of sj_prefill (0: chunks of max_gamma + 1 rows)
+    int pf_rows = 0;           // rows of one prompt chunk of sj_prefill (0: no buffers for them, chunks of max_gamma + 1 rows)
     std::vector<int32_t> cap, len_upper;
     std::vector<int64_t> seq_off;
     int64_t layer_stride = 0;
@@ -346,6 +346,55 @@ static void rule_plans(sj_kv* kv) {
     }
 }
 
+// fp32 elements of the projections' partials for blocks of up to `rows` rows; element offsets into them are 32-bit
+constexpr size_t PART_LIMIT = (size_t)1 << 31;
+static size_t forward_elems(const sj_kv* kv, int rows) {
+    const sj_config& c = kv->m->cfg;
+    const int d = c.d_model, Nq = c.n_q_heads * c.head_dim, Nk = c.n_kv_heads * c.head_dim, kstep = c.dtype == SJ_DTYPE_FP32 ? 16 : 32;
+    return std::max({part_elems(kv->plan_qkv[1].split, Nq + 2 * Nk, d / kstep, rows), part_elems(kv->plan_o[1].split, d, Nq / kstep, rows),
+                     part_elems(kv->plan_d[1].split, d, c.d_ffn / kstep, rows)});
+}
+
+// Buffers of a prompt chunk, as long as the longest sequence allows, up to PREFILL_ROWS: allocated with the cache object's first
+// prompt of more than a block, so that objects which see none (draft and scoring caches filled by sj_kv_set) neither hold them (120 MB
+// for the 8B shape) nor take the time (0.3 ms).  They are apart from those of the blocks (a block's planes then stay close together:
+// with one set for both, the steps of small models took 3 % longer), in one allocation.  Where it does not fit, prompts go through in
+// blocks of max_gamma + 1 rows.
+static void get_chunk(sj_kv* kv) {
+    const sj_model* m = kv->m;
+    const sj_config& c = m->cfg;
+    const int pf = std::min(PREFILL_ROWS, kv->cap_max), pad = (pf + 15) / 16 * 16;
+    if (kv->pf_rows || pf <= c.max_gamma + 1) return;
+    const size_t elems = forward_elems(kv, pf);
+    if (elems >= PART_LIMIT) return;
+    const int d = c.d_model, Nq = c.n_q_heads * c.head_dim;
+    Forward& w = kv->chunk;
+    char* base = nullptr;
+    size_t used = 0;
+    auto carve = [&](auto*& ptr, size_t bytes) {
+        if (base) ptr = reinterpret_cast<std::remove_reference_t<decltype(ptr)>>(base + used);
+        used = (used + bytes + 255) / 256 * 256;
+    };
+    for (int round = 0; round < 2; ++round) {                  // sizes first, then the pieces
+        used = 0;
+        carve(w.xn, (size_t)3 * pad * d * m->esz);
+        carve(w.row_tok, (size_t)pf * 4);
+        carve(w.x, (size_t)pf * d * 4);
+        carve(w.part, elems * 4);
+        carve(w.attn_out, (size_t)3 * pad * Nq * m->esz);
+        // also holds the chunk's rotated query fragments (pad x Nq elements per plane) until the gate / up projection
+        carve(w.act, (size_t)3 * pad * std::max(c.d_ffn, Nq) * m->esz);
+        carve(w.cs, (size_t)pf * c.head_dim * 4);
+        carve(w.ss, (size_t)std::min(pf, FEW_ROWS) * (d / 16) * 4);
+        carve(w.prefill_tok, (size_t)pf * 4);
+        if (round == 0 && hipMalloc((void**)&base, used) != hipSuccess) { (void)hipGetLastError(); return; }
+    }
+    kv->allocs.push_back(base);
+    w.rpad = pad;
+    w.part_elems = elems;
+    kv->pf_rows = pf;
+}
+
 extern "C" int sj_kv_create(const sj_model* m, int32_t batch, const int32_t* capacity, sj_kv** out) {
     if (!m || !out) return fail(SJ_EINVAL, "model / out is null");
     if (batch < 1 || batch > 4096) return fail(SJ_EINVAL, "batch must be in 1..4096");
@@ -403,13 +452,14 @@ extern "C" int sj_kv_create(const sj_model* m, int32_t batch, const int32_t* cap
         kv->nslab = blocks * 256;
         kv->slab_len = (V + kv->nslab - 1) / kv->nslab;
     }
-    ALLOC(kv->epart, (size_t)batch * kv->nslab * 8);
-    ALLOC(kv->wpart, (size_t)batch * kv->nslab * 8);
-    ALLOC(kv->eblk, (size_t)batch * (kv->nslab / 256) * 8);
-    ALLOC(kv->wblk, (size_t)batch * (kv->nslab / 256) * 8);
+    const size_t slabs = (size_t)batch * kv->nslab;            // a multiple of 256
+    ALLOC(kv->epart, (2 * slabs + slabs / 128) * 8);           // slab sums of both passes, then their workgroup sums (an allocation takes 20 us)
+    kv->wpart = kv->epart + slabs;
+    kv->eblk = kv->wpart + slabs;
+    kv->wblk = kv->eblk + slabs / 256;
     if (c.n_layers == 0) ALLOC(kv->xn, (size_t)3 * kv->rpad * d * m->esz);          // up to three operand planes
     if (c.n_layers > 0) {
-        const int hd = c.head_dim, Nq = c.n_q_heads * hd, Nk = c.n_kv_heads * hd, F = c.d_ffn;
+        const int hd = c.head_dim, Nq = c.n_q_heads * hd, F = c.d_ffn;
         const int G = c.n_q_heads / c.n_kv_heads;
         rule_plans(kv);
         kv->mpad = (G * (c.max_gamma + 1) + 63) / 64 * 64;   // whole groups of 4 MFMA tiles
@@ -429,15 +479,8 @@ extern "C" int sj_kv_create(const sj_model* m, int32_t batch, const int32_t* cap
         // per (sequence, kv head, key range): mpad rows of hd accumulators + (max, sum) in lane order
         ALLOC(kv->opart, (size_t)batch * c.n_kv_heads * kv->nchunk_max * kv->mpad * (hd + 8) * 4);
         ALLOC(kv->tickets, (size_t)batch * c.n_kv_heads * (kv->mpad / 16) * 4);
-        // the buffers of the forward, for `rows` rows
-        const int kstep = (c.dtype == SJ_DTYPE_FP32) ? 16 : 32;
-        auto forward_elems = [&](int rows) {
-            return std::max({part_elems(kv->plan_qkv[1].split, Nq + 2 * Nk, d / kstep, rows), part_elems(kv->plan_o[1].split, d, Nq / kstep, rows),
-                             part_elems(kv->plan_d[1].split, d, F / kstep, rows)});
-        };
-        const size_t limit = (size_t)1 << 31;              // element offsets into the partials are 32-bit
-        kv->part_elems = forward_elems(R);
-        if (kv->part_elems >= limit) return bail(fail(SJ_EINVAL, "batch * (max_gamma + 1) rows need a projection workspace beyond 2^31 elements"));
+        kv->part_elems = forward_elems(kv, R);
+        if (kv->part_elems >= PART_LIMIT) return bail(fail(SJ_EINVAL, "batch * (max_gamma + 1) rows need a projection workspace beyond 2^31 elements"));
         ALLOC(kv->xn, (size_t)3 * kv->rpad * d * m->esz);      // up to three operand planes
         ALLOC(kv->row_tok, (size_t)R * 4);
         ALLOC(kv->x, (size_t)R * d * 4);
@@ -446,37 +489,9 @@ extern "C" int sj_kv_create(const sj_model* m, int32_t batch, const int32_t* cap
         // also holds the rotated query fragments of many-row attention until the gate / up projection (whole tiles of 16 columns)
         const size_t qcols = (size_t)(G * (c.max_gamma + 1) + 15) / 16 * 16;
         ALLOC(kv->act, (size_t)3 * std::max((size_t)kv->rpad * F, R > FEW_ROWS ? batch * c.n_kv_heads * qcols * hd : 0) * m->esz);
-        ALLOC(kv->cs, (size_t)R * hd * 4);
-        ALLOC(kv->ss, (size_t)std::min(R, FEW_ROWS) * (d / 16) * 4);
+        ALLOC(kv->cs, ((size_t)R * hd + (size_t)std::min(R, FEW_ROWS) * (d / 16)) * 4);
+        kv->ss = kv->cs + (size_t)R * hd;                      // 16-byte pieces: hd and d are multiples of 64
         ALLOC(kv->prefill_tok, (size_t)R * 4);
-        // A prompt chunk of sj_prefill is as long as the longest sequence allows, up to PREFILL_ROWS.  Its buffers are apart from
-        // those of the blocks (a block's planes then stay close together: with one set for both, the steps of small models took
-        // 3 % longer), in one allocation.  Where it does not fit, prompts go through in blocks of max_gamma + 1 rows.
-        const int pf = std::min(PREFILL_ROWS, cap_max), pad = (pf + 15) / 16 * 16;
-        if (pf > c.max_gamma + 1 && forward_elems(pf) < limit) {
-            Forward& w = kv->chunk;
-            char* base = nullptr;
-            size_t used = 0;
-            auto carve = [&](auto*& ptr, size_t bytes) {
-                if (base) ptr = reinterpret_cast<std::remove_reference_t<decltype(ptr)>>(base + used);
-                used = (used + bytes + 255) / 256 * 256;
-            };
-            for (int round = 0; round < 2; ++round) {          // sizes first, then the pieces
-                used = 0;
-                carve(w.xn, (size_t)3 * pad * d * m->esz);
-                carve(w.row_tok, (size_t)pf * 4);
-                carve(w.x, (size_t)pf * d * 4);
-                carve(w.part, forward_elems(pf) * 4);
-                carve(w.attn_out, (size_t)3 * pad * Nq * m->esz);
-                // also holds the chunk's rotated query fragments (pad x Nq elements per plane) until the gate / up projection
-                carve(w.act, (size_t)3 * pad * std::max(F, Nq) * m->esz);
-                carve(w.cs, (size_t)pf * hd * 4);
-                carve(w.ss, (size_t)std::min(pf, FEW_ROWS) * (d / 16) * 4);
-                carve(w.prefill_tok, (size_t)pf * 4);
-                if (round == 0 && hipMalloc((void**)&base, used) != hipSuccess) { (void)hipGetLastError(); base = nullptr; break; }
-            }
-            if (base) { A.push_back(base); w.rpad = pad; w.part_elems = forward_elems(pf); kv->pf_rows = pf; }
-        }
     }
 #undef ALLOC
     if (hipMemcpy(kv->seq_off_dev, kv->seq_off.data(), sizeof(int64_t) * batch, hipMemcpyHostToDevice) != hipSuccess ||
@@ -1826,6 +1841,7 @@ extern "C" int sj_verify_head_static(sj_model* m, int32_t batch, int32_t gamma, 
 template <typename T, int SPL>
 static int prefill_impl(sj_model* m, sj_kv* kv, int seq, const int32_t* tokens, int n, hipStream_t st) {
     const int block = std::min(kv->max_rows, m->cfg.max_gamma + 1);
+    if (n > block) get_chunk(kv);
     const int rows_max = n > block && kv->pf_rows > block ? kv->pf_rows : block;
     const bool long_chunks = rows_max > block;
     const int nchunks = (n + rows_max - 1) / rows_max;

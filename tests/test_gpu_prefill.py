@@ -68,3 +68,30 @@ def test_long_prompt_matches_oracle(dtype, hq, hkv, hd, prompts):
             assert pend[1] == int(np.argmax(logits[tail - 1]))
     finally:
         gpu.close()
+
+
+def test_prompt_buffers_come_with_the_first_long_prompt():
+    """A cache object that sees no prompt longer than a block holds no buffers for prompt chunks."""
+    import torch
+    shape = dataclasses.replace(SMALL, name="prefill_memory", d_model=1024, d_ffn=4096, n_layers=1, batch=1, gamma=4)
+    gpu = G.Gpu(shape, synth.WeightSource(shape, seed=23), [1024])
+    free = lambda: (torch.cuda.synchronize(), torch.cuda.mem_get_info()[0])[1] / 2.0 ** 20  # noqa: E731
+    try:
+        prompt = synth.make_prompt(shape, 24, 700).tolist()
+        f0 = free()
+        kv = sj.sj_kv_create(gpu.model, 1, [1024])
+        f1 = free()
+        sj.sj_prefill(gpu.model, kv, 0, prompt[:5])            # one block
+        f2 = free()
+        sj.sj_prefill(gpu.model, kv, 0, prompt[5:600])
+        f3 = free()
+        sj.sj_kv_set_state(kv, 0, 0, 0)
+        sj.sj_prefill(gpu.model, kv, 0, prompt)
+        f4 = free()
+        sj.sj_kv_free(kv)
+        # cache 1 MB, workspace of 5 rows below 3 MB (logits, statistics, partials of at most 8 slices); planes of 576 rows alone are
+        # 3 * 576 * (1024 + 1024 + 4096) * 2 = 20 MB.  Allocations come in pieces of 2 MB.
+        assert f0 - f1 <= 12 and f2 == f1 and f2 - f3 >= 20 and f4 == f3, (f0 - f1, f1 - f2, f2 - f3, f3 - f4)
+        assert free() >= f0 - 2
+    finally:
+        gpu.close()
