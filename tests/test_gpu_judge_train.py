@@ -131,3 +131,21 @@ def test_grid_equals_its_values_one_at_a_time(n, d, n_C):
         w = out["w_all"][c]
         g = np.append(w[:d], 0.0) + grid[c] * (x.T @ (1.0 / (1.0 + np.exp(-(x @ w))) - y))
         assert np.abs(g).max() <= 2e-11 * max(1.0, grid[c] * n) + 1e-12 * np.abs(x).sum(axis=0).max() * grid[c]
+
+
+@pytest.mark.parametrize("n_val,n_C", [(6000, 1), (4097, 2), (3, 4)])
+def test_validation_over_every_launch_size(n_val, n_C):
+    """Scores of one model or several over validation sets with more rows than the launch has waves, and with fewer than a
+    workgroup has: AUC and thresholds against the definitions, on the scores of the returned weights."""
+    d = 8
+    H, y = synth.make_judge_dataset(51, 200, d)
+    Hv, yv = synth.make_judge_dataset(52, n_val, d)
+    y[:2] = yv[:2] = [0, 1]
+    out = sj.sj_judge_train(_dev(H), _dev(y), _dev(Hv), _dev(yv), np.logspace(-2, 1, n_C), torch.cuda.current_stream())
+    for c in range(n_C):
+        w = out["w_all"][c]
+        sv = jt.scores_of(Hv, w[:d], w[d])
+        assert abs(out["auc"][c] - jt.roc_auc(sv, yv)) <= _auc_slack(sv, yv, 1e-9) + 1e-15
+    sv = jt.scores_of(Hv, out["w"], out["b"])
+    assert abs(out["theta_recall"] - jt.best_recall_threshold(sv, yv)) < 1e-9
+    assert abs(out["theta_f1"] - jt.best_f1_threshold(sv, yv)["theta"]) < 1e-9
