@@ -225,7 +225,8 @@ int sj_verify_head_static(sj_model* m, int32_t batch, int32_t gamma, const void*
  * Everything is computed on the device in fp64 (features read as fp32); the call allocates its workspace
  * (about 32 n_train + 16 n_val min(n_C, 2^22 / n_val) + 8 MB * (d / 1024) bytes), synchronises `stream` and frees it before returning.
  * Errors: SJ_EINVAL (null / misaligned pointer, sizes, a label other than 0 / 1, a set with one class only,
- * non-positive C), SJ_ENOMEM, SJ_EHIP (also when the solver fails to converge). */
+ * non-positive C), SJ_ENOMEM, SJ_EHIP (also when the solver fails to converge, as it does on training features
+ * that are not finite). */
 int sj_judge_train(const float* H_train, const int32_t* y_train, int64_t n_train, const float* H_val,
                    const int32_t* y_val, int64_t n_val, int32_t d, const double* C_grid, int32_t n_C,
                    double* w_all, double* auc, int32_t* passes, int32_t* best_index, double* w_best,

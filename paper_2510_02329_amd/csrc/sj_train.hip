@@ -500,7 +500,7 @@ __global__ __launch_bounds__(1024) void lr_advance_kernel(TrainArgs a) {
         } else
             S.g0 = sqrt(gg);
         if (accepted) {
-            if (S.it >= 100) done = true;
+            if (S.it >= 100 || !isfinite(gg) || !isfinite(f)) done = true;   // a NaN gradient has no maximum: gm would be 0
             else if (gm <= S.tol) done = converged = true;
             else {
                 S.f = f;

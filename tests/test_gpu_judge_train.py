@@ -149,3 +149,16 @@ def test_validation_over_every_launch_size(n_val, n_C):
     sv = jt.scores_of(Hv, out["w"], out["b"])
     assert abs(out["theta_recall"] - jt.best_recall_threshold(sv, yv)) < 1e-9
     assert abs(out["theta_f1"] - jt.best_f1_threshold(sv, yv)["theta"]) < 1e-9
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("d", [8, 1028])
+def test_features_that_are_not_finite_do_not_converge(value, d):
+    H, y = synth.make_judge_dataset(61, 120, d)
+    bad = H.copy()
+    bad[77, d - 3] = value
+    yd = _dev(y)
+    with pytest.raises(sj.SJError, match="did not converge") as e:
+        sj.sj_judge_train(_dev(bad), yd, _dev(H), yd, [0.1, 1.0, 10.0])
+    assert e.value.code == -3
+    assert sj.sj_judge_train(_dev(H), yd, _dev(H), yd, [0.1])["passes"][0] > 0
