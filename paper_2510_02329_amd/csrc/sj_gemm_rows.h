@@ -247,7 +247,7 @@ constexpr int R4_LW = 4;           // loader waves: two for the weights, two for
 // the pace, and 12 % slower on the one-plane LM head of the verify-head workload (909 -> 799 us).
 constexpr int R8_CW = 8;
 
-// RT = row tiles of a row group: up to 9 (144 rows), or 18 with a single operand plane (288 rows: the same 18 operand
+// RT = row tiles of a row group: up to 9 (144 rows), or 18 with a single bf16 operand plane (288 rows: the same 18 operand
 // fragments per k-step in LDS, half as many workgroups re-reading every weight tile through L2).  A wave owns RT / 4
 // whole row tiles for its half of the n-tiles and n-tile w of each of the RT % 4 tiles left over.  Every tile of the group is
 // fetched and multiplied whether it has rows or not, so the group is chosen to fit the rows (row_tiles in sj_plan.h).
@@ -355,6 +355,27 @@ __global__ __launch_bounds__((R8_CW + R4_LW) * 64) void gemm_rows8_kernel(GemmAr
         for (int t = 0; t < NH; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int j = 0; j < NREM; ++j) acc8[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // Where the products are exact to 24 bits, the rounding of the running sums is the error: the accumulators are added to totals of
+    // their own every FOLD k-steps, so that a sum is a chain of short chains, as it is in the few-row kernels, whose waves share K
+    // (fp32, K = 1024 / 8192: rms error against 64 bits 3.7e-7 / 2.9e-6 in one chain, 1.0e-7 / 4.6e-7 folded, 1.9e-7 / 1.5e-6 in the
+    // few-row kernels).  It takes 1 - 2 % of a step of 33 - 144 rows.
+    constexpr int FOLD = std::is_same<T, float>::value ? 4 : 0;
+    f32x4 tot[FOLD ? NFULL : 1][NH], tot8[FOLD && NREM ? NREM : 1];
+    auto fold = [&](bool first) {
+#pragma unroll
+        for (int i = 0; i < NFULL; ++i)
+#pragma unroll
+            for (int t = 0; t < NH; ++t) {
+                tot[i][t] = first ? acc[i][t] : tot[i][t] + acc[i][t];
+                acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+#pragma unroll
+        for (int j = 0; j < NREM; ++j) {
+            tot8[j] = first ? acc8[j] : tot8[j] + acc8[j];
+            acc8[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    if constexpr (FOLD > 0) fold(true);
 
     struct Frags { Frag wf[NH]; Frag w8; Frag bq[NFULL + NREM][SPL]; };
     Frags fA, fB;
@@ -396,6 +417,17 @@ __global__ __launch_bounds__((R8_CW + R4_LW) * 64) void gemm_rows8_kernel(GemmAr
             multiply(fB);
             lds_barrier();                             // stage s + 3 has landed
         }
+        if constexpr (FOLD > 0) {
+            if ((s + 2) % FOLD == 0) fold(false);      // uniform
+        }
+    }
+    if constexpr (FOLD > 0) {
+#pragma unroll
+        for (int i = 0; i < NFULL; ++i)
+#pragma unroll
+            for (int t = 0; t < NH; ++t) acc[i][t] += tot[i][t];
+#pragma unroll
+        for (int j = 0; j < NREM; ++j) acc8[j] += tot8[j];
     }
     if constexpr (EPI == EPI_LOGITS) {
         // Logits, and ONE softmax partial per row and workgroup: a partial per n-tile (16 bytes for 64 bytes of logits) was 74 MB

@@ -576,7 +576,7 @@ extern "C" int sj_kernel_class_shape(const sj_kv* kv, int32_t kernel_class, int3
     if (rows > FEW_ROWS) {
         const sj_config& c = kv->m->cfg;
         const int Nq = c.n_q_heads * c.head_dim, kstep = c.dtype == SJ_DTYPE_FP32 ? 16 : 32;
-        const int planes = c.dtype == SJ_DTYPE_FP32 ? 1 : kv->planes;
+        const int planes = c.dtype == SJ_DTYPE_FP32 ? 0 : kv->planes;
         const GemmPlan* p = kernel_class == 1 ? &kv->plan_qkv[1] : kernel_class == 2 ? &kv->plan_o[1] : kernel_class == 4 ? &kv->plan_d[1] : nullptr;
         const int N = kernel_class == 1 ? Nq + 2 * c.n_kv_heads * c.head_dim : c.d_model;
         const int K = kernel_class == 1 ? c.d_model : kernel_class == 2 ? Nq : c.d_ffn;
@@ -1132,12 +1132,13 @@ static int tune_plans(sj_kv* kv, int rows) {
 
 // More rows: groups of at most 144 rows (9 MFMA row tiles) through the loader-wave kernel; the statistics
 // of EPI_LOGITS are per workgroup (of 8 n-tiles) there, per n-tile with three operand planes.
+template <typename T, int SPL> constexpr int rows_planes = std::is_same<T, float>::value ? 0 : SPL;   // as row_tiles and rows_split count them
 template <typename T, int EPI, int SPL>
 static int gemm_rows(hipStream_t st, const void* Wt, const void* X, size_t xplane, int K, int N, int rows, int split,
                      float* out, void* act, size_t actplane, float4* stats, float inv_temp) {
     const int ntiles = N / 16;
     // a group of rows (whole row tiles) starts row0 * K elements into the plane
-    const int rt = row_tiles(SPL, rows), group_rows = rt * 16;
+    const int rt = row_tiles(rows_planes<T, SPL>, rows), group_rows = rt * 16;
     auto args_of = [&](int row0, int nr) {
         GemmArgs a{};
         a.Wt = Wt;
@@ -1173,20 +1174,14 @@ static int gemm_rows(hipStream_t st, const void* Wt, const void* X, size_t xplan
                 if (!seven) gemm_rows8_kernel<T, EPI, SPL, R2_NT, RT><<<grid, (R8_CW + R4_LW) * 64, 0, st>>>(a, mt);
             }
         };
-        if constexpr (SPL == 1) {
-            switch (rt) {
-                case 4: launch(std::integral_constant<int, 4>{}); break;
-                case 9: launch(std::integral_constant<int, 9>{}); break;
-                case 16: launch(std::integral_constant<int, 16>{}); break;
-                default: launch(std::integral_constant<int, 18>{}); break;
-            }
-        } else {
-            switch (rt) {
-                case 4: launch(std::integral_constant<int, 4>{}); break;
-                case 6: launch(std::integral_constant<int, 6>{}); break;
-                case 8: launch(std::integral_constant<int, 8>{}); break;
-                default: launch(std::integral_constant<int, 9>{}); break;
-            }
+        if (rt == 4) launch(std::integral_constant<int, 4>{});
+        else if (rt == 9) launch(std::integral_constant<int, 9>{});
+        else if constexpr (SPL == 2) {
+            if (rt == 6) launch(std::integral_constant<int, 6>{});
+            else launch(std::integral_constant<int, 8>{});
+        } else if constexpr (std::is_same<T, bf16_t>::value) {
+            if (rt == 16) launch(std::integral_constant<int, 16>{});
+            else launch(std::integral_constant<int, 18>{});
         }
         LAUNCHCHK("gemm_rows");
     } else {
@@ -1232,7 +1227,7 @@ struct Runner {
         const int ksteps = K / Traits<T>::KSTEP;
         if (R <= FEW_ROWS) return resolve_partial(pl[0], N / 16, ksteps, R, SPL, std::is_same<T, bf16_t>::value);
         GemmPlan p = pl[1];
-        p.split = rows_split(p.split, N / 16, ksteps, R, SPL);
+        p.split = rows_split(p.split, N / 16, ksteps, R, rows_planes<T, SPL>);
         return p;
     }
     // `parts`: the K-slices it leaves in w->part

@@ -143,10 +143,12 @@ inline std::vector<GemmPlan> partial_candidates(int ntiles, int ksteps, int rows
 // holds, the one of the two largest that pads them least (equal: fewer groups).  The kernel spends matrix and L2 time on
 // every tile of a group: 126 rows in groups of 144 (score block of 6 x 21, 8B shape): QKV / O / down 30.6 us, LM head 348, in
 // one group of 128: 29.3, 325; 509 rows, 4 x 144 against 4 x 128: gate / up 277 -> 249 us.
+// planes: bf16 operand planes, 0 = fp32 storage, whose folded accumulators leave registers for 144 rows (and groups of 256 or 288 were
+// the slower ones: 252 rows, d 1024: 962 -> 572 us, 500 rows 1195 -> 882).
 inline int row_tiles(int planes, int rows) {
-    static const int one[] = {4, 9, 16, 18}, two[] = {4, 6, 8, 9};
+    static const int lists[3][4] = {{4, 4, 4, 9}, {4, 9, 16, 18}, {4, 6, 8, 9}};
     if (planes > 2) return ROWS_MT;
-    const int* rt = planes == 1 ? one : two;
+    const int* rt = lists[planes];
     for (int i = 0; i < 4; ++i)
         if (rows <= rt[i] * 16) return rt[i];
     auto padded = [&](int t) { return (rows + t * 16 - 1) / (t * 16) * t; };
@@ -176,7 +178,7 @@ inline int rows_split(int rule, int ntiles, int ksteps, int rows, int planes) {
 // and fewer groups can mean more slices), and for any few-row plan the start-up measurement may pick (at most 8 K-slices)
 inline size_t part_elems(int rule, int N, int ksteps, int rows) {
     size_t most = (size_t)8 * std::min(rows, FEW_ROWS) * N;
-    for (int planes = 1; planes <= 3; ++planes)
+    for (int planes = 0; planes <= 3; ++planes)
         for (int r = 0; r < rows; r += 16) {
             const int upto = std::min(r + 16, rows);
             most = std::max(most, (size_t)rows_split(rule, N / 16, ksteps, upto, planes) * upto * N);

@@ -14,7 +14,7 @@ int main() {
                 const int rule = plan_partial(N / 16, ksteps, false).split;
                 size_t need = 0;
                 for (int rows = 1; rows <= 4200; ++rows) {
-                    for (int planes = 1; planes <= 3; ++planes) need = std::max(need, (size_t)rows_split(rule, N / 16, ksteps, rows, planes) * rows * N);
+                    for (int planes = 0; planes <= 3; ++planes) need = std::max(need, (size_t)rows_split(rule, N / 16, ksteps, rows, planes) * rows * N);
                     if (rows % 7 && rows % 16 && rows % 9) continue;
                     ++checked;
                     if (part_elems(rule, N, ksteps, rows) < need && bad++ < 10)
