@@ -1,23 +1,19 @@
-// Weight-streaming GEMM for more than one row tile (batched verification: R = batch * (gamma + 1)
-// rows, up to 144 per launch): Y[R][N] = X[R][K] * W[N][K]^T with W in the re-tiled layout.
+// Weight-streaming GEMM for more than two row tiles (batched verification, scoring, prompt chunks: more than 32 rows, in row groups of
+// 64 - 288): Y[R][N] = X[R][K] * W[N][K]^T with W in the re-tiled layout.
 // Paper reference: the projections of the target forward, Eq. 2 / Eq. 4.
 //
 // With many rows the few-row kernel's scheme (every wave fetches the operand fragments of all rows
 // for its own K-slice) makes the operand the dominant traffic, and every weight byte should still be
-// read once.  Two measured facts shaped this kernel:
+// read once.  Measured facts that shaped this kernel:
 //  * a wave's loads return in order, so a wave that requests weights (HBM, ~2 us) and operand
 //    (L2, < 1 us) can never consume the operand before the weights requested ahead of it arrive -
 //    mixing the two streams in one wave ties the short latency to the long one;
-//  * a workgroup barrier every two k-steps keeps all waves in lock step with the slowest weight load.
-// So the two streams belong to different waves.  Two LOADER waves move the workgroup's weight tiles
-// (8 n-tiles x 4 k-steps = 32 KB per stage) straight from global memory into a ring of 4 LDS
-// buffers, three stages ahead: up to 96 KB per CU in flight, no registers, and they alone wait for
-// HBM (two waves because one wave can have at most 63 loads outstanding).  Four COMPUTE waves share
-// those tiles and split the ROWS: wave w owns row tiles w, w + 4, w + 8, reads their operand
-// fragments straight into a private register ring (3 k-steps ahead) and keeps 3 x 8 accumulator
-// tiles.  One workgroup barrier per 4 k-steps; a weight fragment read from LDS feeds up to 6
-// products, so LDS reads are a third of the MFMA time.  No cross-wave reduction is needed: the
-// epilogue runs straight from the accumulators.  Split-K across workgroups (gridDim.y slices,
+//  * a barrier that also waits for global loads keeps all waves in lock step with the slowest weight load;
+//  * compute waves that load operand fragments themselves run at the sum of weight stream and MFMA time, without those loads at their
+//    maximum, and a row-major operand fragment touches 16 cache lines of which it uses half.
+// So LOADER waves move weight tiles and operand fragments straight from global memory into LDS rings, from planes that the
+// producing kernels wrote as fragments (opnd_off: 1 KB of consecutive memory each), and COMPUTE waves issue no global loads at all.
+// No cross-wave reduction is needed: the epilogue runs straight from the accumulators.  Split-K across workgroups (gridDim.y slices,
 // partials summed by the consumer in slice order) keeps the short projections on all CUs.
 //
 // MFMA convention as in the few-row kernel: A = weight fragment (rows = n), B = operand fragment
@@ -30,13 +26,7 @@
 
 namespace sj {
 
-constexpr int R2_CW = 4;           // compute waves
-constexpr int R2_LW = 2;           // loader waves (each moves half of the n-tiles)
-constexpr int R2_NT = 8;           // n-tiles per workgroup
-constexpr int R2_KB = 4;           // k-steps per stage
-constexpr int R2_NB = 4;           // LDS stage buffers
-constexpr int R2_MTW = 3;          // row tiles per compute wave (4 waves x 3 >= 9 row tiles)
-constexpr int R2_RING = 4;         // operand ring (k-steps) = k-steps per stage
+constexpr int ROWS_NT = 8;         // n-tiles per workgroup
 
 // Softmax partial (max, sum exp((l - max)/T), lowest arg-max) of a row over `n` <= NTILES neighbouring n-tiles from nt on: the row's four
 // lanes hold four columns of each tile; all of them get the result.
@@ -67,10 +57,10 @@ __device__ __forceinline__ float4 rows_softmax_stat(const f32x4* v, int nt, int 
     return float4{mx, se, __int_as_float(arg), 0.f};
 }
 
-// Epilogue of the many-row kernels for ONE accumulator tile (row tile m, n-tile nt): the lane holds columns
+// Epilogue of partial sums and SwiGLU for ONE accumulator tile (row tile m, n-tile nt): the lane holds columns
 // nt*16 + 4g .. +3 of row m*16 + r.  Uniform per wave; rows >= R take part in the shuffles and store nothing.
 template <typename T, int EPI>
-__device__ __forceinline__ void rows_epilogue_tile(const GemmArgs& a, const f32x4& v, int m, int nt, int ntiles, int r, int g) {
+__device__ __forceinline__ void rows_epilogue_tile(const GemmArgs& a, const f32x4& v, int m, int nt, int r, int g) {
     const int row = m * 16 + r;
     const bool valid = row < a.R;
     if constexpr (EPI == EPI_PARTIAL) {
@@ -88,143 +78,12 @@ __device__ __forceinline__ void rows_epilogue_tile(const GemmArgs& a, const f32x
         }
         if (valid && g < 2)
             Traits<T>::store_split4(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, nt * 8 + 4 * g, a.N / 2), a.actplane, y);
-    } else {
-        // logits + this tile's softmax partial of the row
-        const float4 st = rows_softmax_stat<1>(&v, nt, 1, a.inv_temp, g);
-        if (valid) {
-            *reinterpret_cast<f32x4*>(a.out + (size_t)row * a.N + (size_t)nt * 16 + 4 * g) = v;
-            if (g == 0) a.stats[(size_t)row * ntiles + nt] = st;
-        }
     }
-}
-
-// The same over a wave's tiles: wave w owns row tiles w, w + 4, w + 8.
-template <typename T, int EPI, int NT = R2_NT>
-__device__ __forceinline__ void rows_epilogue(const GemmArgs& a, const f32x4 (&acc)[R2_MTW][NT], int w, int my_tiles, int nt0,
-                                              int ntiles, int r, int g) {
-#pragma unroll
-    for (int i = 0; i < R2_MTW; ++i) {
-        if (i >= my_tiles) continue;                       // wave-uniform
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            if (nt0 + t >= ntiles) continue;               // uniform
-            rows_epilogue_tile<T, EPI>(a, acc[i][t], w + R2_CW * i, nt0 + t, ntiles, r, g);
-        }
-    }
-}
-
-template <typename T, int EPI, int SPL>
-__global__ __launch_bounds__((R2_CW + R2_LW) * 64) void gemm_rows2_kernel(GemmArgs a, int mt) {
-    constexpr int KF = Traits<T>::KF, KSTEP = Traits<T>::KSTEP;
-    __shared__ u32x4 Ws[R2_NB][R2_KB][R2_NT][64];      // 4 x 32 KB
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int r = lane & 15, g = lane >> 4;
-    const int KS = a.K / KSTEP, ntiles = a.N / 16;
-    const int nt0 = blockIdx.x * R2_NT;
-    const int ks0 = (int)((long long)blockIdx.y * KS / gridDim.y), ks1 = (int)((long long)(blockIdx.y + 1) * KS / gridDim.y);
-    const int nks = ks1 - ks0, nstage = (nks + R2_KB - 1) / R2_KB;
-    if (nstage <= 0) return;                           // uniform for the workgroup
-
-    if (w >= R2_CW) {
-        // ---------------- loader waves: stage s -> buffer s % 4, up to three stages ahead -----------------
-        // tiles past the end of N (last workgroup) and k-steps past the slice re-read valid ones
-        const int half = w - R2_CW;                    // this wave moves tiles half*4 .. half*4 + 3
-        const char* Wbase = reinterpret_cast<const char*>(a.Wt) + (size_t)lane * 16;
-        auto issue = [&](int s) {
-            u32x4* dst = &Ws[s % R2_NB][0][0][0];
-#pragma unroll
-            for (int kb = 0; kb < R2_KB; ++kb) {
-                const size_t k = (size_t)(ks0 + min(s * R2_KB + kb, nks - 1));
-#pragma unroll
-                for (int tt = 0; tt < R2_NT / R2_LW; ++tt) {
-                    const int t = half * (R2_NT / R2_LW) + tt;
-                    const size_t tile = (size_t)min(nt0 + t, ntiles - 1);
-                    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Wbase + (tile * KS + k) * 1024),
-                                                     (__attribute__((address_space(3))) void*)(dst + (kb * R2_NT + t) * 64), 16, 0, 0);
-                }
-            }
-        };
-        // every stage is 16 loads of this wave; stages are always issued (clamped), so the number of
-        // loads outstanding behind the stage that has to be complete is known: 2 stages = 32 loads
-        // (a stage index past the end re-reads the last stage into its own buffer: same bytes)
-        issue(0);
-        issue(min(1, nstage - 1));
-        issue(min(2, nstage - 1));
-        asm volatile("s_waitcnt vmcnt(32)" ::: "memory");          // stage 0 has landed
-        lds_barrier();
-        for (int s = 0; s < nstage; ++s) {
-            // buffer (s + 3) % 4 = (s - 1) % 4 was released by the barrier that ended iteration s - 1
-            issue(min(s + 3, nstage - 1));
-            asm volatile("s_waitcnt vmcnt(32)" ::: "memory");      // stage s + 1 has landed
-            lds_barrier();
-        }
-        wait_vm0();
-        return;
-    }
-
-    // ---------------- compute waves ----------------
-    // row tiles of this wave (tiles past the rows re-read tile 0; rows past R are stale; neither is stored)
-    const T* Xr[R2_MTW];
-#pragma unroll
-    for (int i = 0; i < R2_MTW; ++i) {
-        const int m = (w + R2_CW * i) * 16 < a.R ? w + R2_CW * i : 0;
-        Xr[i] = reinterpret_cast<const T*>(a.X) + (((size_t)m * KS + ks0) * 64 + lane) * KF;
-    }
-    const int my_tiles = (mt > w) ? (mt - w + R2_CW - 1) / R2_CW : 0;     // row tiles w, w+4, .. below mt
-
-    f32x4 acc[R2_MTW][R2_NT];
-#pragma unroll
-    for (int i = 0; i < R2_MTW; ++i)
-#pragma unroll
-        for (int t = 0; t < R2_NT; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    Frag bq[R2_RING][R2_MTW][SPL];
-    auto load_b = [&](int slot, int kk) {
-        const size_t k = (size_t)min(kk, nks - 1) * (16 * KSTEP);
-#pragma unroll
-        for (int i = 0; i < R2_MTW; ++i)
-#pragma unroll
-            for (int sp = 0; sp < SPL; ++sp) bq[slot][i][sp].u = *reinterpret_cast<const u32x4*>(Xr[i] + sp * a.xplane + k);
-    };
-#pragma unroll
-    for (int j = 0; j < R2_RING - 1; ++j) load_b(j, j);
-    lds_barrier();                                   // stage 0 is in LDS
-    for (int s = 0; s < nstage; ++s) {
-        const u32x4* Wb = &Ws[s % R2_NB][0][0][0];
-#pragma unroll
-        for (int kb = 0; kb < R2_KB; ++kb) {
-            const int kk = s * R2_KB + kb;
-            load_b((kb + R2_RING - 1) % R2_RING, kk + R2_RING - 1);
-            if (kk < nks) {
-                Frag wf[R2_NT];
-#pragma unroll
-                for (int t = 0; t < R2_NT; ++t) wf[t].u = Wb[(kb * R2_NT + t) * 64 + lane];
-#pragma unroll
-                for (int i = 0; i < R2_MTW; ++i) {
-                    if (i < my_tiles) {
-#pragma unroll
-                        for (int sp = 0; sp < SPL; ++sp)
-#pragma unroll
-                            for (int t = 0; t < R2_NT; ++t) Traits<T>::mma(wf[t], bq[kb % R2_RING][i][sp], acc[i][t]);
-                    }
-                }
-            }
-        }
-        lds_barrier();                               // everyone is done with this buffer; the next one has landed
-    }
-
-    rows_epilogue<T, EPI>(a, acc, w, my_tiles, nt0, ntiles, r, g);
 }
 
 // ---------------------------------------------------------------------------------------------
-// Same product with the OPERAND delivered through LDS as well (one or two operand planes).
-// Measured on the kernel above: with the compute waves' own operand loads taken out it runs at
-// max(weight stream, MFMA), with them near the sum, and a row-major operand fragment touches 16 cache
-// lines of which it uses half.  Here the compute waves issue no global loads at all: loader waves
-// fetch the operand fragments of all row tiles next to the weight tiles of the same k-step, from
-// planes that the producing kernels wrote as fragments (opnd_off: 1 KB of consecutive memory each).  A stage is ONE k-step; a wave's loads come back in the order
-// it issued them, so weights (HBM: 8 stages of 8 KB) and operand (an L2 hit: 5 stages of
-// 9 x SPL KB) are fetched by different loader waves with rings of their own; one barrier per k-step;
+// A stage is ONE k-step; a wave's loads come back in the order it issued them, so weights (HBM: 8 stages of 8 KB) and operand (an L2
+// hit: 5 stages of RT x SPL KB) are fetched by different loader waves with rings of their own; one barrier per k-step;
 // the compute waves read the fragments of step s + 1 from LDS while they multiply step s.  An
 // operand fragment in LDS has the layout the lanes read it in (lane l: 16 bytes at l * 16), which is
 // also how a direct global->LDS load of 16 bytes per lane deposits it.
@@ -247,13 +106,12 @@ constexpr int R4_LW = 4;           // loader waves: two for the weights, two for
 // the pace, and 12 % slower on the one-plane LM head of the verify-head workload (909 -> 799 us).
 constexpr int R8_CW = 8;
 
-// RT = row tiles of a row group: up to 9 (144 rows), or 18 with a single bf16 operand plane (288 rows: the same 18 operand
-// fragments per k-step in LDS, half as many workgroups re-reading every weight tile through L2).  A wave owns RT / 4
+// RT = row tiles of a row group: up to 9 (144 rows) with two operand planes or fp32, 6 with three, 18 with a single bf16 plane (288
+// rows: the same 18 operand fragments per k-step in LDS, half as many workgroups re-reading every weight tile through L2).  A wave owns RT / 4
 // whole row tiles for its half of the n-tiles and n-tile w of each of the RT % 4 tiles left over.  Every tile of the group is
 // fetched and multiplied whether it has rows or not, so the group is chosen to fit the rows (row_tiles in sj_plan.h).
-template <typename T, int EPI, int SPL, int NT = R2_NT, int RT = ROWS_MT>
+template <typename T, int EPI, int SPL, int NT = ROWS_NT, int RT = ROWS_MT>
 __global__ __launch_bounds__((R8_CW + R4_LW) * 64) void gemm_rows8_kernel(GemmArgs a, int mt) {
-    static_assert(SPL <= 2, "three operand planes do not fit");
     static_assert(NT == 7 || NT == 8, "n-tile halves are 4 + 4 or 4 + 3");
     static_assert(RT * SPL <= 2 * ROWS_MT, "the operand stages in LDS hold 18 fragments");
     constexpr int KF = Traits<T>::KF, KSTEP = Traits<T>::KSTEP;
@@ -358,8 +216,10 @@ __global__ __launch_bounds__((R8_CW + R4_LW) * 64) void gemm_rows8_kernel(GemmAr
     // Where the products are exact to 24 bits, the rounding of the running sums is the error: the accumulators are added to totals of
     // their own every FOLD k-steps, so that a sum is a chain of short chains, as it is in the few-row kernels, whose waves share K
     // (fp32, K = 1024 / 8192: rms error against 64 bits 3.7e-7 / 2.9e-6 in one chain, 1.0e-7 / 4.6e-7 folded, 1.9e-7 / 1.5e-6 in the
-    // few-row kernels).  It takes 1 - 2 % of a step of 33 - 144 rows.
-    constexpr int FOLD = std::is_same<T, float>::value ? 4 : 0;
+    // few-row kernels; three planes, K = 4096: of 1.1 M stored K / V elements 560 round away from the 64-bit value's neighbour in one
+    // chain, 304 folded, 281 in the few-row kernels).  It takes 1 - 2 % of a step of 33 - 144 rows.  With one or two bf16 planes the
+    // operand's rounding (2^-9, 2^-18) is above that of the sums.
+    constexpr int FOLD = std::is_same<T, float>::value ? 4 : SPL == 3 ? 8 : 0;
     f32x4 tot[FOLD ? NFULL : 1][NH], tot8[FOLD && NREM ? NREM : 1];
     auto fold = [&](bool first) {
 #pragma unroll
@@ -489,12 +349,12 @@ __global__ __launch_bounds__((R8_CW + R4_LW) * 64) void gemm_rows8_kernel(GemmAr
         if (t >= nh || nt0 + t0 + t >= ntiles) continue;   // uniform
 #pragma unroll
         for (int i = 0; i < NFULL; ++i)
-            if (ra + 4 * i < mt) rows_epilogue_tile<T, EPI>(a, acc[i][t], ra + 4 * i, nt0 + t0 + t, ntiles, r, g);
+            if (ra + 4 * i < mt) rows_epilogue_tile<T, EPI>(a, acc[i][t], ra + 4 * i, nt0 + t0 + t, r, g);
     }
     if (w < NT && nt0 + w < ntiles) {
 #pragma unroll
         for (int j = 0; j < NREM; ++j)
-            if (4 * NFULL + j < mt) rows_epilogue_tile<T, EPI>(a, acc8[j], 4 * NFULL + j, nt0 + w, ntiles, r, g);
+            if (4 * NFULL + j < mt) rows_epilogue_tile<T, EPI>(a, acc8[j], 4 * NFULL + j, nt0 + w, r, g);
     }
 }
 

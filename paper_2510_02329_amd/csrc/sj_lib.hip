@@ -580,8 +580,8 @@ extern "C" int sj_kernel_class_shape(const sj_kv* kv, int32_t kernel_class, int3
         const GemmPlan* p = kernel_class == 1 ? &kv->plan_qkv[1] : kernel_class == 2 ? &kv->plan_o[1] : kernel_class == 4 ? &kv->plan_d[1] : nullptr;
         const int N = kernel_class == 1 ? Nq + 2 * c.n_kv_heads * c.head_dim : c.d_model;
         const int K = kernel_class == 1 ? c.d_model : kernel_class == 2 ? Nq : c.d_ffn;
-        snprintf(buf, (size_t)buf_len, "gemm_rows%s: row groups of %d in one launch, 8 or 7 n-tiles per workgroup, %d K-slice(s)",
-                 kv->planes == 3 ? "2" : "8", row_tiles(planes, rows) * 16, p ? rows_split(p->split, N / 16, K / kstep, rows, planes) : 1);
+        snprintf(buf, (size_t)buf_len, "gemm_rows8: row groups of %d in one launch, 8 or 7 n-tiles per workgroup, %d K-slice(s)",
+                 row_tiles(planes, rows) * 16, p ? rows_split(p->split, N / 16, K / kstep, rows, planes) : 1);
         return SJ_OK;
     }
     GemmPlan p = kernel_class == 1 ? kv->plan_qkv[0] : kernel_class == 2 ? kv->plan_o[0] : kernel_class == 3 ? kv->plan_gu
@@ -1130,69 +1130,39 @@ static int tune_plans(sj_kv* kv, int rows) {
     return rc;
 }
 
-// More rows: groups of at most 144 rows (9 MFMA row tiles) through the loader-wave kernel; the statistics
-// of EPI_LOGITS are per workgroup (of 8 n-tiles) there, per n-tile with three operand planes.
+// More rows: all row groups in one launch of the loader-wave kernel, the workgroups of an n-tile group side by side on one XCD, so that the
+// weights are fetched from HBM once for all rows.  The statistics of EPI_LOGITS are per workgroup (of 8 n-tiles).
 template <typename T, int SPL> constexpr int rows_planes = std::is_same<T, float>::value ? 0 : SPL;   // as row_tiles and rows_split count them
 template <typename T, int EPI, int SPL>
 static int gemm_rows(hipStream_t st, const void* Wt, const void* X, size_t xplane, int K, int N, int rows, int split,
                      float* out, void* act, size_t actplane, float4* stats, float inv_temp) {
-    const int ntiles = N / 16;
-    // a group of rows (whole row tiles) starts row0 * K elements into the plane
-    const int rt = row_tiles(rows_planes<T, SPL>, rows), group_rows = rt * 16;
-    auto args_of = [&](int row0, int nr) {
-        GemmArgs a{};
-        a.Wt = Wt;
-        a.X = (const char*)X + (size_t)row0 * K * sizeof(T);
-        a.xplane = xplane; a.actplane = actplane;
-        a.K = K; a.N = N;
-        a.R = nr; a.slice_rows = rows;
-        a.inv_temp = inv_temp;
-        if (EPI == EPI_PARTIAL) a.out = out + (size_t)row0 * N;            // [split][rows][N]
-        else if (EPI == EPI_LOGITS) { a.out = out + (size_t)row0 * N; a.stats = stats + (size_t)row0 * ntiles; }
-        else a.act = (char*)act + (size_t)row0 * (N / 2) * sizeof(T);
-        return a;
+    const int ntiles = N / 16, rt = row_tiles(rows_planes<T, SPL>, rows), rgroups = (rows + rt * 16 - 1) / (rt * 16);
+    const int mt = (std::min(rows, rt * 16) + 15) / 16;
+    GemmArgs a{};
+    a.Wt = Wt; a.X = X; a.xplane = xplane; a.actplane = actplane;
+    a.K = K; a.N = N; a.R = rows; a.slice_rows = rows;
+    a.inv_temp = inv_temp;
+    a.out = out; a.stats = stats; a.act = act;
+    a.rgroups = rgroups;
+    // 7 n-tiles per workgroup where that fills whole rounds of the chip and 8 do not (gate/up of the 8B shape: 256 workgroups instead of
+    // 224), from 8 row tiles on (below that the lighter weight stream per CU loses)
+    const bool seven = EPI == EPI_SWIGLU && mt >= 8 && rt >= 8 && ntiles % 7 == 0 && (ntiles / 7) % 256 == 0 && ((ntiles + 7) / 8) % 256 != 0;
+    const int per = seven ? 7 : ROWS_NT, ngroups = (ntiles + per - 1) / per;
+    const dim3 grid(rgroups > 1 ? (ngroups + 7) / 8 * 8 * rgroups : ngroups, EPI == EPI_PARTIAL ? split : 1);
+    auto launch = [&](auto rt_tag) {
+        constexpr int RT = decltype(rt_tag)::value;
+        if (rt != RT) return;
+        if constexpr (EPI == EPI_SWIGLU && RT >= 8) {
+            if (seven) gemm_rows8_kernel<T, EPI, SPL, 7, RT><<<grid, (R8_CW + R4_LW) * 64, 0, st>>>(a, mt);
+        }
+        if (!seven) gemm_rows8_kernel<T, EPI, SPL, ROWS_NT, RT><<<grid, (R8_CW + R4_LW) * 64, 0, st>>>(a, mt);
     };
-    if constexpr (SPL <= 2) {
-        // one launch for all row groups: the workgroups of an n-tile group run side by side on one XCD, so the
-        // weights are fetched from HBM once for all rows (gemm_rows8_kernel).  7 n-tiles per workgroup where that
-        // fills whole rounds of the chip and 8 do not (gate/up of the 8B shape: 256 workgroups instead of 224), from
-        // 8 row tiles on (below that the lighter weight stream per CU loses)
-        const int rgroups = (rows + group_rows - 1) / group_rows;
-        const int mt = (std::min(rows, group_rows) + 15) / 16;
-        GemmArgs a = args_of(0, rgroups > 1 ? rows : std::min(rows, group_rows));
-        a.rgroups = rgroups;
-        const bool seven = EPI == EPI_SWIGLU && mt >= 8 && rt >= 8 && ntiles % 7 == 0 && (ntiles / 7) % 256 == 0 && ((ntiles + 7) / 8) % 256 != 0;
-        const int per = seven ? 7 : R2_NT, ngroups = (ntiles + per - 1) / per;
-        const int gx = rgroups > 1 ? (ngroups + 7) / 8 * 8 * rgroups : ngroups;
-        const dim3 grid(gx, EPI == EPI_PARTIAL ? split : 1);
-        auto launch = [&](auto rt_tag) {
-            constexpr int RT = decltype(rt_tag)::value;
-            if constexpr (RT * SPL <= 2 * ROWS_MT) {
-                if constexpr (EPI == EPI_SWIGLU && RT >= 8) {
-                    if (seven) gemm_rows8_kernel<T, EPI, SPL, 7, RT><<<grid, (R8_CW + R4_LW) * 64, 0, st>>>(a, mt);
-                }
-                if (!seven) gemm_rows8_kernel<T, EPI, SPL, R2_NT, RT><<<grid, (R8_CW + R4_LW) * 64, 0, st>>>(a, mt);
-            }
-        };
-        if (rt == 4) launch(std::integral_constant<int, 4>{});
-        else if (rt == 9) launch(std::integral_constant<int, 9>{});
-        else if constexpr (SPL == 2) {
-            if (rt == 6) launch(std::integral_constant<int, 6>{});
-            else launch(std::integral_constant<int, 8>{});
-        } else if constexpr (std::is_same<T, bf16_t>::value) {
-            if (rt == 16) launch(std::integral_constant<int, 16>{});
-            else launch(std::integral_constant<int, 18>{});
-        }
-        LAUNCHCHK("gemm_rows");
-    } else {
-        for (int row0 = 0; row0 < rows; row0 += group_rows) {
-            const int nr = std::min(group_rows, rows - row0);
-            const GemmArgs a = args_of(row0, nr);
-            const dim3 grid((ntiles + R2_NT - 1) / R2_NT, EPI == EPI_PARTIAL ? split : 1);
-            gemm_rows2_kernel<T, EPI, SPL><<<grid, (R2_CW + R2_LW) * 64, 0, st>>>(a, (nr + 15) / 16);
-            LAUNCHCHK("gemm_rows");
-        }
-    }
+    launch(std::integral_constant<int, 4>{});              // the sizes of row_tiles
+    if constexpr (SPL == 3) { launch(std::integral_constant<int, 5>{}); launch(std::integral_constant<int, 6>{}); }
+    else launch(std::integral_constant<int, 9>{});
+    if constexpr (SPL == 2) { launch(std::integral_constant<int, 6>{}); launch(std::integral_constant<int, 8>{}); }
+    if constexpr (SPL == 1 && std::is_same<T, bf16_t>::value) { launch(std::integral_constant<int, 16>{}); launch(std::integral_constant<int, 18>{}); }
+    LAUNCHCHK("gemm_rows");
     return SJ_OK;
 }
 
@@ -1396,7 +1366,7 @@ struct Runner {
             rc = exact_operand
                 ? gemm_rows<T, EPI_LOGITS, 1>(st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, 1, kv->logits, nullptr, 0, kv->stats, md.inv_temp)
                 : gemm_rows<T, EPI_LOGITS, SPL>(st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, 1, kv->logits, nullptr, 0, kv->stats, md.inv_temp);
-            nblk = exact_operand || SPL <= 2 ? md.V / 16 / R2_NT : md.V / 16;      // gemm_rows8: per workgroup; gemm_rows2: per n-tile
+            nblk = md.V / 16 / ROWS_NT;
         } else {
             rc = exact_operand
                 ? few_logits<T, 1>(kv->plan_lm, st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, kv->logits, kv->stats, md.inv_temp)

@@ -144,10 +144,11 @@ inline std::vector<GemmPlan> partial_candidates(int ntiles, int ksteps, int rows
 // every tile of a group: 126 rows in groups of 144 (score block of 6 x 21, 8B shape): QKV / O / down 30.6 us, LM head 348, in
 // one group of 128: 29.3, 325; 509 rows, 4 x 144 against 4 x 128: gate / up 277 -> 249 us.
 // planes: bf16 operand planes, 0 = fp32 storage, whose folded accumulators leave registers for 144 rows (and groups of 256 or 288 were
-// the slower ones: 252 rows, d 1024: 962 -> 572 us, 500 rows 1195 -> 882).
+// the slower ones: 252 rows, d 1024: 962 -> 572 us, 500 rows 1195 -> 882).  Three planes: the 18 operand fragments that the stages in
+// LDS hold are six row tiles (8B shape cut to 3 layers, 45 / 144 / 288 rows: 1018 / 2937 / 7087 us with compute waves that loaded the
+// operand themselves, in groups of 144; 823 / 1533 / 2582 so).
 inline int row_tiles(int planes, int rows) {
-    static const int lists[3][4] = {{4, 4, 4, 9}, {4, 9, 16, 18}, {4, 6, 8, 9}};
-    if (planes > 2) return ROWS_MT;
+    static const int lists[4][4] = {{4, 4, 4, 9}, {4, 9, 16, 18}, {4, 6, 8, 9}, {4, 4, 5, 6}};
     const int* rt = lists[planes];
     for (int i = 0; i < 4; ++i)
         if (rows <= rt[i] * 16) return rt[i];
@@ -174,8 +175,8 @@ inline int rows_split(int rule, int ntiles, int ksteps, int rows, int planes) {
     return best;
 }
 // fp32 elements of the partials of a projection with up to `rows` rows, for every plane count, since a cache object's can be changed
-// between steps (slices and group depend on the rows in steps of 16; three planes work in groups of 144 rows where two have chosen 128,
-// and fewer groups can mean more slices), and for any few-row plan the start-up measurement may pick (at most 8 K-slices)
+// between steps (slices and group depend on the rows in steps of 16; another plane count has other groups, and fewer groups can
+// mean more slices), and for any few-row plan the start-up measurement may pick (at most 8 K-slices)
 inline size_t part_elems(int rule, int N, int ksteps, int rows) {
     size_t most = (size_t)8 * std::min(rows, FEW_ROWS) * N;
     for (int planes = 0; planes <= 3; ++planes)

@@ -37,3 +37,32 @@ def test_fp32_head_of_many_rows_is_as_exact_as_of_few(d):
         many = rms(_logits(shape, src, hidden, batch, gamma, 0), 32)
         print(f"d {d}, {batch * (gamma + 1)} rows: rms error {many:.3e}, 32 rows {few:.3e}", flush=True)
         assert many <= 1.1 * few
+
+
+def test_three_plane_prompt_chunk_is_as_exact_as_blocks():
+    """The first layer's K / V rows of a prompt are bf16 roundings of one product: the share that rounds to the other neighbour of the
+    64-bit value measures the product's error.  A chunk of 600 rows against blocks of 20 rows through the few-row kernels."""
+    from oracle import selfjudge_oracle as orc
+    from tests import helpers
+    shape = synth.ModelShape("precision_planes", "bf16", 1, 4096, 8, 8, 128, 256, 512, 10000.0, batch=1, gamma=19)
+    src = synth.WeightSource(shape, seed=7, norm_jitter=0.1)
+    n = 560
+    prompt = synth.make_prompt(shape, 8, n).tolist()
+    cache = orc.SeqCache(helpers.oracle_config(shape), n, storage="bf16")
+    orc.block_forward(helpers.oracle_config(shape), helpers.oracle_weights(src), [cache], [prompt])
+    gpu = G.Gpu(shape, src, [n])
+    share = {}
+    try:
+        sj.sj_set_operand_planes(gpu.kv, 3)
+        for way, pieces in (("chunk", [prompt]), ("blocks", [prompt[i:i + 20] for i in range(0, n, 20)])):
+            sj.sj_kv_set_state(gpu.kv, 0, 0, 0)
+            for p in pieces:
+                sj.sj_prefill(gpu.model, gpu.kv, 0, p)
+            k, v = gpu.kv_rows(0, 0, 0, n)
+            share[way] = sum(int((a != b[0][:, :n]).sum()) for a, b in ((k, cache.k), (v, cache.v)))
+    finally:
+        gpu.close()
+    total = 2 * n * 1024
+    print(f"of {total} stored elements take the other neighbour: chunk {share['chunk']}, blocks {share['blocks']}", flush=True)
+    # counts of independent rare events: three standard deviations of their difference, and the 64-bit oracle itself is exact
+    assert share["chunk"] <= share["blocks"] + 3.0 * np.sqrt(share["chunk"] + share["blocks"])

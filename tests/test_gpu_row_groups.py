@@ -15,12 +15,12 @@ from tests.test_gpu_bf16 import SMALL, _fill_caches
 pytestmark = pytest.mark.gpu
 
 
-# rows = batch * (gamma + 1): edges of the groups of 64, 96, 128, 144 (two planes), 64, 144, 256, 288 (one), 144 (three), 64 and
-# 144 (fp32), and two or three groups
+# rows = batch * (gamma + 1): edges of the groups of 64, 96, 128, 144 (two planes), 64, 144, 256, 288 (one), 64, 80, 96 (three), 64 and
+# 144 (fp32), and several groups
 @pytest.mark.parametrize("batch,gamma,planes,dtype", [(11, 2, 2, "bf16"), (16, 3, 2, "bf16"), (13, 4, 2, "bf16"), (12, 7, 2, "bf16"), (14, 8, 2, "bf16"),
                                                       (16, 7, 2, "bf16"), (15, 8, 2, "bf16"), (16, 8, 2, "bf16"), (29, 4, 2, "bf16"), (37, 6, 2, "bf16"),
                                                       (13, 4, 1, "bf16"), (17, 8, 1, "bf16"), (32, 8, 1, "bf16"), (13, 4, 3, "bf16"),
-                                                      (37, 6, 3, "bf16"), (33, 8, 3, "bf16"),
+                                                      (37, 6, 3, "bf16"), (33, 8, 3, "bf16"), (16, 3, 3, "bf16"), (12, 7, 3, "bf16"),
                                                       (9, 3, 1, "fp32"), (29, 4, 1, "fp32"), (32, 4, 1, "fp32"), (32, 8, 1, "fp32")])
 def test_step_over_row_groups(batch, gamma, planes, dtype):
     shape = dataclasses.replace(SMALL, name=f"groups_{batch}_{gamma}_{planes}_{dtype}", dtype=dtype, n_layers=1, batch=batch, gamma=gamma)
