@@ -66,3 +66,30 @@ def test_three_plane_prompt_chunk_is_as_exact_as_blocks():
     print(f"of {total} stored elements take the other neighbour: chunk {share['chunk']}, blocks {share['blocks']}", flush=True)
     # counts of independent rare events: three standard deviations of their difference, and the 64-bit oracle itself is exact
     assert share["chunk"] <= share["blocks"] + 3.0 * np.sqrt(share["chunk"] + share["blocks"])
+
+
+def test_fp32_residual_epilogue_is_as_exact_as_slices():
+    """Blocks of up to 8 rows close a sub-layer without K-slices, larger ones with up to eight (the last layer always): the same
+    rows either way."""
+    import dataclasses
+    from oracle import selfjudge_oracle as orc
+    from tests import helpers
+    from tests.test_gpu_bf16 import _fill_caches
+    shape = synth.ModelShape("precision_resid", "fp32", 2, 512, 8, 8, 64, 16384, 512, 10000.0, batch=1, gamma=5, weight_std=0.05)
+    src = synth.WeightSource(shape, seed=11, norm_jitter=0.1)
+    cfg, W = helpers.oracle_config(shape), helpers.oracle_weights(src)
+    err = {}
+    for batch in (1, 2, 4):                                    # 6, 12, 24 rows; the first sequence is the same
+        many = dataclasses.replace(shape, batch=batch)
+        gpu = G.Gpu(many, src, [64] * batch)
+        try:
+            caches = _fill_caches(many, gpu, cfg, [20] * batch, seed=12, capacity=[64] * batch)
+            draft = synth.make_draft(dataclasses.replace(shape, batch=4), seed=13)
+            draft = {k: v[:batch] for k, v in draft.items()}
+            out = gpu.step(draft, 0.5, 5)
+            ref = orc.block_forward(cfg, W, caches[:1], [[caches[0].pending] + draft["tokens"][0].tolist()])[0]["hn"]
+            err[batch] = float(np.sqrt(((out["hn"][0] - ref) ** 2).mean()))
+        finally:
+            gpu.close()
+    print("rms error of the hidden states, 6 / 12 / 24 rows: %.3e %.3e %.3e" % tuple(err.values()), flush=True)
+    assert err[1] <= 1.1 * max(err[2], err[4])
