@@ -59,7 +59,7 @@ __device__ __forceinline__ float4 rows_softmax_stat(const f32x4* v, int nt, int 
 
 // Epilogue of partial sums and SwiGLU for ONE accumulator tile (row tile m, n-tile nt): the lane holds columns
 // nt*16 + 4g .. +3 of row m*16 + r.  Uniform per wave; rows >= R take part in the shuffles and store nothing.
-template <typename T, int EPI>
+template <typename T, int EPI, int SPL>
 __device__ __forceinline__ void rows_epilogue_tile(const GemmArgs& a, const f32x4& v, int m, int nt, int r, int g) {
     const int row = m * 16 + r;
     const bool valid = row < a.R;
@@ -77,7 +77,7 @@ __device__ __forceinline__ void rows_epilogue_tile(const GemmArgs& a, const f32x
             y[e] = gate / (1.0f + expf(-gate)) * up;
         }
         if (valid && g < 2)
-            Traits<T>::store_split4(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, nt * 8 + 4 * g, a.N / 2), a.actplane, y);
+            Traits<T>::template store_split4<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, nt * 8 + 4 * g, a.N / 2), a.actplane, y);
     }
 }
 
@@ -349,12 +349,12 @@ __global__ __launch_bounds__((R8_CW + R4_LW) * 64) void gemm_rows8_kernel(GemmAr
         if (t >= nh || nt0 + t0 + t >= ntiles) continue;   // uniform
 #pragma unroll
         for (int i = 0; i < NFULL; ++i)
-            if (ra + 4 * i < mt) rows_epilogue_tile<T, EPI>(a, acc[i][t], ra + 4 * i, nt0 + t0 + t, r, g);
+            if (ra + 4 * i < mt) rows_epilogue_tile<T, EPI, SPL>(a, acc[i][t], ra + 4 * i, nt0 + t0 + t, r, g);
     }
     if (w < NT && nt0 + w < ntiles) {
 #pragma unroll
         for (int j = 0; j < NREM; ++j)
-            if (4 * NFULL + j < mt) rows_epilogue_tile<T, EPI>(a, acc8[j], 4 * NFULL + j, nt0 + w, r, g);
+            if (4 * NFULL + j < mt) rows_epilogue_tile<T, EPI, SPL>(a, acc8[j], 4 * NFULL + j, nt0 + w, r, g);
     }
 }
 

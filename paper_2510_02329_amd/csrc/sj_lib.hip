@@ -6,6 +6,7 @@
 #include "sj_attn.h"
 #include "sj_attn_rows.h"
 #include "sj_gemm_rows.h"
+#include "sj_gemm_tile.h"
 #include "sj_gemm_ring.h"
 
 #include <algorithm>
@@ -580,7 +581,9 @@ extern "C" int sj_kernel_class_shape(const sj_kv* kv, int32_t kernel_class, int3
         const GemmPlan* p = kernel_class == 1 ? &kv->plan_qkv[1] : kernel_class == 2 ? &kv->plan_o[1] : kernel_class == 4 ? &kv->plan_d[1] : nullptr;
         const int N = kernel_class == 1 ? Nq + 2 * c.n_kv_heads * c.head_dim : c.d_model;
         const int K = kernel_class == 1 ? c.d_model : kernel_class == 2 ? Nq : c.d_ffn;
-        snprintf(buf, (size_t)buf_len, "gemm_rows8: row groups of %d in one launch, 8 or 7 n-tiles per workgroup, %d K-slice(s)",
+        const int trt = kernel_class == 3 && planes == 2 ? tile_rows(rows, 2 * c.d_ffn / 16) : 0;
+        if (trt) snprintf(buf, (size_t)buf_len, "gemm_tile: row groups of %d in one launch, %d n-tiles per workgroup", trt * 16, TILE_NT);
+        else snprintf(buf, (size_t)buf_len, "gemm_rows8: row groups of %d in one launch, 8 or 7 n-tiles per workgroup, %d K-slice(s)",
                  row_tiles(planes, rows) * 16, p ? rows_split(p->split, N / 16, K / kstep, rows, planes) : 1);
         return SJ_OK;
     }
@@ -1130,12 +1133,36 @@ static int tune_plans(sj_kv* kv, int rows) {
     return rc;
 }
 
+// The gate / up projection of many rows on large tiles; rt = row tiles of a row group (tile_rows).
+template <typename T, int SPL>
+static int gemm_tile(hipStream_t st, const void* Wt, const void* X, size_t xplane, int K, int N, int rows, int rt, void* act, size_t actplane) {
+    GemmArgs a{};
+    a.Wt = Wt; a.X = X; a.xplane = xplane; a.actplane = actplane;
+    a.K = K; a.N = N; a.R = rows;
+    a.act = act;
+    a.rgroups = (rows + rt * 16 - 1) / (rt * 16);
+    const int ngroups = (N / 16 + TILE_NT - 1) / TILE_NT;
+    const int grid = std::min(TILE_WGS, (ngroups + 7) / 8 * 8 * a.rgroups);        // whole rounds of the 8 XCDs
+    switch (rt) {
+        case 10: gemm_tile_kernel<T, SPL, 10, 4><<<grid, TILE_WAVES * 64, 0, st>>>(a); break;
+        case 12: gemm_tile_kernel<T, SPL, 12, 3><<<grid, TILE_WAVES * 64, 0, st>>>(a); break;
+        case 14: gemm_tile_kernel<T, SPL, 14, 3><<<grid, TILE_WAVES * 64, 0, st>>>(a); break;
+        case 16: gemm_tile_kernel<T, SPL, 16, 3><<<grid, TILE_WAVES * 64, 0, st>>>(a); break;
+        default: return fail(SJ_EINVAL, "internal: no large-tile kernel for %d row tiles", rt);
+    }
+    LAUNCHCHK("gemm_tile");
+    return SJ_OK;
+}
+
 // More rows: all row groups in one launch of the loader-wave kernel, the workgroups of an n-tile group side by side on one XCD, so that the
 // weights are fetched from HBM once for all rows.  The statistics of EPI_LOGITS are per workgroup (of 8 n-tiles).
 template <typename T, int SPL> constexpr int rows_planes = std::is_same<T, float>::value ? 0 : SPL;   // as row_tiles and rows_split count them
 template <typename T, int EPI, int SPL>
 static int gemm_rows(hipStream_t st, const void* Wt, const void* X, size_t xplane, int K, int N, int rows, int split,
                      float* out, void* act, size_t actplane, float4* stats, float inv_temp) {
+    if constexpr (EPI == EPI_SWIGLU && SPL == 2 && std::is_same<T, bf16_t>::value) {
+        if (const int trt = tile_rows(rows, N / 16)) return gemm_tile<T, SPL>(st, Wt, X, xplane, K, N, rows, trt, act, actplane);
+    }
     const int ntiles = N / 16, rt = row_tiles(rows_planes<T, SPL>, rows), rgroups = (rows + rt * 16 - 1) / (rt * 16);
     const int mt = (std::min(rows, rt * 16) + 15) / 16;
     GemmArgs a{};

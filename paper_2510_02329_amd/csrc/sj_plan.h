@@ -187,6 +187,21 @@ inline size_t part_elems(int rule, int N, int ksteps, int rows) {
     return most;
 }
 
+// Row tiles of a row group of the large-tile gate / up kernel (gemm_tile_kernel: bf16, two planes, 16 n-tiles a workgroup), 0: not taken.
+// One workgroup to a CU, so its tiles have to come in nearly whole rounds of 256.  us of that kernel / of the loader-wave kernel:
+//   8B shape (4096 -> 2 x 14336), rows 260 / 320 / 380 / 440 / 509 (224 tiles): 150 / 171, 150 / 226, 179 / 228, 207 / 298, 238 / 296;
+//   220 rows (112 tiles): 165 / 138; 576 (336 tiles, a second round a third full): 307 / 343;
+//   70B (8192 -> 2 x 28672), rows 160 / 320 / 576 (224, 448, 672 tiles): 340 / 537, 590 / 759, 920 / 1044;
+//   1B (2048 -> 2 x 8192), rows 160 / 380 / 509 / 576 (64, 128, 128, 192 tiles): 63 / 37, 78 / 66, 100 / 71, 82 / 80.
+constexpr int TILE_NT = 16;
+constexpr int TILE_WGS = 256;
+inline int tile_rows(int rows, int ntiles) {
+    if (rows <= ROWS_MT * 16) return 0;
+    const int groups = (rows + 255) / 256, rt = std::max(10, ((rows + 15) / 16 + groups - 1) / groups + 1) / 2 * 2;
+    const int tiles = (ntiles + TILE_NT - 1) / TILE_NT * groups, rounds = (tiles + TILE_WGS - 1) / TILE_WGS;
+    return tiles * 100 >= rounds * TILE_WGS * (rounds > 1 ? 65 : 80) ? rt : 0;
+}
+
 // A projection that closes a sub-layer (O, down) with the residual add in its epilogue (EPI_RESID; no K-slices): one launch
 // instead of two.  Without slices a workgroup has one n-tile (two, four where that fills the chip) and reads as much operand as
 // weights, so it pays up to 8 rows, where both planes are one packed fragment: 8B shape, 6 rows: down 20.3 -> 21.0 us, O 8.5 ->

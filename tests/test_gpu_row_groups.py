@@ -24,6 +24,23 @@ pytestmark = pytest.mark.gpu
                                                       (9, 3, 1, "fp32"), (29, 4, 1, "fp32"), (32, 4, 1, "fp32"), (32, 8, 1, "fp32")])
 def test_step_over_row_groups(batch, gamma, planes, dtype):
     shape = dataclasses.replace(SMALL, name=f"groups_{batch}_{gamma}_{planes}_{dtype}", dtype=dtype, n_layers=1, batch=batch, gamma=gamma)
+    _step_matches(shape, planes, dtype)
+
+
+# The large-tile gate / up kernel, which needs some 200 tiles of 16 n-tiles x a row group: every group size at its edges (160, 192, 224,
+# 256 rows and one more), two and three groups, fewer k-steps than stages, n-tiles that end in the middle of a tile, a second round of
+# the chip, and the same rows with one plane, where the loader-wave kernel stays.
+@pytest.mark.parametrize("batch,gamma,d,ffn,planes", [(29, 4, 64, 26304, 2), (32, 4, 64, 26240, 2), (23, 6, 128, 26304, 2), (24, 7, 64, 26304, 2),
+                                                      (28, 7, 192, 26240, 2), (32, 7, 64, 26304, 2), (43, 5, 64, 13184, 2), (64, 8, 128, 10432, 2),
+                                                      (57, 8, 64, 21184, 2), (32, 7, 64, 26304, 1)])
+def test_step_on_large_tiles(batch, gamma, d, ffn, planes):
+    shape = dataclasses.replace(SMALL, name=f"tiles_{batch}_{gamma}_{d}_{ffn}", n_layers=1, batch=batch, gamma=gamma, d_model=d, d_ffn=ffn,
+                                n_q_heads=2, n_kv_heads=1, head_dim=64, vocab=512)
+    _step_matches(shape, planes, "bf16", "gemm_tile" if planes == 2 else "gemm_rows8")
+
+
+def _step_matches(shape, planes, dtype, gate_up=""):
+    batch, gamma = shape.batch, shape.gamma
     src = synth.WeightSource(shape, seed=51, norm_jitter=0.1)
     lens = [(7 * b) % 40 for b in range(batch)]
     cap = [64] * batch
@@ -31,6 +48,7 @@ def test_step_over_row_groups(batch, gamma, planes, dtype):
     try:
         if dtype == "bf16":
             sj.sj_set_operand_planes(gpu.kv, planes)
+        assert gate_up in sj.sj_kernel_class_shape(gpu.kv, 3, batch * (gamma + 1))
         cfg = helpers.oracle_config(shape)
         W = helpers.oracle_weights(src)
         caches = _fill_caches(shape, gpu, cfg, lens, seed=52, capacity=cap)

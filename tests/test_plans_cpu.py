@@ -70,3 +70,27 @@ def test_every_split_k_launch_is_an_instantiated_shape(tmp_path):
     """The consumer adds the plan's K-slices: a launch in another shape would leave some of them from an earlier product."""
     out = run_program(tmp_path, LAUNCHES)
     assert out.splitlines()[-1].startswith("0 of "), out
+
+
+TILES = shapes_array() + r"""
+int main() {
+    long bad = 0, taken = 0;
+    for (const auto& s : shapes)
+        for (int rows = 1; rows <= 4200; ++rows) {
+            const int ntiles = 2 * s[3] / 16, rt = tile_rows(rows, ntiles);
+            if (!rt) continue;
+            ++taken;
+            // an instantiated size whose groups hold all rows, none of them empty, with a k-step pair to work on
+            const int groups = (rows + rt * 16 - 1) / (rt * 16);
+            const bool known = rt == 10 || rt == 12 || rt == 14 || rt == 16;
+            if ((!known || rows <= ROWS_MT * 16 || groups * rt * 16 < rows || (groups - 1) * rt * 16 >= rows || s[0] % 64) && bad++ < 10)
+                printf("%d rows, %d tiles: %d\n", rows, ntiles, rt);
+        }
+    printf("%ld of %ld large-tile launches wrong\n", bad, taken);
+}
+"""
+
+
+def test_large_tile_launches_hold_their_rows(tmp_path):
+    out = run_program(tmp_path, TILES).splitlines()[-1]
+    assert out.startswith("0 of ") and not out.startswith("0 of 0 "), out
