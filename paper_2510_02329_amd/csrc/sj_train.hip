@@ -100,6 +100,19 @@ __device__ __forceinline__ double wave_sum(double v) {
 // the vector a slot's next pass multiplies the rows with
 __device__ __forceinline__ int pass_vector(int phase, int flip) { return phase == PH_HESS ? V_P : V_X + (phase == PH_TRIAL ? 1 - flip : flip); }
 
+// x summed over lane pairs O = 32 or 16 apart in the lanes below, y in the lanes above, by the swap of lane halves (of rows of 16
+// lanes) that gfx950 does in one instruction a word; a shuffle takes two selects a word and a trip through the LDS unit.
+template <int O>
+__device__ __forceinline__ double swap_add(double x, double y) {
+    const uint2 xu = __builtin_bit_cast(uint2, x), yu = __builtin_bit_cast(uint2, y);
+    auto swap = [](unsigned p, unsigned q) {
+        if constexpr (O == 32) return __builtin_amdgcn_permlane32_swap(p, q, false, false);
+        else return __builtin_amdgcn_permlane16_swap(p, q, false, false);
+    };
+    const auto lo = swap(xu.x, yu.x), hi = swap(xu.y, yu.y);
+    return __builtin_bit_cast(double, uint2{lo[0], hi[0]}) + __builtin_bit_cast(double, uint2{lo[1], hi[1]});
+}
+
 // Sums of Q values per lane over the wave, Q a power of two: every step halves the number of values a lane keeps and adds
 // the other half's from the lane across, so Q sums cost Q - 1 + log2(64 / Q) exchanges instead of 6 Q.  The sum of value q
 // ends in the lanes with lane / (64 / Q) == q.
@@ -110,8 +123,11 @@ __device__ __forceinline__ void halve_sums(double (&v)[Q], int lane) {
         const bool up = lane & o;
 #pragma unroll
         for (int q = 0; q < M; ++q) {
-            const double send = up ? v[q] : v[q + M], keep = up ? v[q + M] : v[q];
-            v[q] = keep + __shfl_xor(send, o, 64);
+            if constexpr (o >= 16) v[q] = swap_add<o>(v[q], v[q + M]);
+            else {
+                const double send = up ? v[q] : v[q + M], keep = up ? v[q + M] : v[q];
+                v[q] = keep + __shfl_xor(send, o, 64);
+            }
         }
         halve_sums<M / 2, Q>(v, lane);
     }
@@ -145,6 +161,9 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
 // 79 us a pass = 20 us a problem, + 9 us for the sum of the partials and 8 us for the slots' updates; with one problem at a
 // time a pass took 53 us, its vector kernels and the host's look at the result 65 us more.  A grid of ten C: 86 ms -> 26 ms.
 // Converting a row once for dot product and update (32 registers more) measured the same.
+// The exchanges across 32 and 16 lanes as swaps (swap_add): 74 -> 71 us a pass, ten C 26.4 -> 25.4 ms.  Groups of two rows with three
+// buffers, so that the next group's dot products cover a group's exchange and barrier: 30.5 ms (the vectors are read from LDS for
+// half as many rows).
 constexpr int pass_rows(int nj) { return nj > 2 ? 2 : 4; }          // rows per group: at most 32 registers a buffer
 
 template <int NJ, int A, int CW>
