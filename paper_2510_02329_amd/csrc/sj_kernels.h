@@ -739,7 +739,9 @@ __global__ __launch_bounds__(256) void resample_w_kernel(const StepParams* __res
 }
 
 __global__ __launch_bounds__(256) void resample_pick_kernel(const StepParams* __restrict__ sp, ResampleArgs a,
-                                                            int32_t* __restrict__ len, int32_t* __restrict__ pending) {
+                                                            int32_t* __restrict__ len, int32_t* __restrict__ pending,
+                                                            const float* __restrict__ scores, const float* __restrict__ p_at_d,
+                                                            const int32_t* __restrict__ bits) {
     __shared__ double wave_tot[4];
     __shared__ double slab_w[256];
     __shared__ int hit_slab, last_slab;
@@ -750,6 +752,12 @@ __global__ __launch_bounds__(256) void resample_pick_kernel(const StepParams* __
     const int n = a.nacc[bi];
     const int row = bi * (gamma + 1) + n;
     const float4 st = a.rowstat[row];
+    if (sp->mirror && tid < gamma) {                 // gamma <= 63; written through, done when the launch is
+        const int k = bi * gamma + tid;
+        sp->mirror[k] = scores[k];
+        sp->mirror[sp->mirror_stride + k] = p_at_d[k];
+        sp->mirror[2 * sp->mirror_stride + k] = __int_as_float(bits[k]);
+    }
     int next = -1;
     if (!(a.inv_temp > 0.f)) {
         next = __float_as_int(st.z);                 // one-hot target: residual and bonus are the arg-max

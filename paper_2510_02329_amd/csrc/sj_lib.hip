@@ -10,6 +10,7 @@
 #include "sj_gemm_ring.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -128,6 +129,19 @@ struct sj_kv : Forward {       // the inherited buffers serve the blocks of up t
     std::vector<hipEvent_t> tev;          // start/stop pairs
     size_t tev_used = 0;
     int last_gamma = 0, last_rows = 0;
+    // the stream that the work since the last wait for the whole device went to (NONE: there was none, MIXED: several)
+    enum { NONE, ONE, MIXED } work = NONE;
+    hipStream_t work_stream = nullptr;
+    void note(hipStream_t st) {
+        if (work == NONE) { work = ONE; work_stream = st; }
+        else if (work == ONE && work_stream != st) work = MIXED;
+    }
+    bool follows(hipStream_t st) const { return work == NONE || (work == ONE && work_stream == st); }
+    // judge scores, p(draft) and accept bits of the last call, max_rows words each, in host memory that the device writes: there from
+    // the first sj_debug_fetch of one of them on
+    mutable std::atomic<float*> mirror{nullptr};
+    mutable std::mutex mirror_mu;
+    bool mirrored = false;                // the last call wrote it
     std::vector<void*> allocs;
 };
 
@@ -506,10 +520,41 @@ extern "C" int sj_kv_create(const sj_model* m, int32_t batch, const int32_t* cap
     return SJ_OK;
 }
 
+// Host memory for the mirrors of cache objects.  Taking and returning pinned memory costs a program that makes a cache object per batch
+// 80 us, so up to eight blocks of one size (1365 rows) wait for the next object; larger ones go back at once.
+constexpr size_t MIRROR_BYTES = 16384, MIRROR_POOL = 8;
+static std::mutex mirror_pool_mu;
+static std::vector<float*> mirror_pool;
+static float* mirror_take(int rows) {
+    const size_t bytes = (size_t)3 * rows * 4;
+    if (bytes <= MIRROR_BYTES) {
+        std::lock_guard<std::mutex> lock(mirror_pool_mu);
+        if (!mirror_pool.empty()) {
+            float* h = mirror_pool.back();
+            mirror_pool.pop_back();
+            return h;
+        }
+    }
+    void* h = nullptr;
+    if (hipHostMalloc(&h, std::max(bytes, MIRROR_BYTES), hipHostMallocPortable) == hipSuccess) return (float*)h;
+    (void)hipGetLastError();
+    return nullptr;
+}
+// (the device has been waited for)
+static void mirror_give(float* h, int rows) {
+    if (!h) return;
+    if ((size_t)3 * rows * 4 <= MIRROR_BYTES) {
+        std::lock_guard<std::mutex> lock(mirror_pool_mu);
+        if (mirror_pool.size() < MIRROR_POOL) { mirror_pool.push_back(h); return; }
+    }
+    (void)hipHostFree(h);
+}
+
 extern "C" int sj_kv_free(sj_kv* kv) {
     if (!kv) return fail(SJ_EINVAL, "kv is null");
     (void)hipDeviceSynchronize();
     if (kv->pinned_state) (void)hipHostFree(kv->pinned_state);
+    mirror_give(kv->mirror, kv->max_rows);
     if (kv->rewind_done) (void)hipEventDestroy(kv->rewind_done);
     for (hipEvent_t e : kv->tev) (void)hipEventDestroy(e);
     for (auto& g : kv->graphs) (void)hipGraphExecDestroy(g.second);
@@ -545,6 +590,7 @@ extern "C" int sj_kv_rewind(sj_kv* kv, const int32_t* len_host, const int32_t* p
         for (int b = 0; b < kv->batch; ++b) { a.len[b] = len_host[b]; a.pending[b] = pending_host[b]; }
         rewind_kernel<<<1, REWIND_SEQS, 0, st>>>(a, kv->batch, kv->len_dev, kv->pending_dev);
         LAUNCHCHK("rewind");
+        kv->note(st);
         for (int b = 0; b < kv->batch; ++b) kv->len_upper[b] = len_host[b];
         return SJ_OK;
     }
@@ -557,6 +603,7 @@ extern "C" int sj_kv_rewind(sj_kv* kv, const int32_t* len_host, const int32_t* p
     std::memcpy(kv->pinned_state + kv->batch, pending_host, sizeof(int32_t) * kv->batch);
     HIPCHK(hipMemcpyAsync(kv->len_dev, kv->pinned_state, sizeof(int32_t) * 2 * kv->batch, hipMemcpyHostToDevice, st));
     HIPCHK(hipEventRecord(kv->rewind_done, st));
+    kv->note(st);
     kv->rewind_pending = true;
     for (int b = 0; b < kv->batch; ++b) kv->len_upper[b] = len_host[b];
     return SJ_OK;
@@ -749,7 +796,23 @@ extern "C" int sj_kv_read(const sj_kv* kv, int32_t seq, int32_t layer, int32_t p
 
 static int refresh_lengths(sj_kv* kv) {
     HIPCHK(hipDeviceSynchronize());
+    kv->work = sj_kv::NONE;
     HIPCHK(hipMemcpy(kv->len_upper.data(), kv->len_dev, sizeof(int32_t) * kv->batch, hipMemcpyDeviceToHost));
+    return SJ_OK;
+}
+
+// May sequences lo .. hi - 1 take `rows` more positions in a call on `st`?  The host keeps an upper bound of every length: the device is asked
+// only when the bound trips, or when earlier work on the object went to another stream (such a call has always waited for it).
+// Asking each time - a wait, a copy, and an idle device until the next launches - cost draft blocks, scoring and prompts 50 - 60 us.
+static int check_room(sj_kv* kv, hipStream_t st, int lo, int hi, int rows) {
+    bool room = kv->follows(st);
+    for (int b = lo; b < hi; ++b) room = room && kv->len_upper[b] + rows <= kv->cap[b];
+    if (room) return SJ_OK;
+    const int rc = refresh_lengths(kv);
+    if (rc) return rc;
+    for (int b = lo; b < hi; ++b)
+        if (kv->len_upper[b] + rows > kv->cap[b])
+            return fail(SJ_ECAPACITY, "sequence %d: len %d + %d rows exceeds capacity %d", b, kv->len_upper[b], rows, kv->cap[b]);
     return SJ_OK;
 }
 
@@ -1450,7 +1513,7 @@ struct Runner {
             draft_onehot_kernel<<<dim3(std::min(64, (md.V + 255) / 256), nseq), 256, 0, st>>>(kv->sp_dev, md.V, kv->rowstat);
             LAUNCHCHK("draft_onehot");
         }
-        resample_pick_kernel<<<nseq, 256, 0, st>>>(kv->sp_dev, ra, kv->len_dev, kv->pending_dev);
+        resample_pick_kernel<<<nseq, 256, 0, st>>>(kv->sp_dev, ra, kv->len_dev, kv->pending_dev, kv->scores, kv->p_at_d, kv->bits);
         LAUNCHCHK("resample_pick");
         return SJ_OK;
     }
@@ -1584,6 +1647,14 @@ static int check_step_args(sj_model* m, sj_kv* kv, int gamma, const void* a, con
     return SJ_OK;
 }
 
+// A verification call is about to go to `st`: its draw's last kernel also leaves the small per-draft results in host memory where
+// they have been asked for.
+static void set_mirror(sj_kv* kv, hipStream_t st, StepParams& p) {
+    kv->note(st);
+    p.mirror = kv->mirror;
+    p.mirror_stride = kv->max_rows;
+}
+
 extern "C" int sj_verify_step(sj_model* m, sj_kv* kv, int32_t gamma, const int32_t* draft_tokens, const float* draft_probs,
                               const float* uniforms, float judge_threshold, int32_t* accepted_len, int32_t* next_token,
                               void* stream) {
@@ -1606,9 +1677,11 @@ extern "C" int sj_verify_step(sj_model* m, sj_kv* kv, int32_t gamma, const int32
     p.draft_tokens = draft_tokens; p.draft_probs = draft_probs; p.uniforms = uniforms;
     p.accepted_len = accepted_len; p.next_token = next_token;
     hipStream_t st = (hipStream_t)stream;
+    set_mirror(kv, st, p);
     rc = dispatch_step(m, kv, gamma, p, st, false, nullptr);
     if (rc) return rc;
     for (int b = 0; b < kv->batch; ++b) kv->len_upper[b] += gamma + 1;
+    kv->mirrored = p.mirror != nullptr;
     kv->last_gamma = gamma;
     kv->last_rows = kv->batch * (gamma + 1);
     return SJ_OK;
@@ -1643,12 +1716,10 @@ extern "C" int sj_draft_block(sj_model* m, sj_kv* kv, int32_t gamma, const float
     if (!uniforms || !draft_tokens || !draft_probs) return fail(SJ_EINVAL, "null device pointer argument");
     if (m->cfg.n_layers == 0) return fail(SJ_EINVAL, "head-only model has no decode loop");
     const int need = gamma + (feed_last ? 1 : 0);
-    int rc = refresh_lengths(kv);
-    if (rc) return rc;
-    for (int b = 0; b < kv->batch; ++b)
-        if (kv->len_upper[b] + need > kv->cap[b])
-            return fail(SJ_ECAPACITY, "sequence %d: len %d + %d rows exceeds capacity %d", b, kv->len_upper[b], need, kv->cap[b]);
     hipStream_t st = (hipStream_t)stream;
+    int rc = check_room(kv, st, 0, kv->batch, need);
+    if (rc) return rc;
+    kv->note(st);
     StepParams p{};
     p.nseq = kv->batch; p.seq_base = 0; p.rps = 1; p.gamma = 0; p.tok_mode = 0; p.mode = kv->mode; p.topk = kv->topk;
     p.theta = 0.5f;
@@ -1689,12 +1760,10 @@ extern "C" int sj_score_block(sj_model* m, sj_kv* kv, int32_t n, const int32_t* 
     if (n < 1 || n > m->cfg.max_gamma + 1) return fail(SJ_EINVAL, "n %d outside 1..max_gamma + 1 = %d", n, m->cfg.max_gamma + 1);
     if (!input_tokens || !target_tokens || !logprob) return fail(SJ_EINVAL, "null device pointer argument");
     if (hidden_out && (hidden_row < 0 || hidden_row >= n)) return fail(SJ_EINVAL, "hidden_row %d outside the block", hidden_row);
-    int rc = refresh_lengths(kv);
-    if (rc) return rc;
-    for (int b = 0; b < kv->batch; ++b)
-        if (kv->len_upper[b] + n > kv->cap[b])
-            return fail(SJ_ECAPACITY, "sequence %d: len %d + %d rows exceeds capacity %d", b, kv->len_upper[b], n, kv->cap[b]);
     hipStream_t st = (hipStream_t)stream;
+    int rc = check_room(kv, st, 0, kv->batch, n);
+    if (rc) return rc;
+    kv->note(st);
     StepParams p{};
     p.nseq = kv->batch; p.seq_base = 0; p.rps = n; p.gamma = n - 1; p.tok_mode = 2; p.mode = kv->mode; p.topk = kv->topk;
     p.draft_tokens = input_tokens;
@@ -1723,8 +1792,10 @@ extern "C" int sj_verify_head(sj_model* m, sj_kv* kv, int32_t gamma, const void*
     p.accepted_len = accepted_len; p.next_token = next_token;
     p.step = 0;
     hipStream_t st = (hipStream_t)stream;
+    set_mirror(kv, st, p);
     rc = dispatch_step(m, kv, gamma, p, st, true, hidden);
     if (rc) return rc;
+    kv->mirrored = p.mirror != nullptr;
     kv->last_gamma = gamma;
     kv->last_rows = kv->batch * (gamma + 1);
     return SJ_OK;
@@ -1883,10 +1954,10 @@ extern "C" int sj_prefill(sj_model* m, sj_kv* kv, int32_t seq, const int32_t* to
     if (n < 1) return fail(SJ_EINVAL, "n must be positive");
     for (int i = 0; i < n; ++i)
         if (tokens_host[i] < 0 || tokens_host[i] >= m->cfg.vocab) return fail(SJ_EINVAL, "token %d out of range", i);
-    int rc = refresh_lengths(kv);
-    if (rc) return rc;
-    if (kv->len_upper[seq] + n > kv->cap[seq]) return fail(SJ_ECAPACITY, "prefill of %d tokens exceeds capacity", n);
     hipStream_t st = (hipStream_t)stream;
+    int rc = check_room(kv, st, seq, seq + 1, n);
+    if (rc) return rc;
+    kv->note(st);
     if (m->cfg.dtype == SJ_DTYPE_FP32) rc = prefill_impl<float, 1>(m, kv, seq, tokens_host, n, st);
     else if (kv->planes == 1) rc = prefill_impl<bf16_t, 1>(m, kv, seq, tokens_host, n, st);
     else if (kv->planes == 3) rc = prefill_impl<bf16_t, 3>(m, kv, seq, tokens_host, n, st);
@@ -1914,6 +1985,25 @@ extern "C" int sj_debug_fetch(const sj_kv* kv, int32_t what, void* dst_host, siz
     }
     if (want == 0) return fail(SJ_EINVAL, "item not produced by the last call");
     if (nbytes != want) return fail(SJ_EINVAL, "nbytes %zu != expected %zu", nbytes, want);
+    // Per-draft results (a few words a sequence) are in host memory once the device is done, from the call after the first fetch on:
+    // a wait alone takes 11 us, a wait and a copy of 40 bytes 26.
+    const int slot = what == SJ_DBG_JUDGE_SCORES ? 0 : what == SJ_DBG_P_AT_DRAFT ? 1 : what == SJ_DBG_ACCEPT_BITS ? 2 : -1;
+    if (slot >= 0 && kv->mirrored) {
+        HIPCHK(hipDeviceSynchronize());
+        std::memcpy(dst_host, kv->mirror + (size_t)slot * kv->max_rows, want);
+        return SJ_OK;
+    }
+    if (slot >= 0) {
+        std::lock_guard<std::mutex> lock(kv->mirror_mu);
+        if (!kv->mirror) kv->mirror = mirror_take(kv->max_rows);       // null: fetched by copies
+    }
+    // Where all of the object's work is on the default stream, the copy is queued behind it and waited for once (96 KB: 23 us, with a
+    // wait in front of the copy 58).
+    if (kv->work == sj_kv::ONE && !kv->work_stream) {
+        HIPCHK(hipMemcpyAsync(dst_host, src, want, hipMemcpyDeviceToHost, nullptr));
+        HIPCHK(hipStreamSynchronize(nullptr));
+        return SJ_OK;
+    }
     HIPCHK(hipDeviceSynchronize());
     HIPCHK(hipMemcpy(dst_host, src, want, hipMemcpyDeviceToHost));
     return SJ_OK;

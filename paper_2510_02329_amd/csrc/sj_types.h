@@ -27,6 +27,8 @@ struct StepParams {
     int32_t emit_gamma;            // draft block: columns of emit_tokens / emit_probs
     int32_t* emit_tokens;          // draft block: [nseq, emit_gamma], column `step`
     float* emit_probs;             // draft block: [nseq, emit_gamma, V]
+    float* mirror;                 // null, or host memory for the judge scores, p(draft) and accept bits, mirror_stride words each
+    int32_t mirror_stride;
 };
 
 struct ModelDims {

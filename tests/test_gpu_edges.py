@@ -282,3 +282,75 @@ def test_lds_ring_projections(gamma, planes, monkeypatch):
     abs_tol, rel_tol = (5e-3, 1e-2) if planes == 2 else (5e-2, 5e-2)
     print(f"ring vs register-ring kernel, {planes} plane(s), {gamma + 1} rows: max |diff| {float(diff.max()):.3e}")
     assert (diff <= abs_tol + rel_tol * np.abs(logits[0])).all(), float(diff.max())
+
+
+def test_results_are_the_same_by_copy_and_mirror_on_every_stream():
+    """The first fetch of per-draft results copies them, later ones read host memory that the call wrote; calls that move between
+    streams without a wait still see each other's lengths."""
+    shape = BASE.scaled(batch=3, gamma=4)
+    lens = [37, 64, 5]
+    gpu, cfg, W, caches = _setup(shape, lens)
+    side = [torch.cuda.Stream(), torch.cuda.Stream()]
+    try:
+        pending = sj.sj_kv_state(gpu.kv, 3)[1].tolist()
+        for gamma in (4, 2):
+            draft = synth.make_draft(shape.scaled(gamma=gamma), seed=31)
+            outs = []
+            for st in (torch.cuda.default_stream(), torch.cuda.default_stream(), side[0], side[1], torch.cuda.default_stream()):
+                with torch.cuda.stream(st):
+                    sj.sj_kv_rewind(gpu.kv, lens, pending, st)
+                    outs.append(gpu.step(draft, 0.5, gamma))
+            for o in outs[1:]:
+                for k in outs[0]:
+                    assert np.array_equal(outs[0][k], o[k]), (gamma, k)
+        # a draft block and a scoring pass behind a rewind that is still queued on another stream
+        u = torch.rand(3, 3, device="cuda")
+        tok = torch.zeros(3, 4, dtype=torch.int32, device="cuda")
+        torch.cuda.synchronize()
+
+        def run(st_rewind, st):
+            t, q = torch.zeros(3, 3, dtype=torch.int32, device="cuda"), torch.zeros(3, 3, shape.vocab, device="cuda")
+            lp = torch.zeros(3, 4, device="cuda")
+            torch.cuda.synchronize()
+            sj.sj_kv_rewind(gpu.kv, [20, 30, 2], pending, st_rewind)
+            sj.sj_score_block(gpu.model, gpu.kv, 4, tok, tok, lp, 0, None, st)
+            sj.sj_kv_rewind(gpu.kv, [22, 31, 4], pending, st_rewind)
+            sj.sj_draft_block(gpu.model, gpu.kv, 3, u, True, t, q, st)
+            torch.cuda.synchronize()
+            with pytest.raises(sj.SJError):              # not produced by the last call
+                sj.sj_debug_fetch(gpu.kv, sj.SJ_DBG_P_AT_DRAFT, np.empty((3, 2), np.float32))
+            return [x.cpu() for x in (lp, t, q)] + [torch.from_numpy(sj.sj_kv_state(gpu.kv, 3)[0].copy())]
+
+        ref = run(torch.cuda.default_stream(), torch.cuda.default_stream())
+        for pair in ((side[0], side[0]), (torch.cuda.default_stream(), side[1])):
+            for a, b in zip(ref, run(*pair)):
+                assert torch.equal(a, b)
+    finally:
+        gpu.close()
+
+
+def test_room_is_checked_against_true_lengths():
+    """The host's bound of the lengths grows by gamma + 1 a step: a call that the bound refuses is taken when the true length has room,
+    and refused when it has not."""
+    shape = BASE.scaled(batch=1, gamma=4)
+    gpu, cfg, W, caches = _setup(shape, [8], cap=[64])
+    try:
+        draft = synth.make_draft(shape, seed=33)
+        while sj.sj_kv_state(gpu.kv, 1)[0][0] + 5 <= 64:
+            gpu.step(draft, 2.0)                           # the judge never accepts: short steps
+        left = 64 - int(sj.sj_kv_state(gpu.kv, 1)[0][0])
+        assert 1 <= left <= 4
+        ids = torch.zeros(1, 5, dtype=torch.int32, device="cuda")
+        lp = torch.zeros(1, 5, device="cuda")
+        sj.sj_score_block(gpu.model, gpu.kv, left, ids, ids, lp, 0, None, torch.cuda.current_stream())
+        with pytest.raises(sj.SJError):
+            sj.sj_score_block(gpu.model, gpu.kv, left + 1, ids, ids, lp, 0, None, torch.cuda.current_stream())
+        with pytest.raises(sj.SJError):
+            sj.sj_prefill(gpu.model, gpu.kv, 0, [1] * (left + 1))
+        u, q = torch.rand(left + 1, 1, device="cuda"), torch.zeros(1, left + 1, shape.vocab, device="cuda")
+        with pytest.raises(sj.SJError):
+            sj.sj_draft_block(gpu.model, gpu.kv, left + 1, u, False, ids, q, torch.cuda.current_stream())
+        sj.sj_draft_block(gpu.model, gpu.kv, left, u, False, ids, q, torch.cuda.current_stream())
+        assert sj.sj_kv_state(gpu.kv, 1)[0][0] == 64
+    finally:
+        gpu.close()
