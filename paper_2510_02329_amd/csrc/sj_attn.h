@@ -68,7 +68,7 @@ struct AttnSmem {
 template <int HD, int MQ> constexpr int attn_partial_floats() { return (HD / 16 * MQ * 4 + 2 * MQ) * 64; }
 
 template <typename T, int HD, int MQ, int SPL, int PB = 4>
-__global__ __launch_bounds__(256) void attn_fused_kernel(const StepParams* __restrict__ sp, ModelDims md,
+__global__ __launch_bounds__(256) void attn_fused_kernel(int seq_base, int rps, ModelDims md,
                                                          const float* __restrict__ part, int nparts, int R,
                                                          const float* __restrict__ cs, KvView<T> kv, int layer,
                                                          int wave_keys, int nchunk_max, float* __restrict__ opart,
@@ -88,8 +88,7 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(const StepParams* __res
 
     const int chunk = blockIdx.x, kvh = blockIdx.y % md.Hkv, qg = blockIdx.y / md.Hkv, bi = blockIdx.z;
     const int qgroups = gridDim.y / md.Hkv;
-    const int b = sp->seq_base + bi;
-    const int rps = sp->rps;
+    const int b = seq_base + bi;
     const int M = md.G * rps;
     const int L = kv.len[b], cap = kv.cap[b];
     const int wg_keys = 4 * wave_keys;
@@ -119,7 +118,7 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(const StepParams* __res
     load_keys(0, min(key_lo, cap - KSTEP));            // capacities are multiples of 64: always inside
 
     // query fragment group gq = (q tile mq, head-dim step kk): 4 split-K partials per batch of loads
-    float4 qa[PB][KF / 4], qc[PB][KF / 4];
+    float4 qa[PB][KF / 4], qc[PB][KF / 4], qcs[KF / 2];
     auto q_row = [&](int gq, int& row, int& head, bool& valid) {
         const int mq = gq / (KK / 2);
         const int m = (qg * MQ + mq) * 16 + r;
@@ -133,6 +132,9 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(const StepParams* __res
         q_row(gq, row, head, valid);
         const int i0 = (gq % (KK / 2)) * KSTEP + g * KF;
         const int off0 = row * N + head * HD + i0;     // the partials hold fewer than 2^31 elements
+        if (s0 == 0)
+#pragma unroll
+            for (int e = 0; e < KF / 2; ++e) qcs[e] = *reinterpret_cast<const float4*>(cs + (row * HALF + i0) * 2 + 4 * e);
 #pragma unroll
         for (int u = 0; u < PB; ++u) {
             const float* pl = part + (off0 + min(s0 + u, nparts - 1) * R * N);
@@ -173,7 +175,14 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(const StepParams* __res
             ncs[u][1] = cs[(row * HALF + i) * 2 + 1];
         }
     };
-    nr_issue(0, 0);
+    if (tail) {
+        nr_issue(0, 0);
+        // the rows' last key step is padded with zeros: the whole area, while the loads are on their way
+        const int rpad = (rps + KSTEP - 1) / KSTEP * KSTEP;
+        for (int e = tid; e < rpad * HD / KF; e += 256) reinterpret_cast<u32x4*>(&sm.in.knew[0][0])[e] = u32x4{0, 0, 0, 0};
+        for (int e = tid; e < HD * 64 / KF; e += 256) reinterpret_cast<u32x4*>(&sm.in.vnewT[0][0])[e] = u32x4{0, 0, 0, 0};
+        lds_barrier();
+    }
     ATTN_STAMP(1);
 
     // ---------------- query fragments: rotate this wave's groups, exchange through LDS ----------------
@@ -193,14 +202,11 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(const StepParams* __res
                 }
             }
         }
-        int row, head; bool valid;
-        q_row(gq, row, head, valid);
-        const int mq = gq / (KK / 2), kk = gq % (KK / 2), i0 = kk * KSTEP + g * KF;
-        const float* csr = cs + (row * HALF + i0) * 2;
+        const int mq = gq / (KK / 2), kk = gq % (KK / 2);
         Frag f0[SPL], f1[SPL];
 #pragma unroll
         for (int e = 0; e < KF; ++e) {
-            const float c = csr[2 * e], s = csr[2 * e + 1];
+            const float c = e & 1 ? qcs[e / 2].z : qcs[e / 2].x, s = e & 1 ? qcs[e / 2].w : qcs[e / 2].y;
             Traits<T>::template pack_split<SPL>(f0, e, lo[e] * c - hi[e] * s);
             Traits<T>::template pack_split<SPL>(f1, e, hi[e] * c + lo[e] * s);
         }
@@ -215,7 +221,6 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(const StepParams* __res
     // ---------------- the block's own K / V rows (tail workgroup): LDS, and the cache if q group 0 ----
     if (tail) {
         const bool writer = (qg == 0);
-        const int rpad = (rps + KSTEP - 1) / KSTEP * KSTEP;
         for (int base = 0; base < nr_total; base += NB * 256) {
             float lo[NB], hi[NB];
 #pragma unroll
@@ -240,28 +245,26 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(const StepParams* __res
                     const float c = isv ? 1.f : ncs[u][0], s = isv ? 0.f : ncs[u][1];
                     const float olo = lo[u] * c - hi[u] * s, ohi = hi[u] * c + lo[u] * s;
                     const bool in_cap = writer && L + j < cap;
+                    T tlo, thi;
+                    Traits<T>::store(&tlo, olo);
+                    Traits<T>::store(&thi, ohi);
                     if (!isv) {
-                        Traits<T>::store(&sm.in.knew[j][i], olo);
-                        Traits<T>::store(&sm.in.knew[j][i + HALF], ohi);
+                        sm.in.knew[j][i] = tlo;
+                        sm.in.knew[j][i + HALF] = thi;
                         if (in_cap) {
-                            Kb[kv_k_off<T>(L + j, i, HD)] = sm.in.knew[j][i];
-                            Kb[kv_k_off<T>(L + j, i + HALF, HD)] = sm.in.knew[j][i + HALF];
+                            Kb[kv_k_off<T>(L + j, i, HD)] = tlo;
+                            Kb[kv_k_off<T>(L + j, i + HALF, HD)] = thi;
                         }
                     } else {
-                        Traits<T>::store(&sm.in.vnewT[i][j], olo);
-                        Traits<T>::store(&sm.in.vnewT[i + HALF][j], ohi);
+                        sm.in.vnewT[i][j] = tlo;
+                        sm.in.vnewT[i + HALF][j] = thi;
                         if (in_cap) {
-                            Vb[kv_v_off<T>(L + j, i, HD)] = sm.in.vnewT[i][j];
-                            Vb[kv_v_off<T>(L + j, i + HALF, HD)] = sm.in.vnewT[i + HALF][j];
+                            Vb[kv_v_off<T>(L + j, i, HD)] = tlo;
+                            Vb[kv_v_off<T>(L + j, i + HALF, HD)] = thi;
                         }
                     }
                 }
             }
-        }
-        for (int e = tid; e < (rpad - rps) * HD; e += 256) {     // padding rows of the last key step
-            const int j = rps + e / HD, dcol = e % HD;
-            Traits<T>::store(&sm.in.knew[j][dcol], 0.f);
-            Traits<T>::store(&sm.in.vnewT[dcol][j], 0.f);
         }
     }
     __syncthreads();
@@ -485,7 +488,6 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(const StepParams* __res
 
     // ranges in order, CB per batch of independent loads, running maximum carried across batches
     const float* base = opart + group * nchunk_max * PF;
-    constexpr int CB = (MQ <= 2) ? 8 : (MQ == 3 ? 4 : 2);
     float mx[MQ], den[MQ], num[HPW][MQ][4];
 #pragma unroll
     for (int mq = 0; mq < MQ; ++mq) {
@@ -496,45 +498,51 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(const StepParams* __res
 #pragma unroll
             for (int i = 0; i < 4; ++i) num[hh][mq][i] = 0.f;
     }
-    for (int c0 = 0; c0 < nch; c0 += CB) {
-        float mv[CB][MQ], lv[CB][MQ], ov[CB][HPW][MQ][4];
-#pragma unroll
-        for (int u = 0; u < CB; ++u) {
-            const float* pc = base + (size_t)min(c0 + u, nch - 1) * PF;
-#pragma unroll
-            for (int mq = 0; mq < MQ; ++mq) {
-                mv[u][mq] = ld_coh(pc + (NSLOT + mq) * 64 + lane);
-                lv[u][mq] = ld_coh(pc + (NSLOT + MQ + mq) * 64 + lane);
-#pragma unroll
-                for (int hh = 0; hh < HPW; ++hh)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) ov[u][hh][mq][i] = ld_coh(pc + (((wave + 4 * hh) * MQ + mq) * 4 + i) * 64 + lane);
-            }
-        }
-        if (c0 == 0) ATTN_STAMP(10);
-#pragma unroll
-        for (int mq = 0; mq < MQ; ++mq) {
-            float bm = mx[mq];
-#pragma unroll
-            for (int u = 0; u < CB; ++u) bm = fmaxf(bm, (c0 + u < nch) ? mv[u][mq] : -INFINITY);
-            const float resc = (mx[mq] == -INFINITY) ? 0.f : __expf(mx[mq] - bm);
-            mx[mq] = bm;
-            den[mq] *= resc;
-#pragma unroll
-            for (int hh = 0; hh < HPW; ++hh)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) num[hh][mq][i] *= resc;
+    auto merge = [&](auto cb_tag) {
+        constexpr int CB = decltype(cb_tag)::value;
+        for (int c0 = 0; c0 < nch; c0 += CB) {
+            float mv[CB][MQ], lv[CB][MQ], ov[CB][HPW][MQ][4];
 #pragma unroll
             for (int u = 0; u < CB; ++u) {
-                const float f = (c0 + u < nch && mv[u][mq] != -INFINITY) ? __expf(mv[u][mq] - bm) : 0.f;
-                den[mq] += f * lv[u][mq];
+                const float* pc = base + (size_t)min(c0 + u, nch - 1) * PF;
+#pragma unroll
+                for (int mq = 0; mq < MQ; ++mq) {
+                    mv[u][mq] = ld_coh(pc + (NSLOT + mq) * 64 + lane);
+                    lv[u][mq] = ld_coh(pc + (NSLOT + MQ + mq) * 64 + lane);
+#pragma unroll
+                    for (int hh = 0; hh < HPW; ++hh)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) ov[u][hh][mq][i] = ld_coh(pc + (((wave + 4 * hh) * MQ + mq) * 4 + i) * 64 + lane);
+                }
+            }
+            if (c0 == 0) ATTN_STAMP(10);
+#pragma unroll
+            for (int mq = 0; mq < MQ; ++mq) {
+                float bm = mx[mq];
+#pragma unroll
+                for (int u = 0; u < CB; ++u) bm = fmaxf(bm, (c0 + u < nch) ? mv[u][mq] : -INFINITY);
+                const float resc = (mx[mq] == -INFINITY) ? 0.f : __expf(mx[mq] - bm);
+                mx[mq] = bm;
+                den[mq] *= resc;
 #pragma unroll
                 for (int hh = 0; hh < HPW; ++hh)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) num[hh][mq][i] += f * ov[u][hh][mq][i];
+                    for (int i = 0; i < 4; ++i) num[hh][mq][i] *= resc;
+#pragma unroll
+                for (int u = 0; u < CB; ++u) {
+                    const float f = (c0 + u < nch && mv[u][mq] != -INFINITY) ? __expf(mv[u][mq] - bm) : 0.f;
+                    den[mq] += f * lv[u][mq];
+#pragma unroll
+                    for (int hh = 0; hh < HPW; ++hh)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) num[hh][mq][i] += f * ov[u][hh][mq][i];
+                }
             }
         }
-    }
+    };
+    // nine to twelve ranges in one round trip as well (1B-shaped decode over 1029 keys: 0.5 us of 9)
+    if (MQ == 1 && nch > 8) merge(std::integral_constant<int, 12>{});   // uniform
+    else merge(std::integral_constant<int, (MQ <= 2 ? 8 : MQ == 3 ? 4 : 2)>{});
     ATTN_STAMP(11);
 #pragma unroll
     for (int hh = 0; hh < HPW; ++hh)

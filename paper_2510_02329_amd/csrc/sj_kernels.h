@@ -178,6 +178,7 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(int R, int d, float e
     const int r = blockIdx.x;
     float* xr = x + (size_t)r * d;
     f32x4 v[MAXP];
+    T gn[MAXP][4];                                     // the gain, on its way while the row is summed (asked for after the barrier: 0.6 us more)
     float ss = 0.f;
 #pragma unroll
     for (int p = 0; p < MAXP; ++p) {
@@ -185,6 +186,8 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(int R, int d, float e
         v[p] = f32x4{0.f, 0.f, 0.f, 0.f};
         if (c < d) {
             v[p] = *reinterpret_cast<const f32x4*>(xr + c);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) gn[p][i] = gain[c + i];
             // partials in batches of PB independent loads (index clamped, surplus ignored), added in order
             for (int s0 = 0; s0 < nparts; s0 += PB) {
                 f32x4 t[PB];
@@ -212,7 +215,7 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(int R, int d, float e
         if (c < d) {
             float y[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) y[i] = v[p][i] * inv * Traits<T>::load(gain + c + i);
+            for (int i = 0; i < 4; ++i) y[i] = v[p][i] * inv * Traits<T>::load(&gn[p][i]);
             Traits<T>::template store_split4<SPL>(xn + opnd_off<T>(r, c, d, rm), xplane, y);
             if (xn32) *reinterpret_cast<f32x4*>(xn32 + (size_t)r * d + c) = f32x4{y[0], y[1], y[2], y[3]};
         }
@@ -707,11 +710,11 @@ __device__ __forceinline__ double total_of(const double* part, int n) {
     return wave_sum(s);
 }
 
-__global__ __launch_bounds__(256) void resample_w_kernel(const StepParams* __restrict__ sp, ResampleArgs a) {
+// pass 2: the same sums of w (nothing is drawn from them when every draft token was accepted)
+__device__ __forceinline__ void resample_w_slab(const StepParams* __restrict__ sp, const ResampleArgs& a, int n) {
     __shared__ double red[4];
     const int bi = blockIdx.y, slab = blockIdx.x * 256 + threadIdx.x, nblk = a.nslab / 256;
     const int gamma = sp->gamma;
-    const int n = a.nacc[bi];
     double s = 0.0;
     if (n < gamma) {                                   // uniform for the workgroup
         const double Z = total_of(a.eblk + (size_t)bi * nblk, nblk);
@@ -738,18 +741,20 @@ __global__ __launch_bounds__(256) void resample_w_kernel(const StepParams* __res
     if (threadIdx.x == 0) a.wblk[(size_t)bi * nblk + blockIdx.x] = s;
 }
 
-__global__ __launch_bounds__(256) void resample_pick_kernel(const StepParams* __restrict__ sp, ResampleArgs a,
-                                                            int32_t* __restrict__ len, int32_t* __restrict__ pending,
-                                                            const float* __restrict__ scores, const float* __restrict__ p_at_d,
-                                                            const int32_t* __restrict__ bits) {
+__global__ __launch_bounds__(256) void resample_w_kernel(const StepParams* __restrict__ sp, ResampleArgs a) {
+    resample_w_slab(sp, a, a.nacc[blockIdx.y]);
+}
+
+// pass 3 for sequence bi, after n accepted tokens
+__device__ __forceinline__ void resample_pick(const StepParams* __restrict__ sp, const ResampleArgs& a, int bi, int n, int32_t* len,
+                                              int32_t* pending, const float* scores, const float* p_at_d, const int32_t* bits) {
     __shared__ double wave_tot[4];
     __shared__ double slab_w[256];
     __shared__ int hit_slab, last_slab;
     __shared__ double hit_before, last_before;
-    const int bi = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int b = sp->seq_base + bi;
     const int gamma = sp->gamma, nblk = a.nslab / 256;
-    const int n = a.nacc[bi];
     const int row = bi * (gamma + 1) + n;
     const float4 st = a.rowstat[row];
     if (sp->mirror && tid < gamma) {                 // gamma <= 63; written through, done when the launch is
@@ -866,6 +871,35 @@ __global__ __launch_bounds__(256) void resample_pick_kernel(const StepParams* __
         pending[b] = next;
         if (sp->emit_tokens) sp->emit_tokens[(size_t)bi * sp->emit_gamma + sp->step] = next;
     }
+}
+
+__global__ __launch_bounds__(256) void resample_pick_kernel(const StepParams* __restrict__ sp, ResampleArgs a,
+                                                            int32_t* __restrict__ len, int32_t* __restrict__ pending,
+                                                            const float* __restrict__ scores, const float* __restrict__ p_at_d,
+                                                            const int32_t* __restrict__ bits) {
+    resample_pick(sp, a, blockIdx.x, a.nacc[blockIdx.x], len, pending, scores, p_at_d, bits);
+}
+
+// Scan and all three passes in one launch (grid: 1 x sequences) where one workgroup holds the whole vocabulary (up to 4096 entries): what
+// the passes leave for each other is the workgroup's own, and a barrier stands where a launch did (tiny model: 13.2 us in three
+// launches and a gap).
+__global__ __launch_bounds__(256) void scan_draw_kernel(const StepParams* __restrict__ sp, ResampleArgs a, const float* scores, float* p_at_d,
+                                                        int32_t* bits, int32_t* nacc, const int32_t* ranks, int32_t* len, int32_t* pending) {
+    __shared__ int n_sh;
+    const int bi = blockIdx.y;
+    if (threadIdx.x < 64) {
+        const int n = accept_scan_seq(bi, threadIdx.x, true, sp, a.V, a.inv_temp, a.logits, a.rowstat, scores, p_at_d, bits, nacc, ranks);
+        if (threadIdx.x == 0) n_sh = n;
+    }
+    __syncthreads();
+    const int n = n_sh;
+    resample_e_slab(sp, a, n, sp->emit_probs ? sp->emit_probs + ((size_t)bi * sp->emit_gamma + sp->step) * a.V : nullptr);
+    __syncthreads();                                   // its sums are in memory
+    if (n < sp->gamma) {                               // uniform
+        resample_w_slab(sp, a, n);
+        __syncthreads();
+    }
+    resample_pick(sp, a, bi, n, len, pending, scores, p_at_d, bits);
 }
 
 // Draft proposal (Eq. 1) at T = 0: the row's next-token law, one-hot at the arg-max, into column `step` of draft_probs

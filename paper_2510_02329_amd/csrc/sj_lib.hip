@@ -338,10 +338,8 @@ static void rule_plans(sj_kv* kv) {
         kv->plan_o[i] = plan_partial(d / 16, Nq / kstep, i == 0);
         kv->plan_d[i] = plan_partial(d / 16, F / kstep, i == 0);
     }
-    kv->plan_gu = GemmPlan{};
-    kv->plan_gu.nt = (2 * F / 16) % 7 == 0 ? 7 : 8;       // whole rounds of workgroups where 7 tiles give them
-    kv->plan_gu.waves = 8; kv->plan_gu.split = 1; kv->plan_gu.depth = 2;
-    kv->plan_lm = GemmPlan{8, 4, 1, 2};
+    kv->plan_gu = rule_gate_up(2 * F / 16);
+    kv->plan_lm = rule_logits(c.vocab / 16);
     // at most 8 rows with two bf16 planes: the LDS-ring kernel where a shape of it fits (3 - 8 % faster on the
     // 8B-shaped projections at 6 rows; the start-up measurement may still prefer another shape)
     // (SJ_RING_ROWS = 0..16 moves the row limit of this rule; from 9 rows on, and with one plane, the kernel takes one
@@ -353,10 +351,10 @@ static void rule_plans(sj_kv* kv) {
         if (rq.waves) kv->plan_qkv[0] = rq;
         if (ro.waves) kv->plan_o[0] = ro;
         if (rd.waves) kv->plan_d[0] = rd;
-        GemmPlan g = kv->plan_gu;
-        g.waves = RING_WAVES; g.depth = 8;
+        const bool few_gu = kv->plan_gu.nt == 1, few_lm = kv->plan_lm.nt == 2;     // small matrices: four n-tiles, the fewest with a ring
+        const GemmPlan g{few_gu ? 4 : kv->plan_gu.nt, RING_WAVES, 1, few_gu ? 4 : 8};
         if (ring_fits(g, 2 * F / 16, d / kstep, 1, 2, true)) kv->plan_gu = g;
-        GemmPlan l{8, RING_WAVES, 1, 4};
+        const GemmPlan l{few_lm ? 4 : 8, RING_WAVES, 1, few_lm ? 8 : 4};
         if (ring_fits(l, c.vocab / 16, d / kstep, 1, 2, true)) kv->plan_lm = l;
     }
 }
@@ -931,9 +929,9 @@ static int few_swiglu(const GemmPlan& p, hipStream_t st, const void* W, const vo
 #define SJ_SHAPE(NT, WV, D)                                                                                         \
     if (p.nt == NT && p.waves == WV && p.depth == D)                                                                \
         return gemm<T, NT, EPI_SWIGLU, SPL, WV, D>(st, W, X, xplane, K, N2, rows, 1, nullptr, act, actplane, nullptr, 0.f, fa);
-    SJ_SHAPE(7, 8, 2) SJ_SHAPE(8, 8, 2)
+    SJ_SHAPE(7, 8, 2) SJ_SHAPE(8, 8, 2) SJ_SHAPE(1, 8, 2)
     if constexpr (SPL <= 2) {
-        SJ_SHAPE(4, 8, 2) SJ_SHAPE(4, 4, 2) SJ_SHAPE(2, 8, 2) SJ_SHAPE(2, 4, 2) SJ_SHAPE(1, 8, 2)
+        SJ_SHAPE(4, 8, 2) SJ_SHAPE(4, 4, 2) SJ_SHAPE(2, 8, 2) SJ_SHAPE(2, 4, 2)
         SJ_SHAPE(7, 8, 3) SJ_SHAPE(7, 8, 4) SJ_SHAPE(8, 8, 4)
     }
 #undef SJ_SHAPE
@@ -987,7 +985,7 @@ static int few_logits(const GemmPlan& p, hipStream_t st, const void* W, const vo
 #define SJ_SHAPE(NT, WV)                                                                                            \
     if (p.nt == NT && p.waves == WV)                                                                                \
         return gemm<T, NT, EPI_LOGITS, SPL, WV>(st, W, X, xplane, K, V, rows, 1, logits, nullptr, 0, stats, inv_temp, fa);
-    SJ_SHAPE(8, 4)
+    SJ_SHAPE(8, 4) SJ_SHAPE(2, 8)
     if constexpr (SPL <= 2) { SJ_SHAPE(8, 8) SJ_SHAPE(4, 8) SJ_SHAPE(4, 4) }
 #undef SJ_SHAPE
     if (p.nt == 8 && p.waves != 4) return few_logits<T, SPL>(GemmPlan{8, 4, 1, 2}, st, W, X, xplane, K, V, rows, logits, stats, inv_temp, fa);
@@ -1086,7 +1084,8 @@ static int tune_gate_up(sj_kv* kv, int rows, hipEvent_t e0, hipEvent_t e1) {
     for (int i = 0; i < (int)(sizeof(shapes) / sizeof(shapes[0])); ++i) {
         if (SPL > 2 && i >= 2) break;
         const int nt = shapes[i][0], wv = shapes[i][1];
-        if (ntiles % nt || (d / Traits<T>::KSTEP) / wv < 4 || ntiles / nt < 128) continue;
+        const bool small = nt <= rule_gate_up(ntiles).nt;        // the rule's shape of a small matrix, where it starts from a ring
+        if (ntiles % nt || (!small && ((d / Traits<T>::KSTEP) / wv < 4 || ntiles / nt < 128))) continue;
         GemmPlan p;
         p.nt = nt; p.waves = wv; p.split = 1; p.depth = shapes[i][2];
         cands.push_back(p);
@@ -1126,7 +1125,7 @@ static int tune_lm_head(sj_kv* kv, int rows, hipEvent_t e0, hipEvent_t e1) {
         return SJ_OK;
     };
     static const int shapes[][2] = {{8, 4}, {8, 8}, {4, 8}, {4, 4}};
-    std::vector<GemmPlan> cands;
+    std::vector<GemmPlan> cands{rule_logits(V / 16)};
     for (int i = 0; i < (int)(sizeof(shapes) / sizeof(shapes[0])); ++i) {
         if (SPL > 2) break;
         const int nt = shapes[i][0], wv = shapes[i][1];
@@ -1272,6 +1271,7 @@ struct Runner {
     hipStream_t st;
     int nseq, rps, R;
     const Forward* w = kv;     // the buffers it works in
+    int seq_base = 0;          // first sequence (a prompt's: its index)
 
     KvView<T> view() const {
         KvView<T> v;
@@ -1349,13 +1349,14 @@ struct Runner {
         const int mq = small ? 1 : std::min(mtiles, 4);
         const int qgroups = (mtiles + mq - 1) / mq;
         dim3 grid(kv->nchunk_max, md.Hkv * qgroups, nseq);
-        const bool pb2 = parts <= 2;        // at most two QKV partials: fetch them two at a time
+        // at most two QKV partials: fetch them two at a time; blocks of many rows have five or six
+        const bool pb2 = parts <= 2;
 #define ATTN_PB(HD, MQ, PB)                                                                                            \
-    attn_fused_kernel<T, HD, MQ, SPL, PB><<<grid, 256, 0, st>>>(kv->sp_dev, md, w->part, parts, R, w->cs, view(), \
+    attn_fused_kernel<T, HD, MQ, SPL, PB><<<grid, 256, 0, st>>>(seq_base, rps, md, w->part, parts, R, w->cs, view(), \
                                                                 layer, kv->chunk_keys, kv->nchunk_max, kv->opart, kv->tickets,  \
                                                                 (T*)w->attn_out, plane(md.Hq * md.hd), rm())
 #define ATTN(HD, MQ)                                                                                                   \
-    do { if (pb2) ATTN_PB(HD, MQ, 2); else ATTN_PB(HD, MQ, 4); } while (0)
+    do { if (pb2) ATTN_PB(HD, MQ, 2); else ATTN_PB(HD, MQ, (MQ >= 3 ? 6 : 4)); } while (0)
         if (md.hd == 128) {
             switch (mq) { case 1: ATTN(128, 1); break; case 2: ATTN(128, 2); break; case 3: ATTN(128, 3); break; default: ATTN(128, 4); }
         } else {
@@ -1496,6 +1497,12 @@ struct Runner {
         ra.V = md.V; ra.nslab = kv->nslab; ra.slab_len = kv->slab_len; ra.inv_temp = md.inv_temp;
         ra.logits = kv->logits; ra.rowstat = kv->rowstat; ra.nacc = kv->nacc; ra.epart = kv->epart; ra.wpart = kv->wpart;
         ra.eblk = kv->eblk; ra.wblk = kv->wblk;
+        if (md.inv_temp > 0.f && kv->nslab == 256) {       // one workgroup holds the vocabulary
+            scan_draw_kernel<<<dim3(1, nseq), 256, 0, st>>>(kv->sp_dev, ra, kv->scores, kv->p_at_d, kv->bits, kv->nacc, kv->ranks, kv->len_dev,
+                                                            kv->pending_dev);
+            LAUNCHCHK("scan_draw");
+            return SJ_OK;
+        }
         if (md.inv_temp > 0.f) {
             dim3 g(kv->nslab / 256, nseq);
             scan_resample_e_kernel<<<g, 256, 0, st>>>(kv->sp_dev, ra, kv->scores, kv->p_at_d, kv->bits, kv->nacc, kv->ranks);
@@ -1919,7 +1926,7 @@ static int prefill_impl(sj_model* m, sj_kv* kv, int seq, const int32_t* tokens, 
         p.nseq = 1; p.seq_base = seq; p.rps = cn; p.gamma = cn - 1; p.tok_mode = 1; p.prefill_tokens = fw->prefill_tok;
         int rc = set_params(kv, st, p);
         if (rc) return rc;
-        Runner<T, SPL> run{m, kv, st, 1, cn, cn, fw};
+        Runner<T, SPL> run{m, kv, st, 1, cn, cn, fw, seq};
         int head_rows = cn;
         if (!long_chunks) {
             if ((rc = run.layers())) return rc;
