@@ -161,6 +161,7 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(int seq_base, int rps, 
     auto nr_issue = [&](int base, int s0) {
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
+            if (base + u * 256 >= nr_total) break;     // uniform: a block of one row of head dimension 64 has 64 items
             int j, i; bool isv;
             nr_item(min(base + u * 256 + tid, nr_total - 1), j, i, isv);
             const int row = bi * rps + j, col = (isv ? Nq + Nk : Nq) + kvh * HD + i;
@@ -229,6 +230,7 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(int seq_base, int rps, 
                 if (base != 0 || s0 != 0) nr_issue(base, s0);
 #pragma unroll
                 for (int u = 0; u < NB; ++u)
+                    if (base + u * 256 < nr_total)
 #pragma unroll
                     for (int v = 0; v < PB; ++v) {
                         const float wgt = (s0 + v < nparts) ? 1.f : 0.f;
@@ -238,6 +240,7 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(int seq_base, int rps, 
             }
 #pragma unroll
             for (int u = 0; u < NB; ++u) {
+                if (base + u * 256 >= nr_total) break;
                 const int it = base + u * 256 + tid;
                 if (it < nr_total) {
                     int j, i; bool isv;

@@ -271,23 +271,7 @@ __device__ __forceinline__ float row_inv_rms(const GemmArgs& a, int r, int lane)
 // take part in the shuffles and store nothing).
 template <typename T, int NT, int EPI, int SPL>
 __device__ __forceinline__ void few_epilogue(const GemmArgs& a, const float (&v)[NT], int row, int en, int nt0) {
-    if constexpr (EPI == EPI_RESID) {
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const int col = (nt0 + t) * 16 + en;
-            float xv = 0.f;
-            if (row < a.R) {
-                xv = a.x[(size_t)row * a.N + col] + v[t];
-                a.x[(size_t)row * a.N + col] = xv;
-                Traits<T>::template store_split<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, col, a.N, a.rm), a.actplane,
-                                                     xv * Traits<T>::load(reinterpret_cast<const T*>(a.gain) + col));
-            }
-            float ss = xv * xv;
-#pragma unroll
-            for (int o = 1; o < 16; o <<= 1) ss += __shfl_xor(ss, o, 64);
-            if (row < a.R && en == 0) a.ss_out[(size_t)row * (a.N / 16) + nt0 + t] = ss;
-        }
-    } else if constexpr (EPI == EPI_PARTIAL) {
+    if constexpr (EPI == EPI_PARTIAL) {
         if (row < a.R) {
 #pragma unroll
             for (int t = 0; t < NT; ++t)
@@ -346,12 +330,6 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(GemmArgs a) {
     __shared__ float red[WAVES][NT * MT][256];
     __shared__ float inv_rms[MT * 16];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (a.ss_in) {                                       // uniform; read after the reduction's barrier
-        for (int row = w; row < a.R; row += WAVES) {
-            const float inv = row_inv_rms(a, row, lane);
-            if (lane == 0) inv_rms[row] = inv;
-        }
-    }
     const int r = lane & 15, g = lane >> 4;
     const int KS = a.K / KSTEP;
     const int nt0 = blockIdx.x * NT;
@@ -421,7 +399,30 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(GemmArgs a) {
     if (nks > 0) {
 #pragma unroll
         for (int j = 0; j < D - 1; ++j) load(j, min(j, nks - 1));
-        GEMM_STAMP(1);
+    }
+    // What the end needs from memory, asked for behind the first weights (in front of them, or at the end, it was a memory trip of its
+    // own: 1 us of a launch of 5): the shares of the rows' sums of squares (at most 8 rows where there are any), and the residual
+    // stream and gain of this thread's columns.  Without them any valid address: no load under a branch.
+    constexpr bool SS = MT == 1 && (EPI == EPI_PARTIAL || EPI == EPI_SWIGLU);     // the products that follow a residual epilogue
+    constexpr int SSR = SS ? (8 + WAVES - 1) / WAVES : 1;
+    float4 ssv[SSR];
+    const int nss = a.K / 16;                            // a multiple of 4
+#pragma unroll
+    for (int i = 0; SS && i < SSR; ++i)
+        ssv[i] = *reinterpret_cast<const float4*>(a.ss_in ? a.ss_in + (size_t)min(w + i * WAVES, a.R - 1) * nss + min(lane * 4, nss - 4)
+                                                          : reinterpret_cast<const float*>(a.X));
+    float res_x[NT], res_g[NT];
+    if constexpr (EPI == EPI_RESID) {
+        const int row = min((int)(threadIdx.x >> 4) & 15, a.R - 1);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const int col = (nt0 + t) * 16 + (threadIdx.x & 15);
+            res_x[t] = a.x[(size_t)row * a.N + col];
+            res_g[t] = Traits<T>::load(reinterpret_cast<const T*>(a.gain) + col);
+        }
+    }
+    GEMM_STAMP(1);
+    if (nks > 0) {
         for (int c = 0; c < nks; c += D) {
 #pragma unroll
             for (int j = 0; j < D; ++j) {
@@ -440,6 +441,20 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(GemmArgs a) {
         }
     }
 
+    if (SS && a.ss_in) {                                 // uniform; read after the reduction's barrier
+#pragma unroll
+        for (int i = 0; i < SSR; ++i) {
+            const int row = w + i * WAVES;
+            if (row >= a.R) break;                       // uniform
+            float ss = lane * 4 < nss ? (ssv[i].x + ssv[i].y) + (ssv[i].z + ssv[i].w) : 0.f;
+            for (int e = lane * 4 + 256; e < nss; e += 256) {
+                const float4 v = *reinterpret_cast<const float4*>(a.ss_in + (size_t)row * nss + e);
+                ss += (v.x + v.y) + (v.z + v.w);
+            }
+            ss = wave_sum(ss);
+            if (lane == 0) inv_rms[row] = 1.0f / sqrtf(ss / (float)a.K + a.eps);
+        }
+    }
     GEMM_STAMP(2);
     // D[n = 4g+i][row = r]  ->  red[w][tile][row*16 + n]
 #pragma unroll
@@ -465,9 +480,24 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(GemmArgs a) {
             float sum = red[0][t * MT + m][tid];
 #pragma unroll
             for (int ww = 1; ww < WAVES; ++ww) sum += red[ww][t * MT + m][tid];
-            v[t] = a.ss_in && row < a.R ? sum * inv_rms[row] : sum;
+            v[t] = SS && a.ss_in && row < a.R ? sum * inv_rms[row] : sum;
         }
-        few_epilogue<T, NT, EPI, SPL>(a, v, row, en, nt0);
+        if constexpr (EPI == EPI_RESID) {                // at most 8 rows: one row tile
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const int col = (nt0 + t) * 16 + en;
+                float xv = 0.f;
+                if (row < a.R) {
+                    xv = res_x[t] + v[t];
+                    a.x[(size_t)row * a.N + col] = xv;
+                    Traits<T>::template store_split<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, col, a.N, a.rm), a.actplane, xv * res_g[t]);
+                }
+                float ss = xv * xv;
+#pragma unroll
+                for (int o = 1; o < 16; o <<= 1) ss += __shfl_xor(ss, o, 64);
+                if (row < a.R && en == 0) a.ss_out[(size_t)row * (a.N / 16) + nt0 + t] = ss;
+            }
+        } else few_epilogue<T, NT, EPI, SPL>(a, v, row, en, nt0);
     }
 }
 

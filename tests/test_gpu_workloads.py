@@ -130,7 +130,11 @@ def test_llama70b_batch4():
     with the measured figure printed; the replay below shows the same step inside 0.05 of the bar once both sides
     store the same rows."""
     stats = _llama70b(force_rounding=False, scale=2.0)
-    assert stats["decisions"]["unexcused"] == 0 and stats["decisions"]["tokens_equal"] == stats["decisions"]["tokens"]
+    # Which of the summation orders the start-up measurement picks moves these logits by up to the bar tau(l) = 1e-2 + 2e-2 |l|, and with
+    # them a token whose uniform falls next to an edge of its cell: such a token has to lie in the oracle's cell widened by
+    # (e^(2 tau) - 1) min(F, 1 - F) (tests/gpu_common.py; one in ten runs has one of the four there).  Bits and lengths stay exact.
+    d = stats["decisions"]
+    assert d["unexcused"] == 0 and d["bit_excused"] == 0 and d["len_excused"] == 0 and d["tokens_equal"] + d["token_excused"] == d["tokens"]
 
 
 @pytest.mark.skipif(os.environ.get("SJ_RUN_70B_REPLAY") != "1",
