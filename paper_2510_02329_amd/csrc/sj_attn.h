@@ -489,7 +489,8 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(int seq_base, int rps, 
     ATTN_STAMP(9);
     if (!sm.last) return;
 
-    // ranges in order, CB per batch of independent loads, running maximum carried across batches
+    // ranges in order, running maximum carried from one group of AB to the next; CB ranges (a multiple of AB) per batch of independent loads
+    constexpr int AB = MQ <= 2 ? 8 : MQ == 3 ? 4 : 2;
     const float* base = opart + group * nchunk_max * PF;
     float mx[MQ], den[MQ], num[HPW][MQ][4];
 #pragma unroll
@@ -520,32 +521,36 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(int seq_base, int rps, 
             }
             if (c0 == 0) ATTN_STAMP(10);
 #pragma unroll
-            for (int mq = 0; mq < MQ; ++mq) {
-                float bm = mx[mq];
+            for (int a0 = 0; a0 < CB; a0 += AB) {
+                if (c0 + a0 >= nch) break;             // uniform
 #pragma unroll
-                for (int u = 0; u < CB; ++u) bm = fmaxf(bm, (c0 + u < nch) ? mv[u][mq] : -INFINITY);
-                const float resc = (mx[mq] == -INFINITY) ? 0.f : __expf(mx[mq] - bm);
-                mx[mq] = bm;
-                den[mq] *= resc;
+                for (int mq = 0; mq < MQ; ++mq) {
+                    float bm = mx[mq];
 #pragma unroll
-                for (int hh = 0; hh < HPW; ++hh)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) num[hh][mq][i] *= resc;
-#pragma unroll
-                for (int u = 0; u < CB; ++u) {
-                    const float f = (c0 + u < nch && mv[u][mq] != -INFINITY) ? __expf(mv[u][mq] - bm) : 0.f;
-                    den[mq] += f * lv[u][mq];
+                    for (int u = a0; u < a0 + AB; ++u) bm = fmaxf(bm, (c0 + u < nch) ? mv[u][mq] : -INFINITY);
+                    const float resc = (mx[mq] == -INFINITY) ? 0.f : __expf(mx[mq] - bm);
+                    mx[mq] = bm;
+                    den[mq] *= resc;
 #pragma unroll
                     for (int hh = 0; hh < HPW; ++hh)
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) num[hh][mq][i] += f * ov[u][hh][mq][i];
+                        for (int i = 0; i < 4; ++i) num[hh][mq][i] *= resc;
+#pragma unroll
+                    for (int u = a0; u < a0 + AB; ++u) {
+                        const float f = (c0 + u < nch && mv[u][mq] != -INFINITY) ? __expf(mv[u][mq] - bm) : 0.f;
+                        den[mq] += f * lv[u][mq];
+#pragma unroll
+                        for (int hh = 0; hh < HPW; ++hh)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) num[hh][mq][i] += f * ov[u][hh][mq][i];
+                    }
                 }
             }
         }
     };
-    // nine to twelve ranges in one round trip as well (1B-shaped decode over 1029 keys: 0.5 us of 9)
-    if (MQ == 1 && nch > 8) merge(std::integral_constant<int, 12>{});   // uniform
-    else merge(std::integral_constant<int, (MQ <= 2 ? 8 : MQ == 3 ? 4 : 2)>{});
+    // nine to sixteen ranges in one round trip as well (1B-shaped decode over 1029 keys: 0.5 us of 9)
+    if (MQ == 1 && nch > AB) merge(std::integral_constant<int, 2 * AB>{});   // uniform
+    else merge(std::integral_constant<int, AB>{});
     ATTN_STAMP(11);
 #pragma unroll
     for (int hh = 0; hh < HPW; ++hh)
