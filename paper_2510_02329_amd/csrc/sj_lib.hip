@@ -1127,7 +1127,7 @@ static int tune_lm_head(sj_kv* kv, int rows, hipEvent_t e0, hipEvent_t e1) {
     static const int shapes[][2] = {{8, 4}, {8, 8}, {4, 8}, {4, 4}};
     std::vector<GemmPlan> cands{rule_logits(V / 16)};
     for (int i = 0; i < (int)(sizeof(shapes) / sizeof(shapes[0])); ++i) {
-        if (SPL > 2) break;
+        if (SPL > 2 || cands[0].nt == 2) break;         // (a small matrix: the rule's shape, where it starts from a ring)
         const int nt = shapes[i][0], wv = shapes[i][1];
         if ((V / 16) % nt || (d / Traits<T>::KSTEP) / wv < 4) continue;
         GemmPlan p;
