@@ -538,7 +538,7 @@ static float* mirror_take(int rows) {
     (void)hipGetLastError();
     return nullptr;
 }
-// (the device has been waited for)
+// (no kernel writes to it any more)
 static void mirror_give(float* h, int rows) {
     if (!h) return;
     if ((size_t)3 * rows * 4 <= MIRROR_BYTES) {
@@ -552,12 +552,12 @@ extern "C" int sj_kv_free(sj_kv* kv) {
     if (!kv) return fail(SJ_EINVAL, "kv is null");
     (void)hipDeviceSynchronize();
     if (kv->pinned_state) (void)hipHostFree(kv->pinned_state);
-    mirror_give(kv->mirror, kv->max_rows);
     if (kv->rewind_done) (void)hipEventDestroy(kv->rewind_done);
     for (hipEvent_t e : kv->tev) (void)hipEventDestroy(e);
     for (auto& g : kv->graphs) (void)hipGraphExecDestroy(g.second);
     if (kv->cap_stream) (void)hipStreamDestroy(kv->cap_stream);
-    free_all(kv->allocs);
+    free_all(kv->allocs);                                     // waits for the device that holds them
+    mirror_give(kv->mirror, kv->max_rows);
     delete kv;
     return SJ_OK;
 }
