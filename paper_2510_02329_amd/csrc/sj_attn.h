@@ -530,19 +530,18 @@ __global__ __launch_bounds__(256) void attn_fused_kernel(int seq_base, int rps, 
                     for (int u = a0; u < a0 + AB; ++u) bm = fmaxf(bm, (c0 + u < nch) ? mv[u][mq] : -INFINITY);
                     const float resc = (mx[mq] == -INFINITY) ? 0.f : __expf(mx[mq] - bm);
                     mx[mq] = bm;
-                    den[mq] *= resc;
-#pragma unroll
-                    for (int hh = 0; hh < HPW; ++hh)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) num[hh][mq][i] *= resc;
+                    // The sums so far meet a group's first range in one fused operation, spelled out: `sum *= resc; sum += f * x` may be
+                    // fused either way, and the compiler chose differently for another loop around it (1e-4 of a draft's probabilities).
 #pragma unroll
                     for (int u = a0; u < a0 + AB; ++u) {
                         const float f = (c0 + u < nch && mv[u][mq] != -INFINITY) ? __expf(mv[u][mq] - bm) : 0.f;
-                        den[mq] += f * lv[u][mq];
+                        den[mq] = u == a0 ? __builtin_fmaf(den[mq], resc, f * lv[u][mq]) : __builtin_fmaf(f, lv[u][mq], den[mq]);
 #pragma unroll
                         for (int hh = 0; hh < HPW; ++hh)
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) num[hh][mq][i] += f * ov[u][hh][mq][i];
+                            for (int i = 0; i < 4; ++i)
+                                num[hh][mq][i] = u == a0 ? __builtin_fmaf(num[hh][mq][i], resc, f * ov[u][hh][mq][i])
+                                                         : __builtin_fmaf(f, ov[u][hh][mq][i], num[hh][mq][i]);
                     }
                 }
             }

@@ -1,5 +1,7 @@
 """GPU edge cases on small models: draft lengths 1 and max, temperature 0, verifier modes, judge
 thresholds outside (0,1), capacity errors, out-of-range draft tokens, bitwise-repeatable reruns."""
+import zlib
+
 import numpy as np
 import pytest
 import torch
@@ -352,5 +354,26 @@ def test_room_is_checked_against_true_lengths():
             sj.sj_draft_block(gpu.model, gpu.kv, left + 1, u, False, ids, q, torch.cuda.current_stream())
         sj.sj_draft_block(gpu.model, gpu.kv, left, u, False, ids, q, torch.cuda.current_stream())
         assert sj.sj_kv_state(gpu.kv, 1)[0][0] == 64
+    finally:
+        gpu.close()
+
+
+
+@pytest.mark.parametrize("d,heads,kv_heads,hd,length,pinned", [(2048, 32, 8, 64, 1029, 0xad12af47), (2048, 32, 8, 64, 1900, 0x5e7eabe5),
+                                                               (2048, 16, 4, 128, 1900, 0x8fa090b3), (4096, 32, 8, 128, 1060, 0x8d1b4a55)])
+def test_decode_over_many_key_ranges_keeps_its_bits(d, heads, kv_heads, hd, length, pinned, monkeypatch):
+    """Nine and more key ranges are read back in one trip and added in the same order, with the same roundings, as eight at a time: with
+    the shapes of the rule the hidden state is the same to the last bit in every build that keeps its order of sums.  The checksums are those
+    of a build that read eight at a time; a change that means to add in another order brings other ones."""
+    monkeypatch.setenv("SJ_TUNE", "0")
+    shape = synth.ModelShape(f"bits_{d}_{hd}", "bf16", 1, d, heads, kv_heads, hd, 2048, 16384, 500000.0, batch=1, gamma=5, weight_std=0.05)
+    gpu, _, _, _ = _setup(shape, [length], cap=[length + 8])
+    try:
+        u = torch.arange(1, 6, device="cuda", dtype=torch.float32).reshape(5, 1) / 8
+        tokens, probs = torch.zeros(1, 5, dtype=torch.int32, device="cuda"), torch.zeros(1, 5, shape.vocab, device="cuda")
+        sj.sj_draft_block(gpu.model, gpu.kv, 5, u, True, tokens, probs, torch.cuda.current_stream())
+        hidden = sj.sj_debug_fetch(gpu.kv, sj.SJ_DBG_HIDDEN, np.empty((1, d), np.float32))
+        print("tokens", tokens.tolist(), "checksum 0x%08x" % zlib.crc32(hidden.tobytes()))
+        assert zlib.crc32(hidden.tobytes()) == pinned
     finally:
         gpu.close()
