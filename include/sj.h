@@ -17,6 +17,8 @@
  *     current device, owned by the caller, and must stay valid until the stream has run.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  Calls that take
  *     a stream are asynchronous on it; their outputs are valid once the stream is synchronised.
+ *     sj_prefill, sj_draft_block and sj_score_block first wait for all work on the device (they ask it for
+ *     the lengths).
  *   - The library owns sj_model / sj_kv and all workspace; it allocates at load / create time
  *     (plus a one-time launch-graph build on the first step of a given gamma, and the prompt-chunk
  *     buffers with a cache object's first long prompt, see sj_prefill), never per step.

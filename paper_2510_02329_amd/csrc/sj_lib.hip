@@ -136,7 +136,6 @@ struct sj_kv : Forward {       // the inherited buffers serve the blocks of up t
         if (work == NONE) { work = ONE; work_stream = st; }
         else if (work == ONE && work_stream != st) work = MIXED;
     }
-    bool follows(hipStream_t st) const { return work == NONE || (work == ONE && work_stream == st); }
     // judge scores, p(draft) and accept bits of the last call, max_rows words each, in host memory that the device writes: there from
     // the first sj_debug_fetch of one of them on
     mutable std::atomic<float*> mirror{nullptr};
@@ -799,13 +798,11 @@ static int refresh_lengths(sj_kv* kv) {
     return SJ_OK;
 }
 
-// May sequences lo .. hi - 1 take `rows` more positions in a call on `st`?  The host keeps an upper bound of every length: the device is asked
-// only when the bound trips, or when earlier work on the object went to another stream (such a call has always waited for it).
-// Asking each time - a wait, a copy, and an idle device until the next launches - cost draft blocks, scoring and prompts 50 - 60 us.
-static int check_room(sj_kv* kv, hipStream_t st, int lo, int hi, int rows) {
-    bool room = kv->follows(st);
-    for (int b = lo; b < hi; ++b) room = room && kv->len_upper[b] + rows <= kv->cap[b];
-    if (room) return SJ_OK;
+// May sequences lo .. hi - 1 take `rows` more positions, by the lengths on the device once all of its work is done?  Draft blocks, scoring
+// and prompts wait here for the whole device: callers rely on it for inputs and outputs still in use on other streams, and for an object
+// handed from one thread or stream to another (a stream's handle does not tell: hipStreamPerThread is one handle for many streams, a
+// destroyed stream's handle is given out again).
+static int check_room(sj_kv* kv, int lo, int hi, int rows) {
     const int rc = refresh_lengths(kv);
     if (rc) return rc;
     for (int b = lo; b < hi; ++b)
@@ -1724,7 +1721,7 @@ extern "C" int sj_draft_block(sj_model* m, sj_kv* kv, int32_t gamma, const float
     if (m->cfg.n_layers == 0) return fail(SJ_EINVAL, "head-only model has no decode loop");
     const int need = gamma + (feed_last ? 1 : 0);
     hipStream_t st = (hipStream_t)stream;
-    int rc = check_room(kv, st, 0, kv->batch, need);
+    int rc = check_room(kv, 0, kv->batch, need);
     if (rc) return rc;
     kv->note(st);
     StepParams p{};
@@ -1768,7 +1765,7 @@ extern "C" int sj_score_block(sj_model* m, sj_kv* kv, int32_t n, const int32_t* 
     if (!input_tokens || !target_tokens || !logprob) return fail(SJ_EINVAL, "null device pointer argument");
     if (hidden_out && (hidden_row < 0 || hidden_row >= n)) return fail(SJ_EINVAL, "hidden_row %d outside the block", hidden_row);
     hipStream_t st = (hipStream_t)stream;
-    int rc = check_room(kv, st, 0, kv->batch, n);
+    int rc = check_room(kv, 0, kv->batch, n);
     if (rc) return rc;
     kv->note(st);
     StepParams p{};
@@ -1962,7 +1959,7 @@ extern "C" int sj_prefill(sj_model* m, sj_kv* kv, int32_t seq, const int32_t* to
     for (int i = 0; i < n; ++i)
         if (tokens_host[i] < 0 || tokens_host[i] >= m->cfg.vocab) return fail(SJ_EINVAL, "token %d out of range", i);
     hipStream_t st = (hipStream_t)stream;
-    int rc = check_room(kv, st, seq, seq + 1, n);
+    int rc = check_room(kv, seq, seq + 1, n);
     if (rc) return rc;
     kv->note(st);
     if (m->cfg.dtype == SJ_DTYPE_FP32) rc = prefill_impl<float, 1>(m, kv, seq, tokens_host, n, st);
