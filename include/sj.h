@@ -20,8 +20,9 @@
  *     sj_prefill, sj_draft_block and sj_score_block first wait for all work on the device (they ask it for
  *     the lengths).
  *   - The library owns sj_model / sj_kv and all workspace; it allocates at load / create time
- *     (plus a one-time launch-graph build on the first step of a given gamma, and the prompt-chunk
- *     buffers with a cache object's first long prompt, see sj_prefill), never per step.
+ *     (plus a one-time launch-graph build on the first step of a given gamma, the prompt-chunk
+ *     buffers with a cache object's first long prompt, see sj_prefill, and 16 KB of pinned host memory
+ *     with its first fetch of a per-draft result, see sj_debug_fetch), never per step.
  *   - On an argument error no sequence state is modified.
  *   - Storage dtype (sj_config.dtype) applies to weights and the KV cache: 0 = fp32,
  *     1 = bf16 (bit pattern in uint16).  Host tensors handed over are in that dtype.
@@ -280,14 +281,16 @@ int sj_kernel_class_shape(const sj_kv* kv, int32_t kernel_class, int32_t rows, c
  * bf16 in every case and the bytes streamed from HBM do not change.  Ignored for fp32 models. */
 int sj_set_operand_planes(sj_kv* kv, int32_t planes);
 
-/* Intermediate results of the last step, copied to the host (synchronous; for parity tests).
+/* Intermediate results of the last step, copied to the host (for parity tests).  Waits for all work on the device.
  *   SJ_DBG_LOGITS       float [rows, vocab]     rows = batch*(gamma+1)
  *   SJ_DBG_HIDDEN       float [rows, d_model]   final hidden states after the last RMSNorm
  *   SJ_DBG_JUDGE_SCORES float [batch, gamma]    sigmoid scores, entry j for d_{j+1}
  *   SJ_DBG_P_AT_DRAFT   float [batch, gamma]    p(d_{j+1}) under the target
  *   SJ_DBG_ACCEPT_BITS  int32 [batch, gamma]    bit0 = Eq. 3 accepted, bit1 = judge accepted,
  *                                               bit2 = top-k accepted (top-k mode only)
- * nbytes must equal the size above for the gamma of the last step. */
+ * nbytes must equal the size above for the gamma of the last step.  From the first fetch of one of the last three on, the
+ * object's verification calls also write those to pinned host memory (12 bytes a draft token, at least 16 KB; up to eight
+ * freed blocks are kept for other objects), unless the caller has captured one of its calls into a graph. */
 #define SJ_DBG_LOGITS       0
 #define SJ_DBG_HIDDEN       1
 #define SJ_DBG_JUDGE_SCORES 2

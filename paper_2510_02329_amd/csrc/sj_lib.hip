@@ -129,18 +129,12 @@ struct sj_kv : Forward {       // the inherited buffers serve the blocks of up t
     std::vector<hipEvent_t> tev;          // start/stop pairs
     size_t tev_used = 0;
     int last_gamma = 0, last_rows = 0;
-    // the stream that the work since the last wait for the whole device went to (NONE: there was none, MIXED: several)
-    enum { NONE, ONE, MIXED } work = NONE;
-    hipStream_t work_stream = nullptr;
-    void note(hipStream_t st) {
-        if (work == NONE) { work = ONE; work_stream = st; }
-        else if (work == ONE && work_stream != st) work = MIXED;
-    }
     // judge scores, p(draft) and accept bits of the last call, max_rows words each, in host memory that the device writes: there from
     // the first sj_debug_fetch of one of them on
     mutable std::atomic<float*> mirror{nullptr};
     mutable std::mutex mirror_mu;
     bool mirrored = false;                // the last call wrote it
+    bool captured = false;                // graphs of the caller hold verification calls: a replay writes results without the host knowing
     std::vector<void*> allocs;
 };
 
@@ -587,7 +581,6 @@ extern "C" int sj_kv_rewind(sj_kv* kv, const int32_t* len_host, const int32_t* p
         for (int b = 0; b < kv->batch; ++b) { a.len[b] = len_host[b]; a.pending[b] = pending_host[b]; }
         rewind_kernel<<<1, REWIND_SEQS, 0, st>>>(a, kv->batch, kv->len_dev, kv->pending_dev);
         LAUNCHCHK("rewind");
-        kv->note(st);
         for (int b = 0; b < kv->batch; ++b) kv->len_upper[b] = len_host[b];
         return SJ_OK;
     }
@@ -600,7 +593,6 @@ extern "C" int sj_kv_rewind(sj_kv* kv, const int32_t* len_host, const int32_t* p
     std::memcpy(kv->pinned_state + kv->batch, pending_host, sizeof(int32_t) * kv->batch);
     HIPCHK(hipMemcpyAsync(kv->len_dev, kv->pinned_state, sizeof(int32_t) * 2 * kv->batch, hipMemcpyHostToDevice, st));
     HIPCHK(hipEventRecord(kv->rewind_done, st));
-    kv->note(st);
     kv->rewind_pending = true;
     for (int b = 0; b < kv->batch; ++b) kv->len_upper[b] = len_host[b];
     return SJ_OK;
@@ -793,7 +785,6 @@ extern "C" int sj_kv_read(const sj_kv* kv, int32_t seq, int32_t layer, int32_t p
 
 static int refresh_lengths(sj_kv* kv) {
     HIPCHK(hipDeviceSynchronize());
-    kv->work = sj_kv::NONE;
     HIPCHK(hipMemcpy(kv->len_upper.data(), kv->len_dev, sizeof(int32_t) * kv->batch, hipMemcpyDeviceToHost));
     return SJ_OK;
 }
@@ -1652,10 +1643,13 @@ static int check_step_args(sj_model* m, sj_kv* kv, int gamma, const void* a, con
 }
 
 // A verification call is about to go to `st`: its draw's last kernel also leaves the small per-draft results in host memory where
-// they have been asked for.
+// they have been asked for.  A call that the caller captures does not, and ends it for the object: which of its calls ran last is then known
+// to the caller alone.  (The default stream cannot be captured, and must not be asked while another is.)
 static void set_mirror(sj_kv* kv, hipStream_t st, StepParams& p) {
-    kv->note(st);
-    p.mirror = kv->mirror;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (st && hipStreamIsCapturing(st, &status) != hipSuccess) (void)hipGetLastError();
+    if (status != hipStreamCaptureStatusNone) kv->captured = true;
+    p.mirror = kv->captured ? nullptr : kv->mirror.load();
     p.mirror_stride = kv->max_rows;
 }
 
@@ -1723,7 +1717,6 @@ extern "C" int sj_draft_block(sj_model* m, sj_kv* kv, int32_t gamma, const float
     hipStream_t st = (hipStream_t)stream;
     int rc = check_room(kv, 0, kv->batch, need);
     if (rc) return rc;
-    kv->note(st);
     StepParams p{};
     p.nseq = kv->batch; p.seq_base = 0; p.rps = 1; p.gamma = 0; p.tok_mode = 0; p.mode = kv->mode; p.topk = kv->topk;
     p.theta = 0.5f;
@@ -1767,7 +1760,6 @@ extern "C" int sj_score_block(sj_model* m, sj_kv* kv, int32_t n, const int32_t* 
     hipStream_t st = (hipStream_t)stream;
     int rc = check_room(kv, 0, kv->batch, n);
     if (rc) return rc;
-    kv->note(st);
     StepParams p{};
     p.nseq = kv->batch; p.seq_base = 0; p.rps = n; p.gamma = n - 1; p.tok_mode = 2; p.mode = kv->mode; p.topk = kv->topk;
     p.draft_tokens = input_tokens;
@@ -1961,7 +1953,6 @@ extern "C" int sj_prefill(sj_model* m, sj_kv* kv, int32_t seq, const int32_t* to
     hipStream_t st = (hipStream_t)stream;
     int rc = check_room(kv, seq, seq + 1, n);
     if (rc) return rc;
-    kv->note(st);
     if (m->cfg.dtype == SJ_DTYPE_FP32) rc = prefill_impl<float, 1>(m, kv, seq, tokens_host, n, st);
     else if (kv->planes == 1) rc = prefill_impl<bf16_t, 1>(m, kv, seq, tokens_host, n, st);
     else if (kv->planes == 3) rc = prefill_impl<bf16_t, 3>(m, kv, seq, tokens_host, n, st);
@@ -1989,26 +1980,19 @@ extern "C" int sj_debug_fetch(const sj_kv* kv, int32_t what, void* dst_host, siz
     }
     if (want == 0) return fail(SJ_EINVAL, "item not produced by the last call");
     if (nbytes != want) return fail(SJ_EINVAL, "nbytes %zu != expected %zu", nbytes, want);
-    // Per-draft results (a few words a sequence) are in host memory once the device is done, from the call after the first fetch on:
-    // a wait alone takes 11 us, a wait and a copy of 40 bytes 26.
+    // Everything on the device first, on whatever stream: results may come from a graph of the caller's.
+    HIPCHK(hipDeviceSynchronize());
+    // Per-draft results (a few words a sequence) are then in host memory, from the call after the first fetch on (three small
+    // launches and the wait: 21 us, with a copy of 40 bytes behind it 33, of 96 KB 32).
     const int slot = what == SJ_DBG_JUDGE_SCORES ? 0 : what == SJ_DBG_P_AT_DRAFT ? 1 : what == SJ_DBG_ACCEPT_BITS ? 2 : -1;
-    if (slot >= 0 && kv->mirrored) {
-        HIPCHK(hipDeviceSynchronize());
-        std::memcpy(dst_host, kv->mirror + (size_t)slot * kv->max_rows, want);
-        return SJ_OK;
-    }
-    if (slot >= 0) {
+    if (slot >= 0 && !kv->captured) {
+        if (kv->mirrored) {
+            std::memcpy(dst_host, kv->mirror + (size_t)slot * kv->max_rows, want);
+            return SJ_OK;
+        }
         std::lock_guard<std::mutex> lock(kv->mirror_mu);
         if (!kv->mirror) kv->mirror = mirror_take(kv->max_rows);       // null: fetched by copies
     }
-    // Where all of the object's work is on the default stream, the copy is queued behind it and waited for once (96 KB: 23 us, with a
-    // wait in front of the copy 58).
-    if (kv->work == sj_kv::ONE && !kv->work_stream) {
-        HIPCHK(hipMemcpyAsync(dst_host, src, want, hipMemcpyDeviceToHost, nullptr));
-        HIPCHK(hipStreamSynchronize(nullptr));
-        return SJ_OK;
-    }
-    HIPCHK(hipDeviceSynchronize());
     HIPCHK(hipMemcpy(dst_host, src, want, hipMemcpyDeviceToHost));
     return SJ_OK;
 }

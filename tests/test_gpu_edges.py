@@ -377,3 +377,55 @@ def test_decode_over_many_key_ranges_keeps_its_bits(d, heads, kv_heads, hd, leng
         assert zlib.crc32(hidden.tobytes()) == pinned
     finally:
         gpu.close()
+
+
+def test_results_of_a_replayed_graph_are_fetched():
+    """A caller's graph that holds sj_verify_head writes the results of its latest replay, also where an eager call's were in
+    host memory before it, and also on a stream that the library has not seen."""
+    shape = BASE.scaled(batch=2, gamma=3)
+    gpu, cfg, W, caches = _setup(shape, [20, 9])
+    dev, R = gpu.dev, 2 * 4
+    try:
+        draft = synth.make_draft(shape, seed=41)
+        dt, dp, un = (torch.from_numpy(np.ascontiguousarray(draft[k])).to(dev) for k in ("tokens", "probs", "uniforms"))
+        hids = [torch.from_numpy(synth.make_hidden(shape, seed=s).view(np.int16)).to(dev) for s in (1, 2, 3)]
+        hid = hids[0].clone()
+        acc, nxt = torch.zeros(2, dtype=torch.int32, device=dev), torch.zeros(2, dtype=torch.int32, device=dev)
+        ids, lp = torch.zeros(2, 4, dtype=torch.int32, device=dev), torch.zeros(2, 4, device=dev)
+        head = lambda: sj.sj_verify_head(gpu.model, gpu.kv, 3, hid, dt, dp, un, 0.5, acc, nxt, torch.cuda.current_stream())  # noqa: E731
+
+        def fetch():
+            return (sj.sj_debug_fetch(gpu.kv, sj.SJ_DBG_P_AT_DRAFT, np.empty((2, 3), np.float32)).copy(),
+                    sj.sj_debug_fetch(gpu.kv, sj.SJ_DBG_HIDDEN, np.empty((R, shape.d_model), np.float32)).copy())
+
+        ref = []
+        for h in hids:                                       # by eager calls: the first by copies, later ones by the mirror
+            hid.copy_(h)
+            head()
+            torch.cuda.synchronize()
+            ref.append(fetch())
+        assert not np.array_equal(ref[0][0], ref[1][0])
+        # a second object: its first call is the captured one
+        sj.sj_kv_free(gpu.kv)
+        gpu.kv = sj.sj_kv_create(gpu.model, 2, [64, 64])
+        side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            head()
+        big = torch.rand(4096, 4096, device=dev)
+        for rep in range(3):
+            for eager, replayed in ((0, 1), (2, 0), (1, 2)):
+                hid.copy_(hids[eager])
+                sj.sj_score_block(gpu.model, gpu.kv, 4, ids, ids, lp, 0, None, torch.cuda.current_stream())
+                head()
+                for a, b in zip(fetch(), ref[eager]):
+                    assert np.array_equal(a, b), (rep, "eager")
+                hid.copy_(hids[replayed])
+                torch.cuda.synchronize()
+                with torch.cuda.stream(side):
+                    for _ in range(8):
+                        torch.mm(big, big)                   # some milliseconds: the fetch has to wait for them
+                    graph.replay()
+                for a, b in zip(fetch(), ref[replayed]):
+                    assert np.array_equal(a, b), (rep, "replayed")
+    finally:
+        gpu.close()

@@ -27,3 +27,37 @@ int main() {
 def test_calls_that_ask_for_lengths_wait_for_the_device(tmp_path):
     out = run_program(tmp_path, WAITS)
     assert out.splitlines()[-1] == "0 failures", out
+
+
+FETCH = r"""
+// Results are read behind the whole device, not behind the object's own calls: a graph that the caller captured runs them again on any
+// stream, without the library knowing.  It may also write results without the mirror in host memory, so an object with captured calls is
+// read by copies.
+int main() {
+    Small s;
+    std::vector<float> p(s.BATCH * s.GAMMA), h(s.BATCH * (s.GAMMA + 1) * s.D);
+    auto fetch = [&](bool small, bool copies, const char* what) {
+        calls.clear();
+        const int rc = small ? sj_debug_fetch(s.kv, SJ_DBG_P_AT_DRAFT, p.data(), p.size() * 4) : sj_debug_fetch(s.kv, SJ_DBG_HIDDEN, h.data(), h.size() * 4);
+        const int wait = first("hipDeviceSynchronize"), copy = first("hipMemcpy");
+        CHECK(!rc && wait >= 0 && (copies ? copy > wait : copy < 0), "%s: rc %d, wait %d, copy %d", what, rc, wait, copy);
+    };
+    s.score(3, nullptr);
+    s.head(s.GAMMA, nullptr);
+    fetch(false, true, "hidden states");
+    fetch(true, true, "first fetch");
+    s.head(s.GAMMA, nullptr);
+    fetch(true, false, "mirrored");
+    fetch(false, true, "hidden states of a mirrored call");
+    s.head(s.GAMMA, CAPTURING);
+    fetch(true, true, "a captured call");
+    s.head(s.GAMMA, nullptr);
+    fetch(true, true, "a later call of an object with captured calls");
+    std::printf("%d failures\n", failures);
+}
+"""
+
+
+def test_fetches_wait_for_the_device_and_see_captured_calls(tmp_path):
+    out = run_program(tmp_path, FETCH)
+    assert out.splitlines()[-1] == "0 failures", out
