@@ -802,6 +802,12 @@ static int check_room(sj_kv* kv, int lo, int hi, int rows) {
     return SJ_OK;
 }
 
+// The host's bound counts a call's rows before its first launch: a call that fails part of the way has moved the lengths on the device, and
+// one counted too many only costs the next step a look at them.
+static void raise_bound(sj_kv* kv, int lo, int hi, int rows) {
+    for (int b = lo; b < hi; ++b) kv->len_upper[b] += rows;
+}
+
 extern "C" int sj_kv_state(const sj_kv* kv, int32_t* len_host, int32_t* pending_host) {
     if (!kv) return fail(SJ_EINVAL, "kv is null");
     HIPCHK(hipDeviceSynchronize());
@@ -1676,9 +1682,9 @@ extern "C" int sj_verify_step(sj_model* m, sj_kv* kv, int32_t gamma, const int32
     p.accepted_len = accepted_len; p.next_token = next_token;
     hipStream_t st = (hipStream_t)stream;
     set_mirror(kv, st, p);
+    raise_bound(kv, 0, kv->batch, gamma + 1);
     rc = dispatch_step(m, kv, gamma, p, st, false, nullptr);
     if (rc) return rc;
-    for (int b = 0; b < kv->batch; ++b) kv->len_upper[b] += gamma + 1;
     kv->mirrored = p.mirror != nullptr;
     kv->last_gamma = gamma;
     kv->last_rows = kv->batch * (gamma + 1);
@@ -1717,6 +1723,7 @@ extern "C" int sj_draft_block(sj_model* m, sj_kv* kv, int32_t gamma, const float
     hipStream_t st = (hipStream_t)stream;
     int rc = check_room(kv, 0, kv->batch, need);
     if (rc) return rc;
+    raise_bound(kv, 0, kv->batch, need);
     StepParams p{};
     p.nseq = kv->batch; p.seq_base = 0; p.rps = 1; p.gamma = 0; p.tok_mode = 0; p.mode = kv->mode; p.topk = kv->topk;
     p.theta = 0.5f;
@@ -1728,7 +1735,6 @@ extern "C" int sj_draft_block(sj_model* m, sj_kv* kv, int32_t gamma, const float
     else if (kv->planes == 3) rc = draft_block_impl<bf16_t, 3>(m, kv, gamma, feed_last != 0, p, st);
     else rc = draft_block_impl<bf16_t, 2>(m, kv, gamma, feed_last != 0, p, st);
     if (rc) return rc;
-    for (int b = 0; b < kv->batch; ++b) kv->len_upper[b] += need;
     kv->last_gamma = 0;
     kv->last_rows = kv->batch;
     return SJ_OK;
@@ -1953,12 +1959,12 @@ extern "C" int sj_prefill(sj_model* m, sj_kv* kv, int32_t seq, const int32_t* to
     hipStream_t st = (hipStream_t)stream;
     int rc = check_room(kv, seq, seq + 1, n);
     if (rc) return rc;
+    raise_bound(kv, seq, seq + 1, n);
     if (m->cfg.dtype == SJ_DTYPE_FP32) rc = prefill_impl<float, 1>(m, kv, seq, tokens_host, n, st);
     else if (kv->planes == 1) rc = prefill_impl<bf16_t, 1>(m, kv, seq, tokens_host, n, st);
     else if (kv->planes == 3) rc = prefill_impl<bf16_t, 3>(m, kv, seq, tokens_host, n, st);
     else rc = prefill_impl<bf16_t, 2>(m, kv, seq, tokens_host, n, st);
     if (rc) return rc;
-    kv->len_upper[seq] += n;
     kv->last_gamma = 0;
     kv->last_rows = std::min(n, std::min(kv->max_rows, m->cfg.max_gamma + 1));
     return SJ_OK;

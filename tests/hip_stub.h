@@ -1,6 +1,6 @@
 // A HIP runtime without a GPU for tests of the library's host side: a program that includes this file and links libsj.so defines the
-// HIP calls itself, so the library's resolve to these.  Device memory is host memory, kernels do nothing, graphs are empty; every call is
-// written to `calls` by name (launches by the kernel's name), and a call can be told to fail.
+// HIP calls itself, so the library's resolve to these.  Device memory is host memory, kernels do nothing (sj_kv_set_state's sets the
+// length), graphs are empty; every call is written to `calls` by name (launches by the kernel's name), and a call can be told to fail.
 #include "sj.h"
 
 #include <cstdint>
@@ -40,7 +40,11 @@ void __hipRegisterFunction(void**, const void* host, char*, const char* name, un
 void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
 int __hipPushCallConfiguration(Dim3, Dim3, size_t, void*) { return 0; }
 int __hipPopCallConfiguration(Dim3*, Dim3*, size_t*, void**) { return 0; }
-int hipLaunchKernel(const void* f, Dim3, Dim3, void**, size_t, void*) { return seen("launch " + kernel_names()[f]); }
+int hipLaunchKernel(const void* f, Dim3, Dim3, void** args, size_t, void*) {
+    const std::string& name = kernel_names()[f];
+    if (name.find("set_state") != std::string::npos) (*(int32_t**)args[0])[*(int32_t*)args[2]] = *(int32_t*)args[3];      // lengths
+    return seen("launch " + name);
+}
 int hipGetLastError() { const int e = last_error; last_error = 0; return e; }
 const char* hipGetErrorString(int) { return "told to fail"; }
 int hipGetDevice(int* d) { *d = 0; return 0; }

@@ -61,3 +61,30 @@ int main() {
 def test_fetches_wait_for_the_device_and_see_captured_calls(tmp_path):
     out = run_program(tmp_path, FETCH)
     assert out.splitlines()[-1] == "0 failures", out
+
+
+BOUND = r"""
+// A call that fails after some of its launches has moved the lengths on the device.  Verification steps go by the host's upper bound: it
+// counts what was queued, so the next step that the bound refuses asks the device instead of writing past the capacity.
+int main() {
+    struct { const char* call; int nth; const char* what; } fails[] = {
+        {"hipGraphInstantiate", 2, "draft block, last token's layers"}, {"hipGraphLaunch", 3, "draft block, third step"},
+        {"hipStreamSynchronize", 1, "prompt, after its first chunk"}, {"hipGraphLaunch", 1, "verification step"}};
+    for (int i = 0; i < 4; ++i) {
+        Small s;
+        s.lengths(57);
+        fail_next(fails[i].call, fails[i].nth);
+        const int rc = i == 2 ? s.prefill(0, 7, nullptr) : i == 3 ? s.step(s.GAMMA, nullptr) : s.draft(4, 1, nullptr);
+        CHECK(rc == SJ_EHIP, "%s: rc %d", fails[i].what, rc);
+        calls.clear();
+        s.step(s.GAMMA, nullptr);                     // 57 + 5 positions fit, 57 + what was queued + 5 do not
+        CHECK(first("hipMemcpy") >= 0 && first("hipMemcpy") < first("launch"), "%s: the next step did not ask for the lengths", fails[i].what);
+    }
+    std::printf("%d failures\n", failures);
+}
+"""
+
+
+def test_the_bound_counts_what_a_failed_call_queued(tmp_path):
+    out = run_program(tmp_path, BOUND)
+    assert out.splitlines()[-1] == "0 failures", out
