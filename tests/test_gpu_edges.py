@@ -305,18 +305,26 @@ def test_results_are_the_same_by_copy_and_mirror_on_every_stream():
             for o in outs[1:]:
                 for k in outs[0]:
                     assert np.array_equal(outs[0][k], o[k]), (gamma, k)
-        # a draft block and a scoring pass behind a rewind that is still queued on another stream
+        # a draft block and a scoring pass behind a rewind that is still queued on another stream, after work of some milliseconds
         u = torch.rand(3, 3, device="cuda")
         tok = torch.zeros(3, 4, dtype=torch.int32, device="cuda")
+        big = torch.rand(4096, 4096, device="cuda")
         torch.cuda.synchronize()
+
+        def rewind(st, to):
+            with torch.cuda.stream(st):
+                for _ in range(8):
+                    torch.mm(big, big)
+            sj.sj_kv_rewind(gpu.kv, to, pending, st)
 
         def run(st_rewind, st):
             t, q = torch.zeros(3, 3, dtype=torch.int32, device="cuda"), torch.zeros(3, 3, shape.vocab, device="cuda")
             lp = torch.zeros(3, 4, device="cuda")
             torch.cuda.synchronize()
-            sj.sj_kv_rewind(gpu.kv, [20, 30, 2], pending, st_rewind)
+            rewind(st_rewind, [20, 30, 2])
             sj.sj_score_block(gpu.model, gpu.kv, 4, tok, tok, lp, 0, None, st)
-            sj.sj_kv_rewind(gpu.kv, [22, 31, 4], pending, st_rewind)
+            st.synchronize()                             # a rewind waits for nobody
+            rewind(st_rewind, [22, 31, 4])
             sj.sj_draft_block(gpu.model, gpu.kv, 3, u, True, t, q, st)
             torch.cuda.synchronize()
             with pytest.raises(sj.SJError):              # not produced by the last call
