@@ -39,9 +39,12 @@ def test_fp32_head_of_many_rows_is_as_exact_as_of_few(d):
         assert many <= 1.1 * few
 
 
-def test_three_plane_prompt_chunk_is_as_exact_as_blocks():
+def test_three_plane_prompt_chunk_is_as_exact_as_blocks(monkeypatch):
     """The first layer's K / V rows of a prompt are bf16 roundings of one product: the share that rounds to the other neighbour of the
-    64-bit value measures the product's error.  A chunk of 600 rows against blocks of 20 rows through the few-row kernels."""
+    64-bit value measures the product's error.  A chunk of 560 rows against blocks of 20 rows through the few-row kernels, in the shapes
+    of the rule: there 304 against 281 elements, where the start-up measurement sometimes takes 3 n-tiles, 8 waves, 4 K-slices for the
+    blocks, whose 32 chains of a product are half as long (227)."""
+    monkeypatch.setenv("SJ_TUNE", "0")
     from oracle import selfjudge_oracle as orc
     from tests import helpers
     shape = synth.ModelShape("precision_planes", "bf16", 1, 4096, 8, 8, 128, 256, 512, 10000.0, batch=1, gamma=19)
