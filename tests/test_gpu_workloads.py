@@ -116,25 +116,41 @@ def _llama70b(force_rounding, scale):
         out, ref, stats = _compare_step(shape, gpu, cfg, W, caches, draft, 0.5, "70B", force_rounding=force_rounding, scale=scale)
         say("70B %s: logits max err %.3e worst err/bound %.3f" % ("replay on the device's stored rows" if force_rounding else
                                                                    "against the pure oracle", *stats["logits"]))
-        return stats
+        # the same step with the operands exact
+        sj.sj_set_operand_planes(gpu.kv, 3)
+        sj.sj_kv_rewind(gpu.kv, lens, synth.make_pending(shape, 0), torch.cuda.current_stream())
+        return stats, out, ref, draft, gpu.step(draft, 0.5, shape.gamma)
     finally:
         gpu.close()
 
 
-def test_llama70b_batch4():
-    """70B shape, batch 4, gamma 5, cache 2048, against the PURE oracle.  Decisions and emitted tokens must match;
+def test_llama70b_batch4(monkeypatch):
+    """70B shape, batch 4, gamma 5, cache 2048, against the PURE oracle.  Bits and accepted lengths must match;
     hidden states and judge scores meet the bf16 bar.  The logits of this 80-layer random decoder sit AT the bar
-    (measured 1.00 of it with two operand planes, 1.33 with three): a stored K / V element is the bf16 rounding of a
+    (measured 1.03 of it with two operand planes, 1.33 with three): a stored K / V element is the bf16 rounding of a
     value the two sides know to ~1e-6, near a rounding boundary they store neighbouring numbers, and 80 random layers
     amplify those one-ulp differences - it does not shrink with a more exact operand.  Asserted at twice the bar,
     with the measured figure printed; the replay below shows the same step inside 0.05 of the bar once both sides
-    store the same rows."""
-    stats = _llama70b(force_rounding=False, scale=2.0)
-    # Which of the summation orders the start-up measurement picks moves these logits by up to the bar tau(l) = 1e-2 + 2e-2 |l|, and with
-    # them a token whose uniform falls next to an edge of its cell: such a token has to lie in the oracle's cell widened by
-    # (e^(2 tau) - 1) min(F, 1 - F) (tests/gpu_common.py; one in ten runs has one of the four there).  Bits and lengths stay exact.
+    store the same rows.
+
+    Emitted tokens must match, too, wherever the oracle's own draw decides them.  The first sequence's uniform lies
+    3.5e-7 above the lower edge of its token's cell, which is 6.5e-7 wide, and the device's CDF is off by 2e-8 .. 7e-7
+    there: 6.6e-7 with the shapes of the rule (the draw gives the token before), 2e-8 and 2.6e-7 with two choices of
+    the start-up measurement (the oracle's token).  So the shapes are fixed here, and a token may be the
+    oracle's neighbour where the uniform is closer to the edge between the two than 2e-6: three times that error.
+    With three operand planes all four tokens are the oracle's."""
+    monkeypatch.setenv("SJ_TUNE", "0")
+    stats, out, ref, draft, exact = _llama70b(force_rounding=False, scale=2.0)
     d = stats["decisions"]
-    assert d["unexcused"] == 0 and d["bit_excused"] == 0 and d["len_excused"] == 0 and d["tokens_equal"] + d["token_excused"] == d["tokens"]
+    assert d["unexcused"] == 0 and d["bit_excused"] == 0 and d["len_excused"] == 0 and d["token_excused"] <= 1
+    for b, r in enumerate(ref):
+        n, k_dev, k_ref = int(out["accepted_len"][b]), int(out["next_token"][b]), int(r["next_token"])
+        w = r["p"][n] if n == draft["tokens"].shape[1] else np.maximum(0.0, r["p"][n] - np.asarray(draft["probs"][b, n], np.float64))
+        edge = w[:max(k_dev, k_ref)].sum() / w.sum()                 # between the two, if they are neighbours
+        gap = abs(float(draft["uniforms"][b, -1]) - edge)
+        say(f"70B token {b}: {k_dev}, oracle {k_ref}, uniform {gap:.2e} from the lower edge")
+        assert k_dev == k_ref or (abs(k_dev - k_ref) == 1 and gap < 2e-6), (b, k_dev, k_ref, gap)
+        assert int(exact["accepted_len"][b]) == r["accepted_len"] and int(exact["next_token"][b]) == k_ref, (b, exact["next_token"][b], k_ref)
 
 
 @pytest.mark.skipif(os.environ.get("SJ_RUN_70B_REPLAY") != "1",
