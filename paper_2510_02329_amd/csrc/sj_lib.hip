@@ -112,7 +112,7 @@ struct sj_kv : Forward {       // the inherited buffers serve the blocks of up t
     int chunk_keys = 64, nchunk_max = 1, nslab = 0, slab_len = 0;
     GemmPlan plan_qkv[2], plan_o[2], plan_d[2];   // [0]: few-row kernel (at most 32 rows), [1]: more
     GemmPlan plan_gu;                             // gate / up projection with few rows (no K-slices)
-    GemmPlan plan_lm{8, 4, 1, 2};                 // LM head with few rows: nt in {4, 8}, waves in {4, 8}
+    GemmPlan plan_lm{8, 4, 1, 2};                 // LM head with few rows
     int mode = SJ_MODE_TWO_STAGE;
     int ring_rows = RING_PACK_ROWS;       // the rules take the LDS-ring kernel up to this many rows
     int planes = 2;            // bf16 planes of the activation operand (fp32 storage: always 1)
@@ -331,7 +331,7 @@ static void rule_plans(sj_kv* kv) {
         kv->plan_o[i] = plan_partial(d / 16, Nq / kstep, i == 0);
         kv->plan_d[i] = plan_partial(d / 16, F / kstep, i == 0);
     }
-    kv->plan_gu = rule_gate_up(2 * F / 16);
+    kv->plan_gu = rule_gate_up(2 * F / 16, kv->planes);
     kv->plan_lm = rule_logits(c.vocab / 16);
     // at most 8 rows with two bf16 planes: the LDS-ring kernel where a shape of it fits (3 - 8 % faster on the
     // 8B-shaped projections at 6 rows; the start-up measurement may still prefer another shape)
@@ -623,20 +623,25 @@ extern "C" int sj_kernel_class_shape(const sj_kv* kv, int32_t kernel_class, int3
                  row_tiles(planes, rows) * 16, p ? rows_split(p->split, N / 16, K / kstep, rows, planes) : 1);
         return SJ_OK;
     }
-    GemmPlan p = kernel_class == 1 ? kv->plan_qkv[0] : kernel_class == 2 ? kv->plan_o[0] : kernel_class == 3 ? kv->plan_gu
-                 : kernel_class == 4 ? kv->plan_d[0] : kv->plan_lm;
-    if (kernel_class == 2 || kernel_class == 4) {
-        const sj_config& c = kv->m->cfg;
-        const GemmPlan r = resid_plan(c.d_model, kernel_class == 2 ? c.n_q_heads * c.head_dim : c.d_ffn, c.dtype == SJ_DTYPE_FP32 ? 16 : 32, rows,
-                                      c.dtype == SJ_DTYPE_FP32 ? 1 : kv->planes, c.dtype == SJ_DTYPE_BF16, kv->ring_rows);
-        if (r.nt) p = r;
+    // what Runner launches
+    const sj_config& c = kv->m->cfg;
+    const bool bf16 = c.dtype == SJ_DTYPE_BF16;
+    const int kstep = bf16 ? 32 : 16, planes = bf16 ? kv->planes : 1, d = c.d_model, Nq = c.n_q_heads * c.head_dim;
+    auto partial = [&](const GemmPlan& q, int N, int K) { return resolve_partial(q, N / 16, K / kstep, rows, planes, bf16); };
+    GemmPlan p;
+    switch (kernel_class) {
+        case 1: p = partial(kv->plan_qkv[0], Nq + 2 * c.n_kv_heads * c.head_dim, d); break;
+        case 3: p = resolve_gate_up(kv->plan_gu, 2 * c.d_ffn / 16, d / kstep, rows, planes, bf16); break;
+        case 5: p = resolve_logits(kv->plan_lm, c.vocab / 16, d / kstep, rows, c.n_layers ? planes : 1, bf16); break;
+        default: {
+            const int K = kernel_class == 2 ? Nq : c.d_ffn;
+            p = resid_plan(d, K, kstep, rows, planes, bf16, kv->ring_rows);
+            if (!p.nt) p = partial(kernel_class == 2 ? kv->plan_o[0] : kv->plan_d[0], d, K);
+        }
     }
-    const bool ring = p.waves == RING_WAVES && rows <= RING_ROWS && kv->planes <= 2 && kv->m->cfg.dtype == SJ_DTYPE_BF16;
-    if (ring)
+    if (p.waves == RING_WAVES)
         snprintf(buf, (size_t)buf_len, "gemm_ring: %d n-tiles per workgroup, 8 compute + 2 loader waves, %d K-slice(s), LDS ring of %d stages",
                  p.nt, p.split, p.depth);
-    else if (p.waves == RING_WAVES)
-        snprintf(buf, (size_t)buf_len, "gemm_skinny: rule shape (the LDS-ring plan does not take %d rows)", rows);
     else
         snprintf(buf, (size_t)buf_len, "gemm_skinny: %d n-tiles x %d waves per workgroup, %d K-slice(s), register ring of %d", p.nt, p.waves,
                  p.split, p.depth);
@@ -902,37 +907,27 @@ static int few_partial(const GemmPlan& p, hipStream_t st, const void* W, const v
     return fail(SJ_EINVAL, "internal: no few-row kernel for %d tiles x %d waves, %d K-slice(s), ring %d", p.nt, p.waves, p.split, p.depth);
 }
 
-// The few-row gate / up projection (SwiGLU epilogue, no K-slices) in the launch shape of a plan.
+// The few-row gate / up projection (SwiGLU epilogue, no K-slices) in exactly the launch shape of a plan (resolve_gate_up).
 template <typename T, int SPL>
 static int few_swiglu(const GemmPlan& p, hipStream_t st, const void* W, const void* X, size_t xplane, int K, int N2, int rows,
                       void* act, size_t actplane, const FewArgs& fa = FewArgs{}) {
-    if (p.waves == RING_WAVES) {
-        if constexpr (std::is_same<T, bf16_t>::value && SPL <= 2) {
-            if (ring_fits(p, N2 / 16, K / Traits<T>::KSTEP, rows, SPL, true)) {
+    constexpr bool BF16 = std::is_same<T, bf16_t>::value;
+    if (gate_up_fits(p, N2 / 16, K / Traits<T>::KSTEP, rows, SPL, BF16)) {
+        if constexpr (BF16 && SPL <= 2) {
 #define SJ_RING(NT, NSA)                                                                                            \
-    if (p.nt == NT && p.depth == NSA)                                                                               \
+    if (p.waves == RING_WAVES && p.nt == NT && p.depth == NSA)                                                      \
         return gemm_ring<T, NT, EPI_SWIGLU, SPL, NSA>(st, W, X, xplane, K, N2, rows, 1, nullptr, act, actplane, nullptr, 0.f, fa);
-                SJ_RING(7, 8) SJ_RING(8, 8) SJ_RING(4, 8) SJ_RING(2, 8) SJ_RING(7, 4) SJ_RING(8, 4) SJ_RING(4, 4)
+            SJ_RING_GATE_UP_SHAPES(SJ_RING)
 #undef SJ_RING
-            }
         }
-        GemmPlan q;
-        q.nt = (N2 / 16) % 7 == 0 ? 7 : 8; q.waves = 8; q.split = 1; q.depth = 2;
-        return few_swiglu<T, SPL>(q, st, W, X, xplane, K, N2, rows, act, actplane, fa);
-    }
 #define SJ_SHAPE(NT, WV, D)                                                                                         \
     if (p.nt == NT && p.waves == WV && p.depth == D)                                                                \
         return gemm<T, NT, EPI_SWIGLU, SPL, WV, D>(st, W, X, xplane, K, N2, rows, 1, nullptr, act, actplane, nullptr, 0.f, fa);
-    SJ_SHAPE(7, 8, 2) SJ_SHAPE(8, 8, 2) SJ_SHAPE(1, 8, 2)
-    if constexpr (SPL <= 2) {
-        SJ_SHAPE(4, 8, 2) SJ_SHAPE(4, 4, 2) SJ_SHAPE(2, 8, 2) SJ_SHAPE(2, 4, 2)
-        SJ_SHAPE(7, 8, 3) SJ_SHAPE(7, 8, 4) SJ_SHAPE(8, 8, 4)
-    }
+        SJ_FEW_GATE_UP_SHAPES(SJ_SHAPE)
+        if constexpr (SPL <= 2) { SJ_FEW_GATE_UP_SHAPES_2(SJ_SHAPE) }
 #undef SJ_SHAPE
-    GemmPlan q;
-    q.nt = (N2 / 16) % 7 == 0 ? 7 : 8; q.waves = 8; q.split = 1; q.depth = 2;
-    if (q.nt != p.nt || q.waves != p.waves || q.depth != p.depth) return few_swiglu<T, SPL>(q, st, W, X, xplane, K, N2, rows, act, actplane, fa);
-    return fail(SJ_EINVAL, "internal: no few-row gate/up kernel for %d tiles x %d waves", p.nt, p.waves);
+    }
+    return fail(SJ_EINVAL, "internal: no few-row gate/up kernel for %d tiles x %d waves, ring %d", p.nt, p.waves, p.depth);
 }
 
 template <typename T, int SPL>
@@ -955,35 +950,27 @@ static int few_resid(const GemmPlan& p, hipStream_t st, const void* W, const voi
     return fail(SJ_EINVAL, "internal: no residual kernel for %d tiles x %d waves", p.nt, p.waves);
 }
 
-// The few-row LM head (logits + per-workgroup softmax statistics: V / 16 / nt entries per row) in the launch shape of a plan.
+// The few-row LM head (logits + per-workgroup softmax statistics: V / 16 / nt entries per row) in exactly the launch shape of a plan.
 template <typename T, int SPL>
 static int few_logits(const GemmPlan& p, hipStream_t st, const void* W, const void* X, size_t xplane, int K, int V, int rows,
                       float* logits, float4* stats, float inv_temp, const FewArgs& fa = FewArgs{}) {
-    if (p.waves == RING_WAVES) {
-        if constexpr (std::is_same<T, bf16_t>::value && SPL <= 2) {
-            if (ring_fits(p, V / 16, K / Traits<T>::KSTEP, rows, SPL, true)) {
+    constexpr bool BF16 = std::is_same<T, bf16_t>::value;
+    if (logits_fits(p, V / 16, K / Traits<T>::KSTEP, rows, SPL, BF16)) {
+        if constexpr (BF16 && SPL <= 2) {
 #define SJ_RING(NT, NSA)                                                                                            \
-    if (p.nt == NT && p.depth == NSA)                                                                               \
+    if (p.waves == RING_WAVES && p.nt == NT && p.depth == NSA)                                                      \
         return gemm_ring<T, NT, EPI_LOGITS, SPL, NSA>(st, W, X, xplane, K, V, rows, 1, logits, nullptr, 0, stats, inv_temp, fa);
-                SJ_RING(8, 4) SJ_RING(8, 8) SJ_RING(4, 8)
+            SJ_RING_LOGITS_SHAPES(SJ_RING)
 #undef SJ_RING
-            }
         }
-        // the statistics are laid out for p.nt tiles per workgroup: only a kernel with the same count may stand in
-        if (p.nt == 8) return few_logits<T, SPL>(GemmPlan{8, 4, 1, 2}, st, W, X, xplane, K, V, rows, logits, stats, inv_temp, fa);
-        if (p.nt == 4) {
-            if constexpr (SPL <= 2) return few_logits<T, SPL>(GemmPlan{4, 8, 1, 2}, st, W, X, xplane, K, V, rows, logits, stats, inv_temp, fa);
-        }
-        return fail(SJ_EINVAL, "internal: no few-row LM-head kernel for %d tiles per workgroup", p.nt);
-    }
-#define SJ_SHAPE(NT, WV)                                                                                            \
-    if (p.nt == NT && p.waves == WV)                                                                                \
-        return gemm<T, NT, EPI_LOGITS, SPL, WV>(st, W, X, xplane, K, V, rows, 1, logits, nullptr, 0, stats, inv_temp, fa);
-    SJ_SHAPE(8, 4) SJ_SHAPE(2, 8)
-    if constexpr (SPL <= 2) { SJ_SHAPE(8, 8) SJ_SHAPE(4, 8) SJ_SHAPE(4, 4) }
+#define SJ_SHAPE(NT, WV, D)                                                                                         \
+    if (p.nt == NT && p.waves == WV && p.depth == D)                                                                \
+        return gemm<T, NT, EPI_LOGITS, SPL, WV, D>(st, W, X, xplane, K, V, rows, 1, logits, nullptr, 0, stats, inv_temp, fa);
+        SJ_FEW_LOGITS_SHAPES(SJ_SHAPE)
+        if constexpr (SPL <= 2) { SJ_FEW_LOGITS_SHAPES_2(SJ_SHAPE) }
 #undef SJ_SHAPE
-    if (p.nt == 8 && p.waves != 4) return few_logits<T, SPL>(GemmPlan{8, 4, 1, 2}, st, W, X, xplane, K, V, rows, logits, stats, inv_temp, fa);
-    return fail(SJ_EINVAL, "internal: no few-row LM-head kernel for %d tiles x %d waves", p.nt, p.waves);
+    }
+    return fail(SJ_EINVAL, "internal: no few-row LM-head kernel for %d tiles x %d waves, ring %d", p.nt, p.waves, p.depth);
 }
 
 // Picks between the rule's plan and measured candidates.  time_plan(plan, us) times one plan.  The first timings of
@@ -1073,25 +1060,22 @@ static int tune_gate_up(sj_kv* kv, int rows, hipEvent_t e0, hipEvent_t e1) {
         us = (double)ms * 1e3 / nl;
         return SJ_OK;
     };
-    static const int shapes[][3] = {{7, 8, 2}, {8, 8, 2}, {4, 8, 2}, {4, 4, 2}, {2, 8, 2}, {2, 4, 2}, {1, 8, 2}, {7, 8, 3}, {7, 8, 4}, {8, 8, 4}};
+    const int ksteps = d / Traits<T>::KSTEP;
+    const bool one = rule_gate_up(ntiles, SPL).nt == 1;          // small matrices: the rule's shape, where it starts from a ring
     std::vector<GemmPlan> cands;
-    for (int i = 0; i < (int)(sizeof(shapes) / sizeof(shapes[0])); ++i) {
-        if (SPL > 2 && i >= 2) break;
-        const int nt = shapes[i][0], wv = shapes[i][1];
-        const bool small = nt <= rule_gate_up(ntiles).nt;        // the rule's shape of a small matrix, where it starts from a ring
-        if (ntiles % nt || (!small && ((d / Traits<T>::KSTEP) / wv < 4 || ntiles / nt < 128))) continue;
-        GemmPlan p;
-        p.nt = nt; p.waves = wv; p.split = 1; p.depth = shapes[i][2];
-        cands.push_back(p);
-    }
-    for (int nt : {7, 8, 4, 2})
-        for (int depth : {8, 4}) {
-            GemmPlan p;
-            p.nt = nt; p.waves = RING_WAVES; p.split = 1; p.depth = depth;
-            if (nt == 2 && depth == 4) continue;                 // not instantiated
-            if (!ring_fits(p, ntiles, d / Traits<T>::KSTEP, rows, SPL, std::is_same<T, bf16_t>::value) || ntiles / nt < 128) continue;
-            cands.push_back(p);
-        }
+    auto offer = [&](int nt, int waves, int depth) {
+        const GemmPlan p{nt, waves, 1, depth};
+        if (!gate_up_fits(p, ntiles, ksteps, rows, SPL, std::is_same<T, bf16_t>::value)) return;
+        const bool wide = ntiles / nt >= 128 && (waves == RING_WAVES || ksteps / waves >= 4);
+        if (one && waves != RING_WAVES ? nt == 1 : wide) cands.push_back(p);
+    };
+#define SJ_OFFER(NT, WV, D) offer(NT, WV, D);
+    SJ_FEW_GATE_UP_SHAPES(SJ_OFFER)
+    SJ_FEW_GATE_UP_SHAPES_2(SJ_OFFER)
+#undef SJ_OFFER
+#define SJ_OFFER(NT, NSA) offer(NT, RING_WAVES, NSA);
+    SJ_RING_GATE_UP_SHAPES(SJ_OFFER)
+#undef SJ_OFFER
     return pick_plan(kv->plan_gu, cands, time_plan);
 }
 
@@ -1118,22 +1102,22 @@ static int tune_lm_head(sj_kv* kv, int rows, hipEvent_t e0, hipEvent_t e1) {
         us = (double)ms * 1e3 / 3;
         return SJ_OK;
     };
-    static const int shapes[][2] = {{8, 4}, {8, 8}, {4, 8}, {4, 4}};
-    std::vector<GemmPlan> cands{rule_logits(V / 16)};
-    for (int i = 0; i < (int)(sizeof(shapes) / sizeof(shapes[0])); ++i) {
-        if (SPL > 2 || cands[0].nt == 2) break;         // (a small matrix: the rule's shape, where it starts from a ring)
-        const int nt = shapes[i][0], wv = shapes[i][1];
-        if ((V / 16) % nt || (d / Traits<T>::KSTEP) / wv < 4) continue;
-        GemmPlan p;
-        p.nt = nt; p.waves = wv; p.split = 1; p.depth = 2;
-        cands.push_back(p);
-    }
-    static const int ring_shapes[][2] = {{8, 4}, {8, 8}, {4, 8}};
-    for (const auto& rs : ring_shapes) {
-        GemmPlan p;
-        p.nt = rs[0]; p.waves = RING_WAVES; p.split = 1; p.depth = rs[1];
-        if (ring_fits(p, V / 16, d / Traits<T>::KSTEP, rows, SPL, std::is_same<T, bf16_t>::value)) cands.push_back(p);
-    }
+    const int ntiles = V / 16, ksteps = d / Traits<T>::KSTEP;
+    const GemmPlan rule = rule_logits(ntiles);
+    std::vector<GemmPlan> cands{rule};
+    auto offer = [&](int nt, int waves, int depth) {
+        const GemmPlan p{nt, waves, 1, depth};
+        if (!logits_fits(p, ntiles, ksteps, rows, SPL, std::is_same<T, bf16_t>::value)) return;
+        // (a small matrix: the rule's shape, where it starts from a ring; a large one: none of the small ones')
+        if (waves == RING_WAVES || (rule.nt != 2 && nt != 2 && ksteps / waves >= 4)) cands.push_back(p);
+    };
+#define SJ_OFFER(NT, WV, D) offer(NT, WV, D);
+    SJ_FEW_LOGITS_SHAPES(SJ_OFFER)
+    if (SPL <= 2) { SJ_FEW_LOGITS_SHAPES_2(SJ_OFFER) }
+#undef SJ_OFFER
+#define SJ_OFFER(NT, NSA) offer(NT, RING_WAVES, NSA);
+    SJ_RING_LOGITS_SHAPES(SJ_OFFER)
+#undef SJ_OFFER
     return pick_plan(kv->plan_lm, cands, time_plan);
 }
 
@@ -1323,12 +1307,12 @@ struct Runner {
         }
         return SJ_OK;
     }
-    // gate / up projection with the SwiGLU epilogue: 7 n-tiles per workgroup when that gives a whole
-    // number of workgroups per CU (2F/16 = 1792 tiles -> 256 workgroups), else 8
+    // gate / up projection with the SwiGLU epilogue; few rows: the plan's launch shape, or the rule's where that does not take them
     int gate_up(const void* W, bool unscaled = false) {
         const ModelDims& md = m->md;
         if (R > FEW_ROWS) return gemm_rows<T, EPI_SWIGLU, SPL>(st, W, w->xn, plane(md.d), md.d, 2 * md.F, R, 1, nullptr, w->act, plane(md.F), nullptr, 0.f);
-        return few_swiglu<T, SPL>(kv->plan_gu, st, W, w->xn, plane(md.d), md.d, 2 * md.F, R, w->act, plane(md.F), few_args(unscaled));
+        const GemmPlan p = resolve_gate_up(kv->plan_gu, 2 * md.F / 16, md.d / Traits<T>::KSTEP, R, SPL, std::is_same<T, bf16_t>::value);
+        return few_swiglu<T, SPL>(p, st, W, w->xn, plane(md.d), md.d, 2 * md.F, R, w->act, plane(md.F), few_args(unscaled));
     }
 
     // rotary + cache append + attention of one layer from the QKV partials in w->part
@@ -1453,10 +1437,11 @@ struct Runner {
                 : gemm_rows<T, EPI_LOGITS, SPL>(st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, 1, kv->logits, nullptr, 0, kv->stats, md.inv_temp);
             nblk = md.V / 16 / ROWS_NT;
         } else {
+            const GemmPlan p = resolve_logits(kv->plan_lm, md.V / 16, md.d / Traits<T>::KSTEP, R, exact_operand ? 1 : SPL, std::is_same<T, bf16_t>::value);
             rc = exact_operand
-                ? few_logits<T, 1>(kv->plan_lm, st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, kv->logits, kv->stats, md.inv_temp)
-                : few_logits<T, SPL>(kv->plan_lm, st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, kv->logits, kv->stats, md.inv_temp, few_args(false));
-            nblk = md.V / 16 / kv->plan_lm.nt;
+                ? few_logits<T, 1>(p, st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, kv->logits, kv->stats, md.inv_temp)
+                : few_logits<T, SPL>(p, st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, kv->logits, kv->stats, md.inv_temp, few_args(false));
+            nblk = md.V / 16 / p.nt;
         }
         return rc;
     }

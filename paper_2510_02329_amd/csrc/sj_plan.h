@@ -60,6 +60,35 @@ inline bool partial_fits(const GemmPlan& p, int ntiles, int ksteps, int rows, in
     return false;
 }
 
+// The same for the gate / up projection and the LM head with few rows, which have no K-slices: (n-tiles, waves, ring depth) of the
+// register-ring kernel (LM head: depth 2), (n-tiles, ring depth) of the LDS-ring kernel.
+#define SJ_FEW_GATE_UP_SHAPES(X) X(7, 8, 2) X(8, 8, 2) X(1, 8, 2)
+#define SJ_FEW_GATE_UP_SHAPES_2(X) X(4, 8, 2) X(4, 4, 2) X(2, 8, 2) X(2, 4, 2) X(7, 8, 3) X(7, 8, 4) X(8, 8, 4)
+#define SJ_RING_GATE_UP_SHAPES(X) X(7, 8) X(8, 8) X(4, 8) X(2, 8) X(7, 4) X(8, 4) X(4, 4)
+#define SJ_FEW_LOGITS_SHAPES(X) X(8, 4, 2) X(2, 8, 2)
+#define SJ_FEW_LOGITS_SHAPES_2(X) X(8, 8, 2) X(4, 8, 2) X(4, 4, 2)
+#define SJ_RING_LOGITS_SHAPES(X) X(8, 4) X(8, 8) X(4, 8)
+
+// Is there a kernel for exactly this launch?
+#define SJ_IS_RING(NT, NSA) if (p.nt == NT && p.depth == NSA) return ring_fits(p, ntiles, ksteps, rows, planes, bf16);
+#define SJ_IS_FEW(NT, WV, D) if (p.nt == NT && p.waves == WV && p.depth == D) return true;
+inline bool gate_up_fits(const GemmPlan& p, int ntiles, int ksteps, int rows, int planes, bool bf16) {
+    if (p.split != 1 || p.nt < 1 || ntiles % p.nt) return false;
+    if (p.waves == RING_WAVES) { SJ_RING_GATE_UP_SHAPES(SJ_IS_RING) return false; }
+    SJ_FEW_GATE_UP_SHAPES(SJ_IS_FEW)
+    if (planes <= 2) { SJ_FEW_GATE_UP_SHAPES_2(SJ_IS_FEW) }
+    return false;
+}
+inline bool logits_fits(const GemmPlan& p, int ntiles, int ksteps, int rows, int planes, bool bf16) {
+    if (p.split != 1 || p.nt < 1 || ntiles % p.nt) return false;
+    if (p.waves == RING_WAVES) { SJ_RING_LOGITS_SHAPES(SJ_IS_RING) return false; }
+    SJ_FEW_LOGITS_SHAPES(SJ_IS_FEW)
+    if (planes <= 2) { SJ_FEW_LOGITS_SHAPES_2(SJ_IS_FEW) }
+    return false;
+}
+#undef SJ_IS_RING
+#undef SJ_IS_FEW
+
 // Rule shape of a split-K projection on the LDS-ring kernel (rows <= 8, two planes: the measured case), or waves = 0
 // when no shape fits.  Fewest idle workgroup slots first (256 CUs, one round); among those at least two n-tiles per
 // workgroup (with one, the operand is as much traffic as the weights) and two K-slices, else four, else one, else
@@ -89,16 +118,16 @@ inline GemmPlan ring_rule_partial(int ntiles, int ksteps) {
 // d 256, 2 layers, 5 rows: gate / up 7.8 -> 4.6 us, LM head 7.3 -> 5.4, down 7.9 -> 4.9; whole step 125 -> 102 (the draw's one launch
 // among it); bf16, d 512: step of 4 layers, 30 rows 314 -> 224, draft block of 8 layers, one row 1663 -> 1440.
 constexpr int SMALL_TILES = 128;
-inline GemmPlan rule_gate_up(int ntiles) {
+inline GemmPlan rule_gate_up(int ntiles, int planes) {
     GemmPlan p;
     p.waves = 8; p.split = 1; p.depth = 2;
     p.nt = 1;
     if (ntiles < 2 * SMALL_TILES) return p;
     // the n-tiles that leave the fewest workgroup slots of a round of the chip empty, the most of those (8B shape, 1792 tiles: 7; 1B, 1024
-    // tiles: 4 - with 8, on half of the CUs, a decode's gate / up takes 17.0 us instead of 15.4)
+    // tiles: 4 - with 8, on half of the CUs, a decode's gate / up takes 17.0 us instead of 15.4; three planes have no kernel of 4)
     double best = 1e30;
     for (int nt : {8, 7, 4}) {
-        if (ntiles % nt) continue;
+        if (ntiles % nt || (nt == 4 && planes > 2)) continue;
         const int wgs = ntiles / nt;
         const double waste = (double)((wgs + 255) / 256 * 256) / wgs;
         if (waste < best - 1e-9) { best = waste; p.nt = nt; }
@@ -141,6 +170,15 @@ inline GemmPlan plan_partial(int ntiles, int ksteps, bool one_row_tile) {
 // chunk can have more rows than the plan was made for), the register-ring kernel's rule shape, which is always instantiated.
 inline GemmPlan resolve_partial(const GemmPlan& p, int ntiles, int ksteps, int rows, int planes, bool bf16) {
     return partial_fits(p, ntiles, ksteps, rows, planes, bf16) ? p : plan_partial(ntiles, ksteps, true);
+}
+
+// The same for the gate / up projection and the LM head.  (The LM head's statistics are laid out for the n-tiles of the launch: whoever
+// reads them goes by what this returned.)
+inline GemmPlan resolve_gate_up(const GemmPlan& p, int ntiles, int ksteps, int rows, int planes, bool bf16) {
+    return gate_up_fits(p, ntiles, ksteps, rows, planes, bf16) ? p : rule_gate_up(ntiles, planes);
+}
+inline GemmPlan resolve_logits(const GemmPlan& p, int ntiles, int ksteps, int rows, int planes, bool bf16) {
+    return logits_fits(p, ntiles, ksteps, rows, planes, bf16) ? p : rule_logits(ntiles);
 }
 
 // Shapes that the start-up measurement tries for a split-K projection with at most 32 rows.

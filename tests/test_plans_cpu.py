@@ -94,3 +94,41 @@ int main() {
 def test_large_tile_launches_hold_their_rows(tmp_path):
     out = run_program(tmp_path, TILES).splitlines()[-1]
     assert out.startswith("0 of ") and not out.startswith("0 of 0 "), out
+
+
+FEW = shapes_array() + r"""
+// what the gate / up projection and the LM head of at most 32 rows are launched as: the rule's shapes, its ring shapes, and plans that were made for
+// another row or plane count
+int main() {
+    long bad = 0, checked = 0;
+    for (const auto& s : shapes)
+        for (int vocab : {1024, 4096, 4992, 16256, 16384, 32000, 128256})
+            for (int rows = 1; rows <= 32; ++rows)
+                for (int planes = 0; planes <= 3; ++planes) {                 // 0: fp32
+                    const bool bf16 = planes > 0;
+                    const int spl = bf16 ? planes : 1, ksteps = s[0] / (bf16 ? 32 : 16), gu = 2 * s[3] / 16, lm = vocab / 16;
+                    auto see = [&](const char* what, const GemmPlan& q, int ntiles, bool fits) {
+                        ++checked;
+                        if (!fits && bad++ < 10)
+                            printf("%s: %d tiles, %d k-steps, %d rows, %d planes: {%d, %d, %d, %d}\n", what, ntiles, ksteps, rows, planes, q.nt, q.waves, q.split, q.depth);
+                    };
+                    auto gate_up = [&](const char* what, const GemmPlan& q) { see(what, q, gu, gate_up_fits(q, gu, ksteps, rows, spl, bf16)); };
+                    auto logits = [&](const char* what, const GemmPlan& q) { see(what, q, lm, logits_fits(q, lm, ksteps, rows, spl, bf16)); };
+                    gate_up("gate/up rule", rule_gate_up(gu, spl));
+                    logits("LM head rule", rule_logits(lm));
+                    for (int nt : {1, 2, 4, 7, 8})
+                        for (int waves : {4, 8, RING_WAVES})
+                            for (int depth : {2, 3, 4, 8}) {
+                                gate_up("gate/up resolved", resolve_gate_up(GemmPlan{nt, waves, 1, depth}, gu, ksteps, rows, spl, bf16));
+                                logits("LM head resolved", resolve_logits(GemmPlan{nt, waves, 1, depth}, lm, ksteps, rows, spl, bf16));
+                            }
+                }
+    printf("%ld of %ld without a kernel\n", bad, checked);
+}
+"""
+
+
+def test_every_gate_up_and_lm_head_launch_is_an_instantiated_shape(tmp_path):
+    """A shape without a kernel would run as another one: timed, and reported, under the wrong name."""
+    out = run_program(tmp_path, FEW)
+    assert out.splitlines()[-1].startswith("0 of "), out
