@@ -229,8 +229,8 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(int R, int d, float e
 // slice again and are summed through LDS in wave order (deterministic).
 // EPI_RESID closes a sub-layer without a norm launch: the workgroup holds finished output columns (no K-slices), adds them to
 // the fp32 residual stream, writes the next product's operand planes WITHOUT the 1/rms factor - (x + y) * gain - and each
-// tile's share of every row's sum of squares.  The consumer (any epilogue, `ss_in` set) sums the shares and multiplies its finished
-// sums by 1/rms: a factor of the row commutes with the product.
+// tile's share of every row's sum of squares.  The consumer (QKV or gate / up: EPI_PARTIAL or EPI_SWIGLU, at most 8 rows, `ss_in` set) sums
+// the shares and multiplies its finished sums by 1/rms: a factor of the row commutes with the product.
 enum { EPI_PARTIAL = 0, EPI_SWIGLU = 1, EPI_LOGITS = 2, EPI_RESID = 3 };
 
 struct GemmArgs {
@@ -247,7 +247,7 @@ struct GemmArgs {
     float inv_temp;     // 1/T, 0 when T = 0
     int32_t rgroups;    // many-row kernel: row groups of one launch (0 or 1: the launch is one group of R rows); with
                         // more, R is the total row count and every workgroup derives its group's rows and pointers
-    const float* ss_in; // few-row kernels: null, or [R][K / 16] shares of the rows' sums of squares: the operand lacks 1/rms
+    const float* ss_in; // EPI_PARTIAL, EPI_SWIGLU, at most 8 rows: null, or [R][K / 16] shares of the rows' sums of squares: the operand lacks 1/rms
     float eps;
     float* x;           // EPI_RESID: [R][N] residual stream, updated in place
     const void* gain;   // EPI_RESID: [N] norm gain of the next product, storage dtype

@@ -849,10 +849,18 @@ struct FewArgs {
 // blocks whose operand planes are packed: both planes of at most 8 rows in one fragment
 template <typename T, int SPL> constexpr bool packed_rows(int rows) { return std::is_same<T, bf16_t>::value && SPL == 2 && rows <= RING_PACK_ROWS; }
 
+// The kernels apply 1/rms in the products that follow a residual epilogue, for as many rows as one takes (resid_plan); elsewhere an operand
+// that lacks it would go through unscaled.
+template <int EPI> static int check_scaled(const FewArgs& fa, int rows) {
+    if (!fa.ss_in || ((EPI == EPI_PARTIAL || EPI == EPI_SWIGLU) && rows <= RING_PACK_ROWS)) return SJ_OK;
+    return fail(SJ_EINVAL, "internal: product %d of %d rows with an operand that lacks its norm", EPI, rows);
+}
+
 template <typename T, int NT, int EPI, int SPL, int WAVES, int D = 2>
 static int gemm(hipStream_t st, const void* Wt, const void* X, size_t xplane, int K, int N, int rows, int split,
                 float* out, void* act, size_t actplane, float4* stats, float inv_temp, const FewArgs& fa = FewArgs{}) {
     if (rows > FEW_ROWS) return fail(SJ_EINVAL, "internal: few-row kernel called with %d rows", rows);
+    if (const int rc = check_scaled<EPI>(fa, rows)) return rc;
     const int ngroups = N / 16 / NT;
     GemmArgs a{};
     a.Wt = Wt; a.X = X; a.xplane = xplane; a.actplane = actplane;
@@ -870,6 +878,7 @@ static int gemm(hipStream_t st, const void* Wt, const void* X, size_t xplane, in
 template <typename T, int NT, int EPI, int SPL, int NSA>
 static int gemm_ring(hipStream_t st, const void* Wt, const void* X, size_t xplane, int K, int N, int rows, int split,
                      float* out, void* act, size_t actplane, float4* stats, float inv_temp, const FewArgs& fa = FewArgs{}) {
+    if (const int rc = check_scaled<EPI>(fa, rows)) return rc;
     GemmArgs a{};
     a.Wt = Wt; a.X = X; a.xplane = xplane; a.actplane = actplane;
     a.K = K; a.N = N; a.R = rows; a.slice_rows = rows;

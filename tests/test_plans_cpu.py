@@ -114,6 +114,11 @@ int main() {
                     };
                     auto gate_up = [&](const char* what, const GemmPlan& q) { see(what, q, gu, gate_up_fits(q, gu, ksteps, rows, spl, bf16)); };
                     auto logits = [&](const char* what, const GemmPlan& q) { see(what, q, lm, logits_fits(q, lm, ksteps, rows, spl, bf16)); };
+                    // a residual epilogue leaves operands that its consumers scale, for at most 8 rows and two planes
+                    for (int K : {s[2], s[3]}) {
+                        const GemmPlan q = resid_plan(s[0], K, bf16 ? 32 : 16, rows, spl, bf16, RING_PACK_ROWS);
+                        see("residual", q, s[0] / 16, !q.nt || (rows <= 8 && planes <= 2));
+                    }
                     gate_up("gate/up rule", rule_gate_up(gu, spl));
                     logits("LM head rule", rule_logits(lm));
                     for (int nt : {1, 2, 4, 7, 8})
