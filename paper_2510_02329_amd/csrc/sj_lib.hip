@@ -515,16 +515,13 @@ extern "C" int sj_kv_create(const sj_model* m, int32_t batch, const int32_t* cap
 // 80 us, so up to eight blocks of one size (1365 rows) wait for the next object; larger ones go back at once.
 constexpr size_t MIRROR_BYTES = 16384, MIRROR_POOL = 8;
 static std::mutex mirror_pool_mu;
-static std::vector<float*> mirror_pool;
+static float* mirror_pool[MIRROR_POOL];       // plain storage: giving a block back cannot throw, and nothing is destroyed before a late caller
+static size_t mirror_pooled = 0;
 static float* mirror_take(int rows) {
     const size_t bytes = (size_t)3 * rows * 4;
     if (bytes <= MIRROR_BYTES) {
         std::lock_guard<std::mutex> lock(mirror_pool_mu);
-        if (!mirror_pool.empty()) {
-            float* h = mirror_pool.back();
-            mirror_pool.pop_back();
-            return h;
-        }
+        if (mirror_pooled) return mirror_pool[--mirror_pooled];
     }
     void* h = nullptr;
     if (hipHostMalloc(&h, std::max(bytes, MIRROR_BYTES), hipHostMallocPortable) == hipSuccess) return (float*)h;
@@ -536,7 +533,7 @@ static void mirror_give(float* h, int rows) {
     if (!h) return;
     if ((size_t)3 * rows * 4 <= MIRROR_BYTES) {
         std::lock_guard<std::mutex> lock(mirror_pool_mu);
-        if (mirror_pool.size() < MIRROR_POOL) { mirror_pool.push_back(h); return; }
+        if (mirror_pooled < MIRROR_POOL) { mirror_pool[mirror_pooled++] = h; return; }
     }
     (void)hipHostFree(h);
 }

@@ -88,3 +88,58 @@ int main() {
 def test_the_bound_counts_what_a_failed_call_queued(tmp_path):
     out = run_program(tmp_path, BOUND)
     assert out.splitlines()[-1] == "0 failures", out
+
+
+FREE = r"""
+// No call throws: giving an object's host memory back works where there is no memory left for the library's own lists.
+#include <new>
+static bool no_memory = false;
+void* operator new(size_t n) {
+    void* p = no_memory ? nullptr : std::malloc(n);
+    if (!p) throw std::bad_alloc();
+    return p;
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
+int main() {
+    Small s;
+    std::vector<float> p(s.BATCH * s.GAMMA);
+    std::vector<sj_kv*> objects;
+    const int32_t cap[s.BATCH] = {64, 64};
+    for (int i = 0; i < 12; ++i) {
+        sj_kv* kv = nullptr;
+        CHECK(!sj_kv_create(s.m, s.BATCH, cap, &kv), "create %d", i);
+        std::swap(kv, s.kv);
+        s.head(s.GAMMA, nullptr);
+        CHECK(!sj_debug_fetch(s.kv, SJ_DBG_P_AT_DRAFT, p.data(), p.size() * 4), "fetch %d", i);
+        std::swap(kv, s.kv);
+        objects.push_back(kv);
+    }
+    calls.clear();
+    calls.reserve(4096);
+    for (sj_kv* kv : objects) {
+        bool threw = false;
+        quiet = no_memory = true;
+        try { sj_kv_free(kv); } catch (...) { threw = true; }
+        quiet = no_memory = false;
+        CHECK(!threw, "sj_kv_free threw");
+    }
+    calls.clear();
+    for (int i = 0; i < 9; ++i) {                            // eight blocks wait for the next objects, the others went back
+        sj_kv* kv = nullptr;
+        CHECK(!sj_kv_create(s.m, s.BATCH, cap, &kv), "create again %d", i);
+        std::swap(kv, s.kv);
+        s.head(s.GAMMA, nullptr);
+        calls.clear();
+        sj_debug_fetch(s.kv, SJ_DBG_P_AT_DRAFT, p.data(), p.size() * 4);
+        CHECK((first("hipHostMalloc") >= 0) == (i == 8), "block %d", i);
+        std::swap(kv, s.kv);
+    }
+    std::printf("%d failures\n", failures);
+}
+"""
+
+
+def test_host_memory_goes_back_without_throwing(tmp_path):
+    out = run_program(tmp_path, FREE)
+    assert out.splitlines()[-1] == "0 failures", out
