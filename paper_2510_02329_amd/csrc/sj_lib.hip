@@ -1333,14 +1333,16 @@ struct Runner {
         const int mq = small ? 1 : std::min(mtiles, 4);
         const int qgroups = (mtiles + mq - 1) / mq;
         dim3 grid(kv->nchunk_max, md.Hkv * qgroups, nseq);
-        // at most two QKV partials: fetch them two at a time; blocks of many rows have five or six
-        const bool pb2 = parts <= 2;
+        // A batch of loads asks for that many of a value's QKV partials at once (surplus loads repeat the last one): two where there are no
+        // more; six for five or six of them in the launches of three and four query tiles, one trip instead of two (8B shape, 16 x 9 rows, five: 67.5 -> 66.2 us
+        // a layer); else four (1B shape, eight: 39.3 us, in sixes 40.8; 70B shape, three and four: the same either way).
+        const int pb = parts <= 2 ? 2 : mq >= 3 && (parts == 5 || parts == 6) ? 6 : 4;
 #define ATTN_PB(HD, MQ, PB)                                                                                            \
     attn_fused_kernel<T, HD, MQ, SPL, PB><<<grid, 256, 0, st>>>(seq_base, rps, md, w->part, parts, R, w->cs, view(), \
                                                                 layer, kv->chunk_keys, kv->nchunk_max, kv->opart, kv->tickets,  \
                                                                 (T*)w->attn_out, plane(md.Hq * md.hd), rm())
 #define ATTN(HD, MQ)                                                                                                   \
-    do { if (pb2) ATTN_PB(HD, MQ, 2); else ATTN_PB(HD, MQ, (MQ >= 3 ? 6 : 4)); } while (0)
+    do { if (pb == 2) ATTN_PB(HD, MQ, 2); else if (pb == 4) ATTN_PB(HD, MQ, 4); else ATTN_PB(HD, MQ, (MQ >= 3 ? 6 : 4)); } while (0)
         if (md.hd == 128) {
             switch (mq) { case 1: ATTN(128, 1); break; case 2: ATTN(128, 2); break; case 3: ATTN(128, 3); break; default: ATTN(128, 4); }
         } else {

@@ -85,3 +85,28 @@ def test_prompt_chunks(dtype, hq, hkv, hd, prompts, waves):
             G.close_enough(v, cache.v[0][:, L0:cache.length], dtype, "V")
     finally:
         gpu.close()
+
+
+# The single launch over long contexts in its three batch sizes: partials of every number that a block of many rows can have, three query
+# tiles to a workgroup, contexts of one and of seventeen key ranges.
+@pytest.mark.parametrize("dtype,parts", [("fp32", p) for p in range(2, 9)] + [("bf16", 5), ("bf16", 7)])
+def test_long_contexts_over_every_number_of_partials(dtype, parts):
+    shape = dataclasses.replace(SMALL, name=f"partials_{dtype}_{parts}", dtype=dtype, n_layers=1, d_model=(128 if dtype == "fp32" else 256) * parts, d_ffn=256,
+                                vocab=512, n_q_heads=12, n_kv_heads=3, head_dim=64, batch=5, gamma=8)
+    src = synth.WeightSource(shape, seed=95, norm_jitter=0.1)
+    lens, cap = [2090, 40, 0, 700, 1301], [2112] * 5
+    gpu = G.Gpu(shape, src, cap)
+    try:
+        assert f"{parts} K-slice" in sj.sj_kernel_class_shape(gpu.kv, 1, 45)
+        cfg = helpers.oracle_config(shape)
+        caches = _fill_caches(shape, gpu, cfg, lens, seed=96, capacity=cap)
+        draft = synth.make_draft(shape, seed=97)
+        out = gpu.step(draft, 0.5, 8)
+        fw = orc.block_forward(cfg, helpers.oracle_weights(src), caches, [[caches[b].pending] + draft["tokens"][b].tolist() for b in range(5)])
+        for b in range(5):
+            G.close_enough(out["hn"][b], fw[b]["hn"], dtype, f"hidden seq {b}")
+            k, v = gpu.kv_rows(b, 0, lens[b], 9)
+            G.close_enough(k, caches[b].k[0][:, lens[b]:lens[b] + 9], dtype, f"K seq {b}")
+            G.close_enough(v, caches[b].v[0][:, lens[b]:lens[b] + 9], dtype, f"V seq {b}")
+    finally:
+        gpu.close()
