@@ -911,7 +911,7 @@ __global__ __launch_bounds__(256) void resample_pick_kernel(const StepParams* __
 }
 
 // Scan and all three passes in one launch (grid: 1 x sequences) where one workgroup holds the whole vocabulary (up to 4096 entries): what
-// the passes leave for each other is the workgroup's own, and a barrier stands where a launch did (tiny model: 7.2 us, 13.2 in three
+// the passes leave for each other is the workgroup's own, and a barrier stands where a launch did (tiny model: 7.2 - 7.9 us, 13.2 in three
 // launches and a gap).
 __global__ __launch_bounds__(256) void scan_draw_kernel(const StepParams* __restrict__ sp, ResampleArgs a, const float* scores, float* p_at_d,
                                                         int32_t* bits, int32_t* nacc, const int32_t* ranks, int32_t* len, int32_t* pending) {

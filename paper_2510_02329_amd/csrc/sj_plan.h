@@ -115,7 +115,7 @@ inline GemmPlan ring_rule_partial(int ntiles, int ksteps) {
 
 // Small matrices (small models): a launch is over as soon as its longest workgroup, so every n-tile gets one of its own, its eight waves
 // share K (LM head: two n-tiles).  With the shapes of the large ones, 8 or 4 n-tiles to a workgroup on a dozen workgroups: fp32 step of
-// d 256, 2 layers, 5 rows: gate / up 7.8 -> 4.6 us, LM head 7.3 -> 5.4, down 7.9 -> 4.9; whole step 125 -> 102 (the draw's one launch
+// d 256, 2 layers, 5 rows: gate / up 7.8 -> 4.1 us, LM head 7.3 -> 4.7, down 7.9 -> 4.5; whole step 129 -> 108 - 112 (the draw's one launch
 // among it); bf16, d 512: step of 4 layers, 30 rows 314 -> 224, draft block of 8 layers, one row 1663 -> 1440.
 constexpr int SMALL_TILES = 128;
 inline GemmPlan rule_gate_up(int ntiles, int planes) {
@@ -124,7 +124,7 @@ inline GemmPlan rule_gate_up(int ntiles, int planes) {
     p.nt = 1;
     if (ntiles < 2 * SMALL_TILES) return p;
     // the n-tiles that leave the fewest workgroup slots of a round of the chip empty, the most of those (8B shape, 1792 tiles: 7; 1B, 1024
-    // tiles: 4 - with 8, on half of the CUs, a decode's gate / up takes 17.0 us instead of 15.4; three planes have no kernel of 4)
+    // tiles: 4 - with 8, on half of the CUs, a decode's gate / up takes 17.0 us instead of 14.6; three planes have no kernel of 4)
     double best = 1e30;
     for (int nt : {8, 7, 4}) {
         if (ntiles % nt || (nt == 4 && planes > 2)) continue;
