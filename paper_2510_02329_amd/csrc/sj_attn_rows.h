@@ -27,11 +27,13 @@ namespace sj {
 constexpr int ROT_POS = 16;        // positions per workgroup of the rotary kernel (= G whole query tiles)
 
 // Query fragments: qbuf[sequence][kv head][query tile][head-dim step][plane][64 lanes] of 16 bytes; ntiles = ceil(rps * G / 16).
+// q0: positions before it want no attention output (a prompt's last layer; 0: all do).  Their keys and values are appended like the others';
+// their query tiles are not formed, and the output rows begin with position q0.
 template <typename T, int HD, int SPL, int PB>
 __global__ __launch_bounds__(256) void rows_rotary_kernel(const StepParams* __restrict__ sp, ModelDims md,
                                                              const float* __restrict__ part, int nparts, int R,
                                                              const float* __restrict__ cs, KvView<T> kv, int layer,
-                                                             u32x4* __restrict__ qbuf, int ntiles) {
+                                                             u32x4* __restrict__ qbuf, int ntiles, int q0) {
     constexpr int KF = Traits<T>::KF, KSTEP = Traits<T>::KSTEP, KK = HD / KSTEP, HALF = HD / 2;
     __shared__ T vt[HD][ROT_POS + 2];
     const int rps = sp->rps, bi = blockIdx.z, b = sp->seq_base + bi, L = kv.len[b], cap = kv.cap[b];
@@ -62,7 +64,7 @@ __global__ __launch_bounds__(256) void rows_rotary_kernel(const StepParams* __re
     const int role = blockIdx.y / md.Hkv;                // 0: queries, 1: keys, 2: values
 
     // queries: item = (column pair of fragments kk, kk + KK/2; lane group; column of the workgroup's 16 * G)
-    const int nq = role != 0 ? 0 : min(md.G, ntiles - (int)blockIdx.x * md.G) * 16 * 4 * (KK / 2);
+    const int nq = role != 0 || p0 + ROT_POS <= q0 ? 0 : min(md.G, ntiles - (int)blockIdx.x * md.G) * 16 * 4 * (KK / 2);
     for (int it = tid; it < nq; it += 256) {
         const int r = it & 15, g = (it >> 4) & 3, rest = it >> 6;
         const int kk = rest % (KK / 2), tt = rest / (KK / 2);
@@ -127,28 +129,29 @@ constexpr int ROWS_WAVES = 8;
 
 template <typename T, int HD, int KW, int SPL>
 __global__ __launch_bounds__(ROWS_WAVES * 64) void rows_attn_kernel(const StepParams* __restrict__ sp, ModelDims md, KvView<T> kv, int layer,
-                                                                    const u32x4* __restrict__ qbuf, int ntiles, T* __restrict__ attn_out,
-                                                                    size_t aplane) {
+                                                                    const u32x4* __restrict__ qbuf, int ntiles, int q0, T* __restrict__ attn_out,
+                                                                    size_t aplane, int rm) {
     constexpr int KF = Traits<T>::KF, KSTEP = Traits<T>::KSTEP, NS = KF / 4, KK = HD / KSTEP, HT = HD / 16;
     static_assert(KW == 2 || KW == 4 || KW == 8, "waves per tile");
     __shared__ f32x4 mo[ROWS_WAVES][HT][64];
     __shared__ float mm[ROWS_WAVES][64], ml[ROWS_WAVES][64];
     // Workgroups are handed to the 8 XCDs (each with an L2 of its own) round robin: those of one (sequence, kv head) are 8
     // apart, so its keys and values come from HBM once.  Among them a prompt chunk's last tiles, which see the most keys, go first.
-    const int groups = (ntiles * KW + ROWS_WAVES - 1) / ROWS_WAVES, at = blockIdx.x >> 3;
+    const int tile0 = q0 * md.G / 16;                  // the first tile with a position that is wanted
+    const int groups = ((ntiles - tile0) * KW + ROWS_WAVES - 1) / ROWS_WAVES, at = blockIdx.x >> 3;
     const int pair = at / groups * 8 + (blockIdx.x & 7), grp = groups - 1 - at % groups;
     if (pair >= sp->nseq * md.Hkv) return;             // padding of the grid to whole XCD rounds (uniform)
     const int rps = sp->rps, bi = pair / md.Hkv, b = sp->seq_base + bi, L = kv.len[b], cap = kv.cap[b], kvh = pair - bi * md.Hkv;
     const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), ks = w % KW;
-    const int tile = grp * (ROWS_WAVES / KW) + w / KW;
+    const int tile = tile0 + grp * (ROWS_WAVES / KW) + w / KW;
     const bool live = tile < ntiles;                   // waves of a tile past the end only take part in the barrier
     const T* Kb = kv.K + (size_t)layer * kv.layer_stride + kv.seq_off[b] + (size_t)kvh * cap * HD;
     const T* Vb = kv.V + (size_t)layer * kv.layer_stride + kv.seq_off[b] + (size_t)kvh * HD * cap;
 
     // column of the tile: position m / G, head m % G, m = tile * 16 + r
     const int m = min(tile, ntiles - 1) * 16 + r, jrow = small_div(m, md.G), girow = m - jrow * md.G;
-    const bool rowvalid = live && jrow < rps;
+    const bool rowvalid = live && jrow < rps && jrow >= q0;
     const int jmax = min(small_div(min(tile, ntiles - 1) * 16 + 15, md.G), rps - 1);
     const int key_hi = live ? min(L + jmax + 1, cap) : 0;      // keys this tile's rows can see
     Frag qf[KK][SPL];
@@ -269,7 +272,7 @@ __global__ __launch_bounds__(ROWS_WAVES * 64) void rows_attn_kernel(const StepPa
 #pragma unroll
         for (int k = 0; k < KW; ++k) acc += mo[w0 + k][ht][lane] * f[k];
         const float v[4] = {acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
-        Traits<T>::template store_split4<SPL>(attn_out + opnd_off<T>(bi * rps + jrow, (kvh * md.G + girow) * HD + ht * 16 + 4 * g, md.Hq * HD), aplane, v);
+        Traits<T>::template store_split4<SPL>(attn_out + opnd_off<T>(bi * (rps - q0) + jrow - q0, (kvh * md.G + girow) * HD + ht * 16 + 4 * g, md.Hq * HD, rm), aplane, v);
     }
 }
 

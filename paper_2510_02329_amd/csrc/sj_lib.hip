@@ -1354,24 +1354,28 @@ struct Runner {
         return SJ_OK;
     }
 
-    // the same in two launches, for many rows (sj_attn_rows.h)
-    int rows_attention(int layer, int parts) {
+    // the same in two launches, for many rows (sj_attn_rows.h); `tail`: only its rows, the last ones of every sequence, want the
+    // attention's output (it goes to the tail's operand planes), perhaps none
+    int rows_attention(int layer, int parts, const Runner* tail = nullptr) {
         const ModelDims& md = m->md;
-        const int blocks = (rps + ROT_POS - 1) / ROT_POS, ntiles = (rps * md.G + 15) / 16;
+        const int q0 = tail ? rps - tail->rps : 0;
+        const int blocks = (rps + ROT_POS - 1) / ROT_POS, ntiles = (rps * md.G + 15) / 16, used = ntiles - q0 * md.G / 16;
         u32x4* qbuf = (u32x4*)w->act;
         // waves per tile: as many as leave a workgroup for every CU
-        const long long tiles = (long long)ntiles * md.Hkv * nseq;
+        const long long tiles = (long long)used * md.Hkv * nseq;
         const int kw = tiles >= 1024 ? 2 : tiles >= 512 ? 4 : 8;
-        const int grid = (ntiles * kw + ROWS_WAVES - 1) / ROWS_WAVES * ((nseq * md.Hkv + 7) / 8 * 8);
+        const int grid = (used * kw + ROWS_WAVES - 1) / ROWS_WAVES * ((nseq * md.Hkv + 7) / 8 * 8);
+        const Runner& to = tail ? *tail : *this;
 #define ROWS_ATTN_KW(HD, KW)                                                                                           \
-    rows_attn_kernel<T, HD, KW, SPL><<<grid, ROWS_WAVES * 64, 0, st>>>(kv->sp_dev, md, view(), layer, qbuf, ntiles,    \
-                                                                       (T*)w->attn_out, plane(md.Hq * md.hd))
+    rows_attn_kernel<T, HD, KW, SPL><<<grid, ROWS_WAVES * 64, 0, st>>>(kv->sp_dev, md, view(), layer, qbuf, ntiles, q0, \
+                                                                       (T*)w->attn_out, to.plane(md.Hq * md.hd), to.rm())
 #define ROWS_ATTN(HD)                                                                                                  \
     do {                                                                                                               \
         const dim3 rgrid(blocks, 3 * md.Hkv, nseq);                                                                    \
-        if (parts <= 2) rows_rotary_kernel<T, HD, SPL, 2><<<rgrid, 256, 0, st>>>(kv->sp_dev, md, w->part, parts, R, w->cs, view(), layer, qbuf, ntiles); \
-        else rows_rotary_kernel<T, HD, SPL, 6><<<rgrid, 256, 0, st>>>(kv->sp_dev, md, w->part, parts, R, w->cs, view(), layer, qbuf, ntiles); \
+        if (parts <= 2) rows_rotary_kernel<T, HD, SPL, 2><<<rgrid, 256, 0, st>>>(kv->sp_dev, md, w->part, parts, R, w->cs, view(), layer, qbuf, ntiles, q0); \
+        else rows_rotary_kernel<T, HD, SPL, 6><<<rgrid, 256, 0, st>>>(kv->sp_dev, md, w->part, parts, R, w->cs, view(), layer, qbuf, ntiles, q0); \
         LAUNCHCHK("rows_rotary");                                                                                      \
+        if (q0 == rps) break;                                                                                          \
         if (kw == 2) ROWS_ATTN_KW(HD, 2); else if (kw == 4) ROWS_ATTN_KW(HD, 4); else ROWS_ATTN_KW(HD, 8);             \
         LAUNCHCHK("rows_attn");                                                                                        \
     } while (0)
@@ -1394,8 +1398,26 @@ struct Runner {
         else add_rmsnorm_kernel<T, 8, SPL><<<n, 1024, 0, st>>>(R, d, m->md.eps, x, part, parts, (const T*)gain, xn, oplane, h, orm);
     }
 
-    // decoder layers (Eq. 2 / Eq. 4): leaves the last down-projection's K-slices pending in w->part (their number in `parts`)
-    int decoder(int& parts) {
+    // a layer behind its attention: O, gate / up, down; after the last one the down projection's K-slices stay pending in w->part
+    int feed_forward(int l, int& parts, bool& unscaled) {
+        const ModelDims& md = m->md;
+        const LayerW& L = m->layers[l];
+        int rc;
+        if ((rc = close(L.wo, w->attn_out, md.Hq * md.hd, kv->plan_o, L.ffn_norm, 2, unscaled))) return rc;
+        if ((rc = time_mark(kv, 3, st))) return rc;
+        if ((rc = gate_up(L.wgu, unscaled))) return rc;
+        if ((rc = time_mark(kv, 3, st))) return rc;
+        if (l + 1 < m->cfg.n_layers) return close(L.wd, w->act, md.F, kv->plan_d, m->layers[l + 1].attn_norm, 4, unscaled);
+        if ((rc = time_mark(kv, 4, st))) return rc;
+        if ((rc = partial_gemm(L.wd, w->act, md.F, md.d, kv->plan_d, &parts))) return rc;
+        return time_mark(kv, 4, st);
+    }
+
+    // decoder layers (Eq. 2 / Eq. 4): leaves the last down-projection's K-slices pending in w->part (their number in `parts`).
+    // `tail` (a prompt chunk): the runner of the chunk's last rows, the only ones whose final states are wanted, perhaps none.  Nobody reads
+    // what the last layer makes of the other rows beyond their keys and values, so behind its QKV projection that layer is the tail's:
+    // 509 rows of the 8B shape cut to 4 layers, blocks of 6: 367 us of products and attention over all rows give way to 95.
+    int decoder(int& parts, Runner* tail = nullptr) {
         const ModelDims& md = m->md;
         const sj_config& c = m->cfg;
         const int d = md.d, Nq = md.Hq * md.hd, Nk = md.Hkv * md.hd, Nqkv = Nq + 2 * Nk;
@@ -1410,18 +1432,13 @@ struct Runner {
             if ((rc = time_mark(kv, 1, st))) return rc;
             if ((rc = partial_gemm(L.wqkv, w->xn, d, Nqkv, kv->plan_qkv, &parts, unscaled))) return rc;
             if ((rc = time_mark(kv, 1, st))) return rc;
-            if ((rc = attention(l, parts))) return rc;
-            if ((rc = close(L.wo, w->attn_out, Nq, kv->plan_o, L.ffn_norm, 2, unscaled))) return rc;
-            if ((rc = time_mark(kv, 3, st))) return rc;
-            if ((rc = gate_up(L.wgu, unscaled))) return rc;
-            if ((rc = time_mark(kv, 3, st))) return rc;
-            if (l + 1 < c.n_layers) {
-                if ((rc = close(L.wd, w->act, md.F, kv->plan_d, m->layers[l + 1].attn_norm, 4, unscaled))) return rc;
-            } else {
-                if ((rc = time_mark(kv, 4, st))) return rc;
-                if ((rc = partial_gemm(L.wd, w->act, md.F, d, kv->plan_d, &parts))) return rc;
-                if ((rc = time_mark(kv, 4, st))) return rc;
+            if (tail && l + 1 == c.n_layers) {
+                if ((rc = rows_attention(l, parts, tail))) return rc;
+                unscaled = false;
+                return tail->R > 0 ? tail->feed_forward(l, parts, unscaled) : SJ_OK;
             }
+            if ((rc = attention(l, parts))) return rc;
+            if ((rc = feed_forward(l, parts, unscaled))) return rc;
         }
         return SJ_OK;
     }
@@ -1920,13 +1937,16 @@ static int prefill_impl(sj_model* m, sj_kv* kv, int seq, const int32_t* tokens, 
             if ((rc = run.layers())) return rc;
         } else {
             int parts = 0;
-            if ((rc = run.decoder(parts))) return rc;
+            const int keep = last ? std::min(block, cn) : 0;   // chunks are longer than a block: cn > block
+            Forward tail_fw = *fw;                             // the same buffers, the residual stream from the first kept row on
+            tail_fw.x += (size_t)(cn - keep) * m->md.d;
+            Runner<T, SPL> tail{m, kv, st, 1, keep, keep, &tail_fw, seq};
+            if ((rc = run.decoder(parts, &tail))) return rc;
             if (last) {
                 head_rows = n - (n - 1) / block * block;
-                const int keep = std::min(block, cn);          // chunks are longer than a block: cn > block
                 Runner<T, SPL> head{m, kv, st, 1, head_rows, head_rows, fw};
-                if (keep > head_rows) run.norm_rows(parts, m->final_norm, kv->hn32, cn - keep, keep - head_rows, head_rows, run.plane(m->md.d), 0);   // (its operand rows give way to the next ones)
-                run.norm_rows(parts, m->final_norm, kv->hn32, cn - head_rows, head_rows, 0, head.plane(m->md.d), head.rm());
+                if (keep > head_rows) tail.norm_rows(parts, m->final_norm, kv->hn32, 0, keep - head_rows, head_rows, tail.plane(m->md.d), tail.rm());   // (its operand rows give way to the next ones)
+                tail.norm_rows(parts, m->final_norm, kv->hn32, keep - head_rows, head_rows, 0, head.plane(m->md.d), head.rm());
                 LAUNCHCHK("add_rmsnorm");
             }
         }

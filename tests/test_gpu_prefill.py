@@ -70,6 +70,46 @@ def test_long_prompt_matches_oracle(dtype, hq, hkv, hd, prompts):
         gpu.close()
 
 
+# The last layer of a prompt chunk goes on with the rows of the last block only: two rows (operand planes with rows side by side), seven (packed),
+# twelve (not packed), 41 (the many-row kernels), tails that begin inside a tile of query columns, one layer and three, and a group
+# that does not divide 16.
+@pytest.mark.parametrize("dtype,layers,hq,hkv,gamma,prompts", [
+    ("bf16", 1, 8, 2, 1, [3, 64]),
+    ("bf16", 3, 6, 2, 6, [8, 47]),
+    ("bf16", 1, 4, 4, 11, [5, 13, 130]),
+    ("bf16", 2, 8, 2, 40, [42, 100]),
+    ("fp32", 1, 10, 2, 2, [4, 33]),
+    ("fp32", 2, 4, 2, 35, [37, 77]),
+])
+def test_last_layer_runs_over_the_last_block(dtype, layers, hq, hkv, gamma, prompts):
+    shape = dataclasses.replace(SMALL, name=f"prefill_tail_{dtype}_{layers}_{gamma}", dtype=dtype, n_layers=layers, n_q_heads=hq, n_kv_heads=hkv,
+                                head_dim=64, batch=1, gamma=gamma, temperature=1.0)
+    src = synth.WeightSource(shape, seed=25, norm_jitter=0.1)
+    cap, block = sum(prompts), gamma + 1
+    gpu = G.Gpu(shape, src, [cap])
+    try:
+        cfg, W = helpers.oracle_config(shape), helpers.oracle_weights(src)
+        cache = orc.SeqCache(cfg, cap, storage=dtype)
+        for i, n in enumerate(prompts):
+            prompt = synth.make_prompt(shape, 40 + i, n).tolist()
+            L0 = cache.length
+            sj.sj_prefill(gpu.model, gpu.kv, 0, prompt)
+            fw = orc.block_forward(cfg, W, [cache], [prompt])[0]
+            cache.length += n
+            for l in range(layers):
+                k, v = gpu.kv_rows(0, l, L0, n)
+                G.close_enough(k, cache.k[l][:, L0:cache.length], dtype, f"K layer {l}")
+                G.close_enough(v, cache.v[l][:, L0:cache.length], dtype, f"V layer {l}")
+            rows, tail = min(n, block), n - (n - 1) // block * block
+            order = list(range(n - tail, n)) + list(range(n - rows, n - tail))
+            hn = sj.sj_debug_fetch(gpu.kv, sj.SJ_DBG_HIDDEN, np.empty((rows, shape.d_model), np.float32))
+            G.close_enough(hn, fw["hn"][order], dtype, "hidden")
+            logits = sj.sj_debug_fetch(gpu.kv, sj.SJ_DBG_LOGITS, np.empty((rows, shape.vocab), np.float32))
+            G.close_enough(logits[:tail], fw["logits"][n - tail:], dtype, "logits")
+    finally:
+        gpu.close()
+
+
 def test_prompt_buffers_come_with_the_first_long_prompt():
     """A cache object that sees no prompt longer than a block holds no buffers for prompt chunks."""
     import torch
