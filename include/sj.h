@@ -227,8 +227,9 @@ int sj_verify_head_static(sj_model* m, int32_t batch, int32_t gamma, const void*
  *   best_index, w_best [d + 1], theta_f1, theta_recall   HOST out: the kept model (w, then b) and its thresholds
  * Everything is computed on the device in fp64 (features read as fp32); the call allocates its workspace, synchronises
  * `stream` and frees it before returning: 8 S n_train + 16 n_val min(n_C, 2^22 / n_val) + 8 n_val + 8 n_C (d + 1) bytes and the
- * partial sums, 2048 T S (d + 2) bytes at most (S = problems to a pass: 4, above d = 4096 2, and no more than n_C needs; T = 8, 4, 2, 1
- * workgroup teams for d up to 256, 512, 1024 and above): up to 17 MB for d <= 1024, 34 MB for d = 4096 or 8192.
+ * partial sums, 2048 T S (c + 2) bytes at most (S = problems to a pass: 4, above d = 4096 2, and no more than n_C needs; T = 8, 4, 2, 1
+ * workgroup teams for d up to 256, 512, 1024 and above; c = 256, 512, 1024, 2048 or 4096 where d is no larger, else d): up to 17 MB for
+ * d <= 2048, 34 MB for d = 4096 or 8192.
  * Errors: SJ_EINVAL (null / misaligned pointer, sizes, a label other than 0 / 1, a set with one class only,
  * non-positive C), SJ_ENOMEM, SJ_EHIP (also when the solver fails to converge, as it does on training features
  * that are not finite). */

@@ -26,6 +26,7 @@
 #include <cstdarg>
 #include <cstdint>
 #include <cstdio>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -81,9 +82,10 @@ struct TrainArgs {
     double* vecs;                   // [slots][V_COUNT][vstride]
     long long vstride;
     double* D;                      // [slots][n] s (1 - s): written by a gradient pass, read by the Hessian passes
-    double* partial;                // [rows][slots][d + 2]: sum c h, sum c, sum of losses
+    double* partial;                // [rows][slots][pcols + 2]: sum c h, sum c, sum of losses
     double* raw;                    // [slots][d + 2]
-    int nrows;                      // rows of `partial`
+    int nslots;
+    int nrows, pcols;               // rows of `partial`; its columns of a slot besides the two sums (d, or whole waves' slices in lane order: partial_col)
     const double* C_list;           // [n_C]
     const int32_t* order;           // problems in the order they are taken
     int32_t* queue;                 // next entry of `order`, and [1]: problems finished
@@ -141,37 +143,87 @@ __device__ __forceinline__ double wave_sums(double (&v)[Q], int lane) {
     return r;
 }
 
+// v of this lane + v of the lane O behind it in its row of 16 (rotating)
+template <int O>
+__device__ __forceinline__ double block_sum(double v) {
+    const uint2 u = __builtin_bit_cast(uint2, v);
+    const uint2 r{(unsigned)__builtin_amdgcn_update_dpp(0, (int)u.x, 0x120 + O, 0xf, 0xf, false), (unsigned)__builtin_amdgcn_update_dpp(0, (int)u.y, 0x120 + O, 0xf, 0xf, false)};
+    return v + __builtin_bit_cast(double, r);
+}
+
 __device__ __forceinline__ double lane_value(double v, int lane) {
     const long long b = __double_as_longlong(v);
     const int lo = __builtin_amdgcn_readlane((int)b, lane), hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// One pass over the matrix for A slots.  A workgroup of eight waves: CW of them share a group of RB rows, wave c of the CW
-// owning the columns [c * NJ * 256, (c + 1) * NJ * 256) (lane l: elements 4l .. 4l + 3 of each of its NJ 256-column pieces, so
-// every load instruction of a wave covers 1 KB of consecutive memory); the 8 / CW teams take neighbouring row groups.  A wave's
-// slices of the A accumulators stay in registers, those of the vectors in LDS (d = 4096, A = 4: 64 registers and 128 KB; both
-// in registers, next to two row buffers of 32, spilled and ran 99 us).  Per group: partial dot products of RB rows x A
-// slots -> LDS -> one barrier -> every wave finishes all RB x A coefficients itself (lane q / Q; sigmoid only where a slot is in
-// a gradient phase) and updates its columns.  The next group's loads (64 KB a CU) are issued before the current group is used.  Columns at
-// or past d are loaded from a clamped address and meet x = 0; their accumulators are never stored.  An idle slot rides along
-// with a zero vector and zero coefficients.
-// Bound: reads of the matrix (284 MB of 17358 x 4096 in 50 us) and, above them, the chain of a group - dot products, wave
-// sums, barrier, coefficients, update - which the two waves of a SIMD cross together.  Measured at that size with four slots:
-// 79 us a pass = 20 us a problem, + 9 us for the sum of the partials and 8 us for the slots' updates; with one problem at a
-// time a pass took 53 us, its vector kernels and the host's look at the result 65 us more.  A grid of ten C: 86 ms -> 26 ms.
-// Converting a row once for dot product and update (32 registers more) measured the same.
-// The exchanges across 32 and 16 lanes as swaps (swap_add): 74 -> 71 us a pass, ten C 26.4 -> 25.4 ms.  Groups of two rows with three
-// buffers, so that the next group's dot products cover a group's exchange and barrier: 30.5 ms (the vectors are read from LDS for
-// half as many rows).
+// One pass over the matrix for the slots.  A workgroup of eight waves: CW of them share a group of RB rows, wave c of the CW
+// owning the columns [c * NJ * 256, (c + 1) * NJ * 256); the 8 / CW teams take neighbouring row groups.  Rows come through LDS by direct
+// loads, each wave its own columns (1 KB of consecutive memory an instruction) into 16 KB of its own, so no wave waits for another's: the
+// group that a wave has read into registers makes room at once for the one 16 KB later.  A wave's slices of the slots' vectors and
+// accumulators are registers.  Per group: partial dot products of RB rows x slots -> LDS -> one barrier -> every wave finishes all
+// coefficients itself (sigmoid only where a slot is in a gradient phase) and updates its columns.  Columns at or past d are loaded from a
+// clamped address and meet x = 0; their accumulators are never used.  An idle slot rides along with a zero vector and zero coefficients.
+// Bound: reads of the matrix (284 MB of 17358 x 4096: 41 us at 6.9 TB/s), the partial sums (34 MB written, 10 us), and 9 us of launch, first loads
+// and end.  Launched back to back at that size, four slots, Hessian products: 84.5 us with the vectors in LDS, read there for every row, rows in two
+// sets of registers, and the prologue's 32 loads each waited for in a branch of its own; 81.6 with rows through LDS and the prologue's loads
+// together; 66 with the products on the matrix cores (below).  A round is this pass, 5 us for the sum of the partials and 8 us for the slots'
+// updates; a grid of ten C at that size (280 rounds): 27.3 -> 23.9 ms, one card in turn.
+// This form, products on the vector units, is the one of d > 4096, where two slots' vectors and accumulators are all that fits (8000 x 8192:
+// 68.1 -> 59.8 us a pass; 8000 x 5120: 40.1 -> 37.9).
 constexpr int pass_rows(int nj) { return nj > 2 ? 2 : 4; }          // rows per group: at most 32 registers a buffer
+
+// immediate of s_waitcnt vmcnt(n) with the other counters left alone (vmcnt sits in bits 3:0 and 15:14)
+constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ unsigned lds_addr(const void* p) { return (unsigned)(unsigned long long)(const __attribute__((address_space(3))) void*)p; }
+
+// N pieces of 16 bytes a lane, STEP bytes apart in LDS, waited for in the same block.  As ordinary reads they would wait for every direct
+// global->LDS load of the wave, since the compiler cannot tell which of them the data came with.
+template <int STEP, int N> __device__ __forceinline__ void lds_read(f32x4 (&v)[N], unsigned at) {
+    static_assert(N == 4 || N == 6 || N == 8, "pieces");
+    if constexpr (N == 4)
+        asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %4 offset:%5\n\tds_read_b128 %2, %4 offset:%6\n\tds_read_b128 %3, %4 offset:%7\n\t"
+                     "s_waitcnt lgkmcnt(0)" : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]) : "v"(at), "n"(STEP), "n"(2 * STEP), "n"(3 * STEP) : "memory");
+    else if constexpr (N == 6)
+        asm volatile("ds_read_b128 %0, %6\n\tds_read_b128 %1, %6 offset:%7\n\tds_read_b128 %2, %6 offset:%8\n\tds_read_b128 %3, %6 offset:%9\n\t"
+                     "ds_read_b128 %4, %6 offset:%10\n\tds_read_b128 %5, %6 offset:%11\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5])
+                     : "v"(at), "n"(STEP), "n"(2 * STEP), "n"(3 * STEP), "n"(4 * STEP), "n"(5 * STEP) : "memory");
+    else
+        asm volatile("ds_read_b128 %0, %8\n\tds_read_b128 %1, %8 offset:%9\n\tds_read_b128 %2, %8 offset:%10\n\tds_read_b128 %3, %8 offset:%11\n\t"
+                     "ds_read_b128 %4, %8 offset:%12\n\tds_read_b128 %5, %8 offset:%13\n\tds_read_b128 %6, %8 offset:%14\n\t"
+                     "ds_read_b128 %7, %8 offset:%15\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
+                     : "v"(at), "n"(STEP), "n"(2 * STEP), "n"(3 * STEP), "n"(4 * STEP), "n"(5 * STEP), "n"(6 * STEP), "n"(7 * STEP) : "memory");
+}
+
+// The same for what the waves leave one another: a value written, and N values STEP bytes apart read.
+__device__ __forceinline__ void lds_put(unsigned at, double v) { asm volatile("ds_write_b64 %0, %1" :: "v"(at), "v"(v) : "memory"); }
+template <int STEP, int N> __device__ __forceinline__ void lds_get(double (&v)[N], unsigned at) {
+    static_assert(N == 1 || N == 2 || N == 4 || N == 8, "waves that share a row");
+    if constexpr (N == 1) asm volatile("ds_read_b64 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(v[0]) : "v"(at) : "memory");
+    else if constexpr (N == 2)
+        asm volatile("ds_read_b64 %0, %2\n\tds_read_b64 %1, %2 offset:%3\n\ts_waitcnt lgkmcnt(0)" : "=&v"(v[0]), "=&v"(v[1]) : "v"(at), "n"(STEP) : "memory");
+    else if constexpr (N == 4)
+        asm volatile("ds_read_b64 %0, %4\n\tds_read_b64 %1, %4 offset:%5\n\tds_read_b64 %2, %4 offset:%6\n\tds_read_b64 %3, %4 offset:%7\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]) : "v"(at), "n"(STEP), "n"(2 * STEP), "n"(3 * STEP) : "memory");
+    else
+        asm volatile("ds_read_b64 %0, %8\n\tds_read_b64 %1, %8 offset:%9\n\tds_read_b64 %2, %8 offset:%10\n\tds_read_b64 %3, %8 offset:%11\n\t"
+                     "ds_read_b64 %4, %8 offset:%12\n\tds_read_b64 %5, %8 offset:%13\n\tds_read_b64 %6, %8 offset:%14\n\tds_read_b64 %7, %8 offset:%15\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
+                     : "v"(at), "n"(STEP), "n"(2 * STEP), "n"(3 * STEP), "n"(4 * STEP), "n"(5 * STEP), "n"(6 * STEP), "n"(7 * STEP) : "memory");
+}
 
 template <int NJ, int A, int CW>
 __global__ __launch_bounds__(PASS_WAVES * 64) void lr_pass_kernel(TrainArgs a) {
     constexpr int RB = pass_rows(NJ), TEAMS = PASS_WAVES / CW, Q = RB * A;
-    __shared__ double2 xs[CW][NJ * 2 * A][64];           // the vectors: entry (4 j + k) A + s of a lane, in pairs
+    constexpr int PIECES = RB * NJ, DEPTH = 16 / PIECES; // 1 KB pieces of a row group; groups that a wave's 16 KB of LDS hold
+    __shared__ f32x4 ring[PASS_WAVES][DEPTH][PIECES][64];
     __shared__ double part[2][TEAMS][CW][Q];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    static_assert(DEPTH % 2 == 0, "the slots of `part` take turns");
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int team = w / CW, cw = w % CW;
 
     int ph[A];
@@ -186,81 +238,106 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void lr_pass_kernel(TrainArgs a) {
     if (!any) return;                                    // every problem is done (uniform for the launch)
 
     int off[NJ];
-    double acc[NJ][4][A];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-        const int e = (cw * NJ + j) * 256 + lane * 4;
-        off[j] = min(e, a.d - 4);
+    for (int j = 0; j < NJ; ++j) off[j] = min((cw * NJ + j) * 256 + lane * 4, a.d - 4);
+    // the wave's slices of the vectors, all asked for at once (an idle slot's memory is there, too)
+    double2 x2[NJ][A][2];
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
-            for (int s = 0; s < A; ++s) {
-                const int at = (4 * j + k) * A + s;
-                reinterpret_cast<double*>(&xs[cw][at / 2][lane])[at % 2] = ph[s] != PH_IDLE && e + k < a.d ? xv[s][e + k] : 0.0;
-                acc[j][k][s] = 0.0;
-            }
-    }
+        for (int s = 0; s < A; ++s) {
+            x2[j][s][0] = *reinterpret_cast<const double2*>(xv[s] + off[j]);
+            x2[j][s][1] = *reinterpret_cast<const double2*>(xv[s] + off[j] + 2);
+        }
     // this lane's coefficient: row rb of the group, slot sl
     const int ql = lane / (64 / Q), sl = ql % A, rb_l = ql / A;
     int ph_l = PH_IDLE;
-    double xb = 0.0;
 #pragma unroll
     for (int s = 0; s < A; ++s)
-        if (s == sl) { ph_l = ph[s]; xb = ph[s] != PH_IDLE ? xv[s][a.d] : 0.0; }
+        if (s == sl) ph_l = ph[s];
+    double xb_l = 0.0;                                   // its intercept
+#pragma unroll
+    for (int s = 0; s < A; ++s)
+        if (s == sl) xb_l = ph[s] != PH_IDLE ? xv[s][a.d] : 0.0;
     double* Dl = a.D + (long long)sl * a.n;
     double accb = 0.0, loss = 0.0;
 
     const long long ngroups = (a.n + RB - 1) / RB;
-    float4 bufA[RB][NJ], bufB[RB][NJ];
-    double auxA = 0.0, auxB = 0.0;                       // label or D of this lane's row
-    auto load = [&](float4 (&buf)[RB][NJ], double& aux, long long grp) {
+    // D or the label of this lane's row, by two word loads (the label twice) that no branch and no conversion waits for
+    const int32_t* aux_at = ph_l == PH_HESS ? reinterpret_cast<const int32_t*>(Dl) : a.y;
+    const int wide = ph_l == PH_HESS ? 1 : 0;
+    int alo[DEPTH], ahi[DEPTH];
+    auto load = [&](int u, long long grp) {
         const long long g = grp < ngroups ? grp : ngroups - 1;   // groups past the end re-read the last (not used)
+        const long long il = g * RB + rb_l < a.n ? g * RB + rb_l : a.n - 1;
+        alo[u] = aux_at[il << wide];
+        ahi[u] = aux_at[(il << wide) + wide];
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
             const long long i = g * RB + rb;
             const float* row = a.H + (i < a.n ? i : a.n - 1) * a.d;
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) buf[rb][j] = *reinterpret_cast<const float4*>(row + off[j]);
+            for (int j = 0; j < NJ; ++j)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(row + off[j]),
+                                                 (__attribute__((address_space(3))) void*)&ring[w][u][rb * NJ + j][0], 16, 0, 0);
         }
-        const long long il = g * RB + rb_l < a.n ? g * RB + rb_l : a.n - 1;
-        aux = ph_l == PH_HESS ? Dl[il] : (double)a.y[il];
     };
-    auto process = [&](float4 (&buf)[RB][NJ], double aux, long long grp, int par) {
+    // group numbers of this team: blockIdx.x * TEAMS + team, + gridDim.x * TEAMS, ...; the number of turns is the workgroup's
+    // (barriers inside): a team past the last group works on rows that do not count.  A slot of `part` is written again two
+    // turns later, after a barrier every wave passes only once all its reads of the earlier turn are done.
+    const long long G = (long long)gridDim.x * TEAMS;
+    const long long g0 = (long long)blockIdx.x * TEAMS;
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u) load(u, g0 + team + u * G);
+    double x[NJ][4][A], acc[NJ][4][A];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int s = 0; s < A; ++s) {
+            asm volatile("" : "+v"(x2[j][s][0].x), "+v"(x2[j][s][0].y), "+v"(x2[j][s][1].x), "+v"(x2[j][s][1].y));   // (a load that only a branch uses would wait there)
+            const bool in = ph[s] != PH_IDLE && (cw * NJ + j) * 256 + lane * 4 < a.d;
+            x[j][0][s] = in ? x2[j][s][0].x : 0.0;
+            x[j][1][s] = in ? x2[j][s][0].y : 0.0;
+            x[j][2][s] = in ? x2[j][s][1].x : 0.0;
+            x[j][3][s] = in ? x2[j][s][1].y : 0.0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc[j][k][s] = 0.0;
+        }
+    auto process = [&](int u, long long grp) {
+        f32x4 h[PIECES];
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm((DEPTH - 1) * (PIECES + 2)));   // this group has landed (what else the wave asked for since only waits longer)
+        lds_read<1024>(h, lds_addr(&ring[w][u][0][0]) + lane * 16);
+        const int lo = alo[u], hi = ahi[u];
+        load(u, grp + DEPTH * G);                        // the group's place is free
         double dot[Q];
 #pragma unroll
         for (int q = 0; q < Q; ++q) dot[q] = 0.0;
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
 #pragma unroll
-            for (int k = 0; k < 4; k += 2) {             // two columns: 2 A doubles of x
-                double x2[2 * A];
-#pragma unroll
-                for (int t = 0; t < A; ++t) {
-                    const double2 v = xs[cw][(4 * j + k) * A / 2 + t][lane];
-                    x2[2 * t] = v.x;
-                    x2[2 * t + 1] = v.y;
-                }
+            for (int k = 0; k < 4; ++k)
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb) {
-                    const double h0 = k ? buf[rb][j].z : buf[rb][j].x, h1 = k ? buf[rb][j].w : buf[rb][j].y;
+                    const double hd = h[rb * NJ + j][k];
 #pragma unroll
-                    for (int s = 0; s < A; ++s) dot[rb * A + s] += h0 * x2[s];
-#pragma unroll
-                    for (int s = 0; s < A; ++s) dot[rb * A + s] += h1 * x2[A + s];
+                    for (int s = 0; s < A; ++s) dot[rb * A + s] += hd * x[j][k][s];
                 }
-            }
         const double dq = wave_sums<Q>(dot, lane);
-        if (lane % (64 / Q) == 0) part[par][team][cw][ql] = dq;
+        const unsigned pt = lds_addr(&part[u & 1][team][0][ql]);
+        if (lane % (64 / Q) == 0) lds_put(pt + cw * (Q * 8), dq);
         lds_barrier();
         const long long i = grp * RB + rb_l;
-        double z = part[par][team][0][ql];
+        double zs[CW];
+        lds_get<Q * 8>(zs, pt);
+        double z = zs[0];
 #pragma unroll
-        for (int c = 1; c < CW; ++c) z += part[par][team][c][ql];
-        z += xb;
+        for (int c = 1; c < CW; ++c) z += zs[c];
+        z += xb_l;
         double c = 0.0;
         if (i < a.n) {
-            if (ph_l == PH_HESS) c = aux * z;
+            if (ph_l == PH_HESS) c = __hiloint2double(hi, lo) * z;
             else if (ph_l != PH_IDLE) {
+                const double aux = lo;
                 const double sg = 1.0 / (1.0 + exp(-z));
                 c = sg - aux;
                 if (cw == 0) {
@@ -273,38 +350,22 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void lr_pass_kernel(TrainArgs a) {
         accb += c;
         // the update converts the row again: kept from the dot products, its doubles would be 16 registers a row and piece
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-                asm volatile("" : "+v"(buf[rb][j].x), "+v"(buf[rb][j].y), "+v"(buf[rb][j].z), "+v"(buf[rb][j].w));
+        for (int p = 0; p < PIECES; ++p) asm volatile("" : "+v"(h[p]));
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
             for (int s = 0; s < A; ++s) {
                 const double cs = lane_value(c, (rb * A + s) * (64 / Q));
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    acc[j][0][s] += cs * (double)buf[rb][j].x;
-                    acc[j][1][s] += cs * (double)buf[rb][j].y;
-                    acc[j][2][s] += cs * (double)buf[rb][j].z;
-                    acc[j][3][s] += cs * (double)buf[rb][j].w;
-                }
+                for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) acc[j][k][s] += cs * (double)h[rb * NJ + j][k];
             }
     };
-
-    // group numbers of this team: blockIdx.x * TEAMS + team, + gridDim.x * TEAMS, ...; the number of turns is the workgroup's
-    // (barriers inside): a team past the last group works on rows that do not count.  A slot of `part` is written again two
-    // turns later, after a barrier every wave passes only once all its reads of the earlier turn are done.
-    const long long G = (long long)gridDim.x * TEAMS;
-    const long long g0 = (long long)blockIdx.x * TEAMS;
-    load(bufA, auxA, g0 + team);
-    __syncthreads();                                     // the vectors are in LDS
-    for (long long grp = g0; grp < ngroups; grp += 2 * G) {
-        load(bufB, auxB, grp + team + G);
-        process(bufA, auxA, grp + team, 0);
-        load(bufA, auxA, grp + team + 2 * G);
-        if (grp + G < ngroups) process(bufB, auxB, grp + team + G, 1);   // uniform for the workgroup
-    }
+    for (long long grp = g0; grp < ngroups; grp += DEPTH * G)
+#pragma unroll
+        for (int u = 0; u < DEPTH; ++u)
+            if (grp + u * G < ngroups) process(u, grp + team + u * G);   // uniform for the workgroup
 
     double* out = a.partial + ((long long)blockIdx.x * TEAMS + team) * A * (a.d + 2);
 #pragma unroll
@@ -330,21 +391,194 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void lr_pass_kernel(TrainArgs a) {
     }
 }
 
-// raw[s][e] = sum over the rows of `partial` (e <= d + 1), in a fixed order: thread (slice q, column c) adds the rows of slice q
-// of 16 in order, the 16 slice sums are then added in slice order.
-__global__ __launch_bounds__(1024) void lr_reduce_kernel(TrainArgs a, int A) {
+// The same pass with the products on the matrix cores, up to d = 4096.  On the vector units a turn of four rows x four slots is 650 instructions
+// a wave: 16 dot products to be summed over the lanes, 32 read-lanes of coefficients.  Here it is 200: four rows x four slots are one 4x4x4 block
+// (four blocks an instruction, 256 multiply-adds in 8 ns a SIMD where 64 of the vector units' take 2.7), a dot product is one register pair a lane
+//   dot:     D[row][slot] += A[row][column] B[column][slot]     (h, x)
+//   update:  D[column][slot] += A[column][row] B[row][slot]     (h, c)
+// Lane maps of v_mfma_f64_4x4x4_4b: A: i + 4 block + 16 k, B: j + 4 block + 16 k, D: j + 4 block + 16 i.  The dot's result, summed over the
+// four blocks, is a lane's coefficient (slot lane % 4, row lane / 16) and then, as it stands, the update's B operand.  A lane holds a row's
+// columns for the dot and a column's rows for the update: h is read from LDS once in either order, rows 64 bytes apart from a multiple of 256
+// so that no bank is hit twice.  Column of MFMA (m, k) of a wave: m * 64 + 4 * (lane / 4) + k for the dot and x, m * 64 + 4 * (lane % 16) + k for the
+// update's operand, m * 64 + 4 * (lane / 16 + 4 (lane / 4 % 4)) + k for the accumulators.
+template <int NJ, int CW>
+__global__ __launch_bounds__(PASS_WAVES * 64) void lr_pass_mfma_kernel(TrainArgs a) {
+    constexpr int RB = 4, A = 4, TEAMS = PASS_WAVES / CW, NM = NJ * 4;
+    constexpr int DEPTH = 4 / NJ, ROW = NJ * 1024 + 64, GROUP = RB * ROW;    // groups in LDS; bytes of a row's slice, of a group's
+    __shared__ __align__(16) unsigned char ring[PASS_WAVES * DEPTH * GROUP];
+    __shared__ double part[2][TEAMS][CW][RB * A];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int team = w / CW, cw = w % CW;
+    const int sl = lane & 3, rb_l = lane >> 4;           // this lane's coefficient: slot, row of the group
+    bool any = false, gradient = false;
+    for (int s = 0; s < a.nslots; ++s) {
+        const int ph = a.slots[s].phase;
+        any = any || ph != PH_IDLE;
+        gradient = gradient || (ph != PH_IDLE && ph != PH_HESS);
+    }
+    if (!any) return;                                    // every problem is done (uniform for the launch)
+    const int slot = min(sl, a.nslots - 1);
+    const int ph_l = sl < a.nslots ? a.slots[slot].phase : PH_IDLE;
+    const double* xv = a.vecs + ((long long)slot * V_COUNT + pass_vector(ph_l, a.slots[slot].flip)) * a.vstride;
+    double* Dl = a.D + (long long)slot * a.n;
+
+    double2 x2[NM][2];                                   // all asked for at once (an idle slot's memory is there, too)
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+        const double* at = xv + min(cw * NJ * 256 + m * 64 + (lane >> 2) * 4, a.d - 4);
+        x2[m][0] = *reinterpret_cast<const double2*>(at);
+        x2[m][1] = *reinterpret_cast<const double2*>(at + 2);
+    }
+    const double xb_l = xv[a.d];
+    asm volatile("" ::: "memory");                       // (not behind the rows' requests)
+    int off[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) off[j] = min((cw * NJ + j) * 256 + lane * 4, a.d - 4);
+    double accb = 0.0, loss = 0.0;
+
+    const long long ngroups = (a.n + RB - 1) / RB;
+    // D or the label of this lane's row, by two word loads (the label twice) that no branch and no conversion waits for
+    const int32_t* aux_at = ph_l == PH_HESS ? reinterpret_cast<const int32_t*>(Dl) : a.y;
+    const int wide = ph_l == PH_HESS ? 1 : 0;
+    int alo[DEPTH], ahi[DEPTH];
+    unsigned char* mine = ring + w * DEPTH * GROUP;
+    auto load = [&](int u, long long grp) {
+        const long long g = grp < ngroups ? grp : ngroups - 1;   // groups past the end re-read the last (not used)
+        const long long il = g * RB + rb_l < a.n ? g * RB + rb_l : a.n - 1;
+        alo[u] = aux_at[il << wide];
+        ahi[u] = aux_at[(il << wide) + wide];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const long long i = g * RB + rb;
+            const float* row = a.H + (i < a.n ? i : a.n - 1) * a.d;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(row + off[j]),
+                                                 (__attribute__((address_space(3))) void*)(mine + u * GROUP + rb * ROW + j * 1024), 16, 0, 0);
+        }
+    };
+    // group numbers of this team: blockIdx.x * TEAMS + team, + gridDim.x * TEAMS, ...; the number of turns is the workgroup's
+    // (barriers inside): a team past the last group works on rows that do not count.  A slot of `part` is written again two
+    // turns later, after a barrier every wave passes only once all its reads of the earlier turn are done.
+    const long long G = (long long)gridDim.x * TEAMS;
+    const long long g0 = (long long)blockIdx.x * TEAMS;
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u) load(u, g0 + team + u * G);
+    double x[NM][4], acc[NM][4];
+#pragma unroll
+    for (int m = 0; m < NM; ++m) {
+        asm volatile("" : "+v"(x2[m][0].x), "+v"(x2[m][0].y), "+v"(x2[m][1].x), "+v"(x2[m][1].y));   // (a load that only a branch uses would wait there)
+        const bool in = ph_l != PH_IDLE && cw * NJ * 256 + m * 64 + (lane >> 2) * 4 < a.d;
+        x[m][0] = in ? x2[m][0].x : 0.0;
+        x[m][1] = in ? x2[m][0].y : 0.0;
+        x[m][2] = in ? x2[m][1].x : 0.0;
+        x[m][3] = in ? x2[m][1].y : 0.0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[m][k] = 0.0;
+    }
+    const double xb = ph_l != PH_IDLE ? xb_l : 0.0;
+
+    auto process = [&](auto grad, int u, long long grp) {
+        f32x4 h[NM], ht[NM];
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm((DEPTH - 1) * (RB * NJ + 2)));   // this group has landed (what else the wave asked for since only waits longer)
+        const unsigned at = lds_addr(mine + u * GROUP);
+        lds_read<256>(h, at + sl * ROW + (lane >> 2) * 16);
+        const int lo = alo[u], hi = ahi[u];
+        auto free_place = [&]() {                        // the group's second order, and the next group into its place
+            lds_read<256>(ht, at + rb_l * ROW + (lane & 15) * 16);
+            load(u, grp + DEPTH * G);
+        };
+        if constexpr (!decltype(grad)::value) free_place();
+        double dot[4] = {0.0, 0.0, 0.0, 0.0};            // four chains: a product waits for the one before it in its chain
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) dot[k] = __builtin_amdgcn_mfma_f64_4x4x4f64((double)h[m][k], x[m][k], dot[k], 0, 0, 0);
+        double dq = (dot[0] + dot[1]) + (dot[2] + dot[3]);
+        dq = block_sum<8>(dq);                           // over the four blocks
+        dq = block_sum<4>(dq);
+        const unsigned pt = lds_addr(&part[u & 1][team][0][rb_l * A + sl]);
+        if ((lane & 12) == 0) lds_put(pt + cw * (RB * A * 8), dq);
+        lds_barrier();
+        const long long i = grp * RB + rb_l;
+        double zs[CW];
+        lds_get<RB * A * 8>(zs, pt);
+        double z = zs[0];
+#pragma unroll
+        for (int c = 1; c < CW; ++c) z += zs[c];
+        z += xb;
+        double c = 0.0;
+        if (i < a.n) {
+            if (ph_l == PH_HESS) c = __hiloint2double(hi, lo) * z;
+            else if (decltype(grad)::value && ph_l != PH_IDLE) {
+                const double aux = lo;
+                const double t = exp(-fabs(z)), inv = 1.0 / (1.0 + t), sg = z < 0.0 ? t * inv : inv;   // one exp for the sigmoid and the loss
+                c = sg - aux;
+                if (cw == 0) {
+                    loss += fmax(aux > 0.5 ? -z : z, 0.0) + log1p(t);
+                    if ((lane & 12) == 0) Dl[i] = sg * (1.0 - sg);
+                }
+            }
+        }
+        accb += c;
+        if constexpr (decltype(grad)::value) free_place();   // (held since before exp and log1p, the 32 registers would have others spilled)
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) acc[m][k] = __builtin_amdgcn_mfma_f64_4x4x4f64((double)ht[m][k], c, acc[m][k], 0, 0, 0);
+    };
+    // a loop of its own for rounds of Hessian products only: the constants of exp and log1p are registers it does not have
+    auto run = [&](auto grad) {
+        for (long long grp = g0; grp < ngroups; grp += DEPTH * G)
+#pragma unroll
+            for (int u = 0; u < DEPTH; ++u)
+                if (grp + u * G < ngroups) process(grad, u, grp + team + u * G);   // uniform for the workgroup
+    };
+    if (gradient) run(std::true_type{}); else run(std::false_type{});
+
+    if (ph_l == PH_IDLE) return;
+    // 256 bytes of a slot side by side in each store (in column order a lane's neighbours are 32 bytes apart: 6 us more a pass of 17358 x 4096)
+    double* out = a.partial + (((long long)blockIdx.x * TEAMS + team) * a.nslots + sl) * (a.pcols + 2);
+#pragma unroll
+    for (int m = 0; m < NM; ++m)
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
+            *reinterpret_cast<double2*>(out + ((cw * NM + m) * 2 + half) * 32 + (lane >> 2) * 2) = double2{acc[m][2 * half], acc[m][2 * half + 1]};
+    if (cw == 0) {                                       // sums over the rows of a group, in row order
+        double sb = 0.0, sls = 0.0;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            sb += __shfl(accb, rb * 16 + sl, 64);
+            sls += __shfl(loss, rb * 16 + sl, 64);
+        }
+        if (lane < 4) {
+            out[a.pcols] = sb;
+            out[a.pcols + 1] = sls;
+        }
+    }
+}
+// column of position e of a slot's partial sums
+__device__ __forceinline__ int partial_col(int e) {
+    const int u = e % 32 / 2;
+    return e / 64 * 64 + (u / 4 + u % 4 * 4) * 4 + e % 64 / 32 * 2 + e % 2;
+}
+
+// raw[s][column] = sum over the rows of `partial` (and the two sums behind the columns), in a fixed order: thread (slice q, position c) adds
+// the rows of slice q of 16 in order, the 16 slice sums are then added in slice order.
+template <bool LANES>
+__global__ __launch_bounds__(1024) void lr_reduce_kernel(TrainArgs a) {
     __shared__ double sl[16][64];
     const int s = blockIdx.y;
     if (a.slots[s].phase == PH_IDLE) return;             // uniform
     const int c = threadIdx.x & 63, q = threadIdx.x >> 6;
-    const int e = blockIdx.x * 64 + c, nv = a.d + 2;
+    const int e = blockIdx.x * 64 + c, nv = a.pcols + 2;
     const double* p = a.partial + (long long)s * nv + (e < nv ? e : nv - 1);
     const int lo = q * a.nrows / 16, hi = (q + 1) * a.nrows / 16;
     double t = 0.0;
     for (int i0 = lo; i0 < hi; i0 += 16) {               // 16 independent loads (index clamped, surplus ignored)
         double v[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = p[(long long)min(i0 + i, hi - 1) * A * nv];
+        for (int i = 0; i < 16; ++i) v[i] = p[(long long)min(i0 + i, hi - 1) * a.nslots * nv];
 #pragma unroll
         for (int i = 0; i < 16; ++i) t += i0 + i < hi ? v[i] : 0.0;
     }
@@ -354,7 +588,8 @@ __global__ __launch_bounds__(1024) void lr_reduce_kernel(TrainArgs a, int A) {
         double r = 0.0;
 #pragma unroll
         for (int i = 0; i < 16; ++i) r += sl[i][c];
-        a.raw[(long long)s * nv + e] = r;
+        const int col = e >= a.pcols ? a.d + (e - a.pcols) : LANES ? partial_col(e) : e;
+        if (e >= a.pcols || col < a.d) a.raw[(long long)s * (a.d + 2) + col] = r;
     }
 }
 
@@ -715,26 +950,40 @@ PassShape pass_shape(int d) {
     if (pieces <= 4) return {1, 4};
     return {(pieces + 7) / 8, 8};
 }
+bool pass_mfma(int d) { return pass_shape(d).nj <= 2; }      // d <= 4096: the accumulators and vectors of four slots fit the registers
 // Slots of a pass: as many problems as the registers allow (four up to d = 4096, two above), and no more than there are.
 int pass_slots(int d, int n_C) {
-    const int most = pass_shape(d).nj <= 2 ? MAX_SLOTS : 2;
+    const int most = pass_mfma(d) ? MAX_SLOTS : 2;
     return n_C >= 3 ? most : n_C == 2 ? 2 : 1;
 }
 
 int launch_pass(const TrainArgs& a, int A, int grid, hipStream_t st) {
     const PassShape p = pass_shape(a.d);
+#define SJ_PASS_MFMA(NJ, CW)                                                                          \
+    if (p.nj == NJ && p.cw == CW) {                                                                   \
+        lr_pass_mfma_kernel<NJ, CW><<<grid, PASS_WAVES * 64, 0, st>>>(a);                             \
+        LAUNCHCHK("lr_pass_mfma");                                                                    \
+        return SJ_OK;                                                                                 \
+    }
+    SJ_PASS_MFMA(1, 1) SJ_PASS_MFMA(1, 2) SJ_PASS_MFMA(1, 4) SJ_PASS_MFMA(1, 8) SJ_PASS_MFMA(2, 8)
+#undef SJ_PASS_MFMA
 #define SJ_PASS(NJ, CW, AA)                                                                           \
     if (p.nj == NJ && p.cw == CW && A == AA) {                                                        \
         lr_pass_kernel<NJ, AA, CW><<<grid, PASS_WAVES * 64, 0, st>>>(a);                              \
         LAUNCHCHK("lr_pass");                                                                         \
         return SJ_OK;                                                                                 \
     }
-#define SJ_PASS3(NJ, CW) SJ_PASS(NJ, CW, 1) SJ_PASS(NJ, CW, 2) SJ_PASS(NJ, CW, 4)
-    SJ_PASS3(1, 1) SJ_PASS3(1, 2) SJ_PASS3(1, 4) SJ_PASS3(1, 8) SJ_PASS3(2, 8)
     SJ_PASS(3, 8, 1) SJ_PASS(3, 8, 2) SJ_PASS(4, 8, 1) SJ_PASS(4, 8, 2)
-#undef SJ_PASS3
 #undef SJ_PASS
     return fail(SJ_EINVAL, "d = %d above 8192 is not supported", a.d);
+}
+
+int launch_reduce(const TrainArgs& a, hipStream_t st) {
+    const dim3 grid((a.pcols + 2 + 63) / 64, a.nslots);
+    if (pass_mfma(a.d)) lr_reduce_kernel<true><<<grid, 1024, 0, st>>>(a);
+    else lr_reduce_kernel<false><<<grid, 1024, 0, st>>>(a);
+    LAUNCHCHK("lr_reduce");
+    return SJ_OK;
 }
 
 int launch_advance(const TrainArgs& a, int A, hipStream_t st) {
@@ -794,6 +1043,8 @@ extern "C" int sj_judge_train(const float* H_train, const int32_t* y_train, int6
     TrainArgs a{};
     a.H = H_train; a.y = y_train; a.n = n_train; a.d = d; a.n_C = n_C;
     a.vstride = d + 2;
+    a.nslots = A;
+    a.pcols = pass_mfma(d) ? pass_shape(d).cw * pass_shape(d).nj * 256 : d;
     a.nrows = grid * teams;
     double *C_dev, *score;
     int32_t *order_dev, *tp, *fp;
@@ -802,7 +1053,7 @@ extern "C" int sj_judge_train(const float* H_train, const int32_t* y_train, int6
     ar.want(a.slots, (size_t)A);
     ar.want(a.vecs, (size_t)A * V_COUNT * a.vstride);
     ar.want(a.D, (size_t)A * n_train);
-    ar.want(a.partial, (size_t)a.nrows * A * (d + 2));
+    ar.want(a.partial, (size_t)a.nrows * A * (a.pcols + 2));
     ar.want(a.raw, (size_t)A * (d + 2));
     ar.want(C_dev, (size_t)n_C);
     ar.want(order_dev, (size_t)n_C);
@@ -830,8 +1081,7 @@ extern "C" int sj_judge_train(const float* H_train, const int32_t* y_train, int6
     for (int64_t batch = 0;; ++batch) {
         for (int r = 0; r < BATCH; ++r) {
             if ((rc = launch_pass(a, A, grid, st))) return rc;
-            lr_reduce_kernel<<<dim3((d + 2 + 63) / 64, A), 1024, 0, st>>>(a, A);
-            LAUNCHCHK("lr_reduce");
+            if ((rc = launch_reduce(a, st))) return rc;
             if ((rc = launch_advance(a, A, st))) return rc;
         }
         HIPCHK(hipMemcpyAsync(ar.done_host + (batch & 1), a.queue + 1, sizeof(int32_t), hipMemcpyDeviceToHost, st));

@@ -162,3 +162,18 @@ def test_features_that_are_not_finite_do_not_converge(value, d):
         sj.sj_judge_train(_dev(bad), yd, _dev(H), yd, [0.1, 1.0, 10.0])
     assert e.value.code == -3
     assert sj.sj_judge_train(_dev(H), yd, _dev(H), yd, [0.1])["passes"][0] > 0
+
+
+@pytest.mark.parametrize("n,d,n_C", [(1027, 256, 4), (1026, 260, 3), (2049, 508, 1), (300, 1028, 2), (1029, 4096, 3), (1030, 4092, 4), (40, 4100, 2), (41, 8188, 2)])
+def test_every_model_is_stationary_at_the_edges_of_the_pass(n, d, n_C):
+    """Whole and cut column pieces of a wave, groups of rows with one, two and three rows over, one to four slots in use: the gradient in
+    64 bits on the CPU.  Bound: the solver's own tolerance, 1e-11 max(1, C n), and the rounding of its sums and of these."""
+    H, y = synth.make_judge_dataset(41, n, d)
+    y[:2] = [0, 1]
+    grid = np.logspace(-2, 0.0, n_C)
+    out = sj.sj_judge_train(_dev(H), _dev(y), _dev(H), _dev(y), grid, torch.cuda.current_stream())
+    x = np.concatenate([H.astype(np.float64), np.ones((n, 1))], axis=1)
+    for c in range(n_C):
+        w = out["w_all"][c]
+        g = np.append(w[:d], 0.0) + grid[c] * (x.T @ (1.0 / (1.0 + np.exp(-(x @ w))) - y))
+        assert np.abs(g).max() <= 2e-11 * max(1.0, grid[c] * n) + 1e-12 * np.abs(x).sum(axis=0).max() * grid[c]
