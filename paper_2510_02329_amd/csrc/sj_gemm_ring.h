@@ -1,226 +1,269 @@
-// Few-row weight-streaming GEMM with the weights delivered through an LDS ring by loader waves:
-// Y[R][N] = X[R][K] * W[N][K]^T, R <= 16, W in the re-tiled layout (paper: the projections of the target
-// forward, Eq. 2 / Eq. 4).  Same arguments, grid meaning (x: groups of NT n-tiles, y: K-slices) and
-// epilogues as gemm_skinny_kernel; it is a candidate launch shape that the start-up measurement may pick.
+// Few-row weight-streaming GEMM with the weights delivered through LDS, every wave keeping a ring of its own: Y[R][N] = X[R][K] * W[N][K]^T,
+// R <= 16 MT (MT = 1 or 2 row tiles), W in the re-tiled layout (paper: the projections of the target forward, Eq. 2 / Eq. 4).  Same
+// arguments, grid meaning (x: groups of NT n-tiles, y: K-slices) and epilogues as gemm_skinny_kernel, whose loads go to registers.
 //
-// Why a second kernel: in the register-ring kernel a wave alternates between requesting and consuming, and
-// its requests are bounded by its registers.  Here two LOADER waves do nothing but issue direct
-// global->LDS loads with the streaming cache policy, a ring of NSA stages of 8 KB ahead of the consumers
-// (measured on this part: 7.2 TB/s sustained against 6.1 TB/s with the default policy and 7.0 TB/s for a
-// plain read kernel), and eight COMPUTE waves read one 1 KB fragment each per stage.
+// Eight waves interleave K: wave w multiplies k-steps ks0 + 8 kb + w of the slice, so the workgroup pulls 8 KB of consecutive memory per tile
+// and k-block.  Everything a wave multiplies - NT weight fragments and the operand fragments (one packed, or MT x planes) of its k-step - comes
+// by direct global->LDS loads into DEPTH fragments of 1 KB of LDS that no other wave touches: a k-block that the wave has read into registers
+// makes room at once for the fragments DEPTH places on, and the only wait is the wave's own count of loads.  No barrier before the reduction,
+// no loader waves.  The 8 waves' accumulators meet in LDS (the rings' memory, free by then) and are added in wave order: deterministic, and the
+// same sums for every NT and DEPTH.
 //
-// Stage = one n-tile x 8 consecutive k-steps = 8 KB of consecutive memory (the re-tiled layout keeps a
-// tile's k-steps contiguous).  Compute wave w multiplies fragment w of every stage, i.e. k-steps
-// ks0 + 8 kb + w of the slice: the waves interleave K, so the workgroup pulls one contiguous stream per
-// tile, and a wave's operand fragment changes only every NT stages.  One LDS-only barrier per stage keeps
-// loaders and consumers in lock step.  The 8 waves' accumulators meet in LDS (the ring's memory, free by
-// then) and are added in wave order: deterministic.
+// What bounds it: the stream, and the 3 - 4 us that a launch spends before its first fragment and after its last.  us a launch, back to back on
+// rotating weights, before (two loader waves feeding a workgroup-wide ring of 8 KB stages, one barrier a stage; above 8 rows the
+// register-ring kernel) and now: 8B shape, 6 rows: gate / up 39.2 -> 37.4 (6.3 TB/s), QKV 10.6 -> 10.2, O 8.9 -> 8.5, down 22.0 -> 22.0,
+// LM head 172 -> 164 (6.4); 20 rows: gate / up 43.0 -> 39.0, QKV 12.8 -> 11.4, down 23.5 -> 21.6, LM head 201 -> 191; 1B, 1 row: gate / up
+// 14.1 -> 13.0, QKV 5.6 -> 4.9, O 5.2 -> 4.7, LM head 82.5 -> 76.7; 12 rows: gate / up 15.0 -> 13.8, down 9.6 -> 8.6, QKV 6.1 -> 5.2, LM head
+// 104 -> 92; 70B, 24 rows: gate / up 154 -> 147, down 78 -> 72, QKV 31.4 -> 28.8, O 26.3 -> 24.8.
+// DEPTH: 9 leaves room for two workgroups a CU, 18 for one.  More is not better: 1B gate / up, four n-tiles, 6 / 12 / 18 fragments: 14.8 / 16.6 /
+// 18.1 us; two n-tiles, 4 / 9 / 12: 13.2 / 13.0 / 14.7.  Every workgroup starting at another k-block changed nothing.
 //
-// PACK (two operand planes, at most 8 rows): MFMA row r < 8 of the B operand carries plane 0 of row r,
-// row r + 8 plane 1 of the same row, so ONE product per weight fragment yields both planes' contributions
-// in output columns r and r + 8, which the reduction adds (hi first).  Without PACK one product per plane.
-// The operand of such a block is stored that way, too (packed planes: one plane whose rows 8 - 15 are plane 1).
+// PACK (two operand planes, at most 8 rows): MFMA row r < 8 of the B operand carries plane 0 of row r, row r + 8 plane 1 of the same row, so ONE
+// product per weight fragment yields both planes' contributions in output columns r and r + 8, which the reduction adds (hi first).
+// Without PACK one product per plane.  The operand of such a block is stored that way, too (packed planes: one plane whose rows
+// 8 - 15 are plane 1).
 #pragma once
 #include "sj_kernels.h"
 #include "sj_plan.h"
 
 namespace sj {
 
-constexpr int RING_THREADS = (RING_CW + RING_LW) * 64;
-
-// the loader's last NSA - 1 iterations: iteration I may leave NSA - 3 - I stages of its loads in flight
-template <int I, int NSA, int PER>
-__device__ __forceinline__ void ring_tail_waits() {
-    if constexpr (I < NSA - 1) {
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm((NSA - 3 - I > 0 ? NSA - 3 - I : 0) * PER));
-        lds_barrier();
-        ring_tail_waits<I + 1, NSA, PER>();
-    }
+// N fragments at 32-bit LDS addresses, waited for in the same block: as ordinary reads they would wait for every direct load of the wave,
+// since the compiler cannot tell which of them the data came with.
+template <int N> __device__ __forceinline__ void lds_frags(u32x4 (&v)[N], const unsigned (&at)[N]);
+#define SJ_LDS_FRAGS_OUT1 "=&v"(v[0])
+#define SJ_LDS_FRAGS_OUT2 SJ_LDS_FRAGS_OUT1, "=&v"(v[1])
+#define SJ_LDS_FRAGS_OUT3 SJ_LDS_FRAGS_OUT2, "=&v"(v[2])
+#define SJ_LDS_FRAGS_OUT4 SJ_LDS_FRAGS_OUT3, "=&v"(v[3])
+#define SJ_LDS_FRAGS_OUT5 SJ_LDS_FRAGS_OUT4, "=&v"(v[4])
+#define SJ_LDS_FRAGS_OUT6 SJ_LDS_FRAGS_OUT5, "=&v"(v[5])
+template <> __device__ __forceinline__ void lds_frags(u32x4 (&v)[1], const unsigned (&at)[1]) {
+    asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)" : SJ_LDS_FRAGS_OUT1 : "v"(at[0]) : "memory");
+}
+template <> __device__ __forceinline__ void lds_frags(u32x4 (&v)[2], const unsigned (&at)[2]) {
+    asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)" : SJ_LDS_FRAGS_OUT2 : "v"(at[0]), "v"(at[1]) : "memory");
+}
+template <> __device__ __forceinline__ void lds_frags(u32x4 (&v)[3], const unsigned (&at)[3]) {
+    asm volatile("ds_read_b128 %0, %3\n\tds_read_b128 %1, %4\n\tds_read_b128 %2, %5\n\ts_waitcnt lgkmcnt(0)"
+                 : SJ_LDS_FRAGS_OUT3 : "v"(at[0]), "v"(at[1]), "v"(at[2]) : "memory");
+}
+template <> __device__ __forceinline__ void lds_frags(u32x4 (&v)[4], const unsigned (&at)[4]) {
+    asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\ts_waitcnt lgkmcnt(0)"
+                 : SJ_LDS_FRAGS_OUT4 : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]) : "memory");
+}
+template <> __device__ __forceinline__ void lds_frags(u32x4 (&v)[5], const unsigned (&at)[5]) {
+    asm volatile("ds_read_b128 %0, %5\n\tds_read_b128 %1, %6\n\tds_read_b128 %2, %7\n\tds_read_b128 %3, %8\n\tds_read_b128 %4, %9\n\ts_waitcnt lgkmcnt(0)"
+                 : SJ_LDS_FRAGS_OUT5 : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "v"(at[4]) : "memory");
+}
+template <> __device__ __forceinline__ void lds_frags(u32x4 (&v)[6], const unsigned (&at)[6]) {
+    asm volatile("ds_read_b128 %0, %6\n\tds_read_b128 %1, %7\n\tds_read_b128 %2, %8\n\tds_read_b128 %3, %9\n\tds_read_b128 %4, %10\n\tds_read_b128 %5, %11\n\t"
+                 "s_waitcnt lgkmcnt(0)" : SJ_LDS_FRAGS_OUT6 : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "v"(at[4]), "v"(at[5]) : "memory");
 }
 
-template <typename T, int NT, int EPI, int SPL, bool PACK, int NSA>
-__global__ __launch_bounds__(RING_THREADS) void gemm_ring_kernel(GemmArgs a) {
-    static_assert(!PACK || SPL == 2, "packing is for two planes");
-    static_assert(NSA >= 3 && (NSA & (NSA - 1)) == 0, "ring depth: a power of two");
-    constexpr int KF = Traits<T>::KF, KSTEP = Traits<T>::KSTEP;
-    constexpr int PER = RING_CW / RING_LW;             // fragments per loader wave and stage
-    constexpr int LDS_STAGES = NSA > NT ? NSA : NT;    // the reduction needs NT x 8 KB
-    static_assert((NSA - 1) * PER < 64, "the load counter holds 63");
-    __shared__ u32x4 ring[LDS_STAGES][RING_CW][64];
+template <typename F, int... Q> __device__ __forceinline__ void each_const(std::integer_sequence<int, Q...>, F f) { (f(std::integral_constant<int, Q>{}), ...); }
+
+// KB of LDS a wave has a use for: its ring, then its accumulators
+constexpr int ring_lds(int depth, int nt, int mt, int nb) { return depth > nt + nb ? (depth > nt * mt ? depth : nt * mt) : (nt + nb > nt * mt ? nt + nb : nt * mt); }
+
+template <typename T, int NT, int MT, int EPI, int SPL, bool PACK, int DEPTH>
+__global__ __launch_bounds__(RING_CW * 64, ring_lds(DEPTH, NT, MT, ring_operand(PACK, SPL, MT)) <= RING_TWO ? 4 : 2) void gemm_ring_kernel(GemmArgs a) {
+    static_assert(!PACK || (SPL == 2 && MT == 1), "packing is for two planes of one row tile");
+    constexpr int KSTEP = Traits<T>::KSTEP;
+    constexpr int NB = ring_operand(PACK, SPL, MT), PER = NB + NT; // fragments of a k-block, the operand's first
+    constexpr int D = DEPTH < PER ? PER : DEPTH;                  // fragments of a wave's ring: a k-block at least
+    constexpr int CH = (PER + 5) / 6, CF = (PER + CH - 1) / CH;   // read in CH chunks of CF
+    constexpr int TAIL = (D + PER - 1) / PER;                     // last k-blocks, behind which some of a k-block's places have no successor
+    static_assert(D < 64, "the load counter holds 63");
+    __shared__ u32x4 lds[RING_CW * ring_lds(DEPTH, NT, MT, NB) * 64];
     __shared__ float inv_rms[16];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int r = lane & 15, g = lane >> 4;
-    const int KS = a.K / KSTEP;
-    const int nt0 = blockIdx.x * NT;
-    // K-slices of whole stages (the host launches this kernel only when KS / gridDim.y is a multiple of 8)
-    const int nkb = KS / RING_CW / (int)gridDim.y;
-    const int ks0 = blockIdx.y * nkb * RING_CW;
-    const int nstages = nkb * NT;                      // >= NSA (host-checked)
+    const int KS = a.K / KSTEP, nt0 = blockIdx.x * NT;
+    const int nkb = KS / RING_CW / (int)gridDim.y, ks0 = blockIdx.y * nkb * RING_CW;     // whole k-blocks, at least TAIL (ring_fits)
 
-    if (w >= RING_CW) {
-        // ---------------- loader waves: stage s = (k-block s / NT, tile s % NT) -> buffer s % NSA ----------------
-        const int lw = w - RING_CW;
-        const char* src = reinterpret_cast<const char*>(a.Wt) + (((size_t)nt0 * KS + ks0 + lw * PER) * 64 + lane) * 16;
-        const size_t tile_step = (size_t)KS * 1024;                   // next tile, same k-block
-        const size_t kb_step = (size_t)RING_CW * 1024 - (size_t)(NT - 1) * tile_step;   // first tile of the next k-block
-        int t = 0, buf = 0;
-        auto issue = [&]() {
-            u32x4* dst = &ring[buf][lw * PER][0];
-#pragma unroll
-            for (int j = 0; j < PER; ++j)
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + j * 1024),
-                                                 (__attribute__((address_space(3))) void*)(dst + j * 64), 16, 0, 2);
-            buf = (buf + 1) & (NSA - 1);
-            if (++t == NT) { t = 0; src += kb_step; } else src += tile_step;
-        };
-#pragma unroll
-        for (int s = 0; s < NSA - 1; ++s) issue();
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm((NSA - 2) * PER));       // stage 0 has landed
-        lds_barrier();
-        // iteration s: buffer (s - 1) % NSA was read before the barrier that ended iteration s - 1
-        for (int s = 0; s + NSA - 1 < nstages; ++s) {
-            issue();
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm((NSA - 2) * PER));   // stage s + 1 has landed
-            lds_barrier();
-        }
-        // everything is requested: the last NSA - 1 iterations only wait, for one stage less each
-        ring_tail_waits<0, NSA, PER>();
-        __syncthreads();                               // the reduction's barrier (every wave of the workgroup arrives)
-        return;
-    }
-
-    // ---------------- compute waves ----------------
-    constexpr int NB = PACK ? 1 : SPL;                 // operand fragments (products) per weight fragment
-    // fragment of k-step ks0 + w; packed planes are one plane of 16 rows (lanes of rows past R repeat row 0 of their plane)
-    const int xr = PACK ? ((r & 7) < a.R ? r : r & 8) : (r < a.R ? r : 0);
-    const T* Xr[NB];
-#pragma unroll
-    for (int sp = 0; sp < NB; ++sp)
-        Xr[sp] = reinterpret_cast<const T*>(a.X) + (size_t)sp * a.xplane + ((size_t)(ks0 + w) * 64 + (a.rm ? xr * 4 + g : g * 16 + xr)) * KF;
-    f32x4 acc[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // Operand fragments of the next DB - 1 k-blocks are requested ahead.  With several n-tiles per workgroup a k-block lasts
-    // several stages and one block ahead covers the L2; with one tile a stage is a block (0.3 us at the streaming rate).
-    constexpr int DB = NT == 1 ? 4 : 2;
-    Frag fb[DB][NB];
-    auto load_b = [&](Frag (&f)[NB], int kb) {
-#pragma unroll
-        for (int sp = 0; sp < NB; ++sp) f[sp].u = *reinterpret_cast<const u32x4*>(Xr[sp] + (size_t)kb * (RING_CW * 16 * KSTEP));
-    };
-    // what the epilogue needs from memory, requested (and the row factors finished) while the first stage is on its way
-    f32x4 res_x = f32x4{0.f, 0.f, 0.f, 0.f};
-    float res_g[4] = {0.f, 0.f, 0.f, 0.f};
+    // what the end needs from memory, in front of the stream (loads are counted in order): the residual stream and gain of the tiles that this
+    // wave finishes, and the shares of the rows' sums of squares (at most 8 rows)
+    constexpr int FIN = (NT * MT + RING_CW - 1) / RING_CW;        // (tile, row tile) pairs a wave finishes: w, w + 8, ..
+    f32x4 res_x[FIN];
+    float res_g[FIN][4];
     if constexpr (EPI == EPI_RESID) {
-        if (w < NT) {
-            const int row = lane >> 2, col = (nt0 + w) * 16 + (lane & 3) * 4;
-            if (row < a.R) res_x = *reinterpret_cast<const f32x4*>(a.x + (size_t)row * a.N + col);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) res_g[i] = Traits<T>::load(reinterpret_cast<const T*>(a.gain) + col + i);
+        for (int f = 0; f < FIN; ++f) {
+            const int p = min(w + f * RING_CW, NT * MT - 1), row = min(p / NT * 16 + (lane >> 2), a.R - 1), col = (nt0 + p % NT) * 16 + (lane & 3) * 4;
+            res_x[f] = *reinterpret_cast<const f32x4*>(a.x + (size_t)row * a.N + col);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) res_g[f][i] = Traits<T>::load(reinterpret_cast<const T*>(a.gain) + col + i);
         }
     }
-    if (a.ss_in) {                                     // uniform
-        for (int row = w; row < a.R; row += RING_CW) {
-            const float inv = row_inv_rms(a, row, lane);
-            if (lane == 0) inv_rms[row] = inv;
-        }
+    constexpr bool SS = EPI == EPI_PARTIAL || EPI == EPI_SWIGLU;  // the products that follow a residual epilogue
+    const int nss = a.K / 16;                                     // a multiple of 4
+    float4 ssv[2];                                                // of a row of up to 8192 columns
+    if constexpr (SS) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            ssv[i] = *reinterpret_cast<const float4*>(a.ss_in ? a.ss_in + (size_t)min(w, a.R - 1) * nss + min(lane * 4 + i * 256, nss - 4)
+                                                              : reinterpret_cast<const float*>(a.X));   // (any valid address: no load under a branch)
     }
-#pragma unroll
-    for (int j = 0; j < DB - 1; ++j) load_b(fb[j], min(j, nkb - 1));
-    lds_barrier();                                     // stage 0 is in LDS
-    int buf = 0;
-    for (int kb0 = 0; kb0 < nkb; kb0 += DB)
-#pragma unroll
-        for (int j = 0; j < DB; ++j) {
-            load_b(fb[(j + DB - 1) % DB], min(kb0 + j + DB - 1, nkb - 1));   // always issued: no load under a branch
-            if (kb0 + j < nkb) {                       // uniform
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    Frag fa;
-                    fa.u = ring[buf][w][lane];
-#pragma unroll
-                    for (int sp = 0; sp < NB; ++sp) Traits<T>::mma(fa, fb[j][sp], acc[t]);
-                    buf = (buf + 1) & (NSA - 1);
-                    lds_barrier();                     // this buffer is free; the next stage has landed
-                }
-            }
-        }
+    asm volatile("" ::: "memory");                                // (not behind the stream's requests)
 
-    // every stage has been read (last barrier above): the ring's memory now holds the 8 waves' accumulators,
-    // red[w][t][row * 16 + n] with D[n = 4g + i][row = r] in lane 16g + r
-    float* red = reinterpret_cast<float*>(&ring[0][0][0]);
+    // place i = kb * PER + j of the stream: j < NB operand fragment j of the k-block, else weight fragment j - NB
+    u32x4* mine = lds + w * D * 64;
+    const char* wsrc = reinterpret_cast<const char*>(a.Wt) + (((size_t)nt0 * KS + ks0 + w) * 64 + lane) * 16;
+    const char* xsrc[MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+        const int row = m * 16 + (PACK ? r & 7 : r), xr = (PACK ? r & 8 : 0) + (row < a.R ? (PACK ? r & 7 : r) : 0);   // lanes of rows past R repeat the first of the tile
+        xsrc[m] = reinterpret_cast<const char*>(a.X) + (((size_t)m * KS + ks0 + w) * 64 + (a.rm ? xr * 4 + g : g * 16 + xr)) * 16;
+    }
+    const size_t tile_step = (size_t)KS * 1024;
+    auto request = [&](auto jc, int kb, int slot) {
+        constexpr int j = decltype(jc)::value;
+        const size_t at = (size_t)kb * (RING_CW * 1024);
+        auto dst = (__attribute__((address_space(3))) void*)(mine + slot * 64);
+        if constexpr (j < NB)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(xsrc[j / (PACK ? 1 : SPL)] + (j % (PACK ? 1 : SPL)) * a.xplane * sizeof(T) + at), dst, 16, 0, 0);
+        else
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(wsrc + (j - NB) * tile_step + at), dst, 16, 0, 2);
+    };
+    each_const(std::make_integer_sequence<int, D>{}, [&](auto ic) { request(std::integral_constant<int, decltype(ic)::value % PER>{}, decltype(ic)::value / PER, decltype(ic)::value); });
+
+    if constexpr (SS) {
+        if (a.ss_in && w < a.R) {                                 // uniform
+            float s = lane * 4 < nss ? (ssv[0].x + ssv[0].y) + (ssv[0].z + ssv[0].w) : 0.f;
+            if (lane * 4 + 256 < nss) s += (ssv[1].x + ssv[1].y) + (ssv[1].z + ssv[1].w);
+            for (int e = lane * 4 + 512; e < nss; e += 256) {
+                const float4 v = *reinterpret_cast<const float4*>(a.ss_in + (size_t)w * nss + e);
+                s += (v.x + v.y) + (v.z + v.w);
+            }
+            s = wave_sum(s);
+            if (lane == 0) inv_rms[w] = 1.0f / sqrtf(s / (float)a.K + a.eps);
+        }
+    }
+
+    f32x4 acc[NT][MT];
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) red[(w * NT + t) * 256 + r * 16 + 4 * g + i] = acc[t][i];
-    __syncthreads();
-    if constexpr (EPI != EPI_LOGITS && NT <= RING_CW) {
-        // One wave per tile, four neighbouring columns of a row per lane (lane l: row l / 4, columns 4 (l % 4) ..):
-        // 16-byte LDS reads and 8- or 16-byte stores, seven waves at work instead of four threads' worth of scalar
-        // reads per tile (the scalar form below took 2.9 us of the 39 us gate/up launch).  Same sums in the same order.
-        if (w >= NT) return;
-        const int t = w, row = lane >> 2, n0 = (lane & 3) * 4;
-        auto sum_at = [&](int pos) {
-            f32x4 sum = *reinterpret_cast<const f32x4*>(red + t * 256 + pos);
+        for (int m = 0; m < MT; ++m) acc[t][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const unsigned base = (unsigned)(unsigned long long)(const __attribute__((address_space(3))) void*)mine + lane * 16;
+    int slot0 = 0;                                                // place of the k-block's first fragment
+    // one k-block; LEFT = k-blocks from here to the end (TAIL + 1: more)
+    auto step = [&](auto left_c, int kb) {
+        constexpr int LEFT = decltype(left_c)::value;
+        constexpr int END = LEFT > TAIL ? 1 << 20 : LEFT * PER;   // places of the stream that are left, from this k-block's first
+        Frag f[PER];
+        each_const(std::make_integer_sequence<int, CH>{}, [&](auto cc) {
+            constexpr int c0 = decltype(cc)::value * CF, n = c0 + CF < PER ? CF : PER - c0;
+            // requested so far: up to place c0 + D, where there are so many; this chunk ends at c0 + n
+            constexpr int out = (c0 + D < END ? c0 + D : END) - (c0 + n);
+            __builtin_amdgcn_s_waitcnt(vmcnt_imm(out));
+            unsigned at[n];
+            u32x4 v[n];
+            int slot[n];
 #pragma unroll
-            for (int ww = 1; ww < RING_CW; ++ww) sum += *reinterpret_cast<const f32x4*>(red + (ww * NT + t) * 256 + pos);
-            return sum;
-        };
-        f32x4 v = sum_at(lane * 4);
-        if constexpr (PACK) v += sum_at(((lane + 32) & 63) * 4);   // the second plane's products sit 8 rows further on
-        if (a.ss_in && row < a.R) v *= inv_rms[row];
-        if constexpr (EPI == EPI_RESID) {
-            f32x4 xv = res_x + v;
-            const int col = (nt0 + t) * 16 + n0;
-            float ss = 0.f;
-            if (row < a.R) {
-                *reinterpret_cast<f32x4*>(a.x + (size_t)row * a.N + col) = xv;
-                float y[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) { y[i] = xv[i] * res_g[i]; ss += xv[i] * xv[i]; }
-                Traits<T>::template store_split4<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, col, a.N, a.rm), a.actplane, y);
+            for (int i = 0; i < n; ++i) {
+                const int s = slot0 + c0 + i;                     // < 2 D: PER <= D
+                slot[i] = s >= D ? s - D : s;
+                at[i] = base + slot[i] * 1024;
             }
-            ss += __shfl_xor(ss, 1, 64);
-            ss += __shfl_xor(ss, 2, 64);
-            if (row < a.R && (lane & 3) == 0) a.ss_out[(size_t)row * (a.N / 16) + nt0 + t] = ss;
-            return;
-        }
-        if constexpr (EPI == EPI_PARTIAL) {
-            if (row < a.R)
-                *reinterpret_cast<f32x4*>(a.out + ((size_t)blockIdx.y * a.slice_rows + row) * a.N + (size_t)(nt0 + t) * 16 + n0) = v;
-        } else {
-            // tile column n < 8 is gate of FFN column 8 * tile + n, column n + 8 its up projection: two lanes further on
-            f32x4 up;
+            lds_frags(v, at);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) up[i] = __shfl_down(v[i], 2, 64);
-            if (row < a.R && n0 < 8) {
-                float y[4];
+            for (int i = 0; i < n; ++i) f[c0 + i].u = v[i];
+            each_const(std::make_integer_sequence<int, n>{}, [&](auto ic) {
+                constexpr int i = decltype(ic)::value, next = c0 + i + D;
+                if constexpr (next < END) request(std::integral_constant<int, next % PER>{}, kb + next / PER, slot[i]);
+            });
 #pragma unroll
-                for (int i = 0; i < 4; ++i) y[i] = v[i] / (1.0f + expf(-v[i])) * up[i];
-                Traits<T>::template store_split4<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, (nt0 + t) * 8 + n0, a.N / 2, a.rm), a.actplane, y);
+            for (int i = 0; i < n; ++i)
+                if (c0 + i >= NB) {
+#pragma unroll
+                    for (int m = 0; m < MT; ++m)
+#pragma unroll
+                        for (int sp = 0; sp < NB / MT; ++sp) Traits<T>::mma(f[c0 + i], f[m * (NB / MT) + sp], acc[c0 + i - NB][m]);
+                }
+        });
+        slot0 += PER;
+        if (slot0 >= D) slot0 -= D;
+    };
+    int kb = 0;
+    for (; kb < nkb - TAIL; ++kb) step(std::integral_constant<int, TAIL + 1>{}, kb);
+    each_const(std::make_integer_sequence<int, TAIL>{}, [&](auto qc) { step(std::integral_constant<int, TAIL - decltype(qc)::value>{}, kb + decltype(qc)::value); });
+
+    __syncthreads();                                              // every wave is done with its ring
+    float* red = reinterpret_cast<float*>(lds);                   // [wave][tile][row tile][row * 16 + n], D[n = 4g + i][row = r] in lane 16g + r
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int m = 0; m < MT; ++m) *reinterpret_cast<f32x4*>(red + ((w * MT + m) * NT + t) * 256 + r * 16 + 4 * g) = acc[t][m];
+    __syncthreads();
+    if constexpr (EPI != EPI_LOGITS) {
+        // one wave per tile, four neighbouring columns of a row per lane (lane l: row l / 4, columns 4 (l % 4) ..)
+#pragma unroll
+        for (int f = 0; f < FIN; ++f) {
+            const int p = w + f * RING_CW;
+            if (p >= NT * MT) return;                             // uniform
+            const int t = p % NT, row = p / NT * 16 + (lane >> 2), n0 = (lane & 3) * 4;
+            auto sum_at = [&](int pos) {
+                f32x4 sum = *reinterpret_cast<const f32x4*>(red + p * 256 + pos);
+#pragma unroll
+                for (int ww = 1; ww < RING_CW; ++ww) sum += *reinterpret_cast<const f32x4*>(red + (ww * NT * MT + p) * 256 + pos);
+                return sum;
+            };
+            f32x4 v = sum_at(lane * 4);
+            if constexpr (PACK) v += sum_at(((lane + 32) & 63) * 4);   // the second plane's products sit 8 rows further on
+            if constexpr (SS) {
+                if (a.ss_in && row < a.R) v *= inv_rms[row];
+            }
+            if constexpr (EPI == EPI_RESID) {
+                const f32x4 xv = res_x[f] + v;
+                const int col = (nt0 + t) * 16 + n0;
+                float ss = 0.f;
+                if (row < a.R) {
+                    *reinterpret_cast<f32x4*>(a.x + (size_t)row * a.N + col) = xv;
+                    float y[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) { y[i] = xv[i] * res_g[f][i]; ss += xv[i] * xv[i]; }
+                    Traits<T>::template store_split4<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, col, a.N, a.rm), a.actplane, y);
+                }
+                ss += __shfl_xor(ss, 1, 64);
+                ss += __shfl_xor(ss, 2, 64);
+                if (row < a.R && (lane & 3) == 0) a.ss_out[(size_t)row * (a.N / 16) + nt0 + t] = ss;
+            } else if constexpr (EPI == EPI_PARTIAL) {
+                if (row < a.R)
+                    *reinterpret_cast<f32x4*>(a.out + ((size_t)blockIdx.y * a.slice_rows + row) * a.N + (size_t)(nt0 + t) * 16 + n0) = v;
+            } else {
+                // tile column n < 8 is gate of FFN column 8 * tile + n, column n + 8 its up projection: two lanes further on
+                f32x4 up;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) up[i] = __shfl_down(v[i], 2, 64);
+                if (row < a.R && n0 < 8) {
+                    float y[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) y[i] = v[i] / (1.0f + expf(-v[i])) * up[i];
+                    Traits<T>::template store_split4<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, (nt0 + t) * 8 + n0, a.N / 2, a.rm), a.actplane, y);
+                }
             }
         }
         return;
     }
     if (threadIdx.x >= 256) return;
-    const int tid = threadIdx.x, er = tid >> 4, en = tid & 15;
-    float v[NT];
+    const int tid = threadIdx.x;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        float sum = red[t * 256 + tid];
+    for (int m = 0; m < MT; ++m) {
+        float v[NT];
 #pragma unroll
-        for (int ww = 1; ww < RING_CW; ++ww) sum += red[(ww * NT + t) * 256 + tid];
-        if constexpr (PACK) {
-            // the second plane's products sit 8 rows further on (threads of rows >= 8 read in-bounds values they never store)
-            const int o = (tid + 128) & 255;
-            float lo = red[t * 256 + o];
+        for (int t = 0; t < NT; ++t) {
+            auto sum_at = [&](int pos) {
+                float sum = red[(m * NT + t) * 256 + pos];
 #pragma unroll
-            for (int ww = 1; ww < RING_CW; ++ww) lo += red[(ww * NT + t) * 256 + o];
-            sum += lo;
+                for (int ww = 1; ww < RING_CW; ++ww) sum += red[((ww * MT + m) * NT + t) * 256 + pos];
+                return sum;
+            };
+            v[t] = sum_at(tid);
+            if constexpr (PACK) v[t] += sum_at((tid + 128) & 255);
         }
-        v[t] = sum;
+        few_epilogue<T, NT, EPI, SPL>(a, v, m * 16 + (tid >> 4), tid & 15, nt0);
     }
-    few_epilogue<T, NT, EPI, SPL>(a, v, er, en, nt0);
 }
 
 }  // namespace sj

@@ -114,7 +114,7 @@ struct sj_kv : Forward {       // the inherited buffers serve the blocks of up t
     GemmPlan plan_gu;                             // gate / up projection with few rows (no K-slices)
     GemmPlan plan_lm{8, 4, 1, 2};                 // LM head with few rows
     int mode = SJ_MODE_TWO_STAGE;
-    int ring_rows = RING_PACK_ROWS;       // the rules take the LDS-ring kernel up to this many rows
+    int ring_rows = RING_ROWS;            // the rules take the LDS-ring kernel up to this many rows
     int planes = 2;            // bf16 planes of the activation operand (fp32 storage: always 1)
     int32_t* pinned_state = nullptr;      // [2*batch] staging of sj_kv_rewind
     hipEvent_t rewind_done = nullptr;
@@ -321,6 +321,15 @@ constexpr int PREFILL_ROWS = 4 * ROWS_MT * 16;
 
 static int tune_plans(sj_kv* kv, int rows);
 
+// The LM head's launch shape by the rule; planes of its operand: one for hidden states handed in by the caller of a head-only model.
+static void rule_lm_head(sj_kv* kv, int planes) {
+    const sj_config& c = kv->m->cfg;
+    kv->plan_lm = rule_logits(c.vocab / 16);
+    if (c.dtype != SJ_DTYPE_BF16 || planes > 2 || kv->max_rows > kv->ring_rows) return;
+    const GemmPlan l = ring_rule_logits(c.vocab / 16, c.d_model / 32, kv->max_rows, planes);
+    if (l.waves) kv->plan_lm = l;
+}
+
 // the launch shapes the rule gives (before any measurement)
 static void rule_plans(sj_kv* kv) {
     const sj_config& c = kv->m->cfg;
@@ -332,24 +341,22 @@ static void rule_plans(sj_kv* kv) {
         kv->plan_d[i] = plan_partial(d / 16, F / kstep, i == 0);
     }
     kv->plan_gu = rule_gate_up(2 * F / 16, kv->planes);
-    kv->plan_lm = rule_logits(c.vocab / 16);
-    // at most 8 rows with two bf16 planes: the LDS-ring kernel where a shape of it fits (3 - 8 % faster on the
-    // 8B-shaped projections at 6 rows; the start-up measurement may still prefer another shape)
-    // (SJ_RING_ROWS = 0..16 moves the row limit of this rule; from 9 rows on, and with one plane, the kernel takes one
-    // product per plane and measures equal to the register-ring kernel)
+    // bf16 with one or two planes: the LDS-ring kernel where a shape of it fits (4 - 13 % faster than the register-ring kernel from 1 to 32 rows; the
+    // start-up measurement may still prefer another shape).  SJ_RING_ROWS = 0..32 moves the row limit of this rule.
     if (const char* e = std::getenv("SJ_RING_ROWS")) kv->ring_rows = std::min(std::max(std::atoi(e), 0), RING_ROWS);
     if (c.dtype == SJ_DTYPE_BF16 && kv->planes <= 2 && kv->max_rows <= kv->ring_rows) {
-        const GemmPlan rq = ring_rule_partial((Nq + 2 * Nk) / 16, d / kstep), ro = ring_rule_partial(d / 16, Nq / kstep),
-                       rd = ring_rule_partial(d / 16, F / kstep);
-        if (rq.waves) kv->plan_qkv[0] = rq;
-        if (ro.waves) kv->plan_o[0] = ro;
-        if (rd.waves) kv->plan_d[0] = rd;
-        const bool few_gu = kv->plan_gu.nt == 1, few_lm = kv->plan_lm.nt == 2;     // small matrices: four n-tiles, the fewest with a ring
-        const GemmPlan g{few_gu ? 4 : kv->plan_gu.nt, RING_WAVES, 1, few_gu ? 4 : 8};
-        if (ring_fits(g, 2 * F / 16, d / kstep, 1, 2, true)) kv->plan_gu = g;
-        const GemmPlan l{few_lm ? 4 : 8, RING_WAVES, 1, few_lm ? 8 : 4};
-        if (ring_fits(l, c.vocab / 16, d / kstep, 1, 2, true)) kv->plan_lm = l;
+        const int rows = kv->max_rows;
+        auto partial = [&](GemmPlan& plan, int N, int K) {
+            const GemmPlan r = rows <= RING_PACK_ROWS ? ring_rule_partial(N / 16, K / kstep) : ring_rule_partial_rows(N / 16, K / kstep, rows, kv->planes);
+            if (r.waves) plan = r;
+        };
+        partial(kv->plan_qkv[0], Nq + 2 * Nk, d);
+        partial(kv->plan_o[0], d, Nq);
+        partial(kv->plan_d[0], d, F);
+        const GemmPlan g = ring_rule_gate_up(2 * F / 16, d / kstep, rows, kv->planes);
+        if (g.waves) kv->plan_gu = g;
     }
+    rule_lm_head(kv, kv->planes);
 }
 
 // fp32 elements of the projections' partials for blocks of up to `rows` rows; element offsets into them are 32-bit
@@ -463,7 +470,10 @@ extern "C" int sj_kv_create(const sj_model* m, int32_t batch, const int32_t* cap
     kv->wpart = kv->epart + slabs;
     kv->eblk = kv->wpart + slabs;
     kv->wblk = kv->eblk + slabs / 256;
-    if (c.n_layers == 0) ALLOC(kv->xn, (size_t)3 * kv->rpad * d * m->esz);          // up to three operand planes
+    if (c.n_layers == 0) {
+        ALLOC(kv->xn, (size_t)3 * kv->rpad * d * m->esz);      // up to three operand planes
+        rule_lm_head(kv, 1);
+    }
     if (c.n_layers > 0) {
         const int hd = c.head_dim, Nq = c.n_q_heads * hd, F = c.d_ffn;
         const int G = c.n_q_heads / c.n_kv_heads;
@@ -637,7 +647,7 @@ extern "C" int sj_kernel_class_shape(const sj_kv* kv, int32_t kernel_class, int3
         }
     }
     if (p.waves == RING_WAVES)
-        snprintf(buf, (size_t)buf_len, "gemm_ring: %d n-tiles per workgroup, 8 compute + 2 loader waves, %d K-slice(s), LDS ring of %d stages",
+        snprintf(buf, (size_t)buf_len, "gemm_ring: %d n-tiles per workgroup, 8 waves, %d K-slice(s), LDS ring of %d KB a wave",
                  p.nt, p.split, p.depth);
     else
         snprintf(buf, (size_t)buf_len, "gemm_skinny: %d n-tiles x %d waves per workgroup, %d K-slice(s), register ring of %d", p.nt, p.waves,
@@ -871,8 +881,8 @@ static int gemm(hipStream_t st, const void* Wt, const void* X, size_t xplane, in
     return SJ_OK;
 }
 
-// The same product on the LDS-ring kernel (bf16, at most two planes, at most 16 rows; ring_fits has been checked).
-template <typename T, int NT, int EPI, int SPL, int NSA>
+// The same product on the LDS-ring kernel (bf16, at most two planes; ring_fits has been checked).
+template <typename T, int NT, int EPI, int SPL, int DEPTH>
 static int gemm_ring(hipStream_t st, const void* Wt, const void* X, size_t xplane, int K, int N, int rows, int split,
                      float* out, void* act, size_t actplane, float4* stats, float inv_temp, const FewArgs& fa = FewArgs{}) {
     if (const int rc = check_scaled<EPI>(fa, rows)) return rc;
@@ -883,8 +893,10 @@ static int gemm_ring(hipStream_t st, const void* Wt, const void* X, size_t xplan
     a.out = out; a.stats = stats; a.act = act;
     fa.put<T>(a);
     const dim3 grid(N / 16 / NT, split);
-    if (SPL == 2 && rows <= RING_PACK_ROWS) gemm_ring_kernel<T, NT, EPI, 2, true, NSA><<<grid, RING_THREADS, 0, st>>>(a);
-    else gemm_ring_kernel<T, NT, EPI, SPL, false, NSA><<<grid, RING_THREADS, 0, st>>>(a);
+    if (SPL == 2 && rows <= RING_PACK_ROWS) gemm_ring_kernel<T, NT, 1, EPI, 2, true, DEPTH><<<grid, RING_CW * 64, 0, st>>>(a);
+    else if (rows <= 16) gemm_ring_kernel<T, NT, 1, EPI, SPL, false, DEPTH><<<grid, RING_CW * 64, 0, st>>>(a);
+    else if constexpr (EPI != EPI_RESID) gemm_ring_kernel<T, NT, 2, EPI, SPL, false, DEPTH><<<grid, RING_CW * 64, 0, st>>>(a);
+    else return fail(SJ_EINVAL, "internal: residual epilogue over %d rows", rows);
     LAUNCHCHK("gemm_ring");
     return SJ_OK;
 }
@@ -897,9 +909,9 @@ static int few_partial(const GemmPlan& p, hipStream_t st, const void* W, const v
     constexpr bool BF16 = std::is_same<T, bf16_t>::value;
     if (partial_fits(p, N / 16, K / Traits<T>::KSTEP, rows, SPL, BF16)) {
         if constexpr (BF16 && SPL <= 2) {
-#define SJ_RING(NT, NSA)                                                                                            \
-    if (p.waves == RING_WAVES && p.nt == NT && p.depth == NSA)                                                      \
-        return gemm_ring<T, NT, EPI_PARTIAL, SPL, NSA>(st, W, X, xplane, K, N, rows, p.split, out, nullptr, 0, nullptr, 0.f, fa);
+#define SJ_RING(NT, DEPTH)                                                                                            \
+    if (p.waves == RING_WAVES && p.nt == NT && p.depth == DEPTH)                                                      \
+        return gemm_ring<T, NT, EPI_PARTIAL, SPL, DEPTH>(st, W, X, xplane, K, N, rows, p.split, out, nullptr, 0, nullptr, 0.f, fa);
             SJ_RING_PARTIAL_SHAPES(SJ_RING)
 #undef SJ_RING
         }
@@ -920,9 +932,9 @@ static int few_swiglu(const GemmPlan& p, hipStream_t st, const void* W, const vo
     constexpr bool BF16 = std::is_same<T, bf16_t>::value;
     if (gate_up_fits(p, N2 / 16, K / Traits<T>::KSTEP, rows, SPL, BF16)) {
         if constexpr (BF16 && SPL <= 2) {
-#define SJ_RING(NT, NSA)                                                                                            \
-    if (p.waves == RING_WAVES && p.nt == NT && p.depth == NSA)                                                      \
-        return gemm_ring<T, NT, EPI_SWIGLU, SPL, NSA>(st, W, X, xplane, K, N2, rows, 1, nullptr, act, actplane, nullptr, 0.f, fa);
+#define SJ_RING(NT, DEPTH)                                                                                            \
+    if (p.waves == RING_WAVES && p.nt == NT && p.depth == DEPTH)                                                      \
+        return gemm_ring<T, NT, EPI_SWIGLU, SPL, DEPTH>(st, W, X, xplane, K, N2, rows, 1, nullptr, act, actplane, nullptr, 0.f, fa);
             SJ_RING_GATE_UP_SHAPES(SJ_RING)
 #undef SJ_RING
         }
@@ -941,10 +953,10 @@ static int few_resid(const GemmPlan& p, hipStream_t st, const void* W, const voi
                      size_t xgplane, const FewArgs& fa) {
     if constexpr (SPL <= 2) {
         if constexpr (std::is_same<T, bf16_t>::value) {
-#define SJ_RING(NT, NSA)                                                                                            \
-    if (p.waves == RING_WAVES && p.nt == NT && p.depth == NSA)                                                      \
-        return gemm_ring<T, NT, EPI_RESID, SPL, NSA>(st, W, X, xplane, K, N, rows, 1, nullptr, xg, xgplane, nullptr, 0.f, fa);
-            SJ_RING(1, 8) SJ_RING(2, 8) SJ_RING(4, 8) SJ_RING(1, 4) SJ_RING(2, 4) SJ_RING(4, 4)
+#define SJ_RING(NT, DEPTH)                                                                                            \
+    if (p.waves == RING_WAVES && p.nt == NT && p.depth == DEPTH)                                                      \
+        return gemm_ring<T, NT, EPI_RESID, SPL, DEPTH>(st, W, X, xplane, K, N, rows, 1, nullptr, xg, xgplane, nullptr, 0.f, fa);
+            SJ_RING_RESID_SHAPES(SJ_RING)
 #undef SJ_RING
         }
 #define SJ_SHAPE(NT)                                                                                                \
@@ -963,9 +975,9 @@ static int few_logits(const GemmPlan& p, hipStream_t st, const void* W, const vo
     constexpr bool BF16 = std::is_same<T, bf16_t>::value;
     if (logits_fits(p, V / 16, K / Traits<T>::KSTEP, rows, SPL, BF16)) {
         if constexpr (BF16 && SPL <= 2) {
-#define SJ_RING(NT, NSA)                                                                                            \
-    if (p.waves == RING_WAVES && p.nt == NT && p.depth == NSA)                                                      \
-        return gemm_ring<T, NT, EPI_LOGITS, SPL, NSA>(st, W, X, xplane, K, V, rows, 1, logits, nullptr, 0, stats, inv_temp, fa);
+#define SJ_RING(NT, DEPTH)                                                                                            \
+    if (p.waves == RING_WAVES && p.nt == NT && p.depth == DEPTH)                                                      \
+        return gemm_ring<T, NT, EPI_LOGITS, SPL, DEPTH>(st, W, X, xplane, K, V, rows, 1, logits, nullptr, 0, stats, inv_temp, fa);
             SJ_RING_LOGITS_SHAPES(SJ_RING)
 #undef SJ_RING
         }
@@ -1079,7 +1091,7 @@ static int tune_gate_up(sj_kv* kv, int rows, hipEvent_t e0, hipEvent_t e1) {
     SJ_FEW_GATE_UP_SHAPES(SJ_OFFER)
     SJ_FEW_GATE_UP_SHAPES_2(SJ_OFFER)
 #undef SJ_OFFER
-#define SJ_OFFER(NT, NSA) offer(NT, RING_WAVES, NSA);
+#define SJ_OFFER(NT, D) offer(NT, RING_WAVES, D);
     SJ_RING_GATE_UP_SHAPES(SJ_OFFER)
 #undef SJ_OFFER
     return pick_plan(kv->plan_gu, cands, time_plan);
@@ -1121,7 +1133,7 @@ static int tune_lm_head(sj_kv* kv, int rows, hipEvent_t e0, hipEvent_t e1) {
     SJ_FEW_LOGITS_SHAPES(SJ_OFFER)
     if (SPL <= 2) { SJ_FEW_LOGITS_SHAPES_2(SJ_OFFER) }
 #undef SJ_OFFER
-#define SJ_OFFER(NT, NSA) offer(NT, RING_WAVES, NSA);
+#define SJ_OFFER(NT, D) offer(NT, RING_WAVES, D);
     SJ_RING_LOGITS_SHAPES(SJ_OFFER)
 #undef SJ_OFFER
     return pick_plan(kv->plan_lm, cands, time_plan);
@@ -1864,6 +1876,8 @@ extern "C" int sj_verify_head_static(sj_model* m, int32_t batch, int32_t gamma, 
     kv.max_rows = (int)R;
     kv.rpad = ((int)R + 15) / 16 * 16;
     kv.use_graph = false;
+    // eight n-tiles a statistic, as the workspace below has it, on either few-row kernel
+    if (const GemmPlan ring{8, RING_WAVES, 1, RING_TWO}; logits_fits(ring, V / 16, d * (int)m->esz / 64, (int)R, 1, m->cfg.dtype == SJ_DTYPE_BF16)) kv.plan_lm = ring;
     kv.nslab = std::max(1, (V / 16 + 255) / 256) * 256;
     kv.slab_len = (V + kv.nslab - 1) / kv.nslab;
     size_t off = 0;

@@ -8,8 +8,7 @@
 
 namespace sj {
 
-constexpr int RING_CW = 8;         // compute waves = fragments (k-steps) per stage
-constexpr int RING_LW = 2;         // loader waves
+constexpr int RING_CW = 8;         // waves of the LDS-ring kernel, which interleave K
 constexpr int ROWS_MT = 9;         // row tiles per launch (144 rows)
 
 // Up to two row tiles (32 rows) the few-row kernel (every wave fetches its own operand fragments) is the faster
@@ -22,32 +21,36 @@ constexpr int FEW_ROWS = 32;
 // multiple of 256 leaves CUs idle for its whole duration: plan_partial takes, among the first tile groupings
 // the kernel is instantiated for, the one that wastes the fewest workgroup slots, every wave keeping at least
 // 8 k-steps; tune_plans then measures that choice against the other shapes on the model's own weights.
-// waves == RING_WAVES selects the LDS-ring kernel (8 compute + 2 loader waves); `depth` is then its ring depth in
-// stages (4 or 8).
+// waves == RING_WAVES selects the LDS-ring kernel (eight waves, each with a ring of its own); `depth` is then that ring's 1 KB fragments.
 struct GemmPlan { int nt = 4, waves = 4, split = 1, depth = 2; };
-constexpr int RING_WAVES = RING_CW + RING_LW;
-constexpr int RING_ROWS = 16;                  // one MFMA row tile
+constexpr int RING_WAVES = 10;                 // (a mark: the other kernels have 4 or 8)
+constexpr int RING_ROWS = FEW_ROWS;
 constexpr int RING_PACK_ROWS = 8;              // both operand planes in one product
+constexpr int RING_TWO = 9;                    // rings of up to this depth leave room for two workgroups a CU (160 KB of LDS)
+constexpr int RING_MOST = 19;                  // fragments of a ring (and n-tiles x row tiles of a reduction) that one workgroup's LDS holds
 
-// Can the LDS-ring kernel run this product in this launch shape?  bf16 with one or two operand planes, one row tile,
-// whole groups of n-tiles, K-slices of whole 8-k-step stages, and at least `depth` stages per workgroup.
+// operand fragments of a k-step
+constexpr int ring_operand(bool pack, int planes, int row_tiles) { return pack ? 1 : planes * row_tiles; }
+
+// Can the LDS-ring kernel run this product in this launch shape?  bf16 with one or two operand planes, up to two row tiles, whole groups of
+// n-tiles, K-slices of whole k-blocks (8 k-steps), as many as its ring holds in part, and LDS for the rings and for the reduction.
 inline bool ring_fits(const GemmPlan& p, int ntiles, int ksteps, int rows, int planes, bool bf16) {
     if (p.waves != RING_WAVES || !bf16 || planes > 2 || rows > RING_ROWS) return false;
-    if (p.nt < 1 || p.split < 1 || ntiles % p.nt || ksteps % (RING_CW * p.split)) return false;
-    const int nstages = ksteps / RING_CW / p.split * p.nt;
-    return (p.depth == 4 || p.depth == 8) && nstages >= p.depth;
+    if (p.nt < 1 || p.split < 1 || p.depth < 1 || ntiles % p.nt || ksteps % (RING_CW * p.split)) return false;
+    const int mt = rows > 16 ? 2 : 1, per = p.nt + ring_operand(planes == 2 && rows <= RING_PACK_ROWS, planes, mt), d = std::max(p.depth, per);
+    return ksteps / RING_CW / p.split >= (d + per - 1) / per && d <= RING_MOST && p.nt * mt <= RING_MOST;
 }
 
 // The shapes the split-K projections are instantiated for: (n-tiles, waves, ring depth) of the register-ring kernel - the second list
-// for one and two operand planes only - and (n-tiles, ring depth in stages) of the LDS-ring kernel.
+// for one and two operand planes only - and (n-tiles, ring depth in fragments) of the LDS-ring kernel.
 #define SJ_FEW_PARTIAL_SHAPES(X) X(4, 4, 2) X(4, 4, 4) X(3, 8, 2) X(6, 4, 2) X(1, 8, 2)
 #define SJ_FEW_PARTIAL_SHAPES_2(X) X(5, 4, 2) X(8, 8, 2) X(4, 8, 2) X(8, 4, 2) X(3, 4, 4) X(2, 4, 4) X(2, 4, 2) X(2, 8, 2)
-#define SJ_RING_PARTIAL_SHAPES(X) X(1, 8) X(2, 8) X(3, 8) X(4, 8) X(8, 8) X(1, 4) X(2, 4) X(3, 4) X(4, 4)
+#define SJ_RING_PARTIAL_SHAPES(X) X(1, 4) X(1, 9) X(2, 4) X(2, 9) X(3, 4) X(3, 9) X(4, 4) X(4, 9) X(3, 18) X(4, 18) X(5, 18) X(8, 18)
 
 // Is there a kernel for exactly this split-K launch?  The consumer adds p.split K-slices, so no other shape may stand in for it.
 inline bool partial_fits(const GemmPlan& p, int ntiles, int ksteps, int rows, int planes, bool bf16) {
     if (p.waves == RING_WAVES) {
-#define SJ_IS(NT, NSA) if (p.nt == NT && p.depth == NSA) return ring_fits(p, ntiles, ksteps, rows, planes, bf16);
+#define SJ_IS(NT, D) if (p.nt == NT && p.depth == D) return ring_fits(p, ntiles, ksteps, rows, planes, bf16);
         SJ_RING_PARTIAL_SHAPES(SJ_IS)
 #undef SJ_IS
         return false;
@@ -64,13 +67,15 @@ inline bool partial_fits(const GemmPlan& p, int ntiles, int ksteps, int rows, in
 // register-ring kernel (LM head: depth 2), (n-tiles, ring depth) of the LDS-ring kernel.
 #define SJ_FEW_GATE_UP_SHAPES(X) X(7, 8, 2) X(8, 8, 2) X(1, 8, 2)
 #define SJ_FEW_GATE_UP_SHAPES_2(X) X(4, 8, 2) X(4, 4, 2) X(2, 8, 2) X(2, 4, 2) X(7, 8, 3) X(7, 8, 4) X(8, 8, 4)
-#define SJ_RING_GATE_UP_SHAPES(X) X(7, 8) X(8, 8) X(4, 8) X(2, 8) X(7, 4) X(8, 4) X(4, 4)
+#define SJ_RING_GATE_UP_SHAPES(X) X(1, 4) X(1, 9) X(2, 4) X(2, 9) X(4, 4) X(4, 9) X(7, 18) X(8, 18)
 #define SJ_FEW_LOGITS_SHAPES(X) X(8, 4, 2) X(2, 8, 2)
 #define SJ_FEW_LOGITS_SHAPES_2(X) X(8, 8, 2) X(4, 8, 2) X(4, 4, 2)
-#define SJ_RING_LOGITS_SHAPES(X) X(8, 4) X(8, 8) X(4, 8)
+#define SJ_RING_LOGITS_SHAPES(X) X(2, 4) X(2, 9) X(4, 4) X(4, 9) X(8, 9) X(8, 18)
+// and for the projections that close a sub-layer in their epilogue
+#define SJ_RING_RESID_SHAPES(X) X(1, 4) X(1, 9) X(2, 4) X(2, 9) X(4, 4) X(4, 9)
 
 // Is there a kernel for exactly this launch?
-#define SJ_IS_RING(NT, NSA) if (p.nt == NT && p.depth == NSA) return ring_fits(p, ntiles, ksteps, rows, planes, bf16);
+#define SJ_IS_RING(NT, D) if (p.nt == NT && p.depth == D) return ring_fits(p, ntiles, ksteps, rows, planes, bf16);
 #define SJ_IS_FEW(NT, WV, D) if (p.nt == NT && p.waves == WV && p.depth == D) return true;
 inline bool gate_up_fits(const GemmPlan& p, int ntiles, int ksteps, int rows, int planes, bool bf16) {
     if (p.split != 1 || p.nt < 1 || ntiles % p.nt) return false;
@@ -102,15 +107,59 @@ inline GemmPlan ring_rule_partial(int ntiles, int ksteps) {
     for (int split : splits)
         for (int nt : nts) {
             GemmPlan p;
-            p.nt = nt; p.waves = RING_WAVES; p.split = split;
-            const int nstages = (ksteps / RING_CW / split) * nt;
-            p.depth = nstages >= 16 ? 8 : 4;
+            p.nt = nt; p.waves = RING_WAVES; p.split = split; p.depth = RING_TWO;
+            if (!partial_fits(p, ntiles, ksteps, 1, 2, true)) p.depth = 4;
             if (!partial_fits(p, ntiles, ksteps, 1, 2, true)) continue;
             const int wgs = ntiles / nt * split;
             const double waste = (double)((wgs + 255) / 256 * 256) / wgs + (nt == 1 ? 0.25 : 0.0);
             if (waste < best_waste - 1e-9) { best = p; best_waste = waste; }
         }
     return best;
+}
+// The same from 9 rows on, where a k-step has one operand fragment per plane and row tile: whole rounds of 256 workgroups first, then the least
+// of fragments a wave reads + 20 for every K-slice (its sums are written and read).  us of the shapes that fill the chip, n-tiles x slices:
+//   8B, 20 rows: down 4 x 4 21.6, 8 x 8 22.1; QKV 3 x 2 11.4, 3 x 4 12.6;   70B, 24 rows: O 4 x 2 24.8, 8 x 4 28.6; down 8 x 4 72.3, 4 x 2 75.5;
+//   1B, 12 rows: O 1 x 2 4.4; down 2 x 4 8.6, 4 x 8 9.1; QKV (192 or 256 workgroups) 2 x 2 5.2, 3 x 4 5.4.
+inline GemmPlan ring_rule_partial_rows(int ntiles, int ksteps, int rows, int planes) {
+    GemmPlan best;
+    best.waves = 0;
+    double best_cost = 1e30;
+    const int nb = ring_operand(false, planes, rows > 16 ? 2 : 1);
+    for (int split : {1, 2, 4, 8})
+        for (int nt : {1, 2, 3, 4, 5, 8}) {
+            const int wgs = ntiles / nt * split;
+            GemmPlan p;
+            p.nt = nt; p.waves = RING_WAVES; p.split = split; p.depth = wgs <= 256 && nt >= 3 ? 18 : RING_TWO;
+            if (!partial_fits(p, ntiles, ksteps, rows, planes, true)) p.depth = RING_TWO;
+            if (!partial_fits(p, ntiles, ksteps, rows, planes, true)) p.depth = 4;
+            if (!partial_fits(p, ntiles, ksteps, rows, planes, true)) continue;
+            const double rounds = (double)((wgs + 255) / 256 * 256) / wgs;
+            const double cost = rounds * rounds * ((double)ksteps / RING_CW / split * (nt + nb) * ((wgs + 255) / 256) + 20.0 * split);
+            if (cost < best_cost - 1e-9) { best = p; best_cost = cost; }
+        }
+    return best;
+}
+// Gate / up on that kernel: 8 or 7 n-tiles where they make whole rounds of one workgroup a CU (8B, 70B: 7), else two, two workgroups a CU (1B,
+// one row: 2 n-tiles 13.0 us, 4 of them 14.8 - 18; 8B, 6 rows: 7 of them 37.4, 4 of them 41.0).
+inline GemmPlan ring_rule_gate_up(int ntiles, int ksteps, int rows, int planes) {
+    for (int nt : {8, 7, 2, 4, 1})
+        for (int depth : {18, RING_TWO, 4}) {
+            const GemmPlan p{nt, RING_WAVES, 1, depth};
+            if (nt >= 7 && (ntiles / nt) % 256) continue;
+            if (gate_up_fits(p, ntiles, ksteps, rows, planes, true)) return p;
+        }
+    return GemmPlan{4, 0, 1, 0};
+}
+// LM head on it: four n-tiles, two workgroups a CU; two for short rows of packed operand (1B, one row: 2 n-tiles 76.7 us, 4 of them 85.8; 8B, 6 rows:
+// 164 with 4, 169 - 177 with 2); eight from 17 rows on (8B, 20 rows: 191, 4 of them 196).
+inline GemmPlan ring_rule_logits(int ntiles, int ksteps, int rows, int planes) {
+    const bool two = ksteps <= 64 && planes == 2 && rows <= RING_PACK_ROWS;
+    for (int nt : {rows > 16 ? 8 : two ? 2 : 4, 4, 2})
+        for (int depth : {nt == 8 ? 18 : RING_TWO, 4}) {
+            const GemmPlan p{nt, RING_WAVES, 1, depth};
+            if (logits_fits(p, ntiles, ksteps, rows, planes, true)) return p;
+        }
+    return GemmPlan{8, 0, 1, 0};
 }
 
 // Small matrices (small models): a launch is over as soon as its longest workgroup, so every n-tile gets one of its own, its eight waves
@@ -204,7 +253,7 @@ inline std::vector<GemmPlan> partial_candidates(int ntiles, int ksteps, int rows
     SJ_FEW_PARTIAL_SHAPES(SJ_OFFER)
     SJ_FEW_PARTIAL_SHAPES_2(SJ_OFFER)
 #undef SJ_OFFER
-#define SJ_OFFER(NT, NSA) offer(NT, RING_WAVES, NSA);
+#define SJ_OFFER(NT, D) offer(NT, RING_WAVES, D);
     SJ_RING_PARTIAL_SHAPES(SJ_OFFER)
 #undef SJ_OFFER
     return cands;
@@ -285,8 +334,10 @@ inline GemmPlan resid_plan(int N, int K, int kstep, int rows, int planes, bool b
     if (rows > RING_PACK_ROWS || planes > 2 || ntiles % nt) return p;
     p.nt = nt; p.split = 1;
     p.waves = RING_WAVES;
-    p.depth = ksteps / RING_CW * nt >= 16 ? 8 : 4;
-    if (rows <= ring_rows && ring_fits(p, ntiles, ksteps, rows, planes, bf16)) return p;
+    for (int depth : {RING_TWO, 4}) {
+        p.depth = depth;
+        if (rows <= ring_rows && ring_fits(p, ntiles, ksteps, rows, planes, bf16)) return p;
+    }
     p.waves = 8; p.depth = 2;
     return p;
 }

@@ -286,6 +286,38 @@ def test_lds_ring_projections(gamma, planes, monkeypatch):
     assert (diff <= abs_tol + rel_tol * np.abs(logits[0])).all(), float(diff.max())
 
 
+# rows of one and two row tiles, both plane counts, K of two and more k-blocks (rings that hold all of a slice and a part of it), n-tiles of 1 to 8
+# a workgroup, one and several K-slices
+@pytest.mark.parametrize("d,f,vocab,batch,gamma,planes", [(512, 1792, 4992, 1, 16, 2), (768, 1536, 8192, 2, 11, 2), (1024, 14336, 16384, 2, 15, 2),
+                                                          (2048, 2048, 16384, 2, 8, 1), (1536, 4096, 4992, 3, 5, 1), (2048, 8192, 4096, 1, 11, 2)])
+def test_lds_ring_projections_of_many_rows(d, f, vocab, batch, gamma, planes, monkeypatch):
+    """9 to 32 rows: the LDS-ring kernel against the register-ring kernel and, with two planes, both against the oracle."""
+    shape = synth.ModelShape(f"ring_rows_{d}", "bf16", 2, d, 8, 2, 128, f, vocab, 10000.0, batch=batch, gamma=gamma, weight_std=0.06 * (512 / d) ** 0.5)
+    draft = synth.make_draft(shape, seed=gamma)
+    logits = {}
+    for ring_rows in (32, 0):
+        monkeypatch.setenv("SJ_TUNE", "0")
+        monkeypatch.setenv("SJ_RING_ROWS", str(ring_rows))
+        gpu, cfg, W, caches = _setup(shape, [150, 33, 70][:batch])
+        try:
+            if planes != 2:
+                sj.sj_set_operand_planes(gpu.kv, planes)
+            names = [sj.sj_kernel_class_shape(gpu.kv, c, batch * (gamma + 1)) for c in (1, 2, 3, 4, 5)]
+            assert all(n.startswith("gemm_ring" if ring_rows else "gemm_skinny") for n in names), names
+            out = gpu.step(draft, 0.5, gamma)
+            logits[ring_rows] = out["logits"].copy()
+            if planes == 2:
+                ref = _oracle(cfg, W, caches, draft, 0.5)
+                for b in range(batch):
+                    G.close_enough(out["logits"][b], ref[b]["logits"], "bf16", f"logits, ring rows {ring_rows}, sequence {b}")
+        finally:
+            gpu.close()
+    diff = np.abs(logits[32] - logits[0])                  # bounds of the test above
+    abs_tol, rel_tol = (5e-3, 1e-2) if planes == 2 else (5e-2, 5e-2)
+    print(f"ring vs register-ring kernel, {planes} plane(s), {batch * (gamma + 1)} rows: max |diff| {float(diff.max()):.3e}")
+    assert (diff <= abs_tol + rel_tol * np.abs(logits[0])).all(), float(diff.max())
+
+
 def test_results_are_the_same_by_copy_and_mirror_on_every_stream():
     """The first fetch of per-draft results copies them, later ones read host memory that the call wrote; calls that move between
     streams without a wait still see each other's lengths."""
