@@ -113,6 +113,7 @@ struct sj_kv : Forward {       // the inherited buffers serve the blocks of up t
     GemmPlan plan_qkv[2], plan_o[2], plan_d[2];   // [0]: few-row kernel (at most 32 rows), [1]: more
     GemmPlan plan_gu;                             // gate / up projection with few rows (no K-slices)
     GemmPlan plan_lm{8, 4, 1, 2};                 // LM head with few rows
+    int few_rows = 1;                             // rows that the few-row shapes were made for
     int mode = SJ_MODE_TWO_STAGE;
     int ring_rows = RING_ROWS;            // the rules take the LDS-ring kernel up to this many rows
     int planes = 2;            // bf16 planes of the activation operand (fp32 storage: always 1)
@@ -324,39 +325,29 @@ static int tune_plans(sj_kv* kv, int rows);
 // The LM head's launch shape by the rule; planes of its operand: one for hidden states handed in by the caller of a head-only model.
 static void rule_lm_head(sj_kv* kv, int planes) {
     const sj_config& c = kv->m->cfg;
-    kv->plan_lm = rule_logits(c.vocab / 16);
-    if (c.dtype != SJ_DTYPE_BF16 || planes > 2 || kv->max_rows > kv->ring_rows) return;
-    const GemmPlan l = ring_rule_logits(c.vocab / 16, c.d_model / 32, kv->max_rows, planes);
-    if (l.waves) kv->plan_lm = l;
+    const bool bf16 = c.dtype == SJ_DTYPE_BF16;
+    kv->few_rows = std::min(kv->max_rows, FEW_ROWS);
+    kv->plan_lm = rule_logits(c.vocab / 16, c.d_model / (bf16 ? 32 : 16), kv->few_rows, planes, bf16, kv->ring_rows);
 }
 
 // the launch shapes the rule gives (before any measurement)
 static void rule_plans(sj_kv* kv) {
     const sj_config& c = kv->m->cfg;
     const int d = c.d_model, hd = c.head_dim, Nq = c.n_q_heads * hd, Nk = c.n_kv_heads * hd, F = c.d_ffn;
-    const int kstep = (c.dtype == SJ_DTYPE_FP32) ? 16 : 32;
-    for (int i = 0; i < 2; ++i) {
-        kv->plan_qkv[i] = plan_partial((Nq + 2 * Nk) / 16, d / kstep, i == 0);
-        kv->plan_o[i] = plan_partial(d / 16, Nq / kstep, i == 0);
-        kv->plan_d[i] = plan_partial(d / 16, F / kstep, i == 0);
-    }
-    kv->plan_gu = rule_gate_up(2 * F / 16, kv->planes);
+    const bool bf16 = c.dtype == SJ_DTYPE_BF16;
+    const int kstep = bf16 ? 32 : 16, planes = bf16 ? kv->planes : 1, rows = std::min(kv->max_rows, FEW_ROWS);
     // bf16 with one or two planes: the LDS-ring kernel where a shape of it fits (4 - 13 % faster than the register-ring kernel from 1 to 32 rows; the
     // start-up measurement may still prefer another shape).  SJ_RING_ROWS = 0..32 moves the row limit of this rule.
     if (const char* e = std::getenv("SJ_RING_ROWS")) kv->ring_rows = std::min(std::max(std::atoi(e), 0), RING_ROWS);
-    if (c.dtype == SJ_DTYPE_BF16 && kv->planes <= 2 && kv->max_rows <= kv->ring_rows) {
-        const int rows = kv->max_rows;
-        auto partial = [&](GemmPlan& plan, int N, int K) {
-            const GemmPlan r = rows <= RING_PACK_ROWS ? ring_rule_partial(N / 16, K / kstep) : ring_rule_partial_rows(N / 16, K / kstep, rows, kv->planes);
-            if (r.waves) plan = r;
-        };
-        partial(kv->plan_qkv[0], Nq + 2 * Nk, d);
-        partial(kv->plan_o[0], d, Nq);
-        partial(kv->plan_d[0], d, F);
-        const GemmPlan g = ring_rule_gate_up(2 * F / 16, d / kstep, rows, kv->planes);
-        if (g.waves) kv->plan_gu = g;
-    }
-    rule_lm_head(kv, kv->planes);
+    auto partial = [&](GemmPlan (&plan)[2], int N, int K, int most = 8) {
+        plan[0] = rule_partial(N / 16, K / kstep, rows, planes, bf16, kv->ring_rows, most);
+        plan[1] = plan_partial(N / 16, K / kstep, false);
+    };
+    partial(kv->plan_qkv, Nq + 2 * Nk, d, QKV_SLICES);
+    partial(kv->plan_o, d, Nq);
+    partial(kv->plan_d, d, F);
+    kv->plan_gu = rule_gate_up(2 * F / 16, d / kstep, rows, planes, bf16, kv->ring_rows);
+    rule_lm_head(kv, planes);
 }
 
 // fp32 elements of the projections' partials for blocks of up to `rows` rows; element offsets into them are 32-bit
@@ -634,12 +625,12 @@ extern "C" int sj_kernel_class_shape(const sj_kv* kv, int32_t kernel_class, int3
     const sj_config& c = kv->m->cfg;
     const bool bf16 = c.dtype == SJ_DTYPE_BF16;
     const int kstep = bf16 ? 32 : 16, planes = bf16 ? kv->planes : 1, d = c.d_model, Nq = c.n_q_heads * c.head_dim;
-    auto partial = [&](const GemmPlan& q, int N, int K) { return resolve_partial(q, N / 16, K / kstep, rows, planes, bf16); };
+    auto partial = [&](const GemmPlan& q, int N, int K, int most = 8) { return few_partial_plan(q, kv->few_rows, N / 16, K / kstep, rows, planes, bf16, kv->ring_rows, most); };
     GemmPlan p;
     switch (kernel_class) {
-        case 1: p = partial(kv->plan_qkv[0], Nq + 2 * c.n_kv_heads * c.head_dim, d); break;
-        case 3: p = resolve_gate_up(kv->plan_gu, 2 * c.d_ffn / 16, d / kstep, rows, planes, bf16); break;
-        case 5: p = resolve_logits(kv->plan_lm, c.vocab / 16, d / kstep, rows, c.n_layers ? planes : 1, bf16); break;
+        case 1: p = partial(kv->plan_qkv[0], Nq + 2 * c.n_kv_heads * c.head_dim, d, QKV_SLICES); break;
+        case 3: p = few_gate_up_plan(kv->plan_gu, kv->few_rows, 2 * c.d_ffn / 16, d / kstep, rows, planes, bf16, kv->ring_rows); break;
+        case 5: p = few_logits_plan(kv->plan_lm, kv->few_rows, c.vocab / 16, d / kstep, rows, c.n_layers ? planes : 1, bf16, kv->ring_rows); break;
         default: {
             const int K = kernel_class == 2 ? Nq : c.d_ffn;
             p = resid_plan(d, K, kstep, rows, planes, bf16, kv->ring_rows);
@@ -1281,7 +1272,7 @@ struct Runner {
     // launch shape of a split-K projection for this row count
     GemmPlan plan_of(const GemmPlan (&pl)[2], int K, int N) const {
         const int ksteps = K / Traits<T>::KSTEP;
-        if (R <= FEW_ROWS) return resolve_partial(pl[0], N / 16, ksteps, R, SPL, std::is_same<T, bf16_t>::value);
+        if (R <= FEW_ROWS) return few_partial_plan(pl[0], kv->few_rows, N / 16, ksteps, R, SPL, std::is_same<T, bf16_t>::value, kv->ring_rows, &pl == &kv->plan_qkv ? QKV_SLICES : 8);
         GemmPlan p = pl[1];
         p.split = rows_split(p.split, N / 16, ksteps, R, rows_planes<T, SPL>);
         return p;
@@ -1329,7 +1320,7 @@ struct Runner {
     int gate_up(const void* W, bool unscaled = false) {
         const ModelDims& md = m->md;
         if (R > FEW_ROWS) return gemm_rows<T, EPI_SWIGLU, SPL>(st, W, w->xn, plane(md.d), md.d, 2 * md.F, R, 1, nullptr, w->act, plane(md.F), nullptr, 0.f);
-        const GemmPlan p = resolve_gate_up(kv->plan_gu, 2 * md.F / 16, md.d / Traits<T>::KSTEP, R, SPL, std::is_same<T, bf16_t>::value);
+        const GemmPlan p = few_gate_up_plan(kv->plan_gu, kv->few_rows, 2 * md.F / 16, md.d / Traits<T>::KSTEP, R, SPL, std::is_same<T, bf16_t>::value, kv->ring_rows);
         return few_swiglu<T, SPL>(p, st, W, w->xn, plane(md.d), md.d, 2 * md.F, R, w->act, plane(md.F), few_args(unscaled));
     }
 
@@ -1474,7 +1465,7 @@ struct Runner {
                 : gemm_rows<T, EPI_LOGITS, SPL>(st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, 1, kv->logits, nullptr, 0, kv->stats, md.inv_temp);
             nblk = md.V / 16 / ROWS_NT;
         } else {
-            const GemmPlan p = resolve_logits(kv->plan_lm, md.V / 16, md.d / Traits<T>::KSTEP, R, exact_operand ? 1 : SPL, std::is_same<T, bf16_t>::value);
+            const GemmPlan p = few_logits_plan(kv->plan_lm, kv->few_rows, md.V / 16, md.d / Traits<T>::KSTEP, R, exact_operand ? 1 : SPL, std::is_same<T, bf16_t>::value, kv->ring_rows);
             rc = exact_operand
                 ? few_logits<T, 1>(p, st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, kv->logits, kv->stats, md.inv_temp)
                 : few_logits<T, SPL>(p, st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, kv->logits, kv->stats, md.inv_temp, few_args(false));
@@ -1873,7 +1864,7 @@ extern "C" int sj_verify_head_static(sj_model* m, int32_t batch, int32_t gamma, 
     sj_kv kv;
     kv.m = m;
     kv.batch = batch;
-    kv.max_rows = (int)R;
+    kv.max_rows = kv.few_rows = (int)R;
     kv.rpad = ((int)R + 15) / 16 * 16;
     kv.use_graph = false;
     // eight n-tiles a statistic, as the workspace below has it, on either few-row kernel

@@ -116,25 +116,26 @@ inline GemmPlan ring_rule_partial(int ntiles, int ksteps) {
         }
     return best;
 }
-// The same from 9 rows on, where a k-step has one operand fragment per plane and row tile: whole rounds of 256 workgroups first, then the least
-// of fragments a wave reads + 20 for every K-slice (its sums are written and read).  us of the shapes that fill the chip, n-tiles x slices:
+// The same from 9 rows on, where a k-step has one operand fragment per plane and row tile: whole rounds of 256 workgroups, and few fragments for a
+// wave to read (an operand fragment counted twice: it comes from the L2 each time), tiles left to the reduction and K-slices (their sums
+// are written and read).  `most`: largest number of K-slices, two for QKV, whose slices attention adds (1B, 12 rows: 12.7 us with two,
+// 13.8 with four).  us of the shapes that fill the chip, n-tiles x slices:
 //   8B, 20 rows: down 4 x 4 21.6, 8 x 8 22.1; QKV 3 x 2 11.4, 3 x 4 12.6;   70B, 24 rows: O 4 x 2 24.8, 8 x 4 28.6; down 8 x 4 72.3, 4 x 2 75.5;
-//   1B, 12 rows: O 1 x 2 4.4; down 2 x 4 8.6, 4 x 8 9.1; QKV (192 or 256 workgroups) 2 x 2 5.2, 3 x 4 5.4.
-inline GemmPlan ring_rule_partial_rows(int ntiles, int ksteps, int rows, int planes) {
+//   1B, 12 rows: O 1 x 2 4.4; down 2 x 4 8.6, 4 x 8 9.1; QKV (192 workgroups) 2 x 2 5.2, 1 x 1 6.1.
+inline GemmPlan ring_rule_partial_rows(int ntiles, int ksteps, int rows, int planes, int most) {
     GemmPlan best;
     best.waves = 0;
     double best_cost = 1e30;
-    const int nb = ring_operand(false, planes, rows > 16 ? 2 : 1);
-    for (int split : {1, 2, 4, 8})
+    const int mt = rows > 16 ? 2 : 1, nb = ring_operand(false, planes, mt);
+    for (int split = 1; split <= most; split *= 2)
         for (int nt : {1, 2, 3, 4, 5, 8}) {
-            const int wgs = ntiles / nt * split;
+            const int wgs = ntiles / nt * split, to_cu = (wgs + 255) / 256;
             GemmPlan p;
             p.nt = nt; p.waves = RING_WAVES; p.split = split; p.depth = wgs <= 256 && nt >= 3 ? 18 : RING_TWO;
             if (!partial_fits(p, ntiles, ksteps, rows, planes, true)) p.depth = RING_TWO;
             if (!partial_fits(p, ntiles, ksteps, rows, planes, true)) p.depth = 4;
             if (!partial_fits(p, ntiles, ksteps, rows, planes, true)) continue;
-            const double rounds = (double)((wgs + 255) / 256 * 256) / wgs;
-            const double cost = rounds * rounds * ((double)ksteps / RING_CW / split * (nt + nb) * ((wgs + 255) / 256) + 20.0 * split);
+            const double cost = 256.0 * to_cu / wgs * (to_cu * ((double)ksteps / RING_CW / split * (nt + 2 * nb) + 4 * nt * mt + 8) + 6 * split);
             if (cost < best_cost - 1e-9) { best = p; best_cost = cost; }
         }
     return best;
@@ -228,6 +229,44 @@ inline GemmPlan resolve_gate_up(const GemmPlan& p, int ntiles, int ksteps, int r
 }
 inline GemmPlan resolve_logits(const GemmPlan& p, int ntiles, int ksteps, int rows, int planes, bool bf16) {
     return logits_fits(p, ntiles, ksteps, rows, planes, bf16) ? p : rule_logits(ntiles);
+}
+
+// The rules over both kernels; the LDS-ring kernel up to `ring_rows` rows.
+inline GemmPlan rule_partial(int ntiles, int ksteps, int rows, int planes, bool bf16, int ring_rows, int most = 8) {
+    if (bf16 && planes <= 2 && rows <= ring_rows) {
+        const GemmPlan r = rows <= RING_PACK_ROWS ? ring_rule_partial(ntiles, ksteps) : ring_rule_partial_rows(ntiles, ksteps, rows, planes, most);
+        if (r.waves) return r;
+    }
+    return plan_partial(ntiles, ksteps, true);
+}
+inline GemmPlan rule_gate_up(int ntiles, int ksteps, int rows, int planes, bool bf16, int ring_rows) {
+    if (bf16 && planes <= 2 && rows <= ring_rows) {
+        const GemmPlan r = ring_rule_gate_up(ntiles, ksteps, rows, planes);
+        if (r.waves) return r;
+    }
+    return rule_gate_up(ntiles, planes);
+}
+inline GemmPlan rule_logits(int ntiles, int ksteps, int rows, int planes, bool bf16, int ring_rows) {
+    if (bf16 && planes <= 2 && rows <= ring_rows) {
+        const GemmPlan r = ring_rule_logits(ntiles, ksteps, rows, planes);
+        if (r.waves) return r;
+    }
+    return rule_logits(ntiles);
+}
+
+// A shape made (by the rule or the measurement) for one row count speaks for others with as many operand fragments to a k-step: one packed, one
+// row tile, two.  A draft block of 12 sequences runs 12 rows on an object made for blocks of 60: in the shapes of 32 rows, or what stood in
+// for those that do not take 12, its QKV and O took 7.2 us each; in the rule's for 12 rows 5.2 and 4.9.
+constexpr int QKV_SLICES = 2;
+inline int few_class(int rows) { return rows <= RING_PACK_ROWS ? 0 : rows <= 16 ? 1 : 2; }
+inline GemmPlan few_partial_plan(const GemmPlan& made, int made_rows, int ntiles, int ksteps, int rows, int planes, bool bf16, int ring_rows, int most = 8) {
+    return resolve_partial(few_class(rows) == few_class(made_rows) ? made : rule_partial(ntiles, ksteps, rows, planes, bf16, ring_rows, most), ntiles, ksteps, rows, planes, bf16);
+}
+inline GemmPlan few_gate_up_plan(const GemmPlan& made, int made_rows, int ntiles, int ksteps, int rows, int planes, bool bf16, int ring_rows) {
+    return resolve_gate_up(few_class(rows) == few_class(made_rows) ? made : rule_gate_up(ntiles, ksteps, rows, planes, bf16, ring_rows), ntiles, ksteps, rows, planes, bf16);
+}
+inline GemmPlan few_logits_plan(const GemmPlan& made, int made_rows, int ntiles, int ksteps, int rows, int planes, bool bf16, int ring_rows) {
+    return resolve_logits(few_class(rows) == few_class(made_rows) ? made : rule_logits(ntiles, ksteps, rows, planes, bf16, ring_rows), ntiles, ksteps, rows, planes, bf16);
 }
 
 // Shapes that the start-up measurement tries for a split-K projection with at most 32 rows.
