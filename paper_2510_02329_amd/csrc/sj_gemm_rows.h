@@ -237,50 +237,57 @@ __global__ __launch_bounds__((R8_CW + R4_LW) * 64) void gemm_rows8_kernel(GemmAr
     };
     if constexpr (FOLD > 0) fold(true);
 
-    struct Frags { Frag wf[NH]; Frag w8; Frag bq[NFULL + NREM][SPL]; };
-    Frags fA, fB;
-    auto fetch = [&](Frags& f, int s) {
-        const u32x4* Xs = &Xst[s % R4_NSX][0][0];
-        const u32x4* Ws = &Wst[s % R4_NSW][0][0];
+    // The k-steps of a wave with NHW n-tiles in its half.  No predicate in the k-step: a row tile past the rows (tile 0 again) is multiplied into an
+    // accumulator that the epilogue never stores.  The second half of seven n-tiles has a loop of its own: its waves multiplied a fourth
+    // tile for nothing, and these kernels run at the clock that their products and fetches leave (1.5 - 2.3 of 2.4 GHz).
+    auto k_steps = [&](auto nhw_tag) {
+        constexpr int NHW = decltype(nhw_tag)::value;
+        struct Frags { Frag wf[NHW]; Frag w8; Frag bq[NFULL + NREM][SPL]; };
+        Frags fA, fB;
+        auto fetch = [&](Frags& f, int s) {
+            const u32x4* Xs = &Xst[s % R4_NSX][0][0];
+            const u32x4* Ws = &Wst[s % R4_NSW][0][0];
 #pragma unroll
-        for (int sp = 0; sp < SPL; ++sp) {
+            for (int sp = 0; sp < SPL; ++sp) {
 #pragma unroll
-            for (int i = 0; i < NFULL; ++i) f.bq[i][sp].u = Xs[((ra + 4 * i) * SPL + sp) * 64 + lane];
+                for (int i = 0; i < NFULL; ++i) f.bq[i][sp].u = Xs[((ra + 4 * i) * SPL + sp) * 64 + lane];
 #pragma unroll
-            for (int j = 0; j < NREM; ++j) f.bq[NFULL + j][sp].u = Xs[((4 * NFULL + j) * SPL + sp) * 64 + lane];
+                for (int j = 0; j < NREM; ++j) f.bq[NFULL + j][sp].u = Xs[((4 * NFULL + j) * SPL + sp) * 64 + lane];
+            }
+#pragma unroll
+            for (int t = 0; t < NHW; ++t) f.wf[t].u = Ws[(t0 + t) * 64 + lane];
+            f.w8.u = Ws[min(w, NT - 1) * 64 + lane];
+        };
+        auto multiply = [&](const Frags& f) {
+#pragma unroll
+            for (int sp = 0; sp < SPL; ++sp) {
+#pragma unroll
+                for (int t = 0; t < NHW; ++t)
+#pragma unroll
+                    for (int i = 0; i < NFULL; ++i) Traits<T>::mma(f.wf[t], f.bq[i][sp], acc[i][t]);
+#pragma unroll
+                for (int j = 0; j < NREM; ++j) Traits<T>::mma(f.w8, f.bq[NFULL + j][sp], acc8[j]);
+            }
+        };
+        lds_barrier();                                     // stages 0 and 1 are in LDS
+        fetch(fA, 0);
+        for (int s = 0; s < nks; s += 2) {
+            fetch(fB, s + 1);
+            multiply(fA);
+            lds_barrier();                                 // stage s + 2 has landed
+            if (s + 1 < nks) {                             // uniform
+                fetch(fA, s + 2);
+                multiply(fB);
+                lds_barrier();                             // stage s + 3 has landed
+            }
+            if constexpr (FOLD > 0) {
+                if ((s + 2) % FOLD == 0) fold(false);      // uniform
+            }
         }
-#pragma unroll
-        for (int t = 0; t < NH; ++t) f.wf[t].u = Ws[min(t0 + t, NT - 1) * 64 + lane];
-        f.w8.u = Ws[min(w, NT - 1) * 64 + lane];
     };
-    // No predicate in the k-step: a tile that does not exist (row tiles past the rows re-read tile 0, n-tiles past the
-    // workgroup's are clamped) is multiplied into an accumulator that the epilogue never stores.
-    auto multiply = [&](const Frags& f) {
-#pragma unroll
-        for (int sp = 0; sp < SPL; ++sp) {
-#pragma unroll
-            for (int t = 0; t < NH; ++t)
-#pragma unroll
-                for (int i = 0; i < NFULL; ++i) Traits<T>::mma(f.wf[t], f.bq[i][sp], acc[i][t]);
-#pragma unroll
-            for (int j = 0; j < NREM; ++j) Traits<T>::mma(f.w8, f.bq[NFULL + j][sp], acc8[j]);
-        }
-    };
-    lds_barrier();                                     // stages 0 and 1 are in LDS
-    fetch(fA, 0);
-    for (int s = 0; s < nks; s += 2) {
-        fetch(fB, s + 1);
-        multiply(fA);
-        lds_barrier();                                 // stage s + 2 has landed
-        if (s + 1 < nks) {                             // uniform
-            fetch(fA, s + 2);
-            multiply(fB);
-            lds_barrier();                             // stage s + 3 has landed
-        }
-        if constexpr (FOLD > 0) {
-            if ((s + 2) % FOLD == 0) fold(false);      // uniform
-        }
-    }
+    if constexpr (NT == 2 * NH) k_steps(std::integral_constant<int, NH>{});
+    else if (nb == 0) k_steps(std::integral_constant<int, NH>{});
+    else k_steps(std::integral_constant<int, NT - NH>{});
     if constexpr (FOLD > 0) {
 #pragma unroll
         for (int i = 0; i < NFULL; ++i)
