@@ -18,6 +18,11 @@
 // DEPTH: 9 leaves room for two workgroups a CU, 18 for one.  More is not better: 1B gate / up, four n-tiles, 6 / 12 / 18 fragments: 14.8 / 16.6 /
 // 18.1 us; two n-tiles, 4 / 9 / 12: 13.2 / 13.0 / 14.7.  Every workgroup starting at another k-block changed nothing.
 //
+// Closing a sub-layer from 9 rows on (`tickets`): O and down need K-slices there (one n-tile a workgroup, all of K: down of the 1B shape at 12 rows
+// 15.7 us against 8.6), so the slices of a group of n-tiles draw tickets and the last to finish adds them, in slice order, to the residual
+// stream and leaves what EPI_RESID leaves, 1/rms to be applied by the consumer.  The norm launch it replaces takes 4.6 - 6.7 us, store, ticket and
+// reading back 2 - 3.
+//
 // PACK (two operand planes, at most 8 rows): MFMA row r < 8 of the B operand carries plane 0 of row r, row r + 8 plane 1 of the same row, so ONE
 // product per weight fragment yields both planes' contributions in output columns r and r + 8, which the reduction adds (hi first).
 // Without PACK one product per plane.  The operand of such a block is stored that way, too (packed planes: one plane whose rows
@@ -75,7 +80,8 @@ __global__ __launch_bounds__(RING_CW * 64, ring_lds(DEPTH, NT, MT, ring_operand(
     constexpr int TAIL = (D + PER - 1) / PER;                     // last k-blocks, behind which some of a k-block's places have no successor
     static_assert(D < 64, "the load counter holds 63");
     __shared__ u32x4 lds[RING_CW * ring_lds(DEPTH, NT, MT, NB) * 64];
-    __shared__ float inv_rms[16];
+    __shared__ float inv_rms[MT * 16];
+    __shared__ int last;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int r = lane & 15, g = lane >> 4;
     const int KS = a.K / KSTEP, nt0 = blockIdx.x * NT;
@@ -96,13 +102,16 @@ __global__ __launch_bounds__(RING_CW * 64, ring_lds(DEPTH, NT, MT, ring_operand(
         }
     }
     constexpr bool SS = EPI == EPI_PARTIAL || EPI == EPI_SWIGLU;  // the products that follow a residual epilogue
+    constexpr int SSR = PACK ? 1 : MT * 16 / RING_CW;             // rows whose 1/rms a wave finds: w, w + 8, ..
     const int nss = a.K / 16;                                     // a multiple of 4
-    float4 ssv[2];                                                // of a row of up to 8192 columns
+    float4 ssv[SSR][2];                                           // of a row of up to 8192 columns
     if constexpr (SS) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-            ssv[i] = *reinterpret_cast<const float4*>(a.ss_in ? a.ss_in + (size_t)min(w, a.R - 1) * nss + min(lane * 4 + i * 256, nss - 4)
-                                                              : reinterpret_cast<const float*>(a.X));   // (any valid address: no load under a branch)
+        for (int q = 0; q < SSR; ++q)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                ssv[q][i] = *reinterpret_cast<const float4*>(a.ss_in ? a.ss_in + (size_t)min(w + q * RING_CW, a.R - 1) * nss + min(lane * 4 + i * 256, nss - 4)
+                                                                     : reinterpret_cast<const float*>(a.X));   // (any valid address: no load under a branch)
     }
     asm volatile("" ::: "memory");                                // (not behind the stream's requests)
 
@@ -128,15 +137,20 @@ __global__ __launch_bounds__(RING_CW * 64, ring_lds(DEPTH, NT, MT, ring_operand(
     each_const(std::make_integer_sequence<int, D>{}, [&](auto ic) { request(std::integral_constant<int, decltype(ic)::value % PER>{}, decltype(ic)::value / PER, decltype(ic)::value); });
 
     if constexpr (SS) {
-        if (a.ss_in && w < a.R) {                                 // uniform
-            float s = lane * 4 < nss ? (ssv[0].x + ssv[0].y) + (ssv[0].z + ssv[0].w) : 0.f;
-            if (lane * 4 + 256 < nss) s += (ssv[1].x + ssv[1].y) + (ssv[1].z + ssv[1].w);
-            for (int e = lane * 4 + 512; e < nss; e += 256) {
-                const float4 v = *reinterpret_cast<const float4*>(a.ss_in + (size_t)w * nss + e);
-                s += (v.x + v.y) + (v.z + v.w);
+        if (a.ss_in) {                                            // uniform
+#pragma unroll
+            for (int q = 0; q < SSR; ++q) {
+                const int row = w + q * RING_CW;
+                if (row >= a.R) break;                            // uniform
+                float s = lane * 4 < nss ? (ssv[q][0].x + ssv[q][0].y) + (ssv[q][0].z + ssv[q][0].w) : 0.f;
+                if (lane * 4 + 256 < nss) s += (ssv[q][1].x + ssv[q][1].y) + (ssv[q][1].z + ssv[q][1].w);
+                for (int e = lane * 4 + 512; e < nss; e += 256) {
+                    const float4 v = *reinterpret_cast<const float4*>(a.ss_in + (size_t)row * nss + e);
+                    s += (v.x + v.y) + (v.z + v.w);
+                }
+                s = wave_sum(s);
+                if (lane == 0) inv_rms[row] = 1.0f / sqrtf(s / (float)a.K + a.eps);
             }
-            s = wave_sum(s);
-            if (lane == 0) inv_rms[w] = 1.0f / sqrtf(s / (float)a.K + a.eps);
         }
     }
 
@@ -198,11 +212,27 @@ __global__ __launch_bounds__(RING_CW * 64, ring_lds(DEPTH, NT, MT, ring_operand(
     __syncthreads();
     if constexpr (EPI != EPI_LOGITS) {
         // one wave per tile, four neighbouring columns of a row per lane (lane l: row l / 4, columns 4 (l % 4) ..)
+        const int n0 = (lane & 3) * 4;
+        // a finished piece of the residual stream: the stream, the next operand without its 1/rms, the tile's share of the row's sum of squares
+        auto close = [&](const f32x4& xv, const float (&gn)[4], int t, int row) {
+            const int col = (nt0 + t) * 16 + n0;
+            float ss = 0.f;
+            if (row < a.R) {
+                *reinterpret_cast<f32x4*>(a.x + (size_t)row * a.N + col) = xv;
+                float y[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) { y[i] = xv[i] * gn[i]; ss += xv[i] * xv[i]; }
+                Traits<T>::template store_split4<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, col, a.N, a.rm), a.actplane, y);
+            }
+            ss += __shfl_xor(ss, 1, 64);
+            ss += __shfl_xor(ss, 2, 64);
+            if (row < a.R && (lane & 3) == 0) a.ss_out[(size_t)row * (a.N / 16) + nt0 + t] = ss;
+        };
 #pragma unroll
         for (int f = 0; f < FIN; ++f) {
             const int p = w + f * RING_CW;
-            if (p >= NT * MT) return;                             // uniform
-            const int t = p % NT, row = p / NT * 16 + (lane >> 2), n0 = (lane & 3) * 4;
+            if (p >= NT * MT) break;                              // uniform
+            const int t = p % NT, row = p / NT * 16 + (lane >> 2);
             auto sum_at = [&](int pos) {
                 f32x4 sum = *reinterpret_cast<const f32x4*>(red + p * 256 + pos);
 #pragma unroll
@@ -214,23 +244,15 @@ __global__ __launch_bounds__(RING_CW * 64, ring_lds(DEPTH, NT, MT, ring_operand(
             if constexpr (SS) {
                 if (a.ss_in && row < a.R) v *= inv_rms[row];
             }
-            if constexpr (EPI == EPI_RESID) {
-                const f32x4 xv = res_x[f] + v;
-                const int col = (nt0 + t) * 16 + n0;
-                float ss = 0.f;
+            if constexpr (EPI == EPI_RESID) close(res_x[f] + v, res_g[f], t, row);
+            else if constexpr (EPI == EPI_PARTIAL) {
+                float* at = a.out + ((size_t)blockIdx.y * a.slice_rows + row) * a.N + (size_t)(nt0 + t) * 16 + n0;
                 if (row < a.R) {
-                    *reinterpret_cast<f32x4*>(a.x + (size_t)row * a.N + col) = xv;
-                    float y[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) { y[i] = xv[i] * res_g[f][i]; ss += xv[i] * xv[i]; }
-                    Traits<T>::template store_split4<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, col, a.N, a.rm), a.actplane, y);
+                    if (a.tickets) {                              // uniform; write-through: another XCD's workgroup may read it in this launch
+                        st_coh(reinterpret_cast<unsigned long long*>(at), __builtin_bit_cast(unsigned long long, float2{v[0], v[1]}));
+                        st_coh(reinterpret_cast<unsigned long long*>(at) + 1, __builtin_bit_cast(unsigned long long, float2{v[2], v[3]}));
+                    } else *reinterpret_cast<f32x4*>(at) = v;
                 }
-                ss += __shfl_xor(ss, 1, 64);
-                ss += __shfl_xor(ss, 2, 64);
-                if (row < a.R && (lane & 3) == 0) a.ss_out[(size_t)row * (a.N / 16) + nt0 + t] = ss;
-            } else if constexpr (EPI == EPI_PARTIAL) {
-                if (row < a.R)
-                    *reinterpret_cast<f32x4*>(a.out + ((size_t)blockIdx.y * a.slice_rows + row) * a.N + (size_t)(nt0 + t) * 16 + n0) = v;
             } else {
                 // tile column n < 8 is gate of FFN column 8 * tile + n, column n + 8 its up projection: two lanes further on
                 f32x4 up;
@@ -243,6 +265,43 @@ __global__ __launch_bounds__(RING_CW * 64, ring_lds(DEPTH, NT, MT, ring_operand(
                     Traits<T>::template store_split4<SPL>(reinterpret_cast<T*>(a.act) + opnd_off<T>(row, (nt0 + t) * 8 + n0, a.N / 2, a.rm), a.actplane, y);
                 }
             }
+        }
+        if constexpr (EPI == EPI_PARTIAL) {
+            if (!a.tickets) return;                               // uniform
+            wait_vm0();                                           // this wave's write-through stores are acknowledged ..
+            __syncthreads();                                      // .. and so are the other waves', before the ticket is drawn
+            if (threadIdx.x == 0)
+                last = __hip_atomic_fetch_add(&a.tickets[blockIdx.x], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.y - 1;
+            __syncthreads();
+            if (!last) return;                                    // uniform for the workgroup
+            constexpr int SB = 4;                                 // slices asked for at once (clamped, surplus ignored), added in order as the norm kernel does
+#pragma unroll
+            for (int f = 0; f < FIN; ++f) {
+                const int p = w + f * RING_CW;
+                if (p >= NT * MT) break;                          // uniform
+                const int t = p % NT, row = p / NT * 16 + (lane >> 2), rd = min(row, a.R - 1), col = (nt0 + t) * 16 + n0;
+                f32x4 xv = *reinterpret_cast<const f32x4*>(a.x + (size_t)rd * a.N + col);
+                float gn[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) gn[i] = Traits<T>::load(reinterpret_cast<const T*>(a.gain) + col + i);
+                for (int s0 = 0; s0 < (int)gridDim.y; s0 += SB) {
+                    unsigned long long q[SB][2];
+#pragma unroll
+                    for (int u = 0; u < SB; ++u) {
+                        const auto* at = reinterpret_cast<const unsigned long long*>(a.out + ((size_t)min(s0 + u, (int)gridDim.y - 1) * a.slice_rows + rd) * a.N + col);
+                        q[u][0] = ld_coh(at);
+                        q[u][1] = ld_coh(at + 1);
+                    }
+#pragma unroll
+                    for (int u = 0; u < SB; ++u)
+                        if (s0 + u < (int)gridDim.y) {
+                            const float2 lo = __builtin_bit_cast(float2, q[u][0]), hi = __builtin_bit_cast(float2, q[u][1]);
+                            xv += f32x4{lo.x, lo.y, hi.x, hi.y};
+                        }
+                }
+                close(xv, gn, t, row);
+            }
+            if (threadIdx.x == 0) st_coh(&a.tickets[blockIdx.x], 0u);   // ready for the next launch
         }
         return;
     }

@@ -247,11 +247,13 @@ struct GemmArgs {
     float inv_temp;     // 1/T, 0 when T = 0
     int32_t rgroups;    // many-row kernel: row groups of one launch (0 or 1: the launch is one group of R rows); with
                         // more, R is the total row count and every workgroup derives its group's rows and pointers
-    const float* ss_in; // EPI_PARTIAL, EPI_SWIGLU, at most 8 rows: null, or [R][K / 16] shares of the rows' sums of squares: the operand lacks 1/rms
+    const float* ss_in; // EPI_PARTIAL, EPI_SWIGLU, few rows: null, or [R][K / 16] shares of the rows' sums of squares: the operand lacks 1/rms
     float eps;
     float* x;           // EPI_RESID: [R][N] residual stream, updated in place
     const void* gain;   // EPI_RESID: [N] norm gain of the next product, storage dtype
     float* ss_out;      // EPI_RESID: [R][N / 16]; the operand planes go to act / actplane ([R][N])
+    unsigned* tickets;  // EPI_PARTIAL of the LDS-ring kernel: null, or one word per workgroup of the grid's x, zero between launches: the last
+                        // K-slice of a group of n-tiles adds all of them in slice order and closes the sub-layer as EPI_RESID does
 };
 
 // 1/rms of row r from the shares of its sum of squares, by one wave (fixed order); K = width of the row, a multiple of 64

@@ -106,6 +106,7 @@ struct sj_kv : Forward {       // the inherited buffers serve the blocks of up t
     int32_t* ranks = nullptr;        // [R] rank of every draft token in its target row (top-k mode)
     int topk = 2;
     unsigned* tickets = nullptr;
+    unsigned* close_tickets = nullptr;            // of the split-K products that close a sub-layer: one per n-tile
     float4 *stats = nullptr, *rowstat = nullptr;
     int32_t *bits = nullptr, *nacc = nullptr, *draft_tok = nullptr;
     double *epart = nullptr, *wpart = nullptr, *eblk = nullptr, *wblk = nullptr;
@@ -485,7 +486,9 @@ extern "C" int sj_kv_create(const sj_model* m, int32_t batch, const int32_t* cap
         ALLOC(kv->V, (size_t)kv->layer_stride * c.n_layers * m->esz);
         // per (sequence, kv head, key range): mpad rows of hd accumulators + (max, sum) in lane order
         ALLOC(kv->opart, (size_t)batch * c.n_kv_heads * kv->nchunk_max * kv->mpad * (hd + 8) * 4);
-        ALLOC(kv->tickets, (size_t)batch * c.n_kv_heads * (kv->mpad / 16) * 4);
+        const size_t attn_tickets = (size_t)batch * c.n_kv_heads * (kv->mpad / 16);
+        ALLOC(kv->tickets, (attn_tickets + d / 16) * 4);
+        kv->close_tickets = kv->tickets + attn_tickets;
         kv->part_elems = forward_elems(kv, R);
         if (kv->part_elems >= PART_LIMIT) return bail(fail(SJ_EINVAL, "batch * (max_gamma + 1) rows need a projection workspace beyond 2^31 elements"));
         ALLOC(kv->xn, (size_t)3 * kv->rpad * d * m->esz);      // up to three operand planes
@@ -838,7 +841,11 @@ struct FewArgs {
     float* x = nullptr;
     const void* gain = nullptr;
     float* ss_out = nullptr;
+    unsigned* tickets = nullptr;       // split-K product that closes its sub-layer: the next operand goes to xg
+    void* xg = nullptr;
+    size_t xgplane = 0;
     template <typename T> void put(GemmArgs& a) const {
+        if (tickets) { a.tickets = tickets; a.act = xg; a.actplane = xgplane; }
         if (packed) a.xplane = a.actplane = packed_plane<T>(rm);
         a.rm = rm;
         a.ss_in = ss_in; a.eps = eps; a.x = x; a.gain = gain; a.ss_out = ss_out;
@@ -847,10 +854,10 @@ struct FewArgs {
 // blocks whose operand planes are packed: both planes of at most 8 rows in one fragment
 template <typename T, int SPL> constexpr bool packed_rows(int rows) { return std::is_same<T, bf16_t>::value && SPL == 2 && rows <= RING_PACK_ROWS; }
 
-// The kernels apply 1/rms in the products that follow a residual epilogue, for as many rows as one takes (resid_plan); elsewhere an operand
-// that lacks it would go through unscaled.
-template <int EPI> static int check_scaled(const FewArgs& fa, int rows) {
-    if (!fa.ss_in || ((EPI == EPI_PARTIAL || EPI == EPI_SWIGLU) && rows <= RING_PACK_ROWS)) return SJ_OK;
+// The kernels apply 1/rms in the products that follow a residual epilogue, the register-ring kernel up to `most` = 8 rows, the LDS-ring kernel
+// up to 32; elsewhere an operand that lacks it would go through unscaled.
+template <int EPI> static int check_scaled(const FewArgs& fa, int rows, int most) {
+    if (!fa.ss_in || ((EPI == EPI_PARTIAL || EPI == EPI_SWIGLU) && rows <= most)) return SJ_OK;
     return fail(SJ_EINVAL, "internal: product %d of %d rows with an operand that lacks its norm", EPI, rows);
 }
 
@@ -858,7 +865,8 @@ template <typename T, int NT, int EPI, int SPL, int WAVES, int D = 2>
 static int gemm(hipStream_t st, const void* Wt, const void* X, size_t xplane, int K, int N, int rows, int split,
                 float* out, void* act, size_t actplane, float4* stats, float inv_temp, const FewArgs& fa = FewArgs{}) {
     if (rows > FEW_ROWS) return fail(SJ_EINVAL, "internal: few-row kernel called with %d rows", rows);
-    if (const int rc = check_scaled<EPI>(fa, rows)) return rc;
+    if (const int rc = check_scaled<EPI>(fa, rows, RING_PACK_ROWS)) return rc;
+    if (fa.tickets) return fail(SJ_EINVAL, "internal: the register-ring kernel closes no split-K product");
     const int ngroups = N / 16 / NT;
     GemmArgs a{};
     a.Wt = Wt; a.X = X; a.xplane = xplane; a.actplane = actplane;
@@ -876,7 +884,7 @@ static int gemm(hipStream_t st, const void* Wt, const void* X, size_t xplane, in
 template <typename T, int NT, int EPI, int SPL, int DEPTH>
 static int gemm_ring(hipStream_t st, const void* Wt, const void* X, size_t xplane, int K, int N, int rows, int split,
                      float* out, void* act, size_t actplane, float4* stats, float inv_temp, const FewArgs& fa = FewArgs{}) {
-    if (const int rc = check_scaled<EPI>(fa, rows)) return rc;
+    if (const int rc = check_scaled<EPI>(fa, rows, RING_ROWS)) return rc;
     GemmArgs a{};
     a.Wt = Wt; a.X = X; a.xplane = xplane; a.actplane = actplane;
     a.K = K; a.N = N; a.R = rows; a.slice_rows = rows;
@@ -1285,6 +1293,13 @@ struct Runner {
         if (R > FEW_ROWS) return gemm_rows<T, EPI_PARTIAL, SPL>(st, W, X, plane(K), K, N, R, p.split, w->part, nullptr, 0, nullptr, 0.f);
         return few_partial<T, SPL>(p, st, W, X, plane(K), K, N, R, w->part, few_args(unscaled));
     }
+    // does the product that reads what O (or else down) leaves run on the LDS-ring kernel?
+    bool ring_consumer(bool after_o) const {
+        const ModelDims& md = m->md;
+        const GemmPlan p = after_o ? few_gate_up_plan(kv->plan_gu, kv->few_rows, 2 * md.F / 16, md.d / Traits<T>::KSTEP, R, SPL, std::is_same<T, bf16_t>::value, kv->ring_rows)
+                                   : plan_of(kv->plan_qkv, md.d, (md.Hq + 2 * md.Hkv) * md.hd);
+        return p.waves == RING_WAVES;
+    }
     // the operand in w->xn lacks its 1/rms factors (it came from a residual epilogue)
     FewArgs few_args(bool unscaled) const {
         FewArgs n;
@@ -1295,11 +1310,21 @@ struct Runner {
     }
     // O or down projection with its sub-layer's residual add, either in its epilogue (`unscaled`: the next operand, with the norm
     // gain, is in w->xn without its 1/rms factors) or left in `parts` K-slices for norm()
+    // (or, from 9 rows on, in the epilogue of the last of its K-slices, where both this product and the next run on the LDS-ring kernel)
     int closing_gemm(const void* W, const void* X, int K, const GemmPlan (&pl)[2], const void* gain, int& parts, bool& unscaled) {
         const int d = m->md.d;
         const GemmPlan p = resid_plan(d, K, Traits<T>::KSTEP, R, SPL, std::is_same<T, bf16_t>::value, kv->ring_rows);
         unscaled = p.nt > 0;
-        if (!unscaled) return partial_gemm(W, X, K, d, pl, &parts);
+        if (!unscaled) {
+            const GemmPlan q = plan_of(pl, K, d);
+            if (R > FEW_ROWS || R <= RING_PACK_ROWS || q.waves != RING_WAVES || !ring_consumer(&pl == &kv->plan_o)) return partial_gemm(W, X, K, d, pl, &parts);
+            if ((size_t)q.split * R * d > w->part_elems) return fail(SJ_EINVAL, "internal: %d K-slices of %d rows exceed the partials' buffer", q.split, R);
+            unscaled = true;
+            FewArgs n = few_args(false);
+            n.x = w->x; n.gain = gain; n.ss_out = w->ss;
+            n.tickets = kv->close_tickets; n.xg = w->xn; n.xgplane = plane(d);
+            return few_partial<T, SPL>(q, st, W, X, plane(K), K, d, R, w->part, n);
+        }
         FewArgs n = few_args(false);
         n.x = w->x; n.gain = gain; n.ss_out = w->ss;
         return few_resid<T, SPL>(p, st, W, X, plane(K), K, d, R, w->xn, plane(d), n);
