@@ -618,7 +618,8 @@ extern "C" int sj_kernel_class_shape(const sj_kv* kv, int32_t kernel_class, int3
         const GemmPlan* p = kernel_class == 1 ? &kv->plan_qkv[1] : kernel_class == 2 ? &kv->plan_o[1] : kernel_class == 4 ? &kv->plan_d[1] : nullptr;
         const int N = kernel_class == 1 ? Nq + 2 * c.n_kv_heads * c.head_dim : c.d_model;
         const int K = kernel_class == 1 ? c.d_model : kernel_class == 2 ? Nq : c.d_ffn;
-        const int trt = kernel_class == 3 && planes == 2 ? tile_rows(rows, 2 * c.d_ffn / 16) : 0;
+        const int lm_planes = !planes || c.n_layers ? planes : 1;      // a head alone: its input is in the storage type
+        const int trt = kernel_class == 3 && planes == 2 ? tile_rows(rows, 2 * c.d_ffn / 16) : kernel_class == 5 ? tile_logits(rows, c.vocab / 16, lm_planes) : 0;
         if (trt) snprintf(buf, (size_t)buf_len, "gemm_tile: row groups of %d in one launch, %d n-tiles per workgroup", trt * 16, TILE_NT);
         else snprintf(buf, (size_t)buf_len, "gemm_rows8: row groups of %d in one launch, 8 or 7 n-tiles per workgroup, %d K-slice(s)",
                  row_tiles(planes, rows) * 16, p ? rows_split(p->split, N / 16, K / kstep, rows, planes) : 1);
@@ -1190,23 +1191,38 @@ static int tune_plans(sj_kv* kv, int rows) {
     return rc;
 }
 
-// The gate / up projection of many rows on large tiles; rt = row tiles of a row group (tile_rows).
-template <typename T, int SPL>
-static int gemm_tile(hipStream_t st, const void* Wt, const void* X, size_t xplane, int K, int N, int rows, int rt, void* act, size_t actplane) {
+// The gate / up projection, or the LM head, of many rows on large tiles; rt = row tiles of a row group (tile_rows, tile_logits).
+template <typename T, int EPI, int SPL>
+static int gemm_tile(hipStream_t st, const void* Wt, const void* X, size_t xplane, int K, int N, int rows, int rt, float* out, void* act, size_t actplane,
+                     float4* stats, float inv_temp) {
     GemmArgs a{};
     a.Wt = Wt; a.X = X; a.xplane = xplane; a.actplane = actplane;
     a.K = K; a.N = N; a.R = rows;
-    a.act = act;
+    a.act = act; a.out = out; a.stats = stats; a.inv_temp = inv_temp;
     a.rgroups = (rows + rt * 16 - 1) / (rt * 16);
     const int ngroups = (N / 16 + TILE_NT - 1) / TILE_NT;
     const int grid = std::min(TILE_WGS, (ngroups + 7) / 8 * 8 * a.rgroups);        // whole rounds of the 8 XCDs
-    switch (rt) {
-        case 10: gemm_tile_kernel<T, SPL, 10, 4><<<grid, TILE_WAVES * 64, 0, st>>>(a); break;
-        case 12: gemm_tile_kernel<T, SPL, 12, 3><<<grid, TILE_WAVES * 64, 0, st>>>(a); break;
-        case 14: gemm_tile_kernel<T, SPL, 14, 3><<<grid, TILE_WAVES * 64, 0, st>>>(a); break;
-        case 16: gemm_tile_kernel<T, SPL, 16, 3><<<grid, TILE_WAVES * 64, 0, st>>>(a); break;
-        default: return fail(SJ_EINVAL, "internal: no large-tile kernel for %d row tiles", rt);
+    bool done = false;
+    auto launch = [&](auto rt_tag, auto ns_tag) {
+        constexpr int RT = decltype(rt_tag)::value, NS = decltype(ns_tag)::value;
+        if (rt != RT) return;
+        gemm_tile_kernel<T, EPI, SPL, RT, NS><<<grid, TILE_WAVES * 64, 0, st>>>(a);
+        done = true;
+    };
+    if constexpr (SPL == 1) {
+        launch(std::integral_constant<int, 16>{}, std::integral_constant<int, 5>{});
+        launch(std::integral_constant<int, 18>{}, std::integral_constant<int, 4>{});
+    } else {
+        if constexpr (EPI == EPI_LOGITS) {
+            launch(std::integral_constant<int, 8>{}, std::integral_constant<int, 5>{});
+            launch(std::integral_constant<int, 9>{}, std::integral_constant<int, 4>{});
+        }
+        launch(std::integral_constant<int, 10>{}, std::integral_constant<int, 4>{});
+        launch(std::integral_constant<int, 12>{}, std::integral_constant<int, 3>{});
+        launch(std::integral_constant<int, 14>{}, std::integral_constant<int, 3>{});
+        launch(std::integral_constant<int, 16>{}, std::integral_constant<int, 3>{});
     }
+    if (!done) return fail(SJ_EINVAL, "internal: no large-tile kernel for %d row tiles", rt);
     LAUNCHCHK("gemm_tile");
     return SJ_OK;
 }
@@ -1218,7 +1234,10 @@ template <typename T, int EPI, int SPL>
 static int gemm_rows(hipStream_t st, const void* Wt, const void* X, size_t xplane, int K, int N, int rows, int split,
                      float* out, void* act, size_t actplane, float4* stats, float inv_temp) {
     if constexpr (EPI == EPI_SWIGLU && SPL == 2 && std::is_same<T, bf16_t>::value) {
-        if (const int trt = tile_rows(rows, N / 16)) return gemm_tile<T, SPL>(st, Wt, X, xplane, K, N, rows, trt, act, actplane);
+        if (const int trt = tile_rows(rows, N / 16)) return gemm_tile<T, EPI, SPL>(st, Wt, X, xplane, K, N, rows, trt, nullptr, act, actplane, nullptr, 0.f);
+    }
+    if constexpr (EPI == EPI_LOGITS && SPL <= 2 && std::is_same<T, bf16_t>::value) {
+        if (const int trt = tile_logits(rows, N / 16, SPL)) return gemm_tile<T, EPI, SPL>(st, Wt, X, xplane, K, N, rows, trt, out, nullptr, 0, stats, inv_temp);
     }
     const int ntiles = N / 16, rt = row_tiles(rows_planes<T, SPL>, rows), rgroups = (rows + rt * 16 - 1) / (rt * 16);
     const int mt = (std::min(rows, rt * 16) + 15) / 16;
@@ -1488,7 +1507,8 @@ struct Runner {
             rc = exact_operand
                 ? gemm_rows<T, EPI_LOGITS, 1>(st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, 1, kv->logits, nullptr, 0, kv->stats, md.inv_temp)
                 : gemm_rows<T, EPI_LOGITS, SPL>(st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, 1, kv->logits, nullptr, 0, kv->stats, md.inv_temp);
-            nblk = md.V / 16 / ROWS_NT;
+            const int planes = std::is_same<T, float>::value ? 0 : exact_operand ? 1 : SPL;
+            nblk = md.V / 16 / (planes && planes <= 2 && tile_logits(R, md.V / 16, planes) ? TILE_STAT : ROWS_NT);
         } else {
             const GemmPlan p = few_logits_plan(kv->plan_lm, kv->few_rows, md.V / 16, md.d / Traits<T>::KSTEP, R, exact_operand ? 1 : SPL, std::is_same<T, bf16_t>::value, kv->ring_rows);
             rc = exact_operand

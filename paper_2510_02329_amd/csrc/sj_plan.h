@@ -361,6 +361,19 @@ inline int tile_rows(int rows, int ntiles) {
     return tiles * 100 >= rounds * TILE_WGS * (rounds > 1 ? 65 : 80) ? rt : 0;
 }
 
+// The same for the LM head: row tiles of a row group of the large-tile kernel, 0: not taken.  From 97 rows on two planes, from 225 on one (a wave needs
+// four row tiles or more for its fragments of weights to pay), where the tiles fill the chip's rounds.
+constexpr int TILE_STAT = 4;                   // n-tiles of a wave, and of a softmax statistic
+inline int tile_logits(int rows, int ntiles, int planes) {
+    const int tiles = (rows + 15) / 16;
+    int rt = 0;
+    if (planes == 2 && tiles >= 7) rt = tiles <= 8 ? 8 : tiles == 9 ? 9 : std::max(10, (tiles + (tiles + 15) / 16 - 1) / ((tiles + 15) / 16) + 1) / 2 * 2;
+    if (planes == 1 && tiles >= 15) { const int groups = (tiles + 17) / 18; rt = (tiles + groups - 1) / groups <= 16 ? 16 : 18; }
+    if (!rt) return 0;
+    const int wgs = (ntiles + TILE_NT - 1) / TILE_NT * ((tiles + rt - 1) / rt), rounds = (wgs + TILE_WGS - 1) / TILE_WGS;
+    return wgs * 100 >= rounds * TILE_WGS * (rounds > 1 ? 65 : 80) ? rt : 0;
+}
+
 // A projection that closes a sub-layer (O, down) with the residual add in its epilogue (EPI_RESID; no K-slices): one launch
 // instead of two.  Without slices a workgroup has one n-tile (two, four where that fills the chip) and reads as much operand as
 // weights, so it pays up to 8 rows, where both planes are one packed fragment: 8B shape, 6 rows: down 20.3 -> 21.0 us, O 8.5 ->
