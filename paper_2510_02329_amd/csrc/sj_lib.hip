@@ -1203,25 +1203,22 @@ static int gemm_tile(hipStream_t st, const void* Wt, const void* X, size_t xplan
     const int ngroups = (N / 16 + TILE_NT - 1) / TILE_NT;
     const int grid = std::min(TILE_WGS, (ngroups + 7) / 8 * 8 * a.rgroups);        // whole rounds of the 8 XCDs
     bool done = false;
-    auto launch = [&](auto rt_tag, auto ns_tag) {
-        constexpr int RT = decltype(rt_tag)::value, NS = decltype(ns_tag)::value;
+    auto launch = [&](auto rt_tag) {
+        constexpr int RT = decltype(rt_tag)::value, NS = std::min(5, 160 / (RT * SPL + TILE_NT));      // as many stages as 160 KB hold, up to five
         if (rt != RT) return;
         gemm_tile_kernel<T, EPI, SPL, RT, NS><<<grid, TILE_WAVES * 64, 0, st>>>(a);
         done = true;
     };
-    if constexpr (SPL == 1) {
-        launch(std::integral_constant<int, 16>{}, std::integral_constant<int, 5>{});
-        launch(std::integral_constant<int, 18>{}, std::integral_constant<int, 4>{});
-    } else {
-        if constexpr (EPI == EPI_LOGITS) {
-            launch(std::integral_constant<int, 8>{}, std::integral_constant<int, 5>{});
-            launch(std::integral_constant<int, 9>{}, std::integral_constant<int, 4>{});
-        }
-        launch(std::integral_constant<int, 10>{}, std::integral_constant<int, 4>{});
-        launch(std::integral_constant<int, 12>{}, std::integral_constant<int, 3>{});
-        launch(std::integral_constant<int, 14>{}, std::integral_constant<int, 3>{});
-        launch(std::integral_constant<int, 16>{}, std::integral_constant<int, 3>{});
+    if constexpr (EPI == EPI_LOGITS) {                 // tile_rows has no group below ten row tiles
+        launch(std::integral_constant<int, 6>{});
+        launch(std::integral_constant<int, 8>{});
+        if constexpr (SPL == 2) launch(std::integral_constant<int, 9>{});
+        else launch(std::integral_constant<int, 18>{});
     }
+    launch(std::integral_constant<int, 10>{});
+    launch(std::integral_constant<int, 12>{});
+    launch(std::integral_constant<int, 14>{});
+    launch(std::integral_constant<int, 16>{});
     if (!done) return fail(SJ_EINVAL, "internal: no large-tile kernel for %d row tiles", rt);
     LAUNCHCHK("gemm_tile");
     return SJ_OK;
@@ -1508,7 +1505,7 @@ struct Runner {
                 ? gemm_rows<T, EPI_LOGITS, 1>(st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, 1, kv->logits, nullptr, 0, kv->stats, md.inv_temp)
                 : gemm_rows<T, EPI_LOGITS, SPL>(st, m->lm_head, w->xn, plane(md.d), md.d, md.V, R, 1, kv->logits, nullptr, 0, kv->stats, md.inv_temp);
             const int planes = std::is_same<T, float>::value ? 0 : exact_operand ? 1 : SPL;
-            nblk = md.V / 16 / (planes && planes <= 2 && tile_logits(R, md.V / 16, planes) ? TILE_STAT : ROWS_NT);
+            nblk = md.V / 16 / (tile_logits(R, md.V / 16, planes) ? TILE_STAT : ROWS_NT);
         } else {
             const GemmPlan p = few_logits_plan(kv->plan_lm, kv->few_rows, md.V / 16, md.d / Traits<T>::KSTEP, R, exact_operand ? 1 : SPL, std::is_same<T, bf16_t>::value, kv->ring_rows);
             rc = exact_operand

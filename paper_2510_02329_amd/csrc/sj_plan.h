@@ -361,16 +361,20 @@ inline int tile_rows(int rows, int ntiles) {
     return tiles * 100 >= rounds * TILE_WGS * (rounds > 1 ? 65 : 80) ? rt : 0;
 }
 
-// The same for the LM head: row tiles of a row group of the large-tile kernel, 0: not taken.  From 97 rows on two planes, from 225 on one (a wave needs
-// four row tiles or more for its fragments of weights to pay), where the tiles fill the chip's rounds.
+// The same for the LM head, on one operand plane or two: row tiles of a row group of the large-tile kernel, 0: not taken.  Row groups are
+// as few as LDS allows (16 row tiles of two planes, 18 of one) and of nearly equal size.  us of one layer and the head, or of a head
+// alone (one plane), with the loader-wave kernel / with this one:
+//   8B shape, rows 64 / 81 / 96 / 144 / 154 / 224: 463 / 459, 525 / 502, 535 / 506, 1367 / 1331 (4 layers), 896 / 686, 931 / 809;
+//   head alone, rows 64 / 80 / 128 / 192 / 288 / 360 / 576: 262 / 281, 292 / 286, 326 / 302, 360 / 317, 425 / 394, 605 / 555, 708 / 638;
+//   1B, rows 64 / 96 / 192 / 320: 284 / 280, 328 / 308, 512 / 415, 721 / 615; 70B, rows 64 / 96 / 144 / 192: 903 / 889, 1096 / 1039, 1315 / 1236, 1861 / 1524;
+//   48 rows: 432 / 442 (8B), 261 / 278 (head alone).
+// Gate / up of the 70B shape on these small row groups: 96 and 144 rows 0 %, 99 rows 2 % of a layer and head: not taken.
 constexpr int TILE_STAT = 4;                   // n-tiles of a wave, and of a softmax statistic
 inline int tile_logits(int rows, int ntiles, int planes) {
-    const int tiles = (rows + 15) / 16;
-    int rt = 0;
-    if (planes == 2 && tiles >= 7) rt = tiles <= 8 ? 8 : tiles == 9 ? 9 : std::max(10, (tiles + (tiles + 15) / 16 - 1) / ((tiles + 15) / 16) + 1) / 2 * 2;
-    if (planes == 1 && tiles >= 15) { const int groups = (tiles + 17) / 18; rt = (tiles + groups - 1) / groups <= 16 ? 16 : 18; }
-    if (!rt) return 0;
-    const int wgs = (ntiles + TILE_NT - 1) / TILE_NT * ((tiles + rt - 1) / rt), rounds = (wgs + TILE_WGS - 1) / TILE_WGS;
+    if (rows <= 64 || planes < 1 || planes > 2) return 0;
+    const int tiles = (rows + 15) / 16, most = planes == 2 ? 16 : 18, groups = (tiles + most - 1) / most, per = (tiles + groups - 1) / groups;
+    const int rt = planes == 2 && per == 9 ? 9 : (per + 1) / 2 * 2;                // the sizes gemm_tile launches: even ones, and 9 on two planes
+    const int wgs = (ntiles + TILE_NT - 1) / TILE_NT * groups, rounds = (wgs + TILE_WGS - 1) / TILE_WGS;
     return wgs * 100 >= rounds * TILE_WGS * (rounds > 1 ? 65 : 80) ? rt : 0;
 }
 

@@ -39,17 +39,20 @@ def test_step_on_large_tiles(batch, gamma, d, ffn, planes):
     _step_matches(shape, planes, "bf16", "gemm_tile" if planes == 2 else "gemm_rows8")
 
 
-# The same tiles with the LM head's epilogue: every group size at its edges on two planes (128, 144, 160, 256 rows and one more; 96: the
-# loader waves stay) and on one (225, 256, 288 rows and one more), halves of unequal row tiles, two groups, n-tiles that end in the
-# middle of a tile, a second round of the chip, fewer k-steps than stages.
-@pytest.mark.parametrize("batch,gamma,vocab,d,planes,kernel", [(12, 7, 52480, 64, 2, "gemm_rows8"), (11, 8, 52480, 64, 2, "groups of 128"),
+# The same tiles with the LM head's epilogue, on two planes and on one: the loader waves up to 64 rows, then every group size at its
+# edges, halves of unequal row tiles, two groups, n-tiles that end in the middle of a tile, a second round of the chip, fewer
+# k-steps than stages.
+@pytest.mark.parametrize("batch,gamma,vocab,d,planes,kernel", [(8, 7, 52480, 64, 2, "gemm_rows8"), (13, 4, 52480, 64, 2, "groups of 96"),
+                                                               (12, 7, 52608, 128, 2, "groups of 96"), (11, 8, 52480, 64, 2, "groups of 128"),
                                                                (16, 7, 52480, 192, 2, "groups of 128"), (43, 2, 52480, 128, 2, "groups of 144"),
                                                                (16, 8, 52608, 256, 2, "groups of 144"), (29, 4, 52480, 64, 2, "groups of 160"),
-                                                               (32, 7, 52480, 64, 2, "groups of 256"), (37, 6, 26240, 64, 2, "groups of 160"),
-                                                               (64, 4, 42752, 128, 2, "groups of 160"), (28, 7, 52480, 64, 1, "gemm_rows8"),
+                                                               (28, 7, 52480, 128, 2, "groups of 224"), (32, 7, 52480, 64, 2, "groups of 256"),
+                                                               (37, 6, 26240, 64, 2, "groups of 144"), (64, 4, 42752, 128, 2, "groups of 160"),
+                                                               (8, 7, 52480, 64, 1, "gemm_rows8"), (13, 4, 52480, 64, 1, "groups of 96"),
+                                                               (43, 2, 52480, 64, 1, "groups of 160"), (28, 7, 52480, 64, 1, "groups of 224"),
                                                                (45, 4, 52480, 64, 1, "groups of 256"), (32, 7, 52608, 256, 1, "groups of 256"),
                                                                (43, 5, 52480, 128, 1, "groups of 288"), (32, 8, 85248, 64, 1, "groups of 288"),
-                                                               (37, 7, 26240, 192, 1, "groups of 256")])
+                                                               (37, 7, 26240, 192, 1, "groups of 160")])
 def test_lm_head_on_large_tiles(batch, gamma, vocab, d, planes, kernel):
     shape = dataclasses.replace(SMALL, name=f"lm_{batch}_{gamma}_{vocab}_{d}_{planes}", n_layers=1, batch=batch, gamma=gamma, d_model=d, d_ffn=128,
                                 n_q_heads=2, n_kv_heads=1, head_dim=64, vocab=vocab)
