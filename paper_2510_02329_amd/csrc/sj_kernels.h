@@ -506,19 +506,27 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(GemmArgs a) {
 // ---------------------------------------------------------------------------------------------
 // Vocabulary softmax statistics of each row from the LM-head workgroups' partials:
 // row max, Z = sum exp((l - max)/T), lowest-index arg-max.  One workgroup per row.
-__device__ __forceinline__ void softmax_merge_row(int r, const float4* __restrict__ stats, int nblk, float inv_temp,
-                                                  float4* __restrict__ rowstat) {
+// Bound by the latency of its loads: a thread requests its first KEEP statistics together and keeps them for the sum (MERGE_FEW).
+template <int KEEP>
+__device__ __forceinline__ void softmax_merge_keep(int r, const float4* __restrict__ stats, int nblk, float inv_temp,
+                                                   float4* __restrict__ rowstat) {
     __shared__ float smx[4];
     __shared__ int sarg[4];
     __shared__ float red[4];
     const float4* s = stats + (size_t)r * nblk;
+    const int i0 = threadIdx.x;
+    float4 keep[KEEP];
+#pragma unroll
+    for (int k = 0; k < KEEP; ++k) keep[k] = s[min(i0 + k * 256, nblk - 1)];       // past the end the last one again: no new maximum, not summed
     float mx = -INFINITY;
     int arg = 0x7fffffff;
-    for (int i = threadIdx.x; i < nblk; i += 256) {
-        const float4 v = s[i];
+    auto take = [&](const float4& v) {
         const int a = __float_as_int(v.z);
         if (v.x > mx || (v.x == mx && a < arg)) { mx = v.x; arg = a; }
-    }
+    };
+#pragma unroll
+    for (int k = 0; k < KEEP; ++k) take(keep[k]);
+    for (int i = i0 + KEEP * 256; i < nblk; i += 256) take(s[i]);
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
         const float omx = __shfl_xor(mx, o, 64);
@@ -531,13 +539,23 @@ __device__ __forceinline__ void softmax_merge_row(int r, const float4* __restric
     for (int w = 1; w < 4; ++w)
         if (smx[w] > mx || (smx[w] == mx && sarg[w] < arg)) { mx = smx[w]; arg = sarg[w]; }
     float z = 0.f;
-    if (inv_temp > 0.f)
-        for (int i = threadIdx.x; i < nblk; i += 256) {
+    if (inv_temp > 0.f) {
+#pragma unroll
+        for (int k = 0; k < KEEP; ++k)
+            if (i0 + k * 256 < nblk) z += keep[k].y * expf((keep[k].x - mx) * inv_temp);
+        for (int i = i0 + KEEP * 256; i < nblk; i += 256) {
             const float4 v = s[i];
             z += v.y * expf((v.x - mx) * inv_temp);
         }
+    }
     z = block_sum_256(z, red);
     if (threadIdx.x == 0) rowstat[r] = float4{mx, z, __int_as_float(arg), 0.f};
+}
+
+constexpr int MERGE_FEW = 1024;                // statistics of a row that four to a thread hold; more: sixteen
+__device__ __forceinline__ void softmax_merge_row(int r, const float4* __restrict__ stats, int nblk, float inv_temp, float4* __restrict__ rowstat) {
+    if (nblk <= MERGE_FEW) softmax_merge_keep<MERGE_FEW / 256>(r, stats, nblk, inv_temp, rowstat);          // uniform
+    else softmax_merge_keep<16>(r, stats, nblk, inv_temp, rowstat);
 }
 
 __global__ __launch_bounds__(256) void softmax_merge_kernel(const float4* __restrict__ stats, int nblk, float inv_temp,
