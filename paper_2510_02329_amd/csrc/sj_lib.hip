@@ -1020,14 +1020,14 @@ static int pick_plan(GemmPlan& plan, const std::vector<GemmPlan>& candidates, Ti
     return SJ_OK;
 }
 
-// Launch shapes of the three split-K projections for few rows, chosen by measurement when the cache object is
+// Launch shapes of the three split-K projections for few rows (of up to `most` K-slices), chosen by measurement when the cache object is
 // created: which of (n-tiles, waves, K-slices, ring depth) streams a given weight matrix fastest depends on its
 // shape and on the number of row tiles in ways the workgroup-count rule of plan_partial does not capture (70B-shaped
 // QKV with two row tiles: 50 us with the rule's shape, 35 us with the best one).  Every candidate runs over up to 16
 // layers' weights back to back (distinct layers, so nothing is served from cache); the rule's plan stays unless a
 // candidate is at least 5 % faster (pick_plan).  SJ_TUNE=0 keeps the rule's plans (launch shapes then never differ between runs).
 template <typename T, int SPL>
-static int tune_one(sj_kv* kv, GemmPlan& plan, void* LayerW::*which, const void* X, int K, int N, int rows,
+static int tune_one(sj_kv* kv, GemmPlan& plan, void* LayerW::*which, const void* X, int K, int N, int rows, int most,
                     hipEvent_t e0, hipEvent_t e1) {
     const sj_model* m = kv->m;
     const int ksteps = K / Traits<T>::KSTEP, ntiles = N / 16;
@@ -1051,7 +1051,9 @@ static int tune_one(sj_kv* kv, GemmPlan& plan, void* LayerW::*which, const void*
         us = (double)ms * 1e3 / nl;
         return SJ_OK;
     };
-    return pick_plan(plan, partial_candidates(ntiles, ksteps, rows, SPL, std::is_same<T, bf16_t>::value), time_plan);
+    std::vector<GemmPlan> cands = partial_candidates(ntiles, ksteps, rows, SPL, std::is_same<T, bf16_t>::value);
+    cands.erase(std::remove_if(cands.begin(), cands.end(), [&](const GemmPlan& p) { return p.split > most; }), cands.end());
+    return pick_plan(plan, cands, time_plan);
 }
 
 template <typename T, int SPL>
@@ -1159,9 +1161,9 @@ static int tune_plans(sj_kv* kv, int rows) {
     int rc = SJ_OK;
 #define SJ_TUNE3(T, SPL)                                                                                          \
     do {                                                                                                          \
-        if (!rc) rc = tune_one<T, SPL>(kv, kv->plan_qkv[0], &LayerW::wqkv, kv->xn, d, Nq + 2 * Nk, rows, e0, e1);  \
-        if (!rc) rc = tune_one<T, SPL>(kv, kv->plan_o[0], &LayerW::wo, kv->attn_out, Nq, d, rows, e0, e1);         \
-        if (!rc) rc = tune_one<T, SPL>(kv, kv->plan_d[0], &LayerW::wd, kv->act, F, d, rows, e0, e1);               \
+        if (!rc) rc = tune_one<T, SPL>(kv, kv->plan_qkv[0], &LayerW::wqkv, kv->xn, d, Nq + 2 * Nk, rows, QKV_MEASURED_SLICES, e0, e1);  \
+        if (!rc) rc = tune_one<T, SPL>(kv, kv->plan_o[0], &LayerW::wo, kv->attn_out, Nq, d, rows, 8, e0, e1);         \
+        if (!rc) rc = tune_one<T, SPL>(kv, kv->plan_d[0], &LayerW::wd, kv->act, F, d, rows, 8, e0, e1);               \
         if (!rc) rc = tune_gate_up<T, SPL>(kv, rows, e0, e1);                                                     \
         if (!rc) rc = tune_lm_head<T, SPL>(kv, rows, e0, e1);                                                     \
     } while (0)

@@ -258,6 +258,9 @@ inline GemmPlan rule_logits(int ntiles, int ksteps, int rows, int planes, bool b
 // row tile, two.  A draft block of 12 sequences runs 12 rows on an object made for blocks of 60: in the shapes of 32 rows, or what stood in
 // for those that do not take 12, its QKV and O took 7.2 us each; in the rule's for 12 rows 5.2 and 4.9.
 constexpr int QKV_SLICES = 2;
+// The start-up measurement times a projection without the kernel that adds its K-slices, which for QKV is attention, in every layer: what
+// 8 slices gain there is lost again (1B, 1 row, a draft block: 8 slices 4642 us, 4 slices 4529 - 4580).
+constexpr int QKV_MEASURED_SLICES = 4;
 inline int few_class(int rows) { return rows <= RING_PACK_ROWS ? 0 : rows <= 16 ? 1 : 2; }
 inline GemmPlan few_partial_plan(const GemmPlan& made, int made_rows, int ntiles, int ksteps, int rows, int planes, bool bf16, int ring_rows, int most = 8) {
     return resolve_partial(few_class(rows) == few_class(made_rows) ? made : rule_partial(ntiles, ksteps, rows, planes, bf16, ring_rows, most), ntiles, ksteps, rows, planes, bf16);
