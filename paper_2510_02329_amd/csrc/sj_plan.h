@@ -122,20 +122,25 @@ inline GemmPlan ring_rule_partial(int ntiles, int ksteps) {
 // 13.8 with four).  us of the shapes that fill the chip, n-tiles x slices:
 //   8B, 20 rows: down 4 x 4 21.6, 8 x 8 22.1; QKV 3 x 2 11.4, 3 x 4 12.6;   70B, 24 rows: O 4 x 2 24.8, 8 x 4 28.6; down 8 x 4 72.3, 4 x 2 75.5;
 //   1B, 12 rows: O 1 x 2 4.4; down 2 x 4 8.6, 4 x 8 9.1; QKV (192 workgroups) 2 x 2 5.2, 1 x 1 6.1.
+// Two row tiles: the operand counts 1.3 times (70B, 24 rows, the stack of 80 layers: O 8 x 4 25.37 ms, 4 x 2 24.92).  And a wave of QKV, whose sums are
+// rounded into the cache, adds at most 8 k-steps of 32: the 70B shape takes four slices, which costs what O gains (25.35 ms).
+constexpr int QKV_SLICES = 2;
 inline GemmPlan ring_rule_partial_rows(int ntiles, int ksteps, int rows, int planes, int most) {
     GemmPlan best;
     best.waves = 0;
     double best_cost = 1e30;
     const int mt = rows > 16 ? 2 : 1, nb = ring_operand(false, planes, mt);
-    for (int split = 1; split <= most; split *= 2)
+    const int least = most == QKV_SLICES && rows > 16 ? std::min(8, ksteps / (RING_CW * 8)) : 1;
+    for (int split = 1; split <= most || split < 2 * least; split *= 2)
         for (int nt : {1, 2, 3, 4, 5, 8}) {
+            if (split < least) continue;
             const int wgs = ntiles / nt * split, to_cu = (wgs + 255) / 256;
             GemmPlan p;
             p.nt = nt; p.waves = RING_WAVES; p.split = split; p.depth = wgs <= 256 && nt >= 3 ? 18 : RING_TWO;
             if (!partial_fits(p, ntiles, ksteps, rows, planes, true)) p.depth = RING_TWO;
             if (!partial_fits(p, ntiles, ksteps, rows, planes, true)) p.depth = 4;
             if (!partial_fits(p, ntiles, ksteps, rows, planes, true)) continue;
-            const double cost = 256.0 * to_cu / wgs * (to_cu * ((double)ksteps / RING_CW / split * (nt + 2 * nb) + 4 * nt * mt + 8) + 6 * split);
+            const double cost = 256.0 * to_cu / wgs * (to_cu * ((double)ksteps / RING_CW / split * (nt + (mt == 2 ? 1.3 : 2.0) * nb) + 4 * nt * mt + 8) + 6 * split);
             if (cost < best_cost - 1e-9) { best = p; best_cost = cost; }
         }
     return best;
@@ -257,7 +262,6 @@ inline GemmPlan rule_logits(int ntiles, int ksteps, int rows, int planes, bool b
 // A shape made (by the rule or the measurement) for one row count speaks for others with as many operand fragments to a k-step: one packed, one
 // row tile, two.  A draft block of 12 sequences runs 12 rows on an object made for blocks of 60: in the shapes of 32 rows, or what stood in
 // for those that do not take 12, its QKV and O took 7.2 us each; in the rule's for 12 rows 5.2 and 4.9.
-constexpr int QKV_SLICES = 2;
 // The start-up measurement times a projection without the kernel that adds its K-slices, which for QKV is attention, in every layer: what
 // 8 slices gain there is lost again (1B, 1 row, a draft block: 8 slices 4642 us, 4 slices 4529 - 4580).
 constexpr int QKV_MEASURED_SLICES = 4;
