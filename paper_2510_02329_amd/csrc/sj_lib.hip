@@ -88,6 +88,9 @@ struct Forward {
     int32_t *row_tok = nullptr, *prefill_tok = nullptr;
 };
 
+enum class Product { qkv, o, down };          // the split-K projections
+static Sums sums_of(Product p) { return p == Product::qkv ? Sums::attention : Sums::closing; }
+
 struct sj_kv : Forward {       // the inherited buffers serve the blocks of up to max_gamma + 1 rows per sequence
     const sj_model* m = nullptr;
     int batch = 0, max_rows = 0, mpad = 0, cap_max = 64;
@@ -112,6 +115,7 @@ struct sj_kv : Forward {       // the inherited buffers serve the blocks of up t
     double *epart = nullptr, *wpart = nullptr, *eblk = nullptr, *wblk = nullptr;
     int chunk_keys = 64, nchunk_max = 1, nslab = 0, slab_len = 0;
     GemmPlan plan_qkv[2], plan_o[2], plan_d[2];   // [0]: few-row kernel (at most 32 rows), [1]: more
+    const GemmPlan* plans(Product p) const { return p == Product::qkv ? plan_qkv : p == Product::o ? plan_o : plan_d; }
     GemmPlan plan_gu;                             // gate / up projection with few rows (no K-slices)
     GemmPlan plan_lm{8, 4, 1, 2};                 // LM head with few rows
     int few_rows = 1;                             // rows that the few-row shapes were made for
@@ -340,13 +344,13 @@ static void rule_plans(sj_kv* kv) {
     // bf16 with one or two planes: the LDS-ring kernel where a shape of it fits (4 - 13 % faster than the register-ring kernel from 1 to 32 rows; the
     // start-up measurement may still prefer another shape).  SJ_RING_ROWS = 0..32 moves the row limit of this rule.
     if (const char* e = std::getenv("SJ_RING_ROWS")) kv->ring_rows = std::min(std::max(std::atoi(e), 0), RING_ROWS);
-    auto partial = [&](GemmPlan (&plan)[2], int N, int K, int most = 8) {
-        plan[0] = rule_partial(N / 16, K / kstep, rows, planes, bf16, kv->ring_rows, most);
+    auto partial = [&](GemmPlan (&plan)[2], int N, int K, Sums sums) {
+        plan[0] = rule_partial(N / 16, K / kstep, rows, planes, bf16, kv->ring_rows, sums);
         plan[1] = plan_partial(N / 16, K / kstep, false);
     };
-    partial(kv->plan_qkv, Nq + 2 * Nk, d, QKV_SLICES);
-    partial(kv->plan_o, d, Nq);
-    partial(kv->plan_d, d, F);
+    partial(kv->plan_qkv, Nq + 2 * Nk, d, Sums::attention);
+    partial(kv->plan_o, d, Nq, Sums::closing);
+    partial(kv->plan_d, d, F, Sums::closing);
     kv->plan_gu = rule_gate_up(2 * F / 16, d / kstep, rows, planes, bf16, kv->ring_rows);
     rule_lm_head(kv, planes);
 }
@@ -629,16 +633,16 @@ extern "C" int sj_kernel_class_shape(const sj_kv* kv, int32_t kernel_class, int3
     const sj_config& c = kv->m->cfg;
     const bool bf16 = c.dtype == SJ_DTYPE_BF16;
     const int kstep = bf16 ? 32 : 16, planes = bf16 ? kv->planes : 1, d = c.d_model, Nq = c.n_q_heads * c.head_dim;
-    auto partial = [&](const GemmPlan& q, int N, int K, int most = 8) { return few_partial_plan(q, kv->few_rows, N / 16, K / kstep, rows, planes, bf16, kv->ring_rows, most); };
+    auto partial = [&](const GemmPlan& q, int N, int K, Sums sums) { return few_partial_plan(q, kv->few_rows, N / 16, K / kstep, rows, planes, bf16, kv->ring_rows, sums); };
     GemmPlan p;
     switch (kernel_class) {
-        case 1: p = partial(kv->plan_qkv[0], Nq + 2 * c.n_kv_heads * c.head_dim, d, QKV_SLICES); break;
+        case 1: p = partial(kv->plan_qkv[0], Nq + 2 * c.n_kv_heads * c.head_dim, d, Sums::attention); break;
         case 3: p = few_gate_up_plan(kv->plan_gu, kv->few_rows, 2 * c.d_ffn / 16, d / kstep, rows, planes, bf16, kv->ring_rows); break;
         case 5: p = few_logits_plan(kv->plan_lm, kv->few_rows, c.vocab / 16, d / kstep, rows, c.n_layers ? planes : 1, bf16, kv->ring_rows); break;
         default: {
             const int K = kernel_class == 2 ? Nq : c.d_ffn;
             p = resid_plan(d, K, kstep, rows, planes, bf16, kv->ring_rows);
-            if (!p.nt) p = partial(kernel_class == 2 ? kv->plan_o[0] : kv->plan_d[0], d, K);
+            if (!p.nt) p = partial(kernel_class == 2 ? kv->plan_o[0] : kv->plan_d[0], d, K, Sums::closing);
         }
     }
     if (p.waves == RING_WAVES)
@@ -1020,14 +1024,13 @@ static int pick_plan(GemmPlan& plan, const std::vector<GemmPlan>& candidates, Ti
     return SJ_OK;
 }
 
-// Launch shapes of the three split-K projections for few rows (of up to `most` K-slices), chosen by measurement when the cache object is
-// created: which of (n-tiles, waves, K-slices, ring depth) streams a given weight matrix fastest depends on its
+// Launch shapes of the three split-K projections for few rows, chosen by measurement when the cache object is created: which of (n-tiles, waves, K-slices, ring depth) streams a given weight matrix fastest depends on its
 // shape and on the number of row tiles in ways the workgroup-count rule of plan_partial does not capture (70B-shaped
 // QKV with two row tiles: 50 us with the rule's shape, 35 us with the best one).  Every candidate runs over up to 16
 // layers' weights back to back (distinct layers, so nothing is served from cache); the rule's plan stays unless a
 // candidate is at least 5 % faster (pick_plan).  SJ_TUNE=0 keeps the rule's plans (launch shapes then never differ between runs).
 template <typename T, int SPL>
-static int tune_one(sj_kv* kv, GemmPlan& plan, void* LayerW::*which, const void* X, int K, int N, int rows, int most,
+static int tune_one(sj_kv* kv, GemmPlan& plan, void* LayerW::*which, const void* X, int K, int N, int rows, Sums sums,
                     hipEvent_t e0, hipEvent_t e1) {
     const sj_model* m = kv->m;
     const int ksteps = K / Traits<T>::KSTEP, ntiles = N / 16;
@@ -1051,9 +1054,7 @@ static int tune_one(sj_kv* kv, GemmPlan& plan, void* LayerW::*which, const void*
         us = (double)ms * 1e3 / nl;
         return SJ_OK;
     };
-    std::vector<GemmPlan> cands = partial_candidates(ntiles, ksteps, rows, SPL, std::is_same<T, bf16_t>::value);
-    cands.erase(std::remove_if(cands.begin(), cands.end(), [&](const GemmPlan& p) { return p.split > most; }), cands.end());
-    return pick_plan(plan, cands, time_plan);
+    return pick_plan(plan, measured_partials(plan, ntiles, ksteps, rows, SPL, std::is_same<T, bf16_t>::value, sums), time_plan);
 }
 
 template <typename T, int SPL>
@@ -1161,10 +1162,10 @@ static int tune_plans(sj_kv* kv, int rows) {
     int rc = SJ_OK;
 #define SJ_TUNE3(T, SPL)                                                                                          \
     do {                                                                                                          \
-        if (!rc) rc = tune_one<T, SPL>(kv, kv->plan_qkv[0], &LayerW::wqkv, kv->xn, d, Nq + 2 * Nk, rows, QKV_MEASURED_SLICES, e0, e1);  \
-        if (!rc) rc = tune_one<T, SPL>(kv, kv->plan_o[0], &LayerW::wo, kv->attn_out, Nq, d, rows, 8, e0, e1);         \
-        if (!rc) rc = tune_one<T, SPL>(kv, kv->plan_d[0], &LayerW::wd, kv->act, F, d, rows, 8, e0, e1);               \
-        if (!rc) rc = tune_gate_up<T, SPL>(kv, rows, e0, e1);                                                     \
+        if (!rc) rc = tune_one<T, SPL>(kv, kv->plan_qkv[0], &LayerW::wqkv, kv->xn, d, Nq + 2 * Nk, rows, Sums::attention, e0, e1);  \
+        if (!rc) rc = tune_one<T, SPL>(kv, kv->plan_o[0], &LayerW::wo, kv->attn_out, Nq, d, rows, Sums::closing, e0, e1);  \
+        if (!rc) rc = tune_one<T, SPL>(kv, kv->plan_d[0], &LayerW::wd, kv->act, F, d, rows, Sums::closing, e0, e1);  \
+        if (!rc) rc = tune_gate_up<T, SPL>(kv, rows, e0, e1);                                                  \
         if (!rc) rc = tune_lm_head<T, SPL>(kv, rows, e0, e1);                                                     \
     } while (0)
     if (c.dtype == SJ_DTYPE_FP32) SJ_TUNE3(float, 1);
@@ -1296,26 +1297,27 @@ struct Runner {
     int rm() const { return packed() && R <= RM_ROWS; }
     size_t plane(int ld) const { return packed() ? packed_plane<T>(rm()) : (size_t)w->rpad * ld; }
     // launch shape of a split-K projection for this row count
-    GemmPlan plan_of(const GemmPlan (&pl)[2], int K, int N) const {
+    GemmPlan plan_of(Product product, int K, int N) const {
         const int ksteps = K / Traits<T>::KSTEP;
-        if (R <= FEW_ROWS) return few_partial_plan(pl[0], kv->few_rows, N / 16, ksteps, R, SPL, std::is_same<T, bf16_t>::value, kv->ring_rows, &pl == &kv->plan_qkv ? QKV_SLICES : 8);
+        const GemmPlan* pl = kv->plans(product);
+        if (R <= FEW_ROWS) return few_partial_plan(pl[0], kv->few_rows, N / 16, ksteps, R, SPL, std::is_same<T, bf16_t>::value, kv->ring_rows, sums_of(product));
         GemmPlan p = pl[1];
         p.split = rows_split(p.split, N / 16, ksteps, R, rows_planes<T, SPL>);
         return p;
     }
     // `parts`: the K-slices it leaves in w->part
-    int partial_gemm(const void* W, const void* X, int K, int N, const GemmPlan (&pl)[2], int* parts = nullptr, bool unscaled = false) {
-        const GemmPlan p = plan_of(pl, K, N);
+    int partial_gemm(const void* W, const void* X, int K, int N, Product product, int* parts = nullptr, bool unscaled = false) {
+        const GemmPlan p = plan_of(product, K, N);
         if (parts) *parts = p.split;
         if ((size_t)p.split * R * N > w->part_elems) return fail(SJ_EINVAL, "internal: %d K-slices of %d rows exceed the partials' buffer", p.split, R);
         if (R > FEW_ROWS) return gemm_rows<T, EPI_PARTIAL, SPL>(st, W, X, plane(K), K, N, R, p.split, w->part, nullptr, 0, nullptr, 0.f);
         return few_partial<T, SPL>(p, st, W, X, plane(K), K, N, R, w->part, few_args(unscaled));
     }
-    // does the product that reads what O (or else down) leaves run on the LDS-ring kernel?
-    bool ring_consumer(bool after_o) const {
+    // does the product that reads what O or down leaves run on the LDS-ring kernel?
+    bool ring_consumer(Product product) const {
         const ModelDims& md = m->md;
-        const GemmPlan p = after_o ? few_gate_up_plan(kv->plan_gu, kv->few_rows, 2 * md.F / 16, md.d / Traits<T>::KSTEP, R, SPL, std::is_same<T, bf16_t>::value, kv->ring_rows)
-                                   : plan_of(kv->plan_qkv, md.d, (md.Hq + 2 * md.Hkv) * md.hd);
+        const GemmPlan p = product == Product::o ? few_gate_up_plan(kv->plan_gu, kv->few_rows, 2 * md.F / 16, md.d / Traits<T>::KSTEP, R, SPL, std::is_same<T, bf16_t>::value, kv->ring_rows)
+                                                 : plan_of(Product::qkv, md.d, (md.Hq + 2 * md.Hkv) * md.hd);
         return p.waves == RING_WAVES;
     }
     // the operand in w->xn lacks its 1/rms factors (it came from a residual epilogue)
@@ -1329,13 +1331,13 @@ struct Runner {
     // O or down projection with its sub-layer's residual add, either in its epilogue (`unscaled`: the next operand, with the norm
     // gain, is in w->xn without its 1/rms factors) or left in `parts` K-slices for norm()
     // (or, from 9 rows on, in the epilogue of the last of its K-slices, where both this product and the next run on the LDS-ring kernel)
-    int closing_gemm(const void* W, const void* X, int K, const GemmPlan (&pl)[2], const void* gain, int& parts, bool& unscaled) {
+    int closing_gemm(const void* W, const void* X, int K, Product product, const void* gain, int& parts, bool& unscaled) {
         const int d = m->md.d;
         const GemmPlan p = resid_plan(d, K, Traits<T>::KSTEP, R, SPL, std::is_same<T, bf16_t>::value, kv->ring_rows);
         unscaled = p.nt > 0;
         if (!unscaled) {
-            const GemmPlan q = plan_of(pl, K, d);
-            if (R > FEW_ROWS || R <= RING_PACK_ROWS || q.waves != RING_WAVES || !ring_consumer(&pl == &kv->plan_o)) return partial_gemm(W, X, K, d, pl, &parts);
+            const GemmPlan q = plan_of(product, K, d);
+            if (R > FEW_ROWS || R <= RING_PACK_ROWS || q.waves != RING_WAVES || !ring_consumer(product)) return partial_gemm(W, X, K, d, product, &parts);
             if ((size_t)q.split * R * d > w->part_elems) return fail(SJ_EINVAL, "internal: %d K-slices of %d rows exceed the partials' buffer", q.split, R);
             unscaled = true;
             FewArgs n = few_args(false);
@@ -1348,10 +1350,10 @@ struct Runner {
         return few_resid<T, SPL>(p, st, W, X, plane(K), K, d, R, w->xn, plane(d), n);
     }
     // the same up to and including the next norm
-    int close(const void* W, const void* X, int K, const GemmPlan (&pl)[2], const void* gain, int cls, bool& unscaled) {
+    int close(const void* W, const void* X, int K, Product product, const void* gain, int cls, bool& unscaled) {
         int rc, parts = 0;
         if ((rc = time_mark(kv, cls, st))) return rc;
-        if ((rc = closing_gemm(W, X, K, pl, gain, parts, unscaled))) return rc;
+        if ((rc = closing_gemm(W, X, K, product, gain, parts, unscaled))) return rc;
         if ((rc = time_mark(kv, cls, st))) return rc;
         if (!unscaled) {
             norm(parts, gain, nullptr);
@@ -1449,13 +1451,13 @@ struct Runner {
         const ModelDims& md = m->md;
         const LayerW& L = m->layers[l];
         int rc;
-        if ((rc = close(L.wo, w->attn_out, md.Hq * md.hd, kv->plan_o, L.ffn_norm, 2, unscaled))) return rc;
+        if ((rc = close(L.wo, w->attn_out, md.Hq * md.hd, Product::o, L.ffn_norm, 2, unscaled))) return rc;
         if ((rc = time_mark(kv, 3, st))) return rc;
         if ((rc = gate_up(L.wgu, unscaled))) return rc;
         if ((rc = time_mark(kv, 3, st))) return rc;
-        if (l + 1 < m->cfg.n_layers) return close(L.wd, w->act, md.F, kv->plan_d, m->layers[l + 1].attn_norm, 4, unscaled);
+        if (l + 1 < m->cfg.n_layers) return close(L.wd, w->act, md.F, Product::down, m->layers[l + 1].attn_norm, 4, unscaled);
         if ((rc = time_mark(kv, 4, st))) return rc;
-        if ((rc = partial_gemm(L.wd, w->act, md.F, md.d, kv->plan_d, &parts))) return rc;
+        if ((rc = partial_gemm(L.wd, w->act, md.F, md.d, Product::down, &parts))) return rc;
         return time_mark(kv, 4, st);
     }
 
@@ -1476,7 +1478,7 @@ struct Runner {
         for (int l = 0; l < c.n_layers; ++l) {
             const LayerW& L = m->layers[l];
             if ((rc = time_mark(kv, 1, st))) return rc;
-            if ((rc = partial_gemm(L.wqkv, w->xn, d, Nqkv, kv->plan_qkv, &parts, unscaled))) return rc;
+            if ((rc = partial_gemm(L.wqkv, w->xn, d, Nqkv, Product::qkv, &parts, unscaled))) return rc;
             if ((rc = time_mark(kv, 1, st))) return rc;
             if (tail && l + 1 == c.n_layers) {
                 if ((rc = rows_attention(l, parts, tail))) return rc;
@@ -1665,10 +1667,10 @@ static int time_kernel_impl(sj_model* m, sj_kv* kv, int cls, int launches, int g
         }
         const LayerW& L = m->layers[i % m->cfg.n_layers];        // a different layer each time: no cache reuse
         switch (cls) {
-            case 1: rc = run.partial_gemm(L.wqkv, kv->xn, d, Nq + 2 * Nk, kv->plan_qkv); break;
-            case 2: rc = run.closing_gemm(L.wo, kv->attn_out, Nq, kv->plan_o, L.ffn_norm, parts, unscaled); break;
+            case 1: rc = run.partial_gemm(L.wqkv, kv->xn, d, Nq + 2 * Nk, Product::qkv); break;
+            case 2: rc = run.closing_gemm(L.wo, kv->attn_out, Nq, Product::o, L.ffn_norm, parts, unscaled); break;
             case 3: rc = run.gate_up(L.wgu); break;
-            default: rc = run.closing_gemm(L.wd, kv->act, md.F, kv->plan_d, L.ffn_norm, parts, unscaled); break;
+            default: rc = run.closing_gemm(L.wd, kv->act, md.F, Product::down, L.ffn_norm, parts, unscaled); break;
         }
     }
     hipError_t e = hipEventRecord(e1, st);

@@ -116,33 +116,48 @@ inline GemmPlan ring_rule_partial(int ntiles, int ksteps) {
         }
     return best;
 }
+// Who adds a split-K product's K-slices: attention, in its prologue (QKV), or what closes the sub-layer (O, down).
+enum class Sums { attention, closing };
+
+// The longest chain of a split-K launch: k-steps that one accumulator adds up before the waves' and slices' sums meet.
+inline int partial_chain(const GemmPlan& p, int ksteps) {
+    const int lanes = (p.waves == RING_WAVES ? RING_CW : p.waves) * p.split;
+    return (ksteps + lanes - 1) / lanes;
+}
+inline GemmPlan plan_partial(int ntiles, int ksteps, bool one_row_tile);
+
 // The same from 9 rows on, where a k-step has one operand fragment per plane and row tile: whole rounds of 256 workgroups, and few fragments for a
 // wave to read (an operand fragment counted twice: it comes from the L2 each time), tiles left to the reduction and K-slices (their sums
-// are written and read).  `most`: largest number of K-slices, two for QKV, whose slices attention adds (1B, 12 rows: 12.7 us with two,
-// 13.8 with four).  us of the shapes that fill the chip, n-tiles x slices:
+// are written and read).  QKV_SLICES: slices of QKV, which attention adds (1B, 12 rows: 12.7 us with two, 13.8 with four).  us of the shapes that
+// fill the chip, n-tiles x slices:
 //   8B, 20 rows: down 4 x 4 21.6, 8 x 8 22.1; QKV 3 x 2 11.4, 3 x 4 12.6;   70B, 24 rows: O 4 x 2 24.8, 8 x 4 28.6; down 8 x 4 72.3, 4 x 2 75.5;
 //   1B, 12 rows: O 1 x 2 4.4; down 2 x 4 8.6, 4 x 8 9.1; QKV (192 workgroups) 2 x 2 5.2, 1 x 1 6.1.
-// Two row tiles: the operand counts 1.3 times (70B, 24 rows, the stack of 80 layers: O 8 x 4 25.37 ms, 4 x 2 24.92).  And a wave of QKV, whose sums are
-// rounded into the cache, adds at most 8 k-steps of 32: the 70B shape takes four slices, which costs what O gains (25.35 ms).
+// Fewer slices are longer chains, and a sum's rounding error grows with its chain, so a launch has at least the slices that keep a chain no longer
+// than the register-ring kernel's rule has it for this product (8 - 15 k-steps while eight slices allow that).  It is what takes four slices
+// for QKV and O of the 70B shape, where two would do for the stream.
 constexpr int QKV_SLICES = 2;
-inline GemmPlan ring_rule_partial_rows(int ntiles, int ksteps, int rows, int planes, int most) {
+inline GemmPlan ring_rule_partial_rows(int ntiles, int ksteps, int rows, int planes, Sums sums) {
     GemmPlan best;
     best.waves = 0;
     double best_cost = 1e30;
-    const int mt = rows > 16 ? 2 : 1, nb = ring_operand(false, planes, mt);
-    const int least = most == QKV_SLICES && rows > 16 ? std::min(8, ksteps / (RING_CW * 8)) : 1;
-    for (int split = 1; split <= most || split < 2 * least; split *= 2)
+    const int mt = rows > 16 ? 2 : 1, nb = ring_operand(false, planes, mt), chain = partial_chain(plan_partial(ntiles, ksteps, true), ksteps);
+    int most = sums == Sums::attention ? QKV_SLICES : 8;
+    for (int split = 1; split <= most; split *= 2) {
+        if (partial_chain(GemmPlan{1, RING_WAVES, split, 0}, ksteps) > chain) {
+            most = std::min(8, std::max(most, split * 2));
+            continue;
+        }
         for (int nt : {1, 2, 3, 4, 5, 8}) {
-            if (split < least) continue;
             const int wgs = ntiles / nt * split, to_cu = (wgs + 255) / 256;
             GemmPlan p;
             p.nt = nt; p.waves = RING_WAVES; p.split = split; p.depth = wgs <= 256 && nt >= 3 ? 18 : RING_TWO;
             if (!partial_fits(p, ntiles, ksteps, rows, planes, true)) p.depth = RING_TWO;
             if (!partial_fits(p, ntiles, ksteps, rows, planes, true)) p.depth = 4;
             if (!partial_fits(p, ntiles, ksteps, rows, planes, true)) continue;
-            const double cost = 256.0 * to_cu / wgs * (to_cu * ((double)ksteps / RING_CW / split * (nt + (mt == 2 ? 1.3 : 2.0) * nb) + 4 * nt * mt + 8) + 6 * split);
+            const double cost = 256.0 * to_cu / wgs * (to_cu * ((double)ksteps / RING_CW / split * (nt + 2 * nb) + 4 * nt * mt + 8) + 6 * split);
             if (cost < best_cost - 1e-9) { best = p; best_cost = cost; }
         }
+    }
     return best;
 }
 // Gate / up on that kernel: 8 or 7 n-tiles where they make whole rounds of one workgroup a CU (8B, 70B: 7), else two, two workgroups a CU (1B,
@@ -237,9 +252,9 @@ inline GemmPlan resolve_logits(const GemmPlan& p, int ntiles, int ksteps, int ro
 }
 
 // The rules over both kernels; the LDS-ring kernel up to `ring_rows` rows.
-inline GemmPlan rule_partial(int ntiles, int ksteps, int rows, int planes, bool bf16, int ring_rows, int most = 8) {
+inline GemmPlan rule_partial(int ntiles, int ksteps, int rows, int planes, bool bf16, int ring_rows, Sums sums) {
     if (bf16 && planes <= 2 && rows <= ring_rows) {
-        const GemmPlan r = rows <= RING_PACK_ROWS ? ring_rule_partial(ntiles, ksteps) : ring_rule_partial_rows(ntiles, ksteps, rows, planes, most);
+        const GemmPlan r = rows <= RING_PACK_ROWS ? ring_rule_partial(ntiles, ksteps) : ring_rule_partial_rows(ntiles, ksteps, rows, planes, sums);
         if (r.waves) return r;
     }
     return plan_partial(ntiles, ksteps, true);
@@ -262,12 +277,9 @@ inline GemmPlan rule_logits(int ntiles, int ksteps, int rows, int planes, bool b
 // A shape made (by the rule or the measurement) for one row count speaks for others with as many operand fragments to a k-step: one packed, one
 // row tile, two.  A draft block of 12 sequences runs 12 rows on an object made for blocks of 60: in the shapes of 32 rows, or what stood in
 // for those that do not take 12, its QKV and O took 7.2 us each; in the rule's for 12 rows 5.2 and 4.9.
-// The start-up measurement times a projection without the kernel that adds its K-slices, which for QKV is attention, in every layer: what
-// 8 slices gain there is lost again (1B, 1 row, a draft block: 8 slices 4642 us, 4 slices 4529 - 4580).
-constexpr int QKV_MEASURED_SLICES = 4;
 inline int few_class(int rows) { return rows <= RING_PACK_ROWS ? 0 : rows <= 16 ? 1 : 2; }
-inline GemmPlan few_partial_plan(const GemmPlan& made, int made_rows, int ntiles, int ksteps, int rows, int planes, bool bf16, int ring_rows, int most = 8) {
-    return resolve_partial(few_class(rows) == few_class(made_rows) ? made : rule_partial(ntiles, ksteps, rows, planes, bf16, ring_rows, most), ntiles, ksteps, rows, planes, bf16);
+inline GemmPlan few_partial_plan(const GemmPlan& made, int made_rows, int ntiles, int ksteps, int rows, int planes, bool bf16, int ring_rows, Sums sums) {
+    return resolve_partial(few_class(rows) == few_class(made_rows) ? made : rule_partial(ntiles, ksteps, rows, planes, bf16, ring_rows, sums), ntiles, ksteps, rows, planes, bf16);
 }
 inline GemmPlan few_gate_up_plan(const GemmPlan& made, int made_rows, int ntiles, int ksteps, int rows, int planes, bool bf16, int ring_rows) {
     return resolve_gate_up(few_class(rows) == few_class(made_rows) ? made : rule_gate_up(ntiles, ksteps, rows, planes, bf16, ring_rows), ntiles, ksteps, rows, planes, bf16);
@@ -302,6 +314,19 @@ inline std::vector<GemmPlan> partial_candidates(int ntiles, int ksteps, int rows
 #define SJ_OFFER(NT, D) offer(NT, RING_WAVES, D);
     SJ_RING_PARTIAL_SHAPES(SJ_OFFER)
 #undef SJ_OFFER
+    return cands;
+}
+
+// Those of them that may take the place of `rule`, the rule's shape.  QKV: of no more K-slices, since the measurement does not see the attention
+// launches that add them (1B, 1 row, a draft block: 8 slices 4642 us, 4 slices 4529 - 4580).  From 9 rows on: of no longer chains than the
+// rule's bound.
+inline std::vector<GemmPlan> measured_partials(const GemmPlan& rule, int ntiles, int ksteps, int rows, int planes, bool bf16, Sums sums) {
+    std::vector<GemmPlan> cands = partial_candidates(ntiles, ksteps, rows, planes, bf16);
+    const int chain = std::max(partial_chain(rule, ksteps), partial_chain(plan_partial(ntiles, ksteps, true), ksteps));
+    auto out = [&](const GemmPlan& p) {
+        return (sums == Sums::attention && p.split > rule.split) || (rows > RING_PACK_ROWS && partial_chain(p, ksteps) > chain);
+    };
+    cands.erase(std::remove_if(cands.begin(), cands.end(), out), cands.end());
     return cands;
 }
 

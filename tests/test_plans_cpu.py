@@ -137,3 +137,45 @@ def test_every_gate_up_and_lm_head_launch_is_an_instantiated_shape(tmp_path):
     """A shape without a kernel would run as another one: timed, and reported, under the wrong name."""
     out = run_program(tmp_path, FEW)
     assert out.splitlines()[-1].startswith("0 of "), out
+
+
+CHAINS = shapes_array() + r"""
+// split-K products of 9 to 32 rows: what the rule takes for a row count, what a plan of another class of rows becomes, and what the measurement may
+// put in the rule's place
+int main() {
+    long bad = 0, checked = 0;
+    for (const auto& s : shapes)
+        for (int rows = RING_PACK_ROWS + 1; rows <= FEW_ROWS; ++rows)
+            for (int planes = 1; planes <= 2; ++planes) {
+                const int prod[3][2] = {{s[1], s[0]}, {s[0], s[2]}, {s[0], s[3]}};      // N, K of QKV, O, down
+                for (const auto& p : prod) {
+                    const int ntiles = p[0] / 16, ksteps = p[1] / 32;
+                    const Sums sums = &p == prod ? Sums::attention : Sums::closing;
+                    const int longest = partial_chain(plan_partial(ntiles, ksteps, true), ksteps);
+                    auto see = [&](const char* what, const GemmPlan& q) {
+                        ++checked;
+                        if ((partial_chain(q, ksteps) > longest || !partial_fits(q, ntiles, ksteps, rows, planes, true)) && bad++ < 10)
+                            printf("%s: %d tiles, %d k-steps, %d rows, %d planes: {%d, %d, %d, %d}\n", what, ntiles, ksteps, rows, planes, q.nt, q.waves, q.split, q.depth);
+                    };
+                    const GemmPlan rule = rule_partial(ntiles, ksteps, rows, planes, true, RING_ROWS, sums);
+                    see("rule", rule);
+                    for (int made : {1, 12, 32}) {
+                        const GemmPlan other = rule_partial(ntiles, ksteps, made, planes, true, RING_ROWS, sums);
+                        if (few_class(made) != few_class(rows)) see("another class", few_partial_plan(other, made, ntiles, ksteps, rows, planes, true, RING_ROWS, sums));
+                    }
+                    for (const GemmPlan& q : measured_partials(rule, ntiles, ksteps, rows, planes, true, sums)) {
+                        see("measured", q);
+                        if (sums == Sums::attention && q.split > rule.split && bad++ < 10) printf("QKV of %d slices, the rule has %d\n", q.split, rule.split);
+                    }
+                }
+            }
+    printf("%ld of %ld wrong\n", bad, checked);
+}
+"""
+
+
+def test_few_row_sums_are_no_longer_than_the_register_rings(tmp_path):
+    """Fewer K-slices are longer fp32 sums: no launch of 9 to 32 rows adds more k-steps in one accumulator than the register-ring
+    kernel's rule does for that product, by the rule or by the start-up measurement."""
+    out = run_program(tmp_path, CHAINS)
+    assert out.splitlines()[-1].startswith("0 of "), out
