@@ -1028,9 +1028,10 @@ static int pick_plan(GemmPlan& plan, const std::vector<GemmPlan>& candidates, Ti
 // shape and on the number of row tiles in ways the workgroup-count rule of plan_partial does not capture (70B-shaped
 // QKV with two row tiles: 50 us with the rule's shape, 35 us with the best one).  Every candidate runs over up to 16
 // layers' weights back to back (distinct layers, so nothing is served from cache); the rule's plan stays unless a
-// candidate is at least 5 % faster (pick_plan).  SJ_TUNE=0 keeps the rule's plans (launch shapes then never differ between runs).
+// candidate is at least 5 % faster (pick_plan).  `closes` (tune_plans): O and down are timed as they run, with the tickets of their K-slices and
+// the end of the sub-layer, into buffers that hold nothing between calls.  SJ_TUNE=0 keeps the rule's plans (launch shapes then never differ between runs).
 template <typename T, int SPL>
-static int tune_one(sj_kv* kv, GemmPlan& plan, void* LayerW::*which, const void* X, int K, int N, int rows, Sums sums,
+static int tune_one(sj_kv* kv, GemmPlan& plan, void* LayerW::*which, const void* X, int K, int N, int rows, Sums sums, bool closes,
                     hipEvent_t e0, hipEvent_t e1) {
     const sj_model* m = kv->m;
     const int ksteps = K / Traits<T>::KSTEP, ntiles = N / 16;
@@ -1039,6 +1040,10 @@ static int tune_one(sj_kv* kv, GemmPlan& plan, void* LayerW::*which, const void*
     FewArgs fa;
     fa.packed = packed_rows<T, SPL>(rows);
     fa.rm = fa.packed && rows <= RM_ROWS;
+    if (closes && sums == Sums::closing) {
+        fa.x = kv->x; fa.gain = m->layers[0].ffn_norm; fa.ss_out = kv->ss;
+        fa.tickets = kv->close_tickets; fa.xg = kv->xn; fa.xgplane = (size_t)kv->rpad * N;
+    }
     auto time_plan = [&](const GemmPlan& p, double& us) -> int {
         float ms = 0.f;
         for (int rep = 0; rep < 2; ++rep) {                 // the first repetition warms up
@@ -1054,11 +1059,11 @@ static int tune_one(sj_kv* kv, GemmPlan& plan, void* LayerW::*which, const void*
         us = (double)ms * 1e3 / nl;
         return SJ_OK;
     };
-    return pick_plan(plan, measured_partials(plan, ntiles, ksteps, rows, SPL, std::is_same<T, bf16_t>::value, sums), time_plan);
+    return pick_plan(plan, measured_partials(plan, ntiles, ksteps, rows, SPL, std::is_same<T, bf16_t>::value, sums, closes), time_plan);
 }
 
 template <typename T, int SPL>
-static int tune_gate_up(sj_kv* kv, int rows, hipEvent_t e0, hipEvent_t e1) {
+static int tune_gate_up(sj_kv* kv, int rows, bool closes, hipEvent_t e0, hipEvent_t e1) {
     const sj_model* m = kv->m;
     const int d = m->cfg.d_model, F = m->cfg.d_ffn, ntiles = 2 * F / 16;
     const int nl = std::min(m->cfg.n_layers, 16);
@@ -1086,7 +1091,7 @@ static int tune_gate_up(sj_kv* kv, int rows, hipEvent_t e0, hipEvent_t e1) {
     std::vector<GemmPlan> cands;
     auto offer = [&](int nt, int waves, int depth) {
         const GemmPlan p{nt, waves, 1, depth};
-        if (!gate_up_fits(p, ntiles, ksteps, rows, SPL, std::is_same<T, bf16_t>::value)) return;
+        if (!gate_up_fits(p, ntiles, ksteps, rows, SPL, std::is_same<T, bf16_t>::value) || (closes && waves != RING_WAVES)) return;
         const bool wide = ntiles / nt >= 128 && (waves == RING_WAVES || ksteps / waves >= 4);
         if (one && waves != RING_WAVES ? nt == 1 : wide) cands.push_back(p);
     };
@@ -1160,12 +1165,15 @@ static int tune_plans(sj_kv* kv, int rows) {
     HIPCHK(hipEventCreate(&e0));
     if (hipEventCreate(&e1) != hipSuccess) { (void)hipEventDestroy(e0); return fail(SJ_EHIP, "hipEventCreate failed"); }
     int rc = SJ_OK;
+    // From 9 rows on O and down close their sub-layers where they and their consumers run on the LDS-ring kernel: where the rule has it so, the
+    // measurement stays with that kernel (another, 5 % faster by itself, would bring back a norm launch of 4.7 us).
+    const bool closes = rows > RING_PACK_ROWS && std::min({kv->plan_qkv[0].waves, kv->plan_o[0].waves, kv->plan_d[0].waves, kv->plan_gu.waves}) == RING_WAVES;
 #define SJ_TUNE3(T, SPL)                                                                                          \
     do {                                                                                                          \
-        if (!rc) rc = tune_one<T, SPL>(kv, kv->plan_qkv[0], &LayerW::wqkv, kv->xn, d, Nq + 2 * Nk, rows, Sums::attention, e0, e1);  \
-        if (!rc) rc = tune_one<T, SPL>(kv, kv->plan_o[0], &LayerW::wo, kv->attn_out, Nq, d, rows, Sums::closing, e0, e1);  \
-        if (!rc) rc = tune_one<T, SPL>(kv, kv->plan_d[0], &LayerW::wd, kv->act, F, d, rows, Sums::closing, e0, e1);  \
-        if (!rc) rc = tune_gate_up<T, SPL>(kv, rows, e0, e1);                                                  \
+        if (!rc) rc = tune_one<T, SPL>(kv, kv->plan_qkv[0], &LayerW::wqkv, kv->xn, d, Nq + 2 * Nk, rows, Sums::attention, closes, e0, e1);  \
+        if (!rc) rc = tune_one<T, SPL>(kv, kv->plan_o[0], &LayerW::wo, kv->attn_out, Nq, d, rows, Sums::closing, closes, e0, e1);  \
+        if (!rc) rc = tune_one<T, SPL>(kv, kv->plan_d[0], &LayerW::wd, kv->act, F, d, rows, Sums::closing, closes, e0, e1);  \
+        if (!rc) rc = tune_gate_up<T, SPL>(kv, rows, closes, e0, e1);                                                  \
         if (!rc) rc = tune_lm_head<T, SPL>(kv, rows, e0, e1);                                                     \
     } while (0)
     if (c.dtype == SJ_DTYPE_FP32) SJ_TUNE3(float, 1);

@@ -319,12 +319,12 @@ inline std::vector<GemmPlan> partial_candidates(int ntiles, int ksteps, int rows
 
 // Those of them that may take the place of `rule`, the rule's shape.  QKV: of no more K-slices, since the measurement does not see the attention
 // launches that add them (1B, 1 row, a draft block: 8 slices 4642 us, 4 slices 4529 - 4580).  From 9 rows on: of no longer chains than the
-// rule's bound.
-inline std::vector<GemmPlan> measured_partials(const GemmPlan& rule, int ntiles, int ksteps, int rows, int planes, bool bf16, Sums sums) {
+// rule's bound; `closes`: on the LDS-ring kernel.
+inline std::vector<GemmPlan> measured_partials(const GemmPlan& rule, int ntiles, int ksteps, int rows, int planes, bool bf16, Sums sums, bool closes) {
     std::vector<GemmPlan> cands = partial_candidates(ntiles, ksteps, rows, planes, bf16);
     const int chain = std::max(partial_chain(rule, ksteps), partial_chain(plan_partial(ntiles, ksteps, true), ksteps));
     auto out = [&](const GemmPlan& p) {
-        return (sums == Sums::attention && p.split > rule.split) || (rows > RING_PACK_ROWS && partial_chain(p, ksteps) > chain);
+        return (sums == Sums::attention && p.split > rule.split) || (rows > RING_PACK_ROWS && partial_chain(p, ksteps) > chain) || (closes && p.waves != RING_WAVES);
     };
     cands.erase(std::remove_if(cands.begin(), cands.end(), out), cands.end());
     return cands;

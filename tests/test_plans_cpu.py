@@ -163,10 +163,13 @@ int main() {
                         const GemmPlan other = rule_partial(ntiles, ksteps, made, planes, true, RING_ROWS, sums);
                         if (few_class(made) != few_class(rows)) see("another class", few_partial_plan(other, made, ntiles, ksteps, rows, planes, true, RING_ROWS, sums));
                     }
-                    for (const GemmPlan& q : measured_partials(rule, ntiles, ksteps, rows, planes, true, sums)) {
-                        see("measured", q);
-                        if (sums == Sums::attention && q.split > rule.split && bad++ < 10) printf("QKV of %d slices, the rule has %d\n", q.split, rule.split);
-                    }
+                    for (bool closes : {false, true})
+                        for (const GemmPlan& q : measured_partials(rule, ntiles, ksteps, rows, planes, true, sums, closes)) {
+                            see("measured", q);
+                            if (sums == Sums::attention && q.split > rule.split && bad++ < 10) printf("QKV of %d slices, the rule has %d\n", q.split, rule.split);
+                            // where the sub-layers are closed in the products' launches, a shape of another kernel would bring the norm's launch back
+                            if (closes && q.waves != RING_WAVES && bad++ < 10) printf("not on the LDS rings: {%d, %d, %d, %d}\n", q.nt, q.waves, q.split, q.depth);
+                        }
                 }
             }
     printf("%ld of %ld wrong\n", bad, checked);
