@@ -53,6 +53,13 @@ int main() {
                         see("rule", plan_partial(ntiles, ksteps, true));
                         GemmPlan ring = ring_rule_partial(ntiles, ksteps);
                         if (ring.waves && bf16 && planes <= 2 && rows <= 8) see("ring rule", ring);
+                        // the rule over both kernels, with the ring's limit of rows anywhere, and a plan made for any class of rows
+                        const Sums sums = &p == prod ? Sums::attention : Sums::closing;
+                        for (int ring_rows : {0, 8, 20, RING_ROWS}) {
+                            see("rule over both kernels", rule_partial(ntiles, ksteps, rows, planes, bf16, ring_rows, sums));
+                            for (int made : {1, 8, 9, 16, 17, 32})
+                                see("plan of a class", few_partial_plan(rule_partial(ntiles, ksteps, made, planes, bf16, ring_rows, sums), made, ntiles, ksteps, rows, planes, bf16, ring_rows, sums));
+                        }
                         for (const GemmPlan& q : partial_candidates(ntiles, ksteps, rows, planes, bf16)) see("candidate", q);
                         // plans of other row and plane counts, as a prompt chunk or a changed plane count finds them
                         if (ring.waves) see("resolved ring rule", resolve_partial(ring, ntiles, ksteps, rows, planes, bf16));
@@ -114,16 +121,29 @@ int main() {
                     };
                     auto gate_up = [&](const char* what, const GemmPlan& q) { see(what, q, gu, gate_up_fits(q, gu, ksteps, rows, spl, bf16)); };
                     auto logits = [&](const char* what, const GemmPlan& q) { see(what, q, lm, logits_fits(q, lm, ksteps, rows, spl, bf16)); };
-                    // a residual epilogue leaves operands that its consumers scale, for at most 8 rows and two planes
-                    for (int K : {s[2], s[3]}) {
-                        const GemmPlan q = resid_plan(s[0], K, bf16 ? 32 : 16, rows, spl, bf16, RING_PACK_ROWS);
-                        see("residual", q, s[0] / 16, !q.nt || (rows <= 8 && planes <= 2));
-                    }
+                    // a residual epilogue leaves operands that its consumers scale, for at most 8 rows and two planes; no K-slices; on either kernel
+                    for (int K : {s[2], s[3]})
+                        for (int ring_rows : {0, RING_PACK_ROWS, RING_ROWS}) {
+                            const GemmPlan q = resid_plan(s[0], K, bf16 ? 32 : 16, rows, spl, bf16, ring_rows);
+                            bool known = q.waves == 8 && (q.nt == 1 || q.nt == 2 || q.nt == 4);
+#define SJ_KNOWN(NT, D) if (q.waves == RING_WAVES && q.nt == NT && q.depth == D) known = ring_fits(q, s[0] / 16, K / 32, rows, spl, bf16);
+                            SJ_RING_RESID_SHAPES(SJ_KNOWN)
+#undef SJ_KNOWN
+                            see("residual", q, s[0] / 16, !q.nt || (rows <= 8 && planes <= 2 && q.split == 1 && known));
+                        }
                     gate_up("gate/up rule", rule_gate_up(gu, spl));
                     logits("LM head rule", rule_logits(lm));
+                    for (int ring_rows : {0, 8, 20, RING_ROWS}) {
+                        gate_up("gate/up rule over both kernels", rule_gate_up(gu, ksteps, rows, spl, bf16, ring_rows));
+                        logits("LM head rule over both kernels", rule_logits(lm, ksteps, rows, spl, bf16, ring_rows));
+                        for (int made : {1, 8, 9, 16, 17, 32}) {
+                            gate_up("gate/up plan of a class", few_gate_up_plan(rule_gate_up(gu, ksteps, made, spl, bf16, ring_rows), made, gu, ksteps, rows, spl, bf16, ring_rows));
+                            logits("LM head plan of a class", few_logits_plan(rule_logits(lm, ksteps, made, spl, bf16, ring_rows), made, lm, ksteps, rows, spl, bf16, ring_rows));
+                        }
+                    }
                     for (int nt : {1, 2, 4, 7, 8})
                         for (int waves : {4, 8, RING_WAVES})
-                            for (int depth : {2, 3, 4, 8}) {
+                            for (int depth : {2, 3, 4, 8, 9, 18}) {
                                 gate_up("gate/up resolved", resolve_gate_up(GemmPlan{nt, waves, 1, depth}, gu, ksteps, rows, spl, bf16));
                                 logits("LM head resolved", resolve_logits(GemmPlan{nt, waves, 1, depth}, lm, ksteps, rows, spl, bf16));
                             }
@@ -182,3 +202,28 @@ def test_few_row_sums_are_no_longer_than_the_register_rings(tmp_path):
     kernel's rule does for that product, by the rule or by the start-up measurement."""
     out = run_program(tmp_path, CHAINS)
     assert out.splitlines()[-1].startswith("0 of "), out
+
+
+HEADS = r"""
+int main() {
+    long bad = 0, taken = 0;
+    for (int ntiles = 32; ntiles <= 9600; ntiles += ntiles < 1024 ? 8 : 248)
+        for (int rows = 1; rows <= 4200; ++rows)
+            for (int planes = 0; planes <= 3; ++planes) {
+                const int rt = tile_logits(rows, ntiles, planes);
+                if (!rt) continue;
+                ++taken;
+                // an instantiated size whose groups hold all rows, none of them empty, and whole statistics of a row
+                const int groups = (rows + rt * 16 - 1) / (rt * 16);
+                const bool known = (rt % 2 == 0 && rt >= 6 && rt <= 16) || (planes == 2 && rt == 9) || (planes == 1 && rt == 18);
+                if ((!known || rows <= 64 || planes < 1 || planes > 2 || groups * rt * 16 < rows || (groups - 1) * rt * 16 >= rows || ntiles % TILE_STAT) && bad++ < 10)
+                    printf("%d rows, %d tiles, %d planes: %d\n", rows, ntiles, planes, rt);
+            }
+    printf("%ld of %ld large-tile heads wrong\n", bad, taken);
+}
+"""
+
+
+def test_large_tile_heads_hold_their_rows(tmp_path):
+    out = run_program(tmp_path, HEADS).splitlines()
+    assert out[-1].startswith("0 of ") and not out[-1].startswith("0 of 0 "), out
