@@ -469,3 +469,29 @@ def test_results_of_a_replayed_graph_are_fetched():
                     assert np.array_equal(a, b), (rep, "replayed")
     finally:
         gpu.close()
+
+
+# statistics of a row, one to four n-tiles: at the edges of 1, 4, 8 and 16 to a thread, and more than 16; from the few-row head and from large tiles
+@pytest.mark.parametrize("vocab,batch,gamma", [(256, 1, 2), (16384, 1, 5), (16512, 2, 3), (65536, 1, 1), (65664, 1, 4), (131072, 2, 2), (131200, 1, 3),
+                                               (262144, 1, 1), (262272, 1, 2), (65536, 13, 4), (65664, 13, 4), (131200, 22, 2)])
+def test_softmax_statistics_of_any_number(vocab, batch, gamma):
+    """p(d) of a head alone against the softmax of its own logits in 64 bits.  Bound: 2^-24 for each of at most 64 additions in a row to a
+    row's sum and of the exponents' arguments, here below 40, in numerator and sum."""
+    shape = synth.ModelShape(f"head_{vocab}", "bf16", 0, 512, 8, 2, 64, 512, vocab, 10000.0, batch=batch, gamma=gamma, kv_len=(0, 0), weight_std=0.2)
+    gpu = G.Gpu(shape, synth.WeightSource(shape, seed=3, judge_bias=0.1), None)
+    try:
+        print(sj.sj_kernel_class_shape(gpu.kv, 5, batch * (gamma + 1)), flush=True)
+        hidden = torch.from_numpy(synth.make_hidden(shape, seed=4).view(np.int16)).to(gpu.dev)
+        draft = synth.make_draft(shape, seed=5)
+        out = gpu.step(draft, 0.5, gamma, head_hidden=hidden)
+        bad, _ = G.replay_matches(shape, out, draft, 0.5)
+        assert not bad, bad
+        for b in range(batch):
+            l = out["logits"][b].astype(np.float64)
+            p = np.exp(l - l.max(axis=1, keepdims=True))
+            p /= p.sum(axis=1, keepdims=True)
+            ref = p[np.arange(gamma), draft["tokens"][b]]
+            assert np.abs(l).max() < 40
+            np.testing.assert_allclose(out["p_at_draft"][b], ref, rtol=(64 + 4 * 40) * 2.0 ** -24, atol=0)
+    finally:
+        gpu.close()
