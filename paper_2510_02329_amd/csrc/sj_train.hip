@@ -281,6 +281,7 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void lr_pass_kernel(TrainArgs a) {
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(row + off[j]),
                                                  (__attribute__((address_space(3))) void*)&ring[w][u][rb * NJ + j][0], 16, 0, 0);
         }
+        asm volatile("" ::: "memory");                   // (the waits count a group's requests: they stay in front of the next group's)
     };
     // group numbers of this team: blockIdx.x * TEAMS + team, + gridDim.x * TEAMS, ...; the number of turns is the workgroup's
     // (barriers inside): a team past the last group works on rows that do not count.  A slot of `part` is written again two
@@ -456,6 +457,7 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void lr_pass_mfma_kernel(TrainArgs
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(row + off[j]),
                                                  (__attribute__((address_space(3))) void*)(mine + u * GROUP + rb * ROW + j * 1024), 16, 0, 0);
         }
+        asm volatile("" ::: "memory");                   // (the waits count a group's requests: they stay in front of the next group's)
     };
     // group numbers of this team: blockIdx.x * TEAMS + team, + gridDim.x * TEAMS, ...; the number of turns is the workgroup's
     // (barriers inside): a team past the last group works on rows that do not count.  A slot of `part` is written again two
