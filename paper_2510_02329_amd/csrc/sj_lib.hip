@@ -897,10 +897,13 @@ static int gemm_ring(hipStream_t st, const void* Wt, const void* X, size_t xplan
     a.out = out; a.stats = stats; a.act = act;
     fa.put<T>(a);
     const dim3 grid(N / 16 / NT, split);
-    if (SPL == 2 && rows <= RING_PACK_ROWS) gemm_ring_kernel<T, NT, 1, EPI, 2, true, DEPTH><<<grid, RING_CW * 64, 0, st>>>(a);
-    else if (rows <= 16) gemm_ring_kernel<T, NT, 1, EPI, SPL, false, DEPTH><<<grid, RING_CW * 64, 0, st>>>(a);
-    else if constexpr (EPI != EPI_RESID) gemm_ring_kernel<T, NT, 2, EPI, SPL, false, DEPTH><<<grid, RING_CW * 64, 0, st>>>(a);
-    else return fail(SJ_EINVAL, "internal: residual epilogue over %d rows", rows);
+    if (EPI == EPI_RESID && rows > RING_PACK_ROWS) return fail(SJ_EINVAL, "internal: residual epilogue over %d rows", rows);
+    constexpr bool FEWER = EPI == EPI_RESID;                       // no more than 8 rows: two planes are packed, one row tile
+    if (SPL == 2 && (FEWER || rows <= RING_PACK_ROWS)) gemm_ring_kernel<T, NT, 1, EPI, 2, true, DEPTH><<<grid, RING_CW * 64, 0, st>>>(a);
+    else if constexpr (!FEWER || SPL == 1) {
+        if (FEWER || rows <= 16) gemm_ring_kernel<T, NT, 1, EPI, SPL, false, DEPTH><<<grid, RING_CW * 64, 0, st>>>(a);
+        else if constexpr (!FEWER) gemm_ring_kernel<T, NT, 2, EPI, SPL, false, DEPTH><<<grid, RING_CW * 64, 0, st>>>(a);
+    }
     LAUNCHCHK("gemm_ring");
     return SJ_OK;
 }

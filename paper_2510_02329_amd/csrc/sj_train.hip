@@ -31,6 +31,7 @@
 #include <vector>
 
 #include "../../include/sj.h"
+#include "sj_device.h"
 
 __attribute__((visibility("hidden"))) int sj_set_error(int code, const char* msg);   // defined next to sj_last_error
 
@@ -56,9 +57,9 @@ int fail(int code, const char* fmt, ...) {
         if (e_ != hipSuccess) return fail(SJ_EHIP, "launch of %s failed: %s", name, hipGetErrorString(e_)); \
     } while (0)
 
-// Workgroup barrier that waits for this wave's LDS traffic only: __syncthreads() would also wait for the
-// next rows' loads, which are meant to stay in flight across the barriers of the current rows.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+using sj::f32x4;
+using sj::lds_barrier;      // (__syncthreads() would also wait for the next rows' loads, which stay in flight across the barriers of the current ones)
+using sj::vmcnt_imm;
 
 constexpr int PASS_WG = 256;        // workgroups of a pass: one per compute unit
 constexpr int PASS_WAVES = 8;
@@ -157,10 +158,10 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// One pass over the matrix for the slots.  A workgroup of eight waves: CW of them share a group of RB rows, wave c of the CW
-// owning the columns [c * NJ * 256, (c + 1) * NJ * 256); the 8 / CW teams take neighbouring row groups.  Rows come through LDS by direct
-// loads, each wave its own columns (1 KB of consecutive memory an instruction) into 16 KB of its own, so no wave waits for another's: the
-// group that a wave has read into registers makes room at once for the one 16 KB later.  A wave's slices of the slots' vectors and
+// One pass over the matrix for the slots.  The eight waves of a workgroup share a group of RB rows, wave c owning the columns
+// [c * NJ * 256, (c + 1) * NJ * 256).  Rows come through LDS by direct loads, each wave its own columns (1 KB of consecutive memory an
+// instruction) into 16 KB of its own, so no wave waits for another's: the group that a wave has read into registers makes room at once for the
+// one 16 KB later.  A wave's slices of the slots' vectors and
 // accumulators are registers.  Per group: partial dot products of RB rows x slots -> LDS -> one barrier -> every wave finishes all
 // coefficients itself (sigmoid only where a slot is in a gradient phase) and updates its columns.  Columns at or past d are loaded from a
 // clamped address and meet x = 0; their accumulators are never used.  An idle slot rides along with a zero vector and zero coefficients.
@@ -171,12 +172,8 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
 // updates; a grid of ten C at that size (280 rounds): 27.3 -> 23.9 ms, one card in turn.
 // This form, products on the vector units, is the one of d > 4096, where two slots' vectors and accumulators are all that fits (8000 x 8192:
 // 68.1 -> 59.8 us a pass; 8000 x 5120: 40.1 -> 37.9).
-constexpr int pass_rows(int nj) { return nj > 2 ? 2 : 4; }          // rows per group: at most 32 registers a buffer
+constexpr int PASS_ROWS_MFMA = 4, PASS_ROWS_VALU = 2;                // rows of a group: a matrix block; at most 32 registers a buffer
 
-// immediate of s_waitcnt vmcnt(n) with the other counters left alone (vmcnt sits in bits 3:0 and 15:14)
-constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ unsigned lds_addr(const void* p) { return (unsigned)(unsigned long long)(const __attribute__((address_space(3))) void*)p; }
 
 // N pieces of 16 bytes a lane, STEP bytes apart in LDS, waited for in the same block.  As ordinary reads they would wait for every direct
@@ -216,15 +213,14 @@ template <int STEP, int N> __device__ __forceinline__ void lds_get(double (&v)[N
                      : "v"(at), "n"(STEP), "n"(2 * STEP), "n"(3 * STEP), "n"(4 * STEP), "n"(5 * STEP), "n"(6 * STEP), "n"(7 * STEP) : "memory");
 }
 
-template <int NJ, int A, int CW>
+template <int NJ, int A>
 __global__ __launch_bounds__(PASS_WAVES * 64) void lr_pass_kernel(TrainArgs a) {
-    constexpr int RB = pass_rows(NJ), TEAMS = PASS_WAVES / CW, Q = RB * A;
+    constexpr int RB = PASS_ROWS_VALU, CW = PASS_WAVES, Q = RB * A;
     constexpr int PIECES = RB * NJ, DEPTH = 16 / PIECES; // 1 KB pieces of a row group; groups that a wave's 16 KB of LDS hold
     __shared__ f32x4 ring[PASS_WAVES][DEPTH][PIECES][64];
-    __shared__ double part[2][TEAMS][CW][Q];
+    __shared__ double part[2][CW][Q];
     static_assert(DEPTH % 2 == 0, "the slots of `part` take turns");
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int team = w / CW, cw = w % CW;
 
     int ph[A];
     bool any = false;
@@ -239,7 +235,7 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void lr_pass_kernel(TrainArgs a) {
 
     int off[NJ];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) off[j] = min((cw * NJ + j) * 256 + lane * 4, a.d - 4);
+    for (int j = 0; j < NJ; ++j) off[j] = min((w * NJ + j) * 256 + lane * 4, a.d - 4);
     // the wave's slices of the vectors, all asked for at once (an idle slot's memory is there, too)
     double2 x2[NJ][A][2];
 #pragma unroll
@@ -269,9 +265,6 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void lr_pass_kernel(TrainArgs a) {
     int alo[DEPTH], ahi[DEPTH];
     auto load = [&](int u, long long grp) {
         const long long g = grp < ngroups ? grp : ngroups - 1;   // groups past the end re-read the last (not used)
-        const long long il = g * RB + rb_l < a.n ? g * RB + rb_l : a.n - 1;
-        alo[u] = aux_at[il << wide];
-        ahi[u] = aux_at[(il << wide) + wide];
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
             const long long i = g * RB + rb;
@@ -281,22 +274,25 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void lr_pass_kernel(TrainArgs a) {
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(row + off[j]),
                                                  (__attribute__((address_space(3))) void*)&ring[w][u][rb * NJ + j][0], 16, 0, 0);
         }
-        asm volatile("" ::: "memory");                   // (the waits count a group's requests: they stay in front of the next group's)
+        const long long il = g * RB + rb_l < a.n ? g * RB + rb_l : a.n - 1;
+        alo[u] = aux_at[il << wide];
+        ahi[u] = aux_at[(il << wide) + wide];
     };
-    // group numbers of this team: blockIdx.x * TEAMS + team, + gridDim.x * TEAMS, ...; the number of turns is the workgroup's
-    // (barriers inside): a team past the last group works on rows that do not count.  A slot of `part` is written again two
-    // turns later, after a barrier every wave passes only once all its reads of the earlier turn are done.
-    const long long G = (long long)gridDim.x * TEAMS;
-    const long long g0 = (long long)blockIdx.x * TEAMS;
+    // group numbers: blockIdx.x, + gridDim.x, ...  A slot of `part` is written again two turns later, after a barrier every wave passes only
+    // once all its reads of the earlier turn are done.
+    const long long G = gridDim.x, g0 = blockIdx.x;
 #pragma unroll
-    for (int u = 0; u < DEPTH; ++u) load(u, g0 + team + u * G);
+    for (int u = 0; u < DEPTH; ++u) {
+        load(u, g0 + u * G);
+        asm volatile("" ::: "memory");                   // (the waits count a group's requests: they stay in front of the next group's)
+    }
     double x[NJ][4][A], acc[NJ][4][A];
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int s = 0; s < A; ++s) {
             asm volatile("" : "+v"(x2[j][s][0].x), "+v"(x2[j][s][0].y), "+v"(x2[j][s][1].x), "+v"(x2[j][s][1].y));   // (a load that only a branch uses would wait there)
-            const bool in = ph[s] != PH_IDLE && (cw * NJ + j) * 256 + lane * 4 < a.d;
+            const bool in = ph[s] != PH_IDLE && (w * NJ + j) * 256 + lane * 4 < a.d;
             x[j][0][s] = in ? x2[j][s][0].x : 0.0;
             x[j][1][s] = in ? x2[j][s][0].y : 0.0;
             x[j][2][s] = in ? x2[j][s][1].x : 0.0;
@@ -324,8 +320,8 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void lr_pass_kernel(TrainArgs a) {
                     for (int s = 0; s < A; ++s) dot[rb * A + s] += hd * x[j][k][s];
                 }
         const double dq = wave_sums<Q>(dot, lane);
-        const unsigned pt = lds_addr(&part[u & 1][team][0][ql]);
-        if (lane % (64 / Q) == 0) lds_put(pt + cw * (Q * 8), dq);
+        const unsigned pt = lds_addr(&part[u & 1][0][ql]);
+        if (lane % (64 / Q) == 0) lds_put(pt + w * (Q * 8), dq);
         lds_barrier();
         const long long i = grp * RB + rb_l;
         double zs[CW];
@@ -341,7 +337,7 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void lr_pass_kernel(TrainArgs a) {
                 const double aux = lo;
                 const double sg = 1.0 / (1.0 + exp(-z));
                 c = sg - aux;
-                if (cw == 0) {
+                if (w == 0) {
                     const double m = aux > 0.5 ? -z : z; // -t z
                     loss += fmax(m, 0.0) + log1p(exp(-fabs(m)));
                     if (lane % (64 / Q) == 0) Dl[i] = sg * (1.0 - sg);
@@ -366,19 +362,19 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void lr_pass_kernel(TrainArgs a) {
     for (long long grp = g0; grp < ngroups; grp += DEPTH * G)
 #pragma unroll
         for (int u = 0; u < DEPTH; ++u)
-            if (grp + u * G < ngroups) process(u, grp + team + u * G);   // uniform for the workgroup
+            if (grp + u * G < ngroups) process(u, grp + u * G);   // uniform for the workgroup
 
-    double* out = a.partial + ((long long)blockIdx.x * TEAMS + team) * A * (a.d + 2);
+    double* out = a.partial + (long long)blockIdx.x * A * (a.d + 2);
 #pragma unroll
     for (int s = 0; s < A; ++s)
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-            const int e = (cw * NJ + j) * 256 + lane * 4;
+            const int e = (w * NJ + j) * 256 + lane * 4;
 #pragma unroll
             for (int k = 0; k < 4; ++k)
                 if (e + k < a.d) out[(long long)s * (a.d + 2) + e + k] = acc[j][k][s];
         }
-    if (cw == 0) {                                       // sums over the rows of a group, in row order
+    if (w == 0) {                                       // sums over the rows of a group, in row order
         double sb = 0.0, sls = 0.0;
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
@@ -392,7 +388,8 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void lr_pass_kernel(TrainArgs a) {
     }
 }
 
-// The same pass with the products on the matrix cores, up to d = 4096.  On the vector units a turn of four rows x four slots is 650 instructions
+// The same pass with the products on the matrix cores, up to d = 4096: CW waves share a group of rows, wave c of them with NJ 256-column pieces, and
+// the 8 / CW teams take neighbouring groups.  On the vector units a turn of four rows x four slots is 650 instructions
 // a wave: 16 dot products to be summed over the lanes, 32 read-lanes of coefficients.  Here it is 200: four rows x four slots are one 4x4x4 block
 // (four blocks an instruction, 256 multiply-adds in 8 ns a SIMD where 64 of the vector units' take 2.7), a dot product is one register pair a lane
 //   dot:     D[row][slot] += A[row][column] B[column][slot]     (h, x)
@@ -404,7 +401,7 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void lr_pass_kernel(TrainArgs a) {
 // update's operand, m * 64 + 4 * (lane / 16 + 4 (lane / 4 % 4)) + k for the accumulators.
 template <int NJ, int CW>
 __global__ __launch_bounds__(PASS_WAVES * 64) void lr_pass_mfma_kernel(TrainArgs a) {
-    constexpr int RB = 4, A = 4, TEAMS = PASS_WAVES / CW, NM = NJ * 4;
+    constexpr int RB = PASS_ROWS_MFMA, A = 4, TEAMS = PASS_WAVES / CW, NM = NJ * 4;
     constexpr int DEPTH = 4 / NJ, ROW = NJ * 1024 + 64, GROUP = RB * ROW;    // groups in LDS; bytes of a row's slice, of a group's
     __shared__ __align__(16) unsigned char ring[PASS_WAVES * DEPTH * GROUP];
     __shared__ double part[2][TEAMS][CW][RB * A];
@@ -445,9 +442,6 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void lr_pass_mfma_kernel(TrainArgs
     unsigned char* mine = ring + w * DEPTH * GROUP;
     auto load = [&](int u, long long grp) {
         const long long g = grp < ngroups ? grp : ngroups - 1;   // groups past the end re-read the last (not used)
-        const long long il = g * RB + rb_l < a.n ? g * RB + rb_l : a.n - 1;
-        alo[u] = aux_at[il << wide];
-        ahi[u] = aux_at[(il << wide) + wide];
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
             const long long i = g * RB + rb;
@@ -457,7 +451,9 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void lr_pass_mfma_kernel(TrainArgs
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(row + off[j]),
                                                  (__attribute__((address_space(3))) void*)(mine + u * GROUP + rb * ROW + j * 1024), 16, 0, 0);
         }
-        asm volatile("" ::: "memory");                   // (the waits count a group's requests: they stay in front of the next group's)
+        const long long il = g * RB + rb_l < a.n ? g * RB + rb_l : a.n - 1;
+        alo[u] = aux_at[il << wide];
+        ahi[u] = aux_at[(il << wide) + wide];
     };
     // group numbers of this team: blockIdx.x * TEAMS + team, + gridDim.x * TEAMS, ...; the number of turns is the workgroup's
     // (barriers inside): a team past the last group works on rows that do not count.  A slot of `part` is written again two
@@ -465,7 +461,10 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void lr_pass_mfma_kernel(TrainArgs
     const long long G = (long long)gridDim.x * TEAMS;
     const long long g0 = (long long)blockIdx.x * TEAMS;
 #pragma unroll
-    for (int u = 0; u < DEPTH; ++u) load(u, g0 + team + u * G);
+    for (int u = 0; u < DEPTH; ++u) {
+        load(u, g0 + team + u * G);
+        asm volatile("" ::: "memory");                   // (the waits count a group's requests: they stay in front of the next group's)
+    }
     double x[NM][4], acc[NM][4];
 #pragma unroll
     for (int m = 0; m < NM; ++m) {
@@ -523,7 +522,10 @@ __global__ __launch_bounds__(PASS_WAVES * 64) void lr_pass_mfma_kernel(TrainArgs
             }
         }
         accb += c;
-        if constexpr (decltype(grad)::value) free_place();   // (held since before exp and log1p, the 32 registers would have others spilled)
+        if constexpr (decltype(grad)::value) {
+            free_place();                                // (held since before exp and log1p, the 32 registers would have others spilled)
+            asm volatile("" ::: "memory");               // (as above; in the other order the exchange is between this group's requests and the next wait)
+        }
 #pragma unroll
         for (int m = 0; m < NM; ++m)
 #pragma unroll
@@ -969,13 +971,13 @@ int launch_pass(const TrainArgs& a, int A, int grid, hipStream_t st) {
     }
     SJ_PASS_MFMA(1, 1) SJ_PASS_MFMA(1, 2) SJ_PASS_MFMA(1, 4) SJ_PASS_MFMA(1, 8) SJ_PASS_MFMA(2, 8)
 #undef SJ_PASS_MFMA
-#define SJ_PASS(NJ, CW, AA)                                                                           \
-    if (p.nj == NJ && p.cw == CW && A == AA) {                                                        \
-        lr_pass_kernel<NJ, AA, CW><<<grid, PASS_WAVES * 64, 0, st>>>(a);                              \
+#define SJ_PASS(NJ, AA)                                                                               \
+    if (p.nj == NJ && A == AA) {                                                                      \
+        lr_pass_kernel<NJ, AA><<<grid, PASS_WAVES * 64, 0, st>>>(a);                                  \
         LAUNCHCHK("lr_pass");                                                                         \
         return SJ_OK;                                                                                 \
     }
-    SJ_PASS(3, 8, 1) SJ_PASS(3, 8, 2) SJ_PASS(4, 8, 1) SJ_PASS(4, 8, 2)
+    SJ_PASS(3, 1) SJ_PASS(3, 2) SJ_PASS(4, 1) SJ_PASS(4, 2)
 #undef SJ_PASS
     return fail(SJ_EINVAL, "d = %d above 8192 is not supported", a.d);
 }
@@ -1034,7 +1036,7 @@ extern "C" int sj_judge_train(const float* H_train, const int32_t* y_train, int6
     std::stable_sort(order.begin(), order.end(), [&](int32_t p, int32_t q) { return C_grid[p] > C_grid[q]; });
 
     const int A = pass_slots(d, n_C);
-    const int teams = PASS_WAVES / pass_shape(d).cw, rb = pass_rows(pass_shape(d).nj);
+    const int teams = PASS_WAVES / pass_shape(d).cw, rb = pass_mfma(d) ? PASS_ROWS_MFMA : PASS_ROWS_VALU;
     const int64_t turns = (n_train + (int64_t)rb * teams - 1) / ((int64_t)rb * teams);
     const int grid = (int)std::min<int64_t>(PASS_WG, turns);
     // validation runs over as many models at a time as 64 MB of scores and counts allow
