@@ -1226,8 +1226,12 @@ static int gemm_tile(hipStream_t st, const void* Wt, const void* X, size_t xplan
     if constexpr (EPI == EPI_LOGITS) {                 // tile_rows has no group below ten row tiles
         launch(std::integral_constant<int, 6>{});
         launch(std::integral_constant<int, 8>{});
-        if constexpr (SPL == 2) launch(std::integral_constant<int, 9>{});
-        else launch(std::integral_constant<int, 18>{});
+        if constexpr (SPL == 2) {
+            launch(std::integral_constant<int, 9>{});
+            launch(std::integral_constant<int, 11>{});
+            launch(std::integral_constant<int, 13>{});
+            launch(std::integral_constant<int, 15>{});
+        } else launch(std::integral_constant<int, 18>{});
     }
     launch(std::integral_constant<int, 10>{});
     launch(std::integral_constant<int, 12>{});

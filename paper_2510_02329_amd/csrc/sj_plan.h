@@ -400,12 +400,16 @@ inline int tile_rows(int rows, int ntiles) {
 //   head alone, rows 64 / 80 / 128 / 192 / 288 / 360 / 576: 262 / 281, 292 / 286, 326 / 302, 360 / 317, 425 / 394, 605 / 555, 708 / 638;
 //   1B, rows 64 / 96 / 192 / 320: 284 / 280, 328 / 308, 512 / 415, 721 / 615; 70B, rows 64 / 96 / 144 / 192: 903 / 889, 1096 / 1039, 1315 / 1236, 1861 / 1524;
 //   48 rows: 432 / 442 (8B), 261 / 278 (head alone).
+// Row groups of an odd number of tiles leave one half of the waves a tile less.  From nine tiles of two planes on, where the products bound a
+// k-step, that beats a padded even group; padded / odd, 8B and 1B shapes, one layer and the head: 5 tiles 488 / 491, 294 / 299, 7 tiles 541 / 541,
+// 324 / 327, 9 tiles 602 / 593, 363 / 362, 11 tiles 709 / 690, 391 / 381, 13 tiles 770 / 757, 427 / 422, 15 tiles 833 / 817, 462 / 454.  On one plane
+// it makes no difference: 5 to 15 tiles 286 / 285, 293 / 293, 297 / 299, 300 / 302, 318 / 319, 335 / 335.
 // Gate / up of the 70B shape on these small row groups: 96 and 144 rows 0 %, 99 rows 2 % of a layer and head: not taken.
 constexpr int TILE_STAT = 4;                   // n-tiles of a wave, and of a softmax statistic
 inline int tile_logits(int rows, int ntiles, int planes) {
     if (rows <= 64 || planes < 1 || planes > 2) return 0;
     const int tiles = (rows + 15) / 16, most = planes == 2 ? 16 : 18, groups = (tiles + most - 1) / most, per = (tiles + groups - 1) / groups;
-    const int rt = planes == 2 && per == 9 ? 9 : (per + 1) / 2 * 2;                // the sizes gemm_tile launches: even ones, and 9 on two planes
+    const int rt = planes == 2 && per >= 9 ? per : (per + 1) / 2 * 2;              // the sizes gemm_tile launches
     const int wgs = (ntiles + TILE_NT - 1) / TILE_NT * groups, rounds = (wgs + TILE_WGS - 1) / TILE_WGS;
     return wgs * 100 >= rounds * TILE_WGS * (rounds > 1 ? 65 : 80) ? rt : 0;
 }

@@ -47,6 +47,10 @@ def test_step_on_large_tiles(batch, gamma, d, ffn, planes):
                                                                (16, 7, 52480, 192, 2, "groups of 128"), (43, 2, 52480, 128, 2, "groups of 144"),
                                                                (16, 8, 52608, 256, 2, "groups of 144"), (29, 4, 52480, 64, 2, "groups of 160"),
                                                                (28, 7, 52480, 128, 2, "groups of 224"), (32, 7, 52480, 64, 2, "groups of 256"),
+                                                               (23, 6, 52480, 64, 2, "groups of 176"), (22, 7, 52608, 192, 2, "groups of 176"),
+                                                               (28, 6, 52480, 128, 2, "groups of 208"), (26, 7, 52480, 64, 2, "groups of 208"),
+                                                               (25, 8, 52480, 64, 2, "groups of 240"), (30, 7, 52608, 128, 2, "groups of 240"),
+                                                               (42, 7, 26240, 64, 2, "groups of 176"),
                                                                (37, 6, 26240, 64, 2, "groups of 144"), (64, 4, 42752, 128, 2, "groups of 160"),
                                                                (8, 7, 52480, 64, 1, "gemm_rows8"), (13, 4, 52480, 64, 1, "groups of 96"),
                                                                (43, 2, 52480, 64, 1, "groups of 160"), (28, 7, 52480, 64, 1, "groups of 224"),

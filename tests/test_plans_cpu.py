@@ -215,7 +215,7 @@ int main() {
                 ++taken;
                 // an instantiated size whose groups hold all rows, none of them empty, and whole statistics of a row
                 const int groups = (rows + rt * 16 - 1) / (rt * 16);
-                const bool known = (rt % 2 == 0 && rt >= 6 && rt <= 16) || (planes == 2 && rt == 9) || (planes == 1 && rt == 18);
+                const bool known = (rt % 2 == 0 && rt >= 6 && rt <= 16) || (planes == 2 && rt % 2 && rt >= 9 && rt <= 15) || (planes == 1 && rt == 18);
                 if ((!known || rows <= 64 || planes < 1 || planes > 2 || groups * rt * 16 < rows || (groups - 1) * rt * 16 >= rows || ntiles % TILE_STAT) && bad++ < 10)
                     printf("%d rows, %d tiles, %d planes: %d\n", rows, ntiles, planes, rt);
             }
