@@ -21,7 +21,7 @@
 // Closing a sub-layer from 9 rows on (`tickets`): O and down need K-slices there (one n-tile a workgroup, all of K: down of the 1B shape at 12 rows
 // 15.7 us against 8.6), so the slices of a group of n-tiles draw tickets and the last to finish adds them, in slice order, to the residual
 // stream and leaves what EPI_RESID leaves, 1/rms to be applied by the consumer.  The norm launch it replaces takes 4.6 - 6.7 us, store, ticket and
-// reading back 2 - 3.
+// reading back 2 - 3: 1B, 12 rows, in the order of a draft block, O 7.1 and down 11.4 (QKV, which has no tickets, 6.1).
 //
 // PACK (two operand planes, at most 8 rows): MFMA row r < 8 of the B operand carries plane 0 of row r, row r + 8 plane 1 of the same row, so ONE
 // product per weight fragment yields both planes' contributions in output columns r and r + 8, which the reduction adds (hi first).
@@ -88,7 +88,7 @@ __global__ __launch_bounds__(RING_CW * 64, ring_lds(DEPTH, NT, MT, ring_operand(
     const int nkb = KS / RING_CW / (int)gridDim.y, ks0 = blockIdx.y * nkb * RING_CW;     // whole k-blocks, at least TAIL (ring_fits)
 
     // what the end needs from memory, in front of the stream (loads are counted in order): the residual stream and gain of the tiles that this
-    // wave finishes, and the shares of the rows' sums of squares (at most 8 rows)
+    // wave finishes, and the shares of the rows' sums of squares (packed: at most 8 rows, else MT x 16)
     constexpr int FIN = (NT * MT + RING_CW - 1) / RING_CW;        // (tile, row tile) pairs a wave finishes: w, w + 8, ..
     f32x4 res_x[FIN];
     float res_g[FIN][4];

@@ -229,7 +229,7 @@ __global__ __launch_bounds__(1024) void add_rmsnorm_kernel(int R, int d, float e
 // slice again and are summed through LDS in wave order (deterministic).
 // EPI_RESID closes a sub-layer without a norm launch: the workgroup holds finished output columns (no K-slices), adds them to
 // the fp32 residual stream, writes the next product's operand planes WITHOUT the 1/rms factor - (x + y) * gain - and each
-// tile's share of every row's sum of squares.  The consumer (QKV or gate / up: EPI_PARTIAL or EPI_SWIGLU, at most 8 rows, `ss_in` set) sums
+// tile's share of every row's sum of squares.  The consumer (QKV or gate / up: EPI_PARTIAL or EPI_SWIGLU, few rows, `ss_in` set) sums
 // the shares and multiplies its finished sums by 1/rms: a factor of the row commutes with the product.
 enum { EPI_PARTIAL = 0, EPI_SWIGLU = 1, EPI_LOGITS = 2, EPI_RESID = 3 };
 

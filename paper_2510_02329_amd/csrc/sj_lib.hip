@@ -1027,8 +1027,8 @@ static int pick_plan(GemmPlan& plan, const std::vector<GemmPlan>& candidates, Ti
     return SJ_OK;
 }
 
-// Launch shapes of the three split-K projections for few rows, chosen by measurement when the cache object is created: which of (n-tiles, waves, K-slices, ring depth) streams a given weight matrix fastest depends on its
-// shape and on the number of row tiles in ways the workgroup-count rule of plan_partial does not capture (70B-shaped
+// Launch shapes of the three split-K projections for few rows, chosen by measurement when the cache object is created: which of
+// (n-tiles, waves, K-slices, ring depth) streams a given weight matrix fastest depends on its shape and on the number of row tiles in ways the workgroup-count rule of plan_partial does not capture (70B-shaped
 // QKV with two row tiles: 50 us with the rule's shape, 35 us with the best one).  Every candidate runs over up to 16
 // layers' weights back to back (distinct layers, so nothing is served from cache); the rule's plan stays unless a
 // candidate is at least 5 % faster (pick_plan).  `closes` (tune_plans): O and down are timed as they run, with the tickets of their K-slices and

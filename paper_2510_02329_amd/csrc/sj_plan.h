@@ -94,8 +94,8 @@ inline bool logits_fits(const GemmPlan& p, int ntiles, int ksteps, int rows, int
 #undef SJ_IS_RING
 #undef SJ_IS_FEW
 
-// Rule shape of a split-K projection on the LDS-ring kernel (rows <= 8, two planes: the measured case), or waves = 0
-// when no shape fits.  Fewest idle workgroup slots first (256 CUs, one round); among those at least two n-tiles per
+// Rule shape of a split-K projection of up to 8 rows on the LDS-ring kernel (two planes: the measured case), or waves = 0
+// when no shape fits; from 9 rows on: ring_rule_partial_rows.  Fewest idle workgroup slots first (256 CUs, one round); among those at least two n-tiles per
 // workgroup (with one, the operand is as much traffic as the weights) and two K-slices, else four, else one, else
 // eight (measured on 4096 x 4096, 4096 x 14336 and 6144 x 4096: the middle of the range wins, and fewer slices are
 // less work for the kernel that adds them).
@@ -127,14 +127,17 @@ inline int partial_chain(const GemmPlan& p, int ksteps) {
 inline GemmPlan plan_partial(int ntiles, int ksteps, bool one_row_tile);
 
 // The same from 9 rows on, where a k-step has one operand fragment per plane and row tile: whole rounds of 256 workgroups, and few fragments for a
-// wave to read (an operand fragment counted twice: it comes from the L2 each time), tiles left to the reduction and K-slices (their sums
-// are written and read).  QKV_SLICES: slices of QKV, which attention adds (1B, 12 rows: 12.7 us with two, 13.8 with four).  us of the shapes that
+// wave to read (with one row tile an operand fragment counts twice: it comes from the L2 each time), tiles left to the reduction and K-slices (their
+// sums are written and read).  QKV_SLICES: slices of QKV, which attention adds (1B, 12 rows: 12.7 us with two, 13.8 with four).  us of the shapes that
 // fill the chip, n-tiles x slices:
 //   8B, 20 rows: down 4 x 4 21.6, 8 x 8 22.1; QKV 3 x 2 11.4, 3 x 4 12.6;   70B, 24 rows: O 4 x 2 24.8, 8 x 4 28.6; down 8 x 4 72.3, 4 x 2 75.5;
 //   1B, 12 rows: O 1 x 2 4.4; down 2 x 4 8.6, 4 x 8 9.1; QKV (192 workgroups) 2 x 2 5.2, 1 x 1 6.1.
-// Fewer slices are longer chains, and a sum's rounding error grows with its chain, so a launch has at least the slices that keep a chain no longer
-// than the register-ring kernel's rule has it for this product (8 - 15 k-steps while eight slices allow that).  It is what takes four slices
-// for QKV and O of the 70B shape, where two would do for the stream.
+// (Back to back; in a step these launches take 1 - 3 us more.)  With two row tiles an operand fragment counts once: any weight from 0.4 to 1.3 has the
+// faster of the measured shapes of O and down of 8B and 70B, 2 has O of 70B in 8 x 4.
+// QKV's sums are rounded into the cache: it has at least the slices that keep a chain no longer than the register-ring kernel's rule has it (8 - 15 k-steps
+// while eight slices allow that; four slices for the 70B shape from 9 rows on, where two would do for the stream).  O and down have no such bound, as the
+// rule there never had: their sums stay fp32, and longer chains leave the same error (70B shape, 24 rows, 64 inputs, hidden states against 64 bits: O
+// in two slices 1.010 +- 0.012 of that of the register-ring kernel's eight, in four 1.002 +- 0.017).
 constexpr int QKV_SLICES = 2;
 inline GemmPlan ring_rule_partial_rows(int ntiles, int ksteps, int rows, int planes, Sums sums) {
     GemmPlan best;
@@ -143,7 +146,7 @@ inline GemmPlan ring_rule_partial_rows(int ntiles, int ksteps, int rows, int pla
     const int mt = rows > 16 ? 2 : 1, nb = ring_operand(false, planes, mt), chain = partial_chain(plan_partial(ntiles, ksteps, true), ksteps);
     int most = sums == Sums::attention ? QKV_SLICES : 8;
     for (int split = 1; split <= most; split *= 2) {
-        if (partial_chain(GemmPlan{1, RING_WAVES, split, 0}, ksteps) > chain) {
+        if (sums == Sums::attention && partial_chain(GemmPlan{1, RING_WAVES, split, 0}, ksteps) > chain) {
             most = std::min(8, std::max(most, split * 2));
             continue;
         }
@@ -154,7 +157,7 @@ inline GemmPlan ring_rule_partial_rows(int ntiles, int ksteps, int rows, int pla
             if (!partial_fits(p, ntiles, ksteps, rows, planes, true)) p.depth = RING_TWO;
             if (!partial_fits(p, ntiles, ksteps, rows, planes, true)) p.depth = 4;
             if (!partial_fits(p, ntiles, ksteps, rows, planes, true)) continue;
-            const double cost = 256.0 * to_cu / wgs * (to_cu * ((double)ksteps / RING_CW / split * (nt + 2 * nb) + 4 * nt * mt + 8) + 6 * split);
+            const double cost = 256.0 * to_cu / wgs * (to_cu * ((double)ksteps / RING_CW / split * (nt + (mt == 2 ? 1 : 2) * nb) + 4 * nt * mt + 8) + 6 * split);
             if (cost < best_cost - 1e-9) { best = p; best_cost = cost; }
         }
     }
@@ -318,13 +321,13 @@ inline std::vector<GemmPlan> partial_candidates(int ntiles, int ksteps, int rows
 }
 
 // Those of them that may take the place of `rule`, the rule's shape.  QKV: of no more K-slices, since the measurement does not see the attention
-// launches that add them (1B, 1 row, a draft block: 8 slices 4642 us, 4 slices 4529 - 4580).  From 9 rows on: of no longer chains than the
-// rule's bound; `closes`: on the LDS-ring kernel.
+// launches that add them (1B, 1 row, a draft block: 8 slices 4642 us, 4 slices 4529 - 4580), and from 9 rows on of no longer chains than the rule's
+// bound.  `closes`: on the LDS-ring kernel.
 inline std::vector<GemmPlan> measured_partials(const GemmPlan& rule, int ntiles, int ksteps, int rows, int planes, bool bf16, Sums sums, bool closes) {
     std::vector<GemmPlan> cands = partial_candidates(ntiles, ksteps, rows, planes, bf16);
     const int chain = std::max(partial_chain(rule, ksteps), partial_chain(plan_partial(ntiles, ksteps, true), ksteps));
     auto out = [&](const GemmPlan& p) {
-        return (sums == Sums::attention && p.split > rule.split) || (rows > RING_PACK_ROWS && partial_chain(p, ksteps) > chain) || (closes && p.waves != RING_WAVES);
+        return (sums == Sums::attention && (p.split > rule.split || (rows > RING_PACK_ROWS && partial_chain(p, ksteps) > chain))) || (closes && p.waves != RING_WAVES);
     };
     cands.erase(std::remove_if(cands.begin(), cands.end(), out), cands.end());
     return cands;

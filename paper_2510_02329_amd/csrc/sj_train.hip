@@ -168,8 +168,9 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
 // Bound: reads of the matrix (284 MB of 17358 x 4096: 41 us at 6.9 TB/s), the partial sums (34 MB written, 10 us), and 9 us of launch, first loads
 // and end.  Launched back to back at that size, four slots, Hessian products: 84.5 us with the vectors in LDS, read there for every row, rows in two
 // sets of registers, and the prologue's 32 loads each waited for in a branch of its own; 81.6 with rows through LDS and the prologue's loads
-// together; 66 with the products on the matrix cores (below).  A round is this pass, 5 us for the sum of the partials and 8 us for the slots'
-// updates; a grid of ten C at that size (280 rounds): 27.3 -> 23.9 ms, one card in turn.
+// together; 66 with the products on the matrix cores (below).  A grid of ten C at that size is 280 rounds of, in its trace, 59 us on average for this
+// pass (the last rounds have idle slots), 8.6 for the sum of the partials and 7.8 for the slots' updates; vector units / matrix cores: 25.1 / 22.1 ms, one card
+// in turn.
 // This form, products on the vector units, is the one of d > 4096, where two slots' vectors and accumulators are all that fits (8000 x 8192:
 // 68.1 -> 59.8 us a pass; 8000 x 5120: 40.1 -> 37.9).
 constexpr int PASS_ROWS_MFMA = 4, PASS_ROWS_VALU = 2;                // rows of a group: a matrix block; at most 32 registers a buffer

@@ -120,15 +120,28 @@ def _llama70b(force_rounding, scale):
         sj.sj_set_operand_planes(gpu.kv, 3)
         sj.sj_kv_rewind(gpu.kv, lens, synth.make_pending(shape, 0), torch.cuda.current_stream())
         exact = gpu.step(draft, 0.5, shape.gamma)
-        # and in the launch shapes that the start-up measurement picks
-        os.environ.pop("SJ_TUNE", None)
+        if not force_rounding:
+            _measured_shapes(shape, gpu, lens, draft, ref)
+        return stats, out, ref, draft, exact
+    finally:
+        gpu.close()
+
+
+_measured70b = {}
+
+
+def _measured_shapes(shape, gpu, lens, draft, ref):
+    """The same step with two planes in the launch shapes that the start-up measurement picks, kept for the test of them."""
+    tune = os.environ.pop("SJ_TUNE", None)
+    try:
         sj.sj_set_operand_planes(gpu.kv, 2)
         sj.sj_set_temperature(gpu.model, shape.temperature)              # (a new launch graph: the one of the rule's shapes would be replayed)
         sj.sj_kv_rewind(gpu.kv, lens, synth.make_pending(shape, 0), torch.cuda.current_stream())
         say("70B measured shapes: " + ", ".join(sj.sj_kernel_class_shape(gpu.kv, c, shape.batch * (shape.gamma + 1)) for c in (1, 2, 4)))
-        return stats, out, ref, draft, exact, gpu.step(draft, 0.5, shape.gamma)
+        _measured70b.update(out=gpu.step(draft, 0.5, shape.gamma), ref=ref, draft=draft)
     finally:
-        gpu.close()
+        if tune is not None:
+            os.environ["SJ_TUNE"] = tune
 
 
 def test_llama70b_batch4(monkeypatch):
@@ -141,33 +154,38 @@ def test_llama70b_batch4(monkeypatch):
     store the same rows.
 
     Emitted tokens must match, too, wherever the oracle's own draw decides them.  The first sequence's uniform lies
-    3.5e-7 above the lower edge of its token's cell, which is 6.5e-7 wide with hardly any mass in the five cells behind it, and the device's
-    CDF is off by 2e-8 .. 8e-7 there: the token before with some K-slices of the products, the oracle's with others, the one five
-    tokens on with those of the rule.  So the shapes are fixed here, and a token may be another one where the CDF had to be
-    off by less than 2e-6 for it: three times that error.  With three operand planes all four tokens are the oracle's.
-
-    The step runs once more in the shapes that the start-up measurement picks: bits, lengths and the logits' bound hold there, too.  How far
-    the logits are off is a matter of which stored elements round the other way: over six drafts the worst element of a sequence is 0.2 to
-    4.8 bars from that of exact operands, for a draft the same to 0.1 with 1, 2, 4 or 8 K-slices of any product - but for this
-    draft's fourth sequence, 3.2 with one or two slices of QKV and 1.4 with four or eight, the number that both the rule and the
-    measurement have."""
+    3.5e-7 above the lower edge of its token's cell, which is 6.5e-7 wide, and the device's CDF is off by 2e-8 .. 7e-7
+    there: 6.6e-7 with the shapes of the rule (the draw gives the token before), 2e-8 and 2.6e-7 with two choices of
+    the start-up measurement (the oracle's token).  So the shapes are fixed here, and a token may be the
+    oracle's neighbour where the uniform is closer to the edge between the two than 2e-6: three times that error.
+    With three operand planes all four tokens are the oracle's."""
     monkeypatch.setenv("SJ_TUNE", "0")
-    stats, out, ref, draft, exact, measured = _llama70b(force_rounding=False, scale=2.0)
+    stats, out, ref, draft, exact = _llama70b(force_rounding=False, scale=2.0)
     d = stats["decisions"]
     assert d["unexcused"] == 0 and d["bit_excused"] == 0 and d["len_excused"] == 0 and d["token_excused"] <= 1
     for b, r in enumerate(ref):
         n, k_dev, k_ref = int(out["accepted_len"][b]), int(out["next_token"][b]), int(r["next_token"])
         w = r["p"][n] if n == draft["tokens"].shape[1] else np.maximum(0.0, r["p"][n] - np.asarray(draft["probs"][b, n], np.float64))
-        F = np.cumsum(w) / w.sum()
-        u = float(draft["uniforms"][b, -1])
-        edge = k_dev - 1 if k_dev > k_ref else k_dev                     # the last token that the device's CDF had on the other side of the uniform
-        gap = 0.0 if k_dev == k_ref else abs(u - F[edge])
-        say(f"70B token {b}: {k_dev}, oracle {k_ref}, CDF off by {gap:.2e}, uniform {u - (F[k_ref - 1] if k_ref else 0.0):.2e} above the lower edge")
-        assert k_dev == k_ref or gap < 2e-6, (b, k_dev, k_ref, gap)
+        edge = w[:max(k_dev, k_ref)].sum() / w.sum()                 # between the two, if they are neighbours
+        gap = abs(float(draft["uniforms"][b, -1]) - edge)
+        say(f"70B token {b}: {k_dev}, oracle {k_ref}, uniform {gap:.2e} from the lower edge")
+        assert k_dev == k_ref or (abs(k_dev - k_ref) == 1 and gap < 2e-6), (b, k_dev, k_ref, gap)
         assert int(exact["accepted_len"][b]) == r["accepted_len"] and int(exact["next_token"][b]) == k_ref, (b, exact["next_token"][b], k_ref)
-        err, worst = G.close_enough(measured["logits"][b], r["logits"], "bf16", f"70B measured shapes, logits seq {b}", scale=2.0)
+
+
+def test_llama70b_batch4_in_measured_shapes(monkeypatch):
+    """The step of the test above in the shapes that the start-up measurement picks: the same bound on the logits (twice the bar), bits and lengths.
+    How far the logits are off is a matter of which stored elements round the other way: over six drafts the worst element of a sequence is 0.2 to
+    4.8 bars from that of exact operands, for a draft the same to 0.1 with 1, 2, 4 or 8 K-slices of any product - but for this draft's fourth
+    sequence, 3.2 with one or two slices of QKV and 1.4 with four or eight, the number that both the rule and the measurement have."""
+    if not _measured70b:
+        monkeypatch.setenv("SJ_TUNE", "0")
+        _llama70b(force_rounding=False, scale=2.0)
+    out, ref, draft = (_measured70b[k] for k in ("out", "ref", "draft"))
+    for b, r in enumerate(ref):
+        err, worst = G.close_enough(out["logits"][b], r["logits"], "bf16", f"70B measured shapes, logits seq {b}", scale=2.0)
         say(f"70B measured shapes, sequence {b}: logits max err {err:.3e} worst err/bound {worst:.3f}")
-    d = G.decisions_vs_oracle(synth.CONFIGS[4], measured, ref, draft, 0.5)
+    d = G.decisions_vs_oracle(synth.CONFIGS[4], out, ref, draft, 0.5)
     assert d["unexcused"] == 0 and d["bit_excused"] == 0 and d["len_excused"] == 0, d
 
 
