@@ -218,6 +218,7 @@ def bench_head(args, torch, sj, synth) -> dict:
     # dominant kernel: the LM-head product (+ per-tile softmax partials), back to back between two HIP events
     k_launches = min(args.steps, 50)
     k_ms = sj.sj_time_kernel_class(model, kv, 5, k_launches, stream)
+    lm_shape = sj.sj_kernel_class_shape(kv, 5, R)
     k_s = k_ms / k_launches * 1e-3
     flops = 2.0 * R * V * d                            # one bf16 plane: the hidden states are given in bf16
     w_bytes = V * d * 2
@@ -232,7 +233,7 @@ def bench_head(args, torch, sj, synth) -> dict:
         "mean_tokens_per_seq_step": round(mean_tokens, 3),
         "acceptance_over": f"{len(drafts)} seeded draft batches of {B} sequences",
         "copy_ceiling_gbps": round(ceiling, 1),
-        "roofline": {"kernel": "gemm_rows8 (LM-head product + softmax partials, all 576 rows in one launch)", "bound": "mfma",
+        "roofline": {"kernel": "LM-head product + softmax partials, " + lm_shape, "bound": "mfma",
                      "achieved": round(flops / k_s / 1e12, 1), "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(flops / k_s / 1e12 / MFMA_BF16_PEAK_TFLOPS, 4), "traffic": None,
                      "flops_per_launch": flops, "avg_launch_us": round(k_s * 1e6, 2), "launches_timed": int(k_launches),
