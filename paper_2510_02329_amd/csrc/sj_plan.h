@@ -136,8 +136,8 @@ inline GemmPlan plan_partial(int ntiles, int ksteps, bool one_row_tile);
 // faster of the measured shapes of O and down of 8B and 70B, 2 has O of 70B in 8 x 4.
 // QKV's sums are rounded into the cache: it has at least the slices that keep a chain no longer than the register-ring kernel's rule has it (8 - 15 k-steps
 // while eight slices allow that; four slices for the 70B shape from 9 rows on, where two would do for the stream).  O and down have no such bound, as the
-// rule there never had: their sums stay fp32, and longer chains leave the same error (70B shape, 24 rows, 64 inputs, hidden states against 64 bits: O
-// in two slices 1.010 +- 0.012 of that of the register-ring kernel's eight, in four 1.002 +- 0.017).
+// rule there never had: their sums stay fp32, and longer chains leave the same error (70B shape, 24 rows, 64 inputs, hidden states against 64 bits,
+// relative to the register-ring kernel: O in two slices 1.002 +- 0.017, in four 1.002 +- 0.017).
 constexpr int QKV_SLICES = 2;
 inline GemmPlan ring_rule_partial_rows(int ntiles, int ksteps, int rows, int planes, Sums sums) {
     GemmPlan best;
